@@ -609,7 +609,7 @@ int Block::vit_step(const void* x_in, const int32_t* labels, void* x_out, hipStr
   }
   // ---- every recorded weight-gradient product: one launch, or one by one with split-K for a small set
   // (this launch is the only user of the split-K scratch while it runs: the side stream's launches take none)
-  PPLL_TRY(launch_gemm_group(s, wgrad_jobs.data(), (int)wgrad_jobs.size(), side_busy, true));
+  PPLL_TRY(launch_gemm_group(s, wgrad_jobs.data(), (int)wgrad_jobs.size(), true));
   wgrad_jobs.clear();
   PPLL_TRY(side_wait(s));
   return PPLL_OK;
@@ -938,7 +938,7 @@ int Block::side_launch_wgrads(hipStream_t s) {
   if (!side_join) PPLL_HIP(hipEventCreateWithFlags(&side_join, hipEventDisableTiming));
   PPLL_HIP(hipEventRecord(side_fork, s));
   PPLL_HIP(hipStreamWaitEvent(side, side_fork, 0));
-  PPLL_TRY(launch_gemm_group(side, wgrad_jobs.data(), (int)wgrad_jobs.size(), true));
+  PPLL_TRY(launch_gemm_group(side, wgrad_jobs.data(), (int)wgrad_jobs.size()));
   wgrad_jobs.clear();
   side_busy = true;
   return PPLL_OK;

@@ -452,7 +452,7 @@ struct GroupedProblem {
   int lda, ldb, ldc, M, N, K, tiles_m, tiles_n, first_tile;
   uint32_t a_bytes, b_bytes, c_bytes;
 };
-constexpr int GROUP_MAX = 24;
+constexpr int GROUP_MAX = 40;   // seven encoder layers with the patch embedding; the table stays below the 4 KB of a kernel's arguments
 struct GroupedArgs {
   int n, total_tiles, per_xcd;
   GroupedProblem prob[GROUP_MAX];
@@ -598,8 +598,11 @@ long operand_bytes(bool transposed, int rows, int K, long ld) {
 // True when the MFMA kernel can take this product as it stands.
 bool gemm_mfma_supported(const GemmArgs& g) {
   if (g.a_dt != BF16 || g.b_dt != BF16) return false;
-  if (g.M < 1 || g.N < 1 || g.K < 1 || (g.N & 7) || (g.K & 7)) return false;
+  if (g.M < 1 || g.N < 1 || g.K < 1 || (g.N & 7)) return false;
   const bool at = g.a_sm == 1 && g.a_sk != 1, bt = g.b_sn == 1 && g.b_sk != 1;
+  // an operand whose k is contiguous is read 8 k at a time; where both have the other index contiguous (weight gradients,
+  // reduction over batch x tokens rows) every k row is bounds-checked by itself and any K goes
+  if ((g.K & 7) && !(at && bt)) return false;
   if (!at && g.a_sk != 1) return false;
   if (!bt && g.b_sk != 1) return false;
   const long lda = at ? g.a_sk : g.a_sm, ldb = bt ? g.b_sk : g.b_sn;
@@ -662,7 +665,7 @@ static bool lds_opt_in_due(std::atomic<bool> (&done)[64]) {
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return true;
   return !done[dev].exchange(true);
 }
-constexpr int BALANCED_MAX_CUTS = 4;
+constexpr int BALANCED_MAX_CUTS = 8;
 // room for the parts of the divided tiles: at most two per workgroup
 size_t gemm_mfma_balanced_floats() { return (size_t)balanced_workgroups() * 2 * SLOT_FLOATS; }
 
@@ -689,7 +692,7 @@ int launch_gemm_mfma_grouped(hipStream_t s, const GemmArgs* gs, int n, float* ws
   if (ws && wgs >= 8 && n <= GROUP_MAX && ws_floats >= (size_t)wgs * 2 * SLOT_FLOATS) {
     BalancedArgs a{};
     a.n = n; a.ws = ws;
-    constexpr int LONG_NKT = 32;                    // k-steps from which a reduction counts as long
+    constexpr int LONG_NKT = 8;                     // k-steps from which a reduction counts as long enough to cut
     int tiles = 0, min_nkt = 1 << 30, filled = 0;
     double flops = 0.0;
     for (int pass = 0; pass < 2; ++pass) {          // long reductions first, then the short ones
@@ -706,11 +709,11 @@ int launch_gemm_mfma_grouped(hipStream_t s, const GemmArgs* gs, int n, float* ws
     }
     const int rest = a.long_tiles % wgs;
     // parts per left-over tile: 2, more when the left-over tiles are few (measured at 89 left-over tiles on 256 units:
-    // 2 parts 124 + 10 us for the two kernels, 3 parts 123 + 13, 4 parts 121 + 16; undivided 160), each of 8 k-steps or
-    // more, within the workspace
-    int cuts = rest > 0 ? std::max(2, wgs / (2 * rest)) : 1;
+    // 2 parts 124 + 10 us for the two kernels, 3 parts 123 + 13, 4 parts 121 + 16; undivided 160); with no whole tiles
+    // beside them, one part per unit.  Each of 4 k-steps or more, within the workspace
+    int cuts = rest == 0 ? 1 : a.long_tiles < wgs ? std::max(2, wgs / rest) : std::max(2, wgs / (2 * rest));
     cuts = std::min(cuts, BALANCED_MAX_CUTS);
-    while (cuts > 1 && (min_nkt / cuts < 8 || (long)rest * cuts > 2L * wgs)) --cuts;
+    while (cuts > 1 && (min_nkt / cuts < 4 || (long)rest * cuts > 2L * wgs)) --cuts;
     if (rest > 0 && cuts > 1) {
       a.total_tiles = tiles; a.whole_tiles = a.long_tiles - rest; a.cuts = cuts;
       void* prof = nullptr;

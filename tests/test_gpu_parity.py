@@ -321,6 +321,18 @@ def test_vit_bf16_token_counts_at_tile_edges(tokens):
     run_case(wl, steps=1)
 
 
+@pytest.mark.parametrize("batch,tokens,dim,depth", [
+    (3, 5, 64, 1),       # 15 rows: one ragged k-step of the weight gradients, 64-wide LayerNorm
+    (9, 65, 192, 2),     # 585 rows: odd, tiles divided along the rows; 192-wide LayerNorm
+    (13, 145, 128, 1),   # 1885 rows
+    (33, 256, 64, 3),    # 8448 rows: few tiles, many parts
+])
+def test_vit_bf16_row_counts_off_the_tile_edges(batch, tokens, dim, depth):
+    wl = synth.workload("vit_stage_act_bf16", batch=batch, tokens=tokens, dim=dim, heads=dim // 64, mlp_dim=4 * dim, depth=depth,
+                        aux_depth=1)
+    run_case(wl, steps=1)
+
+
 @pytest.mark.parametrize("tokens,dim,heads", [(20, 128, 4), (65, 96, 1)])
 def test_vit_bf16_attention_shapes_outside_the_matrix_core_kernel(tokens, dim, heads):
     # a head dimension other than 64 (32, 96): the run-time-typed attention kernels on bf16 tensors
