@@ -181,7 +181,7 @@ struct Block {
   int forward_eval_with(const EvalBuffers& e, const void* x_in, void* x_out, float* logits_out, hipStream_t s);
   size_t plan_eval_scratch(char* base, EvalBuffers* e) const;
   int encoder_bwd(int l, const void* x, const void* g_in, void* g_tmp, void* g_out, bool need_dx, hipStream_t s);
-  int encoder_fwd_cls(int l, const void* x, hipStream_t s);
+  int encoder_fwd_cls(int l, const EncoderActs& a, const ClsActs& c, const void* x, hipStream_t s);
   int encoder_bwd_cls(int l, const void* x, const void* d_x2, void* g_out, hipStream_t s);
   // dW[in, out] (row stride ldw) = X^T dY over K rows and db = column sums of dY; recorded for the grouped launch when
   // the matrix-core kernel can take it, else run at once.  x_ld / dy_ld: row strides of X [K, in] and dY [K, out].

@@ -415,11 +415,9 @@ int Block::wgrad_product(const void* xin, long x_ld, int in_dim, const void* dy,
 // the QKV projection run over all B*T rows); the query, the attention output, the output projection, LayerNorm 2 and
 // the MLP are needed for the B class-token rows alone, because only those rows of the layer output reach the head.
 // a.qkv holds [B*T, 2D] keys and values here, cls_a the compact [B, .] tensors; the layer output is cls_a.x2 [B, D].
-int Block::encoder_fwd_cls(int l, const void* x, hipStream_t s) {
+int Block::encoder_fwd_cls(int l, const EncoderActs& a, const ClsActs& c, const void* x, hipStream_t s) {
   const int D = cfg.dim, F = cfg.mlp_dim, T = cfg.tokens, H = cfg.heads, B = cfg.batch, M = B * T;
   const EncoderParams& p = enc_p[l];
-  const EncoderActs& a = enc_a[l];
-  const ClsActs& c = cls_a;
   const size_t wsz = dtype_size(wdt());
   PPLL_TRY(launch_layernorm_fwd(s, x, dt, D, M, D, params + p.ln1_g, params + p.ln1_b, cfg.ln_eps, a.u1, a.mean1, a.rstd1));
   GemmArgs g = gemm_args();   // keys and values of all tokens: columns D..3D of the QKV weight
@@ -527,7 +525,7 @@ int Block::vit_step(const void* x_in, const int32_t* labels, void* x_out, hipStr
   for (int l = L; l < L + A; ++l) {
     layer_in[l] = x;
     if (prune_cls && l == L + A - 1) {
-      PPLL_TRY(encoder_fwd_cls(l, x, s));
+      PPLL_TRY(encoder_fwd_cls(l, enc_a[l], cls_a, x, s));
       x = cls_a.x2;
       head_xs = D;
     } else {
@@ -562,7 +560,7 @@ int Block::vit_step(const void* x_in, const int32_t* labels, void* x_out, hipStr
     g.B = params + head_w; g.b_dt = F32; g.b_sk = 1; g.b_sn = C;
     g.C = dz; g.c_dt = dt; g.ldc = D; g.M = B; g.N = D; g.K = C;
     PPLL_TRY(launch_gemm_generic(s, g));
-    PPLL_TRY(launch_layernorm_bwd(s, dz, x, dt, head_xs, B, D, params + head_ln_g, head_mean, head_rstd, nullptr, dcls,
+    PPLL_TRY(launch_layernorm_bwd(s, dz, x, dt, head_xs, B, D, params + head_ln_g, head_mean, head_rstd, nullptr, 1, dcls,
                                   rq, grads + head_ln_g, grads + head_ln_b));
   }
   PPLL_TRY(mark_phase(2, s));   // auxiliary forward and loss done (the fused head kernel has also run its own backward)
@@ -876,12 +874,23 @@ int Block::forward_eval_with(const EvalBuffers& e, const void* x_in, void* x_out
       PPLL_TRY(encoder_fwd(l, e.enc(l), x, dst, s));
       x = dst;
     }
+    long head_xs = (long)T * D;
     if (!logits_out) return PPLL_OK;
     for (int l = L; l < L + A; ++l) {
-      PPLL_TRY(encoder_fwd(l, e.enc(l), x, e.enc(l).x2, s));
-      x = e.enc(l).x2;
+      const EncoderActs& a = e.enc(l);
+      if (prune_cls && l == L + A - 1) {   // class-token row only, as in a training step
+        ClsActs c{};                       // its [B, .] tensors lie at the start of the layer's own, which are larger
+        c.q = (char*)a.qkv + (size_t)B * T * 2 * D * esz;   // behind the keys and values
+        c.att = a.att; c.x1 = a.x1; c.u2 = a.u2; c.h = a.h; c.gl = a.gl; c.x2 = a.x2;
+        c.mean2 = a.mean2; c.rstd2 = a.rstd2; c.prob = a.lse;
+        PPLL_TRY(encoder_fwd_cls(l, a, c, x, s));
+        head_xs = D;
+      } else {
+        PPLL_TRY(encoder_fwd(l, a, x, a.x2, s));
+      }
+      x = a.x2;
     }
-    PPLL_TRY(launch_layernorm_fwd(s, x, dt, (long)T * D, B, D, params + head_ln_g, params + head_ln_b, cfg.ln_eps, e.z,
+    PPLL_TRY(launch_layernorm_fwd(s, x, dt, head_xs, B, D, params + head_ln_g, params + head_ln_b, cfg.ln_eps, e.z,
                                   e.head_mean, e.head_rstd));
     g = gemm_args();
     g.A = e.z; g.a_dt = dt; g.a_sm = D; g.a_sk = 1;
