@@ -385,14 +385,14 @@ int Block::encoder_bwd(int l, const void* x, const void* g_in, void* g_tmp, void
   PPLL_TRY(wgrad(a.gl, F, g_in, D, p.fc2_w, p.fc2_b));
   PPLL_TRY(launch_gemm(s, dgrad(d_h, F, p.fc1_w, D, d_u)));
   PPLL_TRY(wgrad(a.u2, D, d_h, F, p.fc1_w, p.fc1_b));
-  PPLL_TRY(launch_layernorm_bwd(s, d_u, a.x1, dt, D, M, D, params + p.ln2_g, a.mean2, a.rstd2, g_in, g_tmp, rq,
+  PPLL_TRY(launch_layernorm_bwd(s, d_u, a.x1, dt, D, M, D, params + p.ln2_g, a.mean2, a.rstd2, g_in, 1, g_tmp, rq,
                                 grads + p.ln2_g, grads + p.ln2_b));
   PPLL_TRY(launch_gemm(s, dgrad(g_tmp, D, p.proj_w, D, d_u)));
   PPLL_TRY(wgrad(a.att, D, g_tmp, D, p.proj_w, p.proj_b));
   PPLL_TRY(launch_attention_bwd(s, a.qkv, a.att, d_u, a.lse, dt, cfg.batch, T, H, D / H, d_qkv));
   PPLL_TRY(launch_gemm(s, dgrad(d_qkv, 3 * D, p.qkv_w, D, d_u)));
   PPLL_TRY(wgrad(a.u1, D, d_qkv, 3 * D, p.qkv_w, p.qkv_b));
-  return launch_layernorm_bwd(s, d_u, x, dt, D, M, D, params + p.ln1_g, a.mean1, a.rstd1, g_tmp,
+  return launch_layernorm_bwd(s, d_u, x, dt, D, M, D, params + p.ln1_g, a.mean1, a.rstd1, g_tmp, 1,
                               need_dx ? g_out : nullptr, rq, grads + p.ln1_g, grads + p.ln1_b);
 }
 
@@ -474,7 +474,7 @@ int Block::encoder_bwd_cls(int l, const void* x, const void* d_x2, void* g_out, 
   PPLL_TRY(wgrad_product(c.gl, F, F, d_x2, D, D, B, grads + p.fc2_w, D, grads + p.fc2_b, s));
   PPLL_TRY(launch_gemm(s, dgrad(c.d_h, B, F, wptr(p.fc1_w), F, D, c.d_u2)));
   PPLL_TRY(wgrad_product(c.u2, D, D, c.d_h, F, F, B, grads + p.fc1_w, F, grads + p.fc1_b, s));
-  PPLL_TRY(launch_layernorm_bwd(s, c.d_u2, c.x1, dt, D, B, D, params + p.ln2_g, c.mean2, c.rstd2, d_x2, c.d_x1, rq,
+  PPLL_TRY(launch_layernorm_bwd(s, c.d_u2, c.x1, dt, D, B, D, params + p.ln2_g, c.mean2, c.rstd2, d_x2, 1, c.d_x1, rq,
                                 grads + p.ln2_g, grads + p.ln2_b));
   PPLL_TRY(launch_gemm(s, dgrad(c.d_x1, B, D, wptr(p.proj_w), D, D, c.d_att)));
   PPLL_TRY(wgrad_product(c.att, D, D, c.d_x1, D, D, B, grads + p.proj_w, D, grads + p.proj_b, s));
@@ -487,10 +487,9 @@ int Block::encoder_bwd_cls(int l, const void* x, const void* d_x2, void* g_out, 
   PPLL_TRY(launch_gemm(s, g));
   PPLL_TRY(wgrad_product(a.u1, D, D, d_kv, 2 * D, 2 * D, M, grads + p.qkv_w + D, 3 * D, grads + p.qkv_b + D, s));
   PPLL_TRY(wgrad_product(a.u1, (long)T * D, D, c.d_q, D, D, B, grads + p.qkv_w, 3 * D, grads + p.qkv_b, s));
-  PPLL_TRY(launch_layernorm_bwd(s, d_u, x, dt, D, M, D, params + p.ln1_g, a.mean1, a.rstd1, nullptr, g_out, rq,
-                                grads + p.ln1_g, grads + p.ln1_b));
   // the residual path around the attention block carries d_x1, which lives on the class-token rows only
-  return launch_add_rows(s, g_out, (long)T * D, c.d_x1, B, D, dt);
+  return launch_layernorm_bwd(s, d_u, x, dt, D, M, D, params + p.ln1_g, a.mean1, a.rstd1, c.d_x1, T, g_out, rq,
+                              grads + p.ln1_g, grads + p.ln1_b);
 }
 
 int Block::vit_step(const void* x_in, const int32_t* labels, void* x_out, hipStream_t s,
@@ -874,8 +873,8 @@ int Block::forward_eval_with(const EvalBuffers& e, const void* x_in, void* x_out
       PPLL_TRY(encoder_fwd(l, e.enc(l), x, dst, s));
       x = dst;
     }
-    long head_xs = (long)T * D;
     if (!logits_out) return PPLL_OK;
+    long head_xs = (long)T * D;
     for (int l = L; l < L + A; ++l) {
       const EncoderActs& a = e.enc(l);
       if (prune_cls && l == L + A - 1) {   // class-token row only, as in a training step

@@ -164,9 +164,9 @@ int colsum_mode(hipStream_t s, const void* x, int dt, int rows, int N, int mode,
 int launch_layernorm_fwd(hipStream_t s, const void* x, int dt, long x_row_stride, int rows, int D,
                          const float* g, const float* b, float eps, void* y, float* mean, float* rstd);
 // dx_out = dres + LN'(dy) (either may be null); partial sums of dg/db ([nchunks][2][D]) are
-// reduced into dg, db through the queue.
+// reduced into dg, db through the queue.  dres_every > 1: dres [rows / dres_every, D] belongs to rows 0, dres_every, ...
 int launch_layernorm_bwd(hipStream_t s, const void* dy, const void* x, int dt, long x_row_stride, int rows,
-                         int D, const float* g, const float* mean, const float* rstd, const void* dres,
+                         int D, const float* g, const float* mean, const float* rstd, const void* dres, int dres_every,
                          void* dx_out, ReduceQueue& rq, float* dg, float* db);
 int layernorm_bwd_partial_floats(int rows, int D);
 
@@ -220,8 +220,6 @@ int launch_attention_cls_fwd(hipStream_t s, const void* q, const void* kv, int d
                              float* prob);
 int launch_attention_cls_bwd(hipStream_t s, const void* q, const void* kv, const float* prob, const void* dout, int dt, int B,
                              int T, int H, int dh, void* dq, void* dkv);
-// dst[r * dst_stride + d] += src[r * D + d] for r < rows
-int launch_add_rows(hipStream_t s, void* dst, long dst_stride, const void* src, int rows, int D, int dt);
 
 // ---------------------------------------------------------------- optimizers
 // `shadow` (nullable): bf16 copy of the updated parameters, same offsets

@@ -157,13 +157,6 @@ __global__ __launch_bounds__(CLS_THREADS) void attn_cls_bwd_kernel(const void* q
   }
 }
 
-// dst[r * dst_stride + d] += src[r * D + d]
-__global__ __launch_bounds__(256) void add_rows_kernel(void* dst, long dst_stride, const void* src, int rows, int D, int dt) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (size_t)rows * D) return;
-  const size_t r = i / D, d = i % D, o = r * dst_stride + d;
-  st_f(dst, o, ld_f(dst, o, dt) + ld_f(src, i, dt), dt);
-}
 
 bool cls_vec_ok(int dt, int H, int dh, const void* a, const void* b) {
   return dt == BF16 && !(dh & 7) && !((((uintptr_t)a) | ((uintptr_t)b)) & 15) && H >= 1;
@@ -201,13 +194,6 @@ int launch_attention_cls_bwd(hipStream_t s, const void* q, const void* kv, const
     PPLL_TRY(opt_in_lds((const void*)attn_cls_bwd_kernel<false>, lds, "class-token attention"));
     hipLaunchKernelGGL(attn_cls_bwd_kernel<false>, dim3(B * H), dim3(CLS_THREADS), lds, s, q, kv, prob, dout, dt, T, H, dh, dq, dkv);
   }
-  PPLL_HIP(hipGetLastError());
-  return PPLL_OK;
-}
-
-int launch_add_rows(hipStream_t s, void* dst, long dst_stride, const void* src, int rows, int D, int dt) {
-  const size_t total = (size_t)rows * D;
-  hipLaunchKernelGGL(add_rows_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, dst, dst_stride, src, rows, D, dt);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;
 }

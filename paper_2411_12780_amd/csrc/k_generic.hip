@@ -308,7 +308,7 @@ __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const void* x, int d
 // Each workgroup owns LN_ROWS consecutive rows and emits one partial of dg and db.
 __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const void* dy, const void* x, int dt, long xs, int rows,
                                                             int D, const float* g, const float* mean,
-                                                            const float* rstd, const void* dres, void* dx,
+                                                            const float* rstd, const void* dres, int dres_every, void* dx,
                                                             float* partial) {
   extern __shared__ float sm[];          // [4][2][D]
   int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
@@ -335,7 +335,8 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const void* dy, cons
         float xh = (ld_f(x, xb + d, dt) - mu) * rs;
         float dyh = ld_f(dy, yb + d, dt) * g[d];
         float v = rs * (dyh - s1 - xh * s2);
-        if (dres) v += ld_f(dres, yb + d, dt);
+        if (dres_every > 1 && dt == BF16) v = bf16_to_f32(f32_to_bf16(v));
+        if (dres && row % dres_every == 0) v += ld_f(dres, (size_t)(row / dres_every) * D + d, dt);
         st_f(dx, yb + d, v, dt);
       }
     }
@@ -352,14 +353,15 @@ __device__ __forceinline__ float lo_bf(uint32_t w) { return __uint_as_float(w <<
 __device__ __forceinline__ float hi_bf(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 __device__ __forceinline__ uint32_t pack_bf(float a, float b) { return f32x2_to_bf16x2(a, b); }
 
-// Fast bf16 LayerNorm.  A row of D = 128 NJ elements is held by LPR lanes (16 for D <= 384, 32 up
-// to 768, 64 for 1024), 8 consecutive elements (one 16-byte access) per lane and 8 LPR-column step,
-// so a wave works on 64 / LPR rows at once and the row sums are exchanges inside a lane group.
-template <int NJ> struct LnShape {
-  static constexpr int D = NJ * 128;
-  static constexpr int LPR = NJ <= 3 ? 16 : (NJ <= 6 ? 32 : 64);
+// Fast bf16 LayerNorm.  A row of D elements (a multiple of 64) is held by LPR lanes (8 for 64 and 192, 16 up to 384, 32 up
+// to 768, 64 for 1024), 8 consecutive elements (one 16-byte access) per lane and 8 LPR-column step, so a wave works on
+// 64 / LPR rows at once and the row sums are exchanges inside a lane group.
+template <int D_> struct LnShape {
+  static constexpr int D = D_;
+  static constexpr int LPR = D == 64 || D == 192 ? 8 : (D <= 384 ? 16 : (D <= 768 ? 32 : 64));
   static constexpr int NV = D / (8 * LPR);       // 16-byte pieces per lane and row
   static constexpr int RPW = 64 / LPR;           // rows per wave and pass
+  static_assert(NV * 8 * LPR == D, "a row is a whole number of pieces per lane");
 };
 template <int LPR>
 __device__ __forceinline__ float group_sum(float v) {
@@ -372,11 +374,11 @@ __device__ __forceinline__ void unpack8(const uint4& w, float* v) {
   v[4] = lo_bf(w.z); v[5] = hi_bf(w.z); v[6] = lo_bf(w.w); v[7] = hi_bf(w.w);
 }
 
-template <int NJ>
+template <int DD>
 __global__ __launch_bounds__(256) void layernorm_fwd_bf16_kernel(const uint16_t* x, long xs, int rows,
                                                                  const float* g, const float* b, float eps,
                                                                  uint16_t* y, float* mean, float* rstd) {
-  using S = LnShape<NJ>;
+  using S = LnShape<DD>;
   constexpr int D = S::D, LPR = S::LPR, NV = S::NV, RPW = S::RPW;
   const int lane = threadIdx.x & 63, lr = lane % LPR;
   const int row = (blockIdx.x * 4 + (threadIdx.x >> 6)) * RPW + lane / LPR;
@@ -413,33 +415,45 @@ __global__ __launch_bounds__(256) void layernorm_fwd_bf16_kernel(const uint16_t*
   if (lr == 0) { mean[row] = mu; rstd[row] = rs; }
 }
 
-constexpr int LNF_ROWS = 32;   // rows per workgroup (and per partial of dg, db) in the fast backward
-template <int NJ>
-__global__ __launch_bounds__(256) void layernorm_bwd_bf16_kernel(const uint16_t* dy, const uint16_t* x, long xs,
+// Backward.  What bounds it at training sizes (8320 rows of width 384: 26 MB, 3.6 us at the rate the last-level cache
+// delivers) is the latency of one row's chain - loads, two row sums, the write - so the rows are spread over as many waves
+// as there are: eight waves per workgroup, one pass over 64 / LPR rows each while that gives at most two workgroups per
+// compute unit, more passes beyond (each workgroup leaves one partial row of dg, db, which a later kernel has to add up).
+constexpr int LNB_WAVES = 8;
+template <int DD> constexpr int lnb_rows_per_pass() { return LNB_WAVES * LnShape<DD>::RPW; }
+// lane l and lane l ^ 32 (16): after the swap the sum a + b holds a's total on the lanes whose bit 5 (4) is clear and b's
+// on the others: one exchange folds two values
+__device__ __forceinline__ float fold32(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float fold16(float a, float b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// dres_every: rows r with r % dres_every == 0 take row r / dres_every of dres, the others none (1: every row its own)
+template <int DD, bool ONE, bool SPARSE>
+__global__ __launch_bounds__(64 * LNB_WAVES, 2) void layernorm_bwd_bf16_kernel(const uint16_t* dy, const uint16_t* x, long xs,
                                                                  int rows, const float* g, const float* mean,
-                                                                 const float* rstd, const uint16_t* dres,
-                                                                 uint16_t* dx, float* partial) {
-  using S = LnShape<NJ>;
+                                                                 const float* rstd, const uint16_t* dres, int dres_every,
+                                                                 uint16_t* dx, float* partial, int passes) {
+  using S = LnShape<DD>;
   constexpr int D = S::D, LPR = S::LPR, NV = S::NV, RPW = S::RPW;
-  __shared__ float sm[4][2 * D];
+  __shared__ __align__(16) float sm[LNB_WAVES][2 * D];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane % LPR, sub = lane / LPR;
-  float gg[8 * NV], adg[8 * NV], adb[8 * NV];
-#pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    const int c = 8 * lr + 8 * LPR * j;
-    const float4 g0 = *reinterpret_cast<const float4*>(g + c), g1 = *reinterpret_cast<const float4*>(g + c + 4);
-    gg[8 * j] = g0.x; gg[8 * j + 1] = g0.y; gg[8 * j + 2] = g0.z; gg[8 * j + 3] = g0.w;
-    gg[8 * j + 4] = g1.x; gg[8 * j + 5] = g1.y; gg[8 * j + 6] = g1.z; gg[8 * j + 7] = g1.w;
-  }
+  float adg[8 * NV], adb[8 * NV];
 #pragma unroll
   for (int j = 0; j < 8 * NV; ++j) { adg[j] = 0.f; adb[j] = 0.f; }
-  const int r0 = blockIdx.x * LNF_ROWS;
-  // a wave takes RPW rows per pass; the rows of a workgroup are summed in the same order whatever
-  // the grid: pass by pass inside a lane group, then across lane groups, then across waves
-  for (int rr = wave * RPW + sub; rr < LNF_ROWS; rr += 4 * RPW) {
-    const int row = r0 + rr;
+  const int r0 = blockIdx.x * (ONE ? 1 : passes) * (LNB_WAVES * RPW);
+  // the rows of a workgroup are summed in the same order whatever the grid: pass by pass inside a lane group, then across
+  // lane groups, then across waves
+  for (int pass = 0; pass < (ONE ? 1 : passes); ++pass) {
+    const int row = r0 + pass * (LNB_WAVES * RPW) + wave * RPW + sub;
     const bool ok = row < rows;
     uint4 wx[NV], wd[NV], wr[NV];
+    long rrow = row;
+    bool has_res = dres != nullptr && ok;
+    if (SPARSE) { rrow = row / dres_every; has_res = has_res && row % dres_every == 0; }
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
       const int c = 8 * lr + 8 * LPR * j;
@@ -447,14 +461,17 @@ __global__ __launch_bounds__(256) void layernorm_bwd_bf16_kernel(const uint16_t*
       if (ok) {
         wx[j] = *reinterpret_cast<const uint4*>(x + (size_t)row * xs + c);
         wd[j] = *reinterpret_cast<const uint4*>(dy + (size_t)row * D + c);
-        if (dres) wr[j] = *reinterpret_cast<const uint4*>(dres + (size_t)row * D + c);
       }
+      if (has_res) wr[j] = *reinterpret_cast<const uint4*>(dres + (size_t)rrow * D + c);
     }
     const float mu = ok ? mean[row] : 0.f, rs = ok ? rstd[row] : 0.f;
     float xh[8 * NV], dyh[8 * NV];
     float s1 = 0.f, s2 = 0.f;
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
+      const int c = 8 * lr + 8 * LPR * j;
+      const float4 g0 = *reinterpret_cast<const float4*>(g + c), g1 = *reinterpret_cast<const float4*>(g + c + 4);
+      const float gg[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
       float xv[8], dv[8];
       unpack8(wx[j], xv);
       unpack8(wd[j], dv);
@@ -464,7 +481,7 @@ __global__ __launch_bounds__(256) void layernorm_bwd_bf16_kernel(const uint16_t*
         xh[i] = ok ? (xv[e] - mu) * rs : 0.f;
         adg[i] += dv[e] * xh[i];
         adb[i] += dv[e];
-        dyh[i] = dv[e] * gg[i];
+        dyh[i] = dv[e] * gg[e];
         s1 += dyh[i];
         s2 += dyh[i] * xh[i];
       }
@@ -477,56 +494,90 @@ __global__ __launch_bounds__(256) void layernorm_bwd_bf16_kernel(const uint16_t*
         float o[8], rv[8];
         unpack8(wr[j], rv);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = rs * (dyh[8 * j + e] - s1 - xh[8 * j + e] * s2) + rv[e];
+        for (int e = 0; e < 8; ++e) {
+          o[e] = rs * (dyh[8 * j + e] - s1 - xh[8 * j + e] * s2);
+          // a compact dres is added to the stored gradient: rounded to the activation type before and after
+          if (SPARSE) o[e] = bf16_to_f32(f32_to_bf16(o[e]));
+          o[e] += rv[e];
+        }
         *reinterpret_cast<uint4*>(dx + (size_t)row * D + 8 * lr + 8 * LPR * j) =
             make_uint4(pack_bf(o[0], o[1]), pack_bf(o[2], o[3]), pack_bf(o[4], o[5]), pack_bf(o[6], o[7]));
       }
     }
   }
-  // lane groups of a wave hold the same columns: fold them, then the four waves through LDS
+  // lane groups of a wave hold the same columns: fold them (dg to the lower half of the lanes, db to the upper half, then
+  // the halves of each in turn), then the waves through LDS
+  if (LPR <= 32) {
+    float f[8 * NV];
 #pragma unroll
-  for (int i = 0; i < 8 * NV; ++i) {
+    for (int i = 0; i < 8 * NV; ++i) f[i] = fold32(adg[i], adb[i]);
+    if (LPR <= 16) {
 #pragma unroll
-    for (int o = LPR; o < 64; o <<= 1) { adg[i] += __shfl_xor(adg[i], o, 64); adb[i] += __shfl_xor(adb[i], o, 64); }
-  }
-  if (sub == 0) {
+      for (int i = 0; i < 4 * NV; ++i) f[i] = fold16(f[i], f[i + 4 * NV]);   // bit 4 of the lane now picks value i or i + 4 NV
+      if (LPR == 8) {
 #pragma unroll
-    for (int j = 0; j < NV; ++j)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int c = 8 * lr + 8 * LPR * j + e;
-        sm[wave][c] = adg[8 * j + e];
-        sm[wave][D + c] = adb[8 * j + e];
+        for (int i = 0; i < 4 * NV; ++i) f[i] += __shfl_xor(f[i], 8, 64);
       }
+      const int half = (lane >> 4) & 1, kind = lane >> 5;
+      if ((lane & 15) < LPR) {
+#pragma unroll
+        for (int i = 0; i < 4 * NV; ++i) {
+          const int v = i + half * 4 * NV;
+          sm[wave][kind * D + 8 * lr + 8 * LPR * (v >> 3) + (v & 7)] = f[i];
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8 * NV; ++i) sm[wave][(lane >> 5) * D + 8 * lr + 8 * LPR * (i >> 3) + (i & 7)] = f[i];
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 8 * NV; ++i) {
+      const int c = 8 * lr + 8 * LPR * (i >> 3) + (i & 7);
+      sm[wave][c] = adg[i];
+      sm[wave][D + c] = adb[i];
+    }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < 2 * D; i += 256)
-    partial[(size_t)blockIdx.x * 2 * D + i] = sm[0][i] + sm[1][i] + sm[2][i] + sm[3][i];
+  for (int i = threadIdx.x; i < D / 2; i += 64 * LNB_WAVES) {   // four of the 2 D columns
+    float4 t = *reinterpret_cast<const float4*>(&sm[0][4 * i]);
+#pragma unroll
+    for (int w = 1; w < LNB_WAVES; ++w) {
+      const float4 q = *reinterpret_cast<const float4*>(&sm[w][4 * i]);
+      t.x += q.x; t.y += q.y; t.z += q.z; t.w += q.w;
+    }
+    *reinterpret_cast<float4*>(partial + (size_t)blockIdx.x * 2 * D + 4 * i) = t;
+  }
 }
 
+bool ln_fast_dim(int D) {
+  return D == 64 || D == 128 || D == 192 || D == 256 || D == 384 || D == 512 || D == 768 || D == 1024;
+}
 bool ln_fast_ok(int dt, int D, long xs, const void* a, const void* b, const void* c, const void* d) {
   if (dt != BF16 || (xs & 1)) return false;
-  if (!(D == 128 || D == 256 || D == 384 || D == 512 || D == 768 || D == 1024)) return false;
+  if (!ln_fast_dim(D)) return false;
   return !(xs & 7) && !((((uintptr_t)a) | ((uintptr_t)b) | ((uintptr_t)c) | ((uintptr_t)d)) & 15);
 }
 }  // namespace
 
-#define LN_DISPATCH(NJ_EXPR, CALL)                  \
-  switch (NJ_EXPR) {                                \
-    case 1: { constexpr int NJ = 1; CALL; break; }  \
-    case 2: { constexpr int NJ = 2; CALL; break; }  \
-    case 3: { constexpr int NJ = 3; CALL; break; }  \
-    case 4: { constexpr int NJ = 4; CALL; break; }  \
-    case 6: { constexpr int NJ = 6; CALL; break; }  \
-    default: { constexpr int NJ = 8; CALL; break; } \
+#define LN_DISPATCH(D_EXPR, CALL)                      \
+  switch (D_EXPR) {                                    \
+    case 64: { constexpr int DD = 64; CALL; break; }   \
+    case 128: { constexpr int DD = 128; CALL; break; } \
+    case 192: { constexpr int DD = 192; CALL; break; } \
+    case 256: { constexpr int DD = 256; CALL; break; } \
+    case 384: { constexpr int DD = 384; CALL; break; } \
+    case 512: { constexpr int DD = 512; CALL; break; } \
+    case 768: { constexpr int DD = 768; CALL; break; } \
+    default: { constexpr int DD = 1024; CALL; break; } \
   }
 
 int launch_layernorm_fwd(hipStream_t s, const void* x, int dt, long xs, int rows, int D, const float* g,
                          const float* b, float eps, void* y, float* mean, float* rstd) {
   if (ln_fast_ok(dt, D, xs, x, y, g, b)) {
-    LN_DISPATCH(D / 128, hipLaunchKernelGGL((layernorm_fwd_bf16_kernel<NJ>),
-                                            dim3((rows + 4 * LnShape<NJ>::RPW - 1) / (4 * LnShape<NJ>::RPW)), dim3(256), 0, s,
-                                            (const uint16_t*)x, xs, rows, g, b, eps, (uint16_t*)y, mean, rstd));
+    LN_DISPATCH(D, hipLaunchKernelGGL((layernorm_fwd_bf16_kernel<DD>),
+                                      dim3((rows + 4 * LnShape<DD>::RPW - 1) / (4 * LnShape<DD>::RPW)), dim3(256), 0, s,
+                                      (const uint16_t*)x, xs, rows, g, b, eps, (uint16_t*)y, mean, rstd));
   } else {
     hipLaunchKernelGGL(layernorm_fwd_kernel, dim3((rows + 3) / 4), dim3(256), 0, s, x, dt, xs, rows, D, g, b, eps, y,
                        mean, rstd);
@@ -535,26 +586,47 @@ int launch_layernorm_fwd(hipStream_t s, const void* x, int dt, long xs, int rows
   return PPLL_OK;
 }
 
-int layernorm_bwd_partial_floats(int rows, int D) { return ((rows + LN_ROWS - 1) / LN_ROWS) * 2 * D; }
+// rows per pass of a workgroup of the fast backward, and its passes at a given row count (see the kernel)
+static int lnb_pass_rows(int D) {
+  int v = 1;
+  LN_DISPATCH(D, v = lnb_rows_per_pass<DD>());
+  return v;
+}
+static int lnb_passes(int rows, int D) {
+  const int p = rows / (lnb_pass_rows(D) * 512);
+  return p < 1 ? 1 : p;
+}
+int layernorm_bwd_partial_floats(int rows, int D) {
+  const int chunks = (rows + LN_ROWS - 1) / LN_ROWS;
+  if (!ln_fast_dim(D)) return chunks * 2 * D;
+  const int per = lnb_pass_rows(D) * lnb_passes(rows, D), fast = (rows + per - 1) / per;
+  return (chunks > fast ? chunks : fast) * 2 * D;
+}
 
 int launch_layernorm_bwd(hipStream_t s, const void* dy, const void* x, int dt, long xs, int rows, int D,
-                         const float* g, const float* mean, const float* rstd, const void* dres, void* dx_out,
-                         ReduceQueue& rq, float* dg, float* db) {
+                         const float* g, const float* mean, const float* rstd, const void* dres, int dres_every,
+                         void* dx_out, ReduceQueue& rq, float* dg, float* db) {
   int chunks;
   const bool fast = ln_fast_ok(dt, D, xs, x, dy, dres, dx_out) && !(((uintptr_t)g) & 15);
   bool queued;
-  float* partials = rq.space((size_t)((rows + (fast ? LNF_ROWS : LN_ROWS) - 1) / (fast ? LNF_ROWS : LN_ROWS)) * 2 * D, &queued);
+  float* partials = rq.space((size_t)layernorm_bwd_partial_floats(rows, D), &queued);
   if (fast) {
-    chunks = (rows + LNF_ROWS - 1) / LNF_ROWS;
-    LN_DISPATCH(D / 128, hipLaunchKernelGGL((layernorm_bwd_bf16_kernel<NJ>), dim3(chunks), dim3(256), 0, s,
-                                            (const uint16_t*)dy, (const uint16_t*)x, xs, rows, g, mean, rstd,
-                                            (const uint16_t*)dres, (uint16_t*)dx_out, partials));
+    const int passes = lnb_passes(rows, D), per = lnb_pass_rows(D) * passes;
+    chunks = (rows + per - 1) / per;
+#define LNB_LAUNCH(ONE, SPARSE)                                                                                            \
+  LN_DISPATCH(D, hipLaunchKernelGGL((layernorm_bwd_bf16_kernel<DD, ONE, SPARSE>), dim3(chunks), dim3(64 * LNB_WAVES), 0, s, \
+                                    (const uint16_t*)dy, (const uint16_t*)x, xs, rows, g, mean, rstd,                      \
+                                    (const uint16_t*)dres, dres_every, (uint16_t*)dx_out, partials, passes))
+    if (dres_every > 1) { LNB_LAUNCH(false, true); }   // one layer of a step
+    else if (passes == 1) { LNB_LAUNCH(true, false); }
+    else { LNB_LAUNCH(false, false); }
+#undef LNB_LAUNCH
   } else {
     chunks = (rows + LN_ROWS - 1) / LN_ROWS;
     size_t lds = (size_t)8 * D * sizeof(float);
     if (lds > 48 * 1024) { set_error("layernorm_bwd: dim %d too large", D); return PPLL_ERR_CONFIG; }
     hipLaunchKernelGGL(layernorm_bwd_kernel, dim3(chunks), dim3(256), lds, s, dy, x, dt, xs, rows, D, g, mean, rstd,
-                       dres, dx_out, partials);
+                       dres, dres_every, dx_out, partials);
   }
   PPLL_HIP(hipGetLastError());
   // each partial row is [dg | db]; the two gradients are neighbours in the parameter table
