@@ -404,7 +404,7 @@ int Block::wgrad_product(const void* xin, long x_ld, int in_dim, const void* dy,
   g.C = dW; g.c_dt = F32; g.ldc = ldw; g.M = in_dim; g.N = out_dim; g.K = K;
   g.colsum = db;
   g.splitk_ws = splitk; g.splitk_floats = splitk_floats;
-  if (gemm_mfma_groupable(g)) { wgrad_jobs.push_back(g); return PPLL_OK; }
+  if (gemm_weight_grad_groupable(g)) { wgrad_jobs.push_back(g); return PPLL_OK; }
   g.colsum = nullptr;
   PPLL_TRY(launch_gemm(s, g));
   if (dy_ld != out_dim) { set_error("bias gradient of a strided product needs the matrix-core kernel"); return PPLL_ERR_CONFIG; }
@@ -577,7 +577,7 @@ int Block::vit_step(const void* x_in, const int32_t* labels, void* x_out, hipStr
     // workgroups leave empty (measured: 5 % of the step at width 768 and 197 tokens).  Smaller sets only slow the
     // chain down (measured at width 384: 2 to 8 % slower), so they wait for the grouped launch at the end.
     // (not while launches are being timed one by one: overlapping kernels would stretch each other's brackets)
-    if (use_side && !profile_enabled() && l > 0 && M >= SIDE_MIN_ROWS && gemm_group_in_one_launch(wgrad_jobs.data(), (int)wgrad_jobs.size())) {
+    if (use_side && dt == BF16 && !profile_enabled() && l > 0 && M >= SIDE_MIN_ROWS && wgrad_jobs.size() > 1) {
       long tiles = 0;
       for (size_t j = first_job; j < wgrad_jobs.size(); ++j)
         tiles += (long)((wgrad_jobs[j].M + 127) / 128) * ((wgrad_jobs[j].N + 127) / 128);
@@ -593,7 +593,7 @@ int Block::vit_step(const void* x_in, const int32_t* labels, void* x_out, hipStr
       g.C = grads + pe_w; g.c_dt = F32; g.ldc = D; g.M = ppc; g.N = D; g.K = B * (T - 1);
       g.colsum = grads + pe_b;   // bias gradient: column sums of dE, folded into the product by the MFMA kernel
       g.splitk_ws = splitk; g.splitk_floats = splitk_floats;
-      if (gemm_mfma_groupable(g)) {
+      if (gemm_weight_grad_groupable(g)) {
         wgrad_jobs.push_back(g);
       } else {
         g.colsum = nullptr;

@@ -102,15 +102,19 @@ struct GemmArgs {
   const void* aux; int aux_dt; long ldaux;    // EPI_DGELU: the saved GELU derivative
   float* splitk_ws; size_t splitk_floats;     // optional scratch for split-K partial sums
   float* colsum;                              // optional: out[n] = sum_k B(k,n) (bias gradient of a dW product);
-                                              // honoured only by the MFMA kernel, see gemm_fuses_colsum()
+                                              // honoured only by the matrix-core kernels
 };
 int launch_gemm(hipStream_t s, const GemmArgs& g);          // picks the MFMA kernel when the shape allows
 int launch_gemm_generic(hipStream_t s, const GemmArgs& g);
 // Products with few output rows (the class-token rows of a pruned auxiliary layer): see k_gemm_rows.hip
 bool gemm_rows_supported(const GemmArgs& g);
 int launch_gemm_rows(hipStream_t s, const GemmArgs& g);
+// fp32 products on the matrix cores: see k_f32.hip
+bool gemm_f32_supported(const GemmArgs& g);
+bool gemm_f32_groupable(const GemmArgs& g);
+int launch_gemm_f32(hipStream_t s, const GemmArgs& g);
+int launch_gemm_f32_grouped(hipStream_t s, const GemmArgs* gs, int n);
 bool gemm_mfma_supported(const GemmArgs& g);
-inline bool gemm_fuses_colsum(const GemmArgs& g) { return g.colsum && gemm_mfma_supported(g); }
 size_t gemm_mfma_partial_floats(int M, int N, int K);
 int launch_gemm_mfma(hipStream_t s, const GemmArgs& g, float* partial, size_t partial_floats);
 bool gemm_mfma_groupable(const GemmArgs& g);
@@ -118,9 +122,10 @@ bool gemm_mfma_groupable(const GemmArgs& g);
 // the k-steps out evenly over the compute units (parts of divided tiles pass through it)
 int launch_gemm_mfma_grouped(hipStream_t s, const GemmArgs* gs, int n, float* ws = nullptr, size_t ws_floats = 0);
 size_t gemm_mfma_balanced_floats();
-// A set of independent products; one launch when all of them are groupable, else one by one.
+// A set of independent products of one element type, each a weight gradient that gemm_weight_grad_groupable() accepts, in
+// one launch.
+inline bool gemm_weight_grad_groupable(const GemmArgs& g) { return gemm_mfma_groupable(g) || gemm_f32_groupable(g); }
 int launch_gemm_group(hipStream_t s, const GemmArgs* gs, int n, bool use_workspace = false);
-bool gemm_group_in_one_launch(const GemmArgs* gs, int n);   // every product fits the grouped kernel (n > 1)
 // Per-launch timing of the contraction kernels (a measurement aid, off unless a block asks for it).  A block that
 // times its launches binds its record to the calling thread for the duration of a step; the launch functions
 // below the block engine then bracket each contraction launch with a pair of events on its stream.
@@ -208,6 +213,10 @@ bool attention_mfma_supported(int dt, int T, int H, int dh, const void* a, const
 int launch_attention_fwd_mfma(hipStream_t s, const void* qkv, int B, int T, int H, void* out, float* lse);
 int launch_attention_bwd_mfma(hipStream_t s, const void* qkv, const void* out, const void* dout, const float* lse,
                               int B, int T, int H, void* dqkv);
+bool attention_rows_fits(int T, int H, int dh, bool bwd);
+int launch_attention_rows_fwd(hipStream_t s, const void* qkv, int dt, int B, int T, int H, int dh, void* out, float* lse);
+int launch_attention_rows_bwd(hipStream_t s, const void* qkv, const void* out, const void* dout, const float* lse, int dt,
+                              int B, int T, int H, int dh, void* dqkv);
 int launch_attention_fwd_generic(hipStream_t s, const void* qkv, int dt, int B, int T, int H, int dh, void* out,
                                  float* lse);
 int launch_attention_bwd_generic(hipStream_t s, const void* qkv, const void* out, const void* dout,

@@ -59,33 +59,21 @@ int profile_end(hipStream_t s, void* token) {
 
 int launch_gemm(hipStream_t s, const GemmArgs& g) {
   if (gemm_rows_supported(g)) return launch_gemm_rows(s, g);   // few output rows: latency, not throughput
-  return gemm_mfma_supported(g) ? launch_gemm_mfma(s, g, g.splitk_ws, g.splitk_floats) : launch_gemm_generic(s, g);
-}
-
-bool gemm_group_in_one_launch(const GemmArgs* gs, int n) {
-  bool all = n > 1;
-  for (int j = 0; j < n && all; ++j) all = gemm_mfma_groupable(gs[j]);
-  return all;
+  if (gemm_mfma_supported(g)) return launch_gemm_mfma(s, g, g.splitk_ws, g.splitk_floats);
+  return gemm_f32_supported(g) ? launch_gemm_f32(s, g) : launch_gemm_generic(s, g);
 }
 
 // use_workspace: the grouped launch may pass divided tiles through the products' split-K scratch (gs[0].splitk_ws);
 // only for a launch that is the sole user of that scratch while it runs.
 int launch_gemm_group(hipStream_t s, const GemmArgs* gs, int n, bool use_workspace) {
   if (n <= 0) return PPLL_OK;
-  bool all = true;
-  for (int j = 0; j < n && all; ++j) all = gemm_mfma_groupable(gs[j]);
-  if (all)
-    return launch_gemm_mfma_grouped(s, gs, n, use_workspace ? gs[0].splitk_ws : nullptr, use_workspace ? gs[0].splitk_floats : 0);
-  for (int j = 0; j < n; ++j) {
-    const bool fused = gemm_fuses_colsum(gs[j]);
-    if (gs[j].colsum && !fused) { set_error("launch_gemm_group: column sums need the MFMA kernel"); return PPLL_ERR_CONFIG; }
-    PPLL_TRY(launch_gemm(s, gs[j]));
-  }
-  return PPLL_OK;
+  if (gs[0].a_dt == F32) return launch_gemm_f32_grouped(s, gs, n);
+  return launch_gemm_mfma_grouped(s, gs, n, use_workspace ? gs[0].splitk_ws : nullptr, use_workspace ? gs[0].splitk_floats : 0);
 }
 
 int launch_attention_fwd(hipStream_t s, const void* qkv, int dt, int B, int T, int H, int dh, void* out, float* lse) {
   if (attention_mfma_supported(dt, T, H, dh, qkv, out, nullptr, nullptr)) return launch_attention_fwd_mfma(s, qkv, B, T, H, out, lse);
+  if (attention_rows_fits(T, H, dh, false)) return launch_attention_rows_fwd(s, qkv, dt, B, T, H, dh, out, lse);
   return launch_attention_fwd_generic(s, qkv, dt, B, T, H, dh, out, lse);
 }
 
@@ -93,6 +81,7 @@ int launch_attention_bwd(hipStream_t s, const void* qkv, const void* out, const 
                          int B, int T, int H, int dh, void* dqkv) {
   if (attention_mfma_supported(dt, T, H, dh, qkv, out, dout, dqkv))
     return launch_attention_bwd_mfma(s, qkv, out, dout, lse, B, T, H, dqkv);
+  if (attention_rows_fits(T, H, dh, true)) return launch_attention_rows_bwd(s, qkv, out, dout, lse, dt, B, T, H, dh, dqkv);
   return launch_attention_bwd_generic(s, qkv, out, dout, lse, dt, B, T, H, dh, dqkv);
 }
 

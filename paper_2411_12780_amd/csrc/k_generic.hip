@@ -285,7 +285,7 @@ int launch_colsum(hipStream_t s, const void* x, int dt, int rows, int N, ReduceQ
 
 // ===================================================================== LayerNorm
 namespace {
-constexpr int LN_ROWS = 32;   // rows per workgroup in the backward (4 waves x 8)
+constexpr int LN_ROWS = 8;    // rows per workgroup in the run-time-typed backward (4 waves x 2: a row is a latency chain)
 
 __global__ __launch_bounds__(256) void layernorm_fwd_kernel(const void* x, int dt, long xs, int rows, int D,
                                                             const float* g, const float* b, float eps, void* y,

@@ -313,6 +313,19 @@ def test_resnet_fp32_stage_full_size_natural_statistics():
     run_case(synth.workload("resnet_stage_bf16", precision=synth.FP32), steps=1, check_bn=True, precision_floor=True)
 
 
+@pytest.mark.parametrize("batch,tokens,dim,heads,mlp,depth,aux", [
+    (3, 17, 64, 4, 132, 1, 1),      # 51 rows: ragged tiles and k ranges, 16-wide heads, one query row past a tile of 16
+    (24, 65, 192, 3, 768, 2, 0),    # 64 x 64 tiles, odd number of rows in the weight gradients
+    (2, 130, 96, 3, 100, 1, 1),     # attention over more than 128 tokens
+    (1, 256, 64, 1, 64, 1, 0),      # the most tokens: the attention backward does not fit with its rows in LDS
+    (2, 5, 36, 2, 20, 1, 0),        # 18-wide heads: not a multiple of four
+])
+def test_vit_fp32_products_and_attention_at_tile_edges(batch, tokens, dim, heads, mlp, depth, aux):
+    wl = synth.workload("vit_tiny_fp32", input_kind=synth.ACTIVATION, batch=batch, tokens=tokens, dim=dim, heads=heads, mlp_dim=mlp,
+                        depth=depth, aux_depth=aux)
+    run_case(wl, steps=1)
+
+
 @pytest.mark.parametrize("tokens", [1, 32, 64, 256])
 def test_vit_bf16_token_counts_at_tile_edges(tokens):
     # head dim 64: 1 token, exactly one / two 32-token tiles, and the 256-token maximum
