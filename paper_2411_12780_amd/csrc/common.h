@@ -50,10 +50,33 @@ __device__ __forceinline__ void st_f(void* p, size_t i, float v, int dt) {
   if (dt == BF16) ((uint16_t*)p)[i] = f32_to_bf16(v);
   else ((float*)p)[i] = v;
 }
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+// Reductions over the lanes of a wave (LANES = 64) or of each group of 32 / 16 lanes, every lane receiving the result: the
+// butterfly lane ^ 32, ^ 16, ^ 8, ^ 4, ^ 2, ^ 1 without the LDS crossbar.  Once the lanes that differ in the higher bits hold
+// the same value, a rotation inside a row of 16 by 8, 4, 2, 1 fetches from a lane that holds what lane ^ 8, 4, 2, 1 holds.
+// (__shfl_xor goes through LDS: some 60 clocks per exchange against 8.)
+template <int CTRL> __device__ __forceinline__ float dpp_f(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int LANES, class OP> __device__ __forceinline__ float lanes_reduce(float v, OP op) {
+  if (LANES > 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  }
+  if (LANES > 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  }
+  v = op(v, dpp_f<0x128>(v));   // row_ror:8
+  v = op(v, dpp_f<0x124>(v));
+  v = op(v, dpp_f<0x122>(v));
+  return op(v, dpp_f<0x121>(v));
+}
+template <int LANES> __device__ __forceinline__ float lanes_sum(float v) {
+  return lanes_reduce<LANES>(v, [](float a, float b) { return a + b; });
+}
+__device__ __forceinline__ float wave_sum(float v) { return lanes_sum<64>(v); }
+__device__ __forceinline__ float wave_max(float v) {
+  return lanes_reduce<64>(v, [](float a, float b) { return fmaxf(a, b); });
 }
 // Orders LDS traffic between the lanes of one wave (writes before, reads after).
 __device__ __forceinline__ void wave_sync() {
@@ -72,11 +95,6 @@ __device__ __forceinline__ void cdf_pdf(float h, float& cdf, float& pdf) {
   const float erf_abs = 1.0f - poly * ex;
   cdf = 0.5f * (1.0f + copysignf(erf_abs, h));
   pdf = 0.39894228040143268f * ex;
-}
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
 }
 #endif
 
@@ -151,7 +169,10 @@ int reduce_partials(hipStream_t s, const float* partial, int chunks, int N, long
 // stage is only queued and all queued ones run as one launch in flush() (parameter gradients are
 // not needed before the optimizer update); otherwise from the shared scratch buffer, and the
 // second stage runs at once.  The summation order is the same either way.
-struct ReduceJob { const float* src; float* dst; int chunks, N; long stride; float scale; };
+// outer != null: dst[n * outer_n + c] = sum over rows r of src[r][n] * outer[r][c] (outer [chunks][outer_n], outer_n <=
+// OUTER_MAX), a weight gradient with few output columns
+constexpr int OUTER_MAX = 16;
+struct ReduceJob { const float* src; float* dst; int chunks, N; long stride; float scale; const float* outer; int outer_n; };
 struct ReduceQueue {
   float* scratch = nullptr;            // shared by all reductions that finish at once
   float* arena = nullptr;              // private room for the queued ones, handed out front to back
@@ -159,6 +180,7 @@ struct ReduceQueue {
   std::vector<ReduceJob> jobs;
   float* space(size_t floats, bool* queued);
   int reduce(hipStream_t s, bool queued, const float* src, int chunks, int N, long stride, float scale, float* out);
+  int reduce_outer(hipStream_t s, bool queued, const float* src, int rows, int N, const float* outer, int outer_n, float* out);
   int flush(hipStream_t s);
   void reset() { used = 0; jobs.clear(); }
 };

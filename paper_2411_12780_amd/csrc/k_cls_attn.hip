@@ -41,8 +41,7 @@ __device__ __forceinline__ void stage_head(const void* src, int dt, size_t first
   }
 }
 // sum / maximum over the workgroup through LDS (red: CLS_THREADS / 64 floats), same order for every thread
-__device__ __forceinline__ float block_sum(float v, float* red, int tid) {
-  v = wave_sum(v);
+__device__ __forceinline__ float block_sum_of(float v, float* red, int tid) {   // v: the wave's sum
   __syncthreads();
   if ((tid & 63) == 0) red[tid >> 6] = v;
   __syncthreads();
@@ -50,6 +49,13 @@ __device__ __forceinline__ float block_sum(float v, float* red, int tid) {
 #pragma unroll
   for (int w = 0; w < CLS_THREADS / 64; ++w) t += red[w];
   return t;
+}
+__device__ __forceinline__ float block_sum(float v, float* red, int tid) { return block_sum_of(wave_sum(v), red, tid); }
+// sum of a b, the first exchange (lane ^ 32) taken into a multiply-add with the lane's own product
+__device__ __forceinline__ float block_dot(float a, float b, float* red, int tid) {
+  const uint32_t ab = __float_as_uint(a * b);
+  const auto r = __builtin_amdgcn_permlane32_swap(ab, ab, false, false);
+  return block_sum_of(lanes_sum<32>(fmaf(a, b, __uint_as_float((tid & 32) ? r[0] : r[1]))), red, tid);
 }
 __device__ __forceinline__ float block_max(float v, float* red, int tid) {
   v = wave_max(v);
@@ -124,7 +130,7 @@ __global__ __launch_bounds__(CLS_THREADS) void attn_cls_bwd_kernel(const void* q
     for (int d = 0; d < dh; ++d) dp = fmaf(dos[d], Vs[tid * (dh + 1) + d], dp);
     p = prob[(size_t)blockIdx.x * T + tid];
   }
-  const float delta = block_sum(p * dp, red, tid);
+  const float delta = block_dot(p, dp, red, tid);
   if (tid < T) { ps[tid] = p; ds[tid] = p * (dp - delta); }
   __syncthreads();
   for (int d = tid; d < dh; d += CLS_THREADS) {

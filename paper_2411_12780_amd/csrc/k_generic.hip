@@ -162,20 +162,46 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* parti
   }
 }
 
-// the same for up to 16 reductions in one launch: workgroups first[j] .. first[j+1]-1 belong to job j.
+// the same for up to RED_BATCH reductions in one launch: workgroups first[j] .. first[j+1]-1 belong to job j.
 // A job whose rows are 16-byte aligned with a length that is a multiple of 4 takes four columns per
 // thread (64 columns per workgroup, 256-byte row segments); the 16 thread groups take the partial
 // rows round-robin, eight loads in flight, and are added in group order.
-constexpr int RED_BATCH = 16;
+constexpr int RED_BATCH = 40;   // the table stays below the 4 KB of a kernel's arguments
 struct ReduceBatch { int n; int first[RED_BATCH + 1]; int vec4[RED_BATCH]; ReduceJob job[RED_BATCH]; };
 __global__ __launch_bounds__(256) void reduce_batch_kernel(ReduceBatch a) {
   __shared__ float red[16][65];
+  __shared__ float outer_red[16][16 * OUTER_MAX];
   int j = 0;
   while (j + 1 < a.n && (int)blockIdx.x >= a.first[j + 1]) ++j;
   const float* partial = a.job[j].src;
   const int chunks = a.job[j].chunks, N = a.job[j].N;
   const long stride = a.job[j].stride;
   const int col = threadIdx.x & 15, grp = threadIdx.x >> 4;
+  if (a.job[j].outer) {   // 16 columns n, the 16 thread groups take the rows round-robin, eight rows in flight
+    const float* dl = a.job[j].outer;
+    const int C = a.job[j].outer_n, n = ((int)blockIdx.x - a.first[j]) * 16 + col, nc = min(n, N - 1);
+    float acc[OUTER_MAX] = {};
+    for (int r0 = grp; r0 < chunks; r0 += 16 * 8) {
+      float z[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) z[u] = r0 + 16 * u < chunks ? partial[(size_t)(r0 + 16 * u) * stride + nc] : 0.f;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const float* d = dl + (size_t)min(r0 + 16 * u, chunks - 1) * C;
+#pragma unroll
+        for (int c = 0; c < OUTER_MAX; ++c) acc[c] = fmaf(z[u], d[min(c, C - 1)], acc[c]);
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < OUTER_MAX; ++c) outer_red[grp][col * OUTER_MAX + c] = acc[c];
+    __syncthreads();
+    float t = 0.f;
+#pragma unroll
+    for (int g = 0; g < 16; ++g) t += outer_red[g][threadIdx.x];
+    const int c = threadIdx.x % OUTER_MAX, m = ((int)blockIdx.x - a.first[j]) * 16 + threadIdx.x / OUTER_MAX;
+    if (c < C && m < N) a.job[j].dst[(size_t)m * C + c] = t * a.job[j].scale;
+    return;
+  }
   if (a.vec4[j]) {
     const int n = ((int)blockIdx.x - a.first[j]) * 64 + 4 * col;
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -206,7 +232,13 @@ __global__ __launch_bounds__(256) void reduce_batch_kernel(ReduceBatch a) {
   const int n = ((int)blockIdx.x - a.first[j]) * 16 + col;
   float acc = 0.f;
   if (n < N)
-    for (int c = grp; c < chunks; c += 16) acc += partial[(size_t)c * stride + n];
+    for (int c = grp; c < chunks; c += 16 * 8) {
+      float q[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) q[u] = c + 16 * u < chunks ? partial[(size_t)(c + 16 * u) * stride + n] : 0.f;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc += q[u];
+    }
   red[grp][col] = acc;
   __syncthreads();
   if (grp == 0 && n < N) {
@@ -233,7 +265,17 @@ float* ReduceQueue::space(size_t floats, bool* queued) {
 int ReduceQueue::reduce(hipStream_t s, bool queued, const float* src, int chunks, int N, long stride, float scale,
                         float* out) {
   if (!queued) return reduce_partials(s, src, chunks, N, stride, scale, out);
-  jobs.push_back(ReduceJob{src, out, chunks, N, stride, scale});
+  jobs.push_back(ReduceJob{src, out, chunks, N, stride, scale, nullptr, 0});
+  return PPLL_OK;
+}
+
+int ReduceQueue::reduce_outer(hipStream_t s, bool queued, const float* src, int rows, int N, const float* outer, int outer_n, float* out) {
+  const ReduceJob job{src, out, rows, N, N, 1.0f, outer, outer_n};
+  if (queued) { jobs.push_back(job); return PPLL_OK; }
+  ReduceBatch b{};
+  b.n = 1; b.job[0] = job; b.first[1] = (N + 15) / 16;
+  hipLaunchKernelGGL(reduce_batch_kernel, dim3(b.first[1]), dim3(256), 0, s, b);
+  PPLL_HIP(hipGetLastError());
   return PPLL_OK;
 }
 
@@ -246,7 +288,7 @@ int ReduceQueue::flush(hipStream_t s) {
       b.job[j] = jobs[j0 + j];
       b.first[j] = blocks;
       const ReduceJob& q = b.job[j];
-      b.vec4[j] = q.N >= 64 && (q.N % 4) == 0 && (q.stride % 4) == 0 && !(((uintptr_t)q.src) & 15);
+      b.vec4[j] = !q.outer && q.N >= 64 && (q.N % 4) == 0 && (q.stride % 4) == 0 && !(((uintptr_t)q.src) & 15);
       blocks += b.vec4[j] ? (q.N + 63) / 64 : (q.N + 15) / 16;
     }
     b.first[b.n] = blocks;
@@ -365,6 +407,7 @@ template <int D_> struct LnShape {
 };
 template <int LPR>
 __device__ __forceinline__ float group_sum(float v) {
+  if constexpr (LPR >= 16) return lanes_sum<LPR>(v);
 #pragma unroll
   for (int o = LPR / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
@@ -889,8 +932,140 @@ __global__ __launch_bounds__(HEAD_THREADS) void vit_head_kernel(const void* x, i
 }
 }  // namespace
 
+
+namespace {
+// The same for few classes (C <= OUTER_MAX) and D <= 64 HEAD_NV: one row per workgroup.  The kernel is one dependent chain -
+// row, LayerNorm sums, logits, softmax, gradient, LayerNorm's sums, row - so everything it reads is asked for up front, the
+// four waves share the classes and the columns where there is something to share (each holds the whole row otherwise), and
+// the batch sums are left to the reduction launch: z, dz o xhat, dz, dlogits and loss of every row go out as they are, the
+// weight gradient z^T dlogits is formed there.  18.8 us at 128 rows of width 384 with four rows per workgroup and the weight
+// gradient formed here.  The sums run over the columns in the order of the kernel above.
+constexpr int HEAD_NV = 16;
+__host__ __device__ inline size_t head_row_floats(int D, int C) { return (size_t)3 * D + C + 1; }
+template <int NV>
+__global__ __launch_bounds__(256) void head_row_kernel(const void* x, int dt, long xs, int B, int D, int C, const float* ln_g,
+                                                       const float* ln_b, float eps, const float* W, const float* bias,
+                                                       const int32_t* labels, void* dcls, float* out_z, float* out_dzx,
+                                                       float* out_dz, float* out_dl, float* out_loss, int* flag) {
+  extern __shared__ __align__(16) float sm[];
+  float* wl = sm;                               // [D][C]
+  float* dzs = wl + ((D * C + 3) & ~3);         // [D]
+  float* lr = dzs + D;                          // [C] logits
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, b = blockIdx.x;
+  const bool ln = ln_g != nullptr;
+  // the row and the LayerNorm parameters in registers, column lane + 64 i in element i
+  float xv[NV], gv[NV], bv[NV];
+  const size_t base = (size_t)b * xs;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int d = lane + 64 * i;
+    xv[i] = d < D ? ld_f(x, base + d, dt) : 0.f;
+    gv[i] = ln && d < D ? ln_g[d] : 0.f;
+    bv[i] = ln && d < D ? ln_b[d] : 0.f;
+  }
+  const int y = labels[b];
+  const float my_bias = lane < C ? bias[lane] : 0.f;
+  {
+    const int n4 = (D * C) >> 2;
+    for (int i0 = tid; i0 < n4; i0 += 8 * 256) {
+      float4 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = i0 + 256 * u < n4 ? reinterpret_cast<const float4*>(W)[i0 + 256 * u] : make_float4(0, 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) if (i0 + 256 * u < n4) reinterpret_cast<float4*>(wl)[i0 + 256 * u] = v[u];
+    }
+    for (int i = 4 * n4 + tid; i < D * C; i += 256) wl[i] = W[i];
+  }
+  float zv[NV], rs = 0.f;
+  if (ln) {
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) s += xv[i];
+    const float mu = wave_sum(s) / D;
+    float q = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) { const float c = lane + 64 * i < D ? xv[i] - mu : 0.f; q += c * c; }
+    rs = rsqrtf(wave_sum(q) / D + eps);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      xv[i] = lane + 64 * i < D ? (xv[i] - mu) * rs : 0.f;
+      zv[i] = lane + 64 * i < D ? round_to(xv[i] * gv[i] + bv[i], dt) : 0.f;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) { zv[i] = xv[i]; xv[i] = 0.f; }
+  }
+  __syncthreads();
+  float a[OUTER_MAX / 4];
+#pragma unroll
+  for (int u = 0; u < OUTER_MAX / 4; ++u) a[u] = 0.f;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int d = lane + 64 * i;
+    if (d < D) {
+#pragma unroll
+      for (int u = 0; u < OUTER_MAX / 4; ++u) if (wave + 4 * u < C) a[u] += zv[i] * wl[d * C + wave + 4 * u];
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < OUTER_MAX / 4; ++u) a[u] = wave_sum(a[u]);
+#pragma unroll
+  for (int u = 0; u < OUTER_MAX / 4; ++u) if (lane == 0 && wave + 4 * u < C) lr[wave + 4 * u] = a[u];
+  __syncthreads();
+  const float logit = lane < C ? lr[lane] + my_bias : -INFINITY;
+  const float mx = wave_max(logit);
+  const float lse = mx + logf(wave_sum(lane < C ? expf(logit - mx) : 0.f));
+  const bool ok = y >= 0 && y < C;
+  const float dl = lane < C ? (expf(logit - lse) - ((ok && lane == y) ? 1.f : 0.f)) / B : 0.f;
+  if (wave == 0) {
+    const float ly = __shfl(logit, ok ? y : 0, 64);
+    if (lane < C) out_dl[(size_t)b * C + lane] = dl;
+    if (lane == 0) { out_loss[b] = ok ? lse - ly : 0.f; if (!ok) *flag = 1; }
+  }
+  float dlc[OUTER_MAX];
+#pragma unroll
+  for (int c = 0; c < OUTER_MAX; ++c) dlc[c] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(dl), c));
+  for (int d = tid; d < D; d += 256) {
+    float v = 0.f;
+#pragma unroll
+    for (int c = 0; c < OUTER_MAX; ++c) if (c < C) v += dlc[c] * wl[d * C + c];
+    v = round_to(v, dt);
+    dzs[d] = v;
+    if (!ln) st_f(dcls, (size_t)b * D + d, v, dt);
+  }
+  __syncthreads();
+  float dz[NV], s1 = 0.f, s2 = 0.f;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int d = lane + 64 * i;
+    dz[i] = d < D ? dzs[d] : 0.f;
+    const float dyh = dz[i] * gv[i];
+    s1 += dyh; s2 += dyh * xv[i];
+  }
+  if (ln) { s1 = wave_sum(s1) / D; s2 = wave_sum(s2) / D; }
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {          // the waves share the columns to write
+    const int d = lane + 64 * i;
+    if ((i & 3) == wave && d < D) {
+      const size_t o = (size_t)b * D + d;
+      out_z[o] = zv[i];
+      if (ln) {
+        st_f(dcls, o, rs * fmaf(-xv[i], s2, fmaf(dz[i], gv[i], -s1)), dt);
+        out_dzx[o] = dz[i] * xv[i];
+        out_dz[o] = dz[i];
+      }
+    }
+  }
+}
+size_t head_row_lds(int D, int C) { return ((((size_t)D * C + 3) & ~(size_t)3) + D + C) * sizeof(float); }
+bool head_rows_ok(int D, int C, const float* W) {
+  return C <= OUTER_MAX && D <= 64 * HEAD_NV && head_row_lds(D, C) <= 64 * 1024 && !(((uintptr_t)W) & 15);
+}
+}  // namespace
+
 size_t vit_head_partial_floats(int B, int D, int C) {
-  return (size_t)((B + HEAD_ROWS - 1) / HEAD_ROWS) * ((size_t)D * C + C + 2 * D + 1);
+  const size_t few = (size_t)((B + HEAD_ROWS - 1) / HEAD_ROWS) * ((size_t)D * C + C + 2 * D + 1), rows = (size_t)B * head_row_floats(D, C);
+  return few > rows ? few : rows;
 }
 static size_t vit_head_lds(int D, int C, bool with_w) {
   return ((size_t)3 * HEAD_ROWS * D + HEAD_ROWS * C + HEAD_ROWS + C + 2 * D + (with_w ? (size_t)D * C : 0)) * sizeof(float);
@@ -901,10 +1076,32 @@ int launch_vit_head(hipStream_t s, const void* x, int dt, long xs, int B, int D,
                     const float* ln_b, float eps, const float* W, const float* bias, const int32_t* labels, void* dcls,
                     ReduceQueue& rq, float* d_ln_g, float* d_ln_b, float* dW, float* dbias, float* loss, float* loss2,
                     int* flag) {
+  bool queued;
+  float* partials = rq.space(vit_head_partial_floats(B, D, C), &queued);
+  if (head_rows_ok(D, C, W)) {
+    float *z = partials, *dzx = z + (size_t)B * D, *dz = dzx + (size_t)B * D, *dl = dz + (size_t)B * D, *ls = dl + (size_t)B * C;
+#define HEAD_LAUNCH(NV)                                                                                                        \
+  hipLaunchKernelGGL(head_row_kernel<NV>, dim3(B), dim3(256), head_row_lds(D, C), s, x, dt, xs, B, D, C, ln_g, ln_b, eps, W, bias, \
+                     labels, dcls, z, dzx, dz, dl, ls, flag)
+    if (D <= 64) HEAD_LAUNCH(1);
+    else if (D <= 192) HEAD_LAUNCH(3);
+    else if (D <= 384) HEAD_LAUNCH(6);
+    else if (D <= 768) HEAD_LAUNCH(12);
+    else HEAD_LAUNCH(16);
+#undef HEAD_LAUNCH
+    PPLL_HIP(hipGetLastError());
+    PPLL_TRY(rq.reduce_outer(s, queued, z, B, D, dl, C, dW));
+    PPLL_TRY(rq.reduce(s, queued, dl, B, C, C, 1.0f, dbias));
+    if (ln_g) {
+      PPLL_TRY(rq.reduce(s, queued, dzx, B, D, D, 1.0f, d_ln_g));
+      PPLL_TRY(rq.reduce(s, queued, dz, B, D, D, 1.0f, d_ln_b));
+    }
+    PPLL_TRY(rq.reduce(s, queued, ls, B, 1, 1, 1.0f / B, loss));
+    if (loss2) PPLL_TRY(rq.reduce(s, queued, ls, B, 1, 1, 1.0f / B, loss2));
+    return PPLL_OK;
+  }
   const int chunks = (B + HEAD_ROWS - 1) / HEAD_ROWS;
   const long P = (long)D * C + C + 2 * D + 1;
-  bool queued;
-  float* partials = rq.space((size_t)chunks * P, &queued);
   const bool with_w = vit_head_lds(D, C, true) <= 64 * 1024;
   hipLaunchKernelGGL(vit_head_kernel, dim3(chunks), dim3(HEAD_THREADS), vit_head_lds(D, C, with_w), s, x, dt, xs, B, D, C, ln_g, ln_b,
                      eps, W, bias, labels, dcls, partials, flag, (int)with_w);

@@ -334,6 +334,17 @@ def test_vit_bf16_token_counts_at_tile_edges(tokens):
     run_case(wl, steps=1)
 
 
+@pytest.mark.parametrize("batch,dim,classes", [
+    (1, 64, 2), (5, 192, 16),        # the fewest and the most classes of the row-per-workgroup head
+    (130, 128, 10), (3, 1024, 16),   # more rows than one pass of the reduction; the widest row whose head weight fits in LDS
+    (3, 1024, 17), (2, 1152, 10),    # one class, one width more: the head of four rows per workgroup
+])
+def test_vit_bf16_head_shapes(batch, dim, classes):
+    wl = synth.workload("vit_stage_act_bf16", batch=batch, tokens=3, dim=dim, heads=dim // 64, mlp_dim=64, depth=1, aux_depth=0,
+                        num_classes=classes)
+    run_case(wl, steps=1)
+
+
 @pytest.mark.parametrize("batch,tokens,dim,depth", [
     (3, 5, 64, 1),       # 15 rows: one ragged k-step of the weight gradients, 64-wide LayerNorm
     (9, 65, 192, 2),     # 585 rows: odd, tiles divided along the rows; 192-wide LayerNorm
