@@ -37,6 +37,7 @@ struct BasicBlockDims { int Ci, Co, stride, Hin, Win, Ho, Wo; };
 struct BasicBlockActs {
   void *c1, *y1, *c2, *out;
   void *d1, *d2;   // gradients at the outputs of conv1 / conv2, kept until the grouped weight-gradient launch
+  uint8_t *mask1, *mask2;   // ReLU masks of y1 and of `out` (or the block's x_out), for the fused backward; null where that does not run
   float *mean1, *rstd1, *mean2, *rstd2;
 };
 
@@ -80,7 +81,7 @@ struct Block {
   std::vector<size_t> bn_off;
   float* loss_dev = nullptr;
   int* flag_dev = nullptr;
-  float* partials = nullptr;
+  float *partials = nullptr, *partials2 = nullptr;
   size_t partial_floats = 0;
   ReduceQueue rq;                 // second stages of the gradient reductions, run in one launch before the update
   size_t arena_floats = 0;
@@ -127,6 +128,7 @@ struct Block {
   bool stem = false;                     // conv3x3 (img_c -> in_c) - BN - ReLU on the image in front of the blocks
   size_t stem_w = 0, stem_g = 0, stem_b = 0;
   void *stem_c = nullptr, *stem_y = nullptr, *shortcut = nullptr;
+  uint8_t* stem_mask = nullptr;          // as BasicBlockActs::mask1
   // bf16 path: the image padded to 16 channels and the stem filter padded likewise, so that the stem runs on the
   // 16-channel matrix-core kernels (null: the stem runs on the generic kernels)
   void *stem_xp = nullptr, *stem_wp = nullptr;

@@ -255,6 +255,7 @@ size_t Block::plan(char* base) {
     partial_floats = 0;
     if (stem) {
       stem_c = bump.take(widest * esz); stem_y = bump.take(widest * esz);
+      stem_mask = conv_bn_ok(dt, B, in_h, in_w, in_c) ? (uint8_t*)bump.take(widest / 8) : nullptr;
       stem_mean = bump.floats(in_c); stem_rstd = bump.floats(in_c);
       stem_xp = stem_wp = nullptr;
       stem_pad = dt == BF16 && cfg.img_c < 16 && in_c % 16 == 0 && in_c <= 64;
@@ -273,6 +274,8 @@ size_t Block::plan(char* base) {
       BasicBlockActs a;
       a.c1 = bump.take(act * esz); a.y1 = bump.take(act * esz); a.c2 = bump.take(act * esz); a.out = bump.take(act * esz);
       a.d1 = bump.take(act * esz); a.d2 = bump.take(act * esz);
+      const bool masks = conv_bn_ok(dt, B, d.Ho, d.Wo, d.Co);
+      a.mask1 = masks ? (uint8_t*)bump.take(act / 8) : nullptr; a.mask2 = masks ? (uint8_t*)bump.take(act / 8) : nullptr;
       a.mean1 = bump.floats(d.Co); a.rstd1 = bump.floats(d.Co); a.mean2 = bump.floats(d.Co); a.rstd2 = bump.floats(d.Co);
       rb_a.push_back(a);
       if (d.stride != 1 || d.Ci != d.Co) shortcut = bump.take(act * esz);
@@ -290,7 +293,15 @@ size_t Block::plan(char* base) {
   }
   size_t o = (size_t)colsum_partial_floats(B, C);
   if (o > partial_floats) partial_floats = o;
+  if (cfg.arch == PPLL_RESNET && dt == BF16)   // rows of sums that the fused convolutions leave
+    for (const BasicBlockDims& d : rb_d)
+      if (conv_bn_ok(dt, B, d.Ho, d.Wo, d.Co)) {
+        const size_t f = (size_t)conv_bn_stat_blocks(B, d.Ho, d.Wo, d.Co) * 2 * d.Co;
+        if (f > partial_floats) partial_floats = f;
+      }
   partials = bump.floats(partial_floats);
+  // a convolution that finishes the sums in one area leaves those of its result in the other
+  partials2 = cfg.arch == PPLL_RESNET && dt == BF16 ? bump.floats(partial_floats) : partials;
   rq.scratch = partials;
   // room for every queued reduction of a step: LayerNorm scale/shift gradients of all layers and the
   // head, position / class-token / bias gradients (a reduction that finds no room runs at once)
@@ -634,12 +645,44 @@ int Block::resnet_step(const void* x_in, const int32_t* labels, void* x_out, hip
   std::vector<const void*> block_in(n);
   std::vector<void*> block_out(n);
   const void* x = x_in;
+  // A BatchNorm whose input has just been written waits here: the next convolution applies it on the way in where it can
+  // (stride 1, equal channels, bf16), else it runs on its own.  `area` holds its sums (bn.blocks rows; 0: none yet).
+  // (x_in and x_out are the caller's: the fused kernels need them on a 16-byte boundary)
+  const bool fuse = ((uintptr_t)x_in | (uintptr_t)x_out) % 16 == 0;
+  BnInput bn{};
+  bool waiting = false;
+  int bn_rows = 0, bn_c = 0;
+  float *area = partials, *other = partials2;
+  auto wait_bn = [&](const void* in, int rows, int c, float* mean, float* rstd, int index, size_t g_off, size_t b_off,
+                     const void* res, void* y, uint8_t* mask, int ready) {
+    bn = BnInput{in, area, ready, eps, mom, mean, rstd, run_mean(index), run_var(index), params + g_off, params + b_off, res, y,
+                 fuse ? mask : nullptr};
+    bn_rows = rows; bn_c = c; waiting = true;
+  };
+  auto apply_bn = [&]() -> int {   // on its own
+    if (!waiting) return PPLL_OK;
+    waiting = false;
+    return launch_bn_train_fwd(s, bn.x, dt, bn_rows, bn_c, eps, mom, area, bn.mean, bn.rstd, bn.run_mean, bn.run_var, bn.g, bn.b,
+                               bn.res, bn.y, bn.blocks, bn.mask);
+  };
+  auto conv = [&](const void* in, const void* w, int Hi, int Wi, int Ci, int Co, int stride, void* out, int* ready) -> int {
+    *ready = 0;
+    if (fuse && stride == 1 && Ci == Co && conv_bn_ok(dt, B, Hi, Wi, Ci)) {
+      if (waiting && bn.blocks == 0) PPLL_TRY(launch_bn_sums_fwd_bf16(s, bn.x, bn_rows, bn_c, area, &bn.blocks));
+      const bool take = waiting;
+      waiting = false;
+      PPLL_TRY(launch_conv_bn_fwd(s, take ? &bn : nullptr, in, w, B, Hi, Wi, Ci, out, other, ready));
+      std::swap(area, other);
+      return PPLL_OK;
+    }
+    PPLL_TRY(apply_bn());
+    return launch_conv3x3_fwd(s, in, w, wdt(), dt, B, Hi, Wi, Ci, Co, stride, out, area, ready);
+  };
   if (stem) {
     const int rows0 = B * in_h * in_w;
     int ready = 0;   // partial rows of the BatchNorm sums that the convolution has written itself
-    PPLL_TRY(stem_conv_fwd(x_in, stem_xp, stem_wp, stem_c, s, partials, &ready));
-    PPLL_TRY(launch_bn_train_fwd(s, stem_c, dt, rows0, in_c, eps, mom, partials, stem_mean, stem_rstd, run_mean(0), run_var(0),
-                                 params + stem_g, params + stem_b, nullptr, stem_y, ready));
+    PPLL_TRY(stem_conv_fwd(x_in, stem_xp, stem_wp, stem_c, s, area, &ready));
+    wait_bn(stem_c, rows0, in_c, stem_mean, stem_rstd, 0, stem_g, stem_b, nullptr, stem_y, stem_mask, ready);
     x = stem_y;
   }
   for (int i = 0; i < n; ++i) {
@@ -650,19 +693,18 @@ int Block::resnet_step(const void* x_in, const int32_t* labels, void* x_out, hip
     block_in[i] = x;
     block_out[i] = i == n - 1 ? x_out : a.out;
     int ready = 0;
-    PPLL_TRY(launch_conv3x3_fwd(s, x, wptr(p.conv1_w), wdt(), dt, B, d.Hin, d.Win, d.Ci, d.Co, d.stride, a.c1, partials, &ready));
-    PPLL_TRY(launch_bn_train_fwd(s, a.c1, dt, rows, d.Co, eps, mom, partials, a.mean1, a.rstd1, run_mean(b1), run_var(b1),
-                                 params + p.bn1_g, params + p.bn1_b, nullptr, a.y1, ready));
-    PPLL_TRY(launch_conv3x3_fwd(s, a.y1, wptr(p.conv2_w), wdt(), dt, B, d.Ho, d.Wo, d.Co, d.Co, 1, a.c2, partials, &ready));
+    PPLL_TRY(conv(x, wptr(p.conv1_w), d.Hin, d.Win, d.Ci, d.Co, d.stride, a.c1, &ready));
+    wait_bn(a.c1, rows, d.Co, a.mean1, a.rstd1, b1, p.bn1_g, p.bn1_b, nullptr, a.y1, a.mask1, ready);
+    PPLL_TRY(conv(a.y1, wptr(p.conv2_w), d.Ho, d.Wo, d.Co, d.Co, 1, a.c2, &ready));
     const void* skip = x;
     if (d.stride != 1 || d.Ci != d.Co) {
       PPLL_TRY(launch_shortcut_fwd(s, x, dt, B, d.Hin, d.Win, d.Ci, d.Co, d.stride, shortcut));
       skip = shortcut;
     }
-    PPLL_TRY(launch_bn_train_fwd(s, a.c2, dt, rows, d.Co, eps, mom, partials, a.mean2, a.rstd2, run_mean(b2), run_var(b2),
-                                 params + p.bn2_g, params + p.bn2_b, skip, block_out[i], ready));
+    wait_bn(a.c2, rows, d.Co, a.mean2, a.rstd2, b2, p.bn2_g, p.bn2_b, skip, block_out[i], a.mask2, ready);
     x = block_out[i];
   }
+  PPLL_TRY(apply_bn());
   PPLL_TRY(mark_phase(1, s));   // module forward done
   if (after_forward) PPLL_TRY(after_forward());
   // ---- auxiliary forward
@@ -716,31 +758,57 @@ int Block::resnet_step(const void* x_in, const int32_t* labels, void* x_out, hip
     shape_jobs[k].push_back({xin, dyp, dw});
   };
   // An input-gradient convolution whose result is the output gradient of a BatchNorm also writes that BatchNorm's
-  // backward sums where it can (`ready` partial rows in `partials`, consumed by the launch_bn_bwd right behind it).
+  // backward sums where it can (`ready` rows in `area`, consumed by what handles that BatchNorm next).  Where the shapes
+  // allow, the BatchNorm's own backward runs inside the convolution in front of it.
   int ready = 0;
+  // backward of the BatchNorm (in, out) with output gradient dy into d, then the input gradient of the convolution in front
+  // of it into dst (+ the shortcut's gradient dres where dmask is set); next: the BatchNorm that dst is the output gradient of
+  auto bn_conv_bwd = [&](const void* dy, const void* y, const uint8_t* mask, const void* xin, const float* mean, const float* rstd,
+                         size_t g_off, size_t b_off, void* d, const void* w, int Hh, int Ww, int Co, const void* dres,
+                         const uint8_t* dmask, void* dst, const BnBwdSums* next) -> int {
+    if (ready == 0) PPLL_TRY(launch_bn_sums_bwd_bf16(s, dy, y, xin, B * Hh * Ww, Co, mean, rstd, area, &ready));
+    BnGrad g{dy, xin, mask, area, ready, mean, rstd, params + g_off, params + b_off, grads + g_off, grads + b_off};
+    ready = 0;
+    PPLL_TRY(launch_conv_bn_bwd(s, g, w, B, Hh, Ww, Co, d, dres, dmask, dst, next, other, &ready));
+    std::swap(area, other);
+    return PPLL_OK;
+  };
   for (int i = n - 1; i >= 0; --i) {
     const BasicBlockParams& p = rb_p[i];
     const BasicBlockDims& d = rb_d[i];
     BasicBlockActs& a = rb_a[i];
     const int rows = B * d.Ho * d.Wo;
-    PPLL_TRY(launch_bn_bwd(s, gcur, block_out[i], a.c2, dt, rows, d.Co, a.mean2, a.rstd2, params + p.bn2_g, partials,
-                           grads + p.bn2_g, grads + p.bn2_b, a.d2, ready));
-    ready = 0;
+    const bool fused = fuse && conv_bn_ok(dt, B, d.Ho, d.Wo, d.Co), identity = d.stride == 1 && d.Ci == d.Co;
     defer(a.y1, a.d2, grads + p.conv2_w, d.Ho, d.Wo, d.Co, d.Co, 1);
-    const BnBwdSums bn1{a.y1, a.c1, a.mean1, a.rstd1, partials};
-    PPLL_TRY(launch_conv3x3_dgrad(s, a.d2, wptr(p.conv2_w), wdt(), dt, B, d.Ho, d.Wo, d.Co, d.Co, 1, nullptr, nullptr, r_t1, &bn1,
-                                  &ready));
-    PPLL_TRY(launch_bn_bwd(s, r_t1, a.y1, a.c1, dt, rows, d.Co, a.mean1, a.rstd1, params + p.bn1_g, partials,
+    if (fused) {
+      const BnBwdSums bn1{a.y1, a.c1, a.mean1, a.rstd1, area, a.mask1};
+      PPLL_TRY(bn_conv_bwd(gcur, block_out[i], a.mask2, a.c2, a.mean2, a.rstd2, p.bn2_g, p.bn2_b, a.d2, wptr(p.conv2_w), d.Ho, d.Wo,
+                           d.Co, nullptr, nullptr, r_t1, &bn1));
+    } else {
+      PPLL_TRY(launch_bn_bwd(s, gcur, block_out[i], a.c2, dt, rows, d.Co, a.mean2, a.rstd2, params + p.bn2_g, area,
+                             grads + p.bn2_g, grads + p.bn2_b, a.d2, ready));
+      ready = 0;
+      const BnBwdSums bn1{a.y1, a.c1, a.mean1, a.rstd1, area, nullptr};
+      PPLL_TRY(launch_conv3x3_dgrad(s, a.d2, wptr(p.conv2_w), wdt(), dt, B, d.Ho, d.Wo, d.Co, d.Co, 1, nullptr, nullptr, r_t1, &bn1,
+                                    &ready));
+    }
+    defer(block_in[i], a.d1, grads + p.conv1_w, d.Hin, d.Win, d.Ci, d.Co, d.stride);
+    // the BatchNorm in front of conv1: the second one of the block before (output block_out[i - 1]) or the stem's
+    BnBwdSums front{};
+    if (i > 0) front = BnBwdSums{block_out[i - 1], rb_a[i - 1].c2, rb_a[i - 1].mean2, rb_a[i - 1].rstd2, area, rb_a[i - 1].mask2};
+    else if (stem) front = BnBwdSums{stem_y, stem_c, stem_mean, stem_rstd, area, stem_mask};
+    if (fused && identity && (i > 0 || stem)) {   // identity shortcut folded into the input gradient
+      PPLL_TRY(bn_conv_bwd(r_t1, a.y1, a.mask1, a.c1, a.mean1, a.rstd1, p.bn1_g, p.bn1_b, a.d1, wptr(p.conv1_w), d.Hin, d.Win, d.Ci,
+                           gcur, a.mask2, gcur, &front));
+      continue;
+    }
+    PPLL_TRY(launch_bn_bwd(s, r_t1, a.y1, a.c1, dt, rows, d.Co, a.mean1, a.rstd1, params + p.bn1_g, area,
                            grads + p.bn1_g, grads + p.bn1_b, a.d1, ready));
     ready = 0;
-    defer(block_in[i], a.d1, grads + p.conv1_w, d.Hin, d.Win, d.Ci, d.Co, d.stride);
     if (i == 0 && !stem) break;   // the block input is the detached x_{j-1}
-    if (d.stride == 1 && d.Ci == d.Co) {   // identity shortcut folded into the input gradient
-      // the result is the output gradient of the second BatchNorm of the block before
-      BnBwdSums bn2{};
-      if (i > 0) bn2 = BnBwdSums{block_out[i - 1], rb_a[i - 1].c2, rb_a[i - 1].mean2, rb_a[i - 1].rstd2, partials};
+    if (identity) {
       PPLL_TRY(launch_conv3x3_dgrad(s, a.d1, wptr(p.conv1_w), wdt(), dt, B, d.Hin, d.Win, d.Ci, d.Co, 1, gcur, block_out[i], gcur,
-                                    i > 0 ? &bn2 : nullptr, &ready));
+                                    i > 0 ? &front : nullptr, &ready));
     } else {
       PPLL_TRY(launch_conv3x3_dgrad(s, a.d1, wptr(p.conv1_w), wdt(), dt, B, d.Hin, d.Win, d.Ci, d.Co, d.stride, nullptr, nullptr,
                                     gnext));
@@ -753,8 +821,8 @@ int Block::resnet_step(const void* x_in, const int32_t* labels, void* x_out, hip
                                         shapes[k].Ci, shapes[k].Co, shapes[k].stride, rq));
   if (stem) {
     const int rows0 = B * in_h * in_w;
-    PPLL_TRY(launch_bn_bwd(s, gcur, stem_y, stem_c, dt, rows0, in_c, stem_mean, stem_rstd, params + stem_g, partials,
-                           grads + stem_g, grads + stem_b, r_t1));
+    PPLL_TRY(launch_bn_bwd(s, gcur, stem_y, stem_c, dt, rows0, in_c, stem_mean, stem_rstd, params + stem_g, area,
+                           grads + stem_g, grads + stem_b, r_t1, ready));
     if (stem_pad)   // the padded image is still in place from the forward pass
       PPLL_TRY(launch_conv3x3_wgrad(s, stem_xp, r_t1, dt, B, in_h, in_w, 16, in_c, 1, rq, grads + stem_w, cfg.img_c));
     else

@@ -271,12 +271,42 @@ int launch_conv3x3_fwd(hipStream_t s, const void* x, const void* w, int wdt, int
 // dx = dgrad(dy, w) (+ dres * (ymask > 0) when dres != null)
 // The BatchNorm whose output gradient a convolution's input gradient dx is: output y (ReLU mask), input x, saved
 // statistics, and room for the partial sums of its backward pass (bn_partial_floats of its shape).
-struct BnBwdSums { const void* y; const void* x; const float* mean; const float* rstd; float* partials; };
+// mask: what launch_conv_bn_bwd takes in place of y
+struct BnBwdSums {
+  const void* y; const void* x; const float* mean; const float* rstd; float* partials;
+  const uint8_t* mask;
+};
 // bn / stat_blocks (nullable): on return *stat_blocks is the number of partial rows of that BatchNorm's two backward
 // sums that the convolution wrote to bn->partials itself (0: none, launch_bn_bwd has to make its own pass)
 int launch_conv3x3_dgrad(hipStream_t s, const void* dy, const void* w, int wdt, int dt, int B, int H, int W, int Ci,
                          int Co, int stride, const void* dres, const void* ymask, void* dx, const BnBwdSums* bn = nullptr,
                          int* stat_blocks = nullptr);
+// Convolution (stride 1, C -> C) that applies the BatchNorm in front of it on the way in (k_resnet_fused.hip).
+// The BatchNorm: input x, `blocks` partial rows of its sums, where statistics go, parameters, residual, output y.
+struct BnInput {
+  const void* x; float* partials; int blocks;
+  float eps, momentum; float *mean, *rstd, *run_mean, *run_var;
+  const float *g, *b; const void* res; void* y; uint8_t* mask;   // mask (nullable): receives the ReLU mask of y, a bit an element
+};
+// Backward: gradient dy at the BatchNorm's output, the output's ReLU mask, partial rows of its two sums, saved statistics,
+// where dgamma and dbeta go.
+struct BnGrad {
+  const void *dy, *x; const uint8_t* mask; float* partials; int blocks;
+  const float *mean, *rstd, *g, *b; float *dg, *db;
+};
+bool conv_bn_ok(int dt, int B, int H, int W, int C);
+int conv_bn_stat_blocks(int B, int H, int W, int C);   // partial rows it leaves
+// dst = conv(y) with y = relu(bn(bn->x) + bn->res), stored in bn->y; without bn, dst = conv(x).  stat: sums of dst.
+int launch_conv_bn_fwd(hipStream_t s, const BnInput* bn, const void* x, const void* w, int B, int H, int W, int C, void* dst,
+                       float* stat, int* stat_blocks);
+// d = gradient at the BatchNorm's input, dst = conv^T(d) (+ dres where dmask is set); next (nullable): the BatchNorm whose
+// output gradient dst is, its sums go to stat
+int launch_conv_bn_bwd(hipStream_t s, const BnGrad& bn, const void* w, int B, int H, int W, int C, void* d, const void* dres,
+                       const uint8_t* dmask, void* dst, const BnBwdSums* next, float* stat, int* stat_blocks);
+// the sums alone ([*blocks][2][C] partial rows, at most 256)
+int launch_bn_sums_fwd_bf16(hipStream_t s, const void* x, int rows, int C, float* partials, int* blocks);
+int launch_bn_sums_bwd_bf16(hipStream_t s, const void* dy, const void* y, const void* x, int rows, int C, const float* mean,
+                            const float* rstd, float* partials, int* blocks);
 // dw [9][ci_keep][Co]: the gradient for the first ci_keep input channels (all of them by default; fewer when
 // the caller padded x with zero channels)
 int launch_conv3x3_wgrad(hipStream_t s, const void* x, const void* dy, int dt, int B, int H, int W, int Ci,
@@ -305,9 +335,10 @@ int launch_bn_stats(hipStream_t s, const void* x, int dt, int rows, int C, float
                     float* partials, float* mean, float* rstd, float* run_mean, float* run_var);
 // statistics of x, running-statistics update and y = relu(bn(x) (+ res)): the BatchNorm of a training step
 // ready_blocks: rows of `partials` the producing convolution has already filled (see launch_conv3x3_fwd), else 0
+// mask (nullable, bf16 only): receives the ReLU mask of y, one bit an element
 int launch_bn_train_fwd(hipStream_t s, const void* x, int dt, int rows, int C, float eps, float momentum, float* partials,
                         float* mean, float* rstd, float* run_mean, float* run_var, const float* g, const float* b,
-                        const void* res, void* y, int ready_blocks = 0);
+                        const void* res, void* y, int ready_blocks = 0, uint8_t* mask = nullptr);
 // y = relu(bn(x) (+ res))
 int launch_bn_running_stats(hipStream_t s, const float* run_mean, const float* run_var, int C, float eps, float* mean,
                             float* rstd);
@@ -348,9 +379,9 @@ int launch_bn_stats_bf16(hipStream_t s, const void* x, int rows, int C, float ep
                          float* mean, float* rstd, float* run_mean, float* run_var);
 int launch_bn_train_fwd_bf16(hipStream_t s, const void* x, int rows, int C, float eps, float momentum, float* partials,
                              float* mean, float* rstd, float* run_mean, float* run_var, const float* g, const float* b,
-                             const void* res, void* y, int ready_blocks = 0);
+                             const void* res, void* y, int ready_blocks = 0, uint8_t* mask = nullptr);
 int launch_bn_apply_bf16(hipStream_t s, const void* x, int rows, int C, const float* mean, const float* rstd,
-                         const float* g, const float* b, const void* res, void* y);
+                         const float* g, const float* b, const void* res, void* y, uint8_t* mask = nullptr);
 int launch_bn_bwd_bf16(hipStream_t s, const void* dy, const void* y, const void* x, int rows, int C, const float* mean,
                        const float* rstd, const float* g, float* partials, float* dg, float* db, void* dx, int ready_blocks = 0);
 int launch_gap_fwd(hipStream_t s, const void* x, int dt, int B, int HW, int C, void* pooled);

@@ -16,36 +16,11 @@
 //    or, on small tensors, by every workgroup of the kernel that applies them (a
 //    last-arrival scheme in one launch was slower: device-scope fences cost more).
 //  * the elementwise pieces: shortcut of a downsampling block, global average pooling.
-#include "common.h"
+#include "resnet_bf16.h"
 
 namespace ppll {
 
 namespace {
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-
-__device__ __forceinline__ float lo_bf(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float hi_bf(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
-__device__ __forceinline__ uint32_t pack2(float a, float b) { return f32x2_to_bf16x2(a, b); }
-__device__ __forceinline__ int out_dim(int in, int stride) { return (in - 1) / stride + 1; }
-
-// Raw buffer access: a load whose byte offset lies beyond the buffer returns 0, so a tap outside the image needs
-// no branch, only the offset CONV_OOB (buffers here stay below 2^30 bytes, checked by the launcher).
-typedef __attribute__((ext_vector_type(4))) uint32_t conv_u32x4;
-constexpr int CONV_OOB = 0x7fffffff;
-__device__ __forceinline__ uint4 conv_buf_load16(__amdgpu_buffer_rsrc_t r, int off) {
-  const conv_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
-  return make_uint4(v.x, v.y, v.z, v.w);
-}
-
-// Transposing LDS read of 16-bit elements: lane r of a 16-lane group hands in the address of 4 elements and receives
-// element r % 4 from the addresses of lanes r / 4, r / 4 + 4, r / 4 + 8, r / 4 + 12 of its group.
-typedef __attribute__((ext_vector_type(4))) short conv_s16x4;
-__device__ __forceinline__ uint2 conv_lds_read_tr(const char* p) {
-  const conv_s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) conv_s16x4*)p);
-  return __builtin_bit_cast(uint2, v);
-}
-
 struct ConvArgs {
   const uint16_t* src;     // forward: x [B,H,W,Ci]; input gradient: dy [B,Ho,Wo,Co]
   const uint16_t* w;       // [9][Ci][Co]
@@ -60,35 +35,6 @@ struct ConvArgs {
   const uint16_t* bn_y; const uint16_t* bn_x; const float* bn_mean; const float* bn_rstd;
 };
 
-// One halving step of a butterfly sum over lanes `step` apart: of the N values a lane holds, it keeps one half
-// (the upper one if `up`), hands the other to its partner and adds what the partner hands over.
-template <int N>
-__device__ __forceinline__ void butterfly_halve(float* v, bool up, int step) {
-#pragma unroll
-  for (int i = 0; i < N / 2; ++i) {
-    const float send = up ? v[i] : v[i + N / 2], keep = up ? v[i + N / 2] : v[i];
-    v[i] = keep + __shfl_xor(send, step, 64);
-  }
-}
-// Sums NV (16 or 32) per-lane values over the 32 lanes of a half-wave in a fixed order: afterwards v[0] of lane li holds
-// the total of value index li >> 1 (NV = 16) or li (NV = 32).
-template <int NV>
-__device__ __forceinline__ void halfwave_sums(float (&v)[NV], int li) {
-  static_assert(NV == 16 || NV == 32, "16 or 32 values per lane");
-  if (NV == 32) {
-    butterfly_halve<32>(v, (li & 16) != 0, 16);
-    butterfly_halve<16>(v, (li & 8) != 0, 8);
-    butterfly_halve<8>(v, (li & 4) != 0, 4);
-    butterfly_halve<4>(v, (li & 2) != 0, 2);
-    butterfly_halve<2>(v, (li & 1) != 0, 1);
-  } else {
-    butterfly_halve<16>(v, (li & 16) != 0, 16);
-    butterfly_halve<8>(v, (li & 8) != 0, 8);
-    butterfly_halve<4>(v, (li & 4) != 0, 4);
-    butterfly_halve<2>(v, (li & 2) != 0, 2);
-    v[0] += __shfl_xor(v[0], 1, 64);
-  }
-}
 // the forward convolution sums its outputs for the BatchNorm behind it up to this many workgroups; the input gradient
 // the backward sums of the BatchNorm before it up to fewer (at 512, 1024 x 8 x 8 x 64, it measured 5 % of the step slower)
 constexpr long CONV_STAT_MAX_BLOCKS = 512, CONV_BWD_STAT_MAX_BLOCKS = 256;
@@ -464,65 +410,6 @@ __global__ __launch_bounds__(256) void conv3x3_wgrad_bf16_kernel(const uint16_t*
 }
 
 // ---------------------------------------------------------------- BatchNorm
-// Per-channel sums over rows with 8 channels per thread.  KIND 0: (sum x, sum x^2) -> mean, rstd,
-// running stats.  KIND 1: (sum dyh, sum dyh*xhat), dyh = dy*(y>0) -> dbeta, dgamma.
-struct BnSumArgs {
-  const uint16_t* x; const uint16_t* dy; const uint16_t* y;
-  int rows, C;
-  const float* mean; const float* rstd;        // KIND 1 inputs
-  float* partial;                              // [blocks][2][C]
-  float eps, momentum;
-  float* out0; float* out1;                    // KIND 0: mean, rstd; KIND 1: dbeta, dgamma
-  float* run_mean; float* run_var;
-};
-
-// Adds the workgroup partials [nblocks][2][C] in workgroup order and finishes mean / rstd / running
-// statistics (KIND 0) or dbeta / dgamma (KIND 1).  One workgroup of NTHR threads.
-// l0 / l1 (LDS, may be null) also receive the two results per channel; `global` says whether this
-// workgroup writes them (and the running statistics) to memory.
-template <int KIND, int NTHR>
-__device__ __forceinline__ void bn_finish(const BnSumArgs& p, unsigned nblocks, float* red, float* l0, float* l1, bool global) {
-  const int tid = threadIdx.x;
-  // 2C values, four per thread (one 16-byte load per partial row); NTHR/(2C/4) thread groups take the workgroup
-  // partials round-robin, eight loads in flight each, then one thread per value adds the groups in order
-  // (at most 32 groups: the last stage adds them one after the other)
-  const int nv = 2 * p.C, nq = nv / 4, parts = NTHR / nq < 32 ? NTHR / nq : 32;
-  if (tid < nq * parts) {
-    const int v4 = tid % nq, part = tid / nq;
-    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-    constexpr int U = 16;                                        // partial rows in flight per thread
-    for (unsigned bk = part; bk < nblocks; bk += U * parts) {   // summed in workgroup order
-      float4 q[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const unsigned bu = bk + u * parts;
-        q[u] = bu < nblocks ? *reinterpret_cast<const float4*>(p.partial + (size_t)bu * nv + 4 * v4) : make_float4(0.f, 0.f, 0.f, 0.f);
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) { t.x += q[u].x; t.y += q[u].y; t.z += q[u].z; t.w += q[u].w; }
-    }
-    *reinterpret_cast<float4*>(red + part * nv + 4 * v4) = t;
-  }
-  __syncthreads();
-  if (tid < p.C) {
-    float s0 = 0.f, s1 = 0.f;
-    for (int part = 0; part < parts; ++part) { s0 += red[part * nv + tid]; s1 += red[part * nv + p.C + tid]; }
-    float v0 = s0, v1 = s1;
-    if (KIND == 0) {
-      const float n = (float)p.rows, m = s0 / n;
-      const float var = fmaxf(s1 / n - m * m, 0.f);
-      v0 = m;
-      v1 = 1.0f / sqrtf(var + p.eps);
-      if (global) {
-        p.run_mean[tid] = (1.f - p.momentum) * p.run_mean[tid] + p.momentum * m;
-        p.run_var[tid] = (1.f - p.momentum) * p.run_var[tid] + p.momentum * var * (n / (n - 1.f));
-      }
-    }
-    if (global) { p.out0[tid] = v0; p.out1[tid] = v1; }
-    if (l0) { l0[tid] = v0; l1[tid] = v1; }
-  }
-}
-
 template <int KIND>
 __global__ __launch_bounds__(256) void bn_sums_kernel(BnSumArgs p) {
   __shared__ float red[256][17];
@@ -601,7 +488,7 @@ __global__ __launch_bounds__(1024) void bn_finish_kernel(BnSumArgs p, unsigned n
 // y = relu(bn(x) (+ res)), 8 channels per thread
 __global__ __launch_bounds__(256) void bn_apply_bf16_kernel(const uint16_t* x, size_t chunks, int C, const float* mean,
                                                             const float* rstd, const float* g, const float* b,
-                                                            const uint16_t* res, uint16_t* y) {
+                                                            const uint16_t* res, uint16_t* y, uint8_t* mask) {
   const uint32_t i32 = blockIdx.x * 256 + threadIdx.x;     // fewer than 2^32 chunks (checked by the launcher)
   if (i32 >= chunks) return;
   const size_t i = i32;
@@ -615,11 +502,13 @@ __global__ __launch_bounds__(256) void bn_apply_bf16_kernel(const uint16_t* x, s
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int c = c0 + 2 * j;
-    float u = (lo_bf(xw[j]) - mean[c]) * rstd[c] * g[c] + b[c] + lo_bf(rw[j]);
-    float v = (hi_bf(xw[j]) - mean[c + 1]) * rstd[c + 1] * g[c + 1] + b[c + 1] + hi_bf(rw[j]);
+    const float u = bn_value(lo_bf(xw[j]), mean[c], rstd[c] * g[c], b[c]) + lo_bf(rw[j]);
+    const float v = bn_value(hi_bf(xw[j]), mean[c + 1], rstd[c + 1] * g[c + 1], b[c + 1]) + hi_bf(rw[j]);
     o[j] = pack2(fmaxf(u, 0.f), fmaxf(v, 0.f));
   }
-  *reinterpret_cast<uint4*>(y + i * 8) = make_uint4(o[0], o[1], o[2], o[3]);
+  const uint4 ov = make_uint4(o[0], o[1], o[2], o[3]);
+  *reinterpret_cast<uint4*>(y + i * 8) = ov;
+  if (mask) mask[i] = relu_mask(ov);
 }
 
 // dx = (g rstd / N) (N dyh - dbeta - xhat dgamma)
@@ -658,7 +547,7 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_bf16_kernel(const uint16_t* 
 // Small tensors: the apply kernels add up the partial sums themselves (every workgroup, in the same order;
 // workgroup 0 writes the results to memory), which saves the finishing launch.
 __global__ __launch_bounds__(256) void bn_apply_fused_kernel(BnSumArgs p, unsigned nblocks, size_t chunks, const float* g,
-                                                             const float* b, const uint16_t* res, uint16_t* y) {
+                                                             const float* b, const uint16_t* res, uint16_t* y, uint8_t* mask) {
   __shared__ __align__(16) float red[1024];
   __shared__ float s_mean[128], s_rstd[128];
   bn_finish<0, 256>(p, nblocks, red, s_mean, s_rstd, blockIdx.x == 0);
@@ -676,11 +565,13 @@ __global__ __launch_bounds__(256) void bn_apply_fused_kernel(BnSumArgs p, unsign
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int c = c0 + 2 * j;
-    float u = (lo_bf(xw[j]) - s_mean[c]) * s_rstd[c] * g[c] + b[c] + lo_bf(rw[j]);
-    float v = (hi_bf(xw[j]) - s_mean[c + 1]) * s_rstd[c + 1] * g[c + 1] + b[c + 1] + hi_bf(rw[j]);
+    const float u = bn_value(lo_bf(xw[j]), s_mean[c], s_rstd[c] * g[c], b[c]) + lo_bf(rw[j]);
+    const float v = bn_value(hi_bf(xw[j]), s_mean[c + 1], s_rstd[c + 1] * g[c + 1], b[c + 1]) + hi_bf(rw[j]);
     o[j] = pack2(fmaxf(u, 0.f), fmaxf(v, 0.f));
   }
-  *reinterpret_cast<uint4*>(y + i * 8) = make_uint4(o[0], o[1], o[2], o[3]);
+  const uint4 ov = make_uint4(o[0], o[1], o[2], o[3]);
+  *reinterpret_cast<uint4*>(y + i * 8) = ov;
+  if (mask) mask[i] = relu_mask(ov);
 }
 __global__ __launch_bounds__(256) void bn_bwd_apply_fused_kernel(BnSumArgs p, unsigned nblocks, size_t chunks, const float* g,
                                                                  uint16_t* dx) {
@@ -1330,7 +1221,7 @@ int launch_bn_stats_bf16(hipStream_t s, const void* x, int rows, int C, float ep
 // ready_blocks > 0: `partials` already holds that many rows of sums, written by the convolution that produced x
 int launch_bn_train_fwd_bf16(hipStream_t s, const void* x, int rows, int C, float eps, float momentum, float* partials,
                              float* mean, float* rstd, float* run_mean, float* run_var, const float* g, const float* b,
-                             const void* res, void* y, int ready_blocks) {
+                             const void* res, void* y, int ready_blocks, uint8_t* mask) {
   BnSumArgs p{};
   p.x = (const uint16_t*)x; p.rows = rows; p.C = C; p.partial = partials; p.eps = eps;
   p.momentum = momentum; p.out0 = mean; p.out1 = rstd; p.run_mean = run_mean; p.run_var = run_var;
@@ -1344,20 +1235,20 @@ int launch_bn_train_fwd_bf16(hipStream_t s, const void* x, int rows, int C, floa
     } else {
       PPLL_TRY(bn_sums_launch<0>(s, p, blocks, true));
     }
-    return launch_bn_apply_bf16(s, x, rows, C, mean, rstd, g, b, res, y);
+    return launch_bn_apply_bf16(s, x, rows, C, mean, rstd, g, b, res, y, mask);
   }
   if (ready_blocks <= 0) PPLL_TRY(bn_sums_launch<0>(s, p, blocks, false));
   hipLaunchKernelGGL(bn_apply_fused_kernel, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, s, p, (unsigned)blocks, chunks,
-                     g, b, (const uint16_t*)res, (uint16_t*)y);
+                     g, b, (const uint16_t*)res, (uint16_t*)y, mask);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;
 }
 
 int launch_bn_apply_bf16(hipStream_t s, const void* x, int rows, int C, const float* mean, const float* rstd,
-                         const float* g, const float* b, const void* res, void* y) {
+                         const float* g, const float* b, const void* res, void* y, uint8_t* mask) {
   const size_t chunks = (size_t)rows * C / 8;
   hipLaunchKernelGGL(bn_apply_bf16_kernel, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, s, (const uint16_t*)x,
-                     chunks, C, mean, rstd, g, b, (const uint16_t*)res, (uint16_t*)y);
+                     chunks, C, mean, rstd, g, b, (const uint16_t*)res, (uint16_t*)y, mask);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;
 }
@@ -1388,6 +1279,21 @@ int launch_bn_bwd_bf16(hipStream_t s, const void* dy, const void* y, const void*
                      (uint16_t*)dx);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;
+}
+
+int launch_bn_sums_fwd_bf16(hipStream_t s, const void* x, int rows, int C, float* partials, int* blocks) {
+  BnSumArgs p{};
+  p.x = (const uint16_t*)x; p.rows = rows; p.C = C; p.partial = partials;
+  *blocks = bn_blocks(rows, C);
+  return bn_sums_launch<0>(s, p, *blocks, false);
+}
+int launch_bn_sums_bwd_bf16(hipStream_t s, const void* dy, const void* y, const void* x, int rows, int C, const float* mean,
+                            const float* rstd, float* partials, int* blocks) {
+  BnSumArgs p{};
+  p.x = (const uint16_t*)x; p.dy = (const uint16_t*)dy; p.y = (const uint16_t*)y; p.rows = rows; p.C = C;
+  p.mean = mean; p.rstd = rstd; p.partial = partials;
+  *blocks = bn_blocks(rows, C);
+  return bn_sums_launch<1>(s, p, *blocks, false);
 }
 
 }  // namespace ppll

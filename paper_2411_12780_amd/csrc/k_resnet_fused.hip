@@ -1,0 +1,456 @@
+// 3x3 convolution, stride 1, C -> C channels (16, 32 or 64), with the BatchNorm in front of it applied on the way in:
+//  forward: y = relu(bn(x) (+ residual)) is formed once per pixel, stored (the backward pass and the shortcut read it) and
+//    laid in LDS with a one-pixel border, the convolution reads it there and leaves the sums that the BatchNorm behind it
+//    needs of the stored outputs;
+//  backward: the input gradient d of the BatchNorm behind the convolution (from dy, the ReLU mask and the two finished sums)
+//    is formed once per pixel, stored (the weight gradient reads it) and laid in LDS, the transposed convolution reads it
+//    there, adds the shortcut's gradient and leaves the backward sums of the BatchNorm in front.
+//
+// What bounds these layers is the number of times a feature map crosses the memory (large maps) and the number of dependent
+// launches (small ones).  A BatchNorm and its convolution, microseconds on an MI355X, as separate kernels (sums, finish,
+// apply, convolution gathering its nine taps from memory) and here:
+//                        1024 x 32 x 32 x 16    848 x 8 x 8 x 64    128 x 16 x 16 x 32
+//   forward                    51 -> 29.5           29.5 -> 16          11.5 -> 7.1
+//   backward                   76 -> 62             36 -> 25            13.6 -> 8.6
+// (at the first of them the maps alone take 20 - 27 and 34 - 41 us at a copy's rate).  A tile of 256 (128) pixels is loaded
+// with 16-byte loads while the tile before it is multiplied, pixels lie 2 C + 16 bytes apart in LDS (16 lanes reading 16
+// bytes of neighbouring pixels hit every bank once), a workgroup keeps its filter for all its tiles.  One workgroup of eight
+// waves per compute unit, two with 16 channels and of four waves: few enough partial sums for every workgroup of the next
+// kernel to add them up itself.  ReLU masks travel as one bit an element.  Partial sums, parameters, first tile and filter are
+// asked for together: waiting for them in turn, a small forward launch took 10.8 instead of 7.1 us.
+#include <atomic>
+#include "resnet_bf16.h"
+
+namespace ppll {
+
+namespace {
+struct ConvBnArgs {
+  const uint16_t* x;      // BatchNorm input [B,H,W,C] (forward with bn = 0: the convolution's input as it is)
+  const uint16_t* aux;    // forward: residual (or null); backward: dy, the gradient at the BatchNorm's output
+  const uint8_t* mask;    // backward: ReLU mask of the BatchNorm's output
+  uint16_t* mid;          // forward: y out; backward: d out
+  uint8_t* mask_out;      // forward: ReLU mask of y (or null), bit e of byte i: element 8 i + e is positive
+  const uint16_t* w;      // [9][C][C]
+  uint16_t* dst;          // the convolution's result
+  float* stat;            // [workgroups][2][C] sums for the next BatchNorm (backward: may be null)
+  const uint16_t* dres; const uint8_t* dmask;    // backward: dst += dres where the mask is set
+  // backward: the BatchNorm that dst is the output gradient of
+  const uint8_t* nmask; const uint16_t* nx; const float *nmean, *nrstd;
+  BnSumArgs sums; unsigned nblocks;              // partial sums of the BatchNorm in front, finished by every workgroup
+  const float *g, *b;
+  int bn;                 // forward: 0 = the input is taken as it is
+  int H, wl;              // rows of an image, log2 of the pixels of a row
+  int rows;               // B * H
+  int sr, srl, seg;       // a tile: seg stretches of sr rows (log2 in srl), each inside one image
+  int inv;                // 65536 / (sr + 2), rounded up
+  int tiles;
+  uint32_t bytes;         // of a [B,H,W,C] tensor
+};
+
+template <int C, bool BWD> constexpr int filter_bytes() {
+  return BWD ? (C + 31) / 32 * 32 * (18 * C + 16) : 9 * C * ((C + 31) / 32 * 64);
+}
+constexpr int pixel_pitch(int C) { return 2 * C + 16; }
+
+template <int C, int WAVES, bool BWD>
+__global__ __launch_bounds__(64 * WAVES, C == 16 ? 4 : 1) void conv_bn_kernel(ConvBnArgs p) {
+  constexpr int TH = 64 * WAVES, NT = (C + 31) / 32, K16 = C / 16, CG = C / 8, PITCH = pixel_pitch(C);
+  constexpr int PB = (C + 31) / 32 * 64, RSW = 18 * C + 16, FILTER = filter_bytes<C, BWD>();
+  // staged pieces per thread: C/16 x (sr + 2) / sr; sr is 4 or more, with eight waves 8 or more
+  constexpr int NIT = WAVES == 4 ? (3 * K16 + 1) / 2 : (5 * K16 + 3) / 4;
+  constexpr int PSTEP = TH / CG;                       // pixels between a thread's pieces
+  constexpr int NV = NT * 16, NQ = C < 32 ? 2 : 4;     // 16 channels: half a tile
+  constexpr bool FOLD = NV == 32;                      // output sums folded over the lanes tile by tile (64 registers less)
+  extern __shared__ __align__(16) char lds[];
+  __shared__ __align__(16) float red[2048];            // partial sums being added up; output sums of the waves
+  __shared__ __align__(16) float s0[C], s1[C], nbn[2][C];
+  char* wl = lds;
+  char* xt = lds + FILTER;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 31, hh = lane >> 5;
+  const int W = 1 << p.wl, WP = W + 2, srp = p.sr + 2;
+  const int cg = tid % CG, pi0 = tid / CG, npx = p.seg * srp * W;
+  const bool bn = BWD || p.bn;
+
+  // Everything a workgroup waits for at its start is asked for at once, in the order in which it is needed.
+  // (1) the partial sums: 2 C values, four per thread; groups of threads take the rows round-robin
+  constexpr int NQ4 = C / 2, PARTS = TH / NQ4 < 32 ? TH / NQ4 : 32, U = C == 32 ? 16 : C == 16 ? 4 : 8;
+  const int v4 = tid % NQ4, part = tid / NQ4;
+  float4 ps[U];
+  if (bn && part < PARTS) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const unsigned bu = part + u * PARTS;
+      ps[u] = bu < p.nblocks ? *reinterpret_cast<const float4*>(p.sums.partial + (size_t)bu * 2 * C + 4 * v4) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  }
+  // (2) the BatchNorm's parameters for this thread's eight channels
+  float pg[8], pb[8], mean[8], prs[8];
+  if (bn) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      pg[j] = p.g[8 * cg + j];
+      if (!BWD) pb[j] = p.b[8 * cg + j];
+      if (BWD) { mean[j] = p.sums.mean[8 * cg + j]; prs[j] = p.sums.rstd[8 * cg + j]; }
+    }
+  }
+  // (3) the first tile
+  const __amdgpu_buffer_rsrc_t rsx = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.x), 0, (int)p.bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsa = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p.aux), 0, p.aux ? (int)p.bytes : 0, 0x00020000);
+  const __amdgpu_buffer_rsrc_t rsm = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.mask), 0, (int)(p.bytes >> 4), 0x00020000);
+  uint4 rx[NIT], ra[NIT];
+  uint32_t rm[BWD ? NIT : 1];
+  // piece `it` of this thread in a tile: its byte offset (out of range: nothing to load), place in LDS, and whether it lies in
+  // the tile proper (not in the border)
+  auto locate = [&](int tile, int it, int& off, int& place, bool& core) {
+    const int pi = pi0 + it * PSTEP, prow = pi >> p.wl, col = pi & (W - 1);
+    const int sg = p.seg > 1 ? (prow * p.inv) >> 16 : 0, lr = prow - sg * srp;
+    const int row0 = tile * (p.sr * p.seg) + sg * p.sr, grow = row0 + lr - 1;
+    const int yy = (p.seg > 1 ? 0 : row0 & (p.H - 1)) + lr - 1;
+    const bool in = pi < npx && (unsigned)yy < (unsigned)p.H && grow < p.rows;
+    off = in ? (((grow << p.wl) + col) * C + 8 * cg) * 2 : CONV_OOB;
+    place = pi < npx ? (prow * WP + col + 1) * PITCH + 16 * cg : -1;
+    core = in && lr >= 1 && lr <= p.sr;
+  };
+  auto load = [&](int tile) {
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+      int off, place;
+      bool core;
+      locate(tile, it, off, place, core);
+      rx[it] = conv_buf_load16(rsx, off);
+      ra[it] = conv_buf_load16(rsa, off);
+      if (BWD) rm[it] = __builtin_amdgcn_raw_buffer_load_b8(rsm, off == CONV_OOB ? CONV_OOB : off >> 4, 0, 0);
+    }
+  };
+  load(blockIdx.x);
+  // (4) the filter
+  constexpr int NVEC = 9 * C * C / 8, FV = (NVEC + TH - 1) / TH;
+  constexpr int FB = FV < 6 ? FV : (FV + 1) / 2;       // 16-byte pieces in flight per thread
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  u32x4 wv[FB];
+  auto filter_load = [&](int f0) {
+#pragma unroll
+    for (int u = 0; u < FB; ++u) wv[u] = *reinterpret_cast<const u32x4*>(p.w + (size_t)min(tid + TH * (f0 + u), NVEC - 1) * 8);
+  };
+  auto filter_store = [&](int f0) {
+#pragma unroll
+    for (int u = 0; u < FB; ++u) {
+      const int v = tid + TH * (f0 + u);
+      const int e = v * 8, co = e % C, ci = (e / C) % C, tap = e / (C * C);
+      if (v < NVEC) *reinterpret_cast<u32x4*>(wl + (BWD ? ci * RSW + 2 * (tap * C + co) : (tap * C + ci) * PB + 2 * co)) = wv[u];
+    }
+  };
+  filter_load(0);
+  // the border columns stay zero
+  for (int i = tid; i < p.seg * srp * 2 * CG; i += TH) {
+    const int c = i % CG, q = i / CG, row = q >> 1;
+    *reinterpret_cast<uint4*>(xt + (row * WP + (q & 1) * (W + 1)) * PITCH + 16 * c) = make_uint4(0, 0, 0, 0);
+  }
+  if (bn) {   // sums added in row order within a group of threads, then group by group
+    if (part < PARTS) {
+      float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (unsigned bk = part;; ) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) { t.x += ps[u].x; t.y += ps[u].y; t.z += ps[u].z; t.w += ps[u].w; }
+        bk += U * PARTS;
+        if (bk >= p.nblocks) break;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const unsigned bu = bk + u * PARTS;
+          ps[u] = bu < p.nblocks ? *reinterpret_cast<const float4*>(p.sums.partial + (size_t)bu * 2 * C + 4 * v4) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+      }
+      *reinterpret_cast<float4*>(red + part * 2 * C + 4 * v4) = t;
+    }
+    __syncthreads();
+    if (tid < C) {
+      float a = 0.f, c = 0.f;
+#pragma unroll 8
+      for (int q = 0; q < PARTS; ++q) { a += red[q * 2 * C + tid]; c += red[q * 2 * C + C + tid]; }
+      if (!BWD) bn_statistics(p.sums, tid, a, c, blockIdx.x == 0);
+      s0[tid] = a; s1[tid] = c;
+      if (blockIdx.x == 0) { p.sums.out0[tid] = a; p.sums.out1[tid] = c; }
+    }
+  }
+  filter_store(0);
+  if constexpr (FB < FV) { filter_load(FB); filter_store(FB); }
+  if (BWD) {
+    for (int c = tid; c < C; c += TH) {
+      nbn[0][c] = p.stat ? p.nmean[c] : 0.f; nbn[1][c] = p.stat ? p.nrstd[c] : 0.f;
+    }
+  }
+  __syncthreads();
+  // this thread's eight channels: mean, scale a = rstd g, shift b; backward: d = a (dyh - k0) - (x - mean) k1
+  float a[8], k0[BWD ? 8 : 1], k1[BWD ? 8 : 1];
+  if (bn) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int c = 8 * cg + j;
+      if (!BWD) mean[j] = s0[c];
+      a[j] = (BWD ? prs[j] : s1[c]) * pg[j];
+      if (BWD) {
+        const float n = (float)p.sums.rows;
+        k0[j] = s0[c] / n;
+        k1[j] = s1[c] / n * prs[j] * a[j];
+      }
+    }
+  }
+  // forward: lane part of a filter fragment address (see conv3x3_mfma_kernel)
+  const int tr_lane = (8 * hh + ((lane & 15) >> 2)) * PB + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
+  // this lane's pixel of a tile
+  const int prow = (wave * 32 + li) >> p.wl, pcol = (wave * 32 + li) & (W - 1);
+  const int psg = prow >> p.srl, plr = prow & (p.sr - 1);
+  const char* xpix = xt + ((psg * srp + plr + 1) * WP + pcol + 1) * PITCH + 16 * hh;
+  float st0[NV], st1[NV], f0 = 0.f, f1 = 0.f;
+#pragma unroll
+  for (int j = 0; j < NV; ++j) { st0[j] = 0.f; st1[j] = 0.f; }
+
+  for (int tile = blockIdx.x; tile < p.tiles; tile += gridDim.x) {
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+      int off, place;
+      bool core;
+      locate(tile, it, off, place, core);
+      const uint32_t* xw = reinterpret_cast<const uint32_t*>(&rx[it]);
+      const uint32_t* aw = reinterpret_cast<const uint32_t*>(&ra[it]);
+      uint4 o = rx[it];
+      uint32_t* ow = reinterpret_cast<uint32_t*>(&o);
+      if (bn) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          float v[2];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const int e = 2 * j + h;
+            const float xv = h ? hi_bf(xw[j]) : lo_bf(xw[j]), av = h ? hi_bf(aw[j]) : lo_bf(aw[j]);
+            if (BWD) {
+              const float dyh = (rm[BWD ? it : 0] >> e) & 1 ? av : 0.f;
+              v[h] = fmaf(a[e], dyh - k0[e], -(xv - mean[e]) * k1[e]);
+            } else {
+              v[h] = fmaxf(bn_value(xv, mean[e], a[e], pb[e]) + av, 0.f);
+            }
+          }
+          ow[j] = pack2(v[0], v[1]);
+        }
+        if (off == CONV_OOB) o = make_uint4(0, 0, 0, 0);      // rows outside the image
+        if (core) {
+          *reinterpret_cast<uint4*>((char*)p.mid + off) = o;
+          if (!BWD && p.mask_out) p.mask_out[off >> 4] = relu_mask(o);
+        }
+      }
+      if (place >= 0) *reinterpret_cast<uint4*>(xt + place) = o;
+    }
+    __syncthreads();
+    const int grow = tile * (p.sr * p.seg) + psg * p.sr + plr;
+    const bool live = grow < p.rows;
+    const size_t pix = ((size_t)grow << p.wl) + pcol;
+    // backward: what the outputs of the tile are combined with, asked for ahead of the next tile (64 channels: registers only
+    // for half of it at a time, asked for at the end)
+    uint2 dr[NT][NQ], nx[NT][NQ];
+    typedef typename std::conditional<C == 16, uint16_t, uint32_t>::type Bits;   // a mask's bits of 16 or 32 channels
+    uint32_t dm[NT], nm[NT];
+    auto outer_load = [&](int t) {
+      const size_t o = pix * C + 32 * t;
+      dm[t] = nm[t] = 0;
+      if (p.dres) dm[t] = *reinterpret_cast<const Bits*>(p.dmask + (o >> 3));
+      if (p.stat) nm[t] = *reinterpret_cast<const Bits*>(p.nmask + (o >> 3));
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        dr[t][q] = nx[t][q] = make_uint2(0, 0);
+        if (p.dres) dr[t][q] = *reinterpret_cast<const uint2*>(p.dres + o + 8 * q + 4 * hh);
+        if (p.stat) nx[t][q] = *reinterpret_cast<const uint2*>(p.nx + o + 8 * q + 4 * hh);
+      }
+    };
+    if (BWD && NT == 1 && live) outer_load(0);
+    if (tile + (int)gridDim.x < p.tiles) load(tile + gridDim.x);
+    f32x16 acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) {
+      const int ky = tap / 3 - 1, kx = tap % 3 - 1;
+      const char* xp = xpix + (BWD ? -1 : 1) * (ky * WP + kx) * PITCH;
+#pragma unroll
+      for (int c16 = 0; c16 < K16; ++c16) {
+        const bf16x8 xf = *reinterpret_cast<const bf16x8*>(xp + 32 * c16);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          bf16x8 wf;
+          if (BWD) {
+            wf = *reinterpret_cast<const bf16x8*>(wl + 2 * (tap * C + 8 * hh) + (t * 32 + li) * RSW + 32 * c16);
+          } else {
+            const char* fp = wl + tr_lane + (tap * C + 16 * c16) * PB + 64 * t;
+            const uint2 lo = conv_lds_read_tr(fp), hi = conv_lds_read_tr(fp + 4 * PB);
+            wf = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
+          }
+          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, xf, acc[t], 0, 0, 0);
+        }
+      }
+    }
+    if (live) {
+      // acc[t][4q+e] = out[pix][32t + 8q + 4hh + e]
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        if (BWD && NT > 1) outer_load(t);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+          const int c = 32 * t + 8 * q + 4 * hh;
+          float v[4] = {acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]};
+          if (BWD) {
+            const float rv[4] = {lo_bf(dr[t][q].x), hi_bf(dr[t][q].x), lo_bf(dr[t][q].y), hi_bf(dr[t][q].y)};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] += (dm[t] >> (8 * q + 4 * hh + e)) & 1 ? rv[e] : 0.f;
+          }
+          const uint2 o = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
+          *reinterpret_cast<uint2*>(p.dst + pix * C + c) = o;
+          const float r[4] = {lo_bf(o.x), hi_bf(o.x), lo_bf(o.y), hi_bf(o.y)};
+          if (!BWD) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { st0[16 * t + 4 * q + e] += r[e]; st1[16 * t + 4 * q + e] += r[e] * r[e]; }
+          } else if (p.stat) {
+            const float xv[4] = {lo_bf(nx[t][q].x), hi_bf(nx[t][q].x), lo_bf(nx[t][q].y), hi_bf(nx[t][q].y)};
+            const float4 mu = *reinterpret_cast<const float4*>(&nbn[0][c]), rs = *reinterpret_cast<const float4*>(&nbn[1][c]);
+            const float mv[4] = {mu.x, mu.y, mu.z, mu.w}, rv[4] = {rs.x, rs.y, rs.z, rs.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const float d = (nm[t] >> (8 * q + 4 * hh + e)) & 1 ? r[e] : 0.f;
+              st0[16 * t + 4 * q + e] += d;
+              st1[16 * t + 4 * q + e] += d * (xv[e] - mv[e]) * rv[e];
+            }
+          }
+        }
+      }
+    }
+    if (FOLD && (!BWD || p.stat)) {
+      halfwave_sums<NV>(st0, li);
+      halfwave_sums<NV>(st1, li);
+      f0 += st0[0]; f1 += st1[0];
+#pragma unroll
+      for (int j = 0; j < NV; ++j) { st0[j] = 0.f; st1[j] = 0.f; }
+    }
+    __syncthreads();
+  }
+  if (!BWD || p.stat) {
+    // value index j = 16 t + 4 q + e of lane half hh is channel 32 t + 8 q + 4 hh + e
+    if (!FOLD) {
+      halfwave_sums<NV>(st0, li);
+      halfwave_sums<NV>(st1, li);
+      f0 = st0[0]; f1 = st1[0];
+    }
+    if (NV == 32 || !(li & 1)) {
+      const int j = NV == 32 ? li : li >> 1;
+      red[((wave * 2 + 0) * 2 + hh) * 32 + j] = f0;
+      red[((wave * 2 + 1) * 2 + hh) * 32 + j] = f1;
+    }
+    __syncthreads();
+    if (tid < 2 * C) {
+      const int which = tid / C, c = tid % C, j = 16 * (c >> 5) + 4 * ((c & 31) >> 3) + (c & 3), h2 = (c & 7) >> 2;
+      float tot = 0.f;
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) tot += red[((w * 2 + which) * 2 + h2) * 32 + j];
+      p.stat[(size_t)blockIdx.x * 2 * C + tid] = tot;
+    }
+  }
+}
+
+bool cb_al16(const void* p) { return !(((uintptr_t)p) & 15); }
+int log2_of(int v) { int l = 0; while ((1 << l) < v) ++l; return l; }
+int compute_units() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
+  return cus;
+}
+
+template <int C, int WAVES, bool BWD>
+int conv_bn_launch(hipStream_t s, const ConvBnArgs& p, int grid, int tile_px_bytes) {
+  const int lds = filter_bytes<C, BWD>() + tile_px_bytes;
+  static std::atomic<int> raised[64];
+  if (lds > 48 * 1024) {
+    int dev = 0;
+    PPLL_HIP(hipGetDevice(&dev));
+    if (dev < 0 || dev >= 64 || raised[dev].load() < lds) {
+      PPLL_HIP(hipFuncSetAttribute((const void*)conv_bn_kernel<C, WAVES, BWD>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+      if (dev >= 0 && dev < 64) raised[dev].store(lds);
+    }
+  }
+  hipLaunchKernelGGL((conv_bn_kernel<C, WAVES, BWD>), dim3(grid), dim3(64 * WAVES), lds, s, p);
+  PPLL_HIP(hipGetLastError());
+  return PPLL_OK;
+}
+
+// Eight waves (256 pixels) a tile once those give most compute units one (at least 200 tiles), else four: with fewer, half the
+// compute units would stand idle, with more, the smaller tile loads its two border rows for half as many pixels.
+struct TileShape { int waves, sr, seg, tiles, grid; };
+TileShape tile_shape(int B, int H, int W, int C) {
+  TileShape t{};
+  const long px = (long)B * H * W;
+  const int cus = compute_units();
+  t.waves = px >= 200L * 256 ? 8 : 4;
+  const int rt = 32 * t.waves / W;
+  t.sr = rt < H ? rt : H;
+  t.seg = rt / t.sr;
+  t.tiles = (int)(((long)B * H + rt - 1) / rt);
+  const int most = t.waves == 8 && C > 16 ? cus : 2 * cus, per = (t.tiles + most - 1) / most;
+  t.grid = (t.tiles + per - 1) / per;
+  return t;
+}
+template <bool BWD>
+int conv_bn_dispatch(hipStream_t s, ConvBnArgs& p, int B, int H, int W, int C, int* stat_blocks) {
+  const TileShape t = tile_shape(B, H, W, C);
+  p.H = H; p.wl = log2_of(W); p.rows = B * H; p.sr = t.sr; p.srl = log2_of(t.sr); p.seg = t.seg;
+  p.inv = (65536 + t.sr + 1) / (t.sr + 2); p.tiles = t.tiles; p.bytes = (uint32_t)((long)B * H * W * C * 2);
+  const int tile_bytes = t.seg * (t.sr + 2) * (W + 2) * pixel_pitch(C);
+  if (stat_blocks) *stat_blocks = p.stat ? t.grid : 0;
+  if (C == 16) return t.waves == 8 ? conv_bn_launch<16, 8, BWD>(s, p, t.grid, tile_bytes) : conv_bn_launch<16, 4, BWD>(s, p, t.grid, tile_bytes);
+  if (C == 32) return t.waves == 8 ? conv_bn_launch<32, 8, BWD>(s, p, t.grid, tile_bytes) : conv_bn_launch<32, 4, BWD>(s, p, t.grid, tile_bytes);
+  return t.waves == 8 ? conv_bn_launch<64, 8, BWD>(s, p, t.grid, tile_bytes) : conv_bn_launch<64, 4, BWD>(s, p, t.grid, tile_bytes);
+}
+}  // namespace
+
+// Square-ish power-of-two maps of 8 to 32 pixels a side: a tile is then whole rows of one image or whole images.
+bool conv_bn_ok(int dt, int B, int H, int W, int C) {
+  auto side = [](int v) { return v == 8 || v == 16 || v == 32; };
+  return dt == BF16 && (C == 16 || C == 32 || C == 64) && side(H) && side(W) && (long)B * H * W * C * 2 < (1L << 30) - 64;
+}
+int conv_bn_stat_blocks(int B, int H, int W, int C) { return tile_shape(B, H, W, C).grid; }
+
+int launch_conv_bn_fwd(hipStream_t s, const BnInput* bn, const void* x, const void* w, int B, int H, int W, int C, void* dst,
+                       float* stat, int* stat_blocks) {
+  ConvBnArgs p{};
+  p.x = (const uint16_t*)(bn ? bn->x : x); p.w = (const uint16_t*)w; p.dst = (uint16_t*)dst; p.stat = stat;
+  if (bn) {
+    p.bn = 1; p.aux = (const uint16_t*)bn->res; p.mid = (uint16_t*)bn->y; p.mask_out = bn->mask; p.g = bn->g; p.b = bn->b; p.nblocks = (unsigned)bn->blocks;
+    p.sums.rows = B * H * W; p.sums.C = C; p.sums.partial = bn->partials; p.sums.eps = bn->eps; p.sums.momentum = bn->momentum;
+    p.sums.out0 = bn->mean; p.sums.out1 = bn->rstd; p.sums.run_mean = bn->run_mean; p.sums.run_var = bn->run_var;
+    if (!cb_al16(bn->res) || !cb_al16(bn->y)) { set_error("conv_bn: unaligned tensors"); return PPLL_ERR_CONFIG; }
+  }
+  if (!cb_al16(p.x) || !cb_al16(w) || !cb_al16(dst)) { set_error("conv_bn: unaligned tensors"); return PPLL_ERR_CONFIG; }
+  void* prof = nullptr;   // algorithmic bytes: input, output and filter once, the residual and the stored activation where present
+  PPLL_TRY(profile_begin(s, 2.0 * ((double)B * H * W * C * (2 + (bn ? 1 : 0) + (bn && bn->res ? 1 : 0)) + 9.0 * C * C), &prof, 1));
+  PPLL_TRY(conv_bn_dispatch<false>(s, p, B, H, W, C, stat_blocks));
+  return profile_end(s, prof);
+}
+
+int launch_conv_bn_bwd(hipStream_t s, const BnGrad& bn, const void* w, int B, int H, int W, int C, void* d, const void* dres,
+                       const uint8_t* dmask, void* dst, const BnBwdSums* next, float* stat,
+                       int* stat_blocks) {
+  ConvBnArgs p{};
+  p.x = (const uint16_t*)bn.x; p.aux = (const uint16_t*)bn.dy; p.mask = bn.mask; p.mid = (uint16_t*)d;
+  p.w = (const uint16_t*)w; p.dst = (uint16_t*)dst; p.dres = (const uint16_t*)dres; p.dmask = dmask;
+  p.g = bn.g; p.b = bn.b; p.nblocks = (unsigned)bn.blocks;
+  p.sums.rows = B * H * W; p.sums.C = C; p.sums.partial = bn.partials; p.sums.mean = bn.mean; p.sums.rstd = bn.rstd;
+  p.sums.out0 = bn.db; p.sums.out1 = bn.dg;
+  if (next) {
+    p.stat = stat; p.nmask = next->mask; p.nx = (const uint16_t*)next->x; p.nmean = next->mean; p.nrstd = next->rstd;
+  }
+  for (const void* q : {(const void*)p.x, (const void*)p.aux, (const void*)d, w, (const void*)dst, dres, (const void*)p.nx})
+    if (!cb_al16(q)) { set_error("conv_bn: unaligned tensors"); return PPLL_ERR_CONFIG; }
+  void* prof = nullptr;   // algorithmic bytes: dy, x, d, dst and filter once, the shortcut gradient where present
+  PPLL_TRY(profile_begin(s, 2.0 * ((double)B * H * W * C * (4 + (dres ? 1 : 0)) + 9.0 * C * C), &prof, 1));
+  PPLL_TRY(conv_bn_dispatch<true>(s, p, B, H, W, C, stat_blocks));
+  return profile_end(s, prof);
+}
+
+}  // namespace ppll

@@ -463,6 +463,19 @@ def test_resnet32_stages_at_their_full_shape_decisive_masks(name):
     run_case(synth.workload(name, batch=100), steps=1, check_bn=True, tweak=_decisive_shifts)
 
 
+@pytest.mark.parametrize("channels,height,width,batch", [
+    # maps that the convolutions with a BatchNorm on the way in take, four waves (tiles of 128 pixels): one image and less
+    # than a tile, two 8 x 8 images a tile and a last one half empty, part of an image a tile, the two oblong shapes
+    (16, 8, 8, 1), (16, 8, 8, 3), (64, 16, 16, 1), (32, 8, 32, 2), (32, 32, 8, 3), (16, 32, 32, 1),
+    # eight waves (tiles of 256 pixels, from 51200 pixels on): four images a tile and a last one with three, one image, a
+    # quarter of one
+    (64, 8, 8, 803), (32, 8, 8, 803), (16, 8, 32, 201), (32, 32, 8, 201), (64, 16, 16, 201), (16, 32, 32, 51),
+])
+def test_resnet_bf16_fused_convolution_tile_edges(channels, height, width, batch):
+    wl = synth.workload("resnet_stage_bf16", n_basic_blocks=2, batch=batch, height=height, width=width, channels=channels)
+    run_case(wl, steps=1, check_bn=True, tweak=_decisive_shifts)
+
+
 def test_resnet_bf16_stage_full_size_natural_statistics():
     run_case(synth.workload("resnet_stage_bf16"), steps=2, check_bn=True)
 
