@@ -11,7 +11,7 @@
 // apply, convolution gathering its nine taps from memory) and here:
 //                        1024 x 32 x 32 x 16    848 x 8 x 8 x 64    128 x 16 x 16 x 32
 //   forward                    51 -> 29.5           29.5 -> 16          11.5 -> 7.1
-//   backward                   76 -> 62             36 -> 25            13.6 -> 8.6
+//   backward                   76 -> 47             36 -> 20            13.6 -> 8.6
 // (at the first of them the maps alone take 20 - 27 and 34 - 41 us at a copy's rate).  A tile of 256 (128) pixels is loaded
 // with 16-byte loads while the tile before it is multiplied, pixels lie 2 C + 16 bytes apart in LDS (16 lanes reading 16
 // bytes of neighbouring pixels hit every bank once), a workgroup keeps its filter for all its tiles.  One workgroup of eight
@@ -99,10 +99,10 @@ __global__ __launch_bounds__(64 * WAVES, C == 16 ? 4 : 1) void conv_bn_kernel(Co
   const __amdgpu_buffer_rsrc_t rsm = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.mask), 0, (int)(p.bytes >> 4), 0x00020000);
   uint4 rx[NIT], ra[NIT];
   uint32_t rm[BWD ? NIT : 1];
-  // piece `it` of this thread in a tile: its byte offset (out of range: nothing to load), place in LDS, and whether it lies in
-  // the tile proper (not in the border)
-  auto locate = [&](int tile, int it, int& off, int& place, bool& core) {
-    const int pi = pi0 + it * PSTEP, prow = pi >> p.wl, col = pi & (W - 1);
+  // a piece of this thread in a tile, of pixel pi: its byte offset (out of range: nothing to load), place in LDS, and whether
+  // it lies in the tile proper (not in the border)
+  auto locate = [&](int tile, int pi, int& off, int& place, bool& core) {
+    const int prow = pi >> p.wl, col = pi & (W - 1);
     const int sg = p.seg > 1 ? (prow * p.inv) >> 16 : 0, lr = prow - sg * srp;
     const int row0 = tile * (p.sr * p.seg) + sg * p.sr, grow = row0 + lr - 1;
     const int yy = (p.seg > 1 ? 0 : row0 & (p.H - 1)) + lr - 1;
@@ -111,18 +111,18 @@ __global__ __launch_bounds__(64 * WAVES, C == 16 ? 4 : 1) void conv_bn_kernel(Co
     place = pi < npx ? (prow * WP + col + 1) * PITCH + 16 * cg : -1;
     core = in && lr >= 1 && lr <= p.sr;
   };
-  auto load = [&](int tile) {
+  auto load = [&](int tile, int p0) {
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
       int off, place;
       bool core;
-      locate(tile, it, off, place, core);
+      locate(tile, p0 + it * PSTEP, off, place, core);
       rx[it] = conv_buf_load16(rsx, off);
       ra[it] = conv_buf_load16(rsa, off);
       if (BWD) rm[it] = __builtin_amdgcn_raw_buffer_load_b8(rsm, off == CONV_OOB ? CONV_OOB : off >> 4, 0, 0);
     }
   };
-  load(blockIdx.x);
+  load(blockIdx.x, pi0);
   // (4) the filter
   constexpr int NVEC = 9 * C * C / 8, FV = (NVEC + TH - 1) / TH;
   constexpr int FB = FV < 6 ? FV : (FV + 1) / 2;       // 16-byte pieces in flight per thread
@@ -206,11 +206,15 @@ __global__ __launch_bounds__(64 * WAVES, C == 16 ? 4 : 1) void conv_bn_kernel(Co
   for (int j = 0; j < NV; ++j) { st0[j] = 0.f; st1[j] = 0.f; }
 
   for (int tile = blockIdx.x; tile < p.tiles; tile += gridDim.x) {
+    // backward: what is formed from it is formed again in every tile; kept in registers it spills, and a reload waits for
+    // the next tile's loads (62 instead of 47 us at 1024 x 32 x 32 x 16)
+    int p0 = pi0;
+    if (BWD) asm volatile("" : "+v"(p0));
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
       int off, place;
       bool core;
-      locate(tile, it, off, place, core);
+      locate(tile, p0 + it * PSTEP, off, place, core);
       const uint32_t* xw = reinterpret_cast<const uint32_t*>(&rx[it]);
       const uint32_t* aw = reinterpret_cast<const uint32_t*>(&ra[it]);
       uint4 o = rx[it];
@@ -243,14 +247,14 @@ __global__ __launch_bounds__(64 * WAVES, C == 16 ? 4 : 1) void conv_bn_kernel(Co
     __syncthreads();
     const int grow = tile * (p.sr * p.seg) + psg * p.sr + plr;
     const bool live = grow < p.rows;
-    const size_t pix = ((size_t)grow << p.wl) + pcol;
+    const uint32_t pix = ((uint32_t)grow << p.wl) + pcol;   // a tensor has fewer than 2^29 elements
     // backward: what the outputs of the tile are combined with, asked for ahead of the next tile (64 channels: registers only
     // for half of it at a time, asked for at the end)
     uint2 dr[NT][NQ], nx[NT][NQ];
     typedef typename std::conditional<C == 16, uint16_t, uint32_t>::type Bits;   // a mask's bits of 16 or 32 channels
     uint32_t dm[NT], nm[NT];
     auto outer_load = [&](int t) {
-      const size_t o = pix * C + 32 * t;
+      const uint32_t o = pix * C + 32 * t;
       dm[t] = nm[t] = 0;
       if (p.dres) dm[t] = *reinterpret_cast<const Bits*>(p.dmask + (o >> 3));
       if (p.stat) nm[t] = *reinterpret_cast<const Bits*>(p.nmask + (o >> 3));
@@ -262,7 +266,7 @@ __global__ __launch_bounds__(64 * WAVES, C == 16 ? 4 : 1) void conv_bn_kernel(Co
       }
     };
     if (BWD && NT == 1 && live) outer_load(0);
-    if (tile + (int)gridDim.x < p.tiles) load(tile + gridDim.x);
+    if (tile + (int)gridDim.x < p.tiles) load(tile + gridDim.x, p0);
     f32x16 acc[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t)
