@@ -318,9 +318,10 @@ int launch_conv3x3_wgrad_group(hipStream_t s, const ConvWgradJob* jobs, int n, i
                                int stride, ReduceQueue& rq);
 int launch_conv3x3_wgrad_group_bf16(hipStream_t s, const ConvWgradJob* jobs, int n, int B, int H, int W, int Ci, int Co,
                                     int stride, ReduceQueue& rq, bool* done);
-// second stage of a convolution weight gradient: adds `rows` partial filters [9][Ci][Co] into dw [9][keep][Co]
-int reduce_conv_filters(hipStream_t s, ReduceQueue& rq, bool queued, const float* partials, int rows, int Ci, int Co,
-                        int keep, float* dw);
+// second stage of a convolution weight gradient: adds `rows` partial filters [9][Ci][Co], `stride` floats apart, into
+// dw [9][keep][Co]
+int reduce_conv_filters(hipStream_t s, ReduceQueue& rq, bool queued, const float* partials, int rows, long stride,
+                        int Ci, int Co, int keep, float* dw);
 // x [P, c] -> y [P, 16] with zero channels appended (c < 16); w [9][c][Co] (fp32 master) -> wp [9][16][Co] bf16
 int launch_pad_channels16(hipStream_t s, const void* x, size_t P, int c, void* y);
 int launch_pad_filter16(hipStream_t s, const float* w, int c, int Co, void* wp);
@@ -355,7 +356,7 @@ bool conv_bf16_supported(int dt, int wdt, int Ci, int Co, const void* a, const v
 bool conv_pixels_fit(int B, int H, int W);
 bool conv_fwd_bf16_ok(int Ci, int Co);
 bool conv_dgrad_bf16_ok(int Ci, int Co);
-bool conv_wgrad_bf16_ok(int Ci, int Co);
+bool conv_wgrad_bf16_ok(int H, int W, int Ci, int Co, int stride);
 // stat (nullable): the kernel also writes per-workgroup per-channel sums of its stored outputs there
 // ([*stat_blocks][2][Co] floats: what the BatchNorm behind the convolution reduces)
 int launch_conv3x3_fwd_bf16(hipStream_t s, const void* x, const void* w, int B, int H, int W, int Ci, int Co,

@@ -305,31 +305,30 @@ int conv3x3_wgrad_partial_floats(int B, int H, int W, int Ci, int Co, int stride
   size_t a = wgrad_chunks(B, H, W, stride) * 9 * Ci * Co, b = conv3x3_wgrad_bf16_partial_floats(B, H, W, Ci, Co, stride);
   return (int)(a > b ? a : b);
 }
-int reduce_conv_filters(hipStream_t s, ReduceQueue& rq, bool queued, const float* partials, int rows, int Ci, int Co,
-                        int keep, float* dw) {
-  const int nw = 9 * Ci * Co;
-  if (keep == Ci) return rq.reduce(s, queued, partials, rows, nw, nw, 1.0f, dw);
+int reduce_conv_filters(hipStream_t s, ReduceQueue& rq, bool queued, const float* partials, int rows, long stride,
+                        int Ci, int Co, int keep, float* dw) {
+  if (keep == Ci) return rq.reduce(s, queued, partials, rows, 9 * Ci * Co, stride, 1.0f, dw);
   for (int tap = 0; tap < 9; ++tap)   // the leading `keep` input channels of every tap
-    PPLL_TRY(rq.reduce(s, queued, partials + (size_t)tap * Ci * Co, rows, keep * Co, nw, 1.0f, dw + (size_t)tap * keep * Co));
+    PPLL_TRY(rq.reduce(s, queued, partials + (size_t)tap * Ci * Co, rows, keep * Co, stride, 1.0f, dw + (size_t)tap * keep * Co));
   return PPLL_OK;
 }
 
 int launch_conv3x3_wgrad(hipStream_t s, const void* x, const void* dy, int dt, int B, int H, int W, int Ci, int Co,
                          int stride, ReduceQueue& rq, float* dw, int ci_keep) {
   if (ci_keep < 0 || ci_keep > Ci) ci_keep = Ci;
-  if (conv_bf16_supported(dt, BF16, Ci, Co, x, dy, dw) && conv_wgrad_bf16_ok(Ci, Co) && conv_pixels_fit(B, H, W))
+  if (conv_bf16_supported(dt, BF16, Ci, Co, x, dy, dw) && conv_wgrad_bf16_ok(H, W, Ci, Co, stride) && conv_pixels_fit(B, H, W))
     return launch_conv3x3_wgrad_bf16(s, x, dy, B, H, W, Ci, Co, stride, rq, dw, ci_keep);
   int chunks = (int)wgrad_chunks(B, H, W, stride), nw = 9 * Ci * Co;
   bool queued;
   float* partials = rq.space((size_t)chunks * nw, &queued);
   hipLaunchKernelGGL(conv3x3_wgrad_kernel, dim3(chunks), dim3(256), 0, s, x, dy, dt, B, H, W, Ci, Co, stride, partials);
   PPLL_HIP(hipGetLastError());
-  return reduce_conv_filters(s, rq, queued, partials, chunks, Ci, Co, ci_keep, dw);
+  return reduce_conv_filters(s, rq, queued, partials, chunks, nw, Ci, Co, ci_keep, dw);
 }
 
 int launch_conv3x3_wgrad_group(hipStream_t s, const ConvWgradJob* jobs, int n, int dt, int B, int H, int W, int Ci, int Co,
                                int stride, ReduceQueue& rq) {
-  bool fast = conv_wgrad_bf16_ok(Ci, Co) && conv_pixels_fit(B, H, W);
+  bool fast = conv_wgrad_bf16_ok(H, W, Ci, Co, stride) && conv_pixels_fit(B, H, W);
   for (int j = 0; j < n && fast; ++j) fast = conv_bf16_supported(dt, BF16, Ci, Co, jobs[j].x, jobs[j].dy, jobs[j].dw);
   if (fast && n > 1) {
     bool done = false;

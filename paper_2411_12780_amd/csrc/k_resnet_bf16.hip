@@ -6,11 +6,6 @@
 //    with transposing LDS reads; input gradient: [in channel][tap, out channel]);
 //    the product is issued filter-first so that a lane ends up with 4 consecutive
 //    output channels of its pixel (8-byte stores).
-//  * weight gradient on the matrix cores with the output pixel as reduction index
-//    (images transposed in LDS; stride 1 and 2, up to 16 convolutions of one shape per
-//    launch); shapes it refuses: 64 output pixels per workgroup, their nine shifted
-//    input vectors and dy staged in LDS, fp32 accumulators per thread.  Partial sums
-//    per workgroup, added in a fixed order by the queued second stage.
 //  * BatchNorm statistics / backward sums: 8 channels per thread (16-byte loads),
 //    per-workgroup partials, added in workgroup order either by a one-workgroup launch
 //    or, on small tensors, by every workgroup of the kernel that applies them (a
@@ -333,80 +328,6 @@ __global__ __launch_bounds__(256) void conv3x3_dgrad_s2_kernel(ConvArgs p) {
       }
     }
   }
-}
-
-// Weight gradient.  CO = 32 or 64.  Thread (co = tid % CO, cig = tid / CO) owns
-// dw[tap][cig*CPT .. +CPT-1][co], CPT = Ci / (256 / CO) input channels.
-constexpr int WG_PIX_F = 64;
-template <int CO, int CPT>
-__global__ __launch_bounds__(256) void conv3x3_wgrad_bf16_kernel(const uint16_t* __restrict__ x,
-                                                                 const uint16_t* __restrict__ dy, int B, int H, int W,
-                                                                 int Ci, int stride, float* __restrict__ partial) {
-  extern __shared__ __align__(16) char sm[];
-  uint16_t* xs = reinterpret_cast<uint16_t*>(sm);                 // [pixels][9][Ci]
-  uint16_t* dys = xs + WG_PIX_F * 9 * Ci;                         // [pixels][CO]
-  const int Ho = out_dim(H, stride), Wo = out_dim(W, stride);
-  const long P = (long)B * Ho * Wo, p0 = (long)blockIdx.x * WG_PIX_F;
-  const int tid = threadIdx.x;
-  const int cpc = Ci / 8;                                         // 16-byte chunks per pixel vector
-  for (int item = tid; item < WG_PIX_F * 9 * cpc; item += 256) {
-    const int ch = item % cpc, tap = (item / cpc) % 9, lp = item / (cpc * 9);
-    const long pp = p0 + lp;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (pp < P) {
-      const uint32_t p32 = (uint32_t)pp, prow = p32 / (uint32_t)Wo;   // the launcher checks that the pixel count fits
-      const int ox = (int)(p32 - prow * (uint32_t)Wo), oy = (int)(prow % (uint32_t)Ho), b = (int)(prow / (uint32_t)Ho);
-      const int iy = oy * stride + tap / 3 - 1, ix = ox * stride + tap % 3 - 1;
-      if (iy >= 0 && iy < H && ix >= 0 && ix < W)
-        v = *reinterpret_cast<const uint4*>(x + (((long)b * H + iy) * W + ix) * Ci + 8 * ch);
-    }
-    *reinterpret_cast<uint4*>(xs + ((size_t)lp * 9 + tap) * Ci + 8 * ch) = v;
-  }
-  for (int item = tid; item < WG_PIX_F * (CO / 8); item += 256) {
-    const int ch = item % (CO / 8), lp = item / (CO / 8);
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (p0 + lp < P) v = *reinterpret_cast<const uint4*>(dy + (p0 + lp) * CO + 8 * ch);
-    *reinterpret_cast<uint4*>(dys + (size_t)lp * CO + 8 * ch) = v;
-  }
-  __syncthreads();
-  const int co = tid % CO, cig = tid / CO;
-  float acc[9][CPT];
-#pragma unroll
-  for (int t = 0; t < 9; ++t)
-#pragma unroll
-    for (int j = 0; j < CPT; ++j) acc[t][j] = 0.f;
-#pragma unroll 2
-  for (int lp = 0; lp < WG_PIX_F; ++lp) {
-    const float d = bf16_to_f32(dys[(size_t)lp * CO + co]);
-    const uint16_t* xp = xs + (size_t)lp * 9 * Ci + cig * CPT;
-    if constexpr (CPT == 1) {      // one input channel per thread: nine 16-bit reads
-      uint16_t x1[9];
-#pragma unroll
-      for (int t = 0; t < 9; ++t) x1[t] = xp[t * Ci];
-#pragma unroll
-      for (int t = 0; t < 9; ++t) acc[t][0] = fmaf(bf16_to_f32(x1[t]), d, acc[t][0]);
-    } else {
-      uint32_t xv[9][CPT / 2];
-#pragma unroll
-      for (int t = 0; t < 9; ++t) {
-        const uint32_t* xw = reinterpret_cast<const uint32_t*>(xp + t * Ci);
-#pragma unroll
-        for (int j = 0; j < CPT / 2; ++j) xv[t][j] = xw[j];
-      }
-#pragma unroll
-      for (int t = 0; t < 9; ++t)
-#pragma unroll
-        for (int j = 0; j < CPT / 2; ++j) {
-          acc[t][2 * j] = fmaf(lo_bf(xv[t][j]), d, acc[t][2 * j]);
-          acc[t][2 * j + 1] = fmaf(hi_bf(xv[t][j]), d, acc[t][2 * j + 1]);
-        }
-    }
-  }
-  float* out = partial + (size_t)blockIdx.x * 9 * Ci * CO;
-#pragma unroll
-  for (int t = 0; t < 9; ++t)
-#pragma unroll
-    for (int j = 0; j < CPT; ++j) out[((size_t)t * Ci + cig * CPT + j) * CO + co] = acc[t][j];
 }
 
 // ---------------------------------------------------------------- BatchNorm
@@ -830,316 +751,6 @@ int launch_conv3x3_dgrad_bf16(hipStream_t s, const void* dy, const void* w, int 
 // forward and input gradient produce up to 64 channels (two MFMA tiles of 32; 16 and 48 leave half a tile idle)
 bool conv_fwd_bf16_ok(int Ci, int Co) { return Co % 16 == 0 && Co <= 64 && Ci <= 64 && conv_mfma_lds(Co, Ci) <= CONV_MFMA_LDS_MAX; }
 bool conv_dgrad_bf16_ok(int Ci, int Co) { return Ci % 16 == 0 && Ci <= 64 && Co <= 64 && conv_mfma_lds(Ci, Co) <= CONV_MFMA_LDS_MAX; }
-bool conv_wgrad_bf16_ok(int Ci, int Co) {
-  if (Co == 16) return Ci == 16;
-  return (Co == 32 || Co == 64) && Ci % 16 == 0 && Ci >= 16 && Ci <= 64;
-}
-
-typedef __attribute__((ext_vector_type(8))) __bf16 wg_bf16x8;
-// ---------------------------------------------------------------------------------------------
-// Weight gradient on the matrix cores for CI -> CO channels (16, 32 or 64 each), stride 1 or 2, output
-// rows of 8, 16, 24, ... pixels.  The reduction index of a 16x16x32 MFMA is the output pixel: a k-step is
-// four groups of 8 consecutive pixels of one output row.  A workgroup of 8 waves takes whole images: it
-// transposes x and dy of an image to [channel][pixel] in LDS.  x gets a 16-byte zero gap in front of every
-// row and a zero row above and below, so that no tap needs a bounds test; with stride 2 a row of x is
-// stored as its odd columns followed by its even columns, which makes the pixels that 8 consecutive
-// outputs read consecutive again.  A wave owns one tile of 16 output channels for all 9 taps and all
-// input-channel tiles and every (8 / tiles)-th k-step.  The fragment of the tap that starts one pixel to
-// the left (and, at stride 1, to the right) is the aligned one shifted by two bytes, the neighbouring
-// pixel read separately.  The k-splits of a workgroup are added in LDS in k-split order: one partial per
-// workgroup, summed over workgroups by the ordered second-stage reduction.
-typedef __attribute__((ext_vector_type(4))) float wg_f32x4;
-constexpr int WGT_WAVES = 8;
-constexpr int WGT_FOLD_BYTES = 9 * 64 * 64 * 4;      // 144 KiB: LDS the k-split sums may take
-__host__ __device__ inline int wgt_pad16(int bytes) { return bytes + ((16 - bytes % 128) + 128) % 128; }   // = 16 mod 128
-__host__ __device__ inline int wgt_row_stride(int W) { return 16 + 2 * W; }
-__host__ __device__ inline int wgt_x_stride(int H, int W) { return wgt_pad16((H + 2) * wgt_row_stride(W) + 16); }
-__host__ __device__ inline int wgt_dy_stride(int Ho, int Wo) { return wgt_pad16(Ho * Wo * 2); }
-
-// 4 pixels x 8 channels (one uint4 per pixel) -> for channel i the 4 pixels as one uint2
-__device__ __forceinline__ uint2 wgt_gather4(const uint4& p0, const uint4& p1, const uint4& p2, const uint4& p3, int i) {
-  const uint32_t sel = (i & 1) ? 0x07060302u : 0x05040100u;
-  uint2 o;
-  o.x = __builtin_amdgcn_perm(reinterpret_cast<const uint32_t*>(&p1)[i >> 1], reinterpret_cast<const uint32_t*>(&p0)[i >> 1], sel);
-  o.y = __builtin_amdgcn_perm(reinterpret_cast<const uint32_t*>(&p3)[i >> 1], reinterpret_cast<const uint32_t*>(&p2)[i >> 1], sel);
-  return o;
-}
-
-// up to 16 convolutions of one shape in a launch: blockIdx.y picks the convolution
-constexpr int WGT_GROUP = 16;
-struct WgtGroup { const uint16_t* x[WGT_GROUP]; const uint16_t* dy[WGT_GROUP]; float* partial[WGT_GROUP]; };
-
-template <int CI, int CO, int S>
-__global__ __launch_bounds__(64 * WGT_WAVES) void conv3x3_wgrad_tiles_kernel(WgtGroup grp, int B, int H, int W) {
-  const uint16_t* __restrict__ x = grp.x[blockIdx.y];
-  const uint16_t* __restrict__ dy = grp.dy[blockIdx.y];
-  float* __restrict__ partial = grp.partial[blockIdx.y];
-  constexpr int CT = CI / 16, WN = CO / 16, WK = WGT_WAVES / WN, NT = 64 * WGT_WAVES, NW = 9 * CI * CO;
-  constexpr bool FOLD_ALL = WK * NW * 4 <= WGT_FOLD_BYTES;
-  static_assert(FOLD_ALL || WK == 2, "the k-splits either fit LDS together or are two");
-  extern __shared__ __align__(16) char sm[];
-  const int Ho = H / S, Wo = W / S;            // S = 2: H and W are even
-  const int RS = wgt_row_stride(W), CSX = wgt_x_stride(H, W), CSD = wgt_dy_stride(Ho, Wo);
-  char* xt = sm;                              // x  as [CI][H + 2 rows][16-byte gap, W pixels]
-  char* dt = sm + CI * CSX;                   // dy as [CO][Ho * Wo pixels]
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r = lane & 15, q = lane >> 4;
-  const int wn = wave % WN, kq = wave / WN;
-  for (int o = tid * 16; o < CI * CSX; o += NT * 16) *reinterpret_cast<uint4*>(xt + o) = make_uint4(0, 0, 0, 0);
-  wg_f32x4 acc[9][CT];
-#pragma unroll
-  for (int t = 0; t < 9; ++t)
-#pragma unroll
-    for (int j = 0; j < CT; ++j)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[t][j][e] = 0.f;
-  const int wo8 = Wo / 8, groups = Ho * wo8, ksteps = (groups + 3) / 4;
-  const int xw = S == 1 ? W / 4 : W / 8, xitems = H * xw * (CI / 8);     // (row, 4 or 8 pixels, 8 channels)
-  const int dw4 = Wo / 4, ditems = Ho * dw4 * (CO / 8);
-  for (int b = blockIdx.x; b < B; b += gridDim.x) {
-    const uint16_t* xb = x + (size_t)b * H * W * CI;
-    const uint16_t* db = dy + (size_t)b * Ho * Wo * CO;
-    __syncthreads();                          // zero fill done / the previous image's tiles are no longer read
-    for (int item = tid; item < xitems; item += NT) {
-      const int cg = item % (CI / 8), pg = item / (CI / 8), y = pg / xw, xg = pg % xw;
-      char* row = xt + (8 * cg) * CSX + (y + 1) * RS + 16;
-      if (S == 1) {
-        uint4 rx[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) rx[j] = *reinterpret_cast<const uint4*>(xb + ((size_t)(y * W + 4 * xg + j)) * CI + 8 * cg);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) *reinterpret_cast<uint2*>(row + i * CSX + 8 * xg) = wgt_gather4(rx[0], rx[1], rx[2], rx[3], i);
-      } else {
-        uint4 rx[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) rx[j] = *reinterpret_cast<const uint4*>(xb + ((size_t)(y * W + 8 * xg + j)) * CI + 8 * cg);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {   // odd columns first, then the even ones
-          *reinterpret_cast<uint2*>(row + i * CSX + 8 * xg) = wgt_gather4(rx[1], rx[3], rx[5], rx[7], i);
-          *reinterpret_cast<uint2*>(row + i * CSX + 2 * Wo + 8 * xg) = wgt_gather4(rx[0], rx[2], rx[4], rx[6], i);
-        }
-      }
-    }
-    for (int item = tid; item < ditems; item += NT) {
-      const int cg = item % (CO / 8), pg = item / (CO / 8);      // pg = 4-pixel group of the image, row-major
-      uint4 rd[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) rd[j] = *reinterpret_cast<const uint4*>(db + ((size_t)(4 * pg + j)) * CO + 8 * cg);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) *reinterpret_cast<uint2*>(dt + (8 * cg + i) * CSD + 8 * pg) = wgt_gather4(rd[0], rd[1], rd[2], rd[3], i);
-    }
-    __syncthreads();
-    for (int ks = kq; ks < ksteps; ks += WK) {
-      // the last k-step of an image may hold fewer than four pixel groups: the others multiply by zero
-      const bool live = 4 * ks + q < groups;
-      const int g = live ? 4 * ks + q : 0, oy = g / wo8, x0 = 8 * (g % wo8);
-      uint4 gv = make_uint4(0, 0, 0, 0);
-      if (live) gv = *reinterpret_cast<const uint4*>(dt + (16 * wn + r) * CSD + g * 16);
-      const wg_bf16x8 gf = __builtin_bit_cast(wg_bf16x8, gv);
-#pragma unroll
-      for (int ky = 0; ky < 3; ++ky)
-#pragma unroll
-        for (int t = 0; t < CT; ++t) {
-          // row S*oy + ky - 1 of the image = row S*oy + ky of the padded tile
-          const char* base = xt + (16 * t + r) * CSX + (S * oy + ky) * RS + 16 + 2 * x0;
-          const uint4 w = *reinterpret_cast<const uint4*>(base);     // S = 1: pixels x0..x0+7; S = 2: odd columns 2 x0 + 1 ..
-          const uint32_t prev = *reinterpret_cast<const uint16_t*>(base - 2);
-          uint4 a0, a1, a2;
-          a0.x = (w.x << 16) | prev;
-          a0.y = __builtin_amdgcn_alignbyte(w.y, w.x, 2);
-          a0.z = __builtin_amdgcn_alignbyte(w.z, w.y, 2);
-          a0.w = __builtin_amdgcn_alignbyte(w.w, w.z, 2);
-          if (S == 1) {
-            const uint32_t next = *reinterpret_cast<const uint16_t*>(base + 16);
-            a1 = w;
-            a2.x = a0.y; a2.y = a0.z; a2.z = a0.w;
-            a2.w = (next << 16) | (w.w >> 16);
-          } else {
-            a1 = *reinterpret_cast<const uint4*>(base + 2 * Wo);     // even columns 2 x0 ..
-            a2 = w;
-          }
-          acc[3 * ky][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(wg_bf16x8, a0), gf, acc[3 * ky][t], 0, 0, 0);
-          acc[3 * ky + 1][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(wg_bf16x8, a1), gf, acc[3 * ky + 1][t], 0, 0, 0);
-          acc[3 * ky + 2][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(wg_bf16x8, a2), gf, acc[3 * ky + 2][t], 0, 0, 0);
-        }
-    }
-  }
-  // acc[tap][t][e] = dw[tap][ci = 16 t + 4 q + e][co = 16 wn + r] of this wave's k-steps
-  float* fold = reinterpret_cast<float*>(sm);
-  float* out = partial + (size_t)blockIdx.x * NW;
-  __syncthreads();                            // the tiles are no longer read
-  if constexpr (FOLD_ALL) {
-#pragma unroll
-    for (int tap = 0; tap < 9; ++tap)
-#pragma unroll
-      for (int t = 0; t < CT; ++t)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) fold[kq * NW + (tap * CI + 16 * t + 4 * q + e) * CO + 16 * wn + r] = acc[tap][t][e];
-    __syncthreads();
-    for (int i = tid; i < NW; i += NT) {
-      float v = fold[i];
-#pragma unroll
-      for (int k = 1; k < WK; ++k) v += fold[k * NW + i];
-      out[i] = v;
-    }
-  } else {
-    // two k-splits: the second half of the waves hands its sums over through LDS
-    if (kq == 1) {
-#pragma unroll
-      for (int tap = 0; tap < 9; ++tap)
-#pragma unroll
-        for (int t = 0; t < CT; ++t)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) fold[(tap * CI + 16 * t + 4 * q + e) * CO + 16 * wn + r] = acc[tap][t][e];
-    }
-    __syncthreads();
-    if (kq == 0) {
-#pragma unroll
-      for (int tap = 0; tap < 9; ++tap)
-#pragma unroll
-        for (int t = 0; t < CT; ++t)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int i = (tap * CI + 16 * t + 4 * q + e) * CO + 16 * wn + r;
-            out[i] = acc[tap][t][e] + fold[i];
-          }
-    }
-  }
-}
-
-static size_t wgrad_tiles_lds(int H, int W, int Ci, int Co, int stride) {
-  const size_t tiles = (size_t)Ci * wgt_x_stride(H, W) + (size_t)Co * wgt_dy_stride(H / stride, W / stride);
-  const size_t nw = (size_t)9 * Ci * Co * 4, wk = WGT_WAVES / (Co / 16);
-  const size_t fold = wk * nw <= (size_t)WGT_FOLD_BYTES ? wk * nw : nw;
-  return tiles > fold ? tiles : fold;
-}
-static bool wgrad_tiles_ok(int H, int W, int Ci, int Co, int stride) {
-  const bool chan = stride == 1 ? (Ci == Co && (Ci == 16 || Ci == 32 || Ci == 64))
-                                : ((Ci == 16 && (Co == 32 || Co == 64)) || (Ci == 32 && Co == 64) || (Ci == 64 && Co == 64));
-  if (!chan || stride < 1 || stride > 2 || (H % stride) || (W % stride)) return false;
-  const int Wo = W / stride;
-  return Wo >= 8 && (Wo % 8) == 0 && wgrad_tiles_lds(H, W, Ci, Co, stride) <= 160 * 1024;
-}
-// Workgroups per convolution.  A workgroup costs about 10 us before and after its images (clearing its LDS tiles,
-// folding the k-splits, writing its partial filter) against 1-1.5 us per image, and its LDS footprint lets one or two
-// of them run on a compute unit, so the n convolutions of a launch together get one round of those places and each
-// workgroup walks over several images (measured at 10 convolutions 32 -> 32 on 128 images: 103 workgroups each 31 us
-// + 9 us for adding the partial filters, 51: 26 + 6, 25: 22 + 5, 12: 32 + 5).  n = 1 gives the most there can be
-// (what the partial sums are sized for).
-static int wgrad_tiles_blocks(int B, int n, int places) {
-  int blocks = places / (n < 1 ? 1 : n);
-  blocks = blocks < 1 ? 1 : blocks;
-  return B < blocks ? B : blocks;
-}
-// places for the workgroups of one launch on the current device: compute units x workgroups that fit one unit's LDS
-static int wgrad_tiles_places(size_t lds) {
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-    cus = 256;
-  const size_t per = lds ? ((size_t)160 * 1024) / lds : 2;
-  return cus * (int)(per < 1 ? 1 : (per > 2 ? 2 : per));     // 512 threads each: two at most
-}
-template <int CI, int CO, int S>
-static int wgrad_tiles_launch(hipStream_t s, const WgtGroup& g, int n, int B, int H, int W, int blocks) {
-  const size_t lds = wgrad_tiles_lds(H, W, CI, CO, S);
-  if (lds > 64 * 1024)
-    PPLL_HIP(hipFuncSetAttribute((const void*)conv3x3_wgrad_tiles_kernel<CI, CO, S>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 (int)lds));
-  hipLaunchKernelGGL((conv3x3_wgrad_tiles_kernel<CI, CO, S>), dim3(blocks, n), dim3(64 * WGT_WAVES), lds, s, g, B, H, W);
-  PPLL_HIP(hipGetLastError());
-  return PPLL_OK;
-}
-static int wgrad_tiles_dispatch(hipStream_t s, const WgtGroup& g, int n, int B, int H, int W, int Ci, int Co, int stride,
-                                int blocks) {
-  if (stride == 1) {
-    if (Ci == 16) return wgrad_tiles_launch<16, 16, 1>(s, g, n, B, H, W, blocks);
-    if (Ci == 32) return wgrad_tiles_launch<32, 32, 1>(s, g, n, B, H, W, blocks);
-    return wgrad_tiles_launch<64, 64, 1>(s, g, n, B, H, W, blocks);
-  }
-  if (Ci == 16 && Co == 32) return wgrad_tiles_launch<16, 32, 2>(s, g, n, B, H, W, blocks);
-  if (Ci == 16 && Co == 64) return wgrad_tiles_launch<16, 64, 2>(s, g, n, B, H, W, blocks);
-  if (Ci == 32 && Co == 64) return wgrad_tiles_launch<32, 64, 2>(s, g, n, B, H, W, blocks);
-  return wgrad_tiles_launch<64, 64, 2>(s, g, n, B, H, W, blocks);
-}
-
-size_t conv3x3_wgrad_bf16_partial_floats(int B, int H, int W, int Ci, int Co, int stride) {
-  const long P = (long)B * ((H - 1) / stride + 1) * ((W - 1) / stride + 1);
-  size_t n = (size_t)((P + WG_PIX_F - 1) / WG_PIX_F) * 9 * Ci * Co;
-  if (wgrad_tiles_ok(H, W, Ci, Co, stride)) {
-    const size_t m = (size_t)wgrad_tiles_blocks(B, 1, wgrad_tiles_places(wgrad_tiles_lds(H, W, Ci, Co, stride))) * 9 * Ci * Co;
-    if (m > n) n = m;
-  }
-  return n;
-}
-
-template <int CO, int CPT>
-static int wgrad_launch(hipStream_t s, const void* x, const void* dy, int B, int H, int W, int Ci, int stride,
-                        float* partials, int chunks) {
-  const size_t lds = ((size_t)WG_PIX_F * 9 * Ci + (size_t)WG_PIX_F * CO) * 2;
-  if (lds > 64 * 1024)
-    PPLL_HIP(hipFuncSetAttribute((const void*)conv3x3_wgrad_bf16_kernel<CO, CPT>,
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL((conv3x3_wgrad_bf16_kernel<CO, CPT>), dim3(chunks), dim3(256), lds, s, (const uint16_t*)x,
-                     (const uint16_t*)dy, B, H, W, Ci, stride, partials);
-  PPLL_HIP(hipGetLastError());
-  return PPLL_OK;
-}
-
-int launch_conv3x3_wgrad_bf16(hipStream_t s, const void* x, const void* dy, int B, int H, int W, int Ci, int Co,
-                              int stride, ReduceQueue& rq, float* dw, int ci_keep) {
-  const long P = (long)B * ((H - 1) / stride + 1) * ((W - 1) / stride + 1);
-  const int chunks = (int)((P + WG_PIX_F - 1) / WG_PIX_F), nw = 9 * Ci * Co;
-  const int cpt = Ci / (256 / Co);
-  bool queued;
-  if (wgrad_tiles_ok(H, W, Ci, Co, stride)) {
-    const int blocks = wgrad_tiles_blocks(B, 1, wgrad_tiles_places(wgrad_tiles_lds(H, W, Ci, Co, stride)));
-    float* part = rq.space((size_t)blocks * nw, &queued);
-    WgtGroup g{};
-    g.x[0] = (const uint16_t*)x; g.dy[0] = (const uint16_t*)dy; g.partial[0] = part;
-    PPLL_TRY(wgrad_tiles_dispatch(s, g, 1, B, H, W, Ci, Co, stride, blocks));
-    return reduce_conv_filters(s, rq, queued, part, blocks, Ci, Co, ci_keep, dw);
-  }
-  float* partials = rq.space((size_t)chunks * nw, &queued);
-  int st = PPLL_ERR_CONFIG;
-  if (Co == 16 && cpt == 1) st = wgrad_launch<16, 1>(s, x, dy, B, H, W, Ci, stride, partials, chunks);
-  else if (Co == 32 && cpt == 2) st = wgrad_launch<32, 2>(s, x, dy, B, H, W, Ci, stride, partials, chunks);
-  else if (Co == 32 && cpt == 4) st = wgrad_launch<32, 4>(s, x, dy, B, H, W, Ci, stride, partials, chunks);
-  else if (Co == 32 && cpt == 6) st = wgrad_launch<32, 6>(s, x, dy, B, H, W, Ci, stride, partials, chunks);
-  else if (Co == 32 && cpt == 8) st = wgrad_launch<32, 8>(s, x, dy, B, H, W, Ci, stride, partials, chunks);
-  else if (Co == 64 && cpt == 4) st = wgrad_launch<64, 4>(s, x, dy, B, H, W, Ci, stride, partials, chunks);
-  else if (Co == 64 && cpt == 8) st = wgrad_launch<64, 8>(s, x, dy, B, H, W, Ci, stride, partials, chunks);
-  else if (Co == 64 && cpt == 12) st = wgrad_launch<64, 12>(s, x, dy, B, H, W, Ci, stride, partials, chunks);
-  else if (Co == 64 && cpt == 16) st = wgrad_launch<64, 16>(s, x, dy, B, H, W, Ci, stride, partials, chunks);
-  else set_error("conv3x3 weight gradient: no kernel for %d -> %d channels", Ci, Co);
-  PPLL_TRY(st);
-  return reduce_conv_filters(s, rq, queued, partials, chunks, Ci, Co, ci_keep, dw);
-}
-
-// Weight gradients of n convolutions of one shape in as few launches as possible (16 per launch).  Returns
-// PPLL_OK with *done = false, having launched nothing, when the shape is not one the tiled kernel takes or the
-// queue has no private room left for all partial sums (the caller then launches them one by one).
-int launch_conv3x3_wgrad_group_bf16(hipStream_t s, const ConvWgradJob* jobs, int n, int B, int H, int W, int Ci, int Co,
-                                    int stride, ReduceQueue& rq, bool* done) {
-  *done = false;
-  if (!wgrad_tiles_ok(H, W, Ci, Co, stride)) return PPLL_OK;
-  const int blocks = wgrad_tiles_blocks(B, n < WGT_GROUP ? n : WGT_GROUP, wgrad_tiles_places(wgrad_tiles_lds(H, W, Ci, Co, stride)));
-  const int nw = 9 * Ci * Co;
-  const size_t need = ((size_t)blocks * nw + 63) & ~(size_t)63;
-  if (!rq.arena || rq.used + need * n > rq.arena_floats) return PPLL_OK;
-  for (int j0 = 0; j0 < n; j0 += WGT_GROUP) {
-    const int m = n - j0 < WGT_GROUP ? n - j0 : WGT_GROUP;
-    WgtGroup g{};
-    for (int j = 0; j < m; ++j) {
-      bool queued;
-      g.x[j] = (const uint16_t*)jobs[j0 + j].x; g.dy[j] = (const uint16_t*)jobs[j0 + j].dy;
-      g.partial[j] = rq.space((size_t)blocks * nw, &queued);     // queued: room was checked above
-    }
-    PPLL_TRY(wgrad_tiles_dispatch(s, g, m, B, H, W, Ci, Co, stride, blocks));
-    for (int j = 0; j < m; ++j) PPLL_TRY(reduce_conv_filters(s, rq, true, g.partial[j], blocks, Ci, Co, Ci, jobs[j0 + j].dw));
-  }
-  *done = true;
-  return PPLL_OK;
-}
-
 bool bn_bf16_supported(int dt, int rows, int C, const void* a, const void* b, const void* c, const void* d) {
   if (dt != BF16 || (C % 8) || C < 8 || C > 128 || (256 % (C / 8))) return false;
   if ((size_t)rows * C / 8 >= ((size_t)1 << 32)) return false;   // the kernels index 16-byte chunks with 32 bits

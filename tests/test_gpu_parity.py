@@ -476,6 +476,20 @@ def test_resnet_bf16_fused_convolution_tile_edges(channels, height, width, batch
     run_case(wl, steps=1, check_bn=True, tweak=_decisive_shifts)
 
 
+@pytest.mark.parametrize("img_c,channels,aux,height,width,batch", [
+    # weight gradients: row lengths that no power of two divides, odd maps at stride 2, maps of one output pixel, rows wider than a
+    # tile (cut into pieces), maps higher than a tile, few images; with an image the stem takes its channels to `channels`
+    (0, 16, 64, 3, 530, 1), (0, 64, 64, 5, 7, 3), (0, 32, 32, 6, 12, 5), (0, 48, 64, 9, 5, 2), (0, 48, 32, 4, 4, 3),
+    (0, 64, 32, 7, 9, 2), (0, 16, 16, 2, 2, 20), (48, 32, 64, 2, 150, 2), (32, 64, 64, 3, 280, 1), (64, 32, 32, 3, 10, 2),
+    (16, 64, 64, 150, 2, 1), (48, 64, 64, 4, 6, 3), (16, 32, 64, 4, 6, 3),
+])
+def test_resnet_bf16_weight_gradient_tile_edges(img_c, channels, aux, height, width, batch):
+    image = dict(input_kind=synth.IMAGE, img_h=height, img_w=width, img_c=img_c) if img_c else {}
+    wl = synth.workload("resnet_stage_bf16", n_basic_blocks=1, batch=batch, height=height, width=width, channels=channels,
+                        aux_channels=aux, **image)
+    run_case(wl, steps=1, check_bn=True, tweak=_decisive_shifts)
+
+
 def test_resnet_bf16_stage_full_size_natural_statistics():
     run_case(synth.workload("resnet_stage_bf16"), steps=2, check_bn=True)
 
