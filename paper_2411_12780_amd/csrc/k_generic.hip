@@ -170,36 +170,56 @@ constexpr int RED_BATCH = 40;   // the table stays below the 4 KB of a kernel's 
 struct ReduceBatch { int n; int first[RED_BATCH + 1]; int vec4[RED_BATCH]; ReduceJob job[RED_BATCH]; };
 __global__ __launch_bounds__(256) void reduce_batch_kernel(ReduceBatch a) {
   __shared__ float red[16][65];
-  __shared__ float outer_red[16][16 * OUTER_MAX];
+  __shared__ float outer_red[64][4 * OUTER_MAX + 1];
   int j = 0;
   while (j + 1 < a.n && (int)blockIdx.x >= a.first[j + 1]) ++j;
   const float* partial = a.job[j].src;
   const int chunks = a.job[j].chunks, N = a.job[j].N;
   const long stride = a.job[j].stride;
   const int col = threadIdx.x & 15, grp = threadIdx.x >> 4;
-  if (a.job[j].outer) {   // 16 columns n, the 16 thread groups take the rows round-robin, eight rows in flight
+  if (a.job[j].outer) {
+    // four columns n and all c: a thread takes 4 n x 4 c of a row, the 64 groups of four threads take the rows round-robin,
+    // four in flight, and are added in group order.  (16 n a workgroup, a thread one n and 16 c of every 16th row: a
+    // load for every product, 20 us at 1024 rows; so the whole launch takes 10.)
+    static_assert(OUTER_MAX == 16, "four threads of four c");
     const float* dl = a.job[j].outer;
-    const int C = a.job[j].outer_n, n = ((int)blockIdx.x - a.first[j]) * 16 + col, nc = min(n, N - 1);
-    float acc[OUTER_MAX] = {};
-    for (int r0 = grp; r0 < chunks; r0 += 16 * 8) {
-      float z[8];
+    const int C = a.job[j].outer_n, n0 = ((int)blockIdx.x - a.first[j]) * 4, c0 = 4 * (threadIdx.x & 3), g4 = threadIdx.x >> 2;
+    float acc[4][4] = {};
+    constexpr int U = 4;
+    for (int r0 = g4; r0 < chunks; r0 += 64 * U) {
+      float z[U][4], d[U][4];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) z[u] = r0 + 16 * u < chunks ? partial[(size_t)(r0 + 16 * u) * stride + nc] : 0.f;
+      for (int u = 0; u < U; ++u) {
+        const bool in = r0 + 64 * u < chunks;
+        const float* zp = partial + (size_t)(r0 + 64 * u) * stride;
+        const float* dp = dl + (size_t)(r0 + 64 * u) * C;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const float* d = dl + (size_t)min(r0 + 16 * u, chunks - 1) * C;
-#pragma unroll
-        for (int c = 0; c < OUTER_MAX; ++c) acc[c] = fmaf(z[u], d[min(c, C - 1)], acc[c]);
+        for (int e = 0; e < 4; ++e) {
+          z[u][e] = in ? zp[min(n0 + e, N - 1)] : 0.f;
+          d[u][e] = in ? dp[min(c0 + e, C - 1)] : 0.f;
+        }
       }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) acc[e][c] = fmaf(z[u][e], d[u][c], acc[e][c]);
     }
 #pragma unroll
-    for (int c = 0; c < OUTER_MAX; ++c) outer_red[grp][col * OUTER_MAX + c] = acc[c];
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) outer_red[g4][e * OUTER_MAX + c0 + c] = acc[e][c];
     __syncthreads();
+    const int o = threadIdx.x & 63, quarter = threadIdx.x >> 6;
     float t = 0.f;
 #pragma unroll
-    for (int g = 0; g < 16; ++g) t += outer_red[g][threadIdx.x];
-    const int c = threadIdx.x % OUTER_MAX, m = ((int)blockIdx.x - a.first[j]) * 16 + threadIdx.x / OUTER_MAX;
-    if (c < C && m < N) a.job[j].dst[(size_t)m * C + c] = t * a.job[j].scale;
+    for (int g = 0; g < 16; ++g) t += outer_red[16 * quarter + g][o];
+    red[quarter][o] = t;
+    __syncthreads();
+    const int c = o % OUTER_MAX, m = n0 + o / OUTER_MAX;
+    if (quarter == 0 && c < C && m < N)
+      a.job[j].dst[(size_t)m * C + c] = (red[0][o] + red[1][o] + red[2][o] + red[3][o]) * a.job[j].scale;
     return;
   }
   if (a.vec4[j]) {
@@ -273,7 +293,7 @@ int ReduceQueue::reduce_outer(hipStream_t s, bool queued, const float* src, int 
   const ReduceJob job{src, out, rows, N, N, 1.0f, outer, outer_n};
   if (queued) { jobs.push_back(job); return PPLL_OK; }
   ReduceBatch b{};
-  b.n = 1; b.job[0] = job; b.first[1] = (N + 15) / 16;
+  b.n = 1; b.job[0] = job; b.first[1] = (N + 3) / 4;
   hipLaunchKernelGGL(reduce_batch_kernel, dim3(b.first[1]), dim3(256), 0, s, b);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;
@@ -289,7 +309,7 @@ int ReduceQueue::flush(hipStream_t s) {
       b.first[j] = blocks;
       const ReduceJob& q = b.job[j];
       b.vec4[j] = !q.outer && q.N >= 64 && (q.N % 4) == 0 && (q.stride % 4) == 0 && !(((uintptr_t)q.src) & 15);
-      blocks += b.vec4[j] ? (q.N + 63) / 64 : (q.N + 15) / 16;
+      blocks += q.outer ? (q.N + 3) / 4 : b.vec4[j] ? (q.N + 63) / 64 : (q.N + 15) / 16;
     }
     b.first[b.n] = blocks;
     if (blocks > 0) {
