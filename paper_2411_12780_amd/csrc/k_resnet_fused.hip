@@ -431,8 +431,8 @@ int launch_conv_bn_fwd(hipStream_t s, const BnInput* bn, const void* x, const vo
     if (!cb_al16(bn->res) || !cb_al16(bn->y)) { set_error("conv_bn: unaligned tensors"); return PPLL_ERR_CONFIG; }
   }
   if (!cb_al16(p.x) || !cb_al16(w) || !cb_al16(dst)) { set_error("conv_bn: unaligned tensors"); return PPLL_ERR_CONFIG; }
-  void* prof = nullptr;   // algorithmic bytes: input, output and filter once, the residual and the stored activation where present
-  PPLL_TRY(profile_begin(s, 2.0 * ((double)B * H * W * C * (2 + (bn ? 1 : 0) + (bn && bn->res ? 1 : 0)) + 9.0 * C * C), &prof, 1));
+  void* prof = nullptr;   // the bytes of the convolution alone: input, output and filter once
+  PPLL_TRY(profile_begin(s, 2.0 * (2.0 * B * H * W * C + 9.0 * C * C), &prof, 1));
   PPLL_TRY(conv_bn_dispatch<false>(s, p, B, H, W, C, stat_blocks));
   return profile_end(s, prof);
 }
@@ -451,8 +451,8 @@ int launch_conv_bn_bwd(hipStream_t s, const BnGrad& bn, const void* w, int B, in
   }
   for (const void* q : {(const void*)p.x, (const void*)p.aux, (const void*)d, w, (const void*)dst, dres, (const void*)p.nx})
     if (!cb_al16(q)) { set_error("conv_bn: unaligned tensors"); return PPLL_ERR_CONFIG; }
-  void* prof = nullptr;   // algorithmic bytes: dy, x, d, dst and filter once, the shortcut gradient where present
-  PPLL_TRY(profile_begin(s, 2.0 * ((double)B * H * W * C * (4 + (dres ? 1 : 0)) + 9.0 * C * C), &prof, 1));
+  void* prof = nullptr;   // the bytes of the convolution alone: its two maps and the filter once, the shortcut gradient where present
+  PPLL_TRY(profile_begin(s, 2.0 * ((double)B * H * W * C * (dres ? 3.0 : 2.0) + 9.0 * C * C), &prof, 1));
   PPLL_TRY(conv_bn_dispatch<true>(s, p, B, H, W, C, stat_blocks));
   return profile_end(s, prof);
 }
