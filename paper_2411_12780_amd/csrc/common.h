@@ -127,6 +127,9 @@ int launch_gemm_generic(hipStream_t s, const GemmArgs& g);
 // Products with few output rows (the class-token rows of a pruned auxiliary layer): see k_gemm_rows.hip
 bool gemm_rows_supported(const GemmArgs& g);
 int launch_gemm_rows(hipStream_t s, const GemmArgs& g);
+// Products with many output tiles, bf16 output: see k_gemm_pipe.hip.  The choice (0: not this kernel) goes to the launch.
+int gemm_pipe_choice(const GemmArgs& g);
+int launch_gemm_pipe(hipStream_t s, const GemmArgs& g, int choice);
 // fp32 products on the matrix cores: see k_f32.hip
 bool gemm_f32_supported(const GemmArgs& g);
 bool gemm_f32_groupable(const GemmArgs& g);

@@ -23,14 +23,6 @@ __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t r, lds_char* 
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, voff, 0, 0, 0);
 }
 
-// Fragment reads are inline assembly: the compiler would order every LDS read it knows of behind all outstanding copies into
-// LDS.  Their results count as ready at once for the compiler, so every use sits behind a wait that names the registers.
-template <int OFF> __device__ __forceinline__ void lds_read16(u32x4& d, int addr) {
-  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF));
-}
-template <int OFF> __device__ __forceinline__ void lds_read_tr(u32x2& d, int addr) {
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(d) : "v"(addr), "n"(OFF));
-}
 template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
 // One operand: ROWS rows (m or n) x KS k per stage.
@@ -49,11 +41,13 @@ template <bool TR, int ROWS> struct Operand {
   int vbase;      // byte offset this lane fetches from at k = 0, copy 0
   int gk;         // TR = false: first k (within the stage) of the lane's granule
   int ld2;        // bytes between rows (TR: between k rows)
-  __device__ __forceinline__ void init(long ld, int row0, int nrows, int lane) {
+  // wave: the k rows of a wave's copies differ from those of its first by a multiple of 4 (an even number of waves of 2 rows,
+  // or 4 rows a copy), so the window permutation is the same in all of them
+  __device__ __forceinline__ void init(long ld, int row0, int nrows, int lane, int wave) {
     ld2 = (int)(ld * 2);
     if (TR) {
       constexpr int SL = PITCH / 16;                     // 16-byte slots of a k row
-      const int kr = lane / SL, slot = lane % SL, win = (slot >> 2) ^ (kr & 3);   // STEP_ROWS is 2 or 4
+      const int kr = lane / SL, slot = lane % SL, win = (slot >> 2) ^ ((kr + STEP_ROWS * wave) & 3);   // STEP_ROWS is 2 or 4
       const int col = row0 + (win * 4 + (slot & 3)) * 8;
       vbase = col < nrows ? kr * ld2 + col * 2 : OOB_BASE;
       gk = kr;
@@ -65,28 +59,28 @@ template <bool TR, int ROWS> struct Operand {
   }
 };
 
-template <bool AT, bool BT, int WGM, int WGN, int IM, int JN, int NS> struct Shape {
-  static constexpr int W = WGM * WGN, THREADS = 64 * W, BM = WGM * IM * 32, BN = WGN * JN * 32;
+// A workgroup of WGM_ x WGN_ waves, each 32 IM_ x 64 of the output tile, and NS_ stages in LDS
+template <bool AT, bool BT, int WGM_, int WGN_, int IM_, int NS_> struct Shape {
+  static constexpr int WGN = WGN_, IM = IM_, NS = NS_, W = WGM_ * WGN_, THREADS = 64 * W, BM = WGM_ * IM * 32, BN = WGN_ * 64;
   using OA = Operand<AT, BM>;
   using OB = Operand<BT, BN>;
   static constexpr int STAGE = OA::BYTES + OB::BYTES, LDS = NS * STAGE;
-  static constexpr int COPIES = (OA::COPIES + OB::COPIES) / W;   // per wave and stage
-  static_assert((OA::COPIES + OB::COPIES) % W == 0, "");
+  static constexpr int COPIES = OA::COPIES / W + OB::COPIES / W;   // per wave and stage, of some waves one more
+  static_assert(OB::COPIES % W == 0 && (!AT || OA::COPIES % W == 0) && W % 2 == 0 && NS >= 3, "");
 };
 
-
-// 8 consecutive k of one row per lane (an MFMA operand)
-template <bool TR> struct Frag;
-template <> struct Frag<false> {
-  u32x4 v;
-  __device__ __forceinline__ void tie() { asm volatile("" : "+v"(v)); }
-  __device__ __forceinline__ bf16x8 get() const { return __builtin_bit_cast(bf16x8, v); }
+// The fragments (8 consecutive k of one row per lane) of a wave's tile, 32 IM rows of A and 64 of B, at one k step of 16.  A
+// transposing read gives half of one.
+template <bool TR, int N> struct Frags {
+  u32x4 v[N];
+  __device__ __forceinline__ u32x4 get(int i) const { return v[i]; }
 };
-template <> struct Frag<true> {
-  u32x2 lo, hi;   // put together only behind the wait
-  __device__ __forceinline__ void tie() { asm volatile("" : "+v"(lo), "+v"(hi)); }
-  __device__ __forceinline__ bf16x8 get() const { return __builtin_bit_cast(bf16x8, (u32x4){lo.x, lo.y, hi.x, hi.y}); }
+template <int N> struct Frags<true, N> {
+  u32x2 lo[N], hi[N];
+  __device__ __forceinline__ u32x4 get(int i) const { return (u32x4){lo[i].x, lo[i].y, hi[i].x, hi[i].y}; }
 };
+template <int N> __device__ __forceinline__ void set_zero(Frags<false, N>& f, int i) { f.v[i] = (u32x4){0, 0, 0, 0}; }
+template <int N> __device__ __forceinline__ void set_zero(Frags<true, N>& f, int i) { f.lo[i] = f.hi[i] = (u32x2){0, 0}; }
 // Lane address of MFMA tile 0 of a wave (rows row0 .. row0 + 31, row0 a multiple of 32 x tiles of the wave), k step 0, stage 0
 template <bool TR, int ROWS> __device__ __forceinline__ int frag_base(int region, int row0, int lane) {
   if (TR) {
@@ -96,41 +90,109 @@ template <bool TR, int ROWS> __device__ __forceinline__ int frag_base(int region
   const int r = lane & 31;
   return region + (row0 + r) * 64 + (((lane >> 5) ^ ((r >> 2) & 3)) << 4);
 }
-// fragments of N tiles, 32 rows apart, at k step KK (16 k) of a stage; addr = frag_base + stage offset
-template <bool TR, int ROWS, int N, int KK, int I = 0> __device__ __forceinline__ void read_frags(Frag<TR> (&f)[N], int addr) {
-  if constexpr (I < N) {
-    if constexpr (TR) {
-      constexpr int P = ROWS * 2;
-      const int a = addr ^ (I << 6);
-      lds_read_tr<KK * 16 * P>(f[I].lo, a);
-      lds_read_tr<KK * 16 * P + 4 * P>(f[I].hi, a);
-    } else {
-      lds_read16<I * 2048>(f[I].v, KK ? addr ^ 32 : addr);
-    }
-    read_frags<TR, ROWS, N, KK, I + 1>(f, addr);
+
+// One k step of a wave: the products of the fragments at hand, and under them the reads of the next fragments (k step KK
+// of the stage that addrA, addrB point into), which have arrived when the block ends.  It is one assembly block because the
+// compiler would order LDS reads that it knows of behind all outstanding copies into LDS; the wait is inside, so every output
+// is there when the compiler thinks it is.  The s_nop covers a register of the products written by a vector instruction before.
+#define PPLL_MMA(J, I) "v_mfma_f32_32x32x16_bf16 %[c" #J #I "], %[q" #J "], %[p" #I "], %[c" #J #I "]\n"
+#define PPLL_ACC [c00] "+v"(acc[0][0]), [c01] "+v"(acc[0][1]), [c02] "+v"(acc[0][2]), [c03] "+v"(acc[0][3]), \
+                 [c10] "+v"(acc[1][0]), [c11] "+v"(acc[1][1]), [c12] "+v"(acc[1][2]), [c13] "+v"(acc[1][3])
+#define PPLL_CUR [p0] "v"(a.get(0)), [p1] "v"(a.get(1)), [p2] "v"(a.get(2)), [p3] "v"(a.get(3)), [q0] "v"(b.get(0)), [q1] "v"(b.get(1))
+template <bool AT, bool BT, int ROWS_A, int ROWS_B, int KK, int IM>
+__device__ __forceinline__ void k_step(f32x16 (&acc)[2][IM], const Frags<AT, IM>& a, const Frags<BT, 2>& b, Frags<AT, IM>& na, Frags<BT, 2>& nb,
+                                       int addrA, int addrB) {
+  static_assert(IM == 4 || (IM == 5 && !AT), "");
+  constexpr int PA = ROWS_A * 2, PB = ROWS_B * 2;
+  if constexpr (IM == 5 && BT) {
+    asm volatile("s_nop 1\n" PPLL_MMA(0, 0)
+                 "ds_read_b64_tr_b16 %[l0], %[rb0] offset:%[ol]\n ds_read_b64_tr_b16 %[h0], %[rb0] offset:%[oh]\n" PPLL_MMA(0, 1)
+                 "ds_read_b128 %[x0], %[ra]\n ds_read_b128 %[x1], %[ra] offset:2048\n" PPLL_MMA(0, 2)
+                 "ds_read_b128 %[x2], %[ra] offset:4096\n ds_read_b128 %[x3], %[ra] offset:6144\n" PPLL_MMA(0, 3)
+                 "ds_read_b128 %[x4], %[ra] offset:8192\n ds_read_b64_tr_b16 %[l1], %[rb1] offset:%[ol]\n" PPLL_MMA(0, 4)
+                 "ds_read_b64_tr_b16 %[h1], %[rb1] offset:%[oh]\n"
+                 PPLL_MMA(1, 0) PPLL_MMA(1, 1) PPLL_MMA(1, 2) PPLL_MMA(1, 3) PPLL_MMA(1, 4) "s_waitcnt lgkmcnt(0)"
+                 : PPLL_ACC, [c04] "+v"(acc[0][4]), [c14] "+v"(acc[1][4]), [x0] "=&v"(na.v[0]), [x1] "=&v"(na.v[1]), [x2] "=&v"(na.v[2]),
+                   [x3] "=&v"(na.v[3]), [x4] "=&v"(na.v[4]), [l0] "=&v"(nb.lo[0]), [h0] "=&v"(nb.hi[0]), [l1] "=&v"(nb.lo[1]), [h1] "=&v"(nb.hi[1])
+                 : PPLL_CUR, [p4] "v"(a.get(4)), [ra] "v"(KK ? addrA ^ 32 : addrA), [rb0] "v"(addrB), [rb1] "v"(addrB ^ 64),
+                   [ol] "n"(KK * 16 * PB), [oh] "n"(KK * 16 * PB + 4 * PB)
+                 : "memory");
+  } else if constexpr (IM == 5) {
+    asm volatile("s_nop 1\n" PPLL_MMA(0, 0) "ds_read_b128 %[y0], %[rb]\n ds_read_b128 %[x0], %[ra]\n" PPLL_MMA(0, 1)
+                 "ds_read_b128 %[x1], %[ra] offset:2048\n ds_read_b128 %[x2], %[ra] offset:4096\n" PPLL_MMA(0, 2)
+                 "ds_read_b128 %[x3], %[ra] offset:6144\n ds_read_b128 %[x4], %[ra] offset:8192\n" PPLL_MMA(0, 3)
+                 "ds_read_b128 %[y1], %[rb] offset:2048\n" PPLL_MMA(0, 4)
+                 PPLL_MMA(1, 0) PPLL_MMA(1, 1) PPLL_MMA(1, 2) PPLL_MMA(1, 3) PPLL_MMA(1, 4) "s_waitcnt lgkmcnt(0)"
+                 : PPLL_ACC, [c04] "+v"(acc[0][4]), [c14] "+v"(acc[1][4]), [x0] "=&v"(na.v[0]), [x1] "=&v"(na.v[1]), [x2] "=&v"(na.v[2]),
+                   [x3] "=&v"(na.v[3]), [x4] "=&v"(na.v[4]), [y0] "=&v"(nb.v[0]), [y1] "=&v"(nb.v[1])
+                 : PPLL_CUR, [p4] "v"(a.get(4)), [ra] "v"(KK ? addrA ^ 32 : addrA), [rb] "v"(KK ? addrB ^ 32 : addrB)
+                 : "memory");
+  } else
+  if constexpr (!AT && BT) {
+    asm volatile("s_nop 1\n" PPLL_MMA(0, 0)
+                 "ds_read_b64_tr_b16 %[l0], %[rb0] offset:%[ol]\n ds_read_b64_tr_b16 %[h0], %[rb0] offset:%[oh]\n" PPLL_MMA(0, 1)
+                 "ds_read_b128 %[x0], %[ra]\n ds_read_b128 %[x1], %[ra] offset:2048\n" PPLL_MMA(0, 2)
+                 "ds_read_b128 %[x2], %[ra] offset:4096\n ds_read_b128 %[x3], %[ra] offset:6144\n" PPLL_MMA(0, 3)
+                 "ds_read_b64_tr_b16 %[l1], %[rb1] offset:%[ol]\n ds_read_b64_tr_b16 %[h1], %[rb1] offset:%[oh]\n"
+                 PPLL_MMA(1, 0) PPLL_MMA(1, 1) PPLL_MMA(1, 2) PPLL_MMA(1, 3) "s_waitcnt lgkmcnt(0)"
+                 : PPLL_ACC, [x0] "=&v"(na.v[0]), [x1] "=&v"(na.v[1]), [x2] "=&v"(na.v[2]), [x3] "=&v"(na.v[3]),
+                   [l0] "=&v"(nb.lo[0]), [h0] "=&v"(nb.hi[0]), [l1] "=&v"(nb.lo[1]), [h1] "=&v"(nb.hi[1])
+                 : PPLL_CUR, [ra] "v"(KK ? addrA ^ 32 : addrA), [rb0] "v"(addrB), [rb1] "v"(addrB ^ 64), [ol] "n"(KK * 16 * PB),
+                   [oh] "n"(KK * 16 * PB + 4 * PB)
+                 : "memory");
+  } else if constexpr (!AT && !BT) {
+    asm volatile("s_nop 1\n" PPLL_MMA(0, 0) "ds_read_b128 %[y0], %[rb]\n ds_read_b128 %[x0], %[ra]\n" PPLL_MMA(0, 1)
+                 "ds_read_b128 %[x1], %[ra] offset:2048\n ds_read_b128 %[x2], %[ra] offset:4096\n" PPLL_MMA(0, 2)
+                 "ds_read_b128 %[x3], %[ra] offset:6144\n ds_read_b128 %[y1], %[rb] offset:2048\n" PPLL_MMA(0, 3)
+                 PPLL_MMA(1, 0) PPLL_MMA(1, 1) PPLL_MMA(1, 2) PPLL_MMA(1, 3) "s_waitcnt lgkmcnt(0)"
+                 : PPLL_ACC, [x0] "=&v"(na.v[0]), [x1] "=&v"(na.v[1]), [x2] "=&v"(na.v[2]), [x3] "=&v"(na.v[3]), [y0] "=&v"(nb.v[0]),
+                   [y1] "=&v"(nb.v[1])
+                 : PPLL_CUR, [ra] "v"(KK ? addrA ^ 32 : addrA), [rb] "v"(KK ? addrB ^ 32 : addrB)
+                 : "memory");
+  } else {
+    static_assert(AT && BT, "");
+    asm volatile("s_nop 1\n" PPLL_MMA(0, 0)
+                 "ds_read_b64_tr_b16 %[m0], %[rb0] offset:%[ol]\n ds_read_b64_tr_b16 %[n0], %[rb0] offset:%[oh]\n"
+                 "ds_read_b64_tr_b16 %[l0], %[ra0] offset:%[al]\n ds_read_b64_tr_b16 %[h0], %[ra0] offset:%[ah]\n" PPLL_MMA(0, 1)
+                 "ds_read_b64_tr_b16 %[l1], %[ra1] offset:%[al]\n ds_read_b64_tr_b16 %[h1], %[ra1] offset:%[ah]\n"
+                 "ds_read_b64_tr_b16 %[l2], %[ra2] offset:%[al]\n ds_read_b64_tr_b16 %[h2], %[ra2] offset:%[ah]\n" PPLL_MMA(0, 2)
+                 "ds_read_b64_tr_b16 %[l3], %[ra3] offset:%[al]\n ds_read_b64_tr_b16 %[h3], %[ra3] offset:%[ah]\n" PPLL_MMA(0, 3)
+                 "ds_read_b64_tr_b16 %[m1], %[rb1] offset:%[ol]\n ds_read_b64_tr_b16 %[n1], %[rb1] offset:%[oh]\n"
+                 PPLL_MMA(1, 0) PPLL_MMA(1, 1) PPLL_MMA(1, 2) PPLL_MMA(1, 3) "s_waitcnt lgkmcnt(0)"
+                 : PPLL_ACC, [l0] "=&v"(na.lo[0]), [h0] "=&v"(na.hi[0]), [l1] "=&v"(na.lo[1]), [h1] "=&v"(na.hi[1]),
+                   [l2] "=&v"(na.lo[2]), [h2] "=&v"(na.hi[2]), [l3] "=&v"(na.lo[3]), [h3] "=&v"(na.hi[3]), [m0] "=&v"(nb.lo[0]),
+                   [n0] "=&v"(nb.hi[0]), [m1] "=&v"(nb.lo[1]), [n1] "=&v"(nb.hi[1])
+                 : PPLL_CUR, [ra0] "v"(addrA), [ra1] "v"(addrA ^ 64), [ra2] "v"(addrA ^ 128), [ra3] "v"(addrA ^ 192), [rb0] "v"(addrB),
+                   [rb1] "v"(addrB ^ 64), [al] "n"(KK * 16 * PA), [ah] "n"(KK * 16 * PA + 4 * PA), [ol] "n"(KK * 16 * PB),
+                   [oh] "n"(KK * 16 * PB + 4 * PB)
+                 : "memory");
   }
 }
-template <int N> __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N < 15 ? N : 15) : "memory"); }
+#undef PPLL_MMA
+#undef PPLL_ACC
+#undef PPLL_CUR
 
 // What one call multiplies: k from k_beg (a multiple of KS) on, nk stages, k >= k_end reads as zero (k_end beyond the operand
 // when its k index is the outer one: the buffer ends there).
 struct Range { int k_beg, nk, k_end; };
 
 // acc[jn][im]: C^T tiles (the B fragment goes first into the MFMA): lane l holds row im*32 + l%32, columns jn*32 + 8 q +
-// 4 (l/32) + e in element 4 q + e.  csum (COLSUM): per-lane sums over k of B's rows, in the same layout.
-template <class S, bool AT, bool BT, int WGM, int WGN, int IM, int JN, int NS, bool COLSUM>
+// 4 (l/32) + e in element 4 q + e.  csum[jn] (COLSUM, wave-uniform do_colsum): this lane's share, its half of every k step, of
+// the sum over k of B's row jn*32 + l%32.
+template <class S, bool AT, bool BT, bool COLSUM>
 __device__ __forceinline__ void multiply(const __amdgpu_buffer_rsrc_t rsA, const __amdgpu_buffer_rsrc_t rsB, long lda, long ldb,
-                                         int m0, int n0, int M, int N, const Range rg, lds_char* lds, f32x16 (&acc)[JN][IM],
-                                         f32x16 (&csum)[JN], bool do_colsum) {
+                                         int m0, int n0, int M, int N, const Range rg, lds_char* lds, f32x16 (&acc)[2][S::IM],
+                                         float (&csum)[2], bool do_colsum) {
+  constexpr int NS = S::NS, IM = S::IM;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / WGN, wn = wave % WGN;
+  const int wm = wave / S::WGN, wn = wave % S::WGN;
   using OA = typename S::OA;
   using OB = typename S::OB;
   OA oa;
   OB ob;
-  oa.init(lda, m0, M, lane);
-  ob.init(ldb, n0, N, lane);
+  oa.init(lda, m0, M, lane, wave);
+  ob.init(ldb, n0, N, lane, wave);
   auto issue = [&](int i) {       // copies of stage i (all zeros past the last one)
     const int k0 = rg.k_beg + i * KS;
     const bool live = i < rg.nk;
@@ -141,9 +203,9 @@ __device__ __forceinline__ void multiply(const __amdgpu_buffer_rsrc_t rsA, const
     if (BT) vb = live ? ob.vbase + k0 * ob.ld2 : OOB_BASE;
     else vb = live && k0 + ob.gk < rg.k_end ? ob.vbase + k0 * 2 : OOB_BASE;
 #pragma unroll
-    for (int c = 0; c < OA::COPIES / S::W; ++c) {
+    for (int c = 0; c < (OA::COPIES + S::W - 1) / S::W; ++c) {
       const int q = c * S::W + wave;
-      load_to_lds(rsA, st + q * 1024, va + q * OA::STEP_ROWS * oa.ld2);
+      if (c < OA::COPIES / S::W || q < OA::COPIES) load_to_lds(rsA, st + q * 1024, va + q * OA::STEP_ROWS * oa.ld2);
     }
 #pragma unroll
     for (int c = 0; c < OB::COPIES / S::W; ++c) {
@@ -152,51 +214,44 @@ __device__ __forceinline__ void multiply(const __amdgpu_buffer_rsrc_t rsA, const
     }
   };
   const int base = (int)(uintptr_t)lds;
-  const int fa0 = frag_base<AT, S::BM>(base, wm * IM * 32, lane), fb0 = frag_base<BT, S::BN>(base + OA::BYTES, wn * JN * 32, lane);
-  Frag<AT> a0[IM], a1[IM];
-  Frag<BT> b0[JN], b1[JN];
-  constexpr int READS = IM * (AT ? 2 : 1) + JN * (BT ? 2 : 1);
-  const bf16x8 ones = {(__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f};
-  auto mma = [&](Frag<AT> (&a)[IM], Frag<BT> (&b)[JN]) {
+  const int fa0 = frag_base<AT, S::BM>(base, wm * IM * 32, lane), fb0 = frag_base<BT, S::BN>(base + OA::BYTES, wn * 64, lane);
+  Frags<AT, IM> a0, a1;
+  Frags<BT, 2> b0, b1;
+  auto column_sums = [&](const Frags<BT, 2>& b) {
+    if (!COLSUM || !do_colsum) return;
 #pragma unroll
-    for (int i = 0; i < IM; ++i) a[i].tie();
+    for (int j = 0; j < 2; ++j) {
+      const u32x4 v = b.get(j);
 #pragma unroll
-    for (int j = 0; j < JN; ++j) b[j].tie();
-#pragma unroll
-    for (int j = 0; j < JN; ++j) {
-      const bf16x8 fb = b[j].get();
-#pragma unroll
-      for (int i = 0; i < IM; ++i) acc[j][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb, a[i].get(), acc[j][i], 0, 0, 0);
-      if (COLSUM && do_colsum) csum[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb, ones, csum[j], 0, 0, 0);
+      for (int e = 0; e < 4; ++e) { csum[j] += __uint_as_float(v[e] << 16); csum[j] += __uint_as_float(v[e] & 0xffff0000u); }
     }
   };
 #pragma unroll
   for (int i = 0; i < NS - 1; ++i) issue(i);
   wait_vm<(NS - 2) * S::COPIES>();
   __builtin_amdgcn_s_barrier();
-  read_frags<AT, S::BM, IM, 0>(a0, fa0);
-  read_frags<BT, S::BN, JN, 0>(b0, fb0);
+  // the first fragments: products with zeros under the reads (the accumulators stay zero)
+#pragma unroll
+  for (int i = 0; i < IM; ++i) set_zero(a1, i);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) set_zero(b1, j);
+  k_step<AT, BT, S::BM, S::BN, 0, IM>(acc, a1, b1, a0, b0, fa0, fb0);
   for (int i = 0; i < rg.nk; ++i) {
     const int st = (i % NS) * S::STAGE, nx = ((i + 1) % NS) * S::STAGE;
     wait_vm<(NS - 3) * S::COPIES>();       // this wave's part of stage i + 1 is in LDS
     __builtin_amdgcn_s_barrier();          // and everyone's; nobody reads stage i - 1 any more
     issue(i + NS - 1);
-    read_frags<AT, S::BM, IM, 1>(a1, fa0 + st);
-    read_frags<BT, S::BN, JN, 1>(b1, fb0 + st);
-    wait_lds<READS>();
-    mma(a0, b0);
-    __builtin_amdgcn_sched_barrier(0);
-    read_frags<AT, S::BM, IM, 0>(a0, fa0 + nx);
-    read_frags<BT, S::BN, JN, 0>(b0, fb0 + nx);
-    wait_lds<READS>();
-    mma(a1, b1);
-    __builtin_amdgcn_sched_barrier(0);
+    column_sums(b0);
+    k_step<AT, BT, S::BM, S::BN, 1, IM>(acc, a0, b0, a1, b1, fa0 + st, fb0 + st);
+    column_sums(b1);
+    k_step<AT, BT, S::BM, S::BN, 0, IM>(acc, a1, b1, a0, b0, fa0 + nx, fb0 + nx);
   }
-  wait_lds<0>();
+  // the last products are through before a vector instruction reads the accumulators
+  asm volatile("s_nop 15\n s_nop 3" ::: "memory");
 #pragma unroll
-  for (int i = 0; i < IM; ++i) a0[i].tie();
+  for (int j = 0; j < 2; ++j)
 #pragma unroll
-  for (int j = 0; j < JN; ++j) b0[j].tie();
+    for (int i = 0; i < IM; ++i) asm volatile("" : "+v"(acc[j][i]));
   wait_vm<0>();
   __builtin_amdgcn_s_barrier();            // the stages are free for the epilogue
 }

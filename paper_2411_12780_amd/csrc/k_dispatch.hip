@@ -59,6 +59,7 @@ int profile_end(hipStream_t s, void* token) {
 
 int launch_gemm(hipStream_t s, const GemmArgs& g) {
   if (gemm_rows_supported(g)) return launch_gemm_rows(s, g);   // few output rows: latency, not throughput
+  if (const int im = gemm_pipe_choice(g)) return launch_gemm_pipe(s, g, im);                // many tiles: throughput
   if (gemm_mfma_supported(g)) return launch_gemm_mfma(s, g, g.splitk_ws, g.splitk_floats);
   return gemm_f32_supported(g) ? launch_gemm_f32(s, g) : launch_gemm_generic(s, g);
 }

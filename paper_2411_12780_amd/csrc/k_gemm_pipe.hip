@@ -1,0 +1,223 @@
+// Linear-layer products with many output tiles: C[M,N] = A[M,K] B, bf16 operands, fp32 accumulation, the epilogues of the
+// tiled kernel, bit-identical results (the same order of k).
+//
+// The tiled kernel is held by the data movement of a 128 x 128 tile: 32 KB into LDS and 96 KB of LDS traffic per 64 k, through
+// registers, a wave reading 64 x 64.  Here a wave owns 128 x 64 or 160 x 64 of a 128 x 256 or 160 x 256 tile, a quarter to a
+// third less to fill and to read per product; operands go straight to LDS, three stages of 32 k deep; the fragment reads of a
+// k step run under the products of the one before.  Two workgroups share a compute unit (72 or 78 KB of LDS each), so that one
+// stores its tile under the other's products.  One 256 x 256 tile per unit, with less traffic still, was slower (25216 x 768 x
+// 3072: 153 us, 25216 x 2304 x 768: 112): nothing runs under its epilogue.
+// Microseconds, tiled kernel -> this one: 25216 x 768 x 3072 145 -> 115 (1037 TFLOP/s), 25216 x 2304 x 768 133 -> 99, 25216 x
+// 3072 x 768 with GELU 223 -> 180 and with its derivative 194 -> 165 (310 MB of epilogue traffic each), 8320 x 1536 x 384 with
+// GELU 31.6 -> 28.1.  What bounds it: LDS traffic beside the products in the main loop, and the epilogue where K is short.
+#include "common.h"
+#include "gemm_pipe.h"
+#include <atomic>
+#include <cmath>
+
+namespace ppll {
+
+namespace {
+using namespace pipe;
+
+struct PipeArgs {
+  const uint16_t* A; long lda;      // A[m*lda + k]
+  const uint16_t* B; long ldb;      // BT ? B[k*ldb + n] : B[n*ldb + k]
+  uint16_t* C; long ldc;
+  int M, N, K, tiles_n, tiles, per_xcd;
+  const float* bias;
+  const uint16_t* residual; long ldr;
+  int epilogue;
+  uint16_t* C2;
+  const uint16_t* aux; long ldaux;
+  uint32_t a_bytes, b_bytes, c_bytes, r_bytes, aux_bytes;
+};
+
+__device__ __forceinline__ u32x4 pipe_load16(__amdgpu_buffer_rsrc_t r, int off) { return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0); }
+__device__ __forceinline__ u32x4 pack8(const float (&v)[8]) {
+  return (u32x4){f32x2_to_bf16x2(v[0], v[1]), f32x2_to_bf16x2(v[2], v[3]), f32x2_to_bf16x2(v[4], v[5]), f32x2_to_bf16x2(v[6], v[7])};
+}
+
+template <bool BT, int WGM, int WGN, int IM, int NS>
+__global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(PipeArgs p) {
+  using S = Shape<false, BT, WGM, WGN, IM, NS>;
+  constexpr int JN = 2;
+  extern __shared__ __align__(1024) char smem[];
+  // XCD x (workgroup id % 8) takes a contiguous range of the tiles, row by row: they share operand panels in its L2
+  const int slot = blockIdx.x >> 3, t = (blockIdx.x & 7) * p.per_xcd + slot;
+  if (slot >= p.per_xcd || t >= p.tiles) return;
+  const int m0 = t / p.tiles_n * S::BM, n0 = t % p.tiles_n * S::BN;
+  f32x16 acc[JN][IM];
+  float none[JN];
+#pragma unroll
+  for (int j = 0; j < JN; ++j)
+#pragma unroll
+    for (int i = 0; i < IM; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[j][i][e] = 0.f;
+  multiply<S, false, BT, false>(make_rsrc(p.A, p.a_bytes), make_rsrc(p.B, p.b_bytes), p.lda, p.ldb, m0, n0, p.M, p.N,
+                                                      Range{0, (p.K + KS - 1) / KS, p.K}, (lds_char*)smem, acc, none, false);
+
+  // Epilogue: a wave passes its accumulators (lane = one row, 4 consecutive columns a group) through its own piece of LDS, 32 rows
+  // at a time, and takes them out 8 consecutive columns a lane; what a piece needs from memory is asked for one piece ahead.
+  constexpr int COLS = JN * 32, PITCH = COLS + 4, LPR = COLS / 8, RPP = 64 / LPR, NP = 32 / RPP;
+  static_assert(S::W * 32 * PITCH * 4 <= S::LDS, "");
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float* st = reinterpret_cast<float*>(smem) + wave * 32 * PITCH;
+  const int mw = m0 + wave / WGN * IM * 32, c8 = lane % LPR * 8, n = n0 + wave % WGN * COLS + c8, r0 = lane / LPR;
+  const int col2 = n < p.N ? 2 * n : OOB_BASE;
+  float bias[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (p.bias) {
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(p.bias, (uint32_t)p.N * 4u);
+    const u32x4 lo = pipe_load16(rs, 2 * col2), hi = pipe_load16(rs, 2 * col2 + 16);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { bias[e] = __uint_as_float(lo[e]); bias[4 + e] = __uint_as_float(hi[e]); }
+  }
+  const bool has_res = p.residual != nullptr, has_aux = p.epilogue == EPI_DGELU;
+  const __amdgpu_buffer_rsrc_t rsR = make_rsrc(p.residual, p.r_bytes), rsX = make_rsrc(p.aux, p.aux_bytes);
+  const __amdgpu_buffer_rsrc_t rsC = make_rsrc(p.C, p.c_bytes), rsC2 = make_rsrc(p.C2, p.C2 ? p.c_bytes : 0u);
+  u32x4 res[2][NP], aux[2][NP];
+  auto ask = [&](int im, u32x4 (&r)[NP], u32x4 (&x)[NP]) {
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const int m = mw + im * 32 + q * RPP + r0;
+      if (has_res) r[q] = pipe_load16(rsR, m < p.M ? (int)(m * p.ldr * 2) + col2 : OOB);
+      if (has_aux) x[q] = pipe_load16(rsX, m < p.M ? (int)(m * p.ldaux * 2) + col2 : OOB);
+    }
+  };
+  ask(0, res[0], aux[0]);
+#pragma unroll
+  for (int im = 0; im < IM; ++im) {
+    if (im + 1 < IM) ask(im + 1, res[(im + 1) & 1], aux[(im + 1) & 1]);
+#pragma unroll
+    for (int jn = 0; jn < JN; ++jn)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<float4*>(st + (lane & 31) * PITCH + jn * 32 + 8 * q + 4 * (lane >> 5)) =
+            make_float4(acc[jn][im][4 * q], acc[jn][im][4 * q + 1], acc[jn][im][4 * q + 2], acc[jn][im][4 * q + 3]);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const int m = mw + im * 32 + q * RPP + r0;
+      const float4 lo = *reinterpret_cast<const float4*>(st + (q * RPP + r0) * PITCH + c8);
+      const float4 hi = *reinterpret_cast<const float4*>(st + (q * RPP + r0) * PITCH + c8 + 4);
+      float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] += bias[e];
+      if (has_res) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t w = res[im & 1][q][e];
+          v[2 * e] += __uint_as_float(w << 16); v[2 * e + 1] += __uint_as_float(w & 0xffff0000u);
+        }
+      }
+      if (has_aux) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {   // the saved GELU derivative
+          const uint32_t w = aux[im & 1][q][e];
+          v[2 * e] *= __uint_as_float(w << 16); v[2 * e + 1] *= __uint_as_float(w & 0xffff0000u);
+        }
+      }
+      const int off = m < p.M ? (int)(m * p.ldc * 2) + col2 : OOB;
+      if (p.epilogue == EPI_GELU) {   // C2 = gelu(h), C = gelu'(h) from one evaluation of the normal CDF and density
+        float dg[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          float cdf, pdf;
+          cdf_pdf(v[e], cdf, pdf);
+          dg[e] = cdf + v[e] * pdf; v[e] *= cdf;
+        }
+        __builtin_amdgcn_raw_buffer_store_b128(pack8(dg), rsC, off, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(pack8(v), rsC2, off, 0, 0);
+      } else {
+        __builtin_amdgcn_raw_buffer_store_b128(pack8(v), rsC, off, 0, 0);
+      }
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+constexpr int WAVES_N = 4, STAGES = 3;
+
+// more than 64 KB of LDS needs an opt-in, once per device
+int opt_in_lds(const void* kernel, int bytes, std::atomic<bool> (&done)[64]) {
+  int dev = 0;
+  PPLL_HIP(hipGetDevice(&dev));
+  const bool known = dev >= 0 && dev < 64;
+  if (known && done[dev].load(std::memory_order_acquire)) return PPLL_OK;
+  PPLL_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+  if (known) done[dev].store(true, std::memory_order_release);
+  return PPLL_OK;
+}
+
+template <bool BT, int IM>
+int pipe_launch(hipStream_t s, PipeArgs& p) {
+  using S = Shape<false, BT, 1, WAVES_N, IM, STAGES>;
+  p.tiles_n = (p.N + S::BN - 1) / S::BN;
+  p.tiles = (p.M + S::BM - 1) / S::BM * p.tiles_n;
+  p.per_xcd = (p.tiles + 7) / 8;
+  static std::atomic<bool> opted_in[64];
+  PPLL_TRY(opt_in_lds((const void*)gemm_pipe_kernel<BT, 1, WAVES_N, IM, STAGES>, S::LDS, opted_in));
+  hipLaunchKernelGGL((gemm_pipe_kernel<BT, 1, WAVES_N, IM, STAGES>), dim3(8 * p.per_xcd), dim3(S::THREADS), S::LDS, s, p);
+  PPLL_HIP(hipGetLastError());
+  return PPLL_OK;
+}
+
+// Time of a launch of `tiles` tiles on `places` workgroup places (two per compute unit), in rounds: a last round of at most one
+// workgroup per unit takes 0.62 of one in which they share units.
+double rounds(long tiles, int places) {
+  const long full = tiles / places, rest = tiles % places;
+  return full + (rest == 0 ? 0.0 : 2 * rest <= places ? 0.62 : 1.0);
+}
+int workgroup_places() {   // on the current device
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+  return 2 * cus;
+}
+long tile_count(int M, int N, int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); }
+}  // namespace
+
+// Rows of a wave's tile / 32 with which this kernel is expected to beat the tiled one, 0 if it is not.  A round of 128 x 256
+// tiles takes 1.58 times, of 160 x 256 tiles 1.74 times as long as one of the tiled kernel's 128 x 128 (25216 rows of width 768:
+// 30, 33 and 19 us), so what decides is how the tiles fill their last round: 25216 x 768 is 2.3 rounds of 128 x 128, 1.15 of 128
+// x 256, 0.93 of 160 x 256 (K = 3072: 145, 142, 115 us); 8320 x 1536 is 1.5, 0.76, 0.61 (31.6, 28.1, 32.6 us); 8320 x 384 stays
+// where it is, on 195 units (21.5, 31.1, 32.6 us).  Even cases stay on the tiled kernel.
+int gemm_pipe_choice(const GemmArgs& g) {
+  if (!gemm_mfma_supported(g) || g.a_sk != 1 || g.colsum || g.c_dt != BF16 || g.K < 4 * KS) return 0;
+  const bool bt = g.b_sn == 1 && g.b_sk != 1;
+  // 32-bit byte offsets also for the rows (k rows) of the last tile that do not exist
+  if (g.a_sm > (1 << 20) || (bt ? g.b_sk : g.b_sn) > (1 << 20)) return 0;
+  const int places = workgroup_places();
+  if (places < 16) return 0;
+  const double tiled = rounds(tile_count(g.M, g.N, 128, 128), places);
+  const double c4 = 1.58 * rounds(tile_count(g.M, g.N, 128, 256), places), c5 = 1.74 * rounds(tile_count(g.M, g.N, 160, 256), places);
+  if (std::fmin(c4, c5) >= 0.95 * tiled) return 0;
+  return c4 <= c5 ? 4 : 5;
+}
+
+int launch_gemm_pipe(hipStream_t s, const GemmArgs& g, int im) {
+  const bool bt = g.b_sn == 1 && g.b_sk != 1;
+  PipeArgs p{};
+  p.A = (const uint16_t*)g.A; p.lda = g.a_sm;
+  p.B = (const uint16_t*)g.B; p.ldb = bt ? g.b_sk : g.b_sn;
+  p.C = (uint16_t*)g.C; p.ldc = g.ldc;
+  p.M = g.M; p.N = g.N; p.K = g.K;
+  p.bias = g.bias; p.residual = (const uint16_t*)g.residual; p.ldr = g.ldr;
+  p.epilogue = g.epilogue; p.C2 = (uint16_t*)g.C2; p.aux = (const uint16_t*)g.aux; p.ldaux = g.ldaux;
+  p.a_bytes = (uint32_t)(((long)(g.M - 1) * p.lda + g.K) * 2);
+  p.b_bytes = (uint32_t)((bt ? (long)(g.K - 1) * p.ldb + g.N : (long)(g.N - 1) * p.ldb + g.K) * 2);
+  p.c_bytes = (uint32_t)(((long)(g.M - 1) * g.ldc + g.N) * 2);
+  p.r_bytes = g.residual ? (uint32_t)(((long)(g.M - 1) * g.ldr + g.N) * 2) : 0u;
+  p.aux_bytes = g.epilogue == EPI_DGELU ? (uint32_t)(((long)(g.M - 1) * g.ldaux + g.N) * 2) : 0u;
+  void* prof = nullptr;
+  PPLL_TRY(profile_begin(s, 2.0 * g.M * g.N * g.K, &prof));
+  if (bt && im == 4) PPLL_TRY((pipe_launch<true, 4>(s, p)));
+  else if (bt) PPLL_TRY((pipe_launch<true, 5>(s, p)));
+  else if (im == 4) PPLL_TRY((pipe_launch<false, 4>(s, p)));
+  else PPLL_TRY((pipe_launch<false, 5>(s, p)));
+  return profile_end(s, prof);
+}
+
+}  // namespace ppll

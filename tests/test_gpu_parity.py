@@ -357,6 +357,18 @@ def test_vit_bf16_row_counts_off_the_tile_edges(batch, tokens, dim, depth):
     run_case(wl, steps=1)
 
 
+@pytest.mark.parametrize("batch,tokens,dim,mlp", [
+    # products with many output tiles: rows and columns that fill no tile of 128 x 256 or 160 x 256, reductions that fill no stage of 32
+    (129, 65, 128, 1528),    # 8385 rows: the MLP on 128-row tiles (GELU and its derivative)
+    (71, 131, 136, 3064),    # 9301 rows: the MLP on 160-row tiles, a last stage of 8 k
+    (97, 129, 768, 64),      # 12513 rows: QKV, projection with residual and their input gradients on 160-row tiles
+    (143, 130, 768, 64),     # 18590 rows: projection and QKV input gradient on 128-row tiles
+])
+def test_vit_bf16_products_with_many_tiles(batch, tokens, dim, mlp):
+    wl = synth.workload("vit_stage_act_bf16", batch=batch, tokens=tokens, dim=dim, heads=max(1, dim // 64 // 2 * 2), mlp_dim=mlp, depth=1, aux_depth=0)
+    run_case(wl, steps=1)
+
+
 @pytest.mark.parametrize("tokens,dim,heads", [(20, 128, 4), (65, 96, 1)])
 def test_vit_bf16_attention_shapes_outside_the_matrix_core_kernel(tokens, dim, heads):
     # a head dimension other than 64 (32, 96): the run-time-typed attention kernels on bf16 tensors
