@@ -1,4 +1,4 @@
-// Main loop of the bf16 products with many output tiles: C tile += A(m, k) B(k, n), fp32 accumulation in
+// Main loop of the bf16 matrix-core products: C tile += A(m, k) B(k, n) over a range of k, fp32 accumulation in
 // v_mfma_f32_32x32x16_bf16, operands copied from memory straight into LDS (buffer loads with an LDS destination).
 #pragma once
 #include "common.h"
@@ -59,13 +59,13 @@ template <bool TR, int ROWS> struct Operand {
 };
 
 // A workgroup of WGM_ x WGN_ waves, each 32 IM_ x 64 of the output tile, and NS_ stages in LDS
-template <bool BT, int WGM_, int WGN_, int IM_, int NS_> struct Shape {
+template <bool AT, bool BT, int WGM_, int WGN_, int IM_, int NS_> struct Shape {
   static constexpr int WGN = WGN_, IM = IM_, NS = NS_, W = WGM_ * WGN_, THREADS = 64 * W, BM = WGM_ * IM * 32, BN = WGN_ * 64;
-  using OA = Operand<false, BM>;
+  using OA = Operand<AT, BM>;
   using OB = Operand<BT, BN>;
   static constexpr int STAGE = OA::BYTES + OB::BYTES, LDS = NS * STAGE;
   static constexpr int COPIES = OA::COPIES / W + OB::COPIES / W;   // per wave and stage, of some waves one more
-  static_assert(OB::COPIES % W == 0 && W % 2 == 0 && NS >= 3, "");
+  static_assert(OB::COPIES % W == 0 && (!AT || OA::COPIES % W == 0) && W % 2 == 0 && NS >= 3, "");
 };
 
 // The fragments (8 consecutive k of one row per lane) of a wave's tile, 32 IM rows of A and 64 of B, at one k step of 16.  A
@@ -98,11 +98,11 @@ template <bool TR, int ROWS> __device__ __forceinline__ int frag_base(int region
 #define PPLL_ACC [c00] "+v"(acc[0][0]), [c01] "+v"(acc[0][1]), [c02] "+v"(acc[0][2]), [c03] "+v"(acc[0][3]), \
                  [c10] "+v"(acc[1][0]), [c11] "+v"(acc[1][1]), [c12] "+v"(acc[1][2]), [c13] "+v"(acc[1][3])
 #define PPLL_CUR [p0] "v"(a.get(0)), [p1] "v"(a.get(1)), [p2] "v"(a.get(2)), [p3] "v"(a.get(3)), [q0] "v"(b.get(0)), [q1] "v"(b.get(1))
-template <bool BT, int ROWS_B, int KK, int IM>
-__device__ __forceinline__ void k_step(f32x16 (&acc)[2][IM], const Frags<false, IM>& a, const Frags<BT, 2>& b, Frags<false, IM>& na, Frags<BT, 2>& nb,
+template <bool AT, bool BT, int ROWS_A, int ROWS_B, int KK, int IM>
+__device__ __forceinline__ void k_step(f32x16 (&acc)[2][IM], const Frags<AT, IM>& a, const Frags<BT, 2>& b, Frags<AT, IM>& na, Frags<BT, 2>& nb,
                                        int addrA, int addrB) {
-  static_assert(IM == 4 || IM == 5, "");
-  constexpr int PB = ROWS_B * 2;
+  static_assert(IM == 4 || (IM == 5 && !AT), "");
+  constexpr int PA = ROWS_A * 2, PB = ROWS_B * 2;
   if constexpr (IM == 5 && BT) {
     asm volatile("s_nop 1\n" PPLL_MMA(0, 0)
                  "ds_read_b64_tr_b16 %[l0], %[rb0] offset:%[ol]\n ds_read_b64_tr_b16 %[h0], %[rb0] offset:%[oh]\n" PPLL_MMA(0, 1)
@@ -126,7 +126,7 @@ __device__ __forceinline__ void k_step(f32x16 (&acc)[2][IM], const Frags<false, 
                    [x3] "=&v"(na.v[3]), [x4] "=&v"(na.v[4]), [y0] "=&v"(nb.v[0]), [y1] "=&v"(nb.v[1])
                  : PPLL_CUR, [p4] "v"(a.get(4)), [ra] "v"(KK ? addrA ^ 32 : addrA), [rb] "v"(KK ? addrB ^ 32 : addrB)
                  : "memory");
-  } else if constexpr (BT) {
+  } else if constexpr (!AT && BT) {
     asm volatile("s_nop 1\n" PPLL_MMA(0, 0)
                  "ds_read_b64_tr_b16 %[l0], %[rb0] offset:%[ol]\n ds_read_b64_tr_b16 %[h0], %[rb0] offset:%[oh]\n" PPLL_MMA(0, 1)
                  "ds_read_b128 %[x0], %[ra]\n ds_read_b128 %[x1], %[ra] offset:2048\n" PPLL_MMA(0, 2)
@@ -138,7 +138,7 @@ __device__ __forceinline__ void k_step(f32x16 (&acc)[2][IM], const Frags<false, 
                  : PPLL_CUR, [ra] "v"(KK ? addrA ^ 32 : addrA), [rb0] "v"(addrB), [rb1] "v"(addrB ^ 64), [ol] "n"(KK * 16 * PB),
                    [oh] "n"(KK * 16 * PB + 4 * PB)
                  : "memory");
-  } else {
+  } else if constexpr (!AT && !BT) {
     asm volatile("s_nop 1\n" PPLL_MMA(0, 0) "ds_read_b128 %[y0], %[rb]\n ds_read_b128 %[x0], %[ra]\n" PPLL_MMA(0, 1)
                  "ds_read_b128 %[x1], %[ra] offset:2048\n ds_read_b128 %[x2], %[ra] offset:4096\n" PPLL_MMA(0, 2)
                  "ds_read_b128 %[x3], %[ra] offset:6144\n ds_read_b128 %[y1], %[rb] offset:2048\n" PPLL_MMA(0, 3)
@@ -147,6 +147,23 @@ __device__ __forceinline__ void k_step(f32x16 (&acc)[2][IM], const Frags<false, 
                    [y1] "=&v"(nb.v[1])
                  : PPLL_CUR, [ra] "v"(KK ? addrA ^ 32 : addrA), [rb] "v"(KK ? addrB ^ 32 : addrB)
                  : "memory");
+  } else {
+    static_assert(AT && BT, "");
+    asm volatile("s_nop 1\n" PPLL_MMA(0, 0)
+                 "ds_read_b64_tr_b16 %[m0], %[rb0] offset:%[ol]\n ds_read_b64_tr_b16 %[n0], %[rb0] offset:%[oh]\n"
+                 "ds_read_b64_tr_b16 %[l0], %[ra0] offset:%[al]\n ds_read_b64_tr_b16 %[h0], %[ra0] offset:%[ah]\n" PPLL_MMA(0, 1)
+                 "ds_read_b64_tr_b16 %[l1], %[ra1] offset:%[al]\n ds_read_b64_tr_b16 %[h1], %[ra1] offset:%[ah]\n"
+                 "ds_read_b64_tr_b16 %[l2], %[ra2] offset:%[al]\n ds_read_b64_tr_b16 %[h2], %[ra2] offset:%[ah]\n" PPLL_MMA(0, 2)
+                 "ds_read_b64_tr_b16 %[l3], %[ra3] offset:%[al]\n ds_read_b64_tr_b16 %[h3], %[ra3] offset:%[ah]\n" PPLL_MMA(0, 3)
+                 "ds_read_b64_tr_b16 %[m1], %[rb1] offset:%[ol]\n ds_read_b64_tr_b16 %[n1], %[rb1] offset:%[oh]\n"
+                 PPLL_MMA(1, 0) PPLL_MMA(1, 1) PPLL_MMA(1, 2) PPLL_MMA(1, 3) "s_waitcnt lgkmcnt(0)"
+                 : PPLL_ACC, [l0] "=&v"(na.lo[0]), [h0] "=&v"(na.hi[0]), [l1] "=&v"(na.lo[1]), [h1] "=&v"(na.hi[1]),
+                   [l2] "=&v"(na.lo[2]), [h2] "=&v"(na.hi[2]), [l3] "=&v"(na.lo[3]), [h3] "=&v"(na.hi[3]), [m0] "=&v"(nb.lo[0]),
+                   [n0] "=&v"(nb.hi[0]), [m1] "=&v"(nb.lo[1]), [n1] "=&v"(nb.hi[1])
+                 : PPLL_CUR, [ra0] "v"(addrA), [ra1] "v"(addrA ^ 64), [ra2] "v"(addrA ^ 128), [ra3] "v"(addrA ^ 192), [rb0] "v"(addrB),
+                   [rb1] "v"(addrB ^ 64), [al] "n"(KK * 16 * PA), [ah] "n"(KK * 16 * PA + 4 * PA), [ol] "n"(KK * 16 * PB),
+                   [oh] "n"(KK * 16 * PB + 4 * PB)
+                 : "memory");
   }
 }
 #undef PPLL_MMA
@@ -154,10 +171,12 @@ __device__ __forceinline__ void k_step(f32x16 (&acc)[2][IM], const Frags<false, 
 #undef PPLL_CUR
 
 // acc[jn][im]: C^T tiles (the B fragment goes first into the MFMA): lane l holds row im*32 + l%32, columns jn*32 + 8 q +
-// 4 (l/32) + e in element 4 q + e.  A is [m][k], B [k][n] with BT, else [n][k].
-template <class S, bool BT>
+// 4 (l/32) + e in element 4 q + e.  csum[jn] (COLSUM, wave-uniform do_colsum): this lane's share, k % 8 = e of its half of every
+// k step in element e, of the sum over k of B's row jn*32 + l%32.
+template <class S, bool AT, bool BT, bool COLSUM>
 __device__ __forceinline__ void multiply(const __amdgpu_buffer_rsrc_t rsA, const __amdgpu_buffer_rsrc_t rsB, long lda, long ldb,
-                                         int m0, int n0, int M, int N, int K, lds_char* lds, f32x16 (&acc)[2][S::IM]) {
+                                         int m0, int n0, int M, int N, int K, lds_char* lds, f32x16 (&acc)[2][S::IM],
+                                         float (&csum)[2][8], bool do_colsum) {
   constexpr int NS = S::NS, IM = S::IM;
   const int nk = (K + KS - 1) / KS;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -173,9 +192,10 @@ __device__ __forceinline__ void multiply(const __amdgpu_buffer_rsrc_t rsA, const
     const int k0 = i * KS;
     const bool live = i < nk;
     lds_char* st = lds + (i % NS) * S::STAGE;
-    const int va = live && k0 + oa.gk < K ? oa.vbase + k0 * 2 : OOB_BASE;
-    int vb;
-    if (BT) vb = live ? ob.vbase + k0 * ob.ld2 : OOB_BASE;   // k rows past the last one lie past the end of the buffer
+    int va, vb;                   // k rows past the last one of an operand stored by k lie past the end of its buffer
+    if (AT) va = live ? oa.vbase + k0 * oa.ld2 : OOB_BASE;
+    else va = live && k0 + oa.gk < K ? oa.vbase + k0 * 2 : OOB_BASE;
+    if (BT) vb = live ? ob.vbase + k0 * ob.ld2 : OOB_BASE;
     else vb = live && k0 + ob.gk < K ? ob.vbase + k0 * 2 : OOB_BASE;
 #pragma unroll
     for (int c = 0; c < (OA::COPIES + S::W - 1) / S::W; ++c) {
@@ -189,9 +209,18 @@ __device__ __forceinline__ void multiply(const __amdgpu_buffer_rsrc_t rsA, const
     }
   };
   const int base = (int)(uintptr_t)lds;
-  const int fa0 = frag_base<false, S::BM>(base, wm * IM * 32, lane), fb0 = frag_base<BT, S::BN>(base + OA::BYTES, wn * 64, lane);
-  Frags<false, IM> a0, a1;
+  const int fa0 = frag_base<AT, S::BM>(base, wm * IM * 32, lane), fb0 = frag_base<BT, S::BN>(base + OA::BYTES, wn * 64, lane);
+  Frags<AT, IM> a0, a1;
   Frags<BT, 2> b0, b1;
+  auto column_sums = [&](const Frags<BT, 2>& b) {
+    if (!COLSUM || !do_colsum) return;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const u32x4 v = b.get(j);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { csum[j][2 * e] += __uint_as_float(v[e] << 16); csum[j][2 * e + 1] += __uint_as_float(v[e] & 0xffff0000u); }
+    }
+  };
 #pragma unroll
   for (int i = 0; i < NS - 1; ++i) issue(i);
   wait_vm<(NS - 2) * S::COPIES>();
@@ -201,14 +230,16 @@ __device__ __forceinline__ void multiply(const __amdgpu_buffer_rsrc_t rsA, const
   for (int i = 0; i < IM; ++i) set_zero(a1, i);
 #pragma unroll
   for (int j = 0; j < 2; ++j) set_zero(b1, j);
-  k_step<BT, S::BN, 0, IM>(acc, a1, b1, a0, b0, fa0, fb0);
+  k_step<AT, BT, S::BM, S::BN, 0, IM>(acc, a1, b1, a0, b0, fa0, fb0);
   for (int i = 0; i < nk; ++i) {
     const int st = (i % NS) * S::STAGE, nx = ((i + 1) % NS) * S::STAGE;
     wait_vm<(NS - 3) * S::COPIES>();       // this wave's part of stage i + 1 is in LDS
     __builtin_amdgcn_s_barrier();          // and everyone's; nobody reads stage i - 1 any more
     issue(i + NS - 1);
-    k_step<BT, S::BN, 1, IM>(acc, a0, b0, a1, b1, fa0 + st, fb0 + st);
-    k_step<BT, S::BN, 0, IM>(acc, a1, b1, a0, b0, fa0 + nx, fb0 + nx);
+    column_sums(b0);
+    k_step<AT, BT, S::BM, S::BN, 1, IM>(acc, a0, b0, a1, b1, fa0 + st, fb0 + st);
+    column_sums(b1);
+    k_step<AT, BT, S::BM, S::BN, 0, IM>(acc, a1, b1, a0, b0, fa0 + nx, fb0 + nx);
   }
   // the last products are through before a vector instruction reads the accumulators
   asm volatile("s_nop 15\n s_nop 3" ::: "memory");

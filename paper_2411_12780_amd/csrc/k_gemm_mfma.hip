@@ -27,6 +27,7 @@
 // split writes its fp32 partial tile, a second kernel adds the splits in a
 // fixed order, so results are reproducible (no float atomics).
 #include "common.h"
+#include "gemm_pipe.h"
 #include <atomic>
 #include <algorithm>
 
@@ -492,6 +493,69 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma_grouped_kernel(GroupedArgs a
   gemm_mfma_tile<true, true, 128>(p, bid, 0);
 }
 
+// The same set of products on 128 x 256 tiles and the main loop of gemm_pipe.h.  A tile of K = 25216 rows keeps its workgroup for
+// half a millisecond, so what counts is the traffic of the loop per product: 24 KB into LDS for 128 x 256 x 32 instead of 32 KB for
+// 128 x 128 x 64, and a wave reads 192 instead of 128 values a k for twice the products.
+// Whole steps with 128 x 128 tiles and with these, microseconds: 25216 rows of width 768 6048 -> 5842, 640 rows 748 -> 732.
+using PipeShape = pipe::Shape<true, true, 1, 4, 4, 3>;
+constexpr int PIPE_BN = PipeShape::BN;
+static_assert(PipeShape::BM == BM, "");
+__global__ __launch_bounds__(PipeShape::THREADS, 2) void gemm_pipe_grouped_kernel(GroupedArgs a) {
+  extern __shared__ __align__(1024) char smem[];
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int t = xcd * a.per_xcd + slot;
+  if (slot >= a.per_xcd || t >= a.total_tiles) return;
+  int bid;
+  const GroupedProblem& p = a.prob[grouped_locate(a, t, bid)];
+  const int m0 = bid / p.tiles_n * BM, n0 = bid % p.tiles_n * PIPE_BN, N = p.N;
+  pipe::f32x16 acc[2][4];
+  float csum[2][8] = {};
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[j][i][e] = 0.f;
+  const bool do_colsum = p.colsum && m0 == 0;
+  pipe::multiply<PipeShape, true, true, true>(pipe::make_rsrc(p.A, p.a_bytes), pipe::make_rsrc(p.B, p.b_bytes), p.lda, p.ldb, m0, n0, p.M,
+                                              N, p.K, (pipe::lds_char*)smem, acc, csum, do_colsum);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nw = n0 + wave * 64;
+  if (do_colsum) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      float sum = ((csum[j][0] + csum[j][1]) + (csum[j][2] + csum[j][3])) + ((csum[j][4] + csum[j][5]) + (csum[j][6] + csum[j][7]));
+      sum += __shfl_xor(sum, 32, 64);   // the other half of every k step
+      const int n = nw + j * 32 + lane;
+      if (lane < 32 && n < N) p.colsum[n] = sum;
+    }
+  }
+  // a wave passes 32 rows at a time through its own piece of LDS and stores them 256 bytes a row
+  constexpr int PITCH = 68;
+  static_assert(4 * 32 * PITCH * 4 <= PipeShape::LDS, "");
+  float* st = reinterpret_cast<float*>(smem) + wave * 32 * PITCH;
+  const int c4 = (lane & 15) * 4;
+#pragma unroll
+  for (int im = 0; im < 4; ++im) {
+#pragma unroll
+    for (int jn = 0; jn < 2; ++jn)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<float4*>(st + (lane & 31) * PITCH + jn * 32 + 8 * q + 4 * (lane >> 5)) =
+            make_float4(acc[jn][im][4 * q], acc[jn][im][4 * q + 1], acc[jn][im][4 * q + 2], acc[jn][im][4 * q + 3]);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int r = q * 4 + (lane >> 4), m = m0 + im * 32 + r, n = nw + c4;
+      const float4 v = *reinterpret_cast<const float4*>(st + r * PITCH + c4);
+      if (m < p.M && n < N) *reinterpret_cast<float4*>(p.C + (size_t)m * p.ldc + n) = v;   // N is a multiple of 8
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
 // The same set of products with the work dealt out more evenly.  One whole tile per workgroup leaves the chip unevenly
 // loaded when the tiles number a little more than the compute units (345 tiles of 130 k-steps on 256 units with two
 // workgroups each: 89 units work on two tiles from start to end while 167 finish their one tile early and idle, and
@@ -669,27 +733,52 @@ constexpr int BALANCED_MAX_CUTS = 8;
 // room for the parts of the divided tiles: at most two per workgroup
 size_t gemm_mfma_balanced_floats() { return (size_t)balanced_workgroups() * 2 * SLOT_FLOATS; }
 
-static void fill_problem(GroupedProblem& q, const GemmArgs& g, int first_tile) {
+static void fill_problem(GroupedProblem& q, const GemmArgs& g, int first_tile, int bn = BN) {
   q.A = (const uint16_t*)g.A; q.lda = (int)g.a_sk; q.B = (const uint16_t*)g.B; q.ldb = (int)g.b_sk;
   q.C = (float*)g.C; q.ldc = (int)g.ldc; q.colsum = g.colsum;
   q.M = g.M; q.N = g.N; q.K = g.K;
-  q.tiles_m = (g.M + BM - 1) / BM; q.tiles_n = (g.N + BN - 1) / BN;
+  q.tiles_m = (g.M + BM - 1) / BM; q.tiles_n = (g.N + bn - 1) / bn;
   q.first_tile = first_tile;
   q.a_bytes = (uint32_t)operand_bytes(true, g.M, g.K, g.a_sk);
   q.b_bytes = (uint32_t)operand_bytes(true, g.N, g.K, g.b_sk);
   q.c_bytes = (uint32_t)(((long)(g.M - 1) * g.ldc + g.N) * 4);
 }
 
+// Whether a set of products runs on 128 x 256 tiles.  Per k a tile takes 1.58 times as long as one of 128 x 128 (two workgroups
+// to a unit either way), so the padded tiles decide: width 768 has none, width 384 (1.5 tiles) loses.  Without a workspace the
+// launch runs beside other work, which fills what it leaves idle.  With one, the alternative is the balanced launch, whose
+// rounds are full.
+static bool grouped_on_pipe(const GemmArgs* gs, int n, bool balanced, int wgs) {
+  double narrow = 0.0, wide = 0.0;
+  long tiles = 0;
+  for (int j = 0; j < n; ++j) {
+    if (gs[j].a_sk > (1 << 20) || gs[j].b_sk > (1 << 20)) return false;   // 32-bit byte offsets for the k rows of a last stage that do not exist
+    const long tm = (gs[j].M + BM - 1) / BM, t = tm * ((gs[j].N + PIPE_BN - 1) / PIPE_BN);
+    narrow += (double)tm * ((gs[j].N + BN - 1) / BN) * gs[j].K;
+    wide += 1.58 * t * gs[j].K;
+    tiles += t;
+  }
+  if (tiles < wgs / 2) return false;
+  if (balanced) {
+    const long full = tiles / (2L * wgs), rest = tiles % (2L * wgs);
+    wide *= (full + (rest == 0 ? 0.0 : rest <= wgs ? 0.62 : 1.0)) * 2 * wgs / tiles;
+  }
+  return wide < 0.95 * narrow;
+}
+
 int launch_gemm_mfma_grouped(hipStream_t s, const GemmArgs* gs, int n, float* ws, size_t ws_floats) {
   static std::atomic<bool> opted_in[64];
   if (lds_opt_in_due(opted_in)) {
+    PPLL_HIP(hipFuncSetAttribute((const void*)gemm_pipe_grouped_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, PipeShape::LDS));
     PPLL_HIP(hipFuncSetAttribute((const void*)gemm_mfma_grouped_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(true, true, 128)));
     PPLL_HIP(hipFuncSetAttribute((const void*)gemm_mfma_balanced_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(true, true, 128)));
   }
   // Balanced launch: the whole set in one launch, a workspace for the divided tiles, tiles that leave a last round
   // partly filled, and a reduction long enough to cut
   const int wgs = balanced_workgroups();
-  if (ws && wgs >= 8 && n <= GROUP_MAX && ws_floats >= (size_t)wgs * 2 * SLOT_FLOATS) {
+  const bool balanced = ws && wgs >= 8 && n <= GROUP_MAX && ws_floats >= (size_t)wgs * 2 * SLOT_FLOATS;
+  const bool on_pipe = wgs >= 8 && grouped_on_pipe(gs, n, balanced, wgs);
+  if (balanced && !on_pipe) {
     BalancedArgs a{};
     a.n = n; a.ws = ws;
     constexpr int LONG_NKT = 8;                     // k-steps from which a reduction counts as long enough to cut
@@ -736,7 +825,7 @@ int launch_gemm_mfma_grouped(hipStream_t s, const GemmArgs* gs, int n, float* ws
     double flops = 0.0;
     for (int j = 0; j < a.n; ++j) {
       const GemmArgs& g = gs[j0 + j];
-      fill_problem(a.prob[j], g, tiles);
+      fill_problem(a.prob[j], g, tiles, on_pipe ? PIPE_BN : BN);
       tiles += a.prob[j].tiles_m * a.prob[j].tiles_n;
       flops += 2.0 * g.M * g.N * g.K;
     }
@@ -744,7 +833,8 @@ int launch_gemm_mfma_grouped(hipStream_t s, const GemmArgs* gs, int n, float* ws
     a.per_xcd = (tiles + 7) / 8;
     void* prof = nullptr;
     PPLL_TRY(profile_begin(s, flops, &prof));
-    hipLaunchKernelGGL(gemm_mfma_grouped_kernel, dim3(8 * a.per_xcd), dim3(256), lds_bytes(true, true, 128), s, a);
+    if (on_pipe) hipLaunchKernelGGL(gemm_pipe_grouped_kernel, dim3(8 * a.per_xcd), dim3(PipeShape::THREADS), PipeShape::LDS, s, a);
+    else hipLaunchKernelGGL(gemm_mfma_grouped_kernel, dim3(8 * a.per_xcd), dim3(256), lds_bytes(true, true, 128), s, a);
     PPLL_HIP(hipGetLastError());
     PPLL_TRY(profile_end(s, prof));
   }

@@ -40,7 +40,7 @@ __device__ __forceinline__ u32x4 pack8(const float (&v)[8]) {
 
 template <bool BT, int WGM, int WGN, int IM, int NS>
 __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(PipeArgs p) {
-  using S = Shape<BT, WGM, WGN, IM, NS>;
+  using S = Shape<false, BT, WGM, WGN, IM, NS>;
   constexpr int JN = 2;
   extern __shared__ __align__(1024) char smem[];
   // XCD x (workgroup id % 8) takes a contiguous range of the tiles, row by row: they share operand panels in its L2
@@ -48,13 +48,15 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(PipeArgs p
   if (slot >= p.per_xcd || t >= p.tiles) return;
   const int m0 = t / p.tiles_n * S::BM, n0 = t % p.tiles_n * S::BN;
   f32x16 acc[JN][IM];
+  float none[JN][8];
 #pragma unroll
   for (int j = 0; j < JN; ++j)
 #pragma unroll
     for (int i = 0; i < IM; ++i)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[j][i][e] = 0.f;
-  multiply<S, BT>(make_rsrc(p.A, p.a_bytes), make_rsrc(p.B, p.b_bytes), p.lda, p.ldb, m0, n0, p.M, p.N, p.K, (lds_char*)smem, acc);
+  multiply<S, false, BT, false>(make_rsrc(p.A, p.a_bytes), make_rsrc(p.B, p.b_bytes), p.lda, p.ldb, m0, n0, p.M, p.N, p.K,
+                                (lds_char*)smem, acc, none, false);
 
   // Epilogue: a wave passes its accumulators (lane = one row, 4 consecutive columns a group) through its own piece of LDS, 32 rows
   // at a time, and takes them out 8 consecutive columns a lane; what a piece needs from memory is asked for one piece ahead.
@@ -152,7 +154,7 @@ int opt_in_lds(const void* kernel, int bytes, std::atomic<bool> (&done)[64]) {
 
 template <bool BT, int IM>
 int pipe_launch(hipStream_t s, PipeArgs& p) {
-  using S = Shape<BT, 1, WAVES_N, IM, STAGES>;
+  using S = Shape<false, BT, 1, WAVES_N, IM, STAGES>;
   p.tiles_n = (p.N + S::BN - 1) / S::BN;
   p.tiles = (p.M + S::BM - 1) / S::BM * p.tiles_n;
   p.per_xcd = (p.tiles + 7) / 8;

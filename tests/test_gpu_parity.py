@@ -475,6 +475,15 @@ def test_resnet32_stages_at_their_full_shape_decisive_masks(name):
     run_case(synth.workload(name, batch=100), steps=1, check_bn=True, tweak=_decisive_shifts)
 
 
+@pytest.mark.parametrize("batch,tokens,depth", [
+    (63, 67, 2),    # 4221 rows: a layer's weight gradients on 128 x 256 tiles, ragged in rows, columns and the last 29 k
+    (40, 5, 3),     # 200 rows: those of all layers together
+])
+def test_vit_bf16_weight_gradients_of_wide_layers(batch, tokens, depth):
+    wl = synth.workload("vit_stage_act_bf16", batch=batch, tokens=tokens, dim=768, heads=12, mlp_dim=3064, depth=depth, aux_depth=0)
+    run_case(wl, steps=1)
+
+
 @pytest.mark.parametrize("channels,height,width,batch", [
     # maps that the convolutions with a BatchNorm on the way in take, four waves (tiles of 128 pixels): one image and less
     # than a tile, two 8 x 8 images a tile and a last one half empty, part of an image a tile, the two oblong shapes
