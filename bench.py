@@ -356,7 +356,7 @@ def main() -> int:
             achieved = gemm_flops / (gemm_ms * 1e-3) / 1e12
             traffic, why_not = measured_traffic(args.workload, "gemm", launches / args.steps)
             out["roofline"] = {"bound": "mfma",
-                               "kernel": "gemm_mfma_kernel on the token matrices (Linear forward, input gradient) and the grouped weight-gradient launch",
+                               "kernel": "gemm_mfma_kernel / gemm_pipe_kernel on the token matrices (Linear forward, input gradient) and the grouped weight-gradient launch",
                                "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                                "frac": achieved / PEAK_BF16_TFLOPS, "traffic": traffic,
                                **({"traffic_missing_because": why_not} if why_not else {}),
@@ -367,7 +367,7 @@ def main() -> int:
                                "gemm_flop_share_of_step": gemm_flops / args.steps / flops}
             if small_launches > 0:
                 # the class-token products of the pruned last auxiliary layer: a few rows each, bound by launch latency
-                out["small_products"] = {"kernel": "gemm_rows_kernel (products with fewer than 256 output rows)",
+                out["small_products"] = {"kernel": "gemm_rows_kernel (products with at most 256 output rows)",
                                          "launches_per_step": small_launches / args.steps,
                                          "avg_launch_us": 1e3 * small_ms / small_launches,
                                          "ms_per_step": small_ms / args.steps,
@@ -377,7 +377,7 @@ def main() -> int:
             # ResNet blocks: the dominant kernel is the 3x3 convolution (forward + input gradient), bound by HBM
             gbs = conv_bytes / (conv_ms * 1e-3) / 1e9
             traffic, why_not = measured_traffic(args.workload, "conv", conv_launches / args.steps)
-            out["roofline"] = {"bound": "hbm", "kernel": "conv3x3_mfma_kernel (forward and input gradient)",
+            out["roofline"] = {"bound": "hbm", "kernel": "conv_bn_kernel and conv3x3_mfma_kernel (forward and input gradient)",
                                "achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": gbs / PEAK_HBM_GBS,
                                "traffic": traffic, **({"traffic_missing_because": why_not} if why_not else {}),
                                "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, scaled by a copy probe)",
