@@ -214,16 +214,20 @@ bool aligned_to(const void* p, uintptr_t a) { return (((uintptr_t)p) & (a - 1)) 
 }  // namespace
 
 // One 32 x 32 tile per compute unit at most, else one 32 x 64 tile (only where the reduction is long enough for the tiled
-// kernel's serial walk to matter, see the figures above); up to 256 rows always.
-constexpr int ROWS_MAX_M = 256, ROWS_MAX_TILES = 256;
+// kernel's serial walk to matter, see the figures above); up to 256 rows always.  Beyond that not where both the width and the
+// reduction exceed 384: every tile reads its own operand rows, and what a launch alone on the chip gains there (640 x 768 x 3072:
+// 14.3 / 22.5 us) pipelined blocks lose, whose streams share it: four blocks of width 768 with 455 rows take 1524 us a batch on
+// this kernel and 1366 on the tiled one, with 663 rows 1018 and 870; at widths 192 and 384 pipelines take the same on either.
+constexpr int ROWS_MAX_M = 256, ROWS_MAX_TILES = 256, ROWS_MAX_WIDTH = 384;
 static bool rows_wide(int M, int N) { return (long)((M + 31) / 32) * ((N + 31) / 32) > ROWS_MAX_TILES && M > ROWS_MAX_M; }
-static bool rows_fit(int M, int N) {
-  return M <= ROWS_MAX_M || (long)((M + 31) / 32) * ((N + 63) / 64) <= ROWS_MAX_TILES;
+static bool rows_fit(int M, int N, int K) {
+  if (M <= ROWS_MAX_M) return true;
+  return (N <= ROWS_MAX_WIDTH || K <= ROWS_MAX_WIDTH) && (long)((M + 31) / 32) * ((N + 63) / 64) <= ROWS_MAX_TILES;
 }
 
 bool gemm_rows_supported(const GemmArgs& g) {
   if (g.a_dt != BF16 || g.b_dt != BF16 || g.colsum) return false;
-  if (g.M < 1 || !rows_fit(g.M, g.N) || g.N < 1 || g.K < 1 || (g.N & 7) || (g.K & 7)) return false;
+  if (g.M < 1 || !rows_fit(g.M, g.N, g.K) || g.N < 1 || g.K < 1 || (g.N & 7) || (g.K & 7)) return false;
   if (g.a_sk != 1 || (g.a_sm & 7) || !aligned_to(g.A, 16)) return false;
   const bool bt = g.b_sn == 1 && g.b_sk != 1;
   if (bt) {
