@@ -8,6 +8,7 @@
 #include <stdint.h>
 
 #include "../../include/ppll.h"
+#include "device.h"
 
 namespace ppll {
 
@@ -32,6 +33,11 @@ void set_error(const char* fmt, ...);
     int s__ = (expr);                 \
     if (s__ != PPLL_OK) return s__;   \
   } while (0)
+
+// More than 64 KB of dynamic LDS needs an opt-in per kernel, and the attribute belongs to a device's copy of the kernel: raises
+// it on the current device.  `bytes` is the most that any launch of the kernel asks for, never the size at hand: a thread with a
+// smaller one would lower what another has just raised.
+int raise_lds(const void* kernel, int bytes, OncePerDevice& once);
 
 #ifdef __HIPCC__
 // bf16 <-> fp32 by bit manipulation, round to nearest even.

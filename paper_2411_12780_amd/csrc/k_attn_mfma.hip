@@ -402,9 +402,8 @@ template <int NKT>
 int launch_fwd(hipStream_t s, const uint16_t* qkv, int B, int T, int H, uint16_t* out, float* lse) {
   constexpr int TP = 32 * NKT, RS = 2 * TP + 8;
   const size_t lds = (size_t)64 * RS + (size_t)TP * 128;
-  if (lds > 64 * 1024)
-    PPLL_HIP(hipFuncSetAttribute((const void*)attn_fwd_mfma_kernel<NKT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 (int)lds));
+  static OncePerDevice once;
+  if (lds > 64 * 1024) PPLL_TRY(raise_lds((const void*)attn_fwd_mfma_kernel<NKT>, (int)lds, once));   // the same for every T of NKT
   hipLaunchKernelGGL((attn_fwd_mfma_kernel<NKT>), dim3(B * H), dim3(64 * NKT), lds, s, qkv, T, H, out, lse);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;
@@ -415,9 +414,8 @@ int launch_bwd(hipStream_t s, const uint16_t* qkv, const uint16_t* out, const ui
                int T, int H, uint16_t* dqkv) {
   constexpr int TP = 32 * NKT, RS = 2 * TP + 8;
   const size_t lds = (size_t)4 * 64 * RS + 2 * TP * sizeof(float);   // 135 KB at T = 256
-  if (lds > 64 * 1024)
-    PPLL_HIP(hipFuncSetAttribute((const void*)attn_bwd_mfma_kernel<NKT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 (int)lds));
+  static OncePerDevice once;
+  if (lds > 64 * 1024) PPLL_TRY(raise_lds((const void*)attn_bwd_mfma_kernel<NKT>, (int)lds, once));   // the same for every T of NKT
   hipLaunchKernelGGL((attn_bwd_mfma_kernel<NKT>), dim3(B * H), dim3(64 * NKT), lds, s, qkv, out, dout, lse, T, H, dqkv);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;

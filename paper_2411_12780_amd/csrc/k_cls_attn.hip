@@ -167,10 +167,10 @@ __global__ __launch_bounds__(CLS_THREADS) void attn_cls_bwd_kernel(const void* q
 bool cls_vec_ok(int dt, int H, int dh, const void* a, const void* b) {
   return dt == BF16 && !(dh & 7) && !((((uintptr_t)a) | ((uintptr_t)b)) & 15) && H >= 1;
 }
-int opt_in_lds(const void* fn, size_t bytes, const char* what) {
-  if (bytes > 160 * 1024) { set_error("%s: %zu bytes of LDS exceed 160 KB", what, bytes); return PPLL_ERR_CONFIG; }
-  if (bytes > 64 * 1024) PPLL_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
-  return PPLL_OK;
+constexpr int CLS_LDS = 160 * 1024;
+int allow_lds(const void* fn, size_t bytes, OncePerDevice& once) {
+  if (bytes > CLS_LDS) { set_error("class-token attention: %zu bytes of LDS exceed 160 KB", bytes); return PPLL_ERR_CONFIG; }
+  return raise_lds(fn, CLS_LDS, once);
 }
 }  // namespace
 
@@ -179,11 +179,12 @@ size_t attention_cls_lds_bytes(int T, int dh) { return (2 * (size_t)T * (dh + 1)
 int launch_attention_cls_fwd(hipStream_t s, const void* q, const void* kv, int dt, int B, int T, int H, int dh, void* out,
                              float* prob) {
   const size_t lds = attention_cls_lds_bytes(T, dh);
+  static OncePerDevice once[2];
   if (cls_vec_ok(dt, H, dh, kv, nullptr)) {
-    PPLL_TRY(opt_in_lds((const void*)attn_cls_fwd_kernel<true>, lds, "class-token attention"));
+    PPLL_TRY(allow_lds((const void*)attn_cls_fwd_kernel<true>, lds, once[1]));
     hipLaunchKernelGGL(attn_cls_fwd_kernel<true>, dim3(B * H), dim3(CLS_THREADS), lds, s, q, kv, dt, T, H, dh, out, prob);
   } else {
-    PPLL_TRY(opt_in_lds((const void*)attn_cls_fwd_kernel<false>, lds, "class-token attention"));
+    PPLL_TRY(allow_lds((const void*)attn_cls_fwd_kernel<false>, lds, once[0]));
     hipLaunchKernelGGL(attn_cls_fwd_kernel<false>, dim3(B * H), dim3(CLS_THREADS), lds, s, q, kv, dt, T, H, dh, out, prob);
   }
   PPLL_HIP(hipGetLastError());
@@ -193,11 +194,12 @@ int launch_attention_cls_fwd(hipStream_t s, const void* q, const void* kv, int d
 int launch_attention_cls_bwd(hipStream_t s, const void* q, const void* kv, const float* prob, const void* dout, int dt, int B,
                              int T, int H, int dh, void* dq, void* dkv) {
   const size_t lds = attention_cls_lds_bytes(T, dh);
+  static OncePerDevice once[2];
   if (cls_vec_ok(dt, H, dh, kv, dkv)) {
-    PPLL_TRY(opt_in_lds((const void*)attn_cls_bwd_kernel<true>, lds, "class-token attention"));
+    PPLL_TRY(allow_lds((const void*)attn_cls_bwd_kernel<true>, lds, once[1]));
     hipLaunchKernelGGL(attn_cls_bwd_kernel<true>, dim3(B * H), dim3(CLS_THREADS), lds, s, q, kv, prob, dout, dt, T, H, dh, dq, dkv);
   } else {
-    PPLL_TRY(opt_in_lds((const void*)attn_cls_bwd_kernel<false>, lds, "class-token attention"));
+    PPLL_TRY(allow_lds((const void*)attn_cls_bwd_kernel<false>, lds, once[0]));
     hipLaunchKernelGGL(attn_cls_bwd_kernel<false>, dim3(B * H), dim3(CLS_THREADS), lds, s, q, kv, prob, dout, dt, T, H, dh, dq, dkv);
   }
   PPLL_HIP(hipGetLastError());

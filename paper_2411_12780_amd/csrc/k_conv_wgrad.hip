@@ -251,8 +251,8 @@ int wgt_run(hipStream_t s, const WgtGroup* grp, int n, int of, int B, int H, int
   *blocks = wgt_blocks(g, K::PER, K::NW, of);
   if (!n) return PPLL_OK;
   const size_t lds = K::lds(g);
-  if (lds > 64 * 1024)
-    PPLL_HIP(hipFuncSetAttribute((const void*)conv3x3_wgrad_mfma_kernel<CIT, COT, S>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  static OncePerDevice once;
+  PPLL_TRY(raise_lds((const void*)conv3x3_wgrad_mfma_kernel<CIT, COT, S>, (int)WGT_LDS, once));
   hipLaunchKernelGGL((conv3x3_wgrad_mfma_kernel<CIT, COT, S>), dim3(*blocks, n), dim3(K::TH), lds, s, *grp, g);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;

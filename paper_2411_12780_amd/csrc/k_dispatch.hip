@@ -57,6 +57,15 @@ int profile_end(hipStream_t s, void* token) {
   return PPLL_OK;
 }
 
+int raise_lds(const void* kernel, int bytes, OncePerDevice& once) {
+  int dev = 0;
+  PPLL_HIP(hipGetDevice(&dev));
+  return once(dev, [&]() -> int {
+    PPLL_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+    return PPLL_OK;
+  });
+}
+
 int launch_gemm(hipStream_t s, const GemmArgs& g) {
   if (gemm_rows_supported(g)) return launch_gemm_rows(s, g);   // few output rows: latency, not throughput
   if (const int im = gemm_pipe_choice(g)) return launch_gemm_pipe(s, g, im);                // many tiles: throughput

@@ -9,7 +9,6 @@
 // (32 neighbouring rows: a full 128-byte line).  The four partial tiles meet in LDS and are added in wave order.  The
 // run-time-typed kernel took 22.6 us per product (and 21.6 us for a weight gradient) at 520 rows of width 64.
 // Weight gradients of a step go out as one launch over a table of products, bias gradients (column sums of B) included.
-#include <atomic>
 #include "common.h"
 
 namespace ppll {
@@ -197,11 +196,6 @@ __global__ __launch_bounds__(256) void gemm_f32_grouped_kernel(F32Group a) {
 
 bool al16(const void* p) { return (((uintptr_t)p) & 15) == 0; }
 long f32_bytes(bool tr, int rows, int K, long ld) { return 4 * (tr ? (long)(K - 1) * ld + rows : (long)(rows - 1) * ld + K); }
-bool lds_opt_in_due(std::atomic<bool> (&done)[64]) {   // once per device (see the bf16 kernels)
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return true;
-  return !done[dev].exchange(true);
-}
 long tiles_of(int M, int N, int edge) { return (long)((M + edge - 1) / edge) * ((N + edge - 1) / edge); }
 }  // namespace
 
@@ -239,13 +233,11 @@ int launch_gemm_f32(hipStream_t s, const GemmArgs& g) {
   p.epilogue = g.epilogue; p.C2 = (float*)g.C2; p.aux = (const float*)g.aux; p.ldaux = (int)g.ldaux;
   p.a_bytes = (uint32_t)f32_bytes(at, g.M, g.K, p.lda); p.b_bytes = (uint32_t)f32_bytes(bt, g.N, g.K, p.ldb);
   const bool wide = tiles_of(g.M, g.N, 64) >= F32_WIDE_TILES;
-  static std::atomic<bool> opted_in[64];
-  if (lds_opt_in_due(opted_in)) {
-    PPLL_HIP(hipFuncSetAttribute((const void*)gemm_f32_kernel<false, false, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, f32_lds_bytes<2>()));
-    PPLL_HIP(hipFuncSetAttribute((const void*)gemm_f32_kernel<false, true, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, f32_lds_bytes<2>()));
-    PPLL_HIP(hipFuncSetAttribute((const void*)gemm_f32_kernel<true, false, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, f32_lds_bytes<2>()));
-    PPLL_HIP(hipFuncSetAttribute((const void*)gemm_f32_kernel<true, true, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, f32_lds_bytes<2>()));
-  }
+  static OncePerDevice nn, nt, tn, tt;
+  PPLL_TRY(raise_lds((const void*)gemm_f32_kernel<false, false, 2>, f32_lds_bytes<2>(), nn));
+  PPLL_TRY(raise_lds((const void*)gemm_f32_kernel<false, true, 2>, f32_lds_bytes<2>(), nt));
+  PPLL_TRY(raise_lds((const void*)gemm_f32_kernel<true, false, 2>, f32_lds_bytes<2>(), tn));
+  PPLL_TRY(raise_lds((const void*)gemm_f32_kernel<true, true, 2>, f32_lds_bytes<2>(), tt));
   const int edge = wide ? 64 : 32;
   const dim3 grid((g.N + edge - 1) / edge, (g.M + edge - 1) / edge);
 #define F32_LAUNCH(AT, BT)                                                                                              \
@@ -264,9 +256,8 @@ int launch_gemm_f32(hipStream_t s, const GemmArgs& g) {
 }
 
 int launch_gemm_f32_grouped(hipStream_t s, const GemmArgs* gs, int n) {
-  static std::atomic<bool> opted_in[64];
-  if (lds_opt_in_due(opted_in))
-    PPLL_HIP(hipFuncSetAttribute((const void*)gemm_f32_grouped_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, f32_lds_bytes<2>()));
+  static OncePerDevice once;
+  PPLL_TRY(raise_lds((const void*)gemm_f32_grouped_kernel<2>, f32_lds_bytes<2>(), once));
   for (int j0 = 0; j0 < n; j0 += F32_GROUP_MAX) {
     F32Group a{};
     a.n = n - j0 < F32_GROUP_MAX ? n - j0 : F32_GROUP_MAX;
@@ -441,19 +432,17 @@ __global__ __launch_bounds__(256) void attn_rows_bwd_kernel(const void* qkv, con
   }
 }
 
-int att_dyn_lds(const void* fn, size_t bytes) {
-  if (bytes > 64 * 1024) PPLL_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
-  return PPLL_OK;
-}
+constexpr int ATT_LDS = 160 * 1024;
 }  // namespace
 
 // head rows of all tokens must fit in LDS beside the score rows; at 256 tokens of 64 the backward does not, and the
 // kernels that keep one score row per wave take it
-bool attention_rows_fits(int T, int H, int dh, bool bwd) { return att_lds(att_shape(T, H, dh), bwd) <= 160 * 1024; }
+bool attention_rows_fits(int T, int H, int dh, bool bwd) { return att_lds(att_shape(T, H, dh), bwd) <= ATT_LDS; }
 
 int launch_attention_rows_fwd(hipStream_t s, const void* qkv, int dt, int B, int T, int H, int dh, void* out, float* lse) {
   const size_t lds = att_lds(att_shape(T, H, dh), false);
-  PPLL_TRY(att_dyn_lds((const void*)attn_rows_fwd_kernel, lds));
+  static OncePerDevice once;
+  PPLL_TRY(raise_lds((const void*)attn_rows_fwd_kernel, ATT_LDS, once));
   hipLaunchKernelGGL(attn_rows_fwd_kernel, dim3(B * H, (T + ATT_ROWS - 1) / ATT_ROWS), dim3(256), lds, s, qkv, dt, T, H, dh, out, lse);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;
@@ -461,7 +450,8 @@ int launch_attention_rows_fwd(hipStream_t s, const void* qkv, int dt, int B, int
 int launch_attention_rows_bwd(hipStream_t s, const void* qkv, const void* out, const void* dout, const float* lse, int dt, int B,
                               int T, int H, int dh, void* dqkv) {
   const size_t lds = att_lds(att_shape(T, H, dh), true);
-  PPLL_TRY(att_dyn_lds((const void*)attn_rows_bwd_kernel, lds));
+  static OncePerDevice once;
+  PPLL_TRY(raise_lds((const void*)attn_rows_bwd_kernel, ATT_LDS, once));
   hipLaunchKernelGGL(attn_rows_bwd_kernel, dim3(B * H, 2 * ((T + ATT_ROWS - 1) / ATT_ROWS)), dim3(256), lds, s, qkv, out, dout, lse,
                      dt, T, H, dh, dqkv);
   PPLL_HIP(hipGetLastError());

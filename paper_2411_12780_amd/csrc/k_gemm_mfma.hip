@@ -28,7 +28,6 @@
 // fixed order, so results are reproducible (no float atomics).
 #include "common.h"
 #include "gemm_pipe.h"
-#include <atomic>
 #include <algorithm>
 
 namespace ppll {
@@ -722,13 +721,6 @@ static int balanced_workgroups() {
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
   return (cus / 8) * 8;
 }
-// More than 64 KB of dynamic LDS needs an opt-in per kernel, and the attribute belongs to a device's copy of the
-// kernel: true (once per device and flag set) when the caller still has to raise it on the current device.
-static bool lds_opt_in_due(std::atomic<bool> (&done)[64]) {
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return true;
-  return !done[dev].exchange(true);
-}
 constexpr int BALANCED_MAX_CUTS = 8;
 // room for the parts of the divided tiles: at most two per workgroup
 size_t gemm_mfma_balanced_floats() { return (size_t)balanced_workgroups() * 2 * SLOT_FLOATS; }
@@ -767,12 +759,10 @@ static bool grouped_on_pipe(const GemmArgs* gs, int n, bool balanced, int wgs) {
 }
 
 int launch_gemm_mfma_grouped(hipStream_t s, const GemmArgs* gs, int n, float* ws, size_t ws_floats) {
-  static std::atomic<bool> opted_in[64];
-  if (lds_opt_in_due(opted_in)) {
-    PPLL_HIP(hipFuncSetAttribute((const void*)gemm_pipe_grouped_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, PipeShape::LDS));
-    PPLL_HIP(hipFuncSetAttribute((const void*)gemm_mfma_grouped_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(true, true, 128)));
-    PPLL_HIP(hipFuncSetAttribute((const void*)gemm_mfma_balanced_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(true, true, 128)));
-  }
+  static OncePerDevice pipe_once, grouped_once, balanced_once;
+  PPLL_TRY(raise_lds((const void*)gemm_pipe_grouped_kernel, PipeShape::LDS, pipe_once));
+  PPLL_TRY(raise_lds((const void*)gemm_mfma_grouped_kernel, lds_bytes(true, true, 128), grouped_once));
+  PPLL_TRY(raise_lds((const void*)gemm_mfma_balanced_kernel, lds_bytes(true, true, 128), balanced_once));
   // Balanced launch: the whole set in one launch, a workspace for the divided tiles, tiles that leave a last round
   // partly filled, and a reduction long enough to cut
   const int wgs = balanced_workgroups();
@@ -879,13 +869,11 @@ int launch_gemm_mfma(hipStream_t s, const GemmArgs& g, float* partial, size_t pa
   dim3 grid(p.tiles_m * p.tiles_n, splits);
   if (p.xcd_map == 1) grid = dim3(((p.tiles_m + 7) / 8) * 8 * p.tiles_n, splits);
   if (p.xcd_map == 2) grid = dim3(p.tiles_m * p.tiles_n * splits, 1);
-  static std::atomic<bool> opted_in[64];
-  if (lds_opt_in_due(opted_in)) {
-    PPLL_HIP(hipFuncSetAttribute((const void*)gemm_mfma_kernel<true, true, 128>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(true, true, 128)));
-    PPLL_HIP(hipFuncSetAttribute((const void*)gemm_mfma_kernel<true, false, 128>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(true, false, 128)));
-    PPLL_HIP(hipFuncSetAttribute((const void*)gemm_mfma_kernel<false, true, 128>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(false, true, 128)));
-    PPLL_HIP(hipFuncSetAttribute((const void*)gemm_mfma_kernel<false, false, 128>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes(false, false, 128)));
-  }
+  static OncePerDevice tt, tn, nt, nn;
+  PPLL_TRY(raise_lds((const void*)gemm_mfma_kernel<true, true, 128>, lds_bytes(true, true, 128), tt));
+  PPLL_TRY(raise_lds((const void*)gemm_mfma_kernel<true, false, 128>, lds_bytes(true, false, 128), tn));
+  PPLL_TRY(raise_lds((const void*)gemm_mfma_kernel<false, true, 128>, lds_bytes(false, true, 128), nt));
+  PPLL_TRY(raise_lds((const void*)gemm_mfma_kernel<false, false, 128>, lds_bytes(false, false, 128), nn));
   void* prof = nullptr;
   PPLL_TRY(profile_begin(s, 2.0 * g.M * g.N * g.K, &prof, g.M < 256 && !at ? 2 : 0));   // few output rows: a class of its own
   if (small_m) {

@@ -12,7 +12,6 @@
 // GELU 31.6 -> 28.1.  What bounds it: LDS traffic beside the products in the main loop, and the epilogue where K is short.
 #include "common.h"
 #include "gemm_pipe.h"
-#include <atomic>
 #include <cmath>
 
 namespace ppll {
@@ -141,25 +140,14 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(PipeArgs p
 
 constexpr int WAVES_N = 4, STAGES = 3;
 
-// more than 64 KB of LDS needs an opt-in, once per device
-int opt_in_lds(const void* kernel, int bytes, std::atomic<bool> (&done)[64]) {
-  int dev = 0;
-  PPLL_HIP(hipGetDevice(&dev));
-  const bool known = dev >= 0 && dev < 64;
-  if (known && done[dev].load(std::memory_order_acquire)) return PPLL_OK;
-  PPLL_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
-  if (known) done[dev].store(true, std::memory_order_release);
-  return PPLL_OK;
-}
-
 template <bool BT, int IM>
 int pipe_launch(hipStream_t s, PipeArgs& p) {
   using S = Shape<false, BT, 1, WAVES_N, IM, STAGES>;
   p.tiles_n = (p.N + S::BN - 1) / S::BN;
   p.tiles = (p.M + S::BM - 1) / S::BM * p.tiles_n;
   p.per_xcd = (p.tiles + 7) / 8;
-  static std::atomic<bool> opted_in[64];
-  PPLL_TRY(opt_in_lds((const void*)gemm_pipe_kernel<BT, 1, WAVES_N, IM, STAGES>, S::LDS, opted_in));
+  static OncePerDevice once;
+  PPLL_TRY(raise_lds((const void*)gemm_pipe_kernel<BT, 1, WAVES_N, IM, STAGES>, S::LDS, once));
   hipLaunchKernelGGL((gemm_pipe_kernel<BT, 1, WAVES_N, IM, STAGES>), dim3(8 * p.per_xcd), dim3(S::THREADS), S::LDS, s, p);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;

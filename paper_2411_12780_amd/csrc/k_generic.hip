@@ -1483,10 +1483,10 @@ __global__ __launch_bounds__(256) void attention_bwd_kernel(const void* qkv, con
   }
 }
 
-int set_dyn_lds(const void* fn, size_t bytes) {
-  if (bytes > 160 * 1024) { set_error("attention: %zu bytes of LDS exceed 160 KB", bytes); return PPLL_ERR_CONFIG; }
-  if (bytes > 64 * 1024) PPLL_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
-  return PPLL_OK;
+constexpr int GENERIC_ATT_LDS = 160 * 1024;
+int allow_lds(const void* fn, size_t bytes, OncePerDevice& once) {
+  if (bytes > GENERIC_ATT_LDS) { set_error("attention: %zu bytes of LDS exceed 160 KB", bytes); return PPLL_ERR_CONFIG; }
+  return raise_lds(fn, GENERIC_ATT_LDS, once);
 }
 }  // namespace
 
@@ -1494,7 +1494,8 @@ int launch_attention_fwd_generic(hipStream_t s, const void* qkv, int dt, int B, 
                                  float* lse) {
   if (T > ATT_MAX_T || T < 1) { set_error("attention: tokens %d outside 1..%d", T, ATT_MAX_T); return PPLL_ERR_CONFIG; }
   size_t lds = ((size_t)2 * T * (dh + 1) + 4 * dh + 4 * T) * sizeof(float);
-  PPLL_TRY(set_dyn_lds((const void*)attention_fwd_kernel, lds));
+  static OncePerDevice once;
+  PPLL_TRY(allow_lds((const void*)attention_fwd_kernel, lds, once));
   hipLaunchKernelGGL(attention_fwd_kernel, dim3(B * H), dim3(256), lds, s, qkv, dt, T, H, dh, out, lse);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;
@@ -1504,7 +1505,8 @@ int launch_attention_bwd_generic(hipStream_t s, const void* qkv, const void* out
                                  int dt, int B, int T, int H, int dh, void* dqkv) {
   if (T > ATT_MAX_T || T < 1) { set_error("attention: tokens %d outside 1..%d", T, ATT_MAX_T); return PPLL_ERR_CONFIG; }
   size_t lds = ((size_t)2 * T * (dh + 1) + 8 * dh + 8 * T + 2 * T) * sizeof(float);
-  PPLL_TRY(set_dyn_lds((const void*)attention_bwd_kernel, lds));
+  static OncePerDevice once;
+  PPLL_TRY(allow_lds((const void*)attention_bwd_kernel, lds, once));
   hipLaunchKernelGGL(attention_bwd_kernel, dim3(B * H), dim3(256), lds, s, qkv, out, dout, lse, dt, T, H, dh, dqkv);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;

@@ -626,17 +626,9 @@ long conv_mfma_blocks(long P) {
 }
 template <int MODE, int K16, int NT, int GRP, bool LIN, bool STAT>
 int conv_mfma_launch_g(hipStream_t s, const ConvArgs& p, long P, size_t lds) {
-  static bool raised[64] = {};    // per device: the attribute belongs to the device's copy of the kernel
   lds += STAT ? CONV_STAT_LDS : 0;
-  if (lds > 64 * 1024) {
-    int dev = 0;
-    PPLL_HIP(hipGetDevice(&dev));
-    if (dev < 0 || dev >= 64 || !raised[dev]) {
-      PPLL_HIP(hipFuncSetAttribute((const void*)conv3x3_mfma_kernel<MODE, K16, NT, GRP, LIN, STAT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   (int)(CONV_MFMA_LDS_MAX + CONV_STAT_LDS)));
-      if (dev >= 0 && dev < 64) raised[dev] = true;
-    }
-  }
+  static OncePerDevice once;
+  PPLL_TRY(raise_lds((const void*)conv3x3_mfma_kernel<MODE, K16, NT, GRP, LIN, STAT>, (int)(CONV_MFMA_LDS_MAX + CONV_STAT_LDS), once));
   hipLaunchKernelGGL((conv3x3_mfma_kernel<MODE, K16, NT, GRP, LIN, STAT>), dim3((unsigned)conv_mfma_blocks(P)), dim3(256), lds, s, p);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;
@@ -681,16 +673,8 @@ bool conv_bf16_supported(int dt, int wdt, int Ci, int Co, const void* a, const v
 
 template <int K16, int NT>
 static int conv_dgrad_s2_launch_k(hipStream_t s, const ConvArgs& p, size_t lds) {
-  static bool raised[64] = {};
-  if (lds > 64 * 1024) {
-    int dev = 0;
-    PPLL_HIP(hipGetDevice(&dev));
-    if (dev < 0 || dev >= 64 || !raised[dev]) {
-      PPLL_HIP(hipFuncSetAttribute((const void*)conv3x3_dgrad_s2_kernel<K16, NT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   (int)CONV_MFMA_LDS_MAX));
-      if (dev >= 0 && dev < 64) raised[dev] = true;
-    }
-  }
+  static OncePerDevice once;
+  PPLL_TRY(raise_lds((const void*)conv3x3_dgrad_s2_kernel<K16, NT>, (int)CONV_MFMA_LDS_MAX, once));
   const long pc = (long)p.B * (p.H / 2) * (p.W / 2), tiles = 4 * ((pc + 127) / 128);
   const long tpw = tiles >= 8192 ? 4 : (tiles >= 4096 ? 2 : 1);
   hipLaunchKernelGGL((conv3x3_dgrad_s2_kernel<K16, NT>), dim3((unsigned)((tiles + tpw - 1) / tpw)), dim3(256), lds, s, p);

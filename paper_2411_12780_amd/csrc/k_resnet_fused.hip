@@ -18,7 +18,6 @@
 // waves per compute unit, two with 16 channels and of four waves: few enough partial sums for every workgroup of the next
 // kernel to add them up itself.  ReLU masks travel as one bit an element.  Partial sums, parameters, first tile and filter are
 // asked for together: waiting for them in turn, a small forward launch took 10.8 instead of 7.1 us.
-#include <atomic>
 #include "resnet_bf16.h"
 
 namespace ppll {
@@ -367,18 +366,23 @@ int compute_units() {
   return cus;
 }
 
+// rows of an image that a tile of 32 `waves` pixels takes, and its bytes in LDS
+constexpr int tile_rows(int waves, int H, int W) { return 32 * waves / W < H ? 32 * waves / W : H; }
+constexpr int tile_bytes(int waves, int H, int W, int C) {
+  return 32 * waves / W / tile_rows(waves, H, W) * (tile_rows(waves, H, W) + 2) * (W + 2) * pixel_pitch(C);
+}
+constexpr int most_tile_bytes(int C, int waves) {   // of any map that conv_bn_ok accepts
+  int most = 0;
+  for (int H = 8; H <= 32; H *= 2)
+    for (int W = 8; W <= 32; W *= 2) most = tile_bytes(waves, H, W, C) > most ? tile_bytes(waves, H, W, C) : most;
+  return most;
+}
+
 template <int C, int WAVES, bool BWD>
-int conv_bn_launch(hipStream_t s, const ConvBnArgs& p, int grid, int tile_px_bytes) {
-  const int lds = filter_bytes<C, BWD>() + tile_px_bytes;
-  static std::atomic<int> raised[64];
-  if (lds > 48 * 1024) {
-    int dev = 0;
-    PPLL_HIP(hipGetDevice(&dev));
-    if (dev < 0 || dev >= 64 || raised[dev].load() < lds) {
-      PPLL_HIP(hipFuncSetAttribute((const void*)conv_bn_kernel<C, WAVES, BWD>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-      if (dev >= 0 && dev < 64) raised[dev].store(lds);
-    }
-  }
+int conv_bn_launch(hipStream_t s, const ConvBnArgs& p, int grid, int in_lds) {
+  const int lds = filter_bytes<C, BWD>() + in_lds;
+  static OncePerDevice once;
+  PPLL_TRY(raise_lds((const void*)conv_bn_kernel<C, WAVES, BWD>, filter_bytes<C, BWD>() + most_tile_bytes(C, WAVES), once));
   hipLaunchKernelGGL((conv_bn_kernel<C, WAVES, BWD>), dim3(grid), dim3(64 * WAVES), lds, s, p);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;
@@ -393,7 +397,7 @@ TileShape tile_shape(int B, int H, int W, int C) {
   const int cus = compute_units();
   t.waves = px >= 200L * 256 ? 8 : 4;
   const int rt = 32 * t.waves / W;
-  t.sr = rt < H ? rt : H;
+  t.sr = tile_rows(t.waves, H, W);
   t.seg = rt / t.sr;
   t.tiles = (int)(((long)B * H + rt - 1) / rt);
   const int most = t.waves == 8 && C > 16 ? cus : 2 * cus, per = (t.tiles + most - 1) / most;
@@ -405,11 +409,11 @@ int conv_bn_dispatch(hipStream_t s, ConvBnArgs& p, int B, int H, int W, int C, i
   const TileShape t = tile_shape(B, H, W, C);
   p.H = H; p.wl = log2_of(W); p.rows = B * H; p.sr = t.sr; p.srl = log2_of(t.sr); p.seg = t.seg;
   p.inv = (65536 + t.sr + 1) / (t.sr + 2); p.tiles = t.tiles; p.bytes = (uint32_t)((long)B * H * W * C * 2);
-  const int tile_bytes = t.seg * (t.sr + 2) * (W + 2) * pixel_pitch(C);
+  const int in_lds = tile_bytes(t.waves, H, W, C);
   if (stat_blocks) *stat_blocks = p.stat ? t.grid : 0;
-  if (C == 16) return t.waves == 8 ? conv_bn_launch<16, 8, BWD>(s, p, t.grid, tile_bytes) : conv_bn_launch<16, 4, BWD>(s, p, t.grid, tile_bytes);
-  if (C == 32) return t.waves == 8 ? conv_bn_launch<32, 8, BWD>(s, p, t.grid, tile_bytes) : conv_bn_launch<32, 4, BWD>(s, p, t.grid, tile_bytes);
-  return t.waves == 8 ? conv_bn_launch<64, 8, BWD>(s, p, t.grid, tile_bytes) : conv_bn_launch<64, 4, BWD>(s, p, t.grid, tile_bytes);
+  if (C == 16) return t.waves == 8 ? conv_bn_launch<16, 8, BWD>(s, p, t.grid, in_lds) : conv_bn_launch<16, 4, BWD>(s, p, t.grid, in_lds);
+  if (C == 32) return t.waves == 8 ? conv_bn_launch<32, 8, BWD>(s, p, t.grid, in_lds) : conv_bn_launch<32, 4, BWD>(s, p, t.grid, in_lds);
+  return t.waves == 8 ? conv_bn_launch<64, 8, BWD>(s, p, t.grid, in_lds) : conv_bn_launch<64, 4, BWD>(s, p, t.grid, in_lds);
 }
 }  // namespace
 

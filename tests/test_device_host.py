@@ -1,0 +1,74 @@
+"""Host-side device bookkeeping of the launchers (csrc/device.h), compiled for the CPU with the system compiler."""
+import os
+import re
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2411_12780_amd", "csrc")
+
+
+def run_cpp(tmp_path, source):
+    src, exe = tmp_path / "t.cpp", tmp_path / "t"
+    src.write_text(source)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-I", CSRC, str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+ONCE = r"""
+#include <chrono>
+#include <cstdio>
+#include <thread>
+#include "device.h"
+#define CHECK(x) do { if (!(x)) { std::printf("failed: %s\n", #x); return 1; } } while (0)
+int main() {
+  // a second thread arrives while the first is still setting: it may not go on before a set has been completed
+  ppll::OncePerDevice once;
+  std::atomic<bool> entered{false}, second_back{false};
+  std::atomic<int> completed{0};
+  std::thread first([&] {
+    once(0, [&] {
+      entered = true;
+      for (int i = 0; i < 2000 && !second_back; ++i) std::this_thread::sleep_for(std::chrono::milliseconds(1));
+      ++completed;
+      return 0;
+    });
+  });
+  while (!entered) std::this_thread::yield();
+  const int status = once(0, [&] { ++completed; return 0; });
+  const int completed_before_second_went_on = completed;
+  second_back = true;
+  first.join();
+  CHECK(status == 0 && completed_before_second_went_on >= 1);
+  // done: not set again; another device on its own; a failure is reported and tried again
+  int calls = 0;
+  CHECK(once(0, [&] { ++calls; return 0; }) == 0 && calls == 0);
+  CHECK(once(1, [&] { ++calls; return 7; }) == 7 && calls == 1);
+  CHECK(once(1, [&] { ++calls; return 0; }) == 0 && calls == 2);
+  CHECK(once(1, [&] { ++calls; return 0; }) == 0 && calls == 2);
+  // devices beyond the table are set every time
+  for (int dev : {-1, ppll::MAX_DEVICES}) {
+    calls = 0;
+    once(dev, [&] { ++calls; return 0; });
+    once(dev, [&] { ++calls; return 0; });
+    CHECK(calls == 2);
+  }
+  return 0;
+}
+"""
+
+
+def test_a_kernel_attribute_counts_as_raised_only_once_it_is(tmp_path):
+    run_cpp(tmp_path, ONCE)
+
+
+def test_the_lds_attribute_is_raised_in_one_place_to_a_size_of_the_kernel_alone():
+    places, raised = [], []
+    for f in sorted(os.listdir(CSRC)):
+        text = open(os.path.join(CSRC, f)).read()
+        places += [f] * text.count("hipFuncSetAttribute(")
+        raised += [(f, m) for m in re.findall(r"raise_lds\(\(const void\*\)[^;]*?, (?:\(int\))?([^;]*), \w+(?:\[\d\])?\)\)?;", text)]
+    assert places == ["k_dispatch.hip"]
+    # a size handed to the launch at hand is called lds; the matrix-core attention's is a function of its template argument
+    assert len(raised) >= 15
+    assert {f for f, m in raised if m == "lds"} <= {"k_attn_mfma.hip"}, raised
