@@ -38,6 +38,9 @@ void set_error(const char* fmt, ...);
 // it on the current device.  `bytes` is the most that any launch of the kernel asks for, never the size at hand: a thread with a
 // smaller one would lower what another has just raised.
 int raise_lds(const void* kernel, int bytes, OncePerDevice& once);
+// Compute units of the current device, 0 where there is none.  The rules of most launches ask, so the runtime is asked once per
+// device: its query takes 117 ns, and a batch of a four-block pipeline of small blocks, bound by the host, asked some 130 times.
+int compute_units();
 
 #ifdef __HIPCC__
 // bf16 <-> fp32 by bit manipulation, round to nearest even.

@@ -22,4 +22,21 @@ class OncePerDevice {
   }
 };
 
+// A positive number that `query` gives for a device (0 or less: it could not say), asked for once.
+class PerDevice {
+  std::atomic<int> value_[MAX_DEVICES] = {};
+
+ public:
+  template <class Query> int operator()(int dev, Query query) {
+    const bool known = dev >= 0 && dev < MAX_DEVICES;
+    if (known) {
+      const int v = value_[dev].load(std::memory_order_relaxed);
+      if (v > 0) return v;
+    }
+    const int v = query();
+    if (known && v > 0) value_[dev].store(v, std::memory_order_relaxed);
+    return v;
+  }
+};
+
 }  // namespace ppll

@@ -223,17 +223,11 @@ WgtShape wgt_shape(int B, int H, int W, int stride) {
   g.tiles = (B + g.seg - 1) / g.seg * g.nrc * g.ncc;
   return g;
 }
-int wgt_compute_units() {
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
-  return cus;
-}
-
 // Workgroups per convolution: the n of a launch share one round of the places on the device.  A partial filter is written and
 // read once more (8 bytes a weight at about 4 bytes a picosecond), a tile takes a workgroup about 3 us: in r rounds of tiles,
 // 3 us x r + 2 ps x workgroups x n x weights.
 int wgt_blocks(const WgtShape& g, int per, int weights, int n) {
-  const int places = std::max(1, per * wgt_compute_units() / n);
+  const int cus = compute_units(), units = cus > 0 ? cus : 256, places = std::max(1, per * units / n);
   int best = 1;
   double least = 1e30;
   for (int r = (g.tiles + places - 1) / places; 3.0 * r < least; ++r) {

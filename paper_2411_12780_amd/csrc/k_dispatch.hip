@@ -66,6 +66,16 @@ int raise_lds(const void* kernel, int bytes, OncePerDevice& once) {
   });
 }
 
+int compute_units() {
+  static PerDevice units;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 0;
+  return units(dev, [&] {
+    int n = 0;
+    return hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess ? n : 0;
+  });
+}
+
 int launch_gemm(hipStream_t s, const GemmArgs& g) {
   if (gemm_rows_supported(g)) return launch_gemm_rows(s, g);   // few output rows: latency, not throughput
   if (const int im = gemm_pipe_choice(g)) return launch_gemm_pipe(s, g, im);                // many tiles: throughput

@@ -715,12 +715,7 @@ bool gemm_mfma_groupable(const GemmArgs& g) {
 }
 
 // Workgroups of a balanced grouped launch on the current device: one per compute unit, a multiple of 8.
-static int balanced_workgroups() {
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  return (cus / 8) * 8;
-}
+static int balanced_workgroups() { return compute_units() / 8 * 8; }
 constexpr int BALANCED_MAX_CUTS = 8;
 // room for the parts of the divided tiles: at most two per workgroup
 size_t gemm_mfma_balanced_floats() { return (size_t)balanced_workgroups() * 2 * SLOT_FLOATS; }

@@ -159,11 +159,6 @@ double rounds(long tiles, int places) {
   const long full = tiles / places, rest = tiles % places;
   return full + (rest == 0 ? 0.0 : 2 * rest <= places ? 0.62 : 1.0);
 }
-int workgroup_places() {   // on the current device
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  return 2 * cus;
-}
 long tile_count(int M, int N, int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); }
 }  // namespace
 
@@ -177,7 +172,7 @@ int gemm_pipe_choice(const GemmArgs& g) {
   const bool bt = g.b_sn == 1 && g.b_sk != 1;
   // 32-bit byte offsets also for the rows (k rows) of the last tile that do not exist
   if (g.a_sm > (1 << 20) || (bt ? g.b_sk : g.b_sn) > (1 << 20)) return 0;
-  const int places = workgroup_places();
+  const int places = 2 * compute_units();
   if (places < 16) return 0;
   const double tiled = rounds(tile_count(g.M, g.N, 128, 128), places);
   const double c4 = 1.58 * rounds(tile_count(g.M, g.N, 128, 256), places), c5 = 1.74 * rounds(tile_count(g.M, g.N, 160, 256), places);

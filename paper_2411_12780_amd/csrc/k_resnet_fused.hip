@@ -360,12 +360,6 @@ __global__ __launch_bounds__(64 * WAVES, C == 16 ? 4 : 1) void conv_bn_kernel(Co
 
 bool cb_al16(const void* p) { return !(((uintptr_t)p) & 15); }
 int log2_of(int v) { int l = 0; while ((1 << l) < v) ++l; return l; }
-int compute_units() {
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
-  return cus;
-}
-
 // rows of an image that a tile of 32 `waves` pixels takes, and its bytes in LDS
 constexpr int tile_rows(int waves, int H, int W) { return 32 * waves / W < H ? 32 * waves / W : H; }
 constexpr int tile_bytes(int waves, int H, int W, int C) {
@@ -394,7 +388,7 @@ struct TileShape { int waves, sr, seg, tiles, grid; };
 TileShape tile_shape(int B, int H, int W, int C) {
   TileShape t{};
   const long px = (long)B * H * W;
-  const int cus = compute_units();
+  const int units = compute_units(), cus = units > 0 ? units : 256;
   t.waves = px >= 200L * 256 ? 8 : 4;
   const int rt = 32 * t.waves / W;
   t.sr = tile_rows(t.waves, H, W);

@@ -62,6 +62,30 @@ def test_a_kernel_attribute_counts_as_raised_only_once_it_is(tmp_path):
     run_cpp(tmp_path, ONCE)
 
 
+PER_DEVICE = r"""
+#include <cstdio>
+#include "device.h"
+#define CHECK(x) do { if (!(x)) { std::printf("failed: %s\n", #x); return 1; } } while (0)
+int main() {
+  ppll::PerDevice units;
+  int asked = 0;
+  for (int i = 0; i < 3; ++i) CHECK(units(0, [&] { ++asked; return 256; }) == 256);
+  CHECK(asked == 1);
+  CHECK(units(1, [&] { return 0; }) == 0);          // no answer: asked again
+  CHECK(units(1, [&] { return 304; }) == 304);
+  CHECK(units(0, [&] { return 1; }) == 256);
+  CHECK(units(ppll::MAX_DEVICES, [&] { return 2; }) == 2 && units(ppll::MAX_DEVICES, [&] { return 3; }) == 3);
+  return 0;
+}
+"""
+
+
+def test_a_device_is_asked_for_its_compute_units_once(tmp_path):
+    run_cpp(tmp_path, PER_DEVICE)
+    asking = [f for f in os.listdir(CSRC) if "hipDeviceAttributeMultiprocessorCount" in open(os.path.join(CSRC, f)).read()]
+    assert asking == ["k_dispatch.hip"]
+
+
 def test_the_lds_attribute_is_raised_in_one_place_to_a_size_of_the_kernel_alone():
     places, raised = [], []
     for f in sorted(os.listdir(CSRC)):
