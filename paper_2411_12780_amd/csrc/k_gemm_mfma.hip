@@ -28,7 +28,7 @@
 // fixed order, so results are reproducible (no float atomics).
 #include "common.h"
 #include "gemm_pipe.h"
-#include <algorithm>
+#include "plan.h"
 
 namespace ppll {
 
@@ -498,7 +498,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma_grouped_kernel(GroupedArgs a
 // Whole steps with 128 x 128 tiles and with these, microseconds: 25216 rows of width 768 6048 -> 5842, 640 rows 748 -> 732.
 using PipeShape = pipe::Shape<true, true, 1, 4, 4, 3>;
 constexpr int PIPE_BN = PipeShape::BN;
-static_assert(PipeShape::BM == BM, "");
+static_assert(PipeShape::BM == BM && BM == WG_EDGE && BN == WG_EDGE && PIPE_BN == WG_WIDE && BK == WG_STEP, "");
 __global__ __launch_bounds__(PipeShape::THREADS, 2) void gemm_pipe_grouped_kernel(GroupedArgs a) {
   extern __shared__ __align__(1024) char smem[];
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
@@ -716,7 +716,6 @@ bool gemm_mfma_groupable(const GemmArgs& g) {
 
 // Workgroups of a balanced grouped launch on the current device: one per compute unit, a multiple of 8.
 static int balanced_workgroups() { return compute_units() / 8 * 8; }
-constexpr int BALANCED_MAX_CUTS = 8;
 // room for the parts of the divided tiles: at most two per workgroup
 size_t gemm_mfma_balanced_floats() { return (size_t)balanced_workgroups() * 2 * SLOT_FLOATS; }
 
@@ -731,76 +730,44 @@ static void fill_problem(GroupedProblem& q, const GemmArgs& g, int first_tile, i
   q.c_bytes = (uint32_t)(((long)(g.M - 1) * g.ldc + g.N) * 4);
 }
 
-// Whether a set of products runs on 128 x 256 tiles.  Per k a tile takes 1.58 times as long as one of 128 x 128 (two workgroups
-// to a unit either way), so the padded tiles decide: width 768 has none, width 384 (1.5 tiles) loses.  Without a workspace the
-// launch runs beside other work, which fills what it leaves idle.  With one, the alternative is the balanced launch, whose
-// rounds are full.
-static bool grouped_on_pipe(const GemmArgs* gs, int n, bool balanced, int wgs) {
-  double narrow = 0.0, wide = 0.0;
-  long tiles = 0;
-  for (int j = 0; j < n; ++j) {
-    if (gs[j].a_sk > (1 << 20) || gs[j].b_sk > (1 << 20)) return false;   // 32-bit byte offsets for the k rows of a last stage that do not exist
-    const long tm = (gs[j].M + BM - 1) / BM, t = tm * ((gs[j].N + PIPE_BN - 1) / PIPE_BN);
-    narrow += (double)tm * ((gs[j].N + BN - 1) / BN) * gs[j].K;
-    wide += 1.58 * t * gs[j].K;
-    tiles += t;
-  }
-  if (tiles < wgs / 2) return false;
-  if (balanced) {
-    const long full = tiles / (2L * wgs), rest = tiles % (2L * wgs);
-    wide *= (full + (rest == 0 ? 0.0 : rest <= wgs ? 0.62 : 1.0)) * 2 * wgs / tiles;
-  }
-  return wide < 0.95 * narrow;
-}
-
 int launch_gemm_mfma_grouped(hipStream_t s, const GemmArgs* gs, int n, float* ws, size_t ws_floats) {
   static OncePerDevice pipe_once, grouped_once, balanced_once;
   PPLL_TRY(raise_lds((const void*)gemm_pipe_grouped_kernel, PipeShape::LDS, pipe_once));
   PPLL_TRY(raise_lds((const void*)gemm_mfma_grouped_kernel, lds_bytes(true, true, 128), grouped_once));
   PPLL_TRY(raise_lds((const void*)gemm_mfma_balanced_kernel, lds_bytes(true, true, 128), balanced_once));
-  // Balanced launch: the whole set in one launch, a workspace for the divided tiles, tiles that leave a last round
-  // partly filled, and a reduction long enough to cut
+  std::vector<ProductShape> shapes(n);
+  bool wide_ok = true;    // 32-bit byte offsets for the k rows of a last stage that do not exist
+  for (int j = 0; j < n; ++j) {
+    shapes[j] = {gs[j].M, gs[j].N, gs[j].K};
+    wide_ok = wide_ok && gs[j].a_sk <= (1 << 20) && gs[j].b_sk <= (1 << 20);
+  }
   const int wgs = balanced_workgroups();
-  const bool balanced = ws && wgs >= 8 && n <= GROUP_MAX && ws_floats >= (size_t)wgs * 2 * SLOT_FLOATS;
-  const bool on_pipe = wgs >= 8 && grouped_on_pipe(gs, n, balanced, wgs);
-  if (balanced && !on_pipe) {
+  const bool workspace = ws && n <= GROUP_MAX && ws_floats >= (size_t)wgs * 2 * SLOT_FLOATS;
+  const WeightGradPlan plan = plan_weight_grads(shapes.data(), n, workspace, wide_ok, wgs);
+  if (plan.cuts > 1) {
     BalancedArgs a{};
     a.n = n; a.ws = ws;
-    constexpr int LONG_NKT = 8;                     // k-steps from which a reduction counts as long enough to cut
-    int tiles = 0, min_nkt = 1 << 30, filled = 0;
+    a.total_tiles = plan.tiles; a.long_tiles = plan.long_tiles; a.whole_tiles = plan.whole_tiles; a.cuts = plan.cuts;
+    int tiles = 0, filled = 0;
     double flops = 0.0;
     for (int pass = 0; pass < 2; ++pass) {          // long reductions first, then the short ones
       for (int j = 0; j < n; ++j) {
-        const int nkt = (gs[j].K + BK - 1) / BK;
-        if ((nkt >= LONG_NKT) != (pass == 0)) continue;
+        if ((wg_steps(gs[j].K) >= plan.long_steps) != (pass == 0)) continue;
         fill_problem(a.prob[filled], gs[j], tiles);
         tiles += a.prob[filled].tiles_m * a.prob[filled].tiles_n;
         ++filled;
-        if (pass == 0) min_nkt = std::min(min_nkt, nkt);
         flops += 2.0 * gs[j].M * gs[j].N * gs[j].K;
       }
-      if (pass == 0) a.long_tiles = tiles;
     }
-    const int rest = a.long_tiles % wgs;
-    // parts per left-over tile: 2, more when the left-over tiles are few (measured at 89 left-over tiles on 256 units:
-    // 2 parts 124 + 10 us for the two kernels, 3 parts 123 + 13, 4 parts 121 + 16; undivided 160); with no whole tiles
-    // beside them, one part per unit.  Each of 4 k-steps or more, within the workspace
-    int cuts = rest == 0 ? 1 : a.long_tiles < wgs ? std::max(2, wgs / rest) : std::max(2, wgs / (2 * rest));
-    cuts = std::min(cuts, BALANCED_MAX_CUTS);
-    while (cuts > 1 && (min_nkt / cuts < 4 || (long)rest * cuts > 2L * wgs)) --cuts;
-    if (rest > 0 && cuts > 1) {
-      a.total_tiles = tiles; a.whole_tiles = a.long_tiles - rest; a.cuts = cuts;
-      void* prof = nullptr;
-      PPLL_TRY(profile_begin(s, flops, &prof));
-      const int parts = rest * cuts;
-      const int grid = 8 * ((a.whole_tiles + 7) / 8 + (parts + 7) / 8 + (tiles - a.long_tiles + 7) / 8);
-      hipLaunchKernelGGL(gemm_mfma_balanced_kernel, dim3(grid), dim3(256), lds_bytes(true, true, 128), s, a);
-      PPLL_HIP(hipGetLastError());
-      hipLaunchKernelGGL(gemm_mfma_balanced_sum_kernel, dim3(4 * rest), dim3(256), 0, s, a);
-      PPLL_HIP(hipGetLastError());
-      PPLL_TRY(profile_end(s, prof));
-      return PPLL_OK;
-    }
+    const int rest = a.long_tiles - a.whole_tiles, parts = rest * a.cuts;
+    void* prof = nullptr;
+    PPLL_TRY(profile_begin(s, flops, &prof));
+    const int grid = 8 * ((a.whole_tiles + 7) / 8 + (parts + 7) / 8 + (tiles - a.long_tiles + 7) / 8);
+    hipLaunchKernelGGL(gemm_mfma_balanced_kernel, dim3(grid), dim3(256), lds_bytes(true, true, 128), s, a);
+    PPLL_HIP(hipGetLastError());
+    hipLaunchKernelGGL(gemm_mfma_balanced_sum_kernel, dim3(4 * rest), dim3(256), 0, s, a);
+    PPLL_HIP(hipGetLastError());
+    return profile_end(s, prof);
   }
 
   for (int j0 = 0; j0 < n; j0 += GROUP_MAX) {
@@ -810,7 +777,7 @@ int launch_gemm_mfma_grouped(hipStream_t s, const GemmArgs* gs, int n, float* ws
     double flops = 0.0;
     for (int j = 0; j < a.n; ++j) {
       const GemmArgs& g = gs[j0 + j];
-      fill_problem(a.prob[j], g, tiles, on_pipe ? PIPE_BN : BN);
+      fill_problem(a.prob[j], g, tiles, plan.wide ? PIPE_BN : BN);
       tiles += a.prob[j].tiles_m * a.prob[j].tiles_n;
       flops += 2.0 * g.M * g.N * g.K;
     }
@@ -818,7 +785,7 @@ int launch_gemm_mfma_grouped(hipStream_t s, const GemmArgs* gs, int n, float* ws
     a.per_xcd = (tiles + 7) / 8;
     void* prof = nullptr;
     PPLL_TRY(profile_begin(s, flops, &prof));
-    if (on_pipe) hipLaunchKernelGGL(gemm_pipe_grouped_kernel, dim3(8 * a.per_xcd), dim3(PipeShape::THREADS), PipeShape::LDS, s, a);
+    if (plan.wide) hipLaunchKernelGGL(gemm_pipe_grouped_kernel, dim3(8 * a.per_xcd), dim3(PipeShape::THREADS), PipeShape::LDS, s, a);
     else hipLaunchKernelGGL(gemm_mfma_grouped_kernel, dim3(8 * a.per_xcd), dim3(256), lds_bytes(true, true, 128), s, a);
     PPLL_HIP(hipGetLastError());
     PPLL_TRY(profile_end(s, prof));

@@ -1,0 +1,74 @@
+// Rules of the dispatch that are pure functions of sizes and of the device's compute units.  No HIP in here.
+#pragma once
+#include <algorithm>
+
+namespace ppll {
+
+struct ProductShape { int M, N, K; };
+
+// ---- A set of weight-gradient products C_j[M,N] = A_j^T B_j, reductions over K (batch x tokens) rows, in one launch
+constexpr int WG_EDGE = 128, WG_WIDE = 256, WG_STEP = 64;      // output tiles of 128 x 128 or 128 x 256; k of a step of the former
+constexpr int WG_MAX_CUTS = 8;
+struct WeightGradPlan {
+  bool wide;         // tiles of 128 x 256, every one whole
+  // else, with cuts > 1, tiles of 128 x 128, some divided along k: the products with a long reduction come first, their tiles
+  // [0, whole_tiles) run whole, [whole_tiles, long_tiles) in `cuts` parts each, the tiles of the others whole at the end
+  int cuts, long_tiles, whole_tiles, tiles;
+  int long_steps;    // steps from which a reduction counts as long
+};
+
+inline int wg_steps(int K) { return (K + WG_STEP - 1) / WG_STEP; }
+inline long wg_tiles(const ProductShape& p, int width) { return (long)((p.M + WG_EDGE - 1) / WG_EDGE) * ((p.N + width - 1) / width); }
+
+// Whether a set of products runs on 128 x 256 tiles.  Per k a tile takes 1.58 times as long as one of 128 x 128 (two workgroups
+// to a unit either way), so the padded tiles decide: width 768 has none, width 384 (1.5 tiles) loses.  Without a workspace the
+// launch runs beside other work, which fills what it leaves idle.  With one, the alternative is the divided launch, whose
+// rounds are full.
+inline bool wg_on_wide_tiles(const ProductShape* p, int n, bool workspace, int units) {
+  double narrow = 0.0, wide = 0.0;
+  long tiles = 0;
+  for (int j = 0; j < n; ++j) {
+    narrow += (double)wg_tiles(p[j], WG_EDGE) * p[j].K;
+    wide += 1.58 * wg_tiles(p[j], WG_WIDE) * p[j].K;
+    tiles += wg_tiles(p[j], WG_WIDE);
+  }
+  if (units < 8 || tiles < units / 2) return false;
+  if (workspace) {
+    const long full = tiles / (2L * units), rest = tiles % (2L * units);
+    wide *= (full + (rest == 0 ? 0.0 : rest <= units ? 0.62 : 1.0)) * 2 * units / tiles;
+  }
+  return wide < 0.95 * narrow;
+}
+
+// workspace: there is room for two parts per unit, and the launch is the only one beside which nothing else runs.
+// wide_ok: the strides allow the wide tiles
+inline WeightGradPlan plan_weight_grads(const ProductShape* p, int n, bool workspace, bool wide_ok, int units) {
+  WeightGradPlan w{};
+  w.cuts = 1;
+  w.wide = wide_ok && wg_on_wide_tiles(p, n, workspace, units);
+  int longest = 0;
+  for (int j = 0; j < n; ++j) longest = std::max(longest, wg_steps(p[j].K));
+  // Long enough to be cut: 8 steps, and a quarter of the longest of the set.  A block of 512 images has reductions over 33280
+  // rows and, in the class-token layer, over 512 (8 steps): counted as long, those tiles were cut
+  // as well, the long ones into no more parts (width 384, two layers: a step took 1255 us, 1091 with them whole at the end).
+  w.long_steps = std::max(8, (longest + 3) / 4);
+  int least = 1 << 30;
+  for (int j = 0; j < n; ++j) {
+    const int t = (int)wg_tiles(p[j], WG_EDGE);
+    w.tiles += t;
+    if (wg_steps(p[j].K) >= w.long_steps) { w.long_tiles += t; least = std::min(least, wg_steps(p[j].K)); }
+  }
+  const int rest = units > 0 ? w.long_tiles % units : 0;
+  w.whole_tiles = w.long_tiles - rest;
+  if (w.wide || !workspace || units < 8 || rest == 0) return w;
+  // Parts per left-over tile: 2, more when the left-over tiles are few (measured at 89 left-over tiles on 256 units: 2 parts
+  // 124 + 10 us for the two kernels, 3 parts 123 + 13, 4 parts 121 + 16; undivided 160); with no whole tiles beside them, one
+  // part per unit.  Each of 4 steps or more, within the workspace.
+  int cuts = w.whole_tiles == 0 ? std::max(2, units / rest) : std::max(2, units / (2 * rest));
+  cuts = std::min(cuts, WG_MAX_CUTS);
+  while (cuts > 1 && (least / cuts < 4 || (long)rest * cuts > 2L * units)) --cuts;
+  w.cuts = cuts;
+  return w;
+}
+
+}  // namespace ppll

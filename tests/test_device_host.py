@@ -1,18 +1,8 @@
 """Host-side device bookkeeping of the launchers (csrc/device.h), compiled for the CPU with the system compiler."""
 import os
 import re
-import subprocess
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-CSRC = os.path.join(ROOT, "paper_2411_12780_amd", "csrc")
-
-
-def run_cpp(tmp_path, source):
-    src, exe = tmp_path / "t.cpp", tmp_path / "t"
-    src.write_text(source)
-    subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-I", CSRC, str(src), "-o", str(exe)], check=True)
-    r = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
-    assert r.returncode == 0, r.stdout + r.stderr
+from host_cpp import CSRC, compile_cpp, run
 
 
 ONCE = r"""
@@ -59,7 +49,7 @@ int main() {
 
 
 def test_a_kernel_attribute_counts_as_raised_only_once_it_is(tmp_path):
-    run_cpp(tmp_path, ONCE)
+    run(compile_cpp(tmp_path, ONCE))
 
 
 PER_DEVICE = r"""
@@ -81,7 +71,7 @@ int main() {
 
 
 def test_a_device_is_asked_for_its_compute_units_once(tmp_path):
-    run_cpp(tmp_path, PER_DEVICE)
+    run(compile_cpp(tmp_path, PER_DEVICE))
     asking = [f for f in os.listdir(CSRC) if "hipDeviceAttributeMultiprocessorCount" in open(os.path.join(CSRC, f)).read()]
     assert asking == ["k_dispatch.hip"]
 

@@ -1,0 +1,78 @@
+"""The rules of the dispatch (csrc/plan.h) at 256 compute units, compiled for the CPU: which kernel a shape goes to and how its
+work is cut."""
+import pytest
+
+from host_cpp import compile_cpp, run
+
+UNITS = 256
+
+MAIN = r"""
+#include <cstdio>
+#include <cstring>
+#include <vector>
+#include "plan.h"
+using namespace ppll;
+int main() {
+  char what[32];
+  while (std::scanf("%31s", what) == 1) {
+    if (!std::strcmp(what, "wgrad")) {
+      int units, workspace, n;
+      if (std::scanf("%d %d %d", &units, &workspace, &n) != 3) return 1;
+      std::vector<ProductShape> p(n);
+      for (ProductShape& q : p) if (std::scanf("%d %d %d", &q.M, &q.N, &q.K) != 3) return 1;
+      const WeightGradPlan w = plan_weight_grads(p.data(), n, workspace, true, units);
+      std::printf("%d %d %d %d %d %d\n", w.wide, w.cuts, w.long_tiles, w.whole_tiles, w.tiles, w.long_steps);
+    } else {
+      return 2;
+    }
+  }
+  return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    exe = compile_cpp(str(tmp_path_factory.mktemp("plan")), MAIN)
+    return lambda *words: [int(v) for v in run(exe, " ".join(map(str, words))).split()]
+
+
+def block_products(batch, tokens, dim, layers, pruned, mlp=None):
+    """(M, N, K) of the weight gradients of a ViT block: `layers` whole encoder layers and, if `pruned`, the class-token one."""
+    F, rows, out = mlp or 4 * dim, batch * tokens, []
+    for _ in range(layers):
+        out += [(F, dim, rows), (dim, F, rows), (dim, dim, rows), (dim, 3 * dim, rows)]
+    if pruned:
+        out += [(F, dim, batch), (dim, F, batch), (dim, dim, batch), (dim, 2 * dim, rows), (dim, dim, batch)]
+    return out
+
+
+def weight_grad_plan(plan, products, workspace=1, units=UNITS):
+    names = ("wide", "cuts", "long_tiles", "whole_tiles", "tiles", "long_steps")
+    return dict(zip(names, plan("wgrad", units, workspace, len(products), *(v for p in products for v in p))))
+
+
+@pytest.mark.parametrize("batch", [128, 448, 449, 512, 1024, 4096])
+def test_reductions_over_images_are_short_beside_those_over_all_tokens(plan, batch):
+    # width 384, one whole and one class-token layer: 126 tiles over batch x 65 rows; the class-token layer's others, over the
+    # images alone, are whole at the end and leave the long ones their parts
+    w = weight_grad_plan(plan, block_products(batch, 65, 384, 1, True))
+    assert (w["wide"], w["tiles"], w["long_tiles"], w["whole_tiles"]) == (0, 126 + 90, 126, 0)
+    assert w["cuts"] == 2
+
+
+def test_every_tile_is_planned_once_and_the_parts_fit_the_workspace(plan):
+    for batch in (1, 3, 24, 128, 700):
+        for tokens in (2, 5, 65, 197):
+            for dim in (64, 192, 384, 768):
+                for layers, pruned in ((1, False), (3, True), (8, True)):
+                    products = block_products(batch, tokens, dim, layers, pruned)
+                    tiles = sum(-(-m // 128) * -(-n // 128) for m, n, _ in products)
+                    w = weight_grad_plan(plan, products)
+                    steps = [-(-k // 64) for _, _, k in products]
+                    assert w["tiles"] == tiles and 0 <= w["whole_tiles"] <= w["long_tiles"] <= tiles
+                    assert w["cuts"] >= 1
+                    if w["cuts"] > 1:
+                        assert not w["wide"]
+                        assert (w["long_tiles"] - w["whole_tiles"]) * w["cuts"] <= 2 * UNITS
+                        assert min(s for s in steps if s >= w["long_steps"]) // w["cuts"] >= 4
