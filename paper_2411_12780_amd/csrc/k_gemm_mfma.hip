@@ -601,30 +601,45 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma_balanced_kernel(BalancedArgs
   }
   gemm_mfma_tile<true, true, 128>(p, bid, 0);
 }
-// One workgroup per divided tile: the sum of its parts, added in ascending k.
-__global__ __launch_bounds__(256) void gemm_mfma_balanced_sum_kernel(BalancedArgs a) {
-  const int d = blockIdx.x >> 2, quarter = blockIdx.x & 3, t = a.whole_tiles + d;   // 4 workgroups per tile, 32 rows each
+// Eight rows of a divided tile per workgroup: the sum of its parts, added in ascending k, eight of them in flight.  Bound by the
+// latency of its loads (7 tiles in 8 parts: 13.3 us with four times the rows a workgroup and one part at a time, so 4.8).
+constexpr int SUM_ROWS = 8;
+__global__ __launch_bounds__(32 * SUM_ROWS) void gemm_mfma_balanced_sum_kernel(BalancedArgs a) {
+  const int d = blockIdx.x / (BM / SUM_ROWS), strip = blockIdx.x % (BM / SUM_ROWS), t = a.whole_tiles + d;
   int bid;
   const int j = grouped_locate(a, t, bid);
   const GroupedProblem& q = a.prob[j];
   const int m0 = (bid / q.tiles_n) * BM, n0 = (bid % q.tiles_n) * BN;
-  const int tid = threadIdx.x, c4 = (tid & 31) * 4;
+  const int tid = threadIdx.x, row = strip * SUM_ROWS + (tid >> 5), c4 = (tid & 31) * 4, m = m0 + row, n = n0 + c4;
   const float* slot0 = a.ws + (size_t)d * a.cuts * SLOT_FLOATS;
+  constexpr int U = 8;
+  if (m < q.M && n < q.N) {   // N is a multiple of 8
+    const float* p = slot0 + row * BN + c4;
+    float4 acc = *reinterpret_cast<const float4*>(p);
+    for (int c = 1; c < a.cuts; c += U) {
+      float4 v[U];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int row = quarter * 32 + r * 8 + (tid >> 5);
-    float4 acc = *reinterpret_cast<const float4*>(slot0 + row * BN + c4);
-    for (int c = 1; c < a.cuts; ++c) {
-      const float4 v = *reinterpret_cast<const float4*>(slot0 + (size_t)c * SLOT_FLOATS + row * BN + c4);
-      acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+      for (int u = 0; u < U; ++u)
+        if (c + u < a.cuts) v[u] = *reinterpret_cast<const float4*>(p + (size_t)(c + u) * SLOT_FLOATS);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (c + u < a.cuts) { acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w; }
     }
-    const int m = m0 + row, n = n0 + c4;
-    if (m < q.M && n < q.N) *reinterpret_cast<float4*>(q.C + (size_t)m * q.ldc + n) = acc;   // N is a multiple of 8
+    *reinterpret_cast<float4*>(q.C + (size_t)m * q.ldc + n) = acc;
   }
-  if (quarter == 0 && q.colsum && m0 == 0 && tid < BN) {
-    float acc = slot0[BM * BN + tid];
-    for (int c = 1; c < a.cuts; ++c) acc += slot0[(size_t)c * SLOT_FLOATS + BM * BN + tid];
-    if (n0 + tid < q.N) q.colsum[n0 + tid] = acc;
+  if (strip == 0 && q.colsum && m0 == 0 && tid < BN && n0 + tid < q.N) {
+    const float* p = slot0 + BM * BN + tid;
+    float acc = *p;
+    for (int c = 1; c < a.cuts; c += U) {
+      float v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (c + u < a.cuts) v[u] = p[(size_t)(c + u) * SLOT_FLOATS];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (c + u < a.cuts) acc += v[u];
+    }
+    q.colsum[n0 + tid] = acc;
   }
 }
 
@@ -765,7 +780,7 @@ int launch_gemm_mfma_grouped(hipStream_t s, const GemmArgs* gs, int n, float* ws
     const int grid = 8 * ((a.whole_tiles + 7) / 8 + (parts + 7) / 8 + (tiles - a.long_tiles + 7) / 8);
     hipLaunchKernelGGL(gemm_mfma_balanced_kernel, dim3(grid), dim3(256), lds_bytes(true, true, 128), s, a);
     PPLL_HIP(hipGetLastError());
-    hipLaunchKernelGGL(gemm_mfma_balanced_sum_kernel, dim3(4 * rest), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(gemm_mfma_balanced_sum_kernel, dim3(BM / SUM_ROWS * rest), dim3(32 * SUM_ROWS), 0, s, a);
     PPLL_HIP(hipGetLastError());
     return profile_end(s, prof);
   }

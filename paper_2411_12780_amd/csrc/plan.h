@@ -8,7 +8,6 @@ struct ProductShape { int M, N, K; };
 
 // ---- A set of weight-gradient products C_j[M,N] = A_j^T B_j, reductions over K (batch x tokens) rows, in one launch
 constexpr int WG_EDGE = 128, WG_WIDE = 256, WG_STEP = 64;      // output tiles of 128 x 128 or 128 x 256; k of a step of the former
-constexpr int WG_MAX_CUTS = 8;
 struct WeightGradPlan {
   bool wide;         // tiles of 128 x 256, every one whole
   // else, with cuts > 1, tiles of 128 x 128, some divided along k: the products with a long reduction come first, their tiles
@@ -63,10 +62,11 @@ inline WeightGradPlan plan_weight_grads(const ProductShape* p, int n, bool works
   if (w.wide || !workspace || units < 8 || rest == 0) return w;
   // Parts per left-over tile: 2, more when the left-over tiles are few (measured at 89 left-over tiles on 256 units: 2 parts
   // 124 + 10 us for the two kernels, 3 parts 123 + 13, 4 parts 121 + 16; undivided 160); with no whole tiles beside them, one
-  // part per unit.  Each of 4 steps or more, within the workspace.
+  // part per unit, however few the tiles: width 64, one layer, has 7, which in 8 parts each take 18 + 5 us at 8320 rows, 159 + 5
+  // at 131072 and 311 + 5 at 262144, in up to 36 parts 14 + 5, 68 + 8 and 133 + 8.  Each of 4 steps or more (beyond 8 parts, whose
+  // sums take longer, of 8: with 4 the first of these takes 14 + 8), within the workspace.
   int cuts = w.whole_tiles == 0 ? std::max(2, units / rest) : std::max(2, units / (2 * rest));
-  cuts = std::min(cuts, WG_MAX_CUTS);
-  while (cuts > 1 && (least / cuts < 4 || (long)rest * cuts > 2L * units)) --cuts;
+  while (cuts > 1 && (least / cuts < (cuts > 8 ? 8 : 4) || (long)rest * cuts > 2L * units)) --cuts;
   w.cuts = cuts;
   return w;
 }

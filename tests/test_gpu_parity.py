@@ -350,6 +350,8 @@ def test_vit_bf16_head_shapes(batch, dim, classes):
     (9, 65, 192, 2),     # 585 rows: odd, tiles divided along the rows; 192-wide LayerNorm
     (13, 145, 128, 1),   # 1885 rows
     (33, 256, 64, 3),    # 8448 rows: few tiles, many parts
+    (61, 256, 64, 1),    # 15616 rows = 244 steps in 30 parts of 9: one of a single step, two of none
+    (67, 255, 64, 1),    # 17085 rows = 267 steps, the last one ragged, in 32 parts of 9: one of 6 steps, two of none
 ])
 def test_vit_bf16_row_counts_off_the_tile_edges(batch, tokens, dim, depth):
     wl = synth.workload("vit_stage_act_bf16", batch=batch, tokens=tokens, dim=dim, heads=dim // 64, mlp_dim=4 * dim, depth=depth,

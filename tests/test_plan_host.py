@@ -75,4 +75,11 @@ def test_every_tile_is_planned_once_and_the_parts_fit_the_workspace(plan):
                     if w["cuts"] > 1:
                         assert not w["wide"]
                         assert (w["long_tiles"] - w["whole_tiles"]) * w["cuts"] <= 2 * UNITS
-                        assert min(s for s in steps if s >= w["long_steps"]) // w["cuts"] >= 4
+                        assert min(s for s in steps if s >= w["long_steps"]) // w["cuts"] >= (8 if w["cuts"] > 8 else 4)
+
+
+@pytest.mark.parametrize("rows,cuts", [(8320, 16), (131072, 36), (262144, 36), (1048576, 36)])
+def test_few_tiles_over_many_rows_are_cut_into_a_part_per_unit(plan, rows, cuts):
+    # one layer of width 64 has 7 tiles: 36 parts each fill 256 units; fewer where a part would have less than 8 steps
+    w = weight_grad_plan(plan, block_products(rows, 1, 64, 1, False))
+    assert (w["tiles"], w["whole_tiles"], w["cuts"]) == (7, 0, cuts)
