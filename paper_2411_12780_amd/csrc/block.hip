@@ -2,6 +2,7 @@
 // local-block step (Algorithm 1: forward, push point, local loss, backward that
 // stops at the block input, update).
 #include "block.h"
+#include "plan.h"
 
 #include <cmath>
 #include <cstdio>
@@ -64,8 +65,7 @@ int validate_config(const ppll_block_config* c) {
     // every limit a kernel of the step would otherwise hit at launch time, when earlier kernels are already enqueued
     const size_t dh = (size_t)(c->dim / c->heads), T = (size_t)c->tokens;
     if (c->precision != PPLL_BF16 || dh != 64) {   // the run-time-typed attention kernels keep K, V (or Q, dO) of one head in LDS
-      const size_t lds = (2 * T * (dh + 1) + 8 * dh + 10 * T) * sizeof(float);
-      if (lds > 160 * 1024) return bad("tokens x head dimension needs more than 160 KB of LDS in the attention kernels of this path");
+      if (att_heads_lds((int)T, (int)dh, true) > UNIT_LDS) return bad("tokens x head dimension needs more than 160 KB of LDS in the attention kernels of this path");
     }
     const size_t widest = (size_t)(3 * c->dim > c->mlp_dim ? 3 * c->dim : c->mlp_dim);
     if ((size_t)c->batch * T * widest > ((size_t)1 << 31) - 1) return bad("batch x tokens x layer width above 2^31 - 1 elements");

@@ -247,7 +247,6 @@ bool attention_mfma_supported(int dt, int T, int H, int dh, const void* a, const
 int launch_attention_fwd_mfma(hipStream_t s, const void* qkv, int B, int T, int H, void* out, float* lse);
 int launch_attention_bwd_mfma(hipStream_t s, const void* qkv, const void* out, const void* dout, const float* lse,
                               int B, int T, int H, void* dqkv);
-bool attention_rows_fits(int T, int H, int dh, bool bwd);
 int launch_attention_rows_fwd(hipStream_t s, const void* qkv, int dt, int B, int T, int H, int dh, void* out, float* lse);
 int launch_attention_rows_bwd(hipStream_t s, const void* qkv, const void* out, const void* dout, const float* lse, int dt,
                               int B, int T, int H, int dh, void* dqkv);

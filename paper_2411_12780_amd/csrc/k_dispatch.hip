@@ -4,6 +4,7 @@
 #include <vector>
 
 #include "common.h"
+#include "plan.h"
 
 namespace ppll {
 
@@ -93,7 +94,7 @@ int launch_gemm_group(hipStream_t s, const GemmArgs* gs, int n, bool use_workspa
 
 int launch_attention_fwd(hipStream_t s, const void* qkv, int dt, int B, int T, int H, int dh, void* out, float* lse) {
   if (attention_mfma_supported(dt, T, H, dh, qkv, out, nullptr, nullptr)) return launch_attention_fwd_mfma(s, qkv, B, T, H, out, lse);
-  if (attention_rows_fits(T, H, dh, false)) return launch_attention_rows_fwd(s, qkv, dt, B, T, H, dh, out, lse);
+  if (att_by_rows(T, H, dh, false, (long)B * H, compute_units())) return launch_attention_rows_fwd(s, qkv, dt, B, T, H, dh, out, lse);
   return launch_attention_fwd_generic(s, qkv, dt, B, T, H, dh, out, lse);
 }
 
@@ -101,7 +102,7 @@ int launch_attention_bwd(hipStream_t s, const void* qkv, const void* out, const 
                          int B, int T, int H, int dh, void* dqkv) {
   if (attention_mfma_supported(dt, T, H, dh, qkv, out, dout, dqkv))
     return launch_attention_bwd_mfma(s, qkv, out, dout, lse, B, T, H, dqkv);
-  if (attention_rows_fits(T, H, dh, true)) return launch_attention_rows_bwd(s, qkv, out, dout, lse, dt, B, T, H, dh, dqkv);
+  if (att_by_rows(T, H, dh, true, (long)B * H, compute_units())) return launch_attention_rows_bwd(s, qkv, out, dout, lse, dt, B, T, H, dh, dqkv);
   return launch_attention_bwd_generic(s, qkv, out, dout, lse, dt, B, T, H, dh, dqkv);
 }
 

@@ -10,6 +10,7 @@
 // run-time-typed kernel took 22.6 us per product (and 21.6 us for a weight gradient) at 520 rows of width 64.
 // Weight gradients of a step go out as one launch over a table of products, bias gradients (column sums of B) included.
 #include "common.h"
+#include "plan.h"
 
 namespace ppll {
 
@@ -288,15 +289,6 @@ int launch_gemm_f32_grouped(hipStream_t s, const GemmArgs* gs, int n) {
 // multiple of 16 so that 16 lanes reading 16 rows hit different banks.  One workgroup per (batch, head) walking all its
 // rows, as before, is 32 workgroups at batch 8: 73 us forward and 190 us backward at 65 tokens, 16-wide heads.
 namespace {
-constexpr int ATT_ROWS = 16;
-struct AttShape { int T, H, dh, q4, pitch, tp; };   // q4: quads of a head row, pitch: floats between rows, tp: of a score row
-__host__ __device__ inline AttShape att_shape(int T, int H, int dh) {
-  const int q4 = (dh + 3) / 4;
-  return {T, H, dh, q4, 4 * q4 + 4, ((T + 3) / 4) * 4 + 4};
-}
-size_t att_lds(const AttShape& a, bool bwd) {
-  return ((size_t)2 * a.T * a.pitch + (bwd ? 2 : 1) * ATT_ROWS * a.pitch + (bwd ? 2 : 1) * ATT_ROWS * a.tp + (bwd ? 2 * a.T + 8 : 0)) * sizeof(float);
-}
 __device__ __forceinline__ float4 ld4(const void* p, size_t i, int dt, int left) {   // elements i .. i+3, zero beyond `left`
   if (left >= 4) {
     if (dt == F32 && !((i | ((uintptr_t)p >> 2)) & 3)) return *reinterpret_cast<const float4*>((const float*)p + i);
@@ -432,26 +424,21 @@ __global__ __launch_bounds__(256) void attn_rows_bwd_kernel(const void* qkv, con
   }
 }
 
-constexpr int ATT_LDS = 160 * 1024;
 }  // namespace
 
-// head rows of all tokens must fit in LDS beside the score rows; at 256 tokens of 64 the backward does not, and the
-// kernels that keep one score row per wave take it
-bool attention_rows_fits(int T, int H, int dh, bool bwd) { return att_lds(att_shape(T, H, dh), bwd) <= ATT_LDS; }
-
 int launch_attention_rows_fwd(hipStream_t s, const void* qkv, int dt, int B, int T, int H, int dh, void* out, float* lse) {
-  const size_t lds = att_lds(att_shape(T, H, dh), false);
+  const size_t lds = att_rows_lds(att_shape(T, H, dh), false);
   static OncePerDevice once;
-  PPLL_TRY(raise_lds((const void*)attn_rows_fwd_kernel, ATT_LDS, once));
+  PPLL_TRY(raise_lds((const void*)attn_rows_fwd_kernel, UNIT_LDS, once));
   hipLaunchKernelGGL(attn_rows_fwd_kernel, dim3(B * H, (T + ATT_ROWS - 1) / ATT_ROWS), dim3(256), lds, s, qkv, dt, T, H, dh, out, lse);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;
 }
 int launch_attention_rows_bwd(hipStream_t s, const void* qkv, const void* out, const void* dout, const float* lse, int dt, int B,
                               int T, int H, int dh, void* dqkv) {
-  const size_t lds = att_lds(att_shape(T, H, dh), true);
+  const size_t lds = att_rows_lds(att_shape(T, H, dh), true);
   static OncePerDevice once;
-  PPLL_TRY(raise_lds((const void*)attn_rows_bwd_kernel, ATT_LDS, once));
+  PPLL_TRY(raise_lds((const void*)attn_rows_bwd_kernel, UNIT_LDS, once));
   hipLaunchKernelGGL(attn_rows_bwd_kernel, dim3(B * H, 2 * ((T + ATT_ROWS - 1) / ATT_ROWS)), dim3(256), lds, s, qkv, out, dout, lse,
                      dt, T, H, dh, dqkv);
   PPLL_HIP(hipGetLastError());

@@ -5,6 +5,7 @@
 // not take.  All reductions are ordered (no float atomics), so results are
 // reproducible run to run.
 #include "common.h"
+#include "plan.h"
 
 namespace ppll {
 
@@ -1483,17 +1484,16 @@ __global__ __launch_bounds__(256) void attention_bwd_kernel(const void* qkv, con
   }
 }
 
-constexpr int GENERIC_ATT_LDS = 160 * 1024;
 int allow_lds(const void* fn, size_t bytes, OncePerDevice& once) {
-  if (bytes > GENERIC_ATT_LDS) { set_error("attention: %zu bytes of LDS exceed 160 KB", bytes); return PPLL_ERR_CONFIG; }
-  return raise_lds(fn, GENERIC_ATT_LDS, once);
+  if (bytes > UNIT_LDS) { set_error("attention: %zu bytes of LDS exceed 160 KB", bytes); return PPLL_ERR_CONFIG; }
+  return raise_lds(fn, UNIT_LDS, once);
 }
 }  // namespace
 
 int launch_attention_fwd_generic(hipStream_t s, const void* qkv, int dt, int B, int T, int H, int dh, void* out,
                                  float* lse) {
   if (T > ATT_MAX_T || T < 1) { set_error("attention: tokens %d outside 1..%d", T, ATT_MAX_T); return PPLL_ERR_CONFIG; }
-  size_t lds = ((size_t)2 * T * (dh + 1) + 4 * dh + 4 * T) * sizeof(float);
+  const size_t lds = att_heads_lds(T, dh, false);
   static OncePerDevice once;
   PPLL_TRY(allow_lds((const void*)attention_fwd_kernel, lds, once));
   hipLaunchKernelGGL(attention_fwd_kernel, dim3(B * H), dim3(256), lds, s, qkv, dt, T, H, dh, out, lse);
@@ -1504,7 +1504,7 @@ int launch_attention_fwd_generic(hipStream_t s, const void* qkv, int dt, int B, 
 int launch_attention_bwd_generic(hipStream_t s, const void* qkv, const void* out, const void* dout, const float* lse,
                                  int dt, int B, int T, int H, int dh, void* dqkv) {
   if (T > ATT_MAX_T || T < 1) { set_error("attention: tokens %d outside 1..%d", T, ATT_MAX_T); return PPLL_ERR_CONFIG; }
-  size_t lds = ((size_t)2 * T * (dh + 1) + 8 * dh + 8 * T + 2 * T) * sizeof(float);
+  const size_t lds = att_heads_lds(T, dh, true);
   static OncePerDevice once;
   PPLL_TRY(allow_lds((const void*)attention_bwd_kernel, lds, once));
   hipLaunchKernelGGL(attention_bwd_kernel, dim3(B * H), dim3(256), lds, s, qkv, out, dout, lse, dt, T, H, dh, dqkv);

@@ -1,6 +1,7 @@
 // Rules of the dispatch that are pure functions of sizes and of the device's compute units.  No HIP in here.
 #pragma once
 #include <algorithm>
+#include <cstddef>
 
 namespace ppll {
 
@@ -69,6 +70,36 @@ inline WeightGradPlan plan_weight_grads(const ProductShape* p, int n, bool works
   while (cuts > 1 && (least / cuts < (cuts > 8 ? 8 : 4) || (long)rest * cuts > 2L * units)) --cuts;
   w.cuts = cuts;
   return w;
+}
+
+// ---- Attention of shapes that the matrix-core kernel does not take: one workgroup per (image, head), or one per 16 rows of one
+constexpr size_t UNIT_LDS = 160 * 1024;
+constexpr int ATT_ROWS = 16;
+// Rows kernel: quads of a head row, floats between rows in LDS, floats of a row of scores
+struct AttShape { int T, H, dh, q4, pitch, tp; };
+#ifdef __HIPCC__
+__host__ __device__
+#endif
+inline AttShape att_shape(int T, int H, int dh) {
+  const int q4 = (dh + 3) / 4;
+  return {T, H, dh, q4, 4 * q4 + 4, ((T + 3) / 4) * 4 + 4};
+}
+inline size_t att_rows_lds(const AttShape& a, bool bwd) {
+  return ((size_t)2 * a.T * a.pitch + (bwd ? 2 : 1) * ATT_ROWS * a.pitch + (bwd ? 2 : 1) * ATT_ROWS * a.tp + (bwd ? 2 * a.T + 8 : 0)) * sizeof(float);
+}
+inline size_t att_heads_lds(int T, int dh, bool bwd) {
+  return ((size_t)2 * T * (dh + 1) + (bwd ? 8 : 4) * (dh + T) + (bwd ? 2 * T : 0)) * sizeof(float);
+}
+// Whether the rows kernel takes it.  It has many times the workgroups, and each of them reads all keys and values of its head
+// again: ahead while there are few heads (2.2 to 30 times at 128 of them), and with many as long as two of its workgroups share
+// a unit.  Where one alone fits and two of the other kernel do, its time grows with the heads while the other's does not up to
+// two a unit, and they cross at about 1.5 heads a unit.  Microseconds on 256 units, heads kernel / rows kernel, 128 heads and 512:
+//   197 tokens, head size 32, backward   1458 / 429   1510 / 1876      65 tokens, 128, backward   621 / 225   647 / 896
+//   256 tokens, head size 32, forward     738 / 182    763 / 805       256 tokens, 32, backward  2176 / 623  2235 / 2731
+inline bool att_by_rows(int T, int H, int dh, bool bwd, long heads, int units) {
+  const size_t rows = att_rows_lds(att_shape(T, H, dh), bwd);
+  if (rows > UNIT_LDS) return false;
+  return 2 * rows <= UNIT_LDS || 2 * att_heads_lds(T, dh, bwd) > UNIT_LDS || heads <= units + units / 4;
 }
 
 }  // namespace ppll

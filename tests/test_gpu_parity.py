@@ -371,10 +371,14 @@ def test_vit_bf16_products_with_many_tiles(batch, tokens, dim, mlp):
     run_case(wl, steps=1)
 
 
-@pytest.mark.parametrize("tokens,dim,heads", [(20, 128, 4), (65, 96, 1)])
-def test_vit_bf16_attention_shapes_outside_the_matrix_core_kernel(tokens, dim, heads):
-    # a head dimension other than 64 (32, 96): the run-time-typed attention kernels on bf16 tensors
-    wl = synth.workload("vit_stage_act_bf16", batch=2, tokens=tokens, dim=dim, heads=heads, mlp_dim=2 * dim, depth=1,
+@pytest.mark.parametrize("tokens,dim,heads,batch", [
+    (20, 128, 4, 2), (65, 96, 1, 2),
+    (197, 128, 4, 90),     # 360 heads of 32: forward by rows, backward one workgroup a head
+    (65, 256, 2, 161),     # 322 heads of 128: likewise
+])
+def test_vit_bf16_attention_shapes_outside_the_matrix_core_kernel(tokens, dim, heads, batch):
+    # a head dimension other than 64 (32, 96, 128): the run-time-typed attention kernels on bf16 tensors
+    wl = synth.workload("vit_stage_act_bf16", batch=batch, tokens=tokens, dim=dim, heads=heads, mlp_dim=2 * dim, depth=1,
                         aux_depth=1)
     run_case(wl, steps=1)
 

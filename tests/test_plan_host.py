@@ -22,6 +22,11 @@ int main() {
       for (ProductShape& q : p) if (std::scanf("%d %d %d", &q.M, &q.N, &q.K) != 3) return 1;
       const WeightGradPlan w = plan_weight_grads(p.data(), n, workspace, true, units);
       std::printf("%d %d %d %d %d %d\n", w.wide, w.cuts, w.long_tiles, w.whole_tiles, w.tiles, w.long_steps);
+    } else if (!std::strcmp(what, "attention")) {
+      int T, H, dh, bwd, units;
+      long heads;
+      if (std::scanf("%d %d %d %d %ld %d", &T, &H, &dh, &bwd, &heads, &units) != 6) return 1;
+      std::printf("%d\n", att_by_rows(T, H, dh, bwd, heads, units));
     } else {
       return 2;
     }
@@ -83,3 +88,16 @@ def test_few_tiles_over_many_rows_are_cut_into_a_part_per_unit(plan, rows, cuts)
     # one layer of width 64 has 7 tiles: 36 parts each fill 256 units; fewer where a part would have less than 8 steps
     w = weight_grad_plan(plan, block_products(rows, 1, 64, 1, False))
     assert (w["tiles"], w["whole_tiles"], w["cuts"]) == (7, 0, cuts)
+
+
+@pytest.mark.parametrize("tokens,head,bwd,few,many", [
+    # at 128 heads and at 512 (batch x heads) the kernel that was measured to be the faster one: 1 rows, 0 heads
+    (17, 16, 0, 1, 1), (65, 32, 1, 1, 1), (65, 96, 1, 1, 1), (65, 128, 0, 1, 1), (65, 128, 1, 1, 0), (130, 32, 1, 1, 1),
+    (130, 96, 0, 1, 1), (130, 96, 1, 1, 1), (197, 16, 1, 1, 1), (197, 32, 0, 1, 1), (197, 32, 1, 1, 0), (256, 16, 0, 1, 1),
+    (256, 32, 0, 1, 0), (256, 32, 1, 1, 0),
+    # no room for the rows kernel
+    (130, 128, 1, 0, 0), (197, 96, 0, 0, 0),
+])
+def test_attention_goes_to_the_kernel_that_is_ahead(plan, tokens, head, bwd, few, many):
+    assert plan("attention", tokens, 4, head, bwd, 128, UNITS) == [few]
+    assert plan("attention", tokens, 4, head, bwd, 512, UNITS) == [many]
