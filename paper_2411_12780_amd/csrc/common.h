@@ -138,6 +138,7 @@ bool gemm_rows_supported(const GemmArgs& g);
 int launch_gemm_rows(hipStream_t s, const GemmArgs& g);
 // Products with many output tiles, bf16 output: see k_gemm_pipe.hip.  The choice (0: not this kernel) goes to the launch.
 int gemm_pipe_choice(const GemmArgs& g);
+bool gemm_pipe_supported(const GemmArgs& g);
 int launch_gemm_pipe(hipStream_t s, const GemmArgs& g, int choice);
 // fp32 products on the matrix cores: see k_f32.hip
 bool gemm_f32_supported(const GemmArgs& g);

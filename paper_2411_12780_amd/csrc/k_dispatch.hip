@@ -107,3 +107,23 @@ int launch_attention_bwd(hipStream_t s, const void* qkv, const void* out, const 
 }
 
 }  // namespace ppll
+
+// One product on one kernel, for tests of a kernel against another (no part of the public interface): 1 few tiles, 2 tiled, 4 / 5
+// 128 / 160 rows of 256 columns.  C[M,N] = A[M][K] B, B [K][N] (bt) or [N][K], bf16 throughout.
+extern "C" int ppll_internal_product(int kernel, int M, int N, int K, const void* A, long lda, const void* B, long ldb, int bt,
+                                     void* C, long ldc, const float* bias, const void* residual, int epilogue, void* C2,
+                                     const void* aux, void* stream) {
+  using namespace ppll;
+  GemmArgs g{};
+  g.A = A; g.a_dt = BF16; g.a_sm = lda; g.a_sk = 1;
+  g.B = B; g.b_dt = BF16; g.b_sk = bt ? ldb : 1; g.b_sn = bt ? 1 : ldb;
+  g.C = C; g.c_dt = BF16; g.ldc = ldc; g.M = M; g.N = N; g.K = K;
+  g.bias = bias; g.residual = residual; g.r_dt = BF16; g.ldr = ldc;
+  g.epilogue = epilogue; g.C2 = C2; g.aux = aux; g.aux_dt = BF16; g.ldaux = ldc;
+  hipStream_t s = (hipStream_t)stream;
+  if (kernel == 1 && gemm_rows_supported(g)) return launch_gemm_rows(s, g);
+  if (kernel == 2 && gemm_mfma_supported(g)) return launch_gemm_mfma(s, g, nullptr, 0);
+  if ((kernel == 4 || kernel == 5) && gemm_pipe_supported(g)) return launch_gemm_pipe(s, g, kernel);
+  set_error("kernel %d does not take this product", kernel);
+  return PPLL_ERR_CONFIG;
+}

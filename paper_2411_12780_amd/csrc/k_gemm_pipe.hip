@@ -12,7 +12,7 @@
 // GELU 31.6 -> 28.1.  What bounds it: LDS traffic beside the products in the main loop, and the epilogue where K is short.
 #include "common.h"
 #include "gemm_pipe.h"
-#include <cmath>
+#include "plan.h"
 
 namespace ppll {
 
@@ -153,31 +153,18 @@ int pipe_launch(hipStream_t s, PipeArgs& p) {
   return PPLL_OK;
 }
 
-// Time of a launch of `tiles` tiles on `places` workgroup places (two per compute unit), in rounds: a last round of at most one
-// workgroup per unit takes 0.62 of one in which they share units.
-double rounds(long tiles, int places) {
-  const long full = tiles / places, rest = tiles % places;
-  return full + (rest == 0 ? 0.0 : 2 * rest <= places ? 0.62 : 1.0);
-}
-long tile_count(int M, int N, int bm, int bn) { return (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); }
 }  // namespace
 
-// Rows of a wave's tile / 32 with which this kernel is expected to beat the tiled one, 0 if it is not.  A round of 128 x 256
-// tiles takes 1.58 times, of 160 x 256 tiles 1.74 times as long as one of the tiled kernel's 128 x 128 (25216 rows of width 768:
-// 30, 33 and 19 us), so what decides is how the tiles fill their last round: 25216 x 768 is 2.3 rounds of 128 x 128, 1.15 of 128
-// x 256, 0.93 of 160 x 256 (K = 3072: 145, 142, 115 us); 8320 x 1536 is 1.5, 0.76, 0.61 (31.6, 28.1, 32.6 us); 8320 x 384 stays
-// where it is, on 195 units (21.5, 31.1, 32.6 us).  Even cases stay on the tiled kernel.
-int gemm_pipe_choice(const GemmArgs& g) {
-  if (!gemm_mfma_supported(g) || g.a_sk != 1 || g.colsum || g.c_dt != BF16 || g.K < 4 * KS) return 0;
+bool gemm_pipe_supported(const GemmArgs& g) {
+  if (!gemm_mfma_supported(g) || g.a_sk != 1 || g.colsum || g.c_dt != BF16 || g.K < PIPE_MIN_K) return false;
   const bool bt = g.b_sn == 1 && g.b_sk != 1;
   // 32-bit byte offsets also for the rows (k rows) of the last tile that do not exist
-  if (g.a_sm > (1 << 20) || (bt ? g.b_sk : g.b_sn) > (1 << 20)) return 0;
-  const int places = 2 * compute_units();
-  if (places < 16) return 0;
-  const double tiled = rounds(tile_count(g.M, g.N, 128, 128), places);
-  const double c4 = 1.58 * rounds(tile_count(g.M, g.N, 128, 256), places), c5 = 1.74 * rounds(tile_count(g.M, g.N, 160, 256), places);
-  if (std::fmin(c4, c5) >= 0.95 * tiled) return 0;
-  return c4 <= c5 ? 4 : 5;
+  return g.a_sm <= (1 << 20) && (bt ? g.b_sk : g.b_sn) <= (1 << 20);
+}
+int gemm_pipe_choice(const GemmArgs& g) {
+  if (!gemm_pipe_supported(g)) return 0;
+  const ProductEnd end = g.epilogue == EPI_GELU ? END_GELU : g.epilogue == EPI_DGELU ? END_DGELU : g.residual ? END_RESIDUAL : g.bias ? END_BIAS : END_PLAIN;
+  return wide_tile_rows(g.M, g.N, g.K, end, compute_units());
 }
 
 int launch_gemm_pipe(hipStream_t s, const GemmArgs& g, int im) {

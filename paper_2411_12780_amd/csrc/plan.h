@@ -72,6 +72,37 @@ inline WeightGradPlan plan_weight_grads(const ProductShape* p, int n, bool works
   return w;
 }
 
+// ---- A bf16 Linear product with k contiguous in A: tiles of 128 x 128 (the tiled kernel), 128 x 256 or 160 x 256
+enum ProductEnd { END_PLAIN, END_BIAS, END_RESIDUAL, END_GELU, END_DGELU };   // what its epilogue adds
+constexpr int PIPE_MIN_K = 128;
+// Time of a launch in rounds of workgroup places (two per compute unit): `last` for a last round of at most one workgroup per
+// unit, in which they share none.
+inline double tile_rounds(int M, int N, int bm, int bn, int units, double last) {
+  const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn), places = 2L * units, full = tiles / places, rest = tiles % places;
+  return full + (rest == 0 ? 0.0 : 2 * rest <= places ? last : 1.0);
+}
+// Rows / 32 of the 256-wide tiles that are expected to beat the tiled kernel, 0 if none.  A round of places takes (per k, and for
+// the epilogue) what a least-squares fit gives for 4059 timings of the products of training steps, widths 128 to 1024, 2080 to
+// 50432 rows, within 12 % (rms), microseconds:
+//   128 x 128   0.0161 K + 4.1 plain, 4.5 bias, 4.9 residual, 8.1 GELU (two tensors out), 5.2 its derivative (one more in)
+//   128 x 256   0.0280 K + 6.0        6.8       6.9           13.5                        10.3
+//   160 x 256   0.0316 K + 7.2        8.6       8.1           17.5                        14.1
+// so the wide tiles gain 11 to 18 % of the loop, and lose with the derivative where K is short; how the tiles fill their last
+// round decides between the rest (25216 x 768 x 3072: 2.3 rounds of 128 x 128, 0.93 of 160 x 256, 145 and 115 us).  Without the
+// epilogue in the rule, 97 of 1353 products ran more than 3 % longer than on the tiled kernel (50432 x 512 x 128 with the
+// derivative 27 -> 38, 33280 x 576 x 192 24 -> 32), 42 do with it; all of them together take 52.9 ms on the tiled kernel, 49.3 ms
+// without it, 49.1 with.  One column of wide tiles reads each row of A once and waits for memory where K is long (33280 x 256 x
+// 768: 28 -> 32 us).
+inline int wide_tile_rows(int M, int N, int K, ProductEnd end, int units) {
+  if (K < PIPE_MIN_K || units < 8 || (N <= 256 && K > N)) return 0;
+  static const double e128[] = {4.1, 4.5, 4.9, 8.1, 5.2}, e4[] = {6.0, 6.8, 6.9, 13.5, 10.3}, e5[] = {7.2, 8.6, 8.1, 17.5, 14.1};
+  const double tiled = tile_rounds(M, N, 128, 128, units, 0.6) * (0.0161 * K + e128[end]);
+  const double c4 = tile_rounds(M, N, 128, 256, units, 0.65) * (0.0280 * K + e4[end]);
+  const double c5 = tile_rounds(M, N, 160, 256, units, 0.65) * (0.0316 * K + e5[end]);
+  if (std::min(c4, c5) >= 0.95 * tiled) return 0;
+  return c4 <= c5 ? 4 : 5;
+}
+
 // ---- Attention of shapes that the matrix-core kernel does not take: one workgroup per (image, head), or one per 16 rows of one
 constexpr size_t UNIT_LDS = 160 * 1024;
 constexpr int ATT_ROWS = 16;

@@ -1,0 +1,64 @@
+"""The bf16 product kernels against each other and against a float64 product, at the edges of their tiles.  The dispatch is passed
+by, so that every kernel is reached whatever its rules say."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2411_12780_amd import binding as P
+
+pytestmark = pytest.mark.gpu
+
+FEW, TILED, WIDE_128, WIDE_160 = 1, 2, 4, 5
+NONE, GELU, DGELU = 0, 1, 2
+
+
+def product(kernel, A, B, bt, bias, residual, epilogue, aux):
+    f = P.lib().ppll_internal_product
+    f.restype = ctypes.c_int
+    vp, i, l = ctypes.c_void_p, ctypes.c_int, ctypes.c_long
+    f.argtypes = [i, i, i, i, vp, l, vp, l, i, vp, l, vp, vp, i, vp, vp, vp]
+    M, K = A.shape
+    N = B.shape[1 if bt else 0]
+    C = torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda")
+    C2 = torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda")
+    ptr = lambda t: None if t is None else t.data_ptr()
+    status = f(kernel, M, N, K, ptr(A), A.stride(0), ptr(B), B.stride(0), bt, ptr(C), N, ptr(bias), ptr(residual), epilogue,
+               ptr(C2) if epilogue == GELU else None, ptr(aux) if epilogue == DGELU else None, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    return status, C, C2
+
+
+@pytest.mark.parametrize("epilogue", [NONE, GELU, DGELU])
+@pytest.mark.parametrize("bt", [0, 1])
+@pytest.mark.parametrize("M,N,K", [
+    (1, 8, 128), (129, 264, 136), (161, 520, 200), (160, 256, 256), (127, 248, 1000), (320, 512, 160), (481, 776, 392), (33, 3072, 128),
+])
+def test_wide_tiles_give_what_the_tiled_kernel_gives(M, N, K, bt, epilogue):
+    g = torch.Generator(device="cuda").manual_seed(M * 1000 + N + K)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    A, B = rnd(M, K), rnd(K, N) if bt else rnd(N, K)
+    bias = torch.randn(N, generator=g, device="cuda") if epilogue != DGELU else None
+    residual = rnd(M, N) if epilogue == NONE else None
+    aux = rnd(M, N)
+    status, C, C2 = product(TILED, A, B, bt, bias, residual, epilogue, aux)
+    assert status == 0
+    v = A.double() @ (B.double() if bt else B.double().t().contiguous())
+    if bias is not None:
+        v = v + bias.double()
+    if residual is not None:
+        v = v + residual.double()
+    ref = {NONE: v, DGELU: v * aux.double(), GELU: 0.5 * (1 + torch.erf(v / 2 ** 0.5)) + v * torch.exp(-0.5 * v * v) / (2 * torch.pi) ** 0.5}[epilogue]
+    # one rounding to bf16 (2^-9 of a value at most), fp32 sums of up to 1000 terms far below it
+    assert float((C.double() - ref).norm() / ref.norm()) <= 2.0 ** -8
+    for kernel in (WIDE_128, WIDE_160):
+        status, D, D2 = product(kernel, A, B, bt, bias, residual, epilogue, aux)
+        assert status == 0
+        assert torch.equal(C, D) and torch.equal(C2, D2), kernel
+
+
+def test_products_that_a_kernel_does_not_take_are_refused():
+    A, B = torch.zeros(16, 120, dtype=torch.bfloat16, device="cuda"), torch.zeros(120, 16, dtype=torch.bfloat16, device="cuda")
+    for kernel in (WIDE_128, WIDE_160, 3):
+        status, C, _ = product(kernel, A, B, 1, None, None, NONE, None)
+        assert status == 2 and bool((C == 7.0).all())

@@ -22,6 +22,10 @@ int main() {
       for (ProductShape& q : p) if (std::scanf("%d %d %d", &q.M, &q.N, &q.K) != 3) return 1;
       const WeightGradPlan w = plan_weight_grads(p.data(), n, workspace, true, units);
       std::printf("%d %d %d %d %d %d\n", w.wide, w.cuts, w.long_tiles, w.whole_tiles, w.tiles, w.long_steps);
+    } else if (!std::strcmp(what, "product")) {
+      int M, N, K, end, units;
+      if (std::scanf("%d %d %d %d %d", &M, &N, &K, &end, &units) != 5) return 1;
+      std::printf("%d\n", 32 * wide_tile_rows(M, N, K, (ProductEnd)end, units));
     } else if (!std::strcmp(what, "attention")) {
       int T, H, dh, bwd, units;
       long heads;
@@ -101,3 +105,39 @@ def test_few_tiles_over_many_rows_are_cut_into_a_part_per_unit(plan, rows, cuts)
 def test_attention_goes_to_the_kernel_that_is_ahead(plan, tokens, head, bwd, few, many):
     assert plan("attention", tokens, 4, head, bwd, 128, UNITS) == [few]
     assert plan("attention", tokens, 4, head, bwd, 512, UNITS) == [many]
+
+
+PLAIN, BIAS, RESIDUAL, GELU, DGELU = range(5)
+
+
+@pytest.mark.parametrize("M,N,K,end,rows", [
+    # rows of the 256-wide tiles (0: the tiled kernel).  Last rounds well filled, long reductions:
+    (25216, 768, 3072, RESIDUAL, 160), (25216, 2304, 768, BIAS, 160), (25216, 3072, 768, GELU, 160), (25216, 768, 768, RESIDUAL, 160),
+    (8320, 1536, 384, GELU, 128), (8320, 1536, 384, DGELU, 128), (8320, 384, 1536, RESIDUAL, 0), (8320, 1152, 384, BIAS, 0),
+    # short reductions behind the derivative or a bias: measured 27 -> 38, 31 -> 40, 24 -> 32, 19 -> 25 us on the wide tiles
+    (50432, 512, 128, DGELU, 0), (33280, 768, 192, DGELU, 0), (33280, 576, 192, BIAS, 0), (24960, 576, 192, BIAS, 0),
+    # one column of wide tiles and a long reduction
+    (33280, 256, 768, PLAIN, 0), (33280, 256, 1024, RESIDUAL, 0),
+    # below the shortest loop of the wide tiles
+    (25216, 768, 120, PLAIN, 0),
+])
+def test_products_go_to_the_tiles_that_are_ahead(plan, M, N, K, end, rows):
+    assert plan("product", M, N, K, end, UNITS) == [rows]
+
+
+def test_products_of_the_parity_cases_reach_the_kernels_they_name(plan):
+    # tests/test_gpu_parity.py, test_vit_bf16_products_with_many_tiles: (batch, tokens, dim, mlp) and the products that have to
+    # run on tiles of 128 and of 160 rows
+    def kinds(batch, tokens, dim, mlp):
+        rows = batch * tokens
+        products = {"qkv": (3 * dim, dim, BIAS), "proj": (dim, dim, RESIDUAL), "fc1": (mlp, dim, GELU), "fc2": (dim, mlp, RESIDUAL),
+                    "d fc2": (mlp, dim, DGELU), "d fc1": (dim, mlp, PLAIN), "d proj": (dim, dim, PLAIN), "d qkv": (dim, 3 * dim, PLAIN)}
+        return {k: plan("product", rows, n, kk, e, UNITS)[0] for k, (n, kk, e) in products.items()}
+
+    def on(rows, *case):
+        return {k for k, v in kinds(*case).items() if v == rows}
+
+    assert on(128, 129, 65, 128, 1528) == on(128, 71, 131, 136, 3064) == {"fc1"}
+    assert on(128, 129, 65, 328, 1528) == {"fc1", "d fc2"} and on(160, 129, 65, 328, 1528) == {"qkv"}
+    assert on(160, 97, 129, 264, 3064) == {"fc1", "d fc2"}
+    assert on(160, 97, 129, 768, 64) == on(128, 143, 130, 768, 64) == {"qkv", "proj", "d proj", "d qkv"}
