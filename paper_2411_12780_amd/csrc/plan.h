@@ -81,25 +81,40 @@ inline double tile_rounds(int M, int N, int bm, int bn, int units, double last) 
   const long tiles = (long)((M + bm - 1) / bm) * ((N + bn - 1) / bn), places = 2L * units, full = tiles / places, rest = tiles % places;
   return full + (rest == 0 ? 0.0 : 2 * rest <= places ? last : 1.0);
 }
-// Rows / 32 of the 256-wide tiles that are expected to beat the tiled kernel, 0 if none.  A round of places takes (per k, and for
-// the epilogue) what a least-squares fit gives for 4059 timings of the products of training steps, widths 128 to 1024, 2080 to
-// 50432 rows, within 12 % (rms), microseconds:
+// Rows / 32 of the 256-wide tiles that are expected to beat the tiled kernel, 0 if none.
+//
+// From width 768 on (the shorter of N and K) the loop is long beside everything else and the rounds decide: one of 128 x 256 tiles
+// takes 1.58 times, of 160 x 256 tiles 1.74 times as long as one of 128 x 128 (25216 rows of width 768: 30, 33 and 19 us).  25216 x
+// 768 is 2.3 rounds of 128 x 128, 1.15 of 128 x 256, 0.93 of 160 x 256 (K = 3072: 145, 142, 115 us).  Even cases stay on the tiled
+// kernel.  Training steps of two layers, all on the tiled kernel / so, 2080 to 33280 rows in all: width 768 29.3 / 27.2 ms, width
+// 1024 40.3 / 35.6.
+//
+// Below, the epilogue and the change of kernels count as well.  Microseconds of a round (per k, and for the epilogue), a
+// least-squares fit to 4059 timings of the products of training steps (within 12 % rms):
 //   128 x 128   0.0161 K + 4.1 plain, 4.5 bias, 4.9 residual, 8.1 GELU (two tensors out), 5.2 its derivative (one more in)
 //   128 x 256   0.0280 K + 6.0        6.8       6.9           13.5                        10.3
 //   160 x 256   0.0316 K + 7.2        8.6       8.1           17.5                        14.1
-// so the wide tiles gain 11 to 18 % of the loop, and lose with the derivative where K is short; how the tiles fill their last
-// round decides between the rest (25216 x 768 x 3072: 2.3 rounds of 128 x 128, 0.93 of 160 x 256, 145 and 115 us).  Without the
-// epilogue in the rule, 97 of 1353 products ran more than 3 % longer than on the tiled kernel (50432 x 512 x 128 with the
-// derivative 27 -> 38, 33280 x 576 x 192 24 -> 32), 42 do with it; all of them together take 52.9 ms on the tiled kernel, 49.3 ms
-// without it, 49.1 with.  One column of wide tiles reads each row of A once and waits for memory where K is long (33280 x 256 x
-// 768: 28 -> 32 us).
+// and each product that runs on other tiles than its neighbours costs them about 3 us (the code of both kernels, 8 and 9 KB, is
+// fetched again: 4 us more for a tiled product behind one on wide tiles).  By rounds alone, some products ran longer (33280 x 576 x
+// 192 with a bias 24 -> 32 us) and steps of width 384 took longer than with none on wide tiles (25216 rows, two layers: 1382 us all
+// on the tiled kernel, 1403 by rounds, 1353 so).  Steps of two layers, 2080 to 50432 rows in all, ms, by rounds / so: width 128
+// 4.78 / 4.52, 192 6.91 / 6.81, 256 8.76 / 8.63, 384 13.87 / 13.67, 512 19.44 / 19.44.  One column of wide tiles reads each row of
+// A once and waits for memory where K is long (33280 x 256 x 768: 28 -> 32 us).
 inline int wide_tile_rows(int M, int N, int K, ProductEnd end, int units) {
-  if (K < PIPE_MIN_K || units < 8 || (N <= 256 && K > N)) return 0;
-  static const double e128[] = {4.1, 4.5, 4.9, 8.1, 5.2}, e4[] = {6.0, 6.8, 6.9, 13.5, 10.3}, e5[] = {7.2, 8.6, 8.1, 17.5, 14.1};
-  const double tiled = tile_rounds(M, N, 128, 128, units, 0.6) * (0.0161 * K + e128[end]);
-  const double c4 = tile_rounds(M, N, 128, 256, units, 0.65) * (0.0280 * K + e4[end]);
-  const double c5 = tile_rounds(M, N, 160, 256, units, 0.65) * (0.0316 * K + e5[end]);
-  if (std::min(c4, c5) >= 0.95 * tiled) return 0;
+  if (K < PIPE_MIN_K || units < 8) return 0;
+  double tiled, c4, c5;
+  if (std::min(N, K) >= 768) {
+    tiled = 0.95 * tile_rounds(M, N, 128, 128, units, 0.62);
+    c4 = 1.58 * tile_rounds(M, N, 128, 256, units, 0.62);
+    c5 = 1.74 * tile_rounds(M, N, 160, 256, units, 0.62);
+  } else {
+    if (N <= 256 && K > N) return 0;
+    static const double e128[] = {4.1, 4.5, 4.9, 8.1, 5.2}, e4[] = {6.0, 6.8, 6.9, 13.5, 10.3}, e5[] = {7.2, 8.6, 8.1, 17.5, 14.1};
+    tiled = 0.97 * tile_rounds(M, N, 128, 128, units, 0.6) * (0.0161 * K + e128[end]) - 3.0;
+    c4 = tile_rounds(M, N, 128, 256, units, 0.65) * (0.0280 * K + e4[end]);
+    c5 = tile_rounds(M, N, 160, 256, units, 0.65) * (0.0316 * K + e5[end]);
+  }
+  if (std::min(c4, c5) >= tiled) return 0;
   return c4 <= c5 ? 4 : 5;
 }
 

@@ -362,12 +362,11 @@ def test_vit_bf16_row_counts_off_the_tile_edges(batch, tokens, dim, depth):
 @pytest.mark.parametrize("batch,tokens,dim,mlp", [
     # products with many output tiles: rows and columns that fill no tile of 128 x 256 or 160 x 256, reductions that fill no stage of 32
     # (what runs on which tiles: tests/test_plan_host.py)
-    (129, 65, 128, 1528),    # 8385 rows: fc1 with GELU on 128-row tiles
-    (71, 131, 136, 3064),    # 9301 rows: fc1 on 128-row tiles, a last stage of 8 k
-    (129, 65, 328, 1528),    # 8385 rows: fc1 and the derivative of GELU on 128-row tiles, QKV on 160-row tiles, a last stage of 8 k
-    (97, 129, 264, 3064),    # 12513 rows: fc1 and the derivative of GELU on 160-row tiles, a last stage of 8 k
+    (129, 65, 128, 1528), (71, 131, 136, 3064),   # 8385 and 9301 rows: many tiles, but of 128 x 128, the reductions being short
+    (129, 65, 328, 1528),    # 8385 rows: fc1 with GELU on 128-row tiles, a last stage of 8 k
+    (97, 129, 520, 1528),    # 12513 rows: fc1 and the derivative of GELU on 160-row tiles, a last stage of 8 k
     (97, 129, 768, 64),      # 12513 rows: QKV, projection with residual and their input gradients on 160-row tiles
-    (143, 130, 768, 64),     # 18590 rows: the same on 128-row tiles
+    (143, 130, 768, 64),     # 18590 rows: projection and the input gradients on 128-row tiles
 ])
 def test_vit_bf16_products_with_many_tiles(batch, tokens, dim, mlp):
     wl = synth.workload("vit_stage_act_bf16", batch=batch, tokens=tokens, dim=dim, heads=max(1, dim // 64 // 2 * 2), mlp_dim=mlp, depth=1, aux_depth=0)
