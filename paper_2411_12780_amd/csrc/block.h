@@ -85,8 +85,8 @@ struct Block {
   size_t partial_floats = 0;
   ReduceQueue rq;                 // second stages of the gradient reductions, run in one launch before the update
   size_t arena_floats = 0;
-  float* splitk = nullptr;       // split-K partial sums of the weight-gradient GEMMs
-  size_t splitk_floats = 0;
+  float* wgrad_ws = nullptr;     // parts of divided tiles of the weight-gradient products
+  size_t wgrad_ws_floats = 0;
 
   // ViT
   size_t pe_w = 0, pe_b = 0, cls = 0, pos = 0, head_ln_g = 0, head_ln_b = 0, head_w = 0, head_b = 0;

@@ -226,16 +226,9 @@ size_t Block::plan(char* base) {
       d_h.push_back(bump.take(M * F * esz));
       d_qkv.push_back(bump.take(M * 3 * D * esz));
     }
-    if (dt == BF16) {
-      const size_t cand[] = {gemm_mfma_partial_floats(D, 3 * D, (int)M), gemm_mfma_partial_floats(D, D, (int)M),
-                             gemm_mfma_partial_floats(D, F, (int)M), gemm_mfma_partial_floats(F, D, (int)M),
-                             cfg.input_kind == PPLL_IN_IMAGE
-                                 ? gemm_mfma_partial_floats(cfg.patch * cfg.patch * cfg.img_c, D, B * (T - 1)) : 0};
-      splitk_floats = 0;
-      for (size_t c : cand) if (c > splitk_floats) splitk_floats = c;
-      // the grouped weight-gradient launch at the end of the backward pass passes divided tiles through the same scratch
-      if (gemm_mfma_balanced_floats() > splitk_floats) splitk_floats = gemm_mfma_balanced_floats();
-      splitk = splitk_floats ? bump.floats(splitk_floats) : nullptr;
+    if (dt == BF16) {   // parts of divided tiles of the weight-gradient launch at the end of the backward pass
+      wgrad_ws_floats = gemm_mfma_balanced_floats();
+      wgrad_ws = wgrad_ws_floats ? bump.floats(wgrad_ws_floats) : nullptr;
     }
     int widest = 3 * D > F ? 3 * D : F;
     partial_floats = (size_t)colsum_partial_floats((int)M, widest);
@@ -317,7 +310,7 @@ size_t Block::plan(char* base) {
       arena_floats += (size_t)embed_bwd_partial_floats(B, T, D) + (size_t)colsum_partial_floats((int)M, D) + 128;
     if (!(dt == BF16))   // the generic GEMM does not fold bias gradients: one column sum per Linear layer
       arena_floats += (size_t)(cfg.depth + cfg.aux_depth) * 4 * ((size_t)colsum_partial_floats((int)M, widest) + 64);
-    if (prune_cls)   // the class-token layer: one more LayerNorm backward over B rows and column sums of its split products
+    if (prune_cls)   // the class-token layer: one more LayerNorm backward over B rows and column sums of its products
       arena_floats += (size_t)layernorm_bwd_partial_floats(B, D) + 6 * ((size_t)colsum_partial_floats((int)M, widest) + 64);
   }
   if (cfg.arch == PPLL_RESNET) {   // the weight-gradient partials of every convolution
@@ -414,7 +407,6 @@ int Block::wgrad_product(const void* xin, long x_ld, int in_dim, const void* dy,
   g.B = dy; g.b_dt = dt; g.b_sk = dy_ld; g.b_sn = 1;
   g.C = dW; g.c_dt = F32; g.ldc = ldw; g.M = in_dim; g.N = out_dim; g.K = K;
   g.colsum = db;
-  g.splitk_ws = splitk; g.splitk_floats = splitk_floats;
   if (gemm_weight_grad_groupable(g)) { wgrad_jobs.push_back(g); return PPLL_OK; }
   g.colsum = nullptr;
   PPLL_TRY(launch_gemm(s, g));
@@ -603,7 +595,6 @@ int Block::vit_step(const void* x_in, const int32_t* labels, void* x_out, hipStr
       g.B = embed_tmp; g.b_dt = dt; g.b_sk = D; g.b_sn = 1;
       g.C = grads + pe_w; g.c_dt = F32; g.ldc = D; g.M = ppc; g.N = D; g.K = B * (T - 1);
       g.colsum = grads + pe_b;   // bias gradient: column sums of dE, folded into the product by the MFMA kernel
-      g.splitk_ws = splitk; g.splitk_floats = splitk_floats;
       if (gemm_weight_grad_groupable(g)) {
         wgrad_jobs.push_back(g);
       } else {
@@ -615,9 +606,9 @@ int Block::vit_step(const void* x_in, const int32_t* labels, void* x_out, hipStr
       PPLL_TRY(launch_fill_zero(s, grads + pe_w, ((size_t)ppc * D + D) * sizeof(float)));
     }
   }
-  // ---- every recorded weight-gradient product: one launch, or one by one with split-K for a small set
-  // (this launch is the only user of the split-K scratch while it runs: the side stream's launches take none)
-  PPLL_TRY(launch_gemm_group(s, wgrad_jobs.data(), (int)wgrad_jobs.size(), true));
+  // ---- every recorded weight-gradient product, in one launch
+  // (the only user of the workspace while it runs: the side stream's launches take none)
+  PPLL_TRY(launch_gemm_group(s, wgrad_jobs.data(), (int)wgrad_jobs.size(), wgrad_ws, wgrad_ws_floats));
   wgrad_jobs.clear();
   PPLL_TRY(side_wait(s));
   return PPLL_OK;
@@ -647,8 +638,7 @@ int Block::resnet_step(const void* x_in, const int32_t* labels, void* x_out, hip
   const void* x = x_in;
   // A BatchNorm whose input has just been written waits here: the next convolution applies it on the way in where it can
   // (stride 1, equal channels, bf16), else it runs on its own.  `area` holds its sums (bn.blocks rows; 0: none yet).
-  // (x_in and x_out are the caller's: the fused kernels need them on a 16-byte boundary)
-  const bool fuse = ((uintptr_t)x_in | (uintptr_t)x_out) % 16 == 0;
+  // (x_in and x_out are the caller's, on a 16-byte boundary: every entry point checks that)
   BnInput bn{};
   bool waiting = false;
   int bn_rows = 0, bn_c = 0;
@@ -656,7 +646,7 @@ int Block::resnet_step(const void* x_in, const int32_t* labels, void* x_out, hip
   auto wait_bn = [&](const void* in, int rows, int c, float* mean, float* rstd, int index, size_t g_off, size_t b_off,
                      const void* res, void* y, uint8_t* mask, int ready) {
     bn = BnInput{in, area, ready, eps, mom, mean, rstd, run_mean(index), run_var(index), params + g_off, params + b_off, res, y,
-                 fuse ? mask : nullptr};
+                 mask};
     bn_rows = rows; bn_c = c; waiting = true;
   };
   auto apply_bn = [&]() -> int {   // on its own
@@ -667,7 +657,7 @@ int Block::resnet_step(const void* x_in, const int32_t* labels, void* x_out, hip
   };
   auto conv = [&](const void* in, const void* w, int Hi, int Wi, int Ci, int Co, int stride, void* out, int* ready) -> int {
     *ready = 0;
-    if (fuse && stride == 1 && Ci == Co && conv_bn_ok(dt, B, Hi, Wi, Ci)) {
+    if (stride == 1 && Ci == Co && conv_bn_ok(dt, B, Hi, Wi, Ci)) {
       if (waiting && bn.blocks == 0) PPLL_TRY(launch_bn_sums_fwd_bf16(s, bn.x, bn_rows, bn_c, area, &bn.blocks));
       const bool take = waiting;
       waiting = false;
@@ -778,7 +768,7 @@ int Block::resnet_step(const void* x_in, const int32_t* labels, void* x_out, hip
     const BasicBlockDims& d = rb_d[i];
     BasicBlockActs& a = rb_a[i];
     const int rows = B * d.Ho * d.Wo;
-    const bool fused = fuse && conv_bn_ok(dt, B, d.Ho, d.Wo, d.Co), identity = d.stride == 1 && d.Ci == d.Co;
+    const bool fused = conv_bn_ok(dt, B, d.Ho, d.Wo, d.Co), identity = d.stride == 1 && d.Ci == d.Co;
     defer(a.y1, a.d2, grads + p.conv2_w, d.Ho, d.Wo, d.Co, d.Co, 1);
     if (fused) {
       const BnBwdSums bn1{a.y1, a.c1, a.mean1, a.rstd1, area, a.mask1};

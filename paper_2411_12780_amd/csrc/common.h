@@ -127,7 +127,6 @@ struct GemmArgs {
   int epilogue;
   void* C2;                                   // EPI_GELU second output (c_dt, ldc)
   const void* aux; int aux_dt; long ldaux;    // EPI_DGELU: the saved GELU derivative
-  float* splitk_ws; size_t splitk_floats;     // optional scratch for split-K partial sums
   float* colsum;                              // optional: out[n] = sum_k B(k,n) (bias gradient of a dW product);
                                               // honoured only by the matrix-core kernels
 };
@@ -146,17 +145,17 @@ bool gemm_f32_groupable(const GemmArgs& g);
 int launch_gemm_f32(hipStream_t s, const GemmArgs& g);
 int launch_gemm_f32_grouped(hipStream_t s, const GemmArgs* gs, int n);
 bool gemm_mfma_supported(const GemmArgs& g);
-size_t gemm_mfma_partial_floats(int M, int N, int K);
-int launch_gemm_mfma(hipStream_t s, const GemmArgs& g, float* partial, size_t partial_floats);
+int launch_gemm_mfma(hipStream_t s, const GemmArgs& g);   // A stored [M][K]
 bool gemm_mfma_groupable(const GemmArgs& g);
 // every product must be groupable; ws (gemm_mfma_balanced_floats() floats or more), when given, lets the launch deal
 // the k-steps out evenly over the compute units (parts of divided tiles pass through it)
 int launch_gemm_mfma_grouped(hipStream_t s, const GemmArgs* gs, int n, float* ws = nullptr, size_t ws_floats = 0);
 size_t gemm_mfma_balanced_floats();
 // A set of independent products of one element type, each a weight gradient that gemm_weight_grad_groupable() accepts, in
-// one launch.
+// one launch.  ws: room of gemm_mfma_balanced_floats() for the parts of divided tiles, for a launch that is the sole user of it
+// while it runs (null: tiles stay whole).
 inline bool gemm_weight_grad_groupable(const GemmArgs& g) { return gemm_mfma_groupable(g) || gemm_f32_groupable(g); }
-int launch_gemm_group(hipStream_t s, const GemmArgs* gs, int n, bool use_workspace = false);
+int launch_gemm_group(hipStream_t s, const GemmArgs* gs, int n, float* ws = nullptr, size_t ws_floats = 0);
 // Per-launch timing of the contraction kernels (a measurement aid, off unless a block asks for it).  A block that
 // times its launches binds its record to the calling thread for the duration of a step; the launch functions
 // below the block engine then bracket each contraction launch with a pair of events on its stream.

@@ -80,16 +80,13 @@ int compute_units() {
 int launch_gemm(hipStream_t s, const GemmArgs& g) {
   if (gemm_rows_supported(g)) return launch_gemm_rows(s, g);   // few output rows: latency, not throughput
   if (const int im = gemm_pipe_choice(g)) return launch_gemm_pipe(s, g, im);                // many tiles: throughput
-  if (gemm_mfma_supported(g)) return launch_gemm_mfma(s, g, g.splitk_ws, g.splitk_floats);
-  return gemm_f32_supported(g) ? launch_gemm_f32(s, g) : launch_gemm_generic(s, g);
+  if (gemm_mfma_supported(g) && g.a_sk == 1) return launch_gemm_mfma(s, g);
+  return gemm_f32_supported(g) && g.a_sk == 1 ? launch_gemm_f32(s, g) : launch_gemm_generic(s, g);
 }
 
-// use_workspace: the grouped launch may pass divided tiles through the products' split-K scratch (gs[0].splitk_ws);
-// only for a launch that is the sole user of that scratch while it runs.
-int launch_gemm_group(hipStream_t s, const GemmArgs* gs, int n, bool use_workspace) {
+int launch_gemm_group(hipStream_t s, const GemmArgs* gs, int n, float* ws, size_t ws_floats) {
   if (n <= 0) return PPLL_OK;
-  if (gs[0].a_dt == F32) return launch_gemm_f32_grouped(s, gs, n);
-  return launch_gemm_mfma_grouped(s, gs, n, use_workspace ? gs[0].splitk_ws : nullptr, use_workspace ? gs[0].splitk_floats : 0);
+  return gs[0].a_dt == F32 ? launch_gemm_f32_grouped(s, gs, n) : launch_gemm_mfma_grouped(s, gs, n, ws, ws_floats);
 }
 
 int launch_attention_fwd(hipStream_t s, const void* qkv, int dt, int B, int T, int H, int dh, void* out, float* lse) {
@@ -122,7 +119,7 @@ extern "C" int ppll_internal_product(int kernel, int M, int N, int K, const void
   g.epilogue = epilogue; g.C2 = C2; g.aux = aux; g.aux_dt = BF16; g.ldaux = ldc;
   hipStream_t s = (hipStream_t)stream;
   if (kernel == 1 && gemm_rows_supported(g)) return launch_gemm_rows(s, g);
-  if (kernel == 2 && gemm_mfma_supported(g)) return launch_gemm_mfma(s, g, nullptr, 0);
+  if (kernel == 2 && gemm_mfma_supported(g)) return launch_gemm_mfma(s, g);
   if ((kernel == 4 || kernel == 5) && gemm_pipe_supported(g)) return launch_gemm_pipe(s, g, kernel);
   set_error("kernel %d does not take this product", kernel);
   return PPLL_ERR_CONFIG;

@@ -173,9 +173,9 @@ __device__ __forceinline__ void gemm_f32_tile(const F32Args& p, const int m0, co
   }
 }
 
-template <bool AT, bool BT, int R>
+template <bool BT, int R>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(F32Args p) {
-  gemm_f32_tile<AT, BT, R>(p, (int)blockIdx.y * 32 * R, (int)blockIdx.x * 32 * R);
+  gemm_f32_tile<false, BT, R>(p, (int)blockIdx.y * 32 * R, (int)blockIdx.x * 32 * R);
 }
 
 // Weight and bias gradients of several layers: C_j = A_j^T B_j with both operands stored [K][.].
@@ -225,35 +225,25 @@ bool gemm_f32_groupable(const GemmArgs& g) {
 // 64 x 64 tiles (half the operand traffic) once they give every compute unit a workgroup
 constexpr long F32_WIDE_TILES = 256;
 
+template <bool BT, int R>
+static int f32_launch(hipStream_t s, const F32Args& p) {
+  static OncePerDevice once;
+  PPLL_TRY(raise_lds((const void*)gemm_f32_kernel<BT, R>, f32_lds_bytes<R>(), once));
+  hipLaunchKernelGGL((gemm_f32_kernel<BT, R>), dim3((p.N + 32 * R - 1) / (32 * R), (p.M + 32 * R - 1) / (32 * R)), dim3(256), f32_lds_bytes<R>(), s, p);
+  PPLL_HIP(hipGetLastError());
+  return PPLL_OK;
+}
 int launch_gemm_f32(hipStream_t s, const GemmArgs& g) {
-  const bool at = g.a_sm == 1 && g.a_sk != 1, bt = g.b_sn == 1 && g.b_sk != 1;
+  if (g.a_sk != 1 || g.colsum) { set_error("launch_gemm_f32: A stored [K][M] and column sums are for sets of weight gradients"); return PPLL_ERR_CONFIG; }
+  const bool bt = g.b_sn == 1 && g.b_sk != 1;
   F32Args p{};
   p.A = (const float*)g.A; p.B = (const float*)g.B; p.C = (float*)g.C;
-  p.lda = (int)(at ? g.a_sk : g.a_sm); p.ldb = (int)(bt ? g.b_sk : g.b_sn); p.ldc = (int)g.ldc;
+  p.lda = (int)g.a_sm; p.ldb = (int)(bt ? g.b_sk : g.b_sn); p.ldc = (int)g.ldc;
   p.M = g.M; p.N = g.N; p.K = g.K; p.bias = g.bias; p.residual = (const float*)g.residual; p.ldr = (int)g.ldr;
   p.epilogue = g.epilogue; p.C2 = (float*)g.C2; p.aux = (const float*)g.aux; p.ldaux = (int)g.ldaux;
-  p.a_bytes = (uint32_t)f32_bytes(at, g.M, g.K, p.lda); p.b_bytes = (uint32_t)f32_bytes(bt, g.N, g.K, p.ldb);
-  const bool wide = tiles_of(g.M, g.N, 64) >= F32_WIDE_TILES;
-  static OncePerDevice nn, nt, tn, tt;
-  PPLL_TRY(raise_lds((const void*)gemm_f32_kernel<false, false, 2>, f32_lds_bytes<2>(), nn));
-  PPLL_TRY(raise_lds((const void*)gemm_f32_kernel<false, true, 2>, f32_lds_bytes<2>(), nt));
-  PPLL_TRY(raise_lds((const void*)gemm_f32_kernel<true, false, 2>, f32_lds_bytes<2>(), tn));
-  PPLL_TRY(raise_lds((const void*)gemm_f32_kernel<true, true, 2>, f32_lds_bytes<2>(), tt));
-  const int edge = wide ? 64 : 32;
-  const dim3 grid((g.N + edge - 1) / edge, (g.M + edge - 1) / edge);
-#define F32_LAUNCH(AT, BT)                                                                                              \
-  do {                                                                                                                  \
-    if (wide) hipLaunchKernelGGL((gemm_f32_kernel<AT, BT, 2>), grid, dim3(256), f32_lds_bytes<2>(), s, p);              \
-    else hipLaunchKernelGGL((gemm_f32_kernel<AT, BT, 1>), grid, dim3(256), f32_lds_bytes<1>(), s, p);                   \
-  } while (0)
-  if (at && bt) F32_LAUNCH(true, true);
-  else if (at) F32_LAUNCH(true, false);
-  else if (bt) F32_LAUNCH(false, true);
-  else F32_LAUNCH(false, false);
-#undef F32_LAUNCH
-  PPLL_HIP(hipGetLastError());
-  if (g.colsum && !bt) { set_error("launch_gemm_f32: column sums need B stored [K][N]"); return PPLL_ERR_CONFIG; }
-  return PPLL_OK;
+  p.a_bytes = (uint32_t)f32_bytes(false, g.M, g.K, p.lda); p.b_bytes = (uint32_t)f32_bytes(bt, g.N, g.K, p.ldb);
+  if (tiles_of(g.M, g.N, 64) >= F32_WIDE_TILES) return bt ? f32_launch<true, 2>(s, p) : f32_launch<false, 2>(s, p);
+  return bt ? f32_launch<true, 1>(s, p) : f32_launch<false, 1>(s, p);
 }
 
 int launch_gemm_f32_grouped(hipStream_t s, const GemmArgs* gs, int n) {

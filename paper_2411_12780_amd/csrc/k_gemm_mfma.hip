@@ -23,9 +23,9 @@
 // transposed: a lane then holds 4 consecutive columns of one C row, so bias,
 // residual, saved GELU derivative and the output move as 8/16-byte vectors.
 //
-// Split-K (weight gradients: tiny outputs, reduction over all tokens): every
-// split writes its fp32 partial tile, a second kernel adds the splits in a
-// fixed order, so results are reproducible (no float atomics).
+// Weight gradients (both operands [k][row], fp32 output, bias gradient folded in) go out as sets, several products a launch;
+// a set that does not fill the chip has some of its tiles divided along k, parts added in a fixed order by a second kernel, so
+// results are reproducible (no float atomics).
 #include "common.h"
 #include "gemm_pipe.h"
 #include "plan.h"
@@ -45,18 +45,14 @@ struct MfmaArgs {
   void* C; int c_f32; long ldc;
   int M, N, K;
   int tiles_m, tiles_n;
-  int kt_per_split;                 // k-tiles per split
-  float* partial;                   // [splits][M][N] when split-K
-  float* colsum;                    // optional: [splits][N] sums over k of B(k, n) (bias gradient), else null
+  float* colsum;                    // optional: [N] sums over k of B(k, n) (bias gradient), else null
   const float* bias;
   const uint16_t* residual; long ldr;
   int epilogue;
   uint16_t* C2;
   const uint16_t* aux; long ldaux;
-  uint32_t a_bytes, b_bytes, c_bytes, r_bytes, aux_bytes, partial_bytes;   // extents of the buffers above
-  int xcd_map;                      // 1: ids 8 apart share a tile row (many tile rows), 2: ids 8 apart share a
-                                    // split (split-K), 0: row-major ids
-  int splits;
+  uint32_t a_bytes, b_bytes, c_bytes, r_bytes, aux_bytes;   // extents of the buffers above
+  int xcd_map;                      // 1: ids 8 apart share a tile row (many tile rows), 0: row-major ids
   // k_range set: the k-range is given outright (balanced grouped launch), kt_count k-tiles from k-tile kt_first on.
   // tile_partial, when set, receives the whole fp32 tile ([128][128], then 128 column sums) in place of C and colsum.
   int k_range, kt_first, kt_count;
@@ -89,7 +85,7 @@ __device__ __forceinline__ uint2 lds_read_tr(const char* p) {
 
 // ---- Buffer addressing.  Operands, outputs and epilogue inputs are reached through raw buffer
 // descriptors: a load whose byte offset lies beyond the buffer returns 0 and a store there is
-// dropped, so the tile edges (rows beyond M or N, k beyond K or beyond a split's range) need no
+// dropped, so the tile edges (rows beyond M or N, k beyond K or beyond a part's range) need no
 // branches: an out-of-range lane simply gets the offset OOB.  Straight-line code also lets the
 // compiler count outstanding loads exactly, so the loads of the k-tile two steps ahead stay in
 // flight while the previous one is written to LDS.
@@ -168,9 +164,9 @@ struct TileRegs { uint4 a[4], b[4]; };
 // AT: A is stored [K][M] (transposing loader), else [M][K].  BT likewise for B ([K][N] / [N][K]).
 // TM = rows of the output tile: 128 (wave tile 64 x 64) or, for outputs with too few 128-row
 // tiles to fill the chip, 64 (wave tile 32 x 64; direct A loader only).
-// One output tile; bid_x, bid_y are the workgroup's place in the (virtual) grid of this product.
+// One output tile; bid is the workgroup's place in the (virtual) grid of this product.
 template <bool AT, bool BT, int TM>
-__device__ __forceinline__ void gemm_mfma_tile(const MfmaArgs& p, const int bid_x, const int bid_y) {
+__device__ __forceinline__ void gemm_mfma_tile(const MfmaArgs& p, const int bid) {
   static_assert(TM == 128 || (TM == 64 && !AT), "64-row tiles are for the direct A loader");
   constexpr int IM = TM / 64;                  // 32-row MFMA tiles per wave along m
   constexpr int OPER_BYTES = oper_bytes(AT, BT, TM);
@@ -181,27 +177,17 @@ __device__ __forceinline__ void gemm_mfma_tile(const MfmaArgs& p, const int bid_
   // Workgroup id -> tile.  Consecutive ids go to the 8 XCDs round-robin and each XCD has its own
   // L2, so the tiles of one row (they share the A panel) are given ids that are 8 apart: they
   // land on one XCD, next to each other in its dispatch order, and the panel is fetched once.
-  // With split-K (xcd_map 2) it is the splits that are dealt to the XCDs: all tiles of one k-range
-  // run on one XCD, so the two token panels of that range are fetched from HBM once.
-  int tm, tn, split = bid_y;
+  int tm, tn;
   if (p.xcd_map == 1) {
-    const int xcd = bid_x & 7, slot = bid_x >> 3;
+    const int xcd = bid & 7, slot = bid >> 3;
     tm = (slot / p.tiles_n) * 8 + xcd; tn = slot % p.tiles_n;
     if (tm >= p.tiles_m) return;
-  } else if (p.xcd_map == 2) {
-    const int tiles = p.tiles_m * p.tiles_n;
-    const int xcd = bid_x & 7, slot = bid_x >> 3;
-    split = (slot / tiles) * 8 + xcd;
-    const int tile = slot % tiles;
-    tm = tile / p.tiles_n; tn = tile % p.tiles_n;
-    if (split >= p.splits) return;
   } else {
-    tm = bid_x / p.tiles_n; tn = bid_x % p.tiles_n;
+    tm = bid / p.tiles_n; tn = bid % p.tiles_n;
   }
   const int m0 = tm * TM, n0 = tn * BN;
   const int nkt = (p.K + BK - 1) / BK;
-  const int kt0 = p.k_range ? p.kt_first : split * p.kt_per_split;
-  const int nk = p.k_range ? p.kt_count : min(nkt, kt0 + p.kt_per_split) - kt0;   // k-tiles of this workgroup (a trailing split may have none)
+  const int kt0 = p.k_range ? p.kt_first : 0, nk = p.k_range ? p.kt_count : nkt;   // k-tiles of this workgroup (a trailing part may have none)
   const int kbeg = kt0 * BK, kend = min(p.K, (kt0 + nk) * BK);
 
   f32x16 acc[2][IM];
@@ -327,8 +313,8 @@ __device__ __forceinline__ void gemm_mfma_tile(const MfmaArgs& p, const int bid_
   const int ncol2 = nok ? 2 * n : OOB_BASE, ncol4 = nok ? 4 * n : OOB_BASE;   // column part of a byte offset; out of range beyond N
   float bias8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   uint4 resv[NPASS], auxv[NPASS];
-  const bool has_bias = p.bias != nullptr && !p.partial, has_res = p.residual != nullptr && !p.partial;
-  const bool has_aux = p.epilogue == EPI_DGELU && !p.partial;
+  const bool has_bias = p.bias != nullptr, has_res = p.residual != nullptr;
+  const bool has_aux = p.epilogue == EPI_DGELU;
   if (has_bias) {
     const __amdgpu_buffer_rsrc_t rs = make_rsrc(p.bias, (uint32_t)p.N * 4u);
     const uint4 b0 = buf_load16(rs, nok ? n * 4 : OOB), b1 = buf_load16(rs, nok ? n * 4 + 16 : OOB);
@@ -364,7 +350,7 @@ __device__ __forceinline__ void gemm_mfma_tile(const MfmaArgs& p, const int bid_
 #pragma unroll
       for (int g = 0; g < 16; ++g) t += cs[g * BN + tid];
       if (p.tile_partial) p.tile_partial[BM * BN + tid] = t;
-      else if (n0 + tid < p.N) p.colsum[(size_t)split * p.N + n0 + tid] = t;
+      else if (n0 + tid < p.N) p.colsum[n0 + tid] = t;
     }
     __syncthreads();
   }
@@ -379,10 +365,9 @@ __device__ __forceinline__ void gemm_mfma_tile(const MfmaArgs& p, const int bid_
             make_float4(acc[jn][im][4 * q], acc[jn][im][4 * q + 1], acc[jn][im][4 * q + 2], acc[jn][im][4 * q + 3]);
       }
   __syncthreads();
-  const __amdgpu_buffer_rsrc_t rsC = p.tile_partial ? make_rsrc(p.tile_partial, BM * BN * 4)
-                                     : p.partial    ? make_rsrc(p.partial, p.partial_bytes) : make_rsrc(p.C, p.c_bytes);
+  const __amdgpu_buffer_rsrc_t rsC = p.tile_partial ? make_rsrc(p.tile_partial, BM * BN * 4) : make_rsrc(p.C, p.c_bytes);
   const __amdgpu_buffer_rsrc_t rsC2 = make_rsrc(p.C2 ? (const void*)p.C2 : p.C, p.C2 ? p.c_bytes : 0u);
-  const bool out_f32 = p.partial != nullptr || p.tile_partial != nullptr || p.c_f32;
+  const bool out_f32 = p.tile_partial != nullptr || p.c_f32;
 #pragma unroll
   for (int pass = 0; pass < NPASS; ++pass) {
     const int row = pass * 16 + prow, m = m0 + row;
@@ -409,8 +394,7 @@ __device__ __forceinline__ void gemm_mfma_tile(const MfmaArgs& p, const int bid_
       }
     }
     if (out_f32) {
-      const long e0 = p.partial ? ((long)split * p.M + m) * p.N : (long)m * p.ldc;
-      const int off = p.tile_partial ? (row * BN + c8) * 4 : ok ? (int)(e0 * 4) + ncol4 : OOB;
+      const int off = p.tile_partial ? (row * BN + c8) * 4 : ok ? (int)((long)m * p.ldc * 4) + ncol4 : OOB;
       buf_store16(rsC, off, make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
       buf_store16(rsC, (ok || p.tile_partial) ? off + 16 : OOB, make_uint4(__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])));
     } else {
@@ -437,13 +421,13 @@ __device__ __forceinline__ void gemm_mfma_tile(const MfmaArgs& p, const int bid_
   }
 }
 
-template <bool AT, bool BT, int TM>
+template <bool BT, int TM>
 __global__ __launch_bounds__(256, 2) void gemm_mfma_kernel(MfmaArgs p) {
-  gemm_mfma_tile<AT, BT, TM>(p, (int)blockIdx.x, (int)blockIdx.y);
+  gemm_mfma_tile<false, BT, TM>(p, (int)blockIdx.x);
 }
 
 // Several products C_j = A_j^T B_j (both operands stored [K][.], fp32 output, optional column sums
-// of B_j: the weight and bias gradients of a set of Linear layers) in one launch, no split-K: the
+// of B_j: the weight and bias gradients of a set of Linear layers) in one launch, undivided: the
 // tiles of all products together fill the chip, so every tile walks its whole K and nothing
 // passes through partial buffers.  Tiles are numbered product by product; XCD x (workgroup id % 8)
 // takes a contiguous range of them, so the tiles that share operand panels share an L2.
@@ -476,10 +460,9 @@ __device__ __forceinline__ MfmaArgs grouped_problem(const Args& a, int j) {
   p.C = a.prob[j].C; p.c_f32 = 1; p.ldc = a.prob[j].ldc;
   p.M = a.prob[j].M; p.N = a.prob[j].N; p.K = a.prob[j].K;
   p.tiles_m = a.prob[j].tiles_m; p.tiles_n = a.prob[j].tiles_n;
-  p.kt_per_split = (p.K + BK - 1) / BK;
   p.colsum = a.prob[j].colsum;
   p.a_bytes = a.prob[j].a_bytes; p.b_bytes = a.prob[j].b_bytes; p.c_bytes = a.prob[j].c_bytes;
-  p.splits = 1; p.xcd_map = 0;
+  p.xcd_map = 0;
   return p;
 }
 __global__ __launch_bounds__(256, 2) void gemm_mfma_grouped_kernel(GroupedArgs a) {
@@ -489,7 +472,7 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma_grouped_kernel(GroupedArgs a
   int bid;
   const int j = grouped_locate(a, t, bid);
   const MfmaArgs p = grouped_problem(a, j);
-  gemm_mfma_tile<true, true, 128>(p, bid, 0);
+  gemm_mfma_tile<true, true, 128>(p, bid);
 }
 
 // The same set of products on 128 x 256 tiles and the main loop of gemm_pipe.h.  A tile of K = 25216 rows keeps its workgroup for
@@ -595,11 +578,11 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma_balanced_kernel(BalancedArgs
   const int j = grouped_locate(a, t, bid);
   MfmaArgs p = grouped_problem(a, j);
   if (c >= 0) {
-    const int nkt = p.kt_per_split, per = (nkt + a.cuts - 1) / a.cuts;
+    const int nkt = (p.K + BK - 1) / BK, per = (nkt + a.cuts - 1) / a.cuts;
     p.k_range = 1; p.kt_first = min(c * per, nkt); p.kt_count = min(per, nkt - p.kt_first);
     p.tile_partial = a.ws + ((size_t)(t - a.whole_tiles) * a.cuts + c) * SLOT_FLOATS;
   }
-  gemm_mfma_tile<true, true, 128>(p, bid, 0);
+  gemm_mfma_tile<true, true, 128>(p, bid);
 }
 // Eight rows of a divided tile per workgroup: the sum of its parts, added in ascending k, eight of them in flight.  Bound by the
 // latency of its loads (7 tiles in 8 parts: 13.3 us with four times the rows a workgroup and one part at a time, so 4.8).
@@ -643,29 +626,6 @@ __global__ __launch_bounds__(32 * SUM_ROWS) void gemm_mfma_balanced_sum_kernel(B
   }
 }
 
-// C[i] = sum over splits of partial[s][i], fixed order; the trailing workgroups do the same for
-// the bias-gradient partials [splits][N] when there are any.
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* partial, int splits, size_t mn, float* C,
-                                                            int main_blocks, const float* cs_partial, int N,
-                                                            float* cs_out) {
-  if ((int)blockIdx.x >= main_blocks) {
-    const int n = ((int)blockIdx.x - main_blocks) * 256 + threadIdx.x;
-    if (n >= N) return;
-    float acc = 0.f;
-    for (int s = 0; s < splits; ++s) acc += cs_partial[(size_t)s * N + n];
-    cs_out[n] = acc;
-    return;
-  }
-  size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
-  if (i >= mn) return;
-  float4 acc = *reinterpret_cast<const float4*>(partial + i);
-  for (int s = 1; s < splits; ++s) {
-    float4 v = *reinterpret_cast<const float4*>(partial + (size_t)s * mn + i);
-    acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
-  }
-  *reinterpret_cast<float4*>(C + i) = acc;
-}
-
 bool aligned16(const void* p) { return (((uintptr_t)p) & 15) == 0; }
 // bytes from the first to one past the last element of an operand (transposed: [K][rows], else [rows][K])
 long operand_bytes(bool transposed, int rows, int K, long ld) {
@@ -698,27 +658,6 @@ bool gemm_mfma_supported(const GemmArgs& g) {
   if (g.residual && ((long)(g.M - 1) * g.ldr + g.N) * 2 > lim) return false;
   if (g.epilogue == EPI_DGELU && ((long)(g.M - 1) * g.ldaux + g.N) * 2 > lim) return false;
   return true;
-}
-
-// Number of K splits for a product (1 = none) and the partial floats it needs.
-int gemm_mfma_splits(int M, int N, int K) {
-  const int tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-  const int nkt = (K + BK - 1) / BK;
-  if (tiles >= 128 || nkt < 8) return 1;
-  int splits = (256 + tiles - 1) / tiles;          // about one workgroup per compute unit
-  if (nkt >= 32) {                                  // a multiple of 8, so that splits can be dealt to the 8 XCDs evenly
-    splits = ((splits + 7) / 8) * 8;
-    while (splits > 8 && splits > nkt / 4) splits -= 8;
-  } else if (splits > nkt / 2) {
-    splits = nkt / 2;
-  }
-  int per = (nkt + splits - 1) / splits;
-  int real = (nkt + per - 1) / per;
-  return (nkt >= 32 && real != splits) ? splits : real;   // keep the multiple of 8 (a trailing split may be short or empty)
-}
-size_t gemm_mfma_partial_floats(int M, int N, int K) {
-  int s = gemm_mfma_splits(M, N, K);
-  return s > 1 ? (size_t)s * M * N + (size_t)s * N : 0;   // tile partials, then bias-gradient partials
 }
 
 // True when a set of products can go into one grouped launch: each a transposed-transposed product
@@ -808,68 +747,45 @@ int launch_gemm_mfma_grouped(hipStream_t s, const GemmArgs* gs, int n, float* ws
   return PPLL_OK;
 }
 
-int launch_gemm_mfma(hipStream_t s, const GemmArgs& g, float* partial, size_t partial_floats) {
-  const bool at = g.a_sm == 1 && g.a_sk != 1, bt = g.b_sn == 1 && g.b_sk != 1;
+namespace {
+template <bool BT, int TM>
+int tiled_launch(hipStream_t s, const MfmaArgs& p, int grid) {
+  static OncePerDevice once;
+  PPLL_TRY(raise_lds((const void*)gemm_mfma_kernel<BT, TM>, lds_bytes(false, BT, TM), once));
+  hipLaunchKernelGGL((gemm_mfma_kernel<BT, TM>), dim3(grid), dim3(256), lds_bytes(false, BT, TM), s, p);
+  PPLL_HIP(hipGetLastError());
+  return PPLL_OK;
+}
+}  // namespace
+
+int launch_gemm_mfma(hipStream_t s, const GemmArgs& g) {
+  if (g.a_sk != 1 || g.colsum) { set_error("launch_gemm_mfma: A stored [K][M] and column sums are for sets of weight gradients"); return PPLL_ERR_CONFIG; }
+  const bool bt = g.b_sn == 1 && g.b_sk != 1;
   MfmaArgs p{};
-  p.A = (const uint16_t*)g.A; p.lda = at ? g.a_sk : g.a_sm;
+  p.A = (const uint16_t*)g.A; p.lda = g.a_sm;
   p.B = (const uint16_t*)g.B; p.ldb = bt ? g.b_sk : g.b_sn;
   p.C = g.C; p.c_f32 = g.c_dt == F32; p.ldc = g.ldc;
   p.M = g.M; p.N = g.N; p.K = g.K;
   p.tiles_n = (g.N + BN - 1) / BN;
   // 64-row tiles when 128-row tiles would leave more than half of the compute units without a workgroup
   // (between 128 and 256 tiles the 128-row kernel was measured faster: 18.2 against 20.3 us at 8320 x 384 x 1536)
-  const bool small_m = !at && ((g.M + BM - 1) / BM) * p.tiles_n < 128;
+  const bool small_m = ((g.M + BM - 1) / BM) * p.tiles_n < 128;
   const int tm_rows = small_m ? 64 : BM;
   p.tiles_m = (g.M + tm_rows - 1) / tm_rows;
   p.bias = g.bias; p.residual = (const uint16_t*)g.residual; p.ldr = g.ldr;
   p.epilogue = g.epilogue; p.C2 = (uint16_t*)g.C2; p.aux = (const uint16_t*)g.aux; p.ldaux = g.ldaux;
-  const int nkt = (g.K + BK - 1) / BK;
-  int splits = 1;
-  const bool plain = !g.bias && !g.residual && g.epilogue == EPI_NONE && g.c_dt == F32 && g.ldc == g.N;
-  if (plain && partial) {
-    splits = gemm_mfma_splits(g.M, g.N, g.K);
-    if ((size_t)splits * g.M * g.N + (size_t)splits * g.N > partial_floats) splits = 1;
-    if ((size_t)splits * g.M * g.N * 4 > ((size_t)1 << 30) - 64) splits = 1;
-  }
-  float* colsum_partial = splits > 1 ? partial + (size_t)splits * g.M * g.N : nullptr;
-  p.colsum = g.colsum ? (splits > 1 ? colsum_partial : g.colsum) : nullptr;
-  p.kt_per_split = (nkt + splits - 1) / splits;
-  p.partial = splits > 1 ? partial : nullptr;
-  p.splits = splits;
-  p.a_bytes = (uint32_t)operand_bytes(at, g.M, g.K, p.lda);
+  p.a_bytes = (uint32_t)operand_bytes(false, g.M, g.K, p.lda);
   p.b_bytes = (uint32_t)operand_bytes(bt, g.N, g.K, p.ldb);
   p.c_bytes = (uint32_t)(((long)(g.M - 1) * g.ldc + g.N) * (p.c_f32 ? 4 : 2));
   p.r_bytes = g.residual ? (uint32_t)(((long)(g.M - 1) * g.ldr + g.N) * 2) : 0u;
   p.aux_bytes = g.epilogue == EPI_DGELU ? (uint32_t)(((long)(g.M - 1) * g.ldaux + g.N) * 2) : 0u;
-  p.partial_bytes = splits > 1 ? (uint32_t)((size_t)splits * g.M * g.N * 4) : 0u;
-  p.xcd_map = (splits > 1 && splits % 8 == 0) ? 2 : (p.tiles_m >= 16 ? 1 : 0);
-  dim3 grid(p.tiles_m * p.tiles_n, splits);
-  if (p.xcd_map == 1) grid = dim3(((p.tiles_m + 7) / 8) * 8 * p.tiles_n, splits);
-  if (p.xcd_map == 2) grid = dim3(p.tiles_m * p.tiles_n * splits, 1);
-  static OncePerDevice tt, tn, nt, nn;
-  PPLL_TRY(raise_lds((const void*)gemm_mfma_kernel<true, true, 128>, lds_bytes(true, true, 128), tt));
-  PPLL_TRY(raise_lds((const void*)gemm_mfma_kernel<true, false, 128>, lds_bytes(true, false, 128), tn));
-  PPLL_TRY(raise_lds((const void*)gemm_mfma_kernel<false, true, 128>, lds_bytes(false, true, 128), nt));
-  PPLL_TRY(raise_lds((const void*)gemm_mfma_kernel<false, false, 128>, lds_bytes(false, false, 128), nn));
+  p.xcd_map = p.tiles_m >= 16 ? 1 : 0;
+  const int grid = p.xcd_map ? (p.tiles_m + 7) / 8 * 8 * p.tiles_n : p.tiles_m * p.tiles_n;
   void* prof = nullptr;
-  PPLL_TRY(profile_begin(s, 2.0 * g.M * g.N * g.K, &prof, g.M < 256 && !at ? 2 : 0));   // few output rows: a class of its own
-  if (small_m) {
-    if (bt) hipLaunchKernelGGL((gemm_mfma_kernel<false, true, 64>), grid, dim3(256), lds_bytes(false, true, 64), s, p);
-    else hipLaunchKernelGGL((gemm_mfma_kernel<false, false, 64>), grid, dim3(256), lds_bytes(false, false, 64), s, p);
-  } else if (at && bt) hipLaunchKernelGGL((gemm_mfma_kernel<true, true, 128>), grid, dim3(256), lds_bytes(true, true, 128), s, p);
-  else if (at) hipLaunchKernelGGL((gemm_mfma_kernel<true, false, 128>), grid, dim3(256), lds_bytes(true, false, 128), s, p);
-  else if (bt) hipLaunchKernelGGL((gemm_mfma_kernel<false, true, 128>), grid, dim3(256), lds_bytes(false, true, 128), s, p);
-  else hipLaunchKernelGGL((gemm_mfma_kernel<false, false, 128>), grid, dim3(256), lds_bytes(false, false, 128), s, p);
-  PPLL_HIP(hipGetLastError());
-  PPLL_TRY(profile_end(s, prof));
-  if (splits > 1) {
-    size_t mn = (size_t)g.M * g.N;
-    const int main_blocks = (int)((mn / 4 + 255) / 256), extra = g.colsum ? (g.N + 255) / 256 : 0;
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3(main_blocks + extra), dim3(256), 0, s, partial, splits, mn, (float*)g.C,
-                       main_blocks, colsum_partial, g.N, g.colsum);
-    PPLL_HIP(hipGetLastError());
-  }
-  return PPLL_OK;
+  PPLL_TRY(profile_begin(s, 2.0 * g.M * g.N * g.K, &prof, g.M < 256 ? 2 : 0));   // few output rows: a class of its own
+  if (small_m) PPLL_TRY((bt ? tiled_launch<true, 64>(s, p, grid) : tiled_launch<false, 64>(s, p, grid)));
+  else PPLL_TRY((bt ? tiled_launch<true, 128>(s, p, grid) : tiled_launch<false, 128>(s, p, grid)));
+  return profile_end(s, prof);
 }
 
 }  // namespace ppll
