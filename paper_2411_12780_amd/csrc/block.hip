@@ -232,7 +232,7 @@ size_t Block::plan(char* base) {
     }
     int widest = 3 * D > F ? 3 * D : F;
     partial_floats = (size_t)colsum_partial_floats((int)M, widest);
-    size_t ln = (size_t)layernorm_bwd_partial_floats((int)M, D);
+    size_t ln = layernorm_bwd_most_floats((int)M, D, dt);
     if (ln > partial_floats) partial_floats = ln;
     if (cfg.input_kind == PPLL_IN_IMAGE) {
       size_t eb = (size_t)embed_bwd_partial_floats(B, T, D);
@@ -303,15 +303,15 @@ size_t Block::plan(char* base) {
     const int B = cfg.batch, T = cfg.tokens, D = cfg.dim;
     const size_t M = (size_t)B * T;
     const int widest = cfg.mlp_dim > 3 * D ? cfg.mlp_dim : 3 * D;
-    arena_floats = (size_t)(2 * (cfg.depth + cfg.aux_depth)) * (layernorm_bwd_partial_floats((int)M, D) + 64) +
-                   (size_t)layernorm_bwd_partial_floats(B, D) + (size_t)colsum_partial_floats(B, C) + 256 +
+    arena_floats = (size_t)(2 * (cfg.depth + cfg.aux_depth)) * (layernorm_bwd_partial_floats((int)M, D, dt) + 64) +
+                   layernorm_bwd_partial_floats(B, D, dt) + (size_t)colsum_partial_floats(B, C) + 256 +
                    vit_head_partial_floats(B, D, C) + 64;
     if (cfg.input_kind == PPLL_IN_IMAGE)
       arena_floats += (size_t)embed_bwd_partial_floats(B, T, D) + (size_t)colsum_partial_floats((int)M, D) + 128;
     if (!(dt == BF16))   // the generic GEMM does not fold bias gradients: one column sum per Linear layer
       arena_floats += (size_t)(cfg.depth + cfg.aux_depth) * 4 * ((size_t)colsum_partial_floats((int)M, widest) + 64);
     if (prune_cls)   // the class-token layer: one more LayerNorm backward over B rows and column sums of its products
-      arena_floats += (size_t)layernorm_bwd_partial_floats(B, D) + 6 * ((size_t)colsum_partial_floats((int)M, widest) + 64);
+      arena_floats += layernorm_bwd_partial_floats(B, D, dt) + 6 * ((size_t)colsum_partial_floats((int)M, widest) + 64);
   }
   if (cfg.arch == PPLL_RESNET) {   // the weight-gradient partials of every convolution
     const int Ch = cfg.channels, A = cfg.aux_channels, Hh = cfg.height, W = cfg.width;

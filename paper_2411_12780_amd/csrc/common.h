@@ -207,7 +207,11 @@ int launch_layernorm_fwd(hipStream_t s, const void* x, int dt, long x_row_stride
 int launch_layernorm_bwd(hipStream_t s, const void* dy, const void* x, int dt, long x_row_stride, int rows,
                          int D, const float* g, const float* mean, const float* rstd, const void* dres, int dres_every,
                          void* dx_out, ReduceQueue& rq, float* dg, float* db);
-int layernorm_bwd_partial_floats(int rows, int D);
+// Partial sums of dg and db: what the kernel of this width leaves (a block holds as much for each of its LayerNorms), and the most
+// there can be (the shared scratch): where parameters lie off 16 bytes the run-time-typed kernel stands in, which leaves up to six
+// times as many rows (3152 instead of 526 at 25216 x 768); what then finds no room of its own is finished at once.
+size_t layernorm_bwd_partial_floats(int rows, int D, int dt);
+size_t layernorm_bwd_most_floats(int rows, int D, int dt);
 
 // out[n] = sum over rows of x[r, n]  (two-stage, deterministic)
 int launch_colsum(hipStream_t s, const void* x, int dt, int rows, int N, ReduceQueue& rq, float* out);

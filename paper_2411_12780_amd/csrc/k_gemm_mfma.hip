@@ -436,7 +436,7 @@ struct GroupedProblem {
   int lda, ldb, ldc, M, N, K, tiles_m, tiles_n, first_tile;
   uint32_t a_bytes, b_bytes, c_bytes;
 };
-constexpr int GROUP_MAX = 40;   // seven encoder layers with the patch embedding; the table stays below the 4 KB of a kernel's arguments
+constexpr int GROUP_MAX = 40;   // eight encoder layers, the class-token one and the patch embedding are 38; the table stays below the 4 KB of a kernel's arguments
 struct GroupedArgs {
   int n, total_tiles, per_xcd;
   GroupedProblem prob[GROUP_MAX];

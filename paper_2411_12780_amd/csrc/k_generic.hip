@@ -481,8 +481,8 @@ __global__ __launch_bounds__(256) void layernorm_fwd_bf16_kernel(const uint16_t*
 
 // Backward.  What bounds it at training sizes (8320 rows of width 384: 26 MB, 3.6 us at the rate the last-level cache
 // delivers) is the latency of one row's chain - loads, two row sums, the write - so the rows are spread over as many waves
-// as there are: eight waves per workgroup, one pass over 64 / LPR rows each while that gives at most two workgroups per
-// compute unit, more passes beyond (each workgroup leaves one partial row of dg, db, which a later kernel has to add up).
+// as there are: eight waves per workgroup, one pass over 64 / LPR rows each up to just under 1024 workgroups (four per unit on
+// 256 units), 512 to 1024 workgroups of more passes beyond (each leaves one partial row of dg, db, which a later kernel adds up).
 constexpr int LNB_WAVES = 8;
 template <int DD> constexpr int lnb_rows_per_pass() { return LNB_WAVES * LnShape<DD>::RPW; }
 // lane l and lane l ^ 32 (16): after the swap the sum a + b holds a's total on the lanes whose bit 5 (4) is clear and b's
@@ -660,11 +660,13 @@ static int lnb_passes(int rows, int D) {
   const int p = rows / (lnb_pass_rows(D) * 512);
   return p < 1 ? 1 : p;
 }
-int layernorm_bwd_partial_floats(int rows, int D) {
-  const int chunks = (rows + LN_ROWS - 1) / LN_ROWS;
-  if (!ln_fast_dim(D)) return chunks * 2 * D;
-  const int per = lnb_pass_rows(D) * lnb_passes(rows, D), fast = (rows + per - 1) / per;
-  return (chunks > fast ? chunks : fast) * 2 * D;
+static size_t ln_floats(int rows, int D, int per) { return (size_t)((rows + per - 1) / per) * 2 * D; }
+size_t layernorm_bwd_partial_floats(int rows, int D, int dt) {
+  return ln_floats(rows, D, dt == BF16 && ln_fast_dim(D) ? lnb_pass_rows(D) * lnb_passes(rows, D) : LN_ROWS);
+}
+size_t layernorm_bwd_most_floats(int rows, int D, int dt) {
+  const size_t usual = layernorm_bwd_partial_floats(rows, D, dt), stand_in = ln_floats(rows, D, LN_ROWS);
+  return usual > stand_in ? usual : stand_in;
 }
 
 int launch_layernorm_bwd(hipStream_t s, const void* dy, const void* x, int dt, long xs, int rows, int D,
@@ -673,7 +675,7 @@ int launch_layernorm_bwd(hipStream_t s, const void* dy, const void* x, int dt, l
   int chunks;
   const bool fast = ln_fast_ok(dt, D, xs, x, dy, dres, dx_out) && !(((uintptr_t)g) & 15);
   bool queued;
-  float* partials = rq.space((size_t)layernorm_bwd_partial_floats(rows, D), &queued);
+  float* partials = rq.space(fast ? layernorm_bwd_partial_floats(rows, D, dt) : ln_floats(rows, D, LN_ROWS), &queued);
   if (fast) {
     const int passes = lnb_passes(rows, D), per = lnb_pass_rows(D) * passes;
     chunks = (rows + per - 1) / per;

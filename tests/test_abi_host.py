@@ -44,6 +44,13 @@ def test_size_queries_match_the_workload(name):
     assert ws % 256 == 0 and ws > 4 * P.ppll_block_param_bytes(cfg) // 2
 
 
+def test_layernorm_scratch_does_not_outgrow_the_activations():
+    # 25216 rows of width 768 in four layers: the partial rows of nine LayerNorms' parameter gradients, one a pass of
+    # the kernel that runs, are less than a hundredth of the workspace (without what depends on the device; sized for the kernel that
+    # stands in where parameters are unaligned it took 4.70 GB)
+    assert P.ppll_block_workspace_bytes(P.make_config(synth.workload("vit_base_224_bf16"))) < 4.60e9
+
+
 def test_bad_configurations_are_rejected_on_the_host():
     good = synth.workload("vit_tiny_fp32")
     for bad in (dict(tokens=64), dict(heads=5), dict(precision=7), dict(arch=3), dict(batch=0),

@@ -345,6 +345,21 @@ def test_vit_bf16_head_shapes(batch, dim, classes):
     run_case(wl, steps=1)
 
 
+@pytest.mark.parametrize("precision", [synth.BF16, synth.FP32])
+def test_vit_more_weight_gradients_than_one_launch_takes(precision):
+    # eleven layers: 44 products (40 a launch), 23 LayerNorms whose reductions fill more than one batch of 40
+    wl = synth.workload("vit_stage_act_bf16", precision=precision, batch=5, tokens=3, dim=64, heads=1, mlp_dim=64, depth=11, aux_depth=0)
+    run_case(wl, steps=1)
+
+
+@pytest.mark.parametrize("batch,tokens,dim", [(9, 17, 128), (3, 11, 64), (1, 2, 192)])
+def test_vit_bf16_layernorm_with_parameters_off_16_bytes(batch, tokens, dim):
+    # an MLP width that is no multiple of four moves the next layer's parameters off 16 bytes: its LayerNorms run on the
+    # run-time-typed kernels, 8 rows a workgroup (153 rows: a ragged last one)
+    wl = synth.workload("vit_stage_act_bf16", batch=batch, tokens=tokens, dim=dim, heads=dim // 64, mlp_dim=130, depth=2, aux_depth=1)
+    run_case(wl, steps=1)
+
+
 @pytest.mark.parametrize("batch,tokens,dim,depth", [
     (3, 5, 64, 1),       # 15 rows: one ragged k-step of the weight gradients, 64-wide LayerNorm
     (9, 65, 192, 2),     # 585 rows: odd, tiles divided along the rows; 192-wide LayerNorm
