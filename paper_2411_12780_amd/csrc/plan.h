@@ -83,27 +83,27 @@ inline double tile_rounds(int M, int N, int bm, int bn, int units, double last) 
 }
 // Rows / 32 of the 256-wide tiles that are expected to beat the tiled kernel, 0 if none.
 //
-// From width 768 on (the shorter of N and K) the loop is long beside everything else and the rounds decide: one of 128 x 256 tiles
+// Above width 512 (the shorter of N and K) the loop is long beside everything else and the rounds decide: one of 128 x 256 tiles
 // takes 1.58 times, of 160 x 256 tiles 1.74 times as long as one of 128 x 128 (25216 rows of width 768: 30, 33 and 19 us).  25216 x
 // 768 is 2.3 rounds of 128 x 128, 1.15 of 128 x 256, 0.93 of 160 x 256 (K = 3072: 145, 142, 115 us).  Even cases stay on the tiled
-// kernel.  Training steps of two layers, all on the tiled kernel / so, 2080 to 33280 rows in all: width 768 29.3 / 27.2 ms, width
-// 1024 40.3 / 35.6.
+// kernel.
 //
-// Below, the epilogue and the change of kernels count as well.  Microseconds of a round (per k, and for the epilogue), a
+// Up to there, the epilogue and the change of kernels count as well.  Microseconds of a round (per k, and for the epilogue), a
 // least-squares fit to 4059 timings of the products of training steps (within 12 % rms):
 //   128 x 128   0.0161 K + 4.1 plain, 4.5 bias, 4.9 residual, 8.1 GELU (two tensors out), 5.2 its derivative (one more in)
 //   128 x 256   0.0280 K + 6.0        6.8       6.9           13.5                        10.3
 //   160 x 256   0.0316 K + 7.2        8.6       8.1           17.5                        14.1
 // and each product that runs on other tiles than its neighbours costs them about 3 us (the code of both kernels, 8 and 9 KB, is
-// fetched again: 4 us more for a tiled product behind one on wide tiles).  By rounds alone, some products ran longer (33280 x 576 x
-// 192 with a bias 24 -> 32 us) and steps of width 384 took longer than with none on wide tiles (25216 rows, two layers: 1382 us all
-// on the tiled kernel, 1403 by rounds, 1353 so).  Steps of two layers, 2080 to 50432 rows in all, ms, by rounds / so: width 128
-// 4.78 / 4.52, 192 6.91 / 6.81, 256 8.76 / 8.63, 384 13.87 / 13.67, 512 19.44 / 19.44.  One column of wide tiles reads each row of
-// A once and waits for memory where K is long (33280 x 256 x 768: 28 -> 32 us).
+// fetched again: 4 us more for a tiled product behind one on wide tiles).  By rounds alone, some products ran longer than on the
+// tiled kernel (33280 x 576 x 192 with a bias 24 -> 32 us), and so did steps of width 384 (25216 rows, two layers: products on the
+// tiled kernel 690 us, 730 by rounds).  Steps of two layers, 12 to 14 row counts from 2080 to 50432 in all, ms, by rounds / with
+// epilogue and change: width 128 4.78 / 4.52, 192 6.91 / 6.81, 256 8.76 / 8.63, 384 13.87 / 13.67, 512 19.44 / 19.44, 576 and 640
+// 42.2 / 42.6.  One column of wide tiles reads each row of A once and waits for memory where K is long (33280 x 256 x 768: 28 ->
+// 32 us).
 inline int wide_tile_rows(int M, int N, int K, ProductEnd end, int units) {
   if (K < PIPE_MIN_K || units < 8) return 0;
   double tiled, c4, c5;
-  if (std::min(N, K) >= 768) {
+  if (std::min(N, K) > 512) {
     tiled = 0.95 * tile_rounds(M, N, 128, 128, units, 0.62);
     c4 = 1.58 * tile_rounds(M, N, 128, 256, units, 0.62);
     c5 = 1.74 * tile_rounds(M, N, 160, 256, units, 0.62);
