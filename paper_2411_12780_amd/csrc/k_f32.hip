@@ -223,7 +223,7 @@ bool gemm_f32_groupable(const GemmArgs& g) {
 }
 
 // 64 x 64 tiles (half the operand traffic) once they give every compute unit a workgroup
-constexpr long F32_WIDE_TILES = 256;
+static long f32_units() { const int units = compute_units(); return units > 0 ? units : 256; }
 
 template <bool BT, int R>
 static int f32_launch(hipStream_t s, const F32Args& p) {
@@ -242,7 +242,7 @@ int launch_gemm_f32(hipStream_t s, const GemmArgs& g) {
   p.M = g.M; p.N = g.N; p.K = g.K; p.bias = g.bias; p.residual = (const float*)g.residual; p.ldr = (int)g.ldr;
   p.epilogue = g.epilogue; p.C2 = (float*)g.C2; p.aux = (const float*)g.aux; p.ldaux = (int)g.ldaux;
   p.a_bytes = (uint32_t)f32_bytes(false, g.M, g.K, p.lda); p.b_bytes = (uint32_t)f32_bytes(bt, g.N, g.K, p.ldb);
-  if (tiles_of(g.M, g.N, 64) >= F32_WIDE_TILES) return bt ? f32_launch<true, 2>(s, p) : f32_launch<false, 2>(s, p);
+  if (tiles_of(g.M, g.N, 64) >= f32_units()) return bt ? f32_launch<true, 2>(s, p) : f32_launch<false, 2>(s, p);
   return bt ? f32_launch<true, 1>(s, p) : f32_launch<false, 1>(s, p);
 }
 
@@ -254,7 +254,7 @@ int launch_gemm_f32_grouped(hipStream_t s, const GemmArgs* gs, int n) {
     a.n = n - j0 < F32_GROUP_MAX ? n - j0 : F32_GROUP_MAX;
     long wide_tiles = 0;
     for (int j = 0; j < a.n; ++j) wide_tiles += tiles_of(gs[j0 + j].M, gs[j0 + j].N, 64);
-    const bool wide = wide_tiles >= 2 * F32_WIDE_TILES;   // the reduction is the long side here: more waves first
+    const bool wide = wide_tiles >= 2 * f32_units();   // the reduction is the long side here: more waves first
     const int edge = wide ? 64 : 32;
     int tiles = 0;
     for (int j = 0; j < a.n; ++j) {

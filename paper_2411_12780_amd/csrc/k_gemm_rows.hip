@@ -9,9 +9,9 @@
 // straight from memory in the MFMA's register layout, several k-steps in flight at once; the four
 // partial tiles meet in LDS, are added in wave order (results do not depend on timing) and pass
 // through the epilogue.  Measured against the tiled kernel: 585 x 384 x 384 3.9 / 6.3 us, 585 x 384
-// x 1536 7.6 / 13.1 us, 640 x 768 x 3072 14.3 / 22.5 us.  Every tile reads its own operand rows, so
-// once there are more tiles than compute units the tiled kernel with its larger tiles is ahead
-// (585 x 2304 x 768: 13.4 / 9.4 us): see gemm_rows_supported.
+// x 1536 7.6 / 13.1 us.  Every tile reads its own operand rows, so once there are more tiles than
+// compute units the tiled kernel with its larger tiles is ahead (585 x 2304 x 768: 13.4 / 9.4 us):
+// see few_tiles in plan.h.
 //
 // Operand layouts: A is [M][K] with k contiguous (row stride lda: the class-token rows of a token
 // matrix are T*D apart).  B is either [N][K] with k contiguous (input gradients: W stored
@@ -21,6 +21,7 @@
 // takes the fragments out with the transposing LDS read; eight two-byte loads per fragment
 // instead were measured at 12.9 us per product against 5.7 us for the k-contiguous case.
 #include "common.h"
+#include "plan.h"
 
 namespace ppll {
 
@@ -213,21 +214,9 @@ __global__ __launch_bounds__(256) void gemm_rows_kernel(RowsArgs p) {
 bool aligned_to(const void* p, uintptr_t a) { return (((uintptr_t)p) & (a - 1)) == 0; }
 }  // namespace
 
-// One 32 x 32 tile per compute unit at most, else one 32 x 64 tile (only where the reduction is long enough for the tiled
-// kernel's serial walk to matter, see the figures above); up to 256 rows always.  Beyond that not where both the width and the
-// reduction exceed 384: every tile reads its own operand rows, and what a launch alone on the chip gains there (640 x 768 x 3072:
-// 14.3 / 22.5 us) pipelined blocks lose, whose streams share it: four blocks of width 768 with 455 rows take 1524 us a batch on
-// this kernel and 1366 on the tiled one, with 663 rows 1018 and 870; at widths 192 and 384 pipelines take the same on either.
-constexpr int ROWS_MAX_M = 256, ROWS_MAX_TILES = 256, ROWS_MAX_WIDTH = 384;
-static bool rows_wide(int M, int N) { return (long)((M + 31) / 32) * ((N + 31) / 32) > ROWS_MAX_TILES && M > ROWS_MAX_M; }
-static bool rows_fit(int M, int N, int K) {
-  if (M <= ROWS_MAX_M) return true;
-  return (N <= ROWS_MAX_WIDTH || K <= ROWS_MAX_WIDTH) && (long)((M + 31) / 32) * ((N + 63) / 64) <= ROWS_MAX_TILES;
-}
-
 bool gemm_rows_supported(const GemmArgs& g) {
   if (g.a_dt != BF16 || g.b_dt != BF16 || g.colsum) return false;
-  if (g.M < 1 || !rows_fit(g.M, g.N, g.K) || g.N < 1 || g.K < 1 || (g.N & 7) || (g.K & 7)) return false;
+  if (g.M < 1 || !few_tiles(g.M, g.N, g.K, compute_units()) || g.N < 1 || g.K < 1 || (g.N & 7) || (g.K & 7)) return false;
   if (g.a_sk != 1 || (g.a_sm & 7) || !aligned_to(g.A, 16)) return false;
   const bool bt = g.b_sn == 1 && g.b_sk != 1;
   if (bt) {
@@ -261,10 +250,10 @@ int launch_gemm_rows(hipStream_t s, const GemmArgs& g) {
   p.b_bytes = (uint32_t)(bt ? ((long)(g.K - 1) * g.b_sk + g.N) * 2 : ((long)(g.N - 1) * g.b_sn + g.K) * 2);
   const int steps = (g.K + 15) / 16;
   p.steps_per_wave = (steps + 3) / 4;
-  const bool wide = rows_wide(g.M, g.N);
+  const bool wide = few_tiles_wide(g.M, g.N, compute_units());
   const dim3 grid(wide ? (g.N + 63) / 64 : (g.N + 31) / 32, (g.M + 31) / 32);
   void* prof = nullptr;
-  PPLL_TRY(profile_begin(s, 2.0 * g.M * g.N * g.K, &prof, g.M <= ROWS_MAX_M ? 2 : 0));
+  PPLL_TRY(profile_begin(s, 2.0 * g.M * g.N * g.K, &prof, g.M <= FEW_ROWS ? 2 : 0));
   if (bt && wide) hipLaunchKernelGGL((gemm_rows_kernel<true, 2>), grid, dim3(256), 0, s, p);
   else if (bt) hipLaunchKernelGGL((gemm_rows_kernel<true, 1>), grid, dim3(256), 0, s, p);
   else if (wide) hipLaunchKernelGGL((gemm_rows_kernel<false, 2>), grid, dim3(256), 0, s, p);

@@ -72,6 +72,19 @@ inline WeightGradPlan plan_weight_grads(const ProductShape* p, int n, bool works
   return w;
 }
 
+// ---- A product with few output tiles, on the kernel whose waves split k: 32 x 32 tiles, one per compute unit at most, else 32 x
+// 64 ones, one per unit at most; up to 256 rows always.  Beyond that only where the width or the reduction is at most 384: every tile
+// reads its own operand rows, and what a launch alone on the chip gains (640 x 768 x 3072: 14.3 us, 22.5 on the tiled kernel; a
+// step of 3 + 1 layers of width 768, 663 rows: 786 and 831) pipelined blocks lose, whose streams share it: four such blocks of 39
+// images of 17 tokens take 2180 us a batch on this kernel and 1770 on the tiled one, of 7 images of 65 tokens (455 rows) 1846 and
+// 1652, with 1 + 1 layers and 663 rows 1012 and 871.  At widths 192 and 384 pipelines take the same on either.
+constexpr int FEW_ROWS = 256, FEW_WIDTH = 384;
+inline bool few_tiles_wide(int M, int N, int units) { return (long)((M + 31) / 32) * ((N + 31) / 32) > units && M > FEW_ROWS; }
+inline bool few_tiles(int M, int N, int K, int units) {
+  if (M <= FEW_ROWS) return true;
+  return (N <= FEW_WIDTH || K <= FEW_WIDTH) && (long)((M + 31) / 32) * ((N + 63) / 64) <= units;
+}
+
 // ---- A bf16 Linear product with k contiguous in A: tiles of 128 x 128 (the tiled kernel), 128 x 256 or 160 x 256
 enum ProductEnd { END_PLAIN, END_BIAS, END_RESIDUAL, END_GELU, END_DGELU };   // what its epilogue adds
 constexpr int PIPE_MIN_K = 128;

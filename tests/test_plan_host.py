@@ -26,6 +26,10 @@ int main() {
       int M, N, K, end, units;
       if (std::scanf("%d %d %d %d %d", &M, &N, &K, &end, &units) != 5) return 1;
       std::printf("%d\n", 32 * wide_tile_rows(M, N, K, (ProductEnd)end, units));
+    } else if (!std::strcmp(what, "few")) {
+      int M, N, K, units;
+      if (std::scanf("%d %d %d %d", &M, &N, &K, &units) != 4) return 1;
+      std::printf("%d\n", few_tiles(M, N, K, units) ? few_tiles_wide(M, N, units) ? 64 : 32 : 0);
     } else if (!std::strcmp(what, "attention")) {
       int T, H, dh, bwd, units;
       long heads;
@@ -145,3 +149,12 @@ def test_products_of_the_parity_cases_reach_the_kernels_they_name(plan):
     assert on(160, 97, 129, 520, 1528) == {"fc1", "d fc2"}
     assert on(160, 97, 129, 768, 64) == {"qkv", "proj", "d proj", "d qkv"}
     assert on(128, 143, 130, 768, 64) == {"proj", "d proj", "d qkv"}
+
+
+@pytest.mark.parametrize("M,N,K,columns", [
+    # columns of a tile of the few-tile kernel (0: not its product)
+    (1, 768, 3072, 32), (256, 3072, 768, 32), (257, 384, 1536, 32), (585, 384, 384, 32), (640, 384, 1536, 32), (683, 384, 384, 64),
+    (585, 1152, 384, 0), (257, 1536, 384, 64), (640, 768, 3072, 0), (257, 768, 768, 0), (640, 768, 48, 64), (8320, 384, 384, 0),
+])
+def test_products_with_few_tiles(plan, M, N, K, columns):
+    assert plan("few", M, N, K, UNITS) == [columns]
