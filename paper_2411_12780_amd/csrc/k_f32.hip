@@ -277,7 +277,8 @@ int launch_gemm_f32_grouped(hipStream_t s, const GemmArgs* gs, int n) {
 // Any head size and element type, T up to 256.  A workgroup takes ATT_ROWS query rows (keys in the second half of the
 // backward) of one (batch, head), 16 lanes each; the rows they are compared with lie in LDS as fp32, 4 floats apart from a
 // multiple of 16 so that 16 lanes reading 16 rows hit different banks.  One workgroup per (batch, head) walking all its
-// rows, as before, is 32 workgroups at batch 8: 73 us forward and 190 us backward at 65 tokens, 16-wide heads.
+// rows is 32 workgroups at batch 8: 73 us forward and 190 us backward at 65 tokens, 16-wide heads.  That kernel keeps the shapes
+// with many heads whose rows leave one of these workgroups a unit, see att_by_rows.
 namespace {
 __device__ __forceinline__ float4 ld4(const void* p, size_t i, int dt, int left) {   // elements i .. i+3, zero beyond `left`
   if (left >= 4) {

@@ -478,7 +478,8 @@ __global__ __launch_bounds__(256, 2) void gemm_mfma_grouped_kernel(GroupedArgs a
 // The same set of products on 128 x 256 tiles and the main loop of gemm_pipe.h.  A tile of K = 25216 rows keeps its workgroup for
 // half a millisecond, so what counts is the traffic of the loop per product: 24 KB into LDS for 128 x 256 x 32 instead of 32 KB for
 // 128 x 128 x 64, and a wave reads 192 instead of 128 values a k for twice the products.
-// Whole steps with 128 x 128 tiles and with these, microseconds: 25216 rows of width 768 6048 -> 5842, 640 rows 748 -> 732.
+// Whole steps of width 768 with 128 x 128 tiles and with these, microseconds: 25216 rows 6048 -> 5842; 640 rows 748 -> 732 (all of
+// whose other products ran on the few-tile kernel then).
 using PipeShape = pipe::Shape<true, true, 1, 4, 4, 3>;
 constexpr int PIPE_BN = PipeShape::BN;
 static_assert(PipeShape::BM == BM && BM == WG_EDGE && BN == WG_EDGE && PIPE_BN == WG_WIDE && BK == WG_STEP, "");

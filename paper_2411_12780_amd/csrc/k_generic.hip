@@ -410,7 +410,7 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const void* dy, cons
 }
 }  // namespace
 
-// ---- bf16 fast path: one wave per row, the row held in registers (NJ x 2 values per lane), one pass
+// ---- bf16 fast path: the row in registers, one pass
 namespace {
 __device__ __forceinline__ float lo_bf(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float hi_bf(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
