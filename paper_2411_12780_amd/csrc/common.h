@@ -139,6 +139,10 @@ int launch_gemm_rows(hipStream_t s, const GemmArgs& g);
 int gemm_pipe_choice(const GemmArgs& g);
 bool gemm_pipe_supported(const GemmArgs& g);
 int launch_gemm_pipe(hipStream_t s, const GemmArgs& g, int choice);
+// Products whose 64 x 64 tiles find a compute unit each, bf16 output: see k_gemm_split.hip
+bool gemm_split_choice(const GemmArgs& g);
+bool gemm_split_supported(const GemmArgs& g);
+int launch_gemm_split(hipStream_t s, const GemmArgs& g);
 // fp32 products on the matrix cores: see k_f32.hip
 bool gemm_f32_supported(const GemmArgs& g);
 bool gemm_f32_groupable(const GemmArgs& g);

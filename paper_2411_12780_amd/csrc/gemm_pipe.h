@@ -18,8 +18,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* ptr, uin
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(ptr), 0, (int)bytes, 0x00020000);
 }
 typedef __attribute__((address_space(3))) char lds_char;
-__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t r, lds_char* dst, int voff) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, voff, 0, 0, 0);
+__device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t r, lds_char* dst, int voff, int soff = 0) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, voff, soff, 0, 0);
 }
 
 template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }

@@ -79,6 +79,7 @@ int compute_units() {
 
 int launch_gemm(hipStream_t s, const GemmArgs& g) {
   if (gemm_rows_supported(g)) return launch_gemm_rows(s, g);   // few output rows: latency, not throughput
+  if (gemm_split_choice(g)) return launch_gemm_split(s, g);   // a tile a unit at most: the chain along k
   if (const int im = gemm_pipe_choice(g)) return launch_gemm_pipe(s, g, im);                // many tiles: throughput
   if (gemm_mfma_supported(g) && g.a_sk == 1) return launch_gemm_mfma(s, g);
   return gemm_f32_supported(g) && g.a_sk == 1 ? launch_gemm_f32(s, g) : launch_gemm_generic(s, g);
@@ -106,7 +107,7 @@ int launch_attention_bwd(hipStream_t s, const void* qkv, const void* out, const 
 }  // namespace ppll
 
 // One product on one kernel, for tests of a kernel against another (no part of the public interface): 1 few tiles, 2 tiled, 4 / 5
-// 128 / 160 rows of 256 columns.  C[M,N] = A[M][K] B, B [K][N] (bt) or [N][K], bf16 throughout.
+// 128 / 160 rows of 256 columns, 6 tiles of 64 x 64.  C[M,N] = A[M][K] B, B [K][N] (bt) or [N][K], bf16 throughout.
 extern "C" int ppll_internal_product(int kernel, int M, int N, int K, const void* A, long lda, const void* B, long ldb, int bt,
                                      void* C, long ldc, const float* bias, const void* residual, int epilogue, void* C2,
                                      const void* aux, void* stream) {
@@ -121,6 +122,7 @@ extern "C" int ppll_internal_product(int kernel, int M, int N, int K, const void
   if (kernel == 1 && gemm_rows_supported(g)) return launch_gemm_rows(s, g);
   if (kernel == 2 && gemm_mfma_supported(g)) return launch_gemm_mfma(s, g);
   if ((kernel == 4 || kernel == 5) && gemm_pipe_supported(g)) return launch_gemm_pipe(s, g, kernel);
+  if (kernel == 6 && gemm_split_supported(g)) return launch_gemm_split(s, g);
   set_error("kernel %d does not take this product", kernel);
   return PPLL_ERR_CONFIG;
 }

@@ -9,7 +9,7 @@ from paper_2411_12780_amd import binding as P
 
 pytestmark = pytest.mark.gpu
 
-FEW, TILED, WIDE_128, WIDE_160 = 1, 2, 4, 5
+FEW, TILED, WIDE_128, WIDE_160, SPLIT = 1, 2, 4, 5, 6
 NONE, GELU, DGELU = 0, 1, 2
 
 
@@ -62,3 +62,39 @@ def test_products_that_a_kernel_does_not_take_are_refused():
     for kernel in (WIDE_128, WIDE_160, 3):
         status, C, _ = product(kernel, A, B, 1, None, None, NONE, None)
         assert status == 2 and bool((C == 7.0).all())
+
+
+@pytest.mark.parametrize("epilogue", [NONE, GELU, DGELU])
+@pytest.mark.parametrize("bt", [0, 1])
+@pytest.mark.parametrize("M,N,K", [
+    # edges of the 64 x 64 tile and of a stage of 64 k; one to five stages (four are in flight), odd and even numbers of them
+    (1, 8, 128), (64, 64, 128), (65, 72, 136), (63, 56, 192), (129, 120, 200), (300, 264, 256), (640, 136, 264), (257, 384, 320), (33, 768, 3072),
+])
+def test_split_products(M, N, K, bt, epilogue):
+    g = torch.Generator(device="cuda").manual_seed(M * 1000 + N + K)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    wide = rnd(M, K + 24)                     # rows of A further apart than they are long
+    A, B = wide[:, :K], rnd(K, N) if bt else rnd(N, K)
+    bias = torch.randn(N, generator=g, device="cuda") if epilogue != DGELU else None
+    residual = rnd(M, N) if epilogue == NONE else None
+    aux = rnd(M, N)
+    status, C, C2 = product(SPLIT, A, B, bt, bias, residual, epilogue, aux)
+    assert status == 0
+    v = A.double() @ (B.double() if bt else B.double().t().contiguous())
+    if bias is not None:
+        v = v + bias.double()
+    if residual is not None:
+        v = v + residual.double()
+    ref = {NONE: v, DGELU: v * aux.double(), GELU: 0.5 * (1 + torch.erf(v / 2 ** 0.5)) + v * torch.exp(-0.5 * v * v) / (2 * torch.pi) ** 0.5}[epilogue]
+    # per element: one rounding to bf16, and fp32 sums of K terms in any order on the scale of the sum of their magnitudes (GELU's
+    # derivative has slope below 1.2; the factor of a saved derivative scales both)
+    size = A.double().abs() @ (B.double() if bt else B.double().t().contiguous()).abs()
+    if epilogue == DGELU:
+        size = size * aux.double().abs()
+    bound = ref.abs() * 2.0 ** -8 + size * (K * 2.0 ** -24) + 1e-6
+    assert bool(((C.double() - ref).abs() <= bound).all())
+    if epilogue == GELU:
+        gelu = v * 0.5 * (1 + torch.erf(v / 2 ** 0.5))
+        assert bool(((C2.double() - gelu).abs() <= gelu.abs() * 2.0 ** -8 + size * (K * 2.0 ** -23) + 1e-6).all())
+    again = product(SPLIT, A, B, bt, bias, residual, epilogue, aux)
+    assert torch.equal(C, again[1]) and torch.equal(C2, again[2])

@@ -30,6 +30,10 @@ int main() {
       int M, N, K, units;
       if (std::scanf("%d %d %d %d", &M, &N, &K, &units) != 4) return 1;
       std::printf("%d\n", few_tiles(M, N, K, units) ? few_tiles_wide(M, N, units) ? 64 : 32 : 0);
+    } else if (!std::strcmp(what, "split")) {
+      int M, N, K, units;
+      if (std::scanf("%d %d %d %d", &M, &N, &K, &units) != 4) return 1;
+      std::printf("%d\n", split_tiles(M, N, K, units));
     } else if (!std::strcmp(what, "attention")) {
       int T, H, dh, bwd, units;
       long heads;
@@ -158,3 +162,13 @@ def test_products_of_the_parity_cases_reach_the_kernels_they_name(plan):
 ])
 def test_products_with_few_tiles(plan, M, N, K, columns):
     assert plan("few", M, N, K, UNITS) == [columns]
+
+
+@pytest.mark.parametrize("M,N,K,taken", [
+    # 64 x 64 tiles, one a unit at most, from K = 128
+    (640, 768, 3072, 1), (640, 1600, 384, 1), (640, 1608, 384, 0), (2688, 384, 1536, 1), (2689, 384, 1536, 0), (1, 16384, 128, 1),
+    (16384, 64, 128, 1), (16385, 64, 128, 0), (640, 768, 120, 0), (8320, 384, 1536, 0),
+])
+def test_products_with_a_tile_a_unit(plan, M, N, K, taken):
+    assert plan("split", M, N, K, UNITS) == [taken]
+    assert plan("split", M, N, K, 4) == [0]
