@@ -13,22 +13,26 @@
 // so the first operand is fetched with the matching key order.  P and dS never
 // pass through memory.
 //
-// Every operand passes through LDS.  K, V, Q and dO tiles are copied there with
-// coalesced 16-byte loads as [token][64] rows of 128 bytes whose 16-byte granule
-// index is XORed with (token/2)%8: the copy's stores, the fragment reads (32
-// tokens x one granule per half wave) and the reads of the transposer below are
-// then free of bank conflicts without padding.  First operands whose reduction
-// index is the token (V^T, K^T, Q^T, dO^T) are transposed once per workgroup into
-// [64][T padded] arrays (8 bytes of padding per row) with an in-register 4 x 8
-// transpose (v_perm_b32 on four 16-byte rows).
+// Forward: K passes through LDS as [token][64] rows of 128 bytes whose 16-byte granule index is XORed with (token/2)%8: the copy's
+// stores and the fragment reads (32 tokens x one granule per half wave) are then free of bank conflicts without padding.  V^T, whose
+// reduction index is the token, is transposed once per workgroup into a [64][T padded] array (8 bytes of padding per row) with an
+// in-register 4 x 8 transpose (v_perm_b32 on four 16-byte rows).
 //
-// Backward: phase A (wave = query tile) forms P and dS with a lane per query
-// and accumulates dQ; phase B (wave = key tile) forms them again with a lane
-// per key (scores recomputed in the other orientation instead of transposing
-// registers) and accumulates dK and dV.  Four LDS regions are reused between the
-// phases (A: K, V, K^T, dO;  B: Q, Q^T, dO^T, dO), which keeps a 96-token
-// workgroup at 51 KB, three to a compute unit.  All sums run in a fixed order.
+// Backward: one part (wave = query tile) forms P and dS with a lane per query and accumulates dQ; another (wave = key tile) forms them
+// again with a lane per key (scores recomputed in the other orientation instead of transposing registers) and accumulates dK and dV.
+// The first needs K and V of the head in LDS, the second Q and dO; the transposed operands come out of the same tiles by transposing
+// reads.  All sums run in a fixed order.
+// What bounds it is memory, each part waiting for its tiles and then storing them: 57 us of 143 at 128 x 197 tokens x 12 heads are
+// loads, 40 stores.  So the tiles, half of what they were with transposed copies beside them, leave room for two or three workgroups a
+// unit; up to 128 tokens one workgroup does both parts behind one barrier, all loads asked for at once, beyond that each part is a
+// workgroup of its own (four tiles of 197 tokens would leave room for one).  Results leave 16 bytes a lane (8 bytes: 152 us; whole rows
+// through LDS: 143).
+// Microseconds with transposed copies, one workgroup a head at every size -> now: 128 images x 197 tokens x 12 heads 171 -> 143,
+// 60 x 145 x 6 36.5 -> 29, 128 x 65 x 6 20.6 -> 16.8, 20 x 65 x 6 10.9 -> 7.9, 64 x 100 x 12 35.6 -> 28.
+#include <type_traits>
+
 #include "common.h"
+#include "gemm_pipe.h"
 
 namespace ppll {
 
@@ -84,15 +88,6 @@ __device__ __forceinline__ void write_transposed(const uint4* r, char* dst, int 
     *reinterpret_cast<uint2*>(dst + (8 * dc + i) * RS + 2 * j0) = o;
   }
 }
-// LDS tile [TP][64] -> dst[64][TP] (row stride 2*TP+8 bytes); one 4 x 8 block per thread of the 2*TP
-template <int TP>
-__device__ __forceinline__ void transpose_tile(const char* rm, char* dst, int tid) {
-  const int jg = tid >> 3, dc = tid & 7, j0 = 4 * jg;
-  uint4 r[4];
-#pragma unroll
-  for (int jj = 0; jj < 4; ++jj) r[jj] = *reinterpret_cast<const uint4*>(rm + rm_off(j0 + jj, dc));
-  write_transposed(r, dst, 2 * TP + 8, dc, j0);
-}
 // global rows -> dst[64][TP], zero for tokens >= T
 template <int TP>
 __device__ __forceinline__ void transpose_to_lds(const uint16_t* __restrict__ src, long ld, int T, char* dst, int tid) {
@@ -113,7 +108,7 @@ __global__ __launch_bounds__(64 * NKT) void attn_fwd_mfma_kernel(const uint16_t*
                                                                  uint16_t* __restrict__ out,
                                                                  float* __restrict__ lse_out) {
   constexpr int TP = 32 * NKT, RS = 2 * TP + 8;
-  extern __shared__ __align__(16) char smem[];
+  extern __shared__ __align__(1024) char smem[];
   char* vt = smem;              // V^T [64][TP]
   char* krm = smem + 64 * RS;   // K   [TP][64]
   const int b = blockIdx.x / H, h = blockIdx.x % H, D = 64 * H;
@@ -195,193 +190,266 @@ __global__ __launch_bounds__(64 * NKT) void attn_fwd_mfma_kernel(const uint16_t*
   }
 }
 
+// ---- Backward tiles: [token][64] bf16, 128-byte rows, the 16-byte granule g of row r at g ^ turn(r).  The fragment reads (16 rows x one
+// granule at a time) and the transposing reads (4 rows x 64 bytes, rows r and r + 2 in different halves of the banks) both spread
+// over all banks.
+__device__ __forceinline__ int turn(int r) { return ((r & 2) << 1) | ((r >> 2) & 3); }
+// Copies rows of 64 bf16 to a tile of TP rows, straight from memory to LDS, zeros beyond T.  off: byte offset of row 0 in the buffer
+template <int TP, int W>
+__device__ __forceinline__ void copy_rows(__amdgpu_buffer_rsrc_t rs, int off, int ld2, int T, pipe::lds_char* tile, int wave, int lane) {
+#pragma unroll
+  for (int i = 0; i < (TP / 8 + W - 1) / W; ++i) {
+    const int q = i * W + wave, r = q * 8 + (lane >> 3);
+    if (TP / 8 % W == 0 || q < TP / 8) pipe::load_to_lds(rs, tile + q * 1024, r < T ? off + r * ld2 + (((lane & 7) ^ turn(r)) << 4) : pipe::OOB);
+  }
+}
+// lane part of the address of rows 0 .. 31 of a tile at k step kk (16 columns), and of their transpose: columns 32 dt .. + 31 as rows,
+// tokens 0 .. 3 and 8 .. 11 (upper lanes: + 4) as k
+__device__ __forceinline__ int row_addr(int lane, int kk) { return (lane & 31) * 128 + (((2 * kk + (lane >> 5)) ^ turn(lane & 31)) << 4); }
+__device__ __forceinline__ int col_addr(int lane, int dt, int hi) {
+  const int r = 8 * hi + 4 * (lane >> 5) + ((lane & 15) >> 2), g = 4 * dt + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+  return r * 128 + ((g ^ turn(r)) << 4) + 8 * (lane & 1);
+}
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+__device__ __forceinline__ bf16x8 tr_frag(const char* lo, const char* hi) {
+  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)lo);
+  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)hi);
+  const uint2 u = __builtin_bit_cast(uint2, a), v = __builtin_bit_cast(uint2, b);
+  return __builtin_bit_cast(bf16x8, make_uint4(u.x, u.y, v.x, v.y));
+}
+__device__ __forceinline__ float dot8(uint4 a, uint4 b) {
+  const uint32_t x[4] = {a.x, a.y, a.z, a.w}, y[4] = {b.x, b.y, b.z, b.w};
+  float d = 0.f;
+#pragma unroll
+  for (int w = 0; w < 4; ++w)
+    d += __uint_as_float(x[w] << 16) * __uint_as_float(y[w] << 16) + __uint_as_float(x[w] & 0xffff0000u) * __uint_as_float(y[w] & 0xffff0000u);
+  return d;
+}
+
+// Waves of a backward workgroup, each with one tile of 32 tokens, from five tiles on with two: 60 images x 145 tokens x 6 heads 29 us,
+// 32 with five waves.  Three waves a SIMD leave 168 registers; with two tiles a wave those spilled (52 us).
+constexpr int bwd_waves(int nkt) { return nkt <= 4 ? nkt : (nkt + 1) / 2; }
+constexpr int bwd_waves_per_simd(int nkt) { return nkt <= 4 ? 3 : 2; }
+// Both parts in one workgroup, us, one / two: 128 images x 65 tokens x 6 heads 16.7 / 21.1, 128 x 17 x 12 8.3 / 10.4, 20 x 100 x 12
+// 11.1 / 12.7; few heads alone are a little ahead in two (20 x 65 x 6 7.9 / 7.3).  Beyond four tiles there is no room.
+constexpr bool bwd_both(int nkt) { return nkt <= 4; }
+constexpr int bwd_lds(int nkt) { return (bwd_both(nkt) ? 4 : 2) * nkt * 4096 + 2 * 32 * nkt * (int)sizeof(float); }
+
 template <int NKT>
-__global__ __launch_bounds__(64 * NKT, (NKT <= 4 ? 3 : 2)) void attn_bwd_mfma_kernel(const uint16_t* __restrict__ qkv,
-                                                                 const uint16_t* __restrict__ out,
-                                                                 const uint16_t* __restrict__ dout,
-                                                                 const float* __restrict__ lse, int T, int H,
-                                                                 uint16_t* __restrict__ dqkv) {
-  constexpr int TP = 32 * NKT, RS = 2 * TP + 8;
-  extern __shared__ __align__(16) char smem[];
-  constexpr int REG = 64 * RS;     // one region: a [TP][64] tile (TP*128 bytes) or a [64][TP] transposed one
-  char* r0 = smem;                 // phase A: K        phase B: Q
-  char* r1 = smem + REG;           // phase A: V        phase B: Q^T
-  char* r2 = smem + 2 * REG;       // phase A: K^T      phase B: dO^T
-  char* r3 = smem + 3 * REG;       // both phases: dO
-  float* Dsh = reinterpret_cast<float*>(smem + 4 * REG);  // [TP] <dO_i, O_i>
-  float* Lsh = Dsh + TP;                                  // [TP] log-sum-exp
-  const int b = blockIdx.x / H, h = blockIdx.x % H, D = 64 * H;
+__global__ __launch_bounds__(64 * bwd_waves(NKT), bwd_waves_per_simd(NKT)) void attn_bwd_mfma_kernel(
+    const uint16_t* __restrict__ qkv, const uint16_t* __restrict__ out, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
+    int T, int H, int heads, uint16_t* __restrict__ dqkv) {
+  constexpr int TP = 32 * NKT, W = bwd_waves(NKT), TILE = TP * 128;
+  constexpr bool BOTH = bwd_both(NKT);
+  constexpr int QO = BOTH ? 2 * TILE : 0;      // tiles: K, V at 0, Q, dO at QO
+  extern __shared__ __align__(1024) char smem[];
+  // the two workgroups of a head are 8 apart: the same XCD, whose L2 holds what both read
+  const int id = BOTH ? blockIdx.x : (blockIdx.x >> 4) * 8 + (blockIdx.x & 7);
+  const bool do_queries = BOTH || !(blockIdx.x & 8), do_keys = BOTH || (blockIdx.x & 8);
+  if (id >= heads) return;
+  const int b = id / H, h = id % H, D = 64 * H;
   const long ld = 3L * D;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 31, hh = lane >> 5;
-  constexpr int NT = 64 * NKT;
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, hh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint16_t* base = qkv + (size_t)b * T * ld + h * 64;
   const uint16_t* obase = out + (size_t)b * T * D + h * 64;
   const uint16_t* dobase = dout + (size_t)b * T * D + h * 64;
-  // K, V, dO -> LDS; D_i = <dO_i, O_i> from the same pass: 8 lanes per token, then a 3-step exchange
+  uint16_t* gbase = dqkv + (size_t)b * T * ld + h * 64;
+  const float* lbase = lse + (size_t)id * T;
+  const __amdgpu_buffer_rsrc_t rs = pipe::make_rsrc(qkv + (size_t)b * T * ld, (uint32_t)(T * ld * 2));
+  pipe::lds_char* lds = (pipe::lds_char*)smem;
+  float* Dsh = reinterpret_cast<float*>(smem + QO + 2 * TILE);   // [TP] <dO_i, O_i>
+  float* Lsh = Dsh + TP;                                         // [TP] log-sum-exp
+  int ra[4], ca[2][2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int c = tid + NT * i, r = c >> 3, g = c & 7;
-    uint4 kv = make_uint4(0, 0, 0, 0), vv = kv, dov = kv, ov = kv;
-    if (r < T) {
-      kv = *reinterpret_cast<const uint4*>(base + (long)r * ld + D + 8 * g);
-      vv = *reinterpret_cast<const uint4*>(base + (long)r * ld + 2 * D + 8 * g);
-      dov = *reinterpret_cast<const uint4*>(dobase + (long)r * D + 8 * g);
-      ov = *reinterpret_cast<const uint4*>(obase + (long)r * D + 8 * g);
-    }
-    const int off = rm_off(r, g);
-    *reinterpret_cast<uint4*>(r0 + off) = kv;
-    *reinterpret_cast<uint4*>(r1 + off) = vv;
-    *reinterpret_cast<uint4*>(r3 + off) = dov;
-    const uint32_t* aw = reinterpret_cast<const uint32_t*>(&dov);
-    const uint32_t* ow = reinterpret_cast<const uint32_t*>(&ov);
-    float dd = 0.f;
+  for (int kk = 0; kk < 4; ++kk) ra[kk] = row_addr(lane, kk);
 #pragma unroll
-    for (int w = 0; w < 4; ++w)
-      dd += __uint_as_float(aw[w] << 16) * __uint_as_float(ow[w] << 16) +
-            __uint_as_float(aw[w] & 0xffff0000u) * __uint_as_float(ow[w] & 0xffff0000u);
-    dd += __shfl_xor(dd, 1, 64);
-    dd += __shfl_xor(dd, 2, 64);
-    dd += __shfl_xor(dd, 4, 64);
-    if (g == 0) {
-      Dsh[r] = dd;
-      Lsh[r] = r < T ? lse[((size_t)b * H + h) * T + r] : 0.f;
-    }
-  }
-  __syncthreads();
-  transpose_tile<TP>(r0, r2, tid);   // K^T
-  __syncthreads();
-
-  // ---------------- phase A: wave = query tile, lane = query; dQ
-  {
-    const int qi = 32 * wave + li;
-    bf16x8 qf[4], dof[4];
+  for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      qf[kk] = ld_frag(base + (long)qi * ld + 16 * kk + 8 * hh, qi < T);
-      dof[kk] = lds_frag(r3, qi, 2 * kk + hh);
-    }
-    const float lse_i = Lsh[qi], d_i = Dsh[qi];
-    f32x16 dq[2];
+    for (int hi = 0; hi < 2; ++hi) ca[dt][hi] = col_addr(lane, dt, hi);
+  auto rows = [&](int at, int tile) { return *reinterpret_cast<const bf16x8*>(smem + at + tile); };
+  // a lane holds 4 consecutive columns of a row, its partner in the other half of the wave the next 4: they trade, and store 16 bytes
+  auto store = [&](uint16_t* row, const f32x16 (&v)[2], float scale) {
 #pragma unroll
     for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) dq[dt][e] = 0.f;
-#pragma unroll 1
-    for (int jt = 0; jt < NKT; ++jt) {
-      const int kj = 32 * jt + li;
-      f32x16 s, dp;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const bf16x8 kf = lds_frag(r0, kj, 2 * kk + hh);
-        const bf16x8 vf = lds_frag(r1, kj, 2 * kk + hh);
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[kk], s, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, dof[kk], dp, 0, 0, 0);
+      for (int q = 0; q < 4; q += 2) {
+        const auto lo = __builtin_amdgcn_permlane32_swap(pack2(v[dt][4 * q] * scale, v[dt][4 * q + 1] * scale),
+                                                         pack2(v[dt][4 * q + 4] * scale, v[dt][4 * q + 5] * scale), false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(pack2(v[dt][4 * q + 2] * scale, v[dt][4 * q + 3] * scale),
+                                                         pack2(v[dt][4 * q + 6] * scale, v[dt][4 * q + 7] * scale), false, false);
+        *reinterpret_cast<uint4*>(row + 32 * dt + 8 * (q + hh)) = make_uint4(lo[0], hi[0], lo[1], hi[1]);
       }
-      float ds[16];
+  };
+  const int whole = T >> 5;   // tiles without padding
+
+  if (do_queries) {
+    copy_rows<TP, W>(rs, (h * 64 + D) * 2, (int)ld * 2, T, lds, wave, lane);
+    copy_rows<TP, W>(rs, (h * 64 + 2 * D) * 2, (int)ld * 2, T, lds + TILE, wave, lane);
+  }
+  if (do_keys) {
+    copy_rows<TP, W>(rs, h * 128, (int)ld * 2, T, lds + QO, wave, lane);
+    // dO -> LDS; D_i = <dO_i, O_i> from the same pass: 8 lanes per token, then a 3-step exchange
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int key = 32 * jt + 8 * (e >> 2) + 4 * hh + (e & 3);
-        const float p = key < T ? __expf(s[e] * kScale - lse_i) : 0.f;
-        ds[e] = p * (dp[e] - d_i);
+    for (int i = 0; i < (TP / 8 + W - 1) / W; ++i) {
+      const int q = i * W + wave, r = q * 8 + (lane >> 3), g = lane & 7;
+      if (TP / 8 % W != 0 && q >= TP / 8) break;
+      uint4 dov = make_uint4(0, 0, 0, 0), ov = dov;
+      if (r < T) {
+        dov = *reinterpret_cast<const uint4*>(dobase + (long)r * D + 8 * g);
+        ov = *reinterpret_cast<const uint4*>(obase + (long)r * D + 8 * g);
       }
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        const bf16x8 dsf = pack8(ds + 8 * half);
-        const int tok = 32 * jt + 16 * half + 4 * hh;
-#pragma unroll
-        for (int dt = 0; dt < 2; ++dt) {
-          const bf16x8 ktf = ld_tfrag(r2 + (32 * dt + li) * RS, tok);
-          dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktf, dsf, dq[dt], 0, 0, 0);
-        }
+      *reinterpret_cast<uint4*>(smem + QO + TILE + r * 128 + ((g ^ turn(r)) << 4)) = dov;
+      float dd = dot8(dov, ov);
+      dd += __shfl_xor(dd, 1, 64);
+      dd += __shfl_xor(dd, 2, 64);
+      dd += __shfl_xor(dd, 4, 64);
+      if (g == 0) {
+        Dsh[r] = dd;
+        Lsh[r] = r < T ? lbase[r] : 0.f;
       }
     }
-    if (qi < T) {
-      uint16_t* row = dqkv + ((size_t)b * T + qi) * ld + h * 64;
+  }
+  if (BOTH) {
+    pipe::wait_vm<0>();
+    __syncthreads();
+  }
+
+  if (do_queries) {   // wave = query tile, lane = query: dQ
+#pragma unroll 1
+    for (int t = wave; t < NKT; t += W) {
+      const int qi = 32 * t + li;
+      const bool ok = qi < T;
+      bf16x8 qf[4], dof[4];
+      float d_i = 0.f, lse_i = 0.f;
+      if (BOTH) {
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) { qf[kk] = rows(t * 4096 + ra[kk], QO); dof[kk] = rows(t * 4096 + ra[kk], QO + TILE); }
+        d_i = Dsh[qi]; lse_i = Lsh[qi];
+      } else {
+        float d[4];
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+          qf[kk] = ld_frag(base + (long)qi * ld + 16 * kk + 8 * hh, ok);
+          dof[kk] = ld_frag(dobase + (long)qi * D + 16 * kk + 8 * hh, ok);
+          d[kk] = dot8(__builtin_bit_cast(uint4, dof[kk]), __builtin_bit_cast(uint4, ld_frag(obase + (long)qi * D + 16 * kk + 8 * hh, ok)));
+          d[kk] += __shfl_xor(d[kk], 32, 64);
+        }
+        d_i = (d[0] + d[1]) + (d[2] + d[3]);     // the order of the keys' workgroup
+        if (ok) lse_i = lbase[qi];
+        if (t == wave) {                // the first tile of every wave
+          pipe::wait_vm<0>();
+          __syncthreads();
+        }
+      }
+      f32x16 dq[2];
 #pragma unroll
       for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          uint2 w = make_uint2(pack2(dq[dt][4 * q] * kScale, dq[dt][4 * q + 1] * kScale),
-                               pack2(dq[dt][4 * q + 2] * kScale, dq[dt][4 * q + 3] * kScale));
-          *reinterpret_cast<uint2*>(row + 32 * dt + 8 * q + 4 * hh) = w;
+        for (int e = 0; e < 16; ++e) dq[dt][e] = 0.f;
+      auto keys = [&](int jt, auto padded) {
+        f32x16 s, dp;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+          const int at = jt * 4096 + ra[kk];
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows(at, 0), qf[kk], s, 0, 0, 0);
+          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows(at, TILE), dof[kk], dp, 0, 0, 0);
         }
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          __builtin_amdgcn_sched_barrier(0);
+          if (padded && 32 * jt + 16 * half >= T) continue;
+          float ds[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int i = 8 * half + e;
+            float p = __expf(s[i] * kScale - lse_i);
+            if (padded && 32 * jt + 8 * (i >> 2) + 4 * hh + (i & 3) >= T) p = 0.f;
+            ds[e] = p * (dp[i] - d_i);
+          }
+          const bf16x8 dsf = pack8(ds);
+#pragma unroll
+          for (int dt = 0; dt < 2; ++dt) {
+            const char *lo = smem + (jt * 4096 + ca[dt][0]), *hi = smem + (jt * 4096 + ca[dt][1]);
+            dq[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_frag(lo + 2048 * half, hi + 2048 * half), dsf, dq[dt], 0, 0, 0);
+          }
+        }
+      };
+#pragma unroll 1
+      for (int jt = 0; jt < whole; ++jt) keys(jt, std::false_type{});
+      if (whole < NKT) keys(whole, std::true_type{});
+      if (ok) store(gbase + (long)qi * ld, dq, kScale);
     }
   }
 
-  // ---------------- phase B: wave = key tile, lane = key; dK, dV
-  {
-    const int kj = 32 * wave + li;
-    bf16x8 kf[4], vf[4];
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      kf[kk] = lds_frag(r0, kj, 2 * kk + hh);
-      vf[kk] = lds_frag(r1, kj, 2 * kk + hh);
-    }
-    __syncthreads();                               // every wave is done with K, V and K^T
-    stage_rows<TP>(base, ld, T, r0, tid);          // Q
-    transpose_tile<TP>(r3, r2, tid);               // dO^T
-    __syncthreads();
-    transpose_tile<TP>(r0, r1, tid);               // Q^T
-    __syncthreads();
-    f32x16 dk[2], dv[2];
-#pragma unroll
-    for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) { dk[dt][e] = 0.f; dv[dt][e] = 0.f; }
+  if (do_keys) {   // wave = key tile, lane = key: dK, dV
 #pragma unroll 1
-    for (int it = 0; it < NKT; ++it) {
-      const int qrow = 32 * it + li;
-      f32x16 s, dp;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
+    for (int t = wave; t < NKT; t += W) {
+      const int kj = 32 * t + li;
+      bf16x8 kf[4], vf[4];
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
-        const bf16x8 qf = lds_frag(r0, qrow, 2 * kk + hh);
-        const bf16x8 dof = lds_frag(r3, qrow, 2 * kk + hh);
-        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf, kf[kk], s, 0, 0, 0);     // rows = queries, lane = key
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dof, vf[kk], dp, 0, 0, 0);
+        if (BOTH) { kf[kk] = rows(t * 4096 + ra[kk], 0); vf[kk] = rows(t * 4096 + ra[kk], TILE); continue; }
+        kf[kk] = ld_frag(base + (long)kj * ld + D + 16 * kk + 8 * hh, kj < T);
+        vf[kk] = ld_frag(base + (long)kj * ld + 2 * D + 16 * kk + 8 * hh, kj < T);
       }
-      float p[16], ds[16];
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int q0 = 32 * it + 8 * q4 + 4 * hh;
-        const float4 l4 = *reinterpret_cast<const float4*>(Lsh + q0);
-        const float4 d4 = *reinterpret_cast<const float4*>(Dsh + q0);
-        const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dvv[4] = {d4.x, d4.y, d4.z, d4.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float pe = (q0 + e) < T ? __expf(s[4 * q4 + e] * kScale - lv[e]) : 0.f;
-          p[4 * q4 + e] = pe;
-          ds[4 * q4 + e] = pe * (dp[4 * q4 + e] - dvv[e]);
-        }
+      if (!BOTH && t == wave) {
+        pipe::wait_vm<0>();
+        __syncthreads();
       }
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        const bf16x8 pf = pack8(p + 8 * half), dsf = pack8(ds + 8 * half);
-        const int tok = 32 * it + 16 * half + 4 * hh;
-#pragma unroll
-        for (int dt = 0; dt < 2; ++dt) {
-          const bf16x8 dotf = ld_tfrag(r2 + (32 * dt + li) * RS, tok);
-          const bf16x8 qtf = ld_tfrag(r1 + (32 * dt + li) * RS, tok);
-          dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(dotf, pf, dv[dt], 0, 0, 0);
-          dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qtf, dsf, dk[dt], 0, 0, 0);
-        }
-      }
-    }
-    if (kj < T) {
-      uint16_t* row = dqkv + ((size_t)b * T + kj) * ld + h * 64;
+      f32x16 dk[2], dv[2];
 #pragma unroll
       for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          uint2 wk = make_uint2(pack2(dk[dt][4 * q] * kScale, dk[dt][4 * q + 1] * kScale),
-                                pack2(dk[dt][4 * q + 2] * kScale, dk[dt][4 * q + 3] * kScale));
-          uint2 wv = make_uint2(pack2(dv[dt][4 * q], dv[dt][4 * q + 1]), pack2(dv[dt][4 * q + 2], dv[dt][4 * q + 3]));
-          *reinterpret_cast<uint2*>(row + D + 32 * dt + 8 * q + 4 * hh) = wk;
-          *reinterpret_cast<uint2*>(row + 2 * D + 32 * dt + 8 * q + 4 * hh) = wv;
+        for (int e = 0; e < 16; ++e) { dk[dt][e] = 0.f; dv[dt][e] = 0.f; }
+      auto queries = [&](int it, auto padded) {
+        f32x16 s, dp;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) { s[e] = 0.f; dp[e] = 0.f; }
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) {
+          const int at = it * 4096 + ra[kk];
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows(at, QO), kf[kk], s, 0, 0, 0);     // rows = queries, lane = key
+          dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(rows(at, QO + TILE), vf[kk], dp, 0, 0, 0);
         }
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          __builtin_amdgcn_sched_barrier(0);
+          if (padded && 32 * it + 16 * half >= T) continue;
+          float p[8], ds[8];
+#pragma unroll
+          for (int q4 = 0; q4 < 2; ++q4) {
+            const int q0 = 32 * it + 16 * half + 8 * q4 + 4 * hh;
+            const float4 l4 = *reinterpret_cast<const float4*>(Lsh + q0);
+            const float4 d4 = *reinterpret_cast<const float4*>(Dsh + q0);
+            const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dvv[4] = {d4.x, d4.y, d4.z, d4.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const int i = 8 * half + 4 * q4 + e;
+              float pe = __expf(s[i] * kScale - lv[e]);
+              if (padded && q0 + e >= T) pe = 0.f;
+              p[4 * q4 + e] = pe;
+              ds[4 * q4 + e] = pe * (dp[i] - dvv[e]);
+            }
+          }
+          const bf16x8 pf = pack8(p), dsf = pack8(ds);
+#pragma unroll
+          for (int dt = 0; dt < 2; ++dt) {
+            const char *lo = smem + (it * 4096 + ca[dt][0]), *hi = smem + (it * 4096 + ca[dt][1]);
+            dv[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_frag(lo + QO + TILE + 2048 * half, hi + QO + TILE + 2048 * half), pf, dv[dt], 0, 0, 0);
+            dk[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_frag(lo + QO + 2048 * half, hi + QO + 2048 * half), dsf, dk[dt], 0, 0, 0);
+          }
+        }
+      };
+#pragma unroll 1
+      for (int it = 0; it < whole; ++it) queries(it, std::false_type{});
+      if (whole < NKT) queries(whole, std::true_type{});
+      if (kj < T) {
+        store(gbase + (long)kj * ld + D, dk, kScale);
+        store(gbase + (long)kj * ld + 2 * D, dv, 1.f);
+      }
     }
   }
 }
@@ -412,11 +480,11 @@ int launch_fwd(hipStream_t s, const uint16_t* qkv, int B, int T, int H, uint16_t
 template <int NKT>
 int launch_bwd(hipStream_t s, const uint16_t* qkv, const uint16_t* out, const uint16_t* dout, const float* lse, int B,
                int T, int H, uint16_t* dqkv) {
-  constexpr int TP = 32 * NKT, RS = 2 * TP + 8;
-  const size_t lds = (size_t)4 * 64 * RS + 2 * TP * sizeof(float);   // 135 KB at T = 256
+  constexpr int lds = bwd_lds(NKT);
+  const int heads = B * H, grid = bwd_both(NKT) ? heads : 16 * ((heads + 7) / 8);
   static OncePerDevice once;
-  if (lds > 64 * 1024) PPLL_TRY(raise_lds((const void*)attn_bwd_mfma_kernel<NKT>, (int)lds, once));   // the same for every T of NKT
-  hipLaunchKernelGGL((attn_bwd_mfma_kernel<NKT>), dim3(B * H), dim3(64 * NKT), lds, s, qkv, out, dout, lse, T, H, dqkv);
+  if (lds > 64 * 1024) PPLL_TRY(raise_lds((const void*)attn_bwd_mfma_kernel<NKT>, lds, once));
+  hipLaunchKernelGGL((attn_bwd_mfma_kernel<NKT>), dim3(grid), dim3(64 * bwd_waves(NKT)), lds, s, qkv, out, dout, lse, T, H, heads, dqkv);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;
 }

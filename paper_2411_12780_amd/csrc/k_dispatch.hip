@@ -126,3 +126,15 @@ extern "C" int ppll_internal_product(int kernel, int M, int N, int K, const void
   set_error("kernel %d does not take this product", kernel);
   return PPLL_ERR_CONFIG;
 }
+
+// Attention on the matrix cores alone, bf16, head size 64, for tests (no part of the public interface): forward, then backward if dqkv
+// is given.  Refuses what that kernel does not take.
+extern "C" int ppll_internal_attention(int B, int T, int H, const void* qkv, void* out, float* lse, const void* dout, void* dqkv, void* stream) {
+  using namespace ppll;
+  if (!attention_mfma_supported(BF16, T, H, 64, qkv, out, dout, dqkv)) {
+    set_error("the matrix-core attention does not take %d tokens", T);
+    return PPLL_ERR_CONFIG;
+  }
+  PPLL_TRY(launch_attention_fwd_mfma((hipStream_t)stream, qkv, B, T, H, out, lse));
+  return dqkv ? launch_attention_bwd_mfma((hipStream_t)stream, qkv, out, dout, lse, B, T, H, dqkv) : PPLL_OK;
+}
