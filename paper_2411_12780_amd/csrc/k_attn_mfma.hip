@@ -1,6 +1,6 @@
 // Multi-head self-attention core for head dimension 64 in bf16 on the matrix
-// cores, forward and backward, one workgroup per (batch, head), one wave per
-// tile of 32 tokens (T <= 256).
+// cores, forward and backward, one workgroup per (batch, head) (of the backward
+// also two), a wave per tile of 32 tokens or per two (T <= 256).
 //
 // Layout trick.  v_mfma_f32_32x32x16_bf16 gives lane l column l%32 of the
 // 32 x 32 result and 16 of its rows (8*(e/4) + 4*(l/32) + e%4).  Scores are
@@ -13,15 +13,17 @@
 // so the first operand is fetched with the matching key order.  P and dS never
 // pass through memory.
 //
-// Forward: K passes through LDS as [token][64] rows of 128 bytes whose 16-byte granule index is XORed with (token/2)%8: the copy's
-// stores and the fragment reads (32 tokens x one granule per half wave) are then free of bank conflicts without padding.  V^T, whose
-// reduction index is the token, is transposed once per workgroup into a [64][T padded] array (8 bytes of padding per row) with an
-// in-register 4 x 8 transpose (v_perm_b32 on four 16-byte rows).
+// Operands whose reduction index is the token (V^T, K^T, Q^T, dO^T) come out of the [token][64] tiles by transposing reads.  All sums run
+// in a fixed order.  16 keys (queries) and more beyond the last token are left out of a last tile.
+//
+// Forward: K and V, 57 KB at 197 tokens, straight from memory to LDS.  What bounds it is memory and, above 160 tokens, the scores held
+// in registers: 7 waves of 160 are all of a unit.  Microseconds with both copied through registers and V transposed there -> now:
+// 128 images x 197 tokens x 12 heads 62 -> 45.5, 60 x 145 x 6 13.8 -> 8.9, 128 x 65 x 6 8.3 -> 6.4; with two tiles a wave, one after the
+// other, and two workgroups a unit 62, 8.8 and 6.5.
 //
 // Backward: one part (wave = query tile) forms P and dS with a lane per query and accumulates dQ; another (wave = key tile) forms them
 // again with a lane per key (scores recomputed in the other orientation instead of transposing registers) and accumulates dK and dV.
-// The first needs K and V of the head in LDS, the second Q and dO; the transposed operands come out of the same tiles by transposing
-// reads.  All sums run in a fixed order.
+// The first needs K and V of the head in LDS, the second Q and dO.
 // What bounds it is memory, each part waiting for its tiles and then storing them: 57 us of 143 at 128 x 197 tokens x 12 heads are
 // loads, 40 stores.  So the tiles, half of what they were with transposed copies beside them, leave room for two or three workgroups a
 // unit; up to 128 tokens one workgroup does both parts behind one barrier, all loads asked for at once, beyond that each part is a
@@ -50,147 +52,9 @@ __device__ __forceinline__ bf16x8 pack8(const float* v) {
   uint4 u = make_uint4(pack2(v[0], v[1]), pack2(v[2], v[3]), pack2(v[4], v[5]), pack2(v[6], v[7]));
   return __builtin_bit_cast(bf16x8, u);
 }
-// two 8-byte halves (tokens t..t+3 and t+8..t+11 of one row of a transposed matrix)
-__device__ __forceinline__ bf16x8 ld_tfrag(const char* row, int tok) {
-  uint2 a = *reinterpret_cast<const uint2*>(row + 2 * tok);
-  uint2 b = *reinterpret_cast<const uint2*>(row + 2 * tok + 16);
-  return __builtin_bit_cast(bf16x8, make_uint4(a.x, a.y, b.x, b.y));
-}
-
-// ---- [token][64] bf16 tiles in LDS, 128-byte rows, granule swizzle
-__device__ __forceinline__ int rm_off(int r, int g) { return r * 128 + ((g ^ ((r >> 1) & 7)) << 4); }
-__device__ __forceinline__ bf16x8 lds_frag(const char* rm, int r, int g) {
-  return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(rm + rm_off(r, g)));
-}
-// copies T rows of 64 bf16 (`ld` elements apart) into a tile of TP rows, zero beyond T
-template <int TP>
-__device__ __forceinline__ void stage_rows(const uint16_t* __restrict__ src, long ld, int T, char* rm, int tid) {
-  constexpr int NT = 2 * TP;   // threads of the workgroup
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int c = tid + NT * i, r = c >> 3, g = c & 7;
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (r < T) v = *reinterpret_cast<const uint4*>(src + (long)r * ld + 8 * g);
-    *reinterpret_cast<uint4*>(rm + rm_off(r, g)) = v;
-  }
-}
-__device__ __forceinline__ void write_transposed(const uint4* r, char* dst, int RS, int dc, int j0) {
-  const uint32_t* w0 = reinterpret_cast<const uint32_t*>(&r[0]);
-  const uint32_t* w1 = reinterpret_cast<const uint32_t*>(&r[1]);
-  const uint32_t* w2 = reinterpret_cast<const uint32_t*>(&r[2]);
-  const uint32_t* w3 = reinterpret_cast<const uint32_t*>(&r[3]);
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const uint32_t sel = (i & 1) ? 0x07060302u : 0x05040100u;
-    uint2 o;
-    o.x = __builtin_amdgcn_perm(w1[i >> 1], w0[i >> 1], sel);
-    o.y = __builtin_amdgcn_perm(w3[i >> 1], w2[i >> 1], sel);
-    *reinterpret_cast<uint2*>(dst + (8 * dc + i) * RS + 2 * j0) = o;
-  }
-}
-// global rows -> dst[64][TP], zero for tokens >= T
-template <int TP>
-__device__ __forceinline__ void transpose_to_lds(const uint16_t* __restrict__ src, long ld, int T, char* dst, int tid) {
-  const int jg = tid >> 3, dc = tid & 7, j0 = 4 * jg;
-  uint4 r[4];
-#pragma unroll
-  for (int jj = 0; jj < 4; ++jj) {
-    r[jj] = make_uint4(0, 0, 0, 0);
-    if (j0 + jj < T) r[jj] = *reinterpret_cast<const uint4*>(src + (long)(j0 + jj) * ld + 8 * dc);
-  }
-  write_transposed(r, dst, 2 * TP + 8, dc, j0);
-}
-
 constexpr float kScale = 0.125f;   // 1/sqrt(64)
 
-template <int NKT>
-__global__ __launch_bounds__(64 * NKT) void attn_fwd_mfma_kernel(const uint16_t* __restrict__ qkv, int T, int H,
-                                                                 uint16_t* __restrict__ out,
-                                                                 float* __restrict__ lse_out) {
-  constexpr int TP = 32 * NKT, RS = 2 * TP + 8;
-  extern __shared__ __align__(1024) char smem[];
-  char* vt = smem;              // V^T [64][TP]
-  char* krm = smem + 64 * RS;   // K   [TP][64]
-  const int b = blockIdx.x / H, h = blockIdx.x % H, D = 64 * H;
-  const long ld = 3L * D;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 31, hh = lane >> 5;
-  const uint16_t* base = qkv + (size_t)b * T * ld + h * 64;
-  const int qi = 32 * wave + li;
-  bf16x8 qf[4];   // a wave's own queries: read once, straight from global memory, in flight with the copies below
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) qf[kk] = ld_frag(base + (long)qi * ld + 16 * kk + 8 * hh, qi < T);
-  transpose_to_lds<TP>(base + 2 * D, ld, T, vt, tid);
-  stage_rows<TP>(base + D, ld, T, krm, tid);
-  __syncthreads();
-  f32x16 s[NKT];
-#pragma unroll
-  for (int jt = 0; jt < NKT; ++jt) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) s[jt][e] = 0.f;
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const bf16x8 kf = lds_frag(krm, 32 * jt + li, 2 * kk + hh);
-      s[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[kk], s[jt], 0, 0, 0);
-    }
-  }
-  // softmax over the keys of query qi: s[jt][e] belongs to key 32*jt + 8*(e/4) + 4*hh + e%4
-  float mx = -INFINITY;
-#pragma unroll
-  for (int jt = 0; jt < NKT; ++jt)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int key = 32 * jt + 8 * (e >> 2) + 4 * hh + (e & 3);
-      const float v = key < T ? s[jt][e] * kScale : -INFINITY;
-      s[jt][e] = v;
-      mx = fmaxf(mx, v);
-    }
-  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-  float sum = 0.f;
-#pragma unroll
-  for (int jt = 0; jt < NKT; ++jt)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const float p = __expf(s[jt][e] - mx);
-      s[jt][e] = p;
-      sum += p;
-    }
-  sum += __shfl_xor(sum, 32, 64);
-  const float inv = 1.0f / sum;
-
-  f32x16 o[2];
-#pragma unroll
-  for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) o[dt][e] = 0.f;
-#pragma unroll
-  for (int jt = 0; jt < NKT; ++jt)
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      float pv[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) pv[e] = s[jt][8 * half + e] * inv;
-      const bf16x8 pf = pack8(pv);
-      const int tok = 32 * jt + 16 * half + 4 * hh;
-#pragma unroll
-      for (int dt = 0; dt < 2; ++dt) {
-        const bf16x8 vf = ld_tfrag(vt + (32 * dt + li) * RS, tok);
-        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf, o[dt], 0, 0, 0);
-      }
-    }
-  if (qi < T) {
-    uint16_t* orow = out + ((size_t)b * T + qi) * D + h * 64;
-#pragma unroll
-    for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        uint2 w = make_uint2(pack2(o[dt][4 * q], o[dt][4 * q + 1]), pack2(o[dt][4 * q + 2], o[dt][4 * q + 3]));
-        *reinterpret_cast<uint2*>(orow + 32 * dt + 8 * q + 4 * hh) = w;
-      }
-    if (hh == 0) lse_out[((size_t)b * H + h) * T + qi] = mx + __logf(sum);
-  }
-}
-
-// ---- Backward tiles: [token][64] bf16, 128-byte rows, the 16-byte granule g of row r at g ^ turn(r).  The fragment reads (16 rows x one
+// ---- Tiles in LDS: [token][64] bf16, 128-byte rows, the 16-byte granule g of row r at g ^ turn(r).  The fragment reads (16 rows x one
 // granule at a time) and the transposing reads (4 rows x 64 bytes, rows r and r + 2 in different halves of the banks) both spread
 // over all banks.
 __device__ __forceinline__ int turn(int r) { return ((r & 2) << 1) | ((r >> 2) & 3); }
@@ -224,6 +88,115 @@ __device__ __forceinline__ float dot8(uint4 a, uint4 b) {
   for (int w = 0; w < 4; ++w)
     d += __uint_as_float(x[w] << 16) * __uint_as_float(y[w] << 16) + __uint_as_float(x[w] & 0xffff0000u) * __uint_as_float(y[w] & 0xffff0000u);
   return d;
+}
+
+// A lane holds 4 consecutive columns of a row of results, its partner in the other half of the wave the next 4: they trade, and store
+// 16 bytes each.
+__device__ __forceinline__ void store_row(uint16_t* row, const f32x16 (&v)[2], float scale, int hh) {
+#pragma unroll
+  for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+    for (int q = 0; q < 4; q += 2) {
+      const auto lo = __builtin_amdgcn_permlane32_swap(pack2(v[dt][4 * q] * scale, v[dt][4 * q + 1] * scale),
+                                                       pack2(v[dt][4 * q + 4] * scale, v[dt][4 * q + 5] * scale), false, false);
+      const auto hi = __builtin_amdgcn_permlane32_swap(pack2(v[dt][4 * q + 2] * scale, v[dt][4 * q + 3] * scale),
+                                                       pack2(v[dt][4 * q + 6] * scale, v[dt][4 * q + 7] * scale), false, false);
+      *reinterpret_cast<uint4*>(row + 32 * dt + 8 * (q + hh)) = make_uint4(lo[0], hi[0], lo[1], hi[1]);
+    }
+}
+
+// Waves a SIMD: as many as the scores of a query, 16 registers a tile, let in beside the rest
+constexpr int fwd_waves_per_simd(int nkt) { return nkt <= 3 ? 4 : nkt <= 5 ? 3 : 2; }
+
+template <int NKT>
+__global__ __launch_bounds__(64 * NKT, fwd_waves_per_simd(NKT)) void attn_fwd_mfma_kernel(const uint16_t* __restrict__ qkv, int T, int H,
+                                                                            uint16_t* __restrict__ out, float* __restrict__ lse_out) {
+  constexpr int TP = 32 * NKT, TILE = TP * 128;
+  extern __shared__ __align__(1024) char smem[];      // K, V
+  const int b = blockIdx.x / H, h = blockIdx.x % H, D = 64 * H;
+  const long ld = 3L * D;
+  const int lane = threadIdx.x & 63, li = lane & 31, hh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint16_t* base = qkv + (size_t)b * T * ld + h * 64;
+  const __amdgpu_buffer_rsrc_t rs = pipe::make_rsrc(qkv + (size_t)b * T * ld, (uint32_t)(T * ld * 2));
+  pipe::lds_char* lds = (pipe::lds_char*)smem;
+  copy_rows<TP, NKT>(rs, (h * 64 + D) * 2, (int)ld * 2, T, lds, wave, lane);
+  copy_rows<TP, NKT>(rs, (h * 64 + 2 * D) * 2, (int)ld * 2, T, lds + TILE, wave, lane);
+  int ra[4], ca[2][2];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) ra[kk] = row_addr(lane, kk);
+#pragma unroll
+  for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+    for (int hi = 0; hi < 2; ++hi) ca[dt][hi] = col_addr(lane, dt, hi);
+  const int qi = 32 * wave + li;
+  bf16x8 qf[4];   // a wave's own queries: read once, straight from memory, in flight with the copies
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) qf[kk] = ld_frag(base + (long)qi * ld + 16 * kk + 8 * hh, qi < T);
+  pipe::wait_vm<0>();
+  __syncthreads();
+  const bool padded = T < TP, last_half = T > TP - 16;   // of the last tile: 16 keys and more beyond the last token are left out
+  f32x16 s[NKT];
+#pragma unroll
+  for (int jt = 0; jt < NKT; ++jt) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) s[jt][e] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+      s[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(smem + ra[kk] + 4096 * jt), qf[kk], s[jt], 0, 0, 0);
+  }
+  // softmax over the keys of query qi: s[jt][e] belongs to key 32 jt + 8 (e / 4) + 4 hh + e % 4
+  if (padded) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e)
+      if (32 * (NKT - 1) + 8 * (e >> 2) + 4 * hh + (e & 3) >= T) s[NKT - 1][e] = -INFINITY;
+  }
+  float mx = -INFINITY;
+#pragma unroll
+  for (int jt = 0; jt < NKT; ++jt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[jt][e]);
+  mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * kScale;
+  float sum = 0.f;
+#pragma unroll
+  for (int jt = 0; jt < NKT; ++jt)
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      if (jt == NKT - 1 && half && !last_half) continue;
+#pragma unroll
+      for (int e = 8 * half; e < 8 * half + 8; ++e) {
+        const float p = __expf(s[jt][e] * kScale - mx);
+        s[jt][e] = p;
+        sum += p;
+      }
+    }
+  sum += __shfl_xor(sum, 32, 64);
+  const float inv = 1.0f / sum;
+
+  f32x16 o[2];
+#pragma unroll
+  for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) o[dt][e] = 0.f;
+#pragma unroll
+  for (int jt = 0; jt < NKT; ++jt)
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      if (jt == NKT - 1 && half && !last_half) continue;
+      float pv[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) pv[e] = s[jt][8 * half + e] * inv;
+      const bf16x8 pf = pack8(pv);
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt) {
+        const int at = TILE + 4096 * jt + 2048 * half;
+        o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_frag(smem + ca[dt][0] + at, smem + ca[dt][1] + at), pf, o[dt], 0, 0, 0);
+      }
+    }
+  if (qi < T) {
+    store_row(out + ((size_t)b * T + qi) * D + h * 64, o, 1.f, hh);
+    if (hh == 0) lse_out[((size_t)b * H + h) * T + qi] = mx + __logf(sum);
+  }
 }
 
 // Waves of a backward workgroup, each with one tile of 32 tokens, from five tiles on with two: 60 images x 145 tokens x 6 heads 29 us,
@@ -268,19 +241,6 @@ __global__ __launch_bounds__(64 * bwd_waves(NKT), bwd_waves_per_simd(NKT)) void 
 #pragma unroll
     for (int hi = 0; hi < 2; ++hi) ca[dt][hi] = col_addr(lane, dt, hi);
   auto rows = [&](int at, int tile) { return *reinterpret_cast<const bf16x8*>(smem + at + tile); };
-  // a lane holds 4 consecutive columns of a row, its partner in the other half of the wave the next 4: they trade, and store 16 bytes
-  auto store = [&](uint16_t* row, const f32x16 (&v)[2], float scale) {
-#pragma unroll
-    for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-      for (int q = 0; q < 4; q += 2) {
-        const auto lo = __builtin_amdgcn_permlane32_swap(pack2(v[dt][4 * q] * scale, v[dt][4 * q + 1] * scale),
-                                                         pack2(v[dt][4 * q + 4] * scale, v[dt][4 * q + 5] * scale), false, false);
-        const auto hi = __builtin_amdgcn_permlane32_swap(pack2(v[dt][4 * q + 2] * scale, v[dt][4 * q + 3] * scale),
-                                                         pack2(v[dt][4 * q + 6] * scale, v[dt][4 * q + 7] * scale), false, false);
-        *reinterpret_cast<uint4*>(row + 32 * dt + 8 * (q + hh)) = make_uint4(lo[0], hi[0], lo[1], hi[1]);
-      }
-  };
   const int whole = T >> 5;   // tiles without padding
 
   if (do_queries) {
@@ -380,7 +340,7 @@ __global__ __launch_bounds__(64 * bwd_waves(NKT), bwd_waves_per_simd(NKT)) void 
 #pragma unroll 1
       for (int jt = 0; jt < whole; ++jt) keys(jt, std::false_type{});
       if (whole < NKT) keys(whole, std::true_type{});
-      if (ok) store(gbase + (long)qi * ld, dq, kScale);
+      if (ok) store_row(gbase + (long)qi * ld, dq, kScale, hh);
     }
   }
 
@@ -447,8 +407,8 @@ __global__ __launch_bounds__(64 * bwd_waves(NKT), bwd_waves_per_simd(NKT)) void 
       for (int it = 0; it < whole; ++it) queries(it, std::false_type{});
       if (whole < NKT) queries(whole, std::true_type{});
       if (kj < T) {
-        store(gbase + (long)kj * ld + D, dk, kScale);
-        store(gbase + (long)kj * ld + 2 * D, dv, 1.f);
+        store_row(gbase + (long)kj * ld + D, dk, kScale, hh);
+        store_row(gbase + (long)kj * ld + 2 * D, dv, 1.f, hh);
       }
     }
   }
@@ -468,10 +428,7 @@ __global__ __launch_bounds__(64 * bwd_waves(NKT), bwd_waves_per_simd(NKT)) void 
 
 template <int NKT>
 int launch_fwd(hipStream_t s, const uint16_t* qkv, int B, int T, int H, uint16_t* out, float* lse) {
-  constexpr int TP = 32 * NKT, RS = 2 * TP + 8;
-  const size_t lds = (size_t)64 * RS + (size_t)TP * 128;
-  static OncePerDevice once;
-  if (lds > 64 * 1024) PPLL_TRY(raise_lds((const void*)attn_fwd_mfma_kernel<NKT>, (int)lds, once));   // the same for every T of NKT
+  constexpr int lds = 2 * 4096 * NKT;   // 64 KB at T = 256
   hipLaunchKernelGGL((attn_fwd_mfma_kernel<NKT>), dim3(B * H), dim3(64 * NKT), lds, s, qkv, T, H, out, lse);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;
