@@ -138,3 +138,11 @@ extern "C" int ppll_internal_attention(int B, int T, int H, const void* qkv, voi
   PPLL_TRY(launch_attention_fwd_mfma((hipStream_t)stream, qkv, B, T, H, out, lse));
   return dqkv ? launch_attention_bwd_mfma((hipStream_t)stream, qkv, out, dout, lse, B, T, H, dqkv) : PPLL_OK;
 }
+
+// Attention of the class token's query, as the dispatch takes it, bf16, for tests (no part of the public interface)
+extern "C" int ppll_internal_attention_cls(int B, int T, int H, int dh, const void* q, const void* kv, void* out, float* prob, const void* dout,
+                                           void* dq, void* dkv, void* stream) {
+  using namespace ppll;
+  PPLL_TRY(launch_attention_cls_fwd((hipStream_t)stream, q, kv, BF16, B, T, H, dh, out, prob));
+  return launch_attention_cls_bwd((hipStream_t)stream, q, kv, prob, dout, BF16, B, T, H, dh, dq, dkv);
+}

@@ -71,3 +71,50 @@ def test_scores_far_from_zero(T):
     status, out, lse, dqkv = attention(2, T, 1, qkv, dout)
     assert status == 0 and bool(torch.isfinite(out.float()).all()) and bool(torch.isfinite(dqkv.float()).all())
     assert float(lse[:2 * T].max()) < -1000.0
+
+
+@pytest.mark.parametrize("T,H,dh", [(t, 2, 64) for t in (1, 5, 8, 9, 31, 32, 33, 64, 65, 96, 97, 145, 161, 197, 224, 225, 256)] + [(17, 3, 32), (256, 2, 48), (65, 1, 64)])
+def test_attention_of_the_class_token(T, H, dh):
+    # edges of the 32 rows a pass, up to the 256 tokens that a block takes; other heads are for the general kernels
+    B, D = 3, H * dh
+    g = torch.Generator(device="cuda").manual_seed(1000 * T + D)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    q, kv, dout = rnd(B, D), rnd(B, T, 2 * D), rnd(B, D)
+    f = P.lib().ppll_internal_attention_cls
+    f.restype = ctypes.c_int
+    f.argtypes = [ctypes.c_int] * 4 + [ctypes.c_void_p] * 8
+
+    def run():
+        bufs = [torch.full((n + GUARD,), 7.0, dtype=t, device="cuda")
+                for n, t in ((B * D, torch.bfloat16), (B * H * T, torch.float32), (B * D, torch.bfloat16), (B * T * 2 * D, torch.bfloat16))]
+        out, prob, dq, dkv = bufs
+        status = f(B, T, H, dh, q.data_ptr(), kv.data_ptr(), out.data_ptr(), prob.data_ptr(), dout.data_ptr(), dq.data_ptr(), dkv.data_ptr(),
+                   torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert status == 0
+        return bufs
+
+    bufs = run()
+    sizes = (B * D, B * H * T, B * D, B * T * 2 * D)
+    for t, n in zip(bufs, sizes):
+        assert bool((t[n:] == 7.0).all())
+    out, prob, dq, dkv = (t[:n].double() for t, n in zip(bufs, sizes))
+    k, v = (t.reshape(B, T, H, dh).double() for t in kv.split(D, dim=2))
+    qd, dod = q.view(B, 1, H, dh).double(), dout.view(B, 1, H, dh).double()
+    s = (qd * k).sum(-1) / dh ** 0.5                            # [B, T, H]
+    p = torch.softmax(s, 1)
+    dp = (dod * v).sum(-1)
+    delta = (p * dp).sum(1, keepdim=True)
+    ds = p * (dp - delta)
+    # every result is rounded to bf16 once; all else is fp32, with exponents and sums of 64 terms good to 2^-18 of the magnitudes
+    mag = (p * dp.abs()).sum(1, keepdim=True) + (dod.abs() * v.abs()).sum(-1)
+    eps = 2.0 ** -18 * (1 + (qd.abs() * k.abs()).sum(-1).max().item() / 16)
+    ps, dss = p[..., None], ds[..., None]
+    want = {"out": (out.view(B, H, dh), (ps * v).sum(1), (ps * v.abs()).sum(1)),
+            "dq": (dq.view(B, H, dh), (dss * k).sum(1) / dh ** 0.5, ((p * mag)[..., None] * k.abs()).sum(1) / dh ** 0.5),
+            "dk": (dkv.view(B, T, 2, H, dh)[:, :, 0], dss * qd / dh ** 0.5, (p * mag)[..., None] * qd.abs() / dh ** 0.5),
+            "dv": (dkv.view(B, T, 2, H, dh)[:, :, 1], ps * dod, ps * dod.abs())}
+    for name, (got, ref, size) in want.items():
+        assert bool(((got - ref).abs() <= 2.0 ** -8 * ref.abs() + eps * size + 1e-30).all()), name
+    assert bool(((prob.view(B, H, T).transpose(1, 2) - p).abs() <= eps * p + 1e-30).all())
+    assert all(torch.equal(x, y) for x, y in zip(bufs, run()))
