@@ -7,13 +7,15 @@
 //              dk_j = ds_j q / sqrt(dh),  dv_j = p_j do
 // Layouts: q, o, dq, do are [B, H*dh]; kv and dkv are [B*T, 2*H*dh] with the keys in the first H*dh columns.
 //
-// Keys and values are read once and what bounds this is memory, so for bf16 heads of 64 they stay in registers as they were loaded
-// (attn_cls64_*): eight lanes hold a row of 64, a workgroup 32 rows a pass, all passes (up to 256 tokens) in flight at once, and LDS
-// carries only sums between the waves.  The general kernels stage both as fp32 in LDS: 103 KB at 197 tokens, one workgroup a unit
-// whose loads nothing covers, and a thread per row or column then walks it alone.
-// Microseconds in a step, general kernel -> this one: 128 images x 197 tokens x 12 heads forward 53.9 -> 15.9 (77 MB), backward
-// 67.1 -> 25.2 (155 MB), 64 x 145 x 6 8.8 -> 6.6 and 11.4 -> 7.2, 128 x 65 x 6 7.7 -> 5.8 and 10.0 -> 6.4.
+// What bounds this is memory: keys and values are read once.  For bf16 heads of 64 (attn_cls64_*) they lie in LDS as bf16, copied
+// straight from memory, 50 KB at 197 tokens: three workgroups a unit, one loading while another multiplies.  The general kernels stage
+// both as fp32 through registers: 103 KB, one workgroup a unit whose loads nothing covers.  Sums run in the same order in both.
+// Microseconds in a step, general kernel -> this one: 128 images x 197 tokens x 12 heads forward 53.9 -> 21.1 (77 MB), backward
+// 67.1 -> 34.3 (155 MB), 64 x 145 x 6 8.8 -> 7.5 and 11.4 -> 8.2, 128 x 65 x 6 7.7 -> 6.0 and 10.0 -> 7.0.  K and V in registers, eight
+// lanes a row, sum in another order and take 15.9, 25.2, 6.6, 7.2, 5.8 and 6.4: 1 % of a step at 197 tokens, for gradients that
+// differ in single values by their size.
 #include "common.h"
+#include "gemm_pipe.h"
 
 namespace ppll {
 
@@ -171,191 +173,107 @@ __global__ __launch_bounds__(CLS_THREADS) void attn_cls_bwd_kernel(const void* q
 }
 
 
-// ---- bf16, heads of 64, at most 256 tokens: row j of K and V at pass j / 32, wave j / 8 % 4, lanes 8 (j % 8) .. + 7
-__device__ __forceinline__ void unpack8(const uint4& w, float (&v)[8]) {
-  const uint32_t u[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-  for (int i = 0; i < 4; ++i) { v[2 * i] = __uint_as_float(u[i] << 16); v[2 * i + 1] = __uint_as_float(u[i] & 0xffff0000u); }
+// ---- bf16, heads of 64, at most 256 tokens.  Tiles in LDS: [token][64] bf16, 128-byte rows, the 16-byte granule g of row r at
+// g ^ turn(r): lanes on consecutive rows and lanes along a row both spread over all banks.
+constexpr int CLS64_TOKENS = CLS_THREADS;   // a thread per token
+__device__ __forceinline__ int turn(int r) { return (r >> 1) & 7; }
+__host__ __device__ inline int cls64_tile(int T) { return (T + 7) / 8 * 1024; }
+// K and V of a head, zeros beyond T; there after the next barrier
+__device__ __forceinline__ void copy_head(const uint16_t* kv, int b, int h, int T, int D, int tid, char* k, char* v) {
+  const __amdgpu_buffer_rsrc_t rs = pipe::make_rsrc(kv + (size_t)b * T * 2 * D, (uint32_t)T * 4u * (uint32_t)D);
+  const int lane = tid & 63, g = lane & 7;
+  for (int t = __builtin_amdgcn_readfirstlane(tid >> 6); t * 8 < T; t += CLS_THREADS / 64) {
+    const int r = t * 8 + (lane >> 3), off = r * 4 * D + h * 128 + ((g ^ turn(r)) << 4);
+    pipe::load_to_lds(rs, (pipe::lds_char*)k + t * 1024, r < T ? off : pipe::OOB);
+    pipe::load_to_lds(rs, (pipe::lds_char*)v + t * 1024, r < T ? off + 2 * D : pipe::OOB);
+  }
 }
-__device__ __forceinline__ uint4 scaled8(const float (&v)[8], float a) {
+// <a, row r>, column by column
+__device__ __forceinline__ float row_dot(const char* tile, int r, const float* a) {
+  float s = 0.f;
+#pragma unroll
+  for (int g = 0; g < 8; ++g) {
+    const uint4 w = *reinterpret_cast<const uint4*>(tile + r * 128 + ((g ^ turn(r)) << 4));
+    const uint32_t u[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      s = fmaf(a[8 * g + 2 * e], __uint_as_float(u[e] << 16), s);
+      s = fmaf(a[8 * g + 2 * e + 1], __uint_as_float(u[e] & 0xffff0000u), s);
+    }
+  }
+  return s;
+}
+// sum of w_r row r at column d, row by row
+__device__ __forceinline__ float column_sum(const char* tile, int d, const float* w, int T) {
+  float s = 0.f;
+#pragma unroll 8
+  for (int r = 0; r < T; ++r)
+    s = fmaf(w[r], bf16_to_f32(*reinterpret_cast<const uint16_t*>(tile + r * 128 + (((d >> 3) ^ turn(r)) << 4) + 2 * (d & 7))), s);
+  return s;
+}
+__device__ __forceinline__ uint4 scaled8(const float* v, float a) {
   return make_uint4(f32x2_to_bf16x2(a * v[0], a * v[1]), f32x2_to_bf16x2(a * v[2], a * v[3]), f32x2_to_bf16x2(a * v[4], a * v[5]),
                     f32x2_to_bf16x2(a * v[6], a * v[7]));
 }
-// <a, row> over the eight lanes of the row
-__device__ __forceinline__ float row_dot(const float (&a)[8], const uint4& row) {
-  float v[8], s = 0.f;
-  unpack8(row, v);
-#pragma unroll
-  for (int e = 0; e < 8; ++e) s = fmaf(a[e], v[e], s);
-#pragma unroll
-  for (int o = 4; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-  return s;
-}
-// sum over the eight rows of a wave of a value that the lanes of a row share
-__device__ __forceinline__ float rows_sum(float v) {
-#pragma unroll
-  for (int o = 32; o >= 8; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-// Sums over the eight rows of a wave of the 8 columns a lane holds: a lane gives away half of what it has at each step and ends with
-// the column that column_of names.
-__device__ __forceinline__ int column_of(int lane) { return 8 * (lane & 7) + 4 * (lane >> 5) + 2 * ((lane >> 4) & 1) + ((lane >> 3) & 1); }
-__device__ __forceinline__ float columns_sum(const float (&v)[8], int lane) {
-  float a[4], b[2];
-  bool up = lane & 32;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) a[e] = (up ? v[4 + e] : v[e]) + __shfl_xor(up ? v[e] : v[4 + e], 32, 64);
-  up = lane & 16;
-#pragma unroll
-  for (int e = 0; e < 2; ++e) b[e] = (up ? a[2 + e] : a[e]) + __shfl_xor(up ? a[e] : a[2 + e], 16, 64);
-  up = lane & 8;
-  return (up ? b[1] : b[0]) + __shfl_xor(up ? b[0] : b[1], 8, 64);
-}
-constexpr int CLS64_TOKENS = 256, CLS64_WAVES = CLS_THREADS / 64;
 
-template <int NP>
 __global__ __launch_bounds__(CLS_THREADS) void attn_cls64_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ kv, int T,
                                                                      int H, uint16_t* __restrict__ out, float* __restrict__ prob) {
-  __shared__ float tops[CLS64_WAVES], sums[CLS64_WAVES], part[CLS64_WAVES][64];
-  const int b = blockIdx.x / H, h = blockIdx.x % H, D = H * 64, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int row0 = tid >> 3, c = 8 * (lane & 7);
-  const uint16_t* base = kv + (size_t)b * T * 2 * D + h * 64 + c;
-  uint4 k[NP], v[NP];
-#pragma unroll
-  for (int i = 0; i < NP; ++i) {
-    const int j = 32 * i + row0;
-    k[i] = j < T ? *reinterpret_cast<const uint4*>(base + (size_t)j * 2 * D) : make_uint4(0, 0, 0, 0);
-  }
-#pragma unroll
-  for (int i = 0; i < NP; ++i) {
-    const int j = 32 * i + row0;
-    v[i] = j < T ? *reinterpret_cast<const uint4*>(base + (size_t)j * 2 * D + D) : make_uint4(0, 0, 0, 0);
-  }
-  float qv[8];
-  unpack8(*reinterpret_cast<const uint4*>(q + (size_t)b * D + h * 64 + c), qv);
-#pragma unroll
-  for (int e = 0; e < 8; ++e) qv[e] *= 0.125f;   // 1 / sqrt(64)
-  float p[NP], mx = -INFINITY;
-#pragma unroll
-  for (int i = 0; i < NP; ++i) {
-    p[i] = row_dot(qv, k[i]);
-    if (32 * i + row0 >= T) p[i] = -INFINITY;
-    mx = fmaxf(mx, p[i]);
-  }
-#pragma unroll
-  for (int o = 32; o >= 8; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
-  if (lane == 0) tops[wave] = mx;
+  extern __shared__ __align__(1024) char tiles[];      // K, V
+  __shared__ __align__(16) float qs[64], ps[CLS64_TOKENS], red[CLS_THREADS / 64];
+  const int b = blockIdx.x / H, h = blockIdx.x % H, D = H * 64, tid = threadIdx.x;
+  char *K = tiles, *V = tiles + cls64_tile(T);
+  copy_head(kv, b, h, T, D, tid, K, V);
+  if (tid < 64) qs[tid] = bf16_to_f32(q[(size_t)b * D + h * 64 + tid]) * 0.125f;   // 1 / sqrt(64)
+  pipe::wait_vm<0>();
   __syncthreads();
-  mx = tops[0];
-#pragma unroll
-  for (int w = 1; w < CLS64_WAVES; ++w) mx = fmaxf(mx, tops[w]);
-  float acc[8] = {}, sum = 0.f;
-#pragma unroll
-  for (int i = 0; i < NP; ++i) {
-    p[i] = 32 * i + row0 < T ? __expf(p[i] - mx) : 0.f;
-    sum += p[i];
-    float x[8];
-    unpack8(v[i], x);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = fmaf(p[i], x[e], acc[e]);
-  }
-  sum = rows_sum(sum);
-  if (lane == 0) sums[wave] = sum;
-  part[wave][column_of(lane)] = columns_sum(acc, lane);
+  const float sc = tid < T ? row_dot(K, tid, qs) : -INFINITY;
+  const float mx = block_max(sc, red, tid);
+  const float e = tid < T ? __expf(sc - mx) : 0.f;
+  const float sum = block_sum(e, red, tid);
+  if (tid < T) { const float p = e / sum; ps[tid] = p; prob[(size_t)blockIdx.x * T + tid] = p; }
   __syncthreads();
-  sum = 0.f;
-#pragma unroll
-  for (int w = 0; w < CLS64_WAVES; ++w) sum += sums[w];
-  if ((lane & 7) == 0) {
-#pragma unroll
-    for (int i = 0; i < NP; ++i)
-      if (32 * i + row0 < T) prob[(size_t)blockIdx.x * T + 32 * i + row0] = p[i] / sum;
-  }
-  if (wave == 0) {
-    float o = 0.f;
-#pragma unroll
-    for (int w = 0; w < CLS64_WAVES; ++w) o += part[w][lane];
-    out[(size_t)b * D + h * 64 + lane] = f32_to_bf16(o / sum);
-  }
+  if (tid < 64) out[(size_t)b * D + h * 64 + tid] = f32_to_bf16(column_sum(V, tid, ps, T));
 }
 
-template <int NP>
 __global__ __launch_bounds__(CLS_THREADS) void attn_cls64_bwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ kv,
                                                                      const float* __restrict__ prob, const uint16_t* __restrict__ dout, int T,
                                                                      int H, uint16_t* __restrict__ dq, uint16_t* __restrict__ dkv) {
-  __shared__ float sums[CLS64_WAVES], part[CLS64_WAVES][64];
-  const int b = blockIdx.x / H, h = blockIdx.x % H, D = H * 64, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int row0 = tid >> 3, c = 8 * (lane & 7);
-  const size_t first = (size_t)b * T * 2 * D + h * 64 + c, head = (size_t)b * D + h * 64;
-  uint4 k[NP], v[NP];
-  float p[NP], dp[NP];
-#pragma unroll
-  for (int i = 0; i < NP; ++i) {
-    const int j = 32 * i + row0;
-    v[i] = j < T ? *reinterpret_cast<const uint4*>(kv + first + (size_t)j * 2 * D + D) : make_uint4(0, 0, 0, 0);
-    p[i] = j < T ? prob[(size_t)blockIdx.x * T + j] : 0.f;
-  }
-#pragma unroll
-  for (int i = 0; i < NP; ++i) {
-    const int j = 32 * i + row0;
-    k[i] = j < T ? *reinterpret_cast<const uint4*>(kv + first + (size_t)j * 2 * D) : make_uint4(0, 0, 0, 0);
-  }
-  float qv[8], dov[8], delta = 0.f;
-  unpack8(*reinterpret_cast<const uint4*>(q + head + c), qv);
-  unpack8(*reinterpret_cast<const uint4*>(dout + head + c), dov);
-#pragma unroll
-  for (int e = 0; e < 8; ++e) qv[e] *= 0.125f;   // 1 / sqrt(64)
-#pragma unroll
-  for (int i = 0; i < NP; ++i) {
-    dp[i] = row_dot(dov, v[i]);
-    delta = fmaf(p[i], dp[i], delta);
-  }
-  delta = rows_sum(delta);
-  if (lane == 0) sums[wave] = delta;
+  extern __shared__ __align__(1024) char tiles[];      // K, V
+  __shared__ __align__(16) float qs[64], dos[64], ps[CLS64_TOKENS], ds[CLS64_TOKENS], red[CLS_THREADS / 64];
+  const int b = blockIdx.x / H, h = blockIdx.x % H, D = H * 64, tid = threadIdx.x;
+  char *K = tiles, *V = tiles + cls64_tile(T);
+  copy_head(kv, b, h, T, D, tid, K, V);
+  const size_t head = (size_t)b * D + h * 64;
+  if (tid < 64) { dos[tid] = bf16_to_f32(dout[head + tid]); qs[tid] = bf16_to_f32(q[head + tid]) * 0.125f; }   // 1 / sqrt(64)
+  const float p = tid < T ? prob[(size_t)blockIdx.x * T + tid] : 0.f;
+  pipe::wait_vm<0>();
   __syncthreads();
-  delta = 0.f;
-#pragma unroll
-  for (int w = 0; w < CLS64_WAVES; ++w) delta += sums[w];
-  float acc[8] = {};
-#pragma unroll
-  for (int i = 0; i < NP; ++i) {
-    const int j = 32 * i + row0;
-    const float ds = p[i] * (dp[i] - delta);
-    float x[8];
-    unpack8(k[i], x);
-    if (j < T) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] = fmaf(ds, x[e], acc[e]);
-      *reinterpret_cast<uint4*>(dkv + first + (size_t)j * 2 * D) = scaled8(qv, ds);
-      *reinterpret_cast<uint4*>(dkv + first + (size_t)j * 2 * D + D) = scaled8(dov, p[i]);
-    }
-  }
-  part[wave][column_of(lane)] = columns_sum(acc, lane);
+  const float dp = tid < T ? row_dot(V, tid, dos) : 0.f;
+  const float delta = block_dot(p, dp, red, tid);
+  if (tid < T) { ps[tid] = p; ds[tid] = p * (dp - delta); }
   __syncthreads();
-  if (wave == 0) {
-    float o = 0.f;
+  if (tid < 64) {              // one wave sums up dq while the others store dk and dv
+    dq[head + tid] = f32_to_bf16(column_sum(K, tid, ds, T) * 0.125f);
+    return;
+  }
+  const int c = 8 * (tid & 7);
+  float qv[8], dov[8];
 #pragma unroll
-    for (int w = 0; w < CLS64_WAVES; ++w) o += part[w][lane];
-    dq[head + lane] = f32_to_bf16(o * 0.125f);
+  for (int e = 0; e < 8; ++e) { qv[e] = qs[c + e]; dov[e] = dos[c + e]; }
+  uint16_t* o = dkv + (size_t)b * T * 2 * D + h * 64 + c;
+#pragma unroll 4
+  for (int j = (tid - 64) >> 3; j < T; j += (CLS_THREADS - 64) / 8) {
+    *reinterpret_cast<uint4*>(o + (size_t)j * 2 * D) = scaled8(qv, ds[j]);
+    *reinterpret_cast<uint4*>(o + (size_t)j * 2 * D + D) = scaled8(dov, ps[j]);
   }
 }
 
-// bf16, heads of 64 at 16-byte aligned addresses, all tokens that a block takes (256: 88 registers hold K, V, p and dp)
-bool cls64_ok(int dt, int T, int H, int dh, const void* a, const void* b, const void* c, const void* d) {
-  return dt == BF16 && dh == 64 && T >= 1 && T <= CLS64_TOKENS && H >= 1 &&
-         !((((uintptr_t)a) | ((uintptr_t)b) | ((uintptr_t)c) | ((uintptr_t)d)) & 15);
+// bf16, heads of 64 at 16-byte aligned addresses, all tokens that a block takes
+bool cls64_ok(int dt, int T, int H, int dh, const void* a, const void* b) {
+  return dt == BF16 && dh == 64 && T >= 1 && T <= CLS64_TOKENS && H >= 1 && (long)T * 256 * H < 0x7fffffffL &&
+         !((((uintptr_t)a) | ((uintptr_t)b)) & 15);
 }
-#define CLS64_LAUNCH(KERNEL, ...)                                                                            \
-  switch ((T + 31) / 32) {                                                                                   \
-    case 1: hipLaunchKernelGGL(KERNEL<1>, dim3(B * H), dim3(CLS_THREADS), 0, s, __VA_ARGS__); break;         \
-    case 2: hipLaunchKernelGGL(KERNEL<2>, dim3(B * H), dim3(CLS_THREADS), 0, s, __VA_ARGS__); break;         \
-    case 3: hipLaunchKernelGGL(KERNEL<3>, dim3(B * H), dim3(CLS_THREADS), 0, s, __VA_ARGS__); break;         \
-    case 4: hipLaunchKernelGGL(KERNEL<4>, dim3(B * H), dim3(CLS_THREADS), 0, s, __VA_ARGS__); break;         \
-    case 5: hipLaunchKernelGGL(KERNEL<5>, dim3(B * H), dim3(CLS_THREADS), 0, s, __VA_ARGS__); break;         \
-    case 6: hipLaunchKernelGGL(KERNEL<6>, dim3(B * H), dim3(CLS_THREADS), 0, s, __VA_ARGS__); break;         \
-    case 7: hipLaunchKernelGGL(KERNEL<7>, dim3(B * H), dim3(CLS_THREADS), 0, s, __VA_ARGS__); break;         \
-    default: hipLaunchKernelGGL(KERNEL<8>, dim3(B * H), dim3(CLS_THREADS), 0, s, __VA_ARGS__); break;        \
-  }
+int cls64_lds(const void* fn, int T, OncePerDevice& once) { return 2 * cls64_tile(T) > 48 * 1024 ? raise_lds(fn, 2 * cls64_tile(CLS64_TOKENS), once) : PPLL_OK; }
 
 bool cls_vec_ok(int dt, int H, int dh, const void* a, const void* b) {
   return dt == BF16 && !(dh & 7) && !((((uintptr_t)a) | ((uintptr_t)b)) & 15) && H >= 1;
@@ -371,8 +289,11 @@ size_t attention_cls_lds_bytes(int T, int dh) { return (2 * (size_t)T * (dh + 1)
 
 int launch_attention_cls_fwd(hipStream_t s, const void* q, const void* kv, int dt, int B, int T, int H, int dh, void* out,
                              float* prob) {
-  if (cls64_ok(dt, T, H, dh, q, kv, out, nullptr)) {
-    CLS64_LAUNCH(attn_cls64_fwd_kernel, (const uint16_t*)q, (const uint16_t*)kv, T, H, (uint16_t*)out, prob);
+  if (cls64_ok(dt, T, H, dh, kv, nullptr)) {
+    static OncePerDevice once64;
+    PPLL_TRY(cls64_lds((const void*)attn_cls64_fwd_kernel, T, once64));
+    hipLaunchKernelGGL(attn_cls64_fwd_kernel, dim3(B * H), dim3(CLS_THREADS), 2 * cls64_tile(T), s, (const uint16_t*)q, (const uint16_t*)kv, T,
+                       H, (uint16_t*)out, prob);
     PPLL_HIP(hipGetLastError());
     return PPLL_OK;
   }
@@ -391,9 +312,11 @@ int launch_attention_cls_fwd(hipStream_t s, const void* q, const void* kv, int d
 
 int launch_attention_cls_bwd(hipStream_t s, const void* q, const void* kv, const float* prob, const void* dout, int dt, int B,
                              int T, int H, int dh, void* dq, void* dkv) {
-  if (cls64_ok(dt, T, H, dh, q, kv, dout, dkv)) {
-    CLS64_LAUNCH(attn_cls64_bwd_kernel, (const uint16_t*)q, (const uint16_t*)kv, prob, (const uint16_t*)dout, T, H, (uint16_t*)dq,
-                 (uint16_t*)dkv);
+  if (cls64_ok(dt, T, H, dh, kv, dkv)) {
+    static OncePerDevice once64;
+    PPLL_TRY(cls64_lds((const void*)attn_cls64_bwd_kernel, T, once64));
+    hipLaunchKernelGGL(attn_cls64_bwd_kernel, dim3(B * H), dim3(CLS_THREADS), 2 * cls64_tile(T), s, (const uint16_t*)q, (const uint16_t*)kv,
+                       prob, (const uint16_t*)dout, T, H, (uint16_t*)dq, (uint16_t*)dkv);
     PPLL_HIP(hipGetLastError());
     return PPLL_OK;
   }

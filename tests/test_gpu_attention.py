@@ -75,7 +75,7 @@ def test_scores_far_from_zero(T):
 
 @pytest.mark.parametrize("T,H,dh", [(t, 2, 64) for t in (1, 5, 8, 9, 31, 32, 33, 64, 65, 96, 97, 145, 161, 197, 224, 225, 256)] + [(17, 3, 32), (256, 2, 48), (65, 1, 64)])
 def test_attention_of_the_class_token(T, H, dh):
-    # edges of the 32 rows a pass, up to the 256 tokens that a block takes; other heads are for the general kernels
+    # edges of a copy of 8 rows and of the waves, up to the 256 tokens that a block takes; other heads are for the general kernels
     B, D = 3, H * dh
     g = torch.Generator(device="cuda").manual_seed(1000 * T + D)
     rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
