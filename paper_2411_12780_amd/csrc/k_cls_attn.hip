@@ -177,7 +177,8 @@ __global__ __launch_bounds__(CLS_THREADS) void attn_cls_bwd_kernel(const void* q
 // g ^ turn(r): lanes on consecutive rows and lanes along a row both spread over all banks.
 constexpr int CLS64_TOKENS = CLS_THREADS;   // a thread per token
 __device__ __forceinline__ int turn(int r) { return (r >> 1) & 7; }
-__host__ __device__ inline int cls64_tile(int T) { return (T + 7) / 8 * 1024; }
+__host__ __device__ constexpr int cls64_tile(int T) { return (T + 7) / 8 * 1024; }
+constexpr int CLS64_LDS = 2 * cls64_tile(CLS64_TOKENS);   // 64 KB, beside what the kernels declare
 // K and V of a head, zeros beyond T; there after the next barrier
 __device__ __forceinline__ void copy_head(const uint16_t* kv, int b, int h, int T, int D, int tid, char* k, char* v) {
   const __amdgpu_buffer_rsrc_t rs = pipe::make_rsrc(kv + (size_t)b * T * 2 * D, (uint32_t)T * 4u * (uint32_t)D);
@@ -273,7 +274,6 @@ bool cls64_ok(int dt, int T, int H, int dh, const void* a, const void* b) {
   return dt == BF16 && dh == 64 && T >= 1 && T <= CLS64_TOKENS && H >= 1 && (long)T * 256 * H < 0x7fffffffL &&
          !((((uintptr_t)a) | ((uintptr_t)b)) & 15);
 }
-int cls64_lds(const void* fn, int T, OncePerDevice& once) { return 2 * cls64_tile(T) > 48 * 1024 ? raise_lds(fn, 2 * cls64_tile(CLS64_TOKENS), once) : PPLL_OK; }
 
 bool cls_vec_ok(int dt, int H, int dh, const void* a, const void* b) {
   return dt == BF16 && !(dh & 7) && !((((uintptr_t)a) | ((uintptr_t)b)) & 15) && H >= 1;
@@ -291,7 +291,7 @@ int launch_attention_cls_fwd(hipStream_t s, const void* q, const void* kv, int d
                              float* prob) {
   if (cls64_ok(dt, T, H, dh, kv, nullptr)) {
     static OncePerDevice once64;
-    PPLL_TRY(cls64_lds((const void*)attn_cls64_fwd_kernel, T, once64));
+    PPLL_TRY(raise_lds((const void*)attn_cls64_fwd_kernel, CLS64_LDS, once64));
     hipLaunchKernelGGL(attn_cls64_fwd_kernel, dim3(B * H), dim3(CLS_THREADS), 2 * cls64_tile(T), s, (const uint16_t*)q, (const uint16_t*)kv, T,
                        H, (uint16_t*)out, prob);
     PPLL_HIP(hipGetLastError());
@@ -314,7 +314,7 @@ int launch_attention_cls_bwd(hipStream_t s, const void* q, const void* kv, const
                              int T, int H, int dh, void* dq, void* dkv) {
   if (cls64_ok(dt, T, H, dh, kv, dkv)) {
     static OncePerDevice once64;
-    PPLL_TRY(cls64_lds((const void*)attn_cls64_bwd_kernel, T, once64));
+    PPLL_TRY(raise_lds((const void*)attn_cls64_bwd_kernel, CLS64_LDS, once64));
     hipLaunchKernelGGL(attn_cls64_bwd_kernel, dim3(B * H), dim3(CLS_THREADS), 2 * cls64_tile(T), s, (const uint16_t*)q, (const uint16_t*)kv,
                        prob, (const uint16_t*)dout, T, H, (uint16_t*)dq, (uint16_t*)dkv);
     PPLL_HIP(hipGetLastError());
