@@ -23,6 +23,14 @@ __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t r, lds_char* 
 }
 
 template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+// A workgroup barrier without the waits of __syncthreads: a wave has waited for its copies itself, its reads are over where split_step
+// and k_step end.  The builtin promises nothing about memory, so the compiler is told that no access moves across it: the epilogues
+// write with ordinary stores to stages that other waves have just read.
+__device__ __forceinline__ void barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
 
 // One operand: ROWS rows (m or n) x KS k per stage.
 //  TR = false: k contiguous in memory.  LDS [row][32 k], 64 bytes a row; the 16-byte granule g of row r sits at
@@ -224,7 +232,7 @@ __device__ __forceinline__ void multiply(const __amdgpu_buffer_rsrc_t rsA, const
 #pragma unroll
   for (int i = 0; i < NS - 1; ++i) issue(i);
   wait_vm<(NS - 2) * S::COPIES>();
-  __builtin_amdgcn_s_barrier();
+  barrier();
   // the first fragments: products with zeros under the reads (the accumulators stay zero)
 #pragma unroll
   for (int i = 0; i < IM; ++i) set_zero(a1, i);
@@ -234,7 +242,7 @@ __device__ __forceinline__ void multiply(const __amdgpu_buffer_rsrc_t rsA, const
   for (int i = 0; i < nk; ++i) {
     const int st = (i % NS) * S::STAGE, nx = ((i + 1) % NS) * S::STAGE;
     wait_vm<(NS - 3) * S::COPIES>();       // this wave's part of stage i + 1 is in LDS
-    __builtin_amdgcn_s_barrier();          // and everyone's; nobody reads stage i - 1 any more
+    barrier();          // and everyone's; nobody reads stage i - 1 any more
     issue(i + NS - 1);
     column_sums(b0);
     k_step<AT, BT, S::BM, S::BN, 1, IM>(acc, a0, b0, a1, b1, fa0 + st, fb0 + st);
@@ -248,7 +256,7 @@ __device__ __forceinline__ void multiply(const __amdgpu_buffer_rsrc_t rsA, const
 #pragma unroll
     for (int i = 0; i < IM; ++i) asm volatile("" : "+v"(acc[j][i]));
   wait_vm<0>();
-  __builtin_amdgcn_s_barrier();            // the stages are free for the epilogue
+  barrier();            // the stages are free for the epilogue
 }
 
 }  // namespace pipe

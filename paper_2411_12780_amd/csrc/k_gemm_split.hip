@@ -107,18 +107,18 @@ __device__ __forceinline__ void copy_stages(const void* ptr, uint32_t bytes, lon
 #pragma unroll 1
   for (int i = 0; i < AHEAD; ++i) c.issue(to + i * STAGE, i, stages, K);
   wait_vm<N * (AHEAD - 1)>();
-  __builtin_amdgcn_s_barrier();
+  barrier();
   int wr = AHEAD * STAGE;
   for (int i = 0; i < stages; ++i) {
     wait_vm<N * (AHEAD - 2)>();          // this wave's part of stage i + 1 is there
-    __builtin_amdgcn_s_barrier();        // and everyone's; nobody reads stage i - 1 any more
+    barrier();        // and everyone's; nobody reads stage i - 1 any more
     c.issue(to + wr, i + AHEAD, stages, K);
     wr += STAGE;
     if (wr == STAGES * STAGE) wr = 0;
   }
   wait_vm<0>();
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_s_barrier();
+  barrier();
+  barrier();
 }
 
 // One k step of a wave, 64 rows x 32 columns: the products of the fragments at hand, and under them the reads of the next ones, which
@@ -172,21 +172,21 @@ __global__ __launch_bounds__(64 * (WAVES + COPY_WAVES), 3) void gemm_split_kerne
   const int base = (int)(uintptr_t)lds, fa = base + frag<false>(0, grp, lane), fb = base + OPER + frag<BT>((wave & 1) * 32, grp, lane);
   Frags<false, 2> a0, a1;
   Frags<BT, 1> b0, b1;
-  __builtin_amdgcn_s_barrier();
+  barrier();
   set_zero(a1, 0); set_zero(a1, 1); set_zero(b1, 0);
   split_step<BT>(acc, a1, b1, a0, b0, fa, fb);          // the first fragments: products with zeros under the reads
   int rd = 0, i = 0;
   auto next = [&] { rd += STAGE; if (rd == STAGES * STAGE) rd = 0; };
   for (; i + 1 < stages; i += 2) {
-    __builtin_amdgcn_s_barrier();                       // stage i + 1 is there, nobody reads stage i - 1 any more
+    barrier();                       // stage i + 1 is there, nobody reads stage i - 1 any more
     next();
     split_step<BT>(acc, a0, b0, a1, b1, fa + rd, fb + rd);
-    __builtin_amdgcn_s_barrier();
+    barrier();
     next();
     split_step<BT>(acc, a1, b1, a0, b0, fa + rd, fb + rd);
   }
   if (i < stages) {
-    __builtin_amdgcn_s_barrier();
+    barrier();
     split_step<BT>(acc, a0, b0, a1, b1, fa + rd, fb + rd);
   }
   asm volatile("s_nop 15\n s_nop 3" : "+v"(acc[0]), "+v"(acc[1])::"memory");     // the last products are through
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(64 * (WAVES + COPY_WAVES), 3) void gemm_split_kerne
   const bool ok = m < p.M && n < p.N;      // N is a multiple of 8
   u32x4 side = {0, 0, 0, 0};
   if (p.side) side = split_load16(make_rsrc(p.side, p.s_bytes), ok ? (int)((m * p.lds + n) * 2) : OOB);
-  __builtin_amdgcn_s_barrier();            // no copy is under way and nobody reads a stage any more
+  barrier();            // no copy is under way and nobody reads a stage any more
   float4* units = reinterpret_cast<float4*>(smem) + (wave & 1) * (GROUPS * 4 * 128) + lane;   // [group][unit][2][64 lanes]
   static_assert(WAVES * 4 * 128 * 16 <= STAGES * STAGE, "");
   float own[8], x[8];

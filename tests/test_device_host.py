@@ -86,3 +86,14 @@ def test_the_lds_attribute_is_raised_in_one_place_to_a_size_of_the_kernel_alone(
     # a size handed to the launch at hand is called lds; the matrix-core attention's is a function of its template argument
     assert len(raised) >= 15
     assert {f for f, m in raised if m == "lds"} <= {"k_attn_mfma.hip"}, raised
+
+
+def test_a_bare_barrier_is_a_barrier_for_the_compiler_too():
+    # the builtin orders execution only; pipe::barrier() holds the accesses on either side of it in place
+    ordered = 'asm volatile("" ::: "memory");\n  __builtin_amdgcn_s_barrier();\n  asm volatile("" ::: "memory");\n'
+    bare = []
+    for f in sorted(os.listdir(CSRC)):
+        if os.path.isfile(os.path.join(CSRC, f)):
+            text = open(os.path.join(CSRC, f)).read()
+            bare += [f] * (text.count("__builtin_amdgcn_s_barrier()") - text.count(ordered))
+    assert bare == []
