@@ -35,6 +35,7 @@
 
 #include "common.h"
 #include "gemm_pipe.h"
+#include "plan.h"
 
 namespace ppll {
 
@@ -448,7 +449,7 @@ int launch_bwd(hipStream_t s, const uint16_t* qkv, const uint16_t* out, const ui
 }  // namespace
 
 bool attention_mfma_supported(int dt, int T, int H, int dh, const void* a, const void* b, const void* c, const void* d) {
-  if (dt != BF16 || dh != 64 || T < 1 || T > 256 || H < 1) return false;
+  if (dt != BF16 || dh != 64 || T < 1 || T > 256 || H < 1 || !att_offsets_fit(T, H)) return false;
   return !((((uintptr_t)a) | ((uintptr_t)b) | ((uintptr_t)c) | ((uintptr_t)d)) & 15);
 }
 

@@ -141,6 +141,9 @@ inline int wide_tile_rows(int M, int N, int K, ProductEnd end, int units) {
   return c4 <= c5 ? 4 : 5;
 }
 
+// ---- The matrix-core attention addresses the keys, queries and values of an image with 32-bit byte offsets
+inline bool att_offsets_fit(int T, int H) { return (long)T * H * (3 * 64 * 2) <= 0x7fffffffL; }
+
 // ---- Attention of shapes that the matrix-core kernel does not take: one workgroup per (image, head), or one per 16 rows of one
 constexpr size_t UNIT_LDS = 160 * 1024;
 constexpr int ATT_ROWS = 16;

@@ -1,6 +1,7 @@
 """Host-side checks of the C ABI that need no GPU: the library loads, exports
 every symbol the header declares, answers size queries and rejects bad
 configurations before touching the device."""
+import ctypes
 import os
 import re
 
@@ -49,6 +50,13 @@ def test_layernorm_scratch_does_not_outgrow_the_activations():
     # the kernel that runs, are less than a hundredth of the workspace (without what depends on the device; sized for the kernel that
     # stands in where parameters are unaligned it took 4.70 GB)
     assert P.ppll_block_workspace_bytes(P.make_config(synth.workload("vit_base_224_bf16"))) < 4.60e9
+
+
+def test_attention_wider_than_its_offsets_is_refused_before_a_launch():
+    f = P.lib().ppll_internal_attention
+    f.restype = ctypes.c_int
+    f.argtypes = [ctypes.c_int] * 3 + [ctypes.c_void_p] * 6
+    assert f(1, 256, 21846, 4096, 8192, 12288, 16384, 20480, None) == 2     # PPLL_ERR_CONFIG
 
 
 def test_bad_configurations_are_rejected_on_the_host():

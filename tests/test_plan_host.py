@@ -39,6 +39,10 @@ int main() {
       long heads;
       if (std::scanf("%d %d %d %d %ld %d", &T, &H, &dh, &bwd, &heads, &units) != 6) return 1;
       std::printf("%d\n", att_by_rows(T, H, dh, bwd, heads, units));
+    } else if (!std::strcmp(what, "offsets")) {
+      int T, H;
+      if (std::scanf("%d %d", &T, &H) != 2) return 1;
+      std::printf("%d\n", att_offsets_fit(T, H));
     } else {
       return 2;
     }
@@ -172,3 +176,9 @@ def test_products_with_few_tiles(plan, M, N, K, columns):
 def test_products_with_a_tile_a_unit(plan, M, N, K, taken):
     assert plan("split", M, N, K, UNITS) == [taken]
     assert plan("split", M, N, K, 4) == [0]
+
+
+@pytest.mark.parametrize("T,H,fit", [(1, 1, 1), (256, 1, 1), (197, 12, 1), (256, 21845, 1), (256, 21846, 0), (1, 5592405, 1), (1, 5592406, 0), (255, 2147483647, 0)])
+def test_matrix_core_attention_within_its_32_bit_offsets(plan, T, H, fit):
+    # T rows of 3 x 64 H bf16 values: 2^31 - 1 bytes at most
+    assert plan("offsets", T, H) == [fit]
