@@ -23,7 +23,7 @@ __device__ __forceinline__ void load_to_lds(__amdgpu_buffer_rsrc_t r, lds_char* 
 }
 
 template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-// A workgroup barrier without the waits of __syncthreads: a wave has waited for its copies itself, its reads are over where split_step
+// A workgroup barrier without the waits of __syncthreads: a wave has waited for its copies itself, its reads are over where split_stage
 // and k_step end.  The builtin promises nothing about memory, so the compiler is told that no access moves across it: the epilogues
 // write with ordinary stores to stages that other waves have just read.
 __device__ __forceinline__ void barrier() {

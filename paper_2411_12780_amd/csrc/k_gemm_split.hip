@@ -2,16 +2,17 @@
 // the epilogues of the tiled kernel.
 //
 // With so few tiles a product takes as long as one tile does, and what bounds that is the chain along k.  A 64 x 128 tile whose four
-// waves copy through registers, multiply and meet at a barrier spends 0.4 us per 64 k (640 x 768 x 3072: 22 us on 60 of 256
-// units), four times what its products take, because the phases follow one another.  Here they run beside one another: four waves
-// do nothing but copy, straight from memory to LDS, three stages ahead of eight waves that multiply; those share out the four
-// k steps of a stage of 64 k, so that each barrier has two products a wave behind it, and add up at the end.  A copy takes rows of
-// 128 bytes, whole cache lines: with 64 bytes a row the loop took half as long again, the lines being fetched twice from beyond L2.
-// Smaller tiles find more units and copy more per product; beyond one a unit the tiled kernel is ahead.  64 KB of LDS and 62
-// registers a wave leave room for a workgroup of another stream (with stages twice as deep and no more waves a pipeline of three
-// blocks of width 192, 4160 rows, took 570 us a batch instead of 520).
-// Microseconds, tiled kernel -> this one: 640 x 768 x 768 8.6 -> 6.2, 640 x 768 x 2304 18.2 -> 12.0, 640 x 768 x 3072 22.2 -> 14.8,
-// 1500 x 384 x 384 6.1 -> 4.5, 1500 x 384 x 1536 13.2 -> 9.0; a step of 3 + 1 layers of width 768, 640 rows, 756 -> 678.
+// waves copy through registers, multiply and meet at a barrier spends 0.37 us per 64 k (640 x 768 x 3072: 22 us on 60 of 256
+// units), because the phases follow one another.  Here they run beside one another, 0.23 us per 64 k: four waves do nothing but copy,
+// straight from memory to LDS, three stages ahead of four waves that multiply, a 32 x 32 quarter of the tile each.  A quarter walks
+// along all of k in order, so the results are the tiled kernel's bit for bit.  (Eight multiplying waves that share out the k steps of
+// a stage and add up at the end were no faster, 14.5 us at 640 x 768 x 3072, and their sums run in an order of their own: through
+// four pipelined blocks of width 768 results moved by 1.4 %.)  A copy takes rows of 128 bytes, whole cache lines: with 64 bytes a row
+// the loop took half as long again, the lines being fetched twice from beyond L2.  Smaller tiles find more units and copy more per
+// product; beyond one a unit the tiled kernel catches up (`split_tiles`).  64 KB of LDS and 118 registers a wave leave room for a workgroup of
+// another stream (with stages twice as deep a pipeline of three blocks of width 192, 4160 rows, took 570 us a batch instead of 520).
+// Microseconds, tiled kernel -> this one: 640 x 768 x 768 8.6 -> 5.8, 640 x 768 x 2304 17.7 -> 11.3, 640 x 768 x 3072 22.4 -> 14.2,
+// 1500 x 384 x 384 6.2 -> 4.3, 1500 x 384 x 1536 13.0 -> 8.3; a step of 3 + 1 layers of width 768, 640 rows, 776 -> 680.
 #include "common.h"
 #include "gemm_pipe.h"
 #include "plan.h"
@@ -34,8 +35,7 @@ struct SplitArgs {
 };
 
 constexpr int EDGE = 64, KT = 64;    // tile, k of a stage: 128 bytes, one cache line, of a row of an operand with k contiguous
-constexpr int WAVES = 8, COPY_WAVES = 4, STAGES = 4;
-constexpr int GROUPS = WAVES / 2;     // of two waves, side by side, each 64 x 32 of the tile; group g takes k step g of a stage
+constexpr int WAVES = 4, COPY_WAVES = 4, STAGES = 4;   // multiplying waves have 32 x 32 of the tile each
 constexpr int OPER = EDGE * KT * 2, STAGE = 2 * OPER;
 
 __device__ __forceinline__ u32x4 split_load16(__amdgpu_buffer_rsrc_t r, int off) { return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0); }
@@ -52,11 +52,12 @@ __device__ __forceinline__ void swap_halves(float& a, float& b) {   // the upper
 //  TR = true: row index contiguous, [64 k][64 rows] as in memory: the 64-byte window w of k row k at w ^ (k / 2 % 2).
 // The fragment reads then spread over all banks.
 __device__ __forceinline__ int window(int k) { return (k >> 1) & 1; }
-// lane address of the fragment of rows row0 .. row0 + 31 at k step kk
-template <bool TR> __device__ __forceinline__ int frag(int row0, int kk, int lane) {
+// lane address of the fragment of rows row0 .. row0 + 31 at the first k step; TR = false: at k step kk with 32 kk flipped in it, else
+// 2048 kk further on
+template <bool TR> __device__ __forceinline__ int frag(int row0, int lane) {
   const int half = lane >> 5, r = lane & 31;
-  if (!TR) return (row0 + r) * 128 + (((2 * kk + half) ^ ((r >> 1) & 7)) << 4);
-  const int k = 16 * kk + 8 * half + ((lane & 15) >> 2);
+  if (!TR) return (row0 + r) * 128 + ((half ^ ((r >> 1) & 7)) << 4);
+  const int k = 8 * half + ((lane & 15) >> 2);
   return k * 128 + (((row0 >> 5) ^ window(k)) << 6) + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
 }
 
@@ -98,7 +99,7 @@ template <bool TR, int N> struct Copies {
   }
 };
 
-// A copying wave, from the first stage to the last.  Barriers: one with stage 0 in LDS, one per stage, two behind the loop.
+// A copying wave, from the first stage to the last.  Barriers: one with stage 0 in LDS, one per stage.
 template <bool TR>
 __device__ __forceinline__ void copy_stages(const void* ptr, uint32_t bytes, long ld, int row0, int nrows, int lane, int w, lds_char* to, int stages, int K) {
   constexpr int N = OPER / 1024 / (COPY_WAVES / 2), AHEAD = STAGES - 1;
@@ -116,38 +117,47 @@ __device__ __forceinline__ void copy_stages(const void* ptr, uint32_t bytes, lon
     wr += STAGE;
     if (wr == STAGES * STAGE) wr = 0;
   }
-  wait_vm<0>();
-  barrier();
-  barrier();
+  wait_vm<0>();                          // no copy outlives the workgroup, whose LDS others get
 }
 
-// One k step of a wave, 64 rows x 32 columns: the products of the fragments at hand, and under them the reads of the next ones, which
-// are there when the block ends (one block, because the compiler would order LDS reads that it knows of behind the copies into LDS).
+// The four k steps of a stage in a wave, in order: the products of the fragments at hand, and under them the reads of the next stage's,
+// which are there when the block ends (one block, because the compiler would order LDS reads that it knows of behind the copies into
+// LDS).  The reads come first, so a vector instruction before the block is two and more away from the first product.
 template <bool BT>
-__device__ __forceinline__ void split_step(f32x16 (&acc)[2], const Frags<false, 2>& a, const Frags<BT, 1>& b, Frags<false, 2>& na, Frags<BT, 1>& nb,
-                                           int addrA, int addrB) {
-#define PPLL_MMA "v_mfma_f32_32x32x16_bf16 %[c0], %[q], %[p0], %[c0]\n v_mfma_f32_32x32x16_bf16 %[c1], %[q], %[p1], %[c1]\n s_waitcnt lgkmcnt(0)"
-  if constexpr (BT) {
-    asm volatile("ds_read_b128 %[x0], %[ra]\n ds_read_b64_tr_b16 %[lo], %[rb]\n ds_read_b64_tr_b16 %[hi], %[rb] offset:512\n"   // k + 4: the same window
-                 "ds_read_b128 %[x1], %[ra] offset:4096\n" PPLL_MMA
-                 : [c0] "+v"(acc[0]), [c1] "+v"(acc[1]), [x0] "=&v"(na.v[0]), [x1] "=&v"(na.v[1]), [lo] "=&v"(nb.lo[0]), [hi] "=&v"(nb.hi[0])
-                 : [p0] "v"(a.get(0)), [p1] "v"(a.get(1)), [q] "v"(b.get(0)), [ra] "v"(addrA), [rb] "v"(addrB)
+__device__ __forceinline__ void split_stage(f32x16& acc, const Frags<false, 4>& a, const Frags<BT, 4>& b, Frags<false, 4>& na, Frags<BT, 4>& nb,
+                                            int addrA, int addrB) {
+#define PPLL_MMA "v_mfma_f32_32x32x16_bf16 %[c], %[q0], %[p0], %[c]\n v_mfma_f32_32x32x16_bf16 %[c], %[q1], %[p1], %[c]\n" \
+                 "v_mfma_f32_32x32x16_bf16 %[c], %[q2], %[p2], %[c]\n v_mfma_f32_32x32x16_bf16 %[c], %[q3], %[p3], %[c]\n s_waitcnt lgkmcnt(0)"
+#define PPLL_NEXT_A [x0] "=&v"(na.v[0]), [x1] "=&v"(na.v[1]), [x2] "=&v"(na.v[2]), [x3] "=&v"(na.v[3])
+#define PPLL_CUR [p0] "v"(a.get(0)), [p1] "v"(a.get(1)), [p2] "v"(a.get(2)), [p3] "v"(a.get(3)), [q0] "v"(b.get(0)), [q1] "v"(b.get(1)), \
+                 [q2] "v"(b.get(2)), [q3] "v"(b.get(3)), [ra0] "v"(addrA), [ra1] "v"(addrA ^ 32), [ra2] "v"(addrA ^ 64), [ra3] "v"(addrA ^ 96)
+  if constexpr (BT) {   // the upper half of a fragment is k + 4: the same window, 512 bytes on
+    asm volatile("ds_read_b128 %[x0], %[ra0]\n ds_read_b64_tr_b16 %[l0], %[rb]\n ds_read_b64_tr_b16 %[h0], %[rb] offset:512\n"
+                 "ds_read_b128 %[x1], %[ra1]\n ds_read_b64_tr_b16 %[l1], %[rb] offset:2048\n ds_read_b64_tr_b16 %[h1], %[rb] offset:2560\n"
+                 "ds_read_b128 %[x2], %[ra2]\n ds_read_b64_tr_b16 %[l2], %[rb] offset:4096\n ds_read_b64_tr_b16 %[h2], %[rb] offset:4608\n"
+                 "ds_read_b128 %[x3], %[ra3]\n ds_read_b64_tr_b16 %[l3], %[rb] offset:6144\n ds_read_b64_tr_b16 %[h3], %[rb] offset:6656\n" PPLL_MMA
+                 : [c] "+v"(acc), PPLL_NEXT_A, [l0] "=&v"(nb.lo[0]), [h0] "=&v"(nb.hi[0]), [l1] "=&v"(nb.lo[1]), [h1] "=&v"(nb.hi[1]),
+                   [l2] "=&v"(nb.lo[2]), [h2] "=&v"(nb.hi[2]), [l3] "=&v"(nb.lo[3]), [h3] "=&v"(nb.hi[3])
+                 : PPLL_CUR, [rb] "v"(addrB)
                  : "memory");
   } else {
-    asm volatile("ds_read_b128 %[x0], %[ra]\n ds_read_b128 %[y], %[rb]\n ds_read_b128 %[x1], %[ra] offset:4096\n" PPLL_MMA
-                 : [c0] "+v"(acc[0]), [c1] "+v"(acc[1]), [x0] "=&v"(na.v[0]), [x1] "=&v"(na.v[1]), [y] "=&v"(nb.v[0])
-                 : [p0] "v"(a.get(0)), [p1] "v"(a.get(1)), [q] "v"(b.get(0)), [ra] "v"(addrA), [rb] "v"(addrB)
+    asm volatile("ds_read_b128 %[x0], %[ra0]\n ds_read_b128 %[y0], %[rb0]\n ds_read_b128 %[x1], %[ra1]\n ds_read_b128 %[y1], %[rb1]\n"
+                 "ds_read_b128 %[x2], %[ra2]\n ds_read_b128 %[y2], %[rb2]\n ds_read_b128 %[x3], %[ra3]\n ds_read_b128 %[y3], %[rb3]\n" PPLL_MMA
+                 : [c] "+v"(acc), PPLL_NEXT_A, [y0] "=&v"(nb.v[0]), [y1] "=&v"(nb.v[1]), [y2] "=&v"(nb.v[2]), [y3] "=&v"(nb.v[3])
+                 : PPLL_CUR, [rb0] "v"(addrB), [rb1] "v"(addrB ^ 32), [rb2] "v"(addrB ^ 64), [rb3] "v"(addrB ^ 96)
                  : "memory");
   }
 #undef PPLL_MMA
+#undef PPLL_NEXT_A
+#undef PPLL_CUR
 }
 
 template <bool BT>
-__global__ __launch_bounds__(64 * (WAVES + COPY_WAVES), 3) void gemm_split_kernel(SplitArgs p) {
+__global__ __launch_bounds__(64 * (WAVES + COPY_WAVES), 4) void gemm_split_kernel(SplitArgs p) {
   __shared__ __align__(1024) char smem[STAGES * STAGE];
   // XCD x (workgroup id % 8) takes a contiguous range of the tiles, row by row: they share operand panels in its L2
-  const int slot = blockIdx.x >> 3, t = (blockIdx.x & 7) * p.per_xcd + slot;
-  if (slot >= p.per_xcd || t >= p.tiles) return;
+  const int t = (blockIdx.x & 7) * p.per_xcd + (blockIdx.x >> 3);
+  if (t >= p.tiles) return;
   const int m0 = t / p.tiles_n * EDGE, n0 = t % p.tiles_n * EDGE;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int K = p.K, stages = (K + KT - 1) / KT;
@@ -158,95 +168,79 @@ __global__ __launch_bounds__(64 * (WAVES + COPY_WAVES), 3) void gemm_split_kerne
     else copy_stages<false>(p.A, p.a_bytes, p.lda, m0, p.M, lane, w >> 1, lds, stages, K);
     return;
   }
-  const int grp = wave >> 1, nw = n0 + (wave & 1) * 32;
-  f32x16 acc[2];
-  {   // the accumulators of the first group start from the bias: a lane holds columns 8 q + 4 (lane / 32) .. + 3
-    const __amdgpu_buffer_rsrc_t rs = make_rsrc(p.bias, p.bias && grp == 0 ? (uint32_t)p.N * 4u : 0u);
+  const int mw = (wave >> 1) * 32, nw = (wave & 1) * 32;
+  const int base = (int)(uintptr_t)lds, fa = base + frag<false>(mw, lane), fb = base + OPER + frag<BT>(nw, lane);
+  // What the epilogue takes from memory, asked for ahead of the loop.  It has a row a lane, columns n .. n + 7 and n + 16 .. n + 23
+  const bool has_aux = p.epilogue == EPI_DGELU, has_res = p.side && !has_aux;
+  const int m = m0 + mw + (lane & 31), n = n0 + nw + 8 * (lane >> 5);
+  u32x4 bias[2][2], side[2];
+  {
+    const __amdgpu_buffer_rsrc_t rsB = make_rsrc(p.bias, p.bias ? (uint32_t)p.N * 4u : 0u), rsS = make_rsrc(p.side, p.s_bytes);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const u32x4 b = split_load16(rs, 4 * (nw + 8 * q + 4 * (lane >> 5)));
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[0][4 * q + e] = acc[1][4 * q + e] = __uint_as_float(b[e]);
+    for (int u = 0; u < 2; ++u) {
+      bias[u][0] = split_load16(rsB, 4 * (n + 16 * u));
+      bias[u][1] = split_load16(rsB, 4 * (n + 16 * u) + 16);
+      side[u] = split_load16(rsS, m < p.M && n + 16 * u < p.N ? (int)((m * p.lds + n + 16 * u) * 2) : OOB);
     }
   }
-  const int base = (int)(uintptr_t)lds, fa = base + frag<false>(0, grp, lane), fb = base + OPER + frag<BT>((wave & 1) * 32, grp, lane);
-  Frags<false, 2> a0, a1;
-  Frags<BT, 1> b0, b1;
+  f32x16 acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+  Frags<false, 4> a0, a1;
+  Frags<BT, 4> b0, b1;
   barrier();
-  set_zero(a1, 0); set_zero(a1, 1); set_zero(b1, 0);
-  split_step<BT>(acc, a1, b1, a0, b0, fa, fb);          // the first fragments: products with zeros under the reads
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) { set_zero(a1, kk); set_zero(b1, kk); }
+  split_stage<BT>(acc, a1, b1, a0, b0, fa, fb);         // the first fragments: products with zeros under the reads
   int rd = 0, i = 0;
   auto next = [&] { rd += STAGE; if (rd == STAGES * STAGE) rd = 0; };
   for (; i + 1 < stages; i += 2) {
-    barrier();                       // stage i + 1 is there, nobody reads stage i - 1 any more
+    barrier();                                          // stage i + 1 is there, nobody reads stage i - 1 any more
     next();
-    split_step<BT>(acc, a0, b0, a1, b1, fa + rd, fb + rd);
+    split_stage<BT>(acc, a0, b0, a1, b1, fa + rd, fb + rd);
     barrier();
     next();
-    split_step<BT>(acc, a1, b1, a0, b0, fa + rd, fb + rd);
+    split_stage<BT>(acc, a1, b1, a0, b0, fa + rd, fb + rd);
   }
   if (i < stages) {
     barrier();
-    split_step<BT>(acc, a0, b0, a1, b1, fa + rd, fb + rd);
+    split_stage<BT>(acc, a0, b0, a1, b1, fa + rd, fb + rd);
   }
-  asm volatile("s_nop 15\n s_nop 3" : "+v"(acc[0]), "+v"(acc[1])::"memory");     // the last products are through
+  asm volatile("s_nop 15\n s_nop 3" : "+v"(acc)::"memory");     // the last products are through
 
-  // Epilogue.  The four units of a wave's tile, 32 rows x 16 columns each, go to the four groups: a wave gives the others' to LDS, lane
-  // for lane, and adds up its own in the order of the groups.
-  const bool has_aux = p.epilogue == EPI_DGELU, has_res = p.side && !has_aux;
-  const int m = m0 + 32 * (grp >> 1) + (lane & 31), n = nw + 16 * (grp & 1) + 8 * (lane >> 5);
-  const bool ok = m < p.M && n < p.N;      // N is a multiple of 8
-  u32x4 side = {0, 0, 0, 0};
-  if (p.side) side = split_load16(make_rsrc(p.side, p.s_bytes), ok ? (int)((m * p.lds + n) * 2) : OOB);
-  barrier();            // no copy is under way and nobody reads a stage any more
-  float4* units = reinterpret_cast<float4*>(smem) + (wave & 1) * (GROUPS * 4 * 128) + lane;   // [group][unit][2][64 lanes]
-  static_assert(WAVES * 4 * 128 * 16 <= STAGES * STAGE, "");
-  float own[8], x[8];
+  const __amdgpu_buffer_rsrc_t rsC = make_rsrc(p.C, p.c_bytes), rsC2 = make_rsrc(p.C2, p.C2 ? p.c_bytes : 0u);
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int i2 = u >> 1, b = 8 * (u & 1);
-    if (u != grp) {
-      units[(grp * 4 + u) * 128] = make_float4(acc[i2][b], acc[i2][b + 1], acc[i2][b + 2], acc[i2][b + 3]);
-      units[(grp * 4 + u) * 128 + 64] = make_float4(acc[i2][b + 4], acc[i2][b + 5], acc[i2][b + 6], acc[i2][b + 7]);
+  for (int u = 0; u < 2; ++u) {
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = acc[8 * u + e];
+    // a lane has columns 4 (lane / 32) .. + 3 of two groups of 8: lanes 0 .. 31 get the first group, lanes 32 .. 63 the second
+#pragma unroll
+    for (int e = 0; e < 4; ++e) swap_halves(x[e], x[4 + e]);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] += __uint_as_float(bias[u][e >> 2][e & 3]);
+    if (has_res) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { x[2 * e] += __uint_as_float(side[u][e] << 16); x[2 * e + 1] += __uint_as_float(side[u][e] & 0xffff0000u); }
+    }
+    if (has_aux) {   // the saved GELU derivative
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { x[2 * e] *= __uint_as_float(side[u][e] << 16); x[2 * e + 1] *= __uint_as_float(side[u][e] & 0xffff0000u); }
+    }
+    const int off = m < p.M && n + 16 * u < p.N ? (int)((m * p.ldc + n + 16 * u) * 2) : OOB;   // N is a multiple of 8
+    if (p.epilogue == EPI_GELU) {   // C2 = gelu(h), C = gelu'(h) from one evaluation of the normal CDF and density
+      float dg[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        float cdf, pdf;
+        cdf_pdf(x[e], cdf, pdf);
+        dg[e] = cdf + x[e] * pdf; x[e] *= cdf;
+      }
+      __builtin_amdgcn_raw_buffer_store_b128(pack8(dg), rsC, off, 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(pack8(x), rsC2, off, 0, 0);
     } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) own[e] = acc[i2][b + e];
+      __builtin_amdgcn_raw_buffer_store_b128(pack8(x), rsC, off, 0, 0);
     }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int g = 0; g < GROUPS; ++g) {
-    float4 lo = make_float4(own[0], own[1], own[2], own[3]), hi = make_float4(own[4], own[5], own[6], own[7]);
-    if (g != grp) { lo = units[(g * 4 + grp) * 128]; hi = units[(g * 4 + grp) * 128 + 64]; }
-    const float v[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-#pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = g ? x[e] + v[e] : v[e];
-  }
-  // lanes 0..31 get columns 0..7, lanes 32..63 columns 8..15 of the unit
-#pragma unroll
-  for (int e = 0; e < 4; ++e) swap_halves(x[e], x[4 + e]);
-  if (has_res) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { x[2 * e] += __uint_as_float(side[e] << 16); x[2 * e + 1] += __uint_as_float(side[e] & 0xffff0000u); }
-  }
-  if (has_aux) {   // the saved GELU derivative
-#pragma unroll
-    for (int e = 0; e < 4; ++e) { x[2 * e] *= __uint_as_float(side[e] << 16); x[2 * e + 1] *= __uint_as_float(side[e] & 0xffff0000u); }
-  }
-  const __amdgpu_buffer_rsrc_t rsC = make_rsrc(p.C, p.c_bytes);
-  const int off = ok ? (int)((m * p.ldc + n) * 2) : OOB;
-  if (p.epilogue == EPI_GELU) {   // C2 = gelu(h), C = gelu'(h) from one evaluation of the normal CDF and density
-    float dg[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      float cdf, pdf;
-      cdf_pdf(x[e], cdf, pdf);
-      dg[e] = cdf + x[e] * pdf; x[e] *= cdf;
-    }
-    __builtin_amdgcn_raw_buffer_store_b128(pack8(dg), rsC, off, 0, 0);
-    __builtin_amdgcn_raw_buffer_store_b128(pack8(x), make_rsrc(p.C2, p.c_bytes), off, 0, 0);
-  } else {
-    __builtin_amdgcn_raw_buffer_store_b128(pack8(x), rsC, off, 0, 0);
   }
 }
 
@@ -274,7 +268,7 @@ int launch_gemm_split(hipStream_t s, const GemmArgs& g) {
   p.per_xcd = (p.tiles + 7) / 8;
   const dim3 grid(8 * p.per_xcd), block(64 * (WAVES + COPY_WAVES));
   void* prof = nullptr;
-  PPLL_TRY(profile_begin(s, 2.0 * g.M * g.N * g.K, &prof, g.M < 256 ? 2 : 0));   // few output rows: a class of its own
+  PPLL_TRY(profile_begin(s, 2.0 * g.M * g.N * g.K, &prof));
   if (bt) hipLaunchKernelGGL(gemm_split_kernel<true>, grid, block, 0, s, p);
   else hipLaunchKernelGGL(gemm_split_kernel<false>, grid, block, 0, s, p);
   PPLL_HIP(hipGetLastError());

@@ -85,11 +85,13 @@ inline bool few_tiles(int M, int N, int K, int units) {
   return (N <= FEW_WIDTH || K <= FEW_WIDTH) && (long)((M + 31) / 32) * ((N + 63) / 64) <= units;
 }
 
-// ---- A product whose 64 x 64 tiles find a compute unit each goes to the kernel with waves that do nothing but copy.  One tile more
-// than units is a second round of all of it: 640 x 2304 x 768 (360 tiles) 9.9 us, 8.9 on the tiled kernel; 640 x 768 x 768 (120) 6.2
-// and 8.6.  Below 128 of K the loop is a stage or two: 777 x 544 x 136 5.0 and 4.9.  Tiles of 128 x 128 on the same scheme (128 KB of
-// LDS) are ahead alone (8320 x 384 x 1536: 14.4 us, 19.5 on the tiled kernel), but not in a step, where the operands come from
-// further off (22 and 22.5), and behind beside other streams (four pipelined blocks of width 384, 8320 rows: 3060 us a batch and 3000).
+// ---- A product whose 64 x 64 tiles find a compute unit each goes to the kernel with waves that do nothing but copy (640 x 768 x 768,
+// 120 tiles: 5.8 us, 8.6 on the tiled kernel).  Beyond that tiles share units: alone on the chip it is ahead a little further (2700 x
+// 384 x 384, 258 tiles: 5.2 and 6.3), level or behind from some 320 tiles on (520 x 2304 x 768, 324: 9.1 and 8.9; 640 x 3072 x 768,
+// 480: 10.0 and 9.0).  It starts where the kernel does, at 128 of K (1500 x 384 x 136: 3.7 and 4.8).  Tiles of 128 x 128 on the same
+// scheme (128 KB of LDS) are ahead alone (8320 x 384 x 1536: 14.4 us, 19.5 on the tiled kernel), but not in a step, where the operands
+// come from further off (22 and 22.5), and behind beside other streams (four pipelined blocks of width 384, 8320 rows: 3060 us a batch
+// and 3000).
 constexpr int SPLIT_MIN_K = 128;
 inline bool split_tiles(int M, int N, int K, int units) {
   return K >= SPLIT_MIN_K && units >= 8 && (long)((M + 63) / 64) * ((N + 63) / 64) <= units;

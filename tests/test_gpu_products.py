@@ -96,5 +96,6 @@ def test_split_products(M, N, K, bt, epilogue):
     if epilogue == GELU:
         gelu = v * 0.5 * (1 + torch.erf(v / 2 ** 0.5))
         assert bool(((C2.double() - gelu).abs() <= gelu.abs() * 2.0 ** -8 + size * (K * 2.0 ** -23) + 1e-6).all())
-    again = product(SPLIT, A, B, bt, bias, residual, epilogue, aux)
-    assert torch.equal(C, again[1]) and torch.equal(C2, again[2])
+    for kernel in (SPLIT, TILED):     # again, and on the kernel that takes the same products one tile of columns further: the same sums
+        status, D, D2 = product(kernel, A, B, bt, bias, residual, epilogue, aux)
+        assert status == 0 and torch.equal(C, D) and torch.equal(C2, D2), kernel
