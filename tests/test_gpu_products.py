@@ -13,17 +13,17 @@ FEW, TILED, WIDE_128, WIDE_160, SPLIT = 1, 2, 4, 5, 6
 NONE, GELU, DGELU = 0, 1, 2
 
 
-def product(kernel, A, B, bt, bias, residual, epilogue, aux):
+def product(kernel, A, B, bt, bias, residual, epilogue, aux, C=None, C2=None):
     f = P.lib().ppll_internal_product
     f.restype = ctypes.c_int
     vp, i, l = ctypes.c_void_p, ctypes.c_int, ctypes.c_long
     f.argtypes = [i, i, i, i, vp, l, vp, l, i, vp, l, vp, vp, i, vp, vp, vp]
     M, K = A.shape
     N = B.shape[1 if bt else 0]
-    C = torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda")
-    C2 = torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda")
+    if C is None:
+        C, C2 = (torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(2))
     ptr = lambda t: None if t is None else t.data_ptr()
-    status = f(kernel, M, N, K, ptr(A), A.stride(0), ptr(B), B.stride(0), bt, ptr(C), N, ptr(bias), ptr(residual), epilogue,
+    status = f(kernel, M, N, K, ptr(A), A.stride(0), ptr(B), B.stride(0), bt, ptr(C), C.stride(0), ptr(bias), ptr(residual), epilogue,
                ptr(C2) if epilogue == GELU else None, ptr(aux) if epilogue == DGELU else None, torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     return status, C, C2
@@ -99,3 +99,51 @@ def test_split_products(M, N, K, bt, epilogue):
     for kernel in (SPLIT, TILED):     # again, and on the kernel that takes the same products one tile of columns further: the same sums
         status, D, D2 = product(kernel, A, B, bt, bias, residual, epilogue, aux)
         assert status == 0 and torch.equal(C, D) and torch.equal(C2, D2), kernel
+
+
+@pytest.mark.parametrize("epilogue", [NONE, GELU, DGELU])
+@pytest.mark.parametrize("bt", [0, 1])
+@pytest.mark.parametrize("M,N,K,apart", [(65, 72, 136, 80), (300, 264, 200, 5 * 264), (129, 120, 328, 128), (257, 384, 384, 17 * 384)])
+def test_split_products_in_and_out_of_wider_buffers(M, N, K, apart, bt, epilogue):
+    # As the class-token layer calls them: a slice of a weight for B, result rows further apart than they are long, of the query gradient
+    # added to what is there.  Between the rows and behind the last one nothing changes.
+    g = torch.Generator(device="cuda").manual_seed(M * 1000 + N + K + apart)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    A = rnd(M, K + 8)[:, :K]
+    B = rnd(K, 3 * N)[:, N:2 * N] if bt else rnd(N, 2 * K)[:, K:]
+    bias = torch.randn(N, generator=g, device="cuda") if epilogue != DGELU else None
+    buf, buf2, aux = rnd(M * apart + 4096), rnd(M * apart + 4096), rnd(M, apart)[:, :N]
+    rows = lambda t: t[:M * apart].view(M, apart)[:, :N]
+    got = {}
+    for kernel in (SPLIT, TILED):
+        c, c2 = buf.clone(), buf2.clone()
+        status, _, _ = product(kernel, A, B, bt, bias, rows(c) if epilogue == NONE else None, epilogue, aux, rows(c), rows(c2))
+        assert status == 0
+        for t, before in ((c, buf), (c2, buf2)):
+            now, was = t.clone(), before.clone()
+            rows(now).zero_(), rows(was).zero_()
+            assert torch.equal(now, was)
+        got[kernel] = rows(c), rows(c2)
+    v = A.double() @ (B.double().contiguous() if bt else B.double().t().contiguous())
+    size = A.double().abs() @ (B.double() if bt else B.double().t()).abs().contiguous()
+    if bias is not None:
+        v = v + bias.double()
+    if epilogue == NONE:
+        v, size = v + rows(buf).double(), size + rows(buf).double().abs()
+    if epilogue == DGELU:
+        v, size = v * aux.double(), size * aux.double().abs()
+    if epilogue == GELU:
+        gelu = v * 0.5 * (1 + torch.erf(v / 2 ** 0.5))
+        assert bool(((got[SPLIT][1].double() - gelu).abs() <= gelu.abs() * 2.0 ** -8 + size * (K * 2.0 ** -23) + 1e-6).all())
+    else:   # one rounding to bf16, fp32 sums of K terms
+        assert bool(((got[SPLIT][0].double() - v).abs() <= v.abs() * 2.0 ** -8 + size * (K * 2.0 ** -24) + 1e-6).all())
+        assert torch.equal(rows(buf2), got[SPLIT][1])
+    assert torch.equal(got[SPLIT][0], got[TILED][0]) and torch.equal(got[SPLIT][1], got[TILED][1])
+
+
+def test_products_that_the_split_kernel_does_not_take_are_refused():
+    rnd = lambda *s: torch.randn(*s, device="cuda").to(torch.bfloat16)
+    A, B, side = rnd(16, 128), rnd(128, 16), rnd(16, 16)
+    for status, C, C2 in (product(SPLIT, A[:, :120], B[:120], 1, None, None, NONE, None),     # a reduction below 128
+                          product(SPLIT, A, B, 1, None, side, DGELU, side)):                  # residual and saved derivative at once
+        assert status == 2 and bool((C == 7.0).all()) and bool((C2 == 7.0).all())
