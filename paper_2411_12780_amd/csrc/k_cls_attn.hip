@@ -8,8 +8,9 @@
 // Layouts: q, o, dq, do are [B, H*dh]; kv and dkv are [B*T, 2*H*dh] with the keys in the first H*dh columns.
 //
 // What bounds this is memory: keys and values are read once.  For bf16 heads of 64 (attn_cls64_*) they lie in LDS as bf16, copied
-// straight from memory, 50 KB at 197 tokens: three workgroups a unit, one loading while another multiplies.  The general kernels stage
-// both as fp32 through registers: 103 KB, one workgroup a unit whose loads nothing covers.  Sums run in the same order in both.
+// straight from memory, 50 KB at 197 tokens: with what the kernels declare beside them (2 and 3 KB) three forward workgroups a unit and
+// two backward ones, one loading while another multiplies.  The general kernels stage both as fp32 through registers: 103 KB, one
+// workgroup a unit whose loads nothing covers.  Sums run in the same order in both.
 // Microseconds in a step, general kernel -> this one: 128 images x 197 tokens x 12 heads forward 53.9 -> 21.1 (77 MB), backward
 // 67.1 -> 34.3 (155 MB), 64 x 145 x 6 8.8 -> 7.5 and 11.4 -> 8.2, 128 x 65 x 6 7.7 -> 6.0 and 10.0 -> 7.0.  K and V in registers, eight
 // lanes a row, sum in another order and take 15.9, 25.2, 6.6, 7.2, 5.8 and 6.4: 1 % of a step at 197 tokens, for gradients that
