@@ -423,6 +423,7 @@ __device__ __forceinline__ void gemm_mfma_tile(const MfmaArgs& p, const int bid)
 
 template <bool BT, int TM>
 __global__ __launch_bounds__(256, 2) void gemm_mfma_kernel(MfmaArgs p) {
+  PPLL_CODE_TO_L2(2);
   gemm_mfma_tile<false, BT, TM>(p, (int)blockIdx.x);
 }
 
@@ -484,6 +485,7 @@ using PipeShape = pipe::Shape<true, true, 1, 4, 4, 3>;
 constexpr int PIPE_BN = PipeShape::BN;
 static_assert(PipeShape::BM == BM && BM == WG_EDGE && BN == WG_EDGE && PIPE_BN == WG_WIDE && BK == WG_STEP, "");
 __global__ __launch_bounds__(PipeShape::THREADS, 2) void gemm_pipe_grouped_kernel(GroupedArgs a) {
+  PPLL_CODE_TO_L2(1);
   extern __shared__ __align__(1024) char smem[];
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
   const int t = xcd * a.per_xcd + slot;

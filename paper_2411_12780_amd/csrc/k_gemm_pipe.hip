@@ -39,6 +39,7 @@ __device__ __forceinline__ u32x4 pack8(const float (&v)[8]) {
 
 template <bool BT, int WGM, int WGN, int IM, int NS>
 __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(PipeArgs p) {
+  PPLL_CODE_TO_L2(4);
   using S = Shape<false, BT, WGM, WGN, IM, NS>;
   constexpr int JN = 2;
   extern __shared__ __align__(1024) char smem[];

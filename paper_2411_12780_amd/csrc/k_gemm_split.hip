@@ -154,6 +154,7 @@ __device__ __forceinline__ void split_stage(f32x16& acc, const Frags<false, 4>& 
 
 template <bool BT>
 __global__ __launch_bounds__(64 * (WAVES + COPY_WAVES), 4) void gemm_split_kernel(SplitArgs p) {
+  PPLL_CODE_TO_L2(1);
   __shared__ __align__(1024) char smem[STAGES * STAGE];
   // XCD x (workgroup id % 8) takes a contiguous range of the tiles, row by row: they share operand panels in its L2
   const int t = (blockIdx.x & 7) * p.per_xcd + (blockIdx.x >> 3);

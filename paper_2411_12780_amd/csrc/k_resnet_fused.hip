@@ -53,6 +53,7 @@ constexpr int pixel_pitch(int C) { return 2 * C + 16; }
 
 template <int C, int WAVES, bool BWD>
 __global__ __launch_bounds__(64 * WAVES, C == 16 ? 4 : 1) void conv_bn_kernel(ConvBnArgs p) {
+  PPLL_CODE_TO_L2(C == 64 ? 2 : 0);    // narrower filters: no difference
   constexpr int TH = 64 * WAVES, NT = (C + 31) / 32, K16 = C / 16, CG = C / 8, PITCH = pixel_pitch(C);
   constexpr int PB = (C + 31) / 32 * 64, RSW = 18 * C + 16, FILTER = filter_bytes<C, BWD>();
   // staged pieces per thread: C/16 x (sr + 2) / sr; sr is 4 or more, with eight waves 8 or more
