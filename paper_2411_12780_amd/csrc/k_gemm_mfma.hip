@@ -99,9 +99,9 @@ __device__ __forceinline__ uint4 buf_load16(__amdgpu_buffer_rsrc_t r, int off) {
   const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
   return make_uint4(v.x, v.y, v.z, v.w);
 }
-__device__ __forceinline__ void buf_store16(__amdgpu_buffer_rsrc_t r, int off, uint4 v) {
+template <int POLICY> __device__ __forceinline__ void buf_store16(__amdgpu_buffer_rsrc_t r, int off, uint4 v) {
   const u32x4 w = {v.x, v.y, v.z, v.w};
-  __builtin_amdgcn_raw_buffer_store_b128(w, r, off, 0, 0);
+  __builtin_amdgcn_raw_buffer_store_b128(w, r, off, 0, POLICY);
 }
 
 // One operand tile (ROWS x 64) on its way from memory to LDS, as seen by one thread.
@@ -395,8 +395,8 @@ __device__ __forceinline__ void gemm_mfma_tile(const MfmaArgs& p, const int bid)
     }
     if (out_f32) {
       const int off = p.tile_partial ? (row * BN + c8) * 4 : ok ? (int)((long)m * p.ldc * 4) + ncol4 : OOB;
-      buf_store16(rsC, off, make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
-      buf_store16(rsC, (ok || p.tile_partial) ? off + 16 : OOB, make_uint4(__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])));
+      buf_store16<0>(rsC, off, make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])));
+      buf_store16<0>(rsC, (ok || p.tile_partial) ? off + 16 : OOB, make_uint4(__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]), __float_as_uint(v[7])));
     } else {
       const int off = ok ? (int)(((long)m * p.ldc) * 2) + ncol2 : OOB;
       if (p.epilogue == EPI_GELU) {   // C2 = gelu(h), C = gelu'(h) from one evaluation of the normal CDF and density
@@ -410,12 +410,12 @@ __device__ __forceinline__ void gemm_mfma_tile(const MfmaArgs& p, const int bid)
         uint4 o, g;
         o.x = pack_bf16x2(dg[0], dg[1]); o.y = pack_bf16x2(dg[2], dg[3]); o.z = pack_bf16x2(dg[4], dg[5]); o.w = pack_bf16x2(dg[6], dg[7]);
         g.x = pack_bf16x2(gl[0], gl[1]); g.y = pack_bf16x2(gl[2], gl[3]); g.z = pack_bf16x2(gl[4], gl[5]); g.w = pack_bf16x2(gl[6], gl[7]);
-        buf_store16(rsC, off, o);
-        buf_store16(rsC2, off, g);
+        buf_store16<THROUGH>(rsC, off, o);
+        buf_store16<THROUGH>(rsC2, off, g);
       } else {
         uint4 o;
         o.x = pack_bf16x2(v[0], v[1]); o.y = pack_bf16x2(v[2], v[3]); o.z = pack_bf16x2(v[4], v[5]); o.w = pack_bf16x2(v[6], v[7]);
-        buf_store16(rsC, off, o);
+        buf_store16<THROUGH>(rsC, off, o);
       }
     }
   }

@@ -128,10 +128,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(PipeArgs p
           cdf_pdf(v[e], cdf, pdf);
           dg[e] = cdf + v[e] * pdf; v[e] *= cdf;
         }
-        __builtin_amdgcn_raw_buffer_store_b128(pack8(dg), rsC, off, 0, 0);
-        __builtin_amdgcn_raw_buffer_store_b128(pack8(v), rsC2, off, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(pack8(dg), rsC, off, 0, THROUGH);
+        __builtin_amdgcn_raw_buffer_store_b128(pack8(v), rsC2, off, 0, THROUGH);
       } else {
-        __builtin_amdgcn_raw_buffer_store_b128(pack8(v), rsC, off, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(pack8(v), rsC, off, 0, THROUGH);
       }
     }
     asm volatile("" ::: "memory");

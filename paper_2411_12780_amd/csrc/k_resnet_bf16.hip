@@ -428,7 +428,7 @@ __global__ __launch_bounds__(256) void bn_apply_bf16_kernel(const uint16_t* x, s
     o[j] = pack2(fmaxf(u, 0.f), fmaxf(v, 0.f));
   }
   const uint4 ov = make_uint4(o[0], o[1], o[2], o[3]);
-  *reinterpret_cast<uint4*>(y + i * 8) = ov;
+  store_through(y + i * 8, ov);
   if (mask) mask[i] = relu_mask(ov);
 }
 
@@ -462,7 +462,7 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_bf16_kernel(const uint16_t* 
     }
     o[j] = pack2(r[0], r[1]);
   }
-  *reinterpret_cast<uint4*>(dx + i * 8) = make_uint4(o[0], o[1], o[2], o[3]);
+  store_through(dx + i * 8, make_uint4(o[0], o[1], o[2], o[3]));
 }
 
 // Small tensors: the apply kernels add up the partial sums themselves (every workgroup, in the same order;
@@ -491,7 +491,7 @@ __global__ __launch_bounds__(256) void bn_apply_fused_kernel(BnSumArgs p, unsign
     o[j] = pack2(fmaxf(u, 0.f), fmaxf(v, 0.f));
   }
   const uint4 ov = make_uint4(o[0], o[1], o[2], o[3]);
-  *reinterpret_cast<uint4*>(y + i * 8) = ov;
+  store_through(y + i * 8, ov);
   if (mask) mask[i] = relu_mask(ov);
 }
 __global__ __launch_bounds__(256) void bn_bwd_apply_fused_kernel(BnSumArgs p, unsigned nblocks, size_t chunks, const float* g,
@@ -525,7 +525,7 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_fused_kernel(BnSumArgs p, un
     }
     o[j] = pack2(r[0], r[1]);
   }
-  *reinterpret_cast<uint4*>(dx + i * 8) = make_uint4(o[0], o[1], o[2], o[3]);
+  store_through(dx + i * 8, make_uint4(o[0], o[1], o[2], o[3]));
 }
 
 // Elementwise helpers of the stage, 8 channels (16 bytes) per thread, 32-bit index arithmetic.
@@ -541,7 +541,7 @@ __global__ __launch_bounds__(256) void gap_bwd_bf16_kernel(const uint16_t* dpool
   uint32_t o[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) o[j] = pack2(lo_bf(w[j]) / hw, hi_bf(w[j]) / hw);
-  *reinterpret_cast<uint4*>(dx + (size_t)i * 8) = make_uint4(o[0], o[1], o[2], o[3]);
+  store_through(dx + (size_t)i * 8, make_uint4(o[0], o[1], o[2], o[3]));
 }
 
 // pooled[b, c] = mean over the HW pixels of x[b, p, c]: one workgroup per image, thread (channel group of 8, pixel
@@ -586,7 +586,7 @@ __global__ __launch_bounds__(256) void shortcut_fwd_bf16_kernel(const uint16_t* 
   const uint32_t cpr = Co / 8, cg = i % cpr, pix = i / cpr, ox = pix % Wo, oy = (pix / Wo) % Ho, b = pix / (Wo * Ho);
   uint4 v = make_uint4(0, 0, 0, 0);
   if (8 * cg < Ci) v = *reinterpret_cast<const uint4*>(x + ((size_t)(b * H + oy * stride) * W + ox * stride) * Ci + 8 * cg);
-  *reinterpret_cast<uint4*>(y + (size_t)i * 8) = v;
+  store_through(y + (size_t)i * 8, v);
 }
 
 // dx[b, oy*stride, ox*stride, c] += dy[b,oy,ox,c] * (ymask[b,oy,ox,c] > 0) for c < Ci
@@ -609,7 +609,7 @@ __global__ __launch_bounds__(256) void shortcut_bwd_bf16_kernel(const uint16_t* 
     const float hi = hi_bf(xw[j]) + (hi_bf(mw[j]) > 0.f ? hi_bf(dw[j]) : 0.f);
     o[j] = pack2(lo, hi);
   }
-  *reinterpret_cast<uint4*>(dx + xi) = make_uint4(o[0], o[1], o[2], o[3]);
+  store_through(dx + xi, make_uint4(o[0], o[1], o[2], o[3]));
 }
 
 bool al16(const void* p) { return !(((uintptr_t)p) & 15); }

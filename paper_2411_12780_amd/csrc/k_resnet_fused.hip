@@ -238,7 +238,7 @@ __global__ __launch_bounds__(64 * WAVES, C == 16 ? 4 : 1) void conv_bn_kernel(Co
         }
         if (off == CONV_OOB) o = make_uint4(0, 0, 0, 0);      // rows outside the image
         if (core) {
-          *reinterpret_cast<uint4*>((char*)p.mid + off) = o;
+          store_through((char*)p.mid + off, o);
           if (!BWD && p.mask_out) p.mask_out[off >> 4] = relu_mask(o);
         }
       }
