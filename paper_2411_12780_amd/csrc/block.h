@@ -106,6 +106,11 @@ struct Block {
   std::vector<void*> g_res, g_mid, d_h, d_qkv;
   void* d_u = nullptr;
   std::vector<GemmArgs> wgrad_jobs;   // weight-gradient products recorded during the backward pass
+  // Whether the order of the sums in those products is free.  AdamW moves a parameter by a whole step to whichever side a gradient of
+  // the size of its own rounding error falls; with sums in another order, four pipelined blocks of width 384 differ by 0.7 % (single
+  // gradients by as much as their rms) two steps on.  Its blocks keep the order of the 128 x 128 tiles; under SGD such blocks differ
+  // by 3e-7.
+  bool wgrad_any_order() const { return cfg.optimizer == PPLL_SGD; }
   // Side stream of the backward pass (created at first use, default priority).  The weight-gradient products of a
   // layer are launched there once the layer's backward is enqueued, so they run next to the input-gradient chain of
   // the layers below, which never reads them; the step's stream waits for the side stream before the update.

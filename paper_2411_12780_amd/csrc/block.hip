@@ -4,6 +4,7 @@
 #include "block.h"
 #include "plan.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -228,6 +229,7 @@ size_t Block::plan(char* base) {
     }
     if (dt == BF16) {   // parts of divided tiles of the weight-gradient launch at the end of the backward pass
       wgrad_ws_floats = gemm_mfma_balanced_floats();
+      if (wgrad_any_order()) wgrad_ws_floats = std::max(wgrad_ws_floats, gemm_big_grads_floats());
       wgrad_ws = wgrad_ws_floats ? bump.floats(wgrad_ws_floats) : nullptr;
     }
     int widest = 3 * D > F ? 3 * D : F;
@@ -584,7 +586,11 @@ int Block::vit_step(const void* x_in, const int32_t* labels, void* x_out, hipStr
       long tiles = 0;
       for (size_t j = first_job; j < wgrad_jobs.size(); ++j)
         tiles += (long)((wgrad_jobs[j].M + 127) / 128) * ((wgrad_jobs[j].N + 127) / 128);
-      if (tiles >= SIDE_MIN_TILES) PPLL_TRY(side_launch_wgrads(s));
+      // nor where the grouped launch runs on tiles of 384 x 192: those fill the chip by themselves and share no unit with the chain
+      // (width 768, 25216 rows: 5129 us a step with the side stream, 5035 without)
+      const bool big = wgrad_any_order() &&
+                       gemm_big_grads_choice(&wgrad_jobs[first_job], (int)(wgrad_jobs.size() - first_job), l + 1);
+      if (tiles >= SIDE_MIN_TILES && !big) PPLL_TRY(side_launch_wgrads(s));
     }
   }
   if (image) {
@@ -608,7 +614,7 @@ int Block::vit_step(const void* x_in, const int32_t* labels, void* x_out, hipStr
   }
   // ---- every recorded weight-gradient product, in one launch
   // (the only user of the workspace while it runs: the side stream's launches take none)
-  PPLL_TRY(launch_gemm_group(s, wgrad_jobs.data(), (int)wgrad_jobs.size(), wgrad_ws, wgrad_ws_floats));
+  PPLL_TRY(launch_gemm_group(s, wgrad_jobs.data(), (int)wgrad_jobs.size(), wgrad_ws, wgrad_ws_floats, wgrad_any_order()));
   wgrad_jobs.clear();
   PPLL_TRY(side_wait(s));
   return PPLL_OK;

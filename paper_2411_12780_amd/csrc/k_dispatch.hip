@@ -85,9 +85,9 @@ int launch_gemm(hipStream_t s, const GemmArgs& g) {
   return gemm_f32_supported(g) && g.a_sk == 1 ? launch_gemm_f32(s, g) : launch_gemm_generic(s, g);
 }
 
-int launch_gemm_group(hipStream_t s, const GemmArgs* gs, int n, float* ws, size_t ws_floats) {
+int launch_gemm_group(hipStream_t s, const GemmArgs* gs, int n, float* ws, size_t ws_floats, bool any_order) {
   if (n <= 0) return PPLL_OK;
-  return gs[0].a_dt == F32 ? launch_gemm_f32_grouped(s, gs, n) : launch_gemm_mfma_grouped(s, gs, n, ws, ws_floats);
+  return gs[0].a_dt == F32 ? launch_gemm_f32_grouped(s, gs, n) : launch_gemm_mfma_grouped(s, gs, n, ws, ws_floats, any_order);
 }
 
 int launch_attention_fwd(hipStream_t s, const void* qkv, int dt, int B, int T, int H, int dh, void* out, float* lse) {
@@ -145,4 +145,32 @@ extern "C" int ppll_internal_attention_cls(int B, int T, int H, int dh, const vo
   using namespace ppll;
   PPLL_TRY(launch_attention_cls_fwd((hipStream_t)stream, q, kv, BF16, B, T, H, dh, out, prob));
   return launch_attention_cls_bwd((hipStream_t)stream, q, kv, prob, dout, BF16, B, T, H, dh, dq, dkv);
+}
+
+// A set of weight-gradient products C[M,N] = A^T B on tiles of 384 x 192, divided as asked for, for tests of that kernel (no part of the
+// public interface).  shape: M, N, K, row strides of A [K][M], B [K][N] and C of each product; column sums of B where asked for.  The
+// tiles of reductions over more than 448 rows but the first `whole` run in `cuts` parts; ws_floats: room in ws.
+extern "C" int ppll_internal_weight_grads(int n, const int* shape, const void* const* A, const void* const* B, float* const* C,
+                                          float* const* colsum, float* ws, size_t ws_floats, int cuts, int whole, void* stream) {
+  using namespace ppll;
+  if (n < 1 || n > BIG_PRODUCTS || cuts < 1) { set_error("a set of %d products in %d parts", n, cuts); return PPLL_ERR_CONFIG; }
+  std::vector<GemmArgs> gs(n);
+  BigGradPlan plan{true, cuts, 0, 0, 0, 8};
+  for (int j = 0; j < n; ++j) {
+    const int* q = shape + 6 * j;
+    GemmArgs g{};
+    g.A = A[j]; g.a_dt = BF16; g.a_sm = 1; g.a_sk = q[3];
+    g.B = B[j]; g.b_dt = BF16; g.b_sk = q[4]; g.b_sn = 1;
+    g.C = C[j]; g.c_dt = F32; g.ldc = q[5]; g.M = q[0]; g.N = q[1]; g.K = q[2];
+    g.colsum = colsum[j];
+    if (!gemm_mfma_groupable(g)) { set_error("product %d is no weight gradient that the matrix-core kernels take", j); return PPLL_ERR_CONFIG; }
+    gs[j] = g;
+    const int tiles = (int)big_tiles({g.M, g.N, g.K});
+    plan.tiles += tiles;
+    if (wg_steps(g.K) >= plan.long_steps) plan.long_tiles += tiles;
+  }
+  plan.whole_tiles = cuts > 1 ? whole : plan.long_tiles;
+  const int rest = plan.long_tiles - plan.whole_tiles;
+  if (rest < 0 || (rest > 0 && (size_t)rest * cuts > ws_floats / gemm_big_grads_floats(1))) { set_error("the workspace is too small"); return PPLL_ERR_WORKSPACE; }
+  return launch_gemm_big_grads((hipStream_t)stream, gs.data(), n, ws, plan);
 }

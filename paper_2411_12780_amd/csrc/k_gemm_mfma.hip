@@ -26,6 +26,8 @@
 // Weight gradients (both operands [k][row], fp32 output, bias gradient folded in) go out as sets, several products a launch;
 // a set that does not fill the chip has some of its tiles divided along k, parts added in a fixed order by a second kernel, so
 // results are reproducible (no float atomics).
+#include <algorithm>
+
 #include "common.h"
 #include "gemm_pipe.h"
 #include "plan.h"
@@ -675,6 +677,7 @@ bool gemm_mfma_groupable(const GemmArgs& g) {
 static int balanced_workgroups() { return compute_units() / 8 * 8; }
 // room for the parts of the divided tiles: at most two per workgroup
 size_t gemm_mfma_balanced_floats() { return (size_t)balanced_workgroups() * 2 * SLOT_FLOATS; }
+size_t gemm_big_grads_floats() { return gemm_big_grads_floats(balanced_workgroups()); }
 
 static void fill_problem(GroupedProblem& q, const GemmArgs& g, int first_tile, int bn = BN) {
   q.A = (const uint16_t*)g.A; q.lda = (int)g.a_sk; q.B = (const uint16_t*)g.B; q.ldb = (int)g.b_sk;
@@ -687,19 +690,34 @@ static void fill_problem(GroupedProblem& q, const GemmArgs& g, int first_tile, i
   q.c_bytes = (uint32_t)(((long)(g.M - 1) * g.ldc + g.N) * 4);
 }
 
-int launch_gemm_mfma_grouped(hipStream_t s, const GemmArgs* gs, int n, float* ws, size_t ws_floats) {
+static std::vector<ProductShape> product_shapes(const GemmArgs* gs, int n, int times) {
+  std::vector<ProductShape> shapes((size_t)n * times);
+  for (size_t j = 0; j < shapes.size(); ++j) shapes[j] = {gs[j % n].M, gs[j % n].N, gs[j % n].K};
+  return shapes;
+}
+// 32-bit byte offsets also for the k rows of a last stage that do not exist
+static bool short_rows(const GemmArgs* gs, int n) {
+  for (int j = 0; j < n; ++j)
+    if (gs[j].a_sk > (1 << 20) || gs[j].b_sk > (1 << 20)) return false;
+  return true;
+}
+bool gemm_big_grads_choice(const GemmArgs* gs, int n, int times) {
+  return n > 0 && short_rows(gs, n) && big_grad_tiles(product_shapes(gs, n, times).data(), n * times, balanced_workgroups()).take;
+}
+
+int launch_gemm_mfma_grouped(hipStream_t s, const GemmArgs* gs, int n, float* ws, size_t ws_floats, bool any_order) {
   static OncePerDevice pipe_once, grouped_once, balanced_once;
   PPLL_TRY(raise_lds((const void*)gemm_pipe_grouped_kernel, PipeShape::LDS, pipe_once));
   PPLL_TRY(raise_lds((const void*)gemm_mfma_grouped_kernel, lds_bytes(true, true, 128), grouped_once));
   PPLL_TRY(raise_lds((const void*)gemm_mfma_balanced_kernel, lds_bytes(true, true, 128), balanced_once));
-  std::vector<ProductShape> shapes(n);
-  bool wide_ok = true;    // 32-bit byte offsets for the k rows of a last stage that do not exist
-  for (int j = 0; j < n; ++j) {
-    shapes[j] = {gs[j].M, gs[j].N, gs[j].K};
-    wide_ok = wide_ok && gs[j].a_sk <= (1 << 20) && gs[j].b_sk <= (1 << 20);
-  }
+  const std::vector<ProductShape> shapes = product_shapes(gs, n, 1);
+  const bool wide_ok = short_rows(gs, n);
   const int wgs = balanced_workgroups();
-  const bool workspace = ws && n <= GROUP_MAX && ws_floats >= (size_t)wgs * 2 * SLOT_FLOATS;
+  const bool workspace = ws && n <= GROUP_MAX && ws_floats >= gemm_mfma_balanced_floats();
+  if (any_order && wide_ok && ws && ws_floats >= gemm_big_grads_floats()) {
+    const BigGradPlan big = big_grad_tiles(shapes.data(), n, wgs);
+    if (big.take) return launch_gemm_big_grads(s, gs, n, ws, big);
+  }
   const WeightGradPlan plan = plan_weight_grads(shapes.data(), n, workspace, wide_ok, wgs);
   if (plan.cuts > 1) {
     BalancedArgs a{};

@@ -72,6 +72,42 @@ inline WeightGradPlan plan_weight_grads(const ProductShape* p, int n, bool works
   return w;
 }
 
+// ---- The same on tiles of 384 x 192, one workgroup a unit, in a launch that is the only one beside which nothing else runs
+constexpr int BIG_EDGE_M = 384, BIG_EDGE = 192, BIG_PRODUCTS = 40;   // products of a launch: their table stays below the 4 KB of a kernel's arguments
+struct BigGradPlan { bool take; int cuts, long_tiles, whole_tiles, tiles, long_steps; };   // as WeightGradPlan
+inline long big_tiles(const ProductShape& p) { return (long)((p.M + BIG_EDGE_M - 1) / BIG_EDGE_M) * ((p.N + BIG_EDGE - 1) / BIG_EDGE); }
+
+// Whether a set of products goes there, and how it is divided: the tiles beyond the last full round in as many parts each as find
+// a unit, of 8 steps of 64 k or more.  The rule compares what both kernels take, fits to 25 sets of 1 to 6 layers of width 192 to 768
+// with 1040 to 25216 rows on 256 units, in microseconds: here 1.96 a step of a round, 8 for the launch, and for divided tiles 4 and 0.107 a
+// part (295 KB written and read again); there 0.74 a step of 128 x 128 tiles and unit, 10, and 12 more where they are fewer than
+// 0.6 a unit.  Measured there / here: width 384, 3 + 1 layers, 4160 rows 72 / 80, 8320 rows 132 / 123, 9280 rows 148 / 132; 3 + 2 layers,
+// 5200 rows 125 / 105; width 768, 2 + 1 layers, 1040 rows 66 / 45.  Shorter reductions were not ahead (640 rows of width 768: 52 / 57).
+inline BigGradPlan big_grad_tiles(const ProductShape* p, int n, int units) {
+  BigGradPlan b{};
+  b.cuts = 1;
+  if (units < 8 || n < 1 || n > BIG_PRODUCTS) return b;
+  int longest = 0, narrow = 0;
+  for (int j = 0; j < n; ++j) longest = std::max(longest, wg_steps(p[j].K));
+  b.long_steps = std::max(8, (longest + 3) / 4);
+  double there = 0.0;
+  for (int j = 0; j < n; ++j) {
+    b.tiles += (int)big_tiles(p[j]);
+    if (wg_steps(p[j].K) < b.long_steps) continue;
+    b.long_tiles += (int)big_tiles(p[j]);
+    narrow += (int)wg_tiles(p[j], WG_EDGE);
+    there += 0.74 * wg_tiles(p[j], WG_EDGE) * wg_steps(p[j].K) / units;
+  }
+  there += 10.0 + (narrow < 0.6 * units ? 12.0 : 0.0);
+  const int rest = b.long_tiles % units;
+  if (rest) b.cuts = std::max(1, std::min(units / rest, longest / 8));
+  b.whole_tiles = b.cuts > 1 ? b.long_tiles - rest : b.long_tiles;
+  const double rounds = b.long_tiles / units + (rest ? 1.0 / b.cuts : 0.0);
+  const double here = 1.96 * rounds * longest + 8.0 + (b.cuts > 1 ? 4.0 + 0.107 * rest * b.cuts : 0.0);
+  b.take = longest >= 16 && here < there;
+  return b;
+}
+
 // ---- A product with few output tiles, on the kernel whose waves split k: 32 x 32 tiles, one per compute unit at most, else 32 x
 // 64 ones, one per unit at most; up to 256 rows always, beyond that only where the width or the reduction is at most 384.  The
 // alternative is the kernel with copying waves (split_tiles, next), below 128 of K the tiled one.  Microseconds alone on 256 units,

@@ -573,6 +573,12 @@ def test_weight_gradients_on_the_side_stream_bf16():
     run_case(synth.workload("vit_base_224_bf16", batch=21, depth=1, aux_depth=1), steps=2)
 
 
+def test_weight_gradients_on_the_side_stream_under_adamw_bf16():
+    # the same under AdamW, whose blocks keep the side stream where SGD's have one launch of bigger tiles at the end
+    run_case(synth.workload("vit_base_224_bf16", batch=21, depth=1, aux_depth=1, optimizer=synth.ADAMW, momentum=0.0, nesterov=0,
+                            weight_decay=0.01, lr=1e-3), steps=2)
+
+
 def test_vit_large_image_bf16_full_size():
     run_case(synth.workload("vit_large_image_bf16"), steps=1)
 

@@ -147,3 +147,44 @@ def test_products_that_the_split_kernel_does_not_take_are_refused():
     for status, C, C2 in (product(SPLIT, A[:, :120], B[:120], 1, None, None, NONE, None),     # a reduction below 128
                           product(SPLIT, A, B, 1, None, side, DGELU, side)):                  # residual and saved derivative at once
         assert status == 2 and bool((C == 7.0).all()) and bool((C2 == 7.0).all())
+
+
+@pytest.mark.parametrize("cuts,whole,shapes", [
+    # M, N, K (and how much further apart the rows of A, B and C are): edges of the 384 x 192 tile, of a stage of 32 k, of the four
+    # stages in flight; parts of unequal length, and one of none; long and short reductions in a set, in either order
+    (1, 0, [(8, 8, 1, 0, 0, 0), (384, 192, 32, 0, 0, 0), (48, 200, 33, 8, 0, 8), (392, 184, 97, 0, 16, 0)]),
+    (3, 0, [(384, 192, 520, 0, 0, 0), (200, 400, 1000, 8, 8, 4)]),
+    (4, 2, [(768, 384, 449, 0, 0, 0), (136, 72, 128, 0, 0, 0), (400, 200, 640, 0, 8, 8)]),
+    (16, 0, [(48, 64, 4500, 0, 0, 0)]),
+    (12, 0, [(56, 8, 520, 0, 0, 0)]),
+])
+def test_weight_gradients_on_big_tiles(cuts, whole, shapes):
+    g = torch.Generator(device="cuda").manual_seed(cuts * 100 + len(shapes))
+    n = len(shapes)
+    rnd = lambda r, c, pad: torch.randn(r, c + pad, generator=g, device="cuda").to(torch.bfloat16)
+    A = [rnd(K, M, pa) for M, N, K, pa, pb, pc in shapes]
+    B = [rnd(K, N, pb) for M, N, K, pa, pb, pc in shapes]
+    C = [torch.full((M, N + pc), 7.0, device="cuda") for M, N, K, pa, pb, pc in shapes]
+    sums = [torch.full((N,), 7.0, device="cuda") if j != 1 else None for j, (M, N, K, pa, pb, pc) in enumerate(shapes)]
+    ws = torch.full((384 * 192 * 40,), float("nan"), device="cuda")
+    f = P.lib().ppll_internal_weight_grads
+    f.restype = ctypes.c_int
+    flat = (ctypes.c_int * (6 * n))(*[v for M, N, K, pa, pb, pc in shapes for v in (M, N, K, M + pa, N + pb, N + pc)])
+    ptrs = lambda ts: (ctypes.c_void_p * n)(*[None if t is None else t.data_ptr() for t in ts])
+    f.argtypes = [ctypes.c_int] + [ctypes.c_void_p] * 6 + [ctypes.c_size_t, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
+    call = lambda: f(n, flat, ptrs(A), ptrs(B), ptrs(C), ptrs(sums), ws.data_ptr(), ws.numel(), cuts, whole, torch.cuda.current_stream().cuda_stream)
+    assert call() == 0
+    torch.cuda.synchronize()
+    for (M, N, K, pa, pb, pc), a, b, c, s in zip(shapes, A, B, C, sums):
+        a, b = a[:, :M].double(), b[:, :N].double()
+        # fp32 sums of K terms in any order, on the scale of the sum of their magnitudes
+        ref, size = a.t().contiguous() @ b, a.t().contiguous().abs() @ b.abs()
+        assert bool(((c[:, :N].double() - ref).abs() <= size * (K * 2.0 ** -24) + 1e-6).all())
+        assert bool((c[:, N:] == 7.0).all())
+        if s is not None:
+            assert bool(((s.double() - b.sum(0)).abs() <= b.abs().sum(0) * (K * 2.0 ** -24) + 1e-6).all())
+    first = [c.clone() for c in C]
+    assert call() == 0 and all(torch.equal(x, c) for x, c in zip(first, C))
+    no_room = f(n, flat, ptrs(A), ptrs(B), ptrs(C), ptrs(sums), ws.data_ptr(), 0, 2, 0, torch.cuda.current_stream().cuda_stream)
+    assert no_room == (4 if any(s[2] > 448 for s in shapes) else 0)
+    torch.cuda.synchronize()

@@ -22,6 +22,13 @@ int main() {
       for (ProductShape& q : p) if (std::scanf("%d %d %d", &q.M, &q.N, &q.K) != 3) return 1;
       const WeightGradPlan w = plan_weight_grads(p.data(), n, workspace, true, units);
       std::printf("%d %d %d %d %d %d\n", w.wide, w.cuts, w.long_tiles, w.whole_tiles, w.tiles, w.long_steps);
+    } else if (!std::strcmp(what, "big")) {
+      int units, n;
+      if (std::scanf("%d %d", &units, &n) != 2) return 1;
+      std::vector<ProductShape> p(n);
+      for (ProductShape& q : p) if (std::scanf("%d %d %d", &q.M, &q.N, &q.K) != 3) return 1;
+      const BigGradPlan b = big_grad_tiles(p.data(), n, units);
+      std::printf("%d %d %d %d %d %d\n", b.take, b.cuts, b.long_tiles, b.whole_tiles, b.tiles, b.long_steps);
     } else if (!std::strcmp(what, "product")) {
       int M, N, K, end, units;
       if (std::scanf("%d %d %d %d %d", &M, &N, &K, &end, &units) != 5) return 1;
@@ -97,6 +104,35 @@ def test_every_tile_is_planned_once_and_the_parts_fit_the_workspace(plan):
                         assert not w["wide"]
                         assert (w["long_tiles"] - w["whole_tiles"]) * w["cuts"] <= 2 * UNITS
                         assert min(s for s in steps if s >= w["long_steps"]) // w["cuts"] >= (8 if w["cuts"] > 8 else 4)
+
+
+def big_grad_plan(plan, products, units=UNITS):
+    names = ("take", "cuts", "long_tiles", "whole_tiles", "tiles", "long_steps")
+    return dict(zip(names, plan("big", units, len(products), *(v for p in products for v in p))))
+
+
+@pytest.mark.parametrize("rows,dim,layers,pruned,take", [
+    # where they were measured to be ahead, and where not
+    (8320, 384, 3, True, 1), (9280, 384, 3, True, 1), (16640, 384, 3, True, 1), (5200, 384, 4, True, 1), (4160, 384, 3, True, 0),
+    (2080, 384, 3, True, 0), (1040, 768, 2, True, 1), (6304, 768, 1, True, 1), (640, 768, 3, True, 0), (25216, 192, 3, True, 1),
+])
+def test_weight_gradients_go_to_big_tiles_where_those_are_ahead(plan, rows, dim, layers, pruned, take):
+    assert big_grad_plan(plan, block_products(rows // 5, 5, dim, layers, pruned))["take"] == take
+
+
+def test_every_big_tile_is_planned_once_and_the_parts_fill_a_round_at_most(plan):
+    for rows in (5, 325, 1040, 8320, 25216, 130000):
+        for dim in (64, 192, 200, 384, 768, 1024):
+            for layers, pruned in ((1, False), (3, True), (7, True)):
+                products = block_products(rows // 5, 5, dim, layers, pruned)
+                b = big_grad_plan(plan, products)
+                assert b["tiles"] == sum(-(-m // 384) * -(-n // 192) for m, n, _ in products)
+                assert 0 <= b["whole_tiles"] <= b["long_tiles"] <= b["tiles"] and b["cuts"] >= 1
+                rest = b["long_tiles"] - b["whole_tiles"]
+                assert rest * b["cuts"] <= UNITS and (rest > 0) == (b["cuts"] > 1)
+                if b["cuts"] > 1:      # none of the divided reductions is left with less than two steps of 64 a part
+                    assert min(-(-k // 64) for m, n, k in products if -(-k // 64) >= b["long_steps"]) // b["cuts"] >= 2
+    assert big_grad_plan(plan, block_products(100, 65, 384, 10, True))["take"] == 0       # more products than a launch takes
 
 
 @pytest.mark.parametrize("rows,cuts", [(8320, 16), (131072, 36), (262144, 36), (1048576, 36)])
