@@ -184,7 +184,8 @@ int launch_gemm_generic(hipStream_t s, const GemmArgs& g);
 // Products with few output rows (the class-token rows of a pruned auxiliary layer): see k_gemm_rows.hip
 bool gemm_rows_supported(const GemmArgs& g);
 int launch_gemm_rows(hipStream_t s, const GemmArgs& g);
-// Products with many output tiles, bf16 output: see k_gemm_pipe.hip.  The choice (0: not this kernel) goes to the launch.
+// Products with many output tiles, bf16 output: see k_gemm_pipe.hip.  The choice (rows of a tile / 32, 0: not this kernel) goes to the
+// launch.
 int gemm_pipe_choice(const GemmArgs& g);
 bool gemm_pipe_supported(const GemmArgs& g);
 int launch_gemm_pipe(hipStream_t s, const GemmArgs& g, int choice);

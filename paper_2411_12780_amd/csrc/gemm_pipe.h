@@ -34,17 +34,18 @@ __device__ __forceinline__ void barrier() {
 
 // One operand: ROWS rows (m or n) x KS k per stage.
 //  TR = false: k contiguous in memory.  LDS [row][32 k], 64 bytes a row; the 16-byte granule g of row r sits at
-//    g ^ ((r / 4) % 4): 16 lanes reading one granule of 16 rows hit every bank once.
+//    g ^ ((r / 4) % 4): 16 lanes reading one granule of 16 rows hit every bank once.  (64 k a stage: 128 bytes a row, a whole cache
+//    line, g at g ^ ((r / 2) % 8).)
 //  TR = true: row index contiguous.  LDS [32 k][ROWS] as in memory; the 64-byte window w of k row k sits at w ^ (k % 4):
 //    the transposing read (16 lanes hand in 4 k rows x 32 bytes) of 8 k rows then spreads over all banks.
 // A copy instruction of a wave fills 1 KB of LDS in lane order, so the permutations are applied to the addresses that the
 // lanes fetch from; they stay inside one row segment, i.e. inside one cache line.
-template <bool TR, int ROWS> struct Operand {
-  static_assert(!TR || ROWS == 128 || ROWS == 256, "");
-  static constexpr int BYTES = ROWS * KS * 2;
+template <bool TR, int ROWS, int KT = KS> struct Operand {
+  static_assert((!TR || ROWS == 128 || ROWS == 256) && (KT == 32 || KT == 64), "");
+  static constexpr int BYTES = ROWS * KT * 2;
   static constexpr int COPIES = BYTES / 1024;            // wave instructions per stage
-  static constexpr int PITCH = TR ? ROWS * 2 : 64;
-  static constexpr int STEP_ROWS = TR ? 1024 / PITCH : 16;   // k rows (rows) per copy instruction
+  static constexpr int PITCH = TR ? ROWS * 2 : KT * 2;
+  static constexpr int STEP_ROWS = 1024 / PITCH;         // k rows (rows) per copy instruction
   int vbase;      // byte offset this lane fetches from at k = 0, copy 0
   int gk;         // TR = false: first k (within the stage) of the lane's granule
   int ld2;        // bytes between rows (TR: between k rows)
@@ -58,22 +59,22 @@ template <bool TR, int ROWS> struct Operand {
       const int col = row0 + (win * 4 + (slot & 3)) * 8;
       vbase = col < nrows ? kr * ld2 + col * 2 : OOB_BASE;
       gk = kr;
-    } else {
-      const int g = (lane & 3) ^ ((lane >> 4) & 3);
+    } else {                                             // rows past the last one lie past the end of the buffer
+      const int g = KT == 32 ? (lane & 3) ^ ((lane >> 4) & 3) : (lane & 7) ^ ((lane >> 4) + 4 * (wave & 1));
       gk = g * 8;
-      vbase = (row0 + (lane >> 2)) * ld2 + g * 16;       // rows past the last one lie past the end of the buffer
+      vbase = (row0 + lane / (PITCH / 16)) * ld2 + g * 16;
     }
   }
 };
 
 // A workgroup of WGM_ x WGN_ waves, each 32 IM_ x 64 of the output tile, and NS_ stages in LDS
-template <bool AT, bool BT, int WGM_, int WGN_, int IM_, int NS_> struct Shape {
-  static constexpr int WGN = WGN_, IM = IM_, NS = NS_, W = WGM_ * WGN_, THREADS = 64 * W, BM = WGM_ * IM * 32, BN = WGN_ * 64;
-  using OA = Operand<AT, BM>;
-  using OB = Operand<BT, BN>;
+template <bool AT, bool BT, int WGM_, int WGN_, int IM_, int NS_, int KT_ = KS> struct Shape {
+  static constexpr int KT = KT_, WGN = WGN_, IM = IM_, NS = NS_, W = WGM_ * WGN_, THREADS = 64 * W, BM = WGM_ * IM * 32, BN = WGN_ * 64;
+  using OA = Operand<AT, BM, KT>;
+  using OB = Operand<BT, BN, KT>;
   static constexpr int STAGE = OA::BYTES + OB::BYTES, LDS = NS * STAGE;
   static constexpr int COPIES = OA::COPIES / W + OB::COPIES / W;   // per wave and stage, of some waves one more
-  static_assert(OB::COPIES % W == 0 && (!AT || OA::COPIES % W == 0) && W % 2 == 0 && NS >= 3, "");
+  static_assert(OB::COPIES % W == 0 && (!AT || OA::COPIES % W == 0) && W % 2 == 0 && (KT == 32 ? NS >= 3 : NS == 2 && W == 8), "");
 };
 
 // The fragments (8 consecutive k of one row per lane) of a wave's tile, 32 IM rows of A and 64 of B, at one k step of 16.  A
@@ -89,12 +90,13 @@ template <int N> struct Frags<true, N> {
 template <int N> __device__ __forceinline__ void set_zero(Frags<false, N>& f, int i) { f.v[i] = (u32x4){0, 0, 0, 0}; }
 template <int N> __device__ __forceinline__ void set_zero(Frags<true, N>& f, int i) { f.lo[i] = f.hi[i] = (u32x2){0, 0}; }
 // Lane address of MFMA tile 0 of a wave (rows row0 .. row0 + 31, row0 a multiple of 32 x tiles of the wave), k step 0, stage 0
-template <bool TR, int ROWS> __device__ __forceinline__ int frag_base(int region, int row0, int lane) {
+template <bool TR, int ROWS, int KT = KS> __device__ __forceinline__ int frag_base(int region, int row0, int lane) {
   if (TR) {
     const int kr = 8 * (lane >> 5) + ((lane & 15) >> 2);
     return region + kr * (ROWS * 2) + (((row0 >> 5) ^ (kr & 3)) << 6) + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
   }
   const int r = lane & 31;
+  if (KT == 64) return region + (row0 + r) * 128 + (((lane >> 5) ^ ((r >> 1) & 7)) << 4);
   return region + (row0 + r) * 64 + (((lane >> 5) ^ ((r >> 2) & 3)) << 4);
 }
 
@@ -106,54 +108,55 @@ template <bool TR, int ROWS> __device__ __forceinline__ int frag_base(int region
 #define PPLL_ACC [c00] "+v"(acc[0][0]), [c01] "+v"(acc[0][1]), [c02] "+v"(acc[0][2]), [c03] "+v"(acc[0][3]), \
                  [c10] "+v"(acc[1][0]), [c11] "+v"(acc[1][1]), [c12] "+v"(acc[1][2]), [c13] "+v"(acc[1][3])
 #define PPLL_CUR [p0] "v"(a.get(0)), [p1] "v"(a.get(1)), [p2] "v"(a.get(2)), [p3] "v"(a.get(3)), [q0] "v"(b.get(0)), [q1] "v"(b.get(1))
-template <bool AT, bool BT, int ROWS_A, int ROWS_B, int KK, int IM>
+#define PPLL_ROWS [r1] "n"(R32), [r2] "n"(2 * R32), [r3] "n"(3 * R32), [r4] "n"(4 * R32)
+template <bool AT, bool BT, int ROWS_A, int ROWS_B, int KK, int IM, int KT = KS>
 __device__ __forceinline__ void k_step(f32x16 (&acc)[2][IM], const Frags<AT, IM>& a, const Frags<BT, 2>& b, Frags<AT, IM>& na, Frags<BT, 2>& nb,
                                        int addrA, int addrB) {
   static_assert(IM == 4 || (IM == 5 && !AT), "");
-  constexpr int PA = ROWS_A * 2, PB = ROWS_B * 2;
+  constexpr int PA = ROWS_A * 2, PB = ROWS_B * 2, R32 = 64 * KT;     // bytes of 32 rows with k contiguous
   if constexpr (IM == 5 && BT) {
     asm volatile("s_nop 1\n" PPLL_MMA(0, 0)
                  "ds_read_b64_tr_b16 %[l0], %[rb0] offset:%[ol]\n ds_read_b64_tr_b16 %[h0], %[rb0] offset:%[oh]\n" PPLL_MMA(0, 1)
-                 "ds_read_b128 %[x0], %[ra]\n ds_read_b128 %[x1], %[ra] offset:2048\n" PPLL_MMA(0, 2)
-                 "ds_read_b128 %[x2], %[ra] offset:4096\n ds_read_b128 %[x3], %[ra] offset:6144\n" PPLL_MMA(0, 3)
-                 "ds_read_b128 %[x4], %[ra] offset:8192\n ds_read_b64_tr_b16 %[l1], %[rb1] offset:%[ol]\n" PPLL_MMA(0, 4)
+                 "ds_read_b128 %[x0], %[ra]\n ds_read_b128 %[x1], %[ra] offset:%[r1]\n" PPLL_MMA(0, 2)
+                 "ds_read_b128 %[x2], %[ra] offset:%[r2]\n ds_read_b128 %[x3], %[ra] offset:%[r3]\n" PPLL_MMA(0, 3)
+                 "ds_read_b128 %[x4], %[ra] offset:%[r4]\n ds_read_b64_tr_b16 %[l1], %[rb1] offset:%[ol]\n" PPLL_MMA(0, 4)
                  "ds_read_b64_tr_b16 %[h1], %[rb1] offset:%[oh]\n"
                  PPLL_MMA(1, 0) PPLL_MMA(1, 1) PPLL_MMA(1, 2) PPLL_MMA(1, 3) PPLL_MMA(1, 4) "s_waitcnt lgkmcnt(0)"
                  : PPLL_ACC, [c04] "+v"(acc[0][4]), [c14] "+v"(acc[1][4]), [x0] "=&v"(na.v[0]), [x1] "=&v"(na.v[1]), [x2] "=&v"(na.v[2]),
                    [x3] "=&v"(na.v[3]), [x4] "=&v"(na.v[4]), [l0] "=&v"(nb.lo[0]), [h0] "=&v"(nb.hi[0]), [l1] "=&v"(nb.lo[1]), [h1] "=&v"(nb.hi[1])
-                 : PPLL_CUR, [p4] "v"(a.get(4)), [ra] "v"(KK ? addrA ^ 32 : addrA), [rb0] "v"(addrB), [rb1] "v"(addrB ^ 64),
-                   [ol] "n"(KK * 16 * PB), [oh] "n"(KK * 16 * PB + 4 * PB)
+                 : PPLL_CUR, [p4] "v"(a.get(4)), [ra] "v"(KK ? addrA ^ (32 * KK) : addrA), [rb0] "v"(addrB), [rb1] "v"(addrB ^ 64),
+                   [ol] "n"(KK * 16 * PB), [oh] "n"(KK * 16 * PB + 4 * PB), PPLL_ROWS
                  : "memory");
   } else if constexpr (IM == 5) {
     asm volatile("s_nop 1\n" PPLL_MMA(0, 0) "ds_read_b128 %[y0], %[rb]\n ds_read_b128 %[x0], %[ra]\n" PPLL_MMA(0, 1)
-                 "ds_read_b128 %[x1], %[ra] offset:2048\n ds_read_b128 %[x2], %[ra] offset:4096\n" PPLL_MMA(0, 2)
-                 "ds_read_b128 %[x3], %[ra] offset:6144\n ds_read_b128 %[x4], %[ra] offset:8192\n" PPLL_MMA(0, 3)
-                 "ds_read_b128 %[y1], %[rb] offset:2048\n" PPLL_MMA(0, 4)
+                 "ds_read_b128 %[x1], %[ra] offset:%[r1]\n ds_read_b128 %[x2], %[ra] offset:%[r2]\n" PPLL_MMA(0, 2)
+                 "ds_read_b128 %[x3], %[ra] offset:%[r3]\n ds_read_b128 %[x4], %[ra] offset:%[r4]\n" PPLL_MMA(0, 3)
+                 "ds_read_b128 %[y1], %[rb] offset:%[r1]\n" PPLL_MMA(0, 4)
                  PPLL_MMA(1, 0) PPLL_MMA(1, 1) PPLL_MMA(1, 2) PPLL_MMA(1, 3) PPLL_MMA(1, 4) "s_waitcnt lgkmcnt(0)"
                  : PPLL_ACC, [c04] "+v"(acc[0][4]), [c14] "+v"(acc[1][4]), [x0] "=&v"(na.v[0]), [x1] "=&v"(na.v[1]), [x2] "=&v"(na.v[2]),
                    [x3] "=&v"(na.v[3]), [x4] "=&v"(na.v[4]), [y0] "=&v"(nb.v[0]), [y1] "=&v"(nb.v[1])
-                 : PPLL_CUR, [p4] "v"(a.get(4)), [ra] "v"(KK ? addrA ^ 32 : addrA), [rb] "v"(KK ? addrB ^ 32 : addrB)
+                 : PPLL_CUR, [p4] "v"(a.get(4)), [ra] "v"(KK ? addrA ^ (32 * KK) : addrA), [rb] "v"(KK ? addrB ^ (32 * KK) : addrB), PPLL_ROWS
                  : "memory");
   } else if constexpr (!AT && BT) {
     asm volatile("s_nop 1\n" PPLL_MMA(0, 0)
                  "ds_read_b64_tr_b16 %[l0], %[rb0] offset:%[ol]\n ds_read_b64_tr_b16 %[h0], %[rb0] offset:%[oh]\n" PPLL_MMA(0, 1)
-                 "ds_read_b128 %[x0], %[ra]\n ds_read_b128 %[x1], %[ra] offset:2048\n" PPLL_MMA(0, 2)
-                 "ds_read_b128 %[x2], %[ra] offset:4096\n ds_read_b128 %[x3], %[ra] offset:6144\n" PPLL_MMA(0, 3)
+                 "ds_read_b128 %[x0], %[ra]\n ds_read_b128 %[x1], %[ra] offset:%[r1]\n" PPLL_MMA(0, 2)
+                 "ds_read_b128 %[x2], %[ra] offset:%[r2]\n ds_read_b128 %[x3], %[ra] offset:%[r3]\n" PPLL_MMA(0, 3)
                  "ds_read_b64_tr_b16 %[l1], %[rb1] offset:%[ol]\n ds_read_b64_tr_b16 %[h1], %[rb1] offset:%[oh]\n"
                  PPLL_MMA(1, 0) PPLL_MMA(1, 1) PPLL_MMA(1, 2) PPLL_MMA(1, 3) "s_waitcnt lgkmcnt(0)"
                  : PPLL_ACC, [x0] "=&v"(na.v[0]), [x1] "=&v"(na.v[1]), [x2] "=&v"(na.v[2]), [x3] "=&v"(na.v[3]),
                    [l0] "=&v"(nb.lo[0]), [h0] "=&v"(nb.hi[0]), [l1] "=&v"(nb.lo[1]), [h1] "=&v"(nb.hi[1])
-                 : PPLL_CUR, [ra] "v"(KK ? addrA ^ 32 : addrA), [rb0] "v"(addrB), [rb1] "v"(addrB ^ 64), [ol] "n"(KK * 16 * PB),
-                   [oh] "n"(KK * 16 * PB + 4 * PB)
+                 : PPLL_CUR, [ra] "v"(KK ? addrA ^ (32 * KK) : addrA), [rb0] "v"(addrB), [rb1] "v"(addrB ^ 64), [ol] "n"(KK * 16 * PB),
+                   [oh] "n"(KK * 16 * PB + 4 * PB), PPLL_ROWS
                  : "memory");
   } else if constexpr (!AT && !BT) {
     asm volatile("s_nop 1\n" PPLL_MMA(0, 0) "ds_read_b128 %[y0], %[rb]\n ds_read_b128 %[x0], %[ra]\n" PPLL_MMA(0, 1)
-                 "ds_read_b128 %[x1], %[ra] offset:2048\n ds_read_b128 %[x2], %[ra] offset:4096\n" PPLL_MMA(0, 2)
-                 "ds_read_b128 %[x3], %[ra] offset:6144\n ds_read_b128 %[y1], %[rb] offset:2048\n" PPLL_MMA(0, 3)
+                 "ds_read_b128 %[x1], %[ra] offset:%[r1]\n ds_read_b128 %[x2], %[ra] offset:%[r2]\n" PPLL_MMA(0, 2)
+                 "ds_read_b128 %[x3], %[ra] offset:%[r3]\n ds_read_b128 %[y1], %[rb] offset:%[r1]\n" PPLL_MMA(0, 3)
                  PPLL_MMA(1, 0) PPLL_MMA(1, 1) PPLL_MMA(1, 2) PPLL_MMA(1, 3) "s_waitcnt lgkmcnt(0)"
                  : PPLL_ACC, [x0] "=&v"(na.v[0]), [x1] "=&v"(na.v[1]), [x2] "=&v"(na.v[2]), [x3] "=&v"(na.v[3]), [y0] "=&v"(nb.v[0]),
                    [y1] "=&v"(nb.v[1])
-                 : PPLL_CUR, [ra] "v"(KK ? addrA ^ 32 : addrA), [rb] "v"(KK ? addrB ^ 32 : addrB)
+                 : PPLL_CUR, [ra] "v"(KK ? addrA ^ (32 * KK) : addrA), [rb] "v"(KK ? addrB ^ (32 * KK) : addrB), PPLL_ROWS
                  : "memory");
   } else {
     static_assert(AT && BT, "");
@@ -177,6 +180,7 @@ __device__ __forceinline__ void k_step(f32x16 (&acc)[2][IM], const Frags<AT, IM>
 #undef PPLL_MMA
 #undef PPLL_ACC
 #undef PPLL_CUR
+#undef PPLL_ROWS
 
 // acc[jn][im]: C^T tiles (the B fragment goes first into the MFMA): lane l holds row im*32 + l%32, columns jn*32 + 8 q +
 // 4 (l/32) + e in element 4 q + e.  csum[jn] (COLSUM, wave-uniform do_colsum): this lane's share, k % 8 = e of its half of every
@@ -185,8 +189,8 @@ template <class S, bool AT, bool BT, bool COLSUM>
 __device__ __forceinline__ void multiply(const __amdgpu_buffer_rsrc_t rsA, const __amdgpu_buffer_rsrc_t rsB, long lda, long ldb,
                                          int m0, int n0, int M, int N, int K, lds_char* lds, f32x16 (&acc)[2][S::IM],
                                          float (&csum)[2][8], bool do_colsum) {
-  constexpr int NS = S::NS, IM = S::IM;
-  const int nk = (K + KS - 1) / KS;
+  constexpr int NS = S::NS, IM = S::IM, KT = S::KT;
+  const int nk = (K + KT - 1) / KT;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / S::WGN, wn = wave % S::WGN;
@@ -197,7 +201,7 @@ __device__ __forceinline__ void multiply(const __amdgpu_buffer_rsrc_t rsA, const
   oa.init(lda, m0, M, lane, wave);
   ob.init(ldb, n0, N, lane, wave);
   auto issue = [&](int i) {       // copies of stage i (all zeros past the last one)
-    const int k0 = i * KS;
+    const int k0 = i * KT;
     const bool live = i < nk;
     lds_char* st = lds + (i % NS) * S::STAGE;
     int va, vb;                   // k rows past the last one of an operand stored by k lie past the end of its buffer
@@ -217,7 +221,7 @@ __device__ __forceinline__ void multiply(const __amdgpu_buffer_rsrc_t rsA, const
     }
   };
   const int base = (int)(uintptr_t)lds;
-  const int fa0 = frag_base<AT, S::BM>(base, wm * IM * 32, lane), fb0 = frag_base<BT, S::BN>(base + OA::BYTES, wn * 64, lane);
+  const int fa0 = frag_base<AT, S::BM, KT>(base, wm * IM * 32, lane), fb0 = frag_base<BT, S::BN, KT>(base + OA::BYTES, wn * 64, lane);
   Frags<AT, IM> a0, a1;
   Frags<BT, 2> b0, b1;
   auto column_sums = [&](const Frags<BT, 2>& b) {
@@ -229,25 +233,48 @@ __device__ __forceinline__ void multiply(const __amdgpu_buffer_rsrc_t rsA, const
       for (int e = 0; e < 4; ++e) { csum[j][2 * e] += __uint_as_float(v[e] << 16); csum[j][2 * e + 1] += __uint_as_float(v[e] & 0xffff0000u); }
     }
   };
+  if constexpr (KT == 32) {
 #pragma unroll
-  for (int i = 0; i < NS - 1; ++i) issue(i);
-  wait_vm<(NS - 2) * S::COPIES>();
-  barrier();
-  // the first fragments: products with zeros under the reads (the accumulators stay zero)
+    for (int i = 0; i < NS - 1; ++i) issue(i);
+    wait_vm<(NS - 2) * S::COPIES>();
+    barrier();
+    // the first fragments: products with zeros under the reads (the accumulators stay zero)
 #pragma unroll
-  for (int i = 0; i < IM; ++i) set_zero(a1, i);
+    for (int i = 0; i < IM; ++i) set_zero(a1, i);
 #pragma unroll
-  for (int j = 0; j < 2; ++j) set_zero(b1, j);
-  k_step<AT, BT, S::BM, S::BN, 0, IM>(acc, a1, b1, a0, b0, fa0, fb0);
-  for (int i = 0; i < nk; ++i) {
-    const int st = (i % NS) * S::STAGE, nx = ((i + 1) % NS) * S::STAGE;
-    wait_vm<(NS - 3) * S::COPIES>();       // this wave's part of stage i + 1 is in LDS
-    barrier();          // and everyone's; nobody reads stage i - 1 any more
-    issue(i + NS - 1);
-    column_sums(b0);
-    k_step<AT, BT, S::BM, S::BN, 1, IM>(acc, a0, b0, a1, b1, fa0 + st, fb0 + st);
-    column_sums(b1);
-    k_step<AT, BT, S::BM, S::BN, 0, IM>(acc, a1, b1, a0, b0, fa0 + nx, fb0 + nx);
+    for (int j = 0; j < 2; ++j) set_zero(b1, j);
+    k_step<AT, BT, S::BM, S::BN, 0, IM>(acc, a1, b1, a0, b0, fa0, fb0);
+    for (int i = 0; i < nk; ++i) {
+      const int st = (i % NS) * S::STAGE, nx = ((i + 1) % NS) * S::STAGE;
+      wait_vm<(NS - 3) * S::COPIES>();       // this wave's part of stage i + 1 is in LDS
+      barrier();          // and everyone's; nobody reads stage i - 1 any more
+      issue(i + NS - 1);
+      column_sums(b0);
+      k_step<AT, BT, S::BM, S::BN, 1, IM>(acc, a0, b0, a1, b1, fa0 + st, fb0 + st);
+      column_sums(b1);
+      k_step<AT, BT, S::BM, S::BN, 0, IM>(acc, a1, b1, a0, b0, fa0 + nx, fb0 + nx);
+    }
+  } else {
+    // two stages of 64 k: one is filled from the moment that everyone has read it until the same point a stage later
+    issue(0);
+    issue(1);
+    wait_vm<S::COPIES>();
+    barrier();
+#pragma unroll
+    for (int i = 0; i < IM; ++i) set_zero(a1, i);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) set_zero(b1, j);
+    k_step<AT, BT, S::BM, S::BN, 0, IM, KT>(acc, a1, b1, a0, b0, fa0, fb0);
+    for (int i = 0; i < nk; ++i) {
+      const int st = (i & 1) * S::STAGE, nx = S::STAGE - st;
+      k_step<AT, BT, S::BM, S::BN, 1, IM, KT>(acc, a0, b0, a1, b1, fa0 + st, fb0 + st);
+      k_step<AT, BT, S::BM, S::BN, 2, IM, KT>(acc, a1, b1, a0, b0, fa0 + st, fb0 + st);
+      k_step<AT, BT, S::BM, S::BN, 3, IM, KT>(acc, a0, b0, a1, b1, fa0 + st, fb0 + st);
+      wait_vm<0>();         // this wave's part of stage i + 1 is in LDS
+      barrier();            // and everyone's; nobody reads stage i any more
+      issue(i + 2);
+      k_step<AT, BT, S::BM, S::BN, 0, IM, KT>(acc, a1, b1, a0, b0, fa0 + nx, fb0 + nx);
+    }
   }
   // the last products are through before a vector instruction reads the accumulators
   asm volatile("s_nop 15\n s_nop 3" ::: "memory");

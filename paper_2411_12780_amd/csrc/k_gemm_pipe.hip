@@ -2,14 +2,17 @@
 // tiled kernel, bit-identical results (the same order of k).
 //
 // The tiled kernel is held by the data movement of a 128 x 128 tile: 32 KB into LDS and 96 KB of LDS traffic per 64 k, through
-// registers, a wave reading 64 x 64.  Here a wave owns 128 x 64 or 160 x 64 of a 128 x 256 or 160 x 256 tile, a quarter to a
-// third less to fill and to read per product; operands go straight to LDS, three stages of 32 k deep; the fragment reads of a
-// k step run under the products of the one before.  Two workgroups share a compute unit (72 or 78 KB of LDS each), so that one
-// stores its tile under the other's products.  One 256 x 256 tile per unit, with less traffic still, was slower (25216 x 768 x
-// 3072: 153 us, 25216 x 2304 x 768: 112): nothing runs under its epilogue.
-// Microseconds, tiled kernel -> this one: 25216 x 768 x 3072 145 -> 115 (1037 TFLOP/s), 25216 x 2304 x 768 133 -> 99, 25216 x
-// 3072 x 768 with GELU 223 -> 180 and with its derivative 194 -> 165 (310 MB of epilogue traffic each), 8320 x 1536 x 384 with
-// GELU 31.6 -> 28.1.  What bounds it: LDS traffic beside the products in the main loop, and the epilogue where K is short.
+// registers, a wave reading 64 x 64.  Here a wave owns 128 x 64 or 160 x 64, operands go straight to LDS, and the fragment reads of a
+// k step run under the products of the one before.  Two forms (the rules are in plan.h):
+//  128 x 256 or 160 x 256 tiles of four waves, three stages of 32 k, two workgroups a unit (72 or 78 KB of LDS each), so that one
+//    stores its tile under the other's products: where the epilogue is long or tiles are few;
+//  256 x 256 or 320 x 256 tiles of eight waves, two stages of 64 k, a unit to themselves (128 or 144 KB): a third less to bring into LDS,
+//    and rows of 128 bytes of an operand with k contiguous.  Rows of 64 bytes come from L2 at 26 bytes a clock and unit, whole cache
+//    lines at 52; brought 64 bytes a row, the copies of 25216 x 768 x 3072 alone took 76 us, whole lines 72 from HBM and 47 from L2.
+// Microseconds, tiled kernel -> first form -> second: 25216 x 768 x 3072 138 -> 117 -> 100 (1192 TFLOP/s), 25216 x 2304 x 768 132 -> 105 ->
+// 93, 25216 x 3072 x 768 with GELU 198 -> 172 -> 162 and with its derivative 182 -> 165 -> 151 (310 MB of epilogue traffic each),
+// 8320 x 1152 x 384 16.8 -> 16.4 -> 14.8, 8320 x 1536 x 384 with GELU 27.9 -> 24.8 -> 24.0.  What bounds it: in the main loop LDS reads and
+// products, which take 85 of those 100 us without any copies and 68 without the reads as well; the epilogue where K is short.
 #include "common.h"
 #include "gemm_pipe.h"
 #include "plan.h"
@@ -37,10 +40,10 @@ __device__ __forceinline__ u32x4 pack8(const float (&v)[8]) {
   return (u32x4){f32x2_to_bf16x2(v[0], v[1]), f32x2_to_bf16x2(v[2], v[3]), f32x2_to_bf16x2(v[4], v[5]), f32x2_to_bf16x2(v[6], v[7])};
 }
 
-template <bool BT, int WGM, int WGN, int IM, int NS>
+template <bool BT, int WGM, int WGN, int IM, int NS, int KT>
 __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(PipeArgs p) {
   PPLL_CODE_TO_L2(4);
-  using S = Shape<false, BT, WGM, WGN, IM, NS>;
+  using S = Shape<false, BT, WGM, WGN, IM, NS, KT>;
   constexpr int JN = 2;
   extern __shared__ __align__(1024) char smem[];
   // XCD x (workgroup id % 8) takes a contiguous range of the tiles, row by row: they share operand panels in its L2
@@ -139,17 +142,17 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(PipeArgs p
   }
 }
 
-constexpr int WAVES_N = 4, STAGES = 3;
+constexpr int WAVES_N = 4;
 
-template <bool BT, int IM>
+template <bool BT, int WGM, int IM, int STAGES, int KT>
 int pipe_launch(hipStream_t s, PipeArgs& p) {
-  using S = Shape<false, BT, 1, WAVES_N, IM, STAGES>;
+  using S = Shape<false, BT, WGM, WAVES_N, IM, STAGES, KT>;
   p.tiles_n = (p.N + S::BN - 1) / S::BN;
   p.tiles = (p.M + S::BM - 1) / S::BM * p.tiles_n;
   p.per_xcd = (p.tiles + 7) / 8;
   static OncePerDevice once;
-  PPLL_TRY(raise_lds((const void*)gemm_pipe_kernel<BT, 1, WAVES_N, IM, STAGES>, S::LDS, once));
-  hipLaunchKernelGGL((gemm_pipe_kernel<BT, 1, WAVES_N, IM, STAGES>), dim3(8 * p.per_xcd), dim3(S::THREADS), S::LDS, s, p);
+  PPLL_TRY(raise_lds((const void*)gemm_pipe_kernel<BT, WGM, WAVES_N, IM, STAGES, KT>, S::LDS, once));
+  hipLaunchKernelGGL((gemm_pipe_kernel<BT, WGM, WAVES_N, IM, STAGES, KT>), dim3(8 * p.per_xcd), dim3(S::THREADS), S::LDS, s, p);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;
 }
@@ -165,7 +168,8 @@ bool gemm_pipe_supported(const GemmArgs& g) {
 int gemm_pipe_choice(const GemmArgs& g) {
   if (!gemm_pipe_supported(g)) return 0;
   const ProductEnd end = g.epilogue == EPI_GELU ? END_GELU : g.epilogue == EPI_DGELU ? END_DGELU : g.residual ? END_RESIDUAL : g.bias ? END_BIAS : END_PLAIN;
-  return wide_tile_rows(g.M, g.N, g.K, end, compute_units());
+  const int units = compute_units(), wide = wide_tile_rows(g.M, g.N, g.K, end, units), alone = unit_tile_rows(g.M, g.N, g.K, end, wide, units);
+  return alone ? alone : wide;
 }
 
 int launch_gemm_pipe(hipStream_t s, const GemmArgs& g, int im) {
@@ -184,10 +188,10 @@ int launch_gemm_pipe(hipStream_t s, const GemmArgs& g, int im) {
   p.aux_bytes = g.epilogue == EPI_DGELU ? (uint32_t)(((long)(g.M - 1) * g.ldaux + g.N) * 2) : 0u;
   void* prof = nullptr;
   PPLL_TRY(profile_begin(s, 2.0 * g.M * g.N * g.K, &prof));
-  if (bt && im == 4) PPLL_TRY((pipe_launch<true, 4>(s, p)));
-  else if (bt) PPLL_TRY((pipe_launch<true, 5>(s, p)));
-  else if (im == 4) PPLL_TRY((pipe_launch<false, 4>(s, p)));
-  else PPLL_TRY((pipe_launch<false, 5>(s, p)));
+  if (im == 4) PPLL_TRY((bt ? pipe_launch<true, 1, 4, 3, 32>(s, p) : pipe_launch<false, 1, 4, 3, 32>(s, p)));
+  else if (im == 5) PPLL_TRY((bt ? pipe_launch<true, 1, 5, 3, 32>(s, p) : pipe_launch<false, 1, 5, 3, 32>(s, p)));
+  else if (im == 8) PPLL_TRY((bt ? pipe_launch<true, 2, 4, 2, 64>(s, p) : pipe_launch<false, 2, 4, 2, 64>(s, p)));
+  else PPLL_TRY((bt ? pipe_launch<true, 2, 5, 2, 64>(s, p) : pipe_launch<false, 2, 5, 2, 64>(s, p)));
   return profile_end(s, prof);
 }
 

@@ -187,6 +187,35 @@ inline int wide_tile_rows(int M, int N, int K, ProductEnd end, int units) {
   return c4 <= c5 ? 4 : 5;
 }
 
+// Rows / 32 of tiles that have a unit to themselves (256 x 256 or 320 x 256, eight waves), where they are expected to beat what
+// wide_tile_rows() says (`wide`), else 0.  Microseconds of a round of such a launch: per k, and with the epilogue; fits to 182
+// products of widths 192 to 1024 with 1800 to 50000 rows (within 5 % rms; the other tiles 8 to 11 %):
+//   128 x 128   0.0150 K + 4.7 plain or bias, 5.8 residual, 9.0 GELU, 6.9 its derivative, and 1.5 a launch
+//   128 x 256   0.0260 K + 8.7       11.4     16.4                   13.9
+//   160 x 256   0.0311 K + 9.7       12.8     20.3                   16.0
+//   256 x 256   0.0237 K + 9.1       11.8     17.7                   13.5
+//   320 x 256   0.0287 K + 10.5      13.6     21.2                   15.9
+// where the first three count a last round of at most one workgroup a unit as 0.55, 0.65 and 0.60 of one, the others one that fills the
+// share f of the units as 0.7 + 0.3 f.  The choice has to be 3 % ahead; over those products it is never behind, and 5 % ahead in
+// sum.  (Beside a tiled product the change of kernels costs less than it did: see CodeToL2.  With a microsecond for it, evaluation
+// forwards of width 384, 8320 rows, took 342 us, without 338.)
+inline int unit_tile_rows(int M, int N, int K, ProductEnd end, int wide, int units) {
+  if (K < PIPE_MIN_K || units < 8) return 0;
+  struct Cost { int rows, cols; double last, k, end[5], launch; };
+  static const Cost tiled = {128, 128, 0.55, 0.0150, {4.7, 4.7, 5.8, 9.0, 6.9}, 1.5}, c4 = {128, 256, 0.65, 0.0260, {8.7, 8.7, 11.4, 16.4, 13.9}, 0.0},
+                    c5 = {160, 256, 0.60, 0.0311, {9.7, 9.7, 12.8, 20.3, 16.0}, 0.0}, c8 = {256, 256, 0.7, 0.0237, {9.1, 9.1, 11.8, 17.7, 13.5}, 0.0},
+                    c10 = {320, 256, 0.7, 0.0287, {10.5, 10.5, 13.6, 21.2, 15.9}, 0.0};
+  const Cost& now = wide == 4 ? c4 : wide == 5 ? c5 : tiled;
+  const double other = tile_rounds(M, N, now.rows, now.cols, units, now.last) * (now.k * K + now.end[end]) + now.launch;
+  auto cost = [&](const Cost& c) {
+    const long tiles = (long)((M + c.rows - 1) / c.rows) * ((N + c.cols - 1) / c.cols), rest = tiles % units;
+    return (tiles / units + (rest ? c.last + (1.0 - c.last) * rest / units : 0.0)) * (c.k * K + c.end[end]);
+  };
+  const double t8 = cost(c8), t10 = cost(c10);
+  if (std::min(t8, t10) >= 0.97 * other) return 0;
+  return t8 <= t10 ? 8 : 10;
+}
+
 // ---- The matrix-core attention addresses the keys, queries and values of an image with 32-bit byte offsets
 inline bool att_offsets_fit(int T, int H) { return (long)T * H * (3 * 64 * 2) <= 0x7fffffffL; }
 

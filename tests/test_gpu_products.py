@@ -9,7 +9,7 @@ from paper_2411_12780_amd import binding as P
 
 pytestmark = pytest.mark.gpu
 
-FEW, TILED, WIDE_128, WIDE_160, SPLIT = 1, 2, 4, 5, 6
+FEW, TILED, WIDE_128, WIDE_160, SPLIT, UNIT_256, UNIT_320 = 1, 2, 4, 5, 6, 8, 10
 NONE, GELU, DGELU = 0, 1, 2
 
 
@@ -52,6 +52,28 @@ def test_wide_tiles_give_what_the_tiled_kernel_gives(M, N, K, bt, epilogue):
     # one rounding to bf16 (2^-9 of a value at most), fp32 sums of up to 1000 terms far below it
     assert float((C.double() - ref).norm() / ref.norm()) <= 2.0 ** -8
     for kernel in (WIDE_128, WIDE_160):
+        status, D, D2 = product(kernel, A, B, bt, bias, residual, epilogue, aux)
+        assert status == 0
+        assert torch.equal(C, D) and torch.equal(C2, D2), kernel
+
+
+@pytest.mark.parametrize("epilogue", [NONE, GELU, DGELU])
+@pytest.mark.parametrize("bt", [0, 1])
+@pytest.mark.parametrize("M,N,K", [
+    # edges of 256 x 256 and 320 x 256 tiles and of a stage of 64 k; two to sixteen stages, of which two are in LDS
+    (1, 8, 128), (257, 264, 136), (321, 520, 200), (256, 256, 192), (320, 248, 1000), (639, 512, 328), (33, 776, 384),
+])
+def test_tiles_of_a_unit_give_what_the_tiled_kernel_gives(M, N, K, bt, epilogue):
+    g = torch.Generator(device="cuda").manual_seed(M * 1000 + N + K)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    wide = rnd(M, K + 40)                     # rows of A further apart than they are long
+    A, B = wide[:, :K], rnd(K, N) if bt else rnd(N, K)
+    bias = torch.randn(N, generator=g, device="cuda") if epilogue != DGELU else None
+    residual = rnd(M, N) if epilogue == NONE else None
+    aux = rnd(M, N)
+    status, C, C2 = product(TILED, A, B, bt, bias, residual, epilogue, aux)
+    assert status == 0
+    for kernel in (UNIT_256, UNIT_320):
         status, D, D2 = product(kernel, A, B, bt, bias, residual, epilogue, aux)
         assert status == 0
         assert torch.equal(C, D) and torch.equal(C2, D2), kernel

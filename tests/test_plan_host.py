@@ -33,6 +33,10 @@ int main() {
       int M, N, K, end, units;
       if (std::scanf("%d %d %d %d %d", &M, &N, &K, &end, &units) != 5) return 1;
       std::printf("%d\n", 32 * wide_tile_rows(M, N, K, (ProductEnd)end, units));
+    } else if (!std::strcmp(what, "unit")) {
+      int M, N, K, end, units;
+      if (std::scanf("%d %d %d %d %d", &M, &N, &K, &end, &units) != 5) return 1;
+      std::printf("%d\n", 32 * unit_tile_rows(M, N, K, (ProductEnd)end, wide_tile_rows(M, N, K, (ProductEnd)end, units), units));
     } else if (!std::strcmp(what, "few")) {
       int M, N, K, units;
       if (std::scanf("%d %d %d %d", &M, &N, &K, &units) != 4) return 1;
@@ -173,6 +177,16 @@ PLAIN, BIAS, RESIDUAL, GELU, DGELU = range(5)
 ])
 def test_products_go_to_the_tiles_that_are_ahead(plan, M, N, K, end, rows):
     assert plan("product", M, N, K, end, UNITS) == [rows]
+
+
+@pytest.mark.parametrize("M,N,K,end,rows", [
+    # rows of the tiles that have a unit to themselves (0: others are ahead), as measured on 256 units
+    (25216, 768, 3072, BIAS, 320), (25216, 2304, 768, BIAS, 320), (25216, 3072, 768, GELU, 320), (8320, 1152, 384, BIAS, 256),
+    (8320, 1536, 384, DGELU, 256), (8320, 384, 1536, BIAS, 0), (8320, 384, 384, BIAS, 0), (12608, 768, 3072, BIAS, 0),
+    (6304, 768, 768, BIAS, 0), (25216, 3072, 120, BIAS, 0),
+])
+def test_products_go_to_tiles_of_a_unit_where_those_are_ahead(plan, M, N, K, end, rows):
+    assert plan("unit", M, N, K, end, UNITS) == [rows]
 
 
 def test_products_of_the_parity_cases_reach_the_kernels_they_name(plan):
