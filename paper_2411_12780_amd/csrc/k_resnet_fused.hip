@@ -298,6 +298,7 @@ __global__ __launch_bounds__(64 * WAVES, C == 16 ? 4 : 1) void conv_bn_kernel(Co
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         if (BWD && NT > 1) outer_load(t);
+        uint32_t first_x, first_y;
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
           const int c = 32 * t + 8 * q + 4 * hh;
@@ -308,7 +309,18 @@ __global__ __launch_bounds__(64 * WAVES, C == 16 ? 4 : 1) void conv_bn_kernel(Co
             for (int e = 0; e < 4; ++e) v[e] += (dm[t] >> (8 * q + 4 * hh + e)) & 1 ? rv[e] : 0.f;
           }
           const uint2 o = make_uint2(pack2(v[0], v[1]), pack2(v[2], v[3]));
-          *reinterpret_cast<uint2*>(p.dst + pix * C + c) = o;
+          // lanes l and l + 32 have channels 0 - 3, 8 - 11 and 4 - 7, 12 - 15 of every 16: exchanged, 0 - 7 and 8 - 15, a 16-byte store
+          // instead of two of 8 (848 x 8 x 8 x 64, a stage of ten: 520 -> 514 us a step; ResNet-32 in eight modules 2579 -> 2550).  With
+          // 16 channels an instruction fills whole lines
+          if (q % 2 == 0) {
+            first_x = o.x; first_y = o.y;
+          } else {
+            const auto x = __builtin_amdgcn_permlane32_swap(first_x, o.x, false, false), y = __builtin_amdgcn_permlane32_swap(first_y, o.y, false, false);
+            uint16_t* to = p.dst + pix * C + 32 * t + 8 * (q - 1) + 8 * hh;
+            const uint4 eight = make_uint4(x[0], y[0], x[1], y[1]);
+            if (C == 16) store_through(to, eight);
+            else *reinterpret_cast<uint4*>(to) = eight;
+          }
           const float r[4] = {lo_bf(o.x), hi_bf(o.x), lo_bf(o.y), hi_bf(o.y)};
           if (!BWD) {
 #pragma unroll
