@@ -91,41 +91,19 @@ __device__ __forceinline__ float dot8(uint4 a, uint4 b) {
   return d;
 }
 
-template <int CTRL> __device__ __forceinline__ uint32_t dpp_u(uint32_t v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); }
-// Stores the first n of 32 rows of 64 results, ld elements apart.  A lane holds 4 consecutive columns of row lane % 32, its partner in the
-// other half of the wave the next 4: they trade, which makes 16 bytes; then four neighbouring lanes trade rows for columns, so that
-// an instruction stores 8 rows of 128 bytes, whole cache lines, which go through L2 (32 bytes of 32 rows an instruction cannot: steps of
-// width 384 took 907 us, 8320 rows, and 1002, 9280 rows; so 900 and 996).
-__device__ __forceinline__ void store_rows(uint16_t* row0, long ld, int n, const f32x16 (&v)[2], float scale, int lane) {
-  const int hh = lane >> 5, j = lane & 3, r0 = lane & 28;
-  uint32_t p[4][4];                      // [columns 16 i + 8 hh .. + 7][two columns each]
+// A lane holds 4 consecutive columns of a row of results, its partner in the other half of the wave the next 4: they trade, and store
+// 16 bytes each.
+__device__ __forceinline__ void store_row(uint16_t* row, const f32x16 (&v)[2], float scale, int hh) {
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int dt = i >> 1, q = 8 * (i & 1);
-    const auto lo = __builtin_amdgcn_permlane32_swap(pack2(v[dt][q] * scale, v[dt][q + 1] * scale),
-                                                     pack2(v[dt][q + 4] * scale, v[dt][q + 5] * scale), false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap(pack2(v[dt][q + 2] * scale, v[dt][q + 3] * scale),
-                                                     pack2(v[dt][q + 6] * scale, v[dt][q + 7] * scale), false, false);
-    p[i][0] = lo[0]; p[i][1] = hi[0]; p[i][2] = lo[1]; p[i][3] = hi[1];
-  }
+  for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
-#pragma unroll
-    for (int i = 0; i < 4; i += 2) {     // with lane ^ 1: p[i + k] is then piece i + j % 2 of row k of the two
-      const uint32_t got = dpp_u<0xB1>(j & 1 ? p[i][w] : p[i + 1][w]);
-      p[i + 1][w] = j & 1 ? p[i + 1][w] : got;
-      p[i][w] = j & 1 ? got : p[i][w];
+    for (int q = 0; q < 4; q += 2) {
+      const auto lo = __builtin_amdgcn_permlane32_swap(pack2(v[dt][4 * q] * scale, v[dt][4 * q + 1] * scale),
+                                                       pack2(v[dt][4 * q + 4] * scale, v[dt][4 * q + 5] * scale), false, false);
+      const auto hi = __builtin_amdgcn_permlane32_swap(pack2(v[dt][4 * q + 2] * scale, v[dt][4 * q + 3] * scale),
+                                                       pack2(v[dt][4 * q + 6] * scale, v[dt][4 * q + 7] * scale), false, false);
+      *reinterpret_cast<uint4*>(row + 32 * dt + 8 * (q + hh)) = make_uint4(lo[0], hi[0], lo[1], hi[1]);
     }
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {        // with lane ^ 2: p[i] is then piece j of row i of the four
-      const uint32_t got = dpp_u<0x4E>(j & 2 ? p[k][w] : p[2 + k][w]);
-      p[2 + k][w] = j & 2 ? p[2 + k][w] : got;
-      p[k][w] = j & 2 ? got : p[k][w];
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (r0 + i < n) store_through(row0 + (long)(r0 + i) * ld + 16 * j + 8 * hh, make_uint4(p[i][0], p[i][1], p[i][2], p[i][3]));
 }
 
 // Waves a SIMD: as many as the scores of a query, 16 registers a tile, let in beside the rest
@@ -217,8 +195,10 @@ __global__ __launch_bounds__(64 * NKT, fwd_waves_per_simd(NKT)) void attn_fwd_mf
         o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tr_frag(smem + ca[dt][0] + at, smem + ca[dt][1] + at), pf, o[dt], 0, 0, 0);
       }
     }
-  store_rows(out + ((size_t)b * T + 32 * wave) * D + h * 64, D, T - 32 * wave, o, 1.f, lane);
-  if (qi < T && hh == 0) lse_out[((size_t)b * H + h) * T + qi] = mx + __logf(sum);
+  if (qi < T) {
+    store_row(out + ((size_t)b * T + qi) * D + h * 64, o, 1.f, hh);
+    if (hh == 0) lse_out[((size_t)b * H + h) * T + qi] = mx + __logf(sum);
+  }
 }
 
 // Waves of a backward workgroup, each with one tile of 32 tokens, from five tiles on with two: 60 images x 145 tokens x 6 heads 29 us,
@@ -363,7 +343,7 @@ __global__ __launch_bounds__(64 * bwd_waves(NKT), bwd_waves_per_simd(NKT)) void 
 #pragma unroll 1
       for (int jt = 0; jt < whole; ++jt) keys(jt, std::false_type{});
       if (whole < NKT) keys(whole, std::true_type{});
-      store_rows(gbase + (long)(32 * t) * ld, ld, T - 32 * t, dq, kScale, lane);
+      if (ok) store_row(gbase + (long)qi * ld, dq, kScale, hh);
     }
   }
 
@@ -429,8 +409,10 @@ __global__ __launch_bounds__(64 * bwd_waves(NKT), bwd_waves_per_simd(NKT)) void 
 #pragma unroll 1
       for (int it = 0; it < whole; ++it) queries(it, std::false_type{});
       if (whole < NKT) queries(whole, std::true_type{});
-      store_rows(gbase + (long)(32 * t) * ld + D, ld, T - 32 * t, dk, kScale, lane);
-      store_rows(gbase + (long)(32 * t) * ld + 2 * D, ld, T - 32 * t, dv, 1.f, lane);
+      if (kj < T) {
+        store_row(gbase + (long)kj * ld + D, dk, kScale, hh);
+        store_row(gbase + (long)kj * ld + 2 * D, dv, 1.f, hh);
+      }
     }
   }
 }
