@@ -97,7 +97,8 @@ __device__ __forceinline__ void wave_sync() {
 // have left there, up to 4 MB in each of the 8, is written back when the kernel ends, with nothing else running (an evaluation forward
 // of 3 + 1 layers of width 384: 359 us with ordinary stores in the products, 343 with these).  For results that other kernels read, where
 // the stores of one instruction fill cache lines: pieces of lines, which L2 puts together otherwise, go out one by one (attention,
-// 32 bytes of a row at a time: that forward 3 us longer; fp32 products, every other 16 bytes: 452 -> 481 us for a step of 148 rows of
+// 32 bytes of a row at a time: that forward 3 us longer; few-tile products likewise: 497 -> 504 us for a step of 585 rows of width
+// 384; fp32 products, every other 16 bytes: 452 -> 481 us for a step of 148 rows of
 // width 768; convolution results, 8 bytes: steps a tenth longer).
 constexpr int THROUGH = 16;     // as the cache policy of a buffer store
 __device__ __forceinline__ void store_through(void* p, uint4 v) {

@@ -237,10 +237,10 @@ __global__ __launch_bounds__(64 * (WAVES + COPY_WAVES), 4) void gemm_split_kerne
         cdf_pdf(x[e], cdf, pdf);
         dg[e] = cdf + x[e] * pdf; x[e] *= cdf;
       }
-      __builtin_amdgcn_raw_buffer_store_b128(pack8(dg), rsC, off, 0, THROUGH);
-      __builtin_amdgcn_raw_buffer_store_b128(pack8(x), rsC2, off, 0, THROUGH);
+      __builtin_amdgcn_raw_buffer_store_b128(pack8(dg), rsC, off, 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(pack8(x), rsC2, off, 0, 0);
     } else {
-      __builtin_amdgcn_raw_buffer_store_b128(pack8(x), rsC, off, 0, THROUGH);
+      __builtin_amdgcn_raw_buffer_store_b128(pack8(x), rsC, off, 0, 0);
     }
   }
 }
