@@ -474,7 +474,7 @@ __global__ __launch_bounds__(256) void layernorm_fwd_bf16_kernel(const uint16_t*
     o.y = pack_bf(t[2] * rs * g0.z + b0.z, t[3] * rs * g0.w + b0.w);
     o.z = pack_bf(t[4] * rs * g1.x + b1.x, t[5] * rs * g1.y + b1.y);
     o.w = pack_bf(t[6] * rs * g1.z + b1.z, t[7] * rs * g1.w + b1.w);
-    store_through(y + (size_t)row * D + c, o);
+    *reinterpret_cast<uint4*>(y + (size_t)row * D + c) = o;
   }
   if (lr == 0) { mean[row] = mu; rstd[row] = rs; }
 }
@@ -564,8 +564,7 @@ __global__ __launch_bounds__(64 * LNB_WAVES, 2) void layernorm_bwd_bf16_kernel(c
           if (SPARSE) o[e] = bf16_to_f32(f32_to_bf16(o[e]));
           o[e] += rv[e];
         }
-        store_through(dx + (size_t)row * D + 8 * lr + 8 * LPR * j,
-                      make_uint4(pack_bf(o[0], o[1]), pack_bf(o[2], o[3]), pack_bf(o[4], o[5]), pack_bf(o[6], o[7])));
+        *reinterpret_cast<uint4*>(dx + (size_t)row * D + 8 * lr + 8 * LPR * j) = make_uint4(pack_bf(o[0], o[1]), pack_bf(o[2], o[3]), pack_bf(o[4], o[5]), pack_bf(o[6], o[7]));
       }
     }
   }
@@ -1168,7 +1167,7 @@ __global__ __launch_bounds__(256) void patchify_bf16_kernel(const uint16_t* img,
   const uint32_t r = t % P, pidx = t / P;
   const uint32_t gx = pidx % gw, q = pidx / gw, gy = q % gh, b = q / gh;
   const size_t src = (((size_t)b * H + gy * P + r) * W + gx * P) * C + 8 * v;
-  store_through(out + (size_t)i * 8, *reinterpret_cast<const uint4*>(img + src));
+  *reinterpret_cast<uint4*>(out + (size_t)i * 8) = *reinterpret_cast<const uint4*>(img + src);
 }
 
 __global__ __launch_bounds__(256) void assemble_tokens_kernel(const void* E, int dt, const float* cls,
@@ -1200,8 +1199,8 @@ __global__ __launch_bounds__(256) void assemble_tokens_bf16_kernel(const uint16_
   }
   const float4 p0 = *reinterpret_cast<const float4*>(pos + (size_t)t * D + d);
   const float4 p1 = *reinterpret_cast<const float4*>(pos + (size_t)t * D + d + 4);
-  store_through(x0 + i, make_uint4(f32x2_to_bf16x2(v[0] + p0.x, v[1] + p0.y), f32x2_to_bf16x2(v[2] + p0.z, v[3] + p0.w),
-                                   f32x2_to_bf16x2(v[4] + p1.x, v[5] + p1.y), f32x2_to_bf16x2(v[6] + p1.z, v[7] + p1.w)));
+  *reinterpret_cast<uint4*>(x0 + i) = make_uint4(f32x2_to_bf16x2(v[0] + p0.x, v[1] + p0.y), f32x2_to_bf16x2(v[2] + p0.z, v[3] + p0.w),
+                                   f32x2_to_bf16x2(v[4] + p1.x, v[5] + p1.y), f32x2_to_bf16x2(v[6] + p1.z, v[7] + p1.w));
 }
 __global__ __launch_bounds__(256) void scatter_cls_bf16_kernel(const uint16_t* dcls, int B, int T, int D, uint16_t* dx) {
   const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 8;
@@ -1210,7 +1209,7 @@ __global__ __launch_bounds__(256) void scatter_cls_bf16_kernel(const uint16_t* d
   const int b = i / ((size_t)D * T);
   uint4 w = make_uint4(0, 0, 0, 0);
   if (t == 0) w = *reinterpret_cast<const uint4*>(dcls + (size_t)b * D + d);
-  store_through(dx + i, w);
+  *reinterpret_cast<uint4*>(dx + i) = w;
 }
 
 constexpr int EMB_ROWS = 8;   // batch entries per partial
@@ -1255,7 +1254,7 @@ __global__ __launch_bounds__(256) void embed_bwd_bf16_kernel(const uint16_t* dx,
     const uint32_t* w = reinterpret_cast<const uint32_t*>(&v[u]);
 #pragma unroll
     for (int e = 0; e < 4; ++e) { acc[2 * e] += __uint_as_float(w[e] << 16); acc[2 * e + 1] += __uint_as_float(w[e] & 0xffff0000u); }
-    if (t > 0) store_through(dE + ((size_t)(b0 + u) * (T - 1) + (t - 1)) * D + d, v[u]);
+    if (t > 0) *reinterpret_cast<uint4*>(dE + ((size_t)(b0 + u) * (T - 1) + (t - 1)) * D + d) = v[u];
   }
   float* out = partial + (size_t)blockIdx.y * T * D + i;
   *reinterpret_cast<float4*>(out) = make_float4(acc[0], acc[1], acc[2], acc[3]);
