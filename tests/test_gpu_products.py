@@ -210,3 +210,34 @@ def test_weight_gradients_on_big_tiles(cuts, whole, shapes):
     no_room = f(n, flat, ptrs(A), ptrs(B), ptrs(C), ptrs(sums), ws.data_ptr(), 0, 2, 0, torch.cuda.current_stream().cuda_stream)
     assert no_room == (4 if any(s[2] > 448 for s in shapes) else 0)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("K,cuts", [(25216, 1), (4501, 1), (9000, 3), (1000, 4)])
+def test_column_sums_on_big_tiles_are_sixteen_chains_a_column(K, cuts):
+    # what the other weight-gradient kernels sum: one chain for each k % 16, then the chains of a half of eight in pairs and the halves;
+    # parts of whole stages of 32 k, added in ascending k.  Values around 1, where the length of a chain shows in its error
+    g = torch.Generator(device="cuda").manual_seed(K)
+    N = 200
+    A = torch.randn(K, 48, generator=g, device="cuda").to(torch.bfloat16)
+    B = (torch.randn(K, N, generator=g, device="cuda") + 1).to(torch.bfloat16)
+    C, sums = torch.empty(48, N, device="cuda"), torch.empty(N, device="cuda")
+    ws = torch.empty(384 * 192 * 2 * 2 * cuts, device="cuda")
+    f = P.lib().ppll_internal_weight_grads
+    f.restype = ctypes.c_int
+    f.argtypes = [ctypes.c_int] + [ctypes.c_void_p] * 6 + [ctypes.c_size_t, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
+    one = lambda t: (ctypes.c_void_p * 1)(t.data_ptr())
+    assert f(1, (ctypes.c_int * 6)(48, N, K, 48, N, N), one(A), one(B), one(C), one(sums), ws.data_ptr(), ws.numel(), cuts, 0,
+             torch.cuda.current_stream().cuda_stream) == 0
+    stages = -(-K // 32)
+    per = 32 * -(-stages // cuts)
+    want = None
+    for k0 in range(0, K, per):
+        part = B[k0:k0 + per].float()
+        part = torch.cat([part, part.new_zeros(-len(part) % 16, N)]).view(-1, 2, 8, N)
+        chains = torch.zeros(2, 8, N, device="cuda")
+        for step in part:
+            chains = chains + step
+        pairs = chains[:, 0::2] + chains[:, 1::2]
+        halves = (pairs[:, 0] + pairs[:, 1]) + (pairs[:, 2] + pairs[:, 3])
+        want = halves[0] + halves[1] if want is None else want + (halves[0] + halves[1])
+    assert torch.equal(sums, want)
