@@ -111,6 +111,11 @@ struct Block {
   // gradients by as much as their rms) two steps on.  Its blocks keep the order of the 128 x 128 tiles; under SGD such blocks differ
   // by 3e-7.
   bool wgrad_any_order() const { return cfg.optimizer == PPLL_SGD; }
+  // Whether they run on the tiles of k_gemm_wgrad.hip, all of them in one launch at the end of the backward pass.  Decided once, from the
+  // products that the configuration gives (weight_grads): the gradients of a block are then the same bits alone, in a pipeline and with
+  // its launches timed, and no layer is held back for a launch that would refuse the set.
+  bool wgrad_big = false;
+  std::vector<GemmArgs> weight_grads() const;   // the products that a ViT block's backward pass records
   // Side stream of the backward pass (created at first use, default priority).  The weight-gradient products of a
   // layer are launched there once the layer's backward is enqueued, so they run next to the input-gradient chain of
   // the layers below, which never reads them; the step's stream waits for the side stream before the update.
@@ -192,6 +197,8 @@ struct Block {
   int encoder_bwd_cls(int l, const void* x, const void* d_x2, void* g_out, hipStream_t s);
   // dW[in, out] (row stride ldw) = X^T dY over K rows and db = column sums of dY; recorded for the grouped launch when
   // the matrix-core kernel can take it, else run at once.  x_ld / dy_ld: row strides of X [K, in] and dY [K, out].
+  GemmArgs wgrad_args(const void* xin, long x_ld, int in_dim, const void* dy, long dy_ld, int out_dim, int K, float* dW, long ldw,
+                      float* db) const;
   int wgrad_product(const void* xin, long x_ld, int in_dim, const void* dy, long dy_ld, int out_dim, int K, float* dW,
                     long ldw, float* db, hipStream_t s);
   int update(float lr, hipStream_t s);

@@ -4,7 +4,6 @@
 #include "block.h"
 #include "plan.h"
 
-#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -228,8 +227,9 @@ size_t Block::plan(char* base) {
       d_qkv.push_back(bump.take(M * 3 * D * esz));
     }
     if (dt == BF16) {   // parts of divided tiles of the weight-gradient launch at the end of the backward pass
-      wgrad_ws_floats = gemm_mfma_balanced_floats();
-      if (wgrad_any_order()) wgrad_ws_floats = std::max(wgrad_ws_floats, gemm_big_grads_floats());
+      const std::vector<GemmArgs> set = weight_grads();
+      wgrad_big = wgrad_any_order() && gemm_big_grads_choice(set.data(), (int)set.size(), &wgrad_ws_floats);
+      if (!wgrad_big) wgrad_ws_floats = gemm_mfma_balanced_floats();
       wgrad_ws = wgrad_ws_floats ? bump.floats(wgrad_ws_floats) : nullptr;
     }
     int widest = 3 * D > F ? 3 * D : F;
@@ -402,16 +402,54 @@ int Block::encoder_bwd(int l, const void* x, const void* g_in, void* g_tmp, void
                               need_dx ? g_out : nullptr, rq, grads + p.ln1_g, grads + p.ln1_b);
 }
 
-int Block::wgrad_product(const void* xin, long x_ld, int in_dim, const void* dy, long dy_ld, int out_dim, int K, float* dW,
-                         long ldw, float* db, hipStream_t s) {
+GemmArgs Block::wgrad_args(const void* xin, long x_ld, int in_dim, const void* dy, long dy_ld, int out_dim, int K, float* dW, long ldw,
+                           float* db) const {
   GemmArgs g = gemm_args();
   g.A = xin; g.a_dt = dt; g.a_sm = 1; g.a_sk = x_ld;
   g.B = dy; g.b_dt = dt; g.b_sk = dy_ld; g.b_sn = 1;
   g.C = dW; g.c_dt = F32; g.ldc = ldw; g.M = in_dim; g.N = out_dim; g.K = K;
   g.colsum = db;
+  return g;
+}
+
+// What wgrad_product() is called with in a backward pass and records.  While the workspace is only measured the pointers are offsets
+// from null (or null): of the same alignment, which is what they are looked at for.
+std::vector<GemmArgs> Block::weight_grads() const {
+  const int D = cfg.dim, F = cfg.mlp_dim, T = cfg.tokens, B = cfg.batch, M = B * T;
+  std::vector<GemmArgs> set;
+  auto add = [&](const void* xin, long x_ld, int in_dim, const void* dy, long dy_ld, int out_dim, int K, size_t w_off, long ldw, size_t b_off) {
+    const GemmArgs g = wgrad_args(xin, x_ld, in_dim, dy, dy_ld, out_dim, K, grads + w_off, ldw, grads + b_off);
+    if (gemm_weight_grad_groupable(g)) set.push_back(g);
+  };
+  for (int l = cfg.depth + cfg.aux_depth - 1; l >= 0; --l) {
+    const EncoderParams& p = enc_p[l];
+    const EncoderActs& a = enc_a[l];
+    if (prune_cls && l == cfg.depth + cfg.aux_depth - 1) {
+      const ClsActs& c = cls_a;
+      add(c.gl, F, F, dcls, D, D, B, p.fc2_w, D, p.fc2_b);
+      add(c.u2, D, D, c.d_h, F, F, B, p.fc1_w, F, p.fc1_b);
+      add(c.att, D, D, c.d_x1, D, D, B, p.proj_w, D, p.proj_b);
+      add(a.u1, D, D, d_qkv[l], 2 * D, 2 * D, M, p.qkv_w + D, 3 * D, p.qkv_b + D);
+      add(a.u1, (long)T * D, D, c.d_q, D, D, B, p.qkv_w, 3 * D, p.qkv_b);
+    } else {
+      add(a.gl, F, F, g_res[l + 1], D, D, M, p.fc2_w, D, p.fc2_b);
+      add(a.u2, D, D, d_h[l], F, F, M, p.fc1_w, F, p.fc1_b);
+      add(a.att, D, D, g_mid[l], D, D, M, p.proj_w, D, p.proj_b);
+      add(a.u1, D, D, d_qkv[l], 3 * D, 3 * D, M, p.qkv_w, 3 * D, p.qkv_b);
+    }
+  }
+  const int ppc = cfg.patch * cfg.patch * cfg.img_c;
+  if (cfg.input_kind == PPLL_IN_IMAGE && T > 1) add(patches, ppc, ppc, embed_tmp, D, D, B * (T - 1), pe_w, D, pe_b);
+  return set;
+}
+
+int Block::wgrad_product(const void* xin, long x_ld, int in_dim, const void* dy, long dy_ld, int out_dim, int K, float* dW,
+                         long ldw, float* db, hipStream_t s) {
+  const GemmArgs g = wgrad_args(xin, x_ld, in_dim, dy, dy_ld, out_dim, K, dW, ldw, db);
   if (gemm_weight_grad_groupable(g)) { wgrad_jobs.push_back(g); return PPLL_OK; }
-  g.colsum = nullptr;
-  PPLL_TRY(launch_gemm(s, g));
+  GemmArgs alone = g;
+  alone.colsum = nullptr;
+  PPLL_TRY(launch_gemm(s, alone));
   if (dy_ld != out_dim) { set_error("bias gradient of a strided product needs the matrix-core kernel"); return PPLL_ERR_CONFIG; }
   return launch_colsum(s, dy, dt, K, out_dim, rq, db);
 }
@@ -581,16 +619,14 @@ int Block::vit_step(const void* x_in, const int32_t* labels, void* x_out, hipStr
     // beside the backward of the layers below, where they take up the slots that the chain's ragged last rounds of
     // workgroups leave empty (measured: 5 % of the step at width 768 and 197 tokens).  Smaller sets only slow the
     // chain down (measured at width 384: 2 to 8 % slower), so they wait for the grouped launch at the end.
-    // (not while launches are being timed one by one: overlapping kernels would stretch each other's brackets)
-    if (use_side && dt == BF16 && !profile_enabled() && l > 0 && M >= SIDE_MIN_ROWS && wgrad_jobs.size() > 1) {
+    // (not while launches are being timed one by one: overlapping kernels would stretch each other's brackets; nor where the launch
+    // at the end runs on tiles of 384 x 192, which fill the chip by themselves and share no unit with the chain: width 768, 25216 rows:
+    // 5129 us a step with the side stream, 5035 without)
+    if (use_side && !wgrad_big && dt == BF16 && !profile_enabled() && l > 0 && M >= SIDE_MIN_ROWS && wgrad_jobs.size() > 1) {
       long tiles = 0;
       for (size_t j = first_job; j < wgrad_jobs.size(); ++j)
         tiles += (long)((wgrad_jobs[j].M + 127) / 128) * ((wgrad_jobs[j].N + 127) / 128);
-      // nor where the grouped launch runs on tiles of 384 x 192: those fill the chip by themselves and share no unit with the chain
-      // (width 768, 25216 rows: 5129 us a step with the side stream, 5035 without)
-      const bool big = wgrad_any_order() &&
-                       gemm_big_grads_choice(&wgrad_jobs[first_job], (int)(wgrad_jobs.size() - first_job), l + 1);
-      if (tiles >= SIDE_MIN_TILES && !big) PPLL_TRY(side_launch_wgrads(s));
+      if (tiles >= SIDE_MIN_TILES) PPLL_TRY(side_launch_wgrads(s));
     }
   }
   if (image) {
@@ -614,7 +650,7 @@ int Block::vit_step(const void* x_in, const int32_t* labels, void* x_out, hipStr
   }
   // ---- every recorded weight-gradient product, in one launch
   // (the only user of the workspace while it runs: the side stream's launches take none)
-  PPLL_TRY(launch_gemm_group(s, wgrad_jobs.data(), (int)wgrad_jobs.size(), wgrad_ws, wgrad_ws_floats, wgrad_any_order()));
+  PPLL_TRY(launch_gemm_group(s, wgrad_jobs.data(), (int)wgrad_jobs.size(), wgrad_ws, wgrad_ws_floats, wgrad_big));
   wgrad_jobs.clear();
   PPLL_TRY(side_wait(s));
   return PPLL_OK;

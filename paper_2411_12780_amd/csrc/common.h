@@ -209,15 +209,14 @@ size_t gemm_mfma_balanced_floats();
 // The same on tiles of 384 x 192: see k_gemm_wgrad.hip.  ws: gemm_big_grads_floats() floats where the plan divides tiles.
 struct BigGradPlan;
 size_t gemm_big_grads_floats(int parts);
-size_t gemm_big_grads_floats();     // parts enough for the current device
 int launch_gemm_big_grads(hipStream_t s, const GemmArgs* gs, int n, float* ws, const BigGradPlan& plan);
-// whether `times` sets like this one, together at the end of a backward pass, go there
-bool gemm_big_grads_choice(const GemmArgs* gs, int n, int times);
+// whether this set goes there, and the workspace that it then needs
+bool gemm_big_grads_choice(const GemmArgs* gs, int n, size_t* ws_floats);
 // A set of independent products of one element type, each a weight gradient that gemm_weight_grad_groupable() accepts, in
 // one launch.  ws: room of gemm_mfma_balanced_floats() for the parts of divided tiles, for a launch that is the sole user of it
 // while it runs (null: tiles stay whole).
 inline bool gemm_weight_grad_groupable(const GemmArgs& g) { return gemm_mfma_groupable(g) || gemm_f32_groupable(g); }
-// any_order: the sums over k may be divided elsewhere than by the 128 x 128 tiles (ws then has room of gemm_big_grads_floats() too).
+// any_order: the sums over k may be divided elsewhere than by the 128 x 128 tiles (ws then has the room that gemm_big_grads_choice() says).
 int launch_gemm_group(hipStream_t s, const GemmArgs* gs, int n, float* ws = nullptr, size_t ws_floats = 0, bool any_order = false);
 // Per-launch timing of the contraction kernels (a measurement aid, off unless a block asks for it).  A block that
 // times its launches binds its record to the calling thread for the duration of a step; the launch functions

@@ -677,7 +677,6 @@ bool gemm_mfma_groupable(const GemmArgs& g) {
 static int balanced_workgroups() { return compute_units() / 8 * 8; }
 // room for the parts of the divided tiles: at most two per workgroup
 size_t gemm_mfma_balanced_floats() { return (size_t)balanced_workgroups() * 2 * SLOT_FLOATS; }
-size_t gemm_big_grads_floats() { return gemm_big_grads_floats(balanced_workgroups()); }
 
 static void fill_problem(GroupedProblem& q, const GemmArgs& g, int first_tile, int bn = BN) {
   q.A = (const uint16_t*)g.A; q.lda = (int)g.a_sk; q.B = (const uint16_t*)g.B; q.ldb = (int)g.b_sk;
@@ -690,9 +689,9 @@ static void fill_problem(GroupedProblem& q, const GemmArgs& g, int first_tile, i
   q.c_bytes = (uint32_t)(((long)(g.M - 1) * g.ldc + g.N) * 4);
 }
 
-static std::vector<ProductShape> product_shapes(const GemmArgs* gs, int n, int times) {
-  std::vector<ProductShape> shapes((size_t)n * times);
-  for (size_t j = 0; j < shapes.size(); ++j) shapes[j] = {gs[j % n].M, gs[j % n].N, gs[j % n].K};
+static std::vector<ProductShape> product_shapes(const GemmArgs* gs, int n) {
+  std::vector<ProductShape> shapes(n);
+  for (int j = 0; j < n; ++j) shapes[j] = {gs[j].M, gs[j].N, gs[j].K};
   return shapes;
 }
 // 32-bit byte offsets also for the k rows of a last stage that do not exist
@@ -701,8 +700,11 @@ static bool short_rows(const GemmArgs* gs, int n) {
     if (gs[j].a_sk > (1 << 20) || gs[j].b_sk > (1 << 20)) return false;
   return true;
 }
-bool gemm_big_grads_choice(const GemmArgs* gs, int n, int times) {
-  return n > 0 && short_rows(gs, n) && big_grad_tiles(product_shapes(gs, n, times).data(), n * times, balanced_workgroups()).take;
+static size_t big_grads_floats(const BigGradPlan& p) { return gemm_big_grads_floats((p.long_tiles - p.whole_tiles) * p.cuts); }
+bool gemm_big_grads_choice(const GemmArgs* gs, int n, size_t* ws_floats) {
+  const BigGradPlan plan = big_grad_tiles(product_shapes(gs, n).data(), n, balanced_workgroups());
+  *ws_floats = big_grads_floats(plan);
+  return plan.take && short_rows(gs, n);
 }
 
 int launch_gemm_mfma_grouped(hipStream_t s, const GemmArgs* gs, int n, float* ws, size_t ws_floats, bool any_order) {
@@ -710,13 +712,13 @@ int launch_gemm_mfma_grouped(hipStream_t s, const GemmArgs* gs, int n, float* ws
   PPLL_TRY(raise_lds((const void*)gemm_pipe_grouped_kernel, PipeShape::LDS, pipe_once));
   PPLL_TRY(raise_lds((const void*)gemm_mfma_grouped_kernel, lds_bytes(true, true, 128), grouped_once));
   PPLL_TRY(raise_lds((const void*)gemm_mfma_balanced_kernel, lds_bytes(true, true, 128), balanced_once));
-  const std::vector<ProductShape> shapes = product_shapes(gs, n, 1);
+  const std::vector<ProductShape> shapes = product_shapes(gs, n);
   const bool wide_ok = short_rows(gs, n);
   const int wgs = balanced_workgroups();
   const bool workspace = ws && n <= GROUP_MAX && ws_floats >= gemm_mfma_balanced_floats();
-  if (any_order && wide_ok && ws && ws_floats >= gemm_big_grads_floats()) {
+  if (any_order && wide_ok) {
     const BigGradPlan big = big_grad_tiles(shapes.data(), n, wgs);
-    if (big.take) return launch_gemm_big_grads(s, gs, n, ws, big);
+    if (big.take && ws_floats >= big_grads_floats(big)) return launch_gemm_big_grads(s, gs, n, ws, big);
   }
   const WeightGradPlan plan = plan_weight_grads(shapes.data(), n, workspace, wide_ok, wgs);
   if (plan.cuts > 1) {

@@ -566,17 +566,52 @@ def test_vit_base_224_shape_bf16():
     run_case(synth.workload("vit_base_224_bf16", batch=8), steps=1)
 
 
-def test_weight_gradients_on_the_side_stream_bf16():
-    # 21 x 197 = 4137 rows of width 768: a layer's weight-gradient products have 432 output tiles and a reduction
-    # over more than 4096 rows, so the auxiliary layer's run on the block's side stream beside the backward of the
-    # module layer; two steps, so that the second forward and update also meet the first step's side work
+# test_plan_host.py, test_products_of_the_step_cases_go_where_they_say, says on which tiles these run
+def test_weight_gradients_on_big_tiles_at_the_end_bf16():
+    # 21 x 197 = 4137 rows of width 768 under SGD: all weight gradients in one launch of 384 x 192 tiles at the end of the backward pass
     run_case(synth.workload("vit_base_224_bf16", batch=21, depth=1, aux_depth=1), steps=2)
 
 
+def test_weight_gradients_on_the_side_stream_bf16():
+    # 64 x 65 = 4160 rows of width 576 under SGD, which 384 x 192 tiles do not suit: a layer's weight-gradient products have 265 output
+    # tiles and a reduction over more than 4096 rows, so the auxiliary layer's run on the block's side stream beside the backward of the
+    # module layer; two steps, so that the second forward and update also meet the first step's side work
+    run_case(synth.workload("vit_stage_act_bf16", batch=64, dim=576, heads=9, mlp_dim=2304, depth=1, aux_depth=1, optimizer=synth.SGD,
+                            momentum=0.9, nesterov=1, weight_decay=1e-4, lr=0.01), steps=2)
+
+
 def test_weight_gradients_on_the_side_stream_under_adamw_bf16():
-    # the same under AdamW, whose blocks keep the side stream where SGD's have one launch of bigger tiles at the end
+    # AdamW's blocks keep the side stream at the width and rows of the first of these
     run_case(synth.workload("vit_base_224_bf16", batch=21, depth=1, aux_depth=1, optimizer=synth.ADAMW, momentum=0.0, nesterov=0,
                             weight_decay=0.01, lr=1e-3), steps=2)
+
+
+def test_weight_gradients_are_the_same_with_launches_timed():
+    # 384 x 192 tiles or not is decided by the shapes alone: with the launches timed, which keeps them off the side stream, the same bits
+    from paper_2411_12780_amd import binding as P
+    from gpu_harness import GpuBlock
+    wl = synth.workload("vit_base_224_bf16", batch=21, depth=1, aux_depth=1)
+    flat = synth.make_params(O.param_spec(oracle_cfg(wl)), seed=3, jitter=True)
+    x, y = synth.make_batch(wl, seed=3, index=0)
+    got = []
+    for timed in (False, True):
+        blk = GpuBlock(wl, flat)
+        P.ppll_block_profile_enable(blk.h, timed)
+        blk.step(x, y, 0.01)
+        got.append(blk.tensors(P.T_GRAD))
+        P.ppll_block_profile_enable(blk.h, False)
+        blk.close()
+    assert all(np.array_equal(got[0][n], got[1][n]) for n in got[0])
+
+
+@pytest.mark.parametrize("kw", [dict(batch=4), dict(batch=128, dim=768, heads=12, mlp_dim=3072, depth=12, aux_depth=0)])
+def test_blocks_without_big_tiles_need_no_workspace_for_them(kw):
+    # few rows; more products than a launch of 384 x 192 tiles takes.  AdamW's blocks, which never have such tiles, keep one more
+    # moment of every parameter (whole 256 bytes)
+    from paper_2411_12780_amd import binding as P
+    bytes_of = lambda **o: P.ppll_block_workspace_bytes(P.make_config(synth.workload("vit_stage_bf16", **kw, **o)))
+    params = P.ppll_block_param_bytes(P.make_config(synth.workload("vit_stage_bf16", **kw)))
+    assert bytes_of(optimizer=synth.SGD) == bytes_of(optimizer=synth.ADAMW) - (params + 255) // 256 * 256
 
 
 def test_vit_large_image_bf16_full_size():

@@ -124,6 +124,15 @@ def test_weight_gradients_go_to_big_tiles_where_those_are_ahead(plan, rows, dim,
     assert big_grad_plan(plan, block_products(rows // 5, 5, dim, layers, pruned))["take"] == take
 
 
+def test_products_of_the_step_cases_go_where_they_say(plan):
+    # tests/test_gpu_parity.py, test_weight_gradients_on_*: 21 x 197 rows of width 768 on big tiles; 64 x 65 rows of width 576 not, with
+    # enough 128 x 128 tiles a layer for the side stream
+    assert big_grad_plan(plan, block_products(21, 197, 768, 1, True))["take"] == 1
+    narrow = block_products(64, 65, 576, 1, True)
+    assert big_grad_plan(plan, narrow)["take"] == 0
+    assert sum(-(-m // 128) * -(-n // 128) for m, n, _ in narrow[4:]) >= 256
+
+
 def test_every_big_tile_is_planned_once_and_the_parts_fill_a_round_at_most(plan):
     for rows in (5, 325, 1040, 8320, 25216, 130000):
         for dim in (64, 192, 200, 384, 768, 1024):
