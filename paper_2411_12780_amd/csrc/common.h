@@ -116,11 +116,14 @@ extern "C" __attribute__((visibility("hidden"))) __device__ const char _etext[];
 // Brings a kernel's own code into the L2 of its XCD at once.  A step goes through more code than the instruction cache holds and
 // through so much data that the code has left L2 as well by the time a kernel comes round again; its waves then wait for one line
 // after another from beyond L2.  So the first wave of the first workgroup on each XCD (workgroups go to the 8 XCDs in turn) asks for a
-// word of every line: CHUNKS instructions of 64 lines of 128 bytes.  The words go to 256 bytes of LDS that nothing else uses, so that
-// no register waits for them, and the wave does not end before they are there.
+// word of every line of the first CHUNKS x 8 KB: CHUNKS instructions of 64 lines of 128 bytes.  The words go to 256 bytes of LDS that
+// nothing else uses, so that no register waits for them, and the wave does not end before they are there.
 // Eight product kernels in turn, on operands that do not stay in L2, take 2.2 us a launch more than each of them over and over; with
-// this 0.7 (8320 x 384 x 384).  A step of 3 + 1 layers of width 384, 8320 rows: 938 -> 923 us.  Kernels of up to 4 KB and those of small
-// steps, whose data leave the code in L2, gain nothing and do without.
+// this 0.7 (8320 x 384 x 384).  A step of 3 + 1 layers of width 384, 8320 rows: 938 -> 923 us.  For the product kernels of full tiles and
+// the convolutions of 64 channels, of which 16 to 32 of up to 34 KB are brought, and for the kernel with copying waves (640 rows of
+// width 768 672 -> 666 us a step).  Not for the few-tile kernel of rows: its launches of some 4 us and of few data find their code in L2,
+// and the wave that waits for it ends last (evaluation of 155 rows of width 384 162.8 -> 164.9 us, a step of 210 rows of width 192
+// 339.4 -> 341.9); nor for attention, where steps of every size are level.
 typedef __attribute__((address_space(3))) char lds_byte;
 template <int CHUNKS> class CodeToL2 {
   const bool on_;

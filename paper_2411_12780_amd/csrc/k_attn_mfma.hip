@@ -112,7 +112,6 @@ constexpr int fwd_waves_per_simd(int nkt) { return nkt <= 3 ? 4 : nkt <= 5 ? 3 :
 template <int NKT>
 __global__ __launch_bounds__(64 * NKT, fwd_waves_per_simd(NKT)) void attn_fwd_mfma_kernel(const uint16_t* __restrict__ qkv, int T, int H,
                                                                             uint16_t* __restrict__ out, float* __restrict__ lse_out) {
-  PPLL_CODE_TO_L2(1);
   constexpr int TP = 32 * NKT, TILE = TP * 128;
   extern __shared__ __align__(1024) char smem[];      // K, V
   const int b = blockIdx.x / H, h = blockIdx.x % H, D = 64 * H;
@@ -214,7 +213,6 @@ template <int NKT>
 __global__ __launch_bounds__(64 * bwd_waves(NKT), bwd_waves_per_simd(NKT)) void attn_bwd_mfma_kernel(
     const uint16_t* __restrict__ qkv, const uint16_t* __restrict__ out, const uint16_t* __restrict__ dout, const float* __restrict__ lse,
     int T, int H, int heads, uint16_t* __restrict__ dqkv) {
-  PPLL_CODE_TO_L2(2);
   constexpr int TP = 32 * NKT, W = bwd_waves(NKT), TILE = TP * 128;
   constexpr bool BOTH = bwd_both(NKT);
   constexpr int QO = BOTH ? 2 * TILE : 0;      // tiles: K, V at 0, Q, dO at QO

@@ -220,7 +220,6 @@ __device__ __forceinline__ uint4 scaled8(const float* v, float a) {
 
 __global__ __launch_bounds__(CLS_THREADS) void attn_cls64_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ kv, int T,
                                                                      int H, uint16_t* __restrict__ out, float* __restrict__ prob) {
-  PPLL_CODE_TO_L2(1);
   extern __shared__ __align__(1024) char tiles[];      // K, V
   __shared__ __align__(16) float qs[64], ps[CLS64_TOKENS], red[CLS_THREADS / 64];
   const int b = blockIdx.x / H, h = blockIdx.x % H, D = H * 64, tid = threadIdx.x;
@@ -241,7 +240,6 @@ __global__ __launch_bounds__(CLS_THREADS) void attn_cls64_fwd_kernel(const uint1
 __global__ __launch_bounds__(CLS_THREADS) void attn_cls64_bwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ kv,
                                                                      const float* __restrict__ prob, const uint16_t* __restrict__ dout, int T,
                                                                      int H, uint16_t* __restrict__ dq, uint16_t* __restrict__ dkv) {
-  PPLL_CODE_TO_L2(1);
   extern __shared__ __align__(1024) char tiles[];      // K, V
   __shared__ __align__(16) float qs[64], dos[64], ps[CLS64_TOKENS], ds[CLS64_TOKENS], red[CLS_THREADS / 64];
   const int b = blockIdx.x / H, h = blockIdx.x % H, D = H * 64, tid = threadIdx.x;

@@ -68,7 +68,6 @@ template <int JN> struct Frags { bf16x8 a[U], b[U][JN]; uint4 raw[U * JN]; };   
 
 template <bool BT, int JN>
 __global__ __launch_bounds__(256) void gemm_rows_kernel(RowsArgs p) {
-  PPLL_CODE_TO_L2(1);
   constexpr int TN = 32 * JN, PART_LD = TN + 4, TR_PITCH = tr_pitch<JN>();
   constexpr int BT_BYTES = BT ? U * 16 * TR_PITCH : 0, PART_BYTES = 4 * 32 * PART_LD * 4;
   // the waves' B tiles, then (behind a barrier) their partial tiles
