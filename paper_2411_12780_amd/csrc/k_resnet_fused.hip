@@ -50,6 +50,11 @@ template <int C, bool BWD> constexpr int filter_bytes() {
   return BWD ? (C + 31) / 32 * 32 * (18 * C + 16) : 9 * C * ((C + 31) / 32 * 64);
 }
 constexpr int pixel_pitch(int C) { return 2 * C + 16; }
+// From this size of a map on, what the convolution stages is stored through L2: the kernels that follow find a smaller one in L2.
+// Microseconds of a step of four basic blocks, ordinary stores / through L2: 32 channels, 0.125 MB 167 / 170, 0.5 MB 175 / 177,
+// 1.5 MB 190 / 191, 2 MB 198 / 198, 4 MB 256 / 249; 16 channels, 0.125 MB 144 / 147, 1 MB 161 / 162, 2 MB 180 / 179, 4 MB 256 / 250.  With 64
+// channels the two are level up to 1.5 MB, and the choice in the kernel costs 1 %: always through.
+constexpr uint32_t THROUGH_BYTES = 2 << 20;
 
 template <int C, int WAVES, bool BWD>
 __global__ __launch_bounds__(64 * WAVES, C == 16 ? 4 : 1) void conv_bn_kernel(ConvBnArgs p) {
@@ -238,7 +243,8 @@ __global__ __launch_bounds__(64 * WAVES, C == 16 ? 4 : 1) void conv_bn_kernel(Co
         }
         if (off == CONV_OOB) o = make_uint4(0, 0, 0, 0);      // rows outside the image
         if (core) {
-          store_through((char*)p.mid + off, o);
+          if (C == 64 || p.bytes >= THROUGH_BYTES) store_through((char*)p.mid + off, o);
+          else *reinterpret_cast<uint4*>((char*)p.mid + off) = o;
           if (!BWD && p.mask_out) p.mask_out[off >> 4] = relu_mask(o);
         }
       }
