@@ -609,7 +609,7 @@ __global__ __launch_bounds__(256) void shortcut_bwd_bf16_kernel(const uint16_t* 
     const float hi = hi_bf(xw[j]) + (hi_bf(mw[j]) > 0.f ? hi_bf(dw[j]) : 0.f);
     o[j] = pack2(lo, hi);
   }
-  store_through(dx + xi, make_uint4(o[0], o[1], o[2], o[3]));
+  *reinterpret_cast<uint4*>(dx + xi) = make_uint4(o[0], o[1], o[2], o[3]);
 }
 
 bool al16(const void* p) { return !(((uintptr_t)p) & 15); }
