@@ -99,17 +99,12 @@ __device__ __forceinline__ void wave_sync() {
 // the stores of one instruction fill cache lines: pieces of lines, which L2 puts together otherwise, go out one by one (attention,
 // 32 bytes of a row at a time: that forward 3 us longer; few-tile products likewise: 497 -> 504 us for a step of 585 rows of width
 // 384; fp32 products, every other 16 bytes: 452 -> 481 us for a step of 148 rows of
-// width 768; convolution results, 8 bytes: steps a tenth longer).
+// width 768; convolution results, 8 bytes: steps a tenth longer).  Nor for maps so small that the next kernel finds them in L2: see
+// k_resnet_fused.hip.
 constexpr int THROUGH = 16;     // as the cache policy of a buffer store
 __device__ __forceinline__ void store_through(void* p, uint4 v) {
   typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;
   __builtin_amdgcn_global_store_b128((__attribute__((address_space(1))) u32x4_t*)p, (u32x4_t){v.x, v.y, v.z, v.w}, "agent");
-}
-__device__ __forceinline__ void store_through(void* p, float4 v) {
-  store_through(p, make_uint4(__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)));
-}
-__device__ __forceinline__ void store_through(void* p, uint2 v) {
-  __hip_atomic_store((uint64_t*)p, (uint64_t)v.y << 32 | v.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // End of the code object's instructions, defined by the linker.
 extern "C" __attribute__((visibility("hidden"))) __device__ const char _etext[];
