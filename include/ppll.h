@@ -127,7 +127,7 @@ int ppll_block_init(const ppll_block_config* cfg, void* workspace_dev, size_t wo
  * again by the backward part, so all three must stay valid and unmodified until
  * the stream has passed this call's work.  loss_dev: one float on the device
  * (may be null; ppll_block_sync still returns the loss).
- * A block with wide layers also launches part of its backward pass (the weight
+ * A block with wide layers may also launch part of its backward pass (the weight
  * gradients of upper layers) on a stream of its own, created at first use at
  * the default priority, forked from and joined back into `hip_stream` inside
  * this call: everything the call enqueued is complete once `hip_stream` has

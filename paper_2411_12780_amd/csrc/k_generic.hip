@@ -564,7 +564,8 @@ __global__ __launch_bounds__(64 * LNB_WAVES, 2) void layernorm_bwd_bf16_kernel(c
           if (SPARSE) o[e] = bf16_to_f32(f32_to_bf16(o[e]));
           o[e] += rv[e];
         }
-        *reinterpret_cast<uint4*>(dx + (size_t)row * D + 8 * lr + 8 * LPR * j) = make_uint4(pack_bf(o[0], o[1]), pack_bf(o[2], o[3]), pack_bf(o[4], o[5]), pack_bf(o[6], o[7]));
+        *reinterpret_cast<uint4*>(dx + (size_t)row * D + 8 * lr + 8 * LPR * j) =
+            make_uint4(pack_bf(o[0], o[1]), pack_bf(o[2], o[3]), pack_bf(o[4], o[5]), pack_bf(o[6], o[7]));
       }
     }
   }
@@ -1199,8 +1200,9 @@ __global__ __launch_bounds__(256) void assemble_tokens_bf16_kernel(const uint16_
   }
   const float4 p0 = *reinterpret_cast<const float4*>(pos + (size_t)t * D + d);
   const float4 p1 = *reinterpret_cast<const float4*>(pos + (size_t)t * D + d + 4);
-  *reinterpret_cast<uint4*>(x0 + i) = make_uint4(f32x2_to_bf16x2(v[0] + p0.x, v[1] + p0.y), f32x2_to_bf16x2(v[2] + p0.z, v[3] + p0.w),
-                                   f32x2_to_bf16x2(v[4] + p1.x, v[5] + p1.y), f32x2_to_bf16x2(v[6] + p1.z, v[7] + p1.w));
+  *reinterpret_cast<uint4*>(x0 + i) =
+      make_uint4(f32x2_to_bf16x2(v[0] + p0.x, v[1] + p0.y), f32x2_to_bf16x2(v[2] + p0.z, v[3] + p0.w),
+                 f32x2_to_bf16x2(v[4] + p1.x, v[5] + p1.y), f32x2_to_bf16x2(v[6] + p1.z, v[7] + p1.w));
 }
 __global__ __launch_bounds__(256) void scatter_cls_bf16_kernel(const uint16_t* dcls, int B, int T, int D, uint16_t* dx) {
   const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 8;

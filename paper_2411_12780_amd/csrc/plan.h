@@ -72,13 +72,14 @@ inline WeightGradPlan plan_weight_grads(const ProductShape* p, int n, bool works
   return w;
 }
 
-// ---- The same on tiles of 384 x 192, one workgroup a unit, in a launch that is the only one beside which nothing else runs
+// ---- The same on tiles of 384 x 192, one workgroup a unit, in the launch at the end of a backward pass (in a pipeline, other blocks' streams run
+// beside it)
 constexpr int BIG_EDGE_M = 384, BIG_EDGE = 192, BIG_PRODUCTS = 40;   // products of a launch: their table stays below the 4 KB of a kernel's arguments
 struct BigGradPlan { bool take; int cuts, long_tiles, whole_tiles, tiles, long_steps; };   // as WeightGradPlan
 inline long big_tiles(const ProductShape& p) { return (long)((p.M + BIG_EDGE_M - 1) / BIG_EDGE_M) * ((p.N + BIG_EDGE - 1) / BIG_EDGE); }
 
 // Whether a set of products goes there, and how it is divided: the tiles beyond the last full round in as many parts each as find
-// a unit, of 8 steps of 64 k or more.  The rule compares what both kernels take, fits to 25 sets of 1 to 6 layers of width 192 to 768
+// a unit: of 8 steps of 64 k or more for the longest reduction, of 2 for one that just counts as long.  The rule compares what both kernels take, fits to 25 sets of 1 to 6 layers of width 192 to 768
 // with 1040 to 25216 rows on 256 units, in microseconds: here 1.96 a step of a round, 8 for the launch, and for divided tiles 4 and 0.107 a
 // part (295 KB written and read again); there 0.74 a step of 128 x 128 tiles and unit, 10, and 12 more where they are fewer than
 // 0.6 a unit.  Measured there / here: width 384, 3 + 1 layers, 4160 rows 72 / 80, 8320 rows 132 / 123, 9280 rows 148 / 132; 3 + 2 layers,
@@ -162,8 +163,9 @@ inline double tile_rounds(int M, int N, int bm, int bn, int units, double last) 
 //   128 x 128   0.0161 K + 4.1 plain, 4.5 bias, 4.9 residual, 8.1 GELU (two tensors out), 5.2 its derivative (one more in)
 //   128 x 256   0.0280 K + 6.0        6.8       6.9           13.5                        10.3
 //   160 x 256   0.0316 K + 7.2        8.6       8.1           17.5                        14.1
-// and each product that runs on other tiles than its neighbours costs them about 3 us (the code of both kernels, 8 and 9 KB, is
-// fetched again: 4 us more for a tiled product behind one on wide tiles).  By rounds alone, some products ran longer than on the
+// and each product that runs on other tiles than its neighbours cost them about 3 us (the code of both kernels was fetched again, 4 us
+// more for a tiled product behind one on wide tiles; now that they bring it into L2 themselves it is less, and 3 us keep these three
+// kinds of tiles apart more than they need be).  By rounds alone, some products ran longer than on the
 // tiled kernel (33280 x 576 x 192 with a bias 24 -> 32 us), and so did steps of width 384 (25216 rows, two layers: products on the
 // tiled kernel 690 us, 730 by rounds).  Steps of two layers, 12 to 14 row counts from 2080 to 50432 in all, ms, by rounds / with
 // epilogue and change: width 128 4.78 / 4.52, 192 6.91 / 6.81, 256 8.76 / 8.63, 384 13.87 / 13.67, 512 19.44 / 19.44, 576 and 640
@@ -198,7 +200,9 @@ inline int wide_tile_rows(int M, int N, int K, ProductEnd end, int units) {
 // where the first three count a last round of at most one workgroup a unit as 0.55, 0.65 and 0.60 of one, the others one that fills the
 // share f of the units as 0.7 + 0.3 f.  The choice has to be 3 % ahead; over those products it is never behind, and 5 % ahead in
 // sum.  (Beside a tiled product the change of kernels costs less than it did: see CodeToL2.  With a microsecond for it, evaluation
-// forwards of width 384, 8320 rows, took 342 us, without 338.)
+// forwards of width 384, 8320 rows, took 342 us, without 338.)  These are launches alone, of one session; the figures of wide_tile_rows() are
+// fits to products inside steps, from before the kernels brought their code into L2 and stored through it.  They decide among the
+// first three kinds of tiles, these whether the fourth or fifth is ahead of that.
 inline int unit_tile_rows(int M, int N, int K, ProductEnd end, int wide, int units) {
   if (K < PIPE_MIN_K || units < 8) return 0;
   struct Cost { int rows, cols; double last, k, end[5], launch; };
