@@ -418,7 +418,8 @@ std::vector<GemmArgs> Block::weight_grads() const {
   const int D = cfg.dim, F = cfg.mlp_dim, T = cfg.tokens, B = cfg.batch, M = B * T;
   std::vector<GemmArgs> set;
   auto add = [&](const void* xin, long x_ld, int in_dim, const void* dy, long dy_ld, int out_dim, int K, size_t w_off, long ldw, size_t b_off) {
-    const GemmArgs g = wgrad_args(xin, x_ld, in_dim, dy, dy_ld, out_dim, K, grads + w_off, ldw, grads + b_off);
+    auto grad = [&](size_t off) { return (float*)((uintptr_t)grads + off * sizeof(float)); };
+    const GemmArgs g = wgrad_args(xin, x_ld, in_dim, dy, dy_ld, out_dim, K, grad(w_off), ldw, grad(b_off));
     if (gemm_weight_grad_groupable(g)) set.push_back(g);
   };
   for (int l = cfg.depth + cfg.aux_depth - 1; l >= 0; --l) {

@@ -204,7 +204,7 @@ bool gemm_mfma_groupable(const GemmArgs& g);
 // the k-steps out evenly over the compute units (parts of divided tiles pass through it)
 int launch_gemm_mfma_grouped(hipStream_t s, const GemmArgs* gs, int n, float* ws = nullptr, size_t ws_floats = 0, bool any_order = false);
 size_t gemm_mfma_balanced_floats();
-// The same on tiles of 384 x 192: see k_gemm_wgrad.hip.  ws: gemm_big_grads_floats() floats where the plan divides tiles.
+// The same on tiles of 384 x 192: see k_gemm_wgrad.hip.  ws: gemm_big_grads_floats(parts of the divided tiles) floats.
 struct BigGradPlan;
 size_t gemm_big_grads_floats(int parts);
 int launch_gemm_big_grads(hipStream_t s, const GemmArgs* gs, int n, float* ws, const BigGradPlan& plan);
