@@ -192,7 +192,11 @@ struct Block {
                const std::function<int()>& after_forward);
   int resnet_step(const void* x_in, const int32_t* labels, void* x_out, hipStream_t s,
                   const std::function<int()>& after_forward);
-  int encoder_fwd(int l, const EncoderActs& a, const void* x, void* x2_out, hipStream_t s);
+  // The layer's first LayerNorm has run (first_norm, or the layer before); `next`: the buffers of the layer that reads x2_out, whose first
+  // LayerNorm then runs here as well
+  int encoder_fwd(int l, const EncoderActs& a, const void* x, void* x2_out, const EncoderActs* next, hipStream_t s);
+  int first_norm(int l, const EncoderActs& a, const void* x, hipStream_t s);
+  NormOut first_norm_out(int l, const EncoderActs& a) const;
   int forward_eval_with(const EvalBuffers& e, const void* x_in, void* x_out, float* logits_out, hipStream_t s);
   size_t plan_eval_scratch(char* base, EvalBuffers* e) const;
   int encoder_bwd(int l, const void* x, const void* g_in, void* g_tmp, void* g_out, bool need_dx, hipStream_t s);

@@ -330,10 +330,17 @@ size_t Block::plan(char* base) {
 }
 
 // ------------------------------------------------------------------ ViT
-int Block::encoder_fwd(int l, const EncoderActs& a, const void* x, void* x2_out, hipStream_t s) {
+NormOut Block::first_norm_out(int l, const EncoderActs& a) const {
+  return {params + enc_p[l].ln1_g, params + enc_p[l].ln1_b, cfg.ln_eps, a.u1, a.mean1, a.rstd1};
+}
+int Block::first_norm(int l, const EncoderActs& a, const void* x, hipStream_t s) {
+  const NormOut n = first_norm_out(l, a);
+  return launch_layernorm_fwd(s, x, dt, cfg.dim, cfg.batch * cfg.tokens, cfg.dim, n.g, n.b, n.eps, n.y, n.mean, n.rstd);
+}
+
+int Block::encoder_fwd(int l, const EncoderActs& a, const void* x, void* x2_out, const EncoderActs* next, hipStream_t s) {
   const int D = cfg.dim, F = cfg.mlp_dim, T = cfg.tokens, H = cfg.heads, M = cfg.batch * T;
   const EncoderParams& p = enc_p[l];
-  PPLL_TRY(launch_layernorm_fwd(s, x, dt, D, M, D, params + p.ln1_g, params + p.ln1_b, cfg.ln_eps, a.u1, a.mean1, a.rstd1));
   GemmArgs g = gemm_args();
   g.A = a.u1; g.a_dt = dt; g.a_sm = D; g.a_sk = 1;
   g.B = wptr(p.qkv_w); g.b_dt = wdt(); g.b_sk = 3 * D; g.b_sn = 1;
@@ -345,8 +352,7 @@ int Block::encoder_fwd(int l, const EncoderActs& a, const void* x, void* x2_out,
   g.B = wptr(p.proj_w); g.b_dt = wdt(); g.b_sk = D; g.b_sn = 1;
   g.C = a.x1; g.c_dt = dt; g.ldc = D; g.M = M; g.N = D; g.K = D; g.bias = params + p.proj_b;
   g.residual = x; g.r_dt = dt; g.ldr = D;
-  PPLL_TRY(launch_gemm(s, g));
-  PPLL_TRY(launch_layernorm_fwd(s, a.x1, dt, D, M, D, params + p.ln2_g, params + p.ln2_b, cfg.ln_eps, a.u2, a.mean2, a.rstd2));
+  PPLL_TRY(launch_gemm_then_norm(s, g, {params + p.ln2_g, params + p.ln2_b, cfg.ln_eps, a.u2, a.mean2, a.rstd2}));
   g = gemm_args();
   g.A = a.u2; g.a_dt = dt; g.a_sm = D; g.a_sk = 1;
   g.B = wptr(p.fc1_w); g.b_dt = wdt(); g.b_sk = F; g.b_sn = 1;
@@ -358,7 +364,7 @@ int Block::encoder_fwd(int l, const EncoderActs& a, const void* x, void* x2_out,
   g.B = wptr(p.fc2_w); g.b_dt = wdt(); g.b_sk = D; g.b_sn = 1;
   g.C = x2_out; g.c_dt = dt; g.ldc = D; g.M = M; g.N = D; g.K = F; g.bias = params + p.fc2_b;
   g.residual = a.x1; g.r_dt = dt; g.ldr = D;
-  return launch_gemm(s, g);
+  return next ? launch_gemm_then_norm(s, g, first_norm_out(l + 1, *next)) : launch_gemm(s, g);
 }
 
 // g_in: gradient w.r.t. the layer output; g_tmp receives the gradient at the
@@ -389,17 +395,16 @@ int Block::encoder_bwd(int l, const void* x, const void* g_in, void* g_tmp, void
   g.epilogue = EPI_DGELU; g.aux = a.h; g.aux_dt = dt; g.ldaux = F;
   PPLL_TRY(launch_gemm(s, g));
   PPLL_TRY(wgrad(a.gl, F, g_in, D, p.fc2_w, p.fc2_b));
-  PPLL_TRY(launch_gemm(s, dgrad(d_h, F, p.fc1_w, D, d_u)));
+  PPLL_TRY(launch_gemm_then_norm_bwd(s, dgrad(d_h, F, p.fc1_w, D, d_u),
+                                     {a.x1, a.mean2, a.rstd2, params + p.ln2_g, g_in, g_tmp, grads + p.ln2_g, grads + p.ln2_b}, rq));
   PPLL_TRY(wgrad(a.u2, D, d_h, F, p.fc1_w, p.fc1_b));
-  PPLL_TRY(launch_layernorm_bwd(s, d_u, a.x1, dt, D, M, D, params + p.ln2_g, a.mean2, a.rstd2, g_in, 1, g_tmp, rq,
-                                grads + p.ln2_g, grads + p.ln2_b));
   PPLL_TRY(launch_gemm(s, dgrad(g_tmp, D, p.proj_w, D, d_u)));
   PPLL_TRY(wgrad(a.att, D, g_tmp, D, p.proj_w, p.proj_b));
   PPLL_TRY(launch_attention_bwd(s, a.qkv, a.att, d_u, a.lse, dt, cfg.batch, T, H, D / H, d_qkv));
-  PPLL_TRY(launch_gemm(s, dgrad(d_qkv, 3 * D, p.qkv_w, D, d_u)));
-  PPLL_TRY(wgrad(a.u1, D, d_qkv, 3 * D, p.qkv_w, p.qkv_b));
-  return launch_layernorm_bwd(s, d_u, x, dt, D, M, D, params + p.ln1_g, a.mean1, a.rstd1, g_tmp, 1,
-                              need_dx ? g_out : nullptr, rq, grads + p.ln1_g, grads + p.ln1_b);
+  PPLL_TRY(launch_gemm_then_norm_bwd(s, dgrad(d_qkv, 3 * D, p.qkv_w, D, d_u),
+                                     {x, a.mean1, a.rstd1, params + p.ln1_g, g_tmp, need_dx ? g_out : nullptr, grads + p.ln1_g,
+                                      grads + p.ln1_b}, rq));
+  return wgrad(a.u1, D, d_qkv, 3 * D, p.qkv_w, p.qkv_b);
 }
 
 GemmArgs Block::wgrad_args(const void* xin, long x_ld, int in_dim, const void* dy, long dy_ld, int out_dim, int K, float* dW, long ldw,
@@ -463,7 +468,6 @@ int Block::encoder_fwd_cls(int l, const EncoderActs& a, const ClsActs& c, const 
   const int D = cfg.dim, F = cfg.mlp_dim, T = cfg.tokens, H = cfg.heads, B = cfg.batch, M = B * T;
   const EncoderParams& p = enc_p[l];
   const size_t wsz = dtype_size(wdt());
-  PPLL_TRY(launch_layernorm_fwd(s, x, dt, D, M, D, params + p.ln1_g, params + p.ln1_b, cfg.ln_eps, a.u1, a.mean1, a.rstd1));
   GemmArgs g = gemm_args();   // keys and values of all tokens: columns D..3D of the QKV weight
   g.A = a.u1; g.a_dt = dt; g.a_sm = D; g.a_sk = 1;
   g.B = (const char*)wptr(p.qkv_w) + (size_t)D * wsz; g.b_dt = wdt(); g.b_sk = 3 * D; g.b_sn = 1;
@@ -555,10 +559,12 @@ int Block::vit_step(const void* x_in, const int32_t* labels, void* x_out, hipStr
     PPLL_TRY(launch_assemble_tokens(s, embed_tmp, dt, params + cls, params + pos, B, T, D, x0));
     x = x0;
   }
+  PPLL_TRY(first_norm(0, enc_a[0], x, s));
+  auto next = [&](int l) { return l + 1 < L + A ? &enc_a[l + 1] : nullptr; };
   for (int l = 0; l < L; ++l) {
     layer_in[l] = x;
     void* dst = l == L - 1 ? x_out : enc_a[l].x2;
-    PPLL_TRY(encoder_fwd(l, enc_a[l], x, dst, s));
+    PPLL_TRY(encoder_fwd(l, enc_a[l], x, dst, next(l), s));
     x = dst;
   }
   PPLL_TRY(mark_phase(1, s));   // module forward done
@@ -572,7 +578,7 @@ int Block::vit_step(const void* x_in, const int32_t* labels, void* x_out, hipStr
       x = cls_a.x2;
       head_xs = D;
     } else {
-      PPLL_TRY(encoder_fwd(l, enc_a[l], x, enc_a[l].x2, s));
+      PPLL_TRY(encoder_fwd(l, enc_a[l], x, enc_a[l].x2, next(l), s));
       x = enc_a[l].x2;
     }
   }
@@ -969,9 +975,12 @@ int Block::forward_eval_with(const EvalBuffers& e, const void* x_in, void* x_out
       PPLL_TRY(launch_assemble_tokens(s, e.embed_tmp, dt, params + cls, params + pos, B, T, D, e.x0));
       x = e.x0;
     }
+    PPLL_TRY(first_norm(0, e.enc(0), x, s));
+    const int layers = logits_out ? L + A : L;
+    auto next = [&](int l) { return l + 1 < layers ? &e.enc(l + 1) : nullptr; };
     for (int l = 0; l < L; ++l) {
       void* dst = l == L - 1 ? x_out : e.enc(l).x2;
-      PPLL_TRY(encoder_fwd(l, e.enc(l), x, dst, s));
+      PPLL_TRY(encoder_fwd(l, e.enc(l), x, dst, next(l), s));
       x = dst;
     }
     if (!logits_out) return PPLL_OK;
@@ -986,7 +995,7 @@ int Block::forward_eval_with(const EvalBuffers& e, const void* x_in, void* x_out
         PPLL_TRY(encoder_fwd_cls(l, a, c, x, s));
         head_xs = D;
       } else {
-        PPLL_TRY(encoder_fwd(l, a, x, a.x2, s));
+        PPLL_TRY(encoder_fwd(l, a, x, a.x2, next(l), s));
       }
       x = a.x2;
     }

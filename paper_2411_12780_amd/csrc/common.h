@@ -272,6 +272,22 @@ int launch_layernorm_bwd(hipStream_t s, const void* dy, const void* x, int dt, l
 // times as many rows (3152 instead of 526 at 25216 x 768); what then finds no room of its own is finished at once.
 size_t layernorm_bwd_partial_floats(int rows, int D, int dt);
 size_t layernorm_bwd_most_floats(int rows, int D, int dt);
+int layernorm_bwd_rows(int rows, int D);       // rows that leave one partial row, on the bf16 path
+// the second stage of those sums
+int layernorm_bwd_reduce(hipStream_t s, ReduceQueue& rq, bool queued, const float* partials, int chunks, int D, float* dg, float* db);
+
+// A Linear product and the LayerNorm behind it, in one launch where that is ahead (k_gemm_norm.hip), else in two.
+// forward: C = product, y = LayerNorm(C)
+struct NormOut { const float *g, *b; float eps; void* y; float *mean, *rstd; };
+int launch_gemm_then_norm(hipStream_t s, const GemmArgs& g, const NormOut& n);
+// backward: the product is the gradient dy at the output of the LayerNorm of x, dx = dres + LN'(dy) (dres, dx may be null).  C is where
+// dy goes if it goes anywhere: nothing else may read it.
+struct NormGrad { const void* x; const float *mean, *rstd, *g; const void* dres; void* dx; float *dg, *db; };
+int launch_gemm_then_norm_bwd(hipStream_t s, const GemmArgs& g, const NormGrad& n, ReduceQueue& rq);
+bool gemm_norm_fwd_supported(const GemmArgs& g, const NormOut& n);
+bool gemm_norm_bwd_supported(const GemmArgs& g, const NormGrad& n);
+int launch_gemm_norm_fwd(hipStream_t s, const GemmArgs& g, const NormOut& n);
+int launch_gemm_norm_bwd(hipStream_t s, const GemmArgs& g, const NormGrad& n, ReduceQueue& rq);
 
 // out[n] = sum over rows of x[r, n]  (two-stage, deterministic)
 int launch_colsum(hipStream_t s, const void* x, int dt, int rows, int N, ReduceQueue& rq, float* out);

@@ -85,6 +85,17 @@ int launch_gemm(hipStream_t s, const GemmArgs& g) {
   return gemm_f32_supported(g) && g.a_sk == 1 ? launch_gemm_f32(s, g) : launch_gemm_generic(s, g);
 }
 
+int launch_gemm_then_norm(hipStream_t s, const GemmArgs& g, const NormOut& n) {
+  if (gemm_norm_fwd_supported(g, n) && norm_tiles(g.M, g.N, g.K, compute_units())) return launch_gemm_norm_fwd(s, g, n);
+  PPLL_TRY(launch_gemm(s, g));
+  return launch_layernorm_fwd(s, g.C, g.c_dt, g.ldc, g.M, g.N, n.g, n.b, n.eps, n.y, n.mean, n.rstd);
+}
+int launch_gemm_then_norm_bwd(hipStream_t s, const GemmArgs& g, const NormGrad& n, ReduceQueue& rq) {
+  if (gemm_norm_bwd_supported(g, n) && norm_tiles(g.M, g.N, g.K, compute_units())) return launch_gemm_norm_bwd(s, g, n, rq);
+  PPLL_TRY(launch_gemm(s, g));
+  return launch_layernorm_bwd(s, g.C, n.x, g.c_dt, g.N, g.M, g.N, n.g, n.mean, n.rstd, n.dres, 1, n.dx, rq, n.dg, n.db);
+}
+
 int launch_gemm_group(hipStream_t s, const GemmArgs* gs, int n, float* ws, size_t ws_floats, bool any_order) {
   if (n <= 0) return PPLL_OK;
   return gs[0].a_dt == F32 ? launch_gemm_f32_grouped(s, gs, n) : launch_gemm_mfma_grouped(s, gs, n, ws, ws_floats, any_order);
@@ -173,4 +184,39 @@ extern "C" int ppll_internal_weight_grads(int n, const int* shape, const void* c
   const int rest = plan.long_tiles - plan.whole_tiles;
   if (rest < 0 || (rest > 0 && (size_t)rest * cuts > ws_floats / gemm_big_grads_floats(1))) { set_error("the workspace is too small"); return PPLL_ERR_WORKSPACE; }
   return launch_gemm_big_grads((hipStream_t)stream, gs.data(), n, ws, plan);
+}
+
+// A Linear product C[M,N] = A[M][K] B (+ bias + residual) and the LayerNorm behind it, in one launch (fused) or in two (the
+// tiled kernel first), for tests (no part of
+// the public interface).  Forward (x null): y, mean, rstd of C.  Backward (x given): dx = dres + LN'(product) and [dg | db] in dgb, with
+// room for the partial sums in scratch (layernorm_bwd_most_floats).
+extern "C" int ppll_internal_product_norm(int fused, int M, int N, int K, const void* A, long lda, const void* B, long ldb, int bt, void* C,
+                                          const float* bias, const void* residual, const float* gamma, const float* beta, float eps, void* y,
+                                          float* mean, float* rstd, const void* x, const void* dres, void* dx, float* dgb, float* scratch, void* stream) {
+  using namespace ppll;
+  GemmArgs g{};
+  g.A = A; g.a_dt = BF16; g.a_sm = lda; g.a_sk = 1;
+  g.B = B; g.b_dt = BF16; g.b_sk = bt ? ldb : 1; g.b_sn = bt ? 1 : ldb;
+  g.C = C; g.c_dt = BF16; g.ldc = N; g.M = M; g.N = N; g.K = K;
+  g.bias = bias; g.residual = residual; g.r_dt = BF16; g.ldr = N;
+  hipStream_t s = (hipStream_t)stream;
+  if (x) {
+    const NormGrad n{x, mean, rstd, gamma, dres, dx, dgb, dgb + N};
+    ReduceQueue rq;
+    rq.scratch = scratch;
+    if (fused && gemm_norm_bwd_supported(g, n)) return launch_gemm_norm_bwd(s, g, n, rq);
+    if (!fused) {
+      PPLL_TRY(launch_gemm_mfma(s, g));
+      return launch_layernorm_bwd(s, C, x, BF16, N, M, N, gamma, mean, rstd, dres, 1, dx, rq, dgb, dgb + N);
+    }
+  } else {
+    const NormOut n{gamma, beta, eps, y, mean, rstd};
+    if (fused && gemm_norm_fwd_supported(g, n)) return launch_gemm_norm_fwd(s, g, n);
+    if (!fused) {
+      PPLL_TRY(launch_gemm_mfma(s, g));
+      return launch_layernorm_fwd(s, C, BF16, N, M, N, gamma, beta, eps, y, mean, rstd);
+    }
+  }
+  set_error("no fused kernel takes this product");
+  return PPLL_ERR_CONFIG;
 }

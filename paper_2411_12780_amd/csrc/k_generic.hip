@@ -6,6 +6,7 @@
 // reproducible run to run.
 #include "common.h"
 #include "plan.h"
+#include "ln_rows.h"
 
 namespace ppll {
 
@@ -410,34 +411,8 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const void* dy, cons
 }
 }  // namespace
 
-// ---- bf16 fast path: the row in registers, one pass
+// ---- bf16 fast path: the row in registers, one pass (ln_rows.h)
 namespace {
-__device__ __forceinline__ float lo_bf(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float hi_bf(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
-__device__ __forceinline__ uint32_t pack_bf(float a, float b) { return f32x2_to_bf16x2(a, b); }
-
-// Fast bf16 LayerNorm.  A row of D elements (a multiple of 64) is held by LPR lanes (8 for 64 and 192, 16 up to 384, 32 up
-// to 768, 64 for 1024), 8 consecutive elements (one 16-byte access) per lane and 8 LPR-column step, so a wave works on
-// 64 / LPR rows at once and the row sums are exchanges inside a lane group.
-template <int D_> struct LnShape {
-  static constexpr int D = D_;
-  static constexpr int LPR = D == 64 || D == 192 ? 8 : (D <= 384 ? 16 : (D <= 768 ? 32 : 64));
-  static constexpr int NV = D / (8 * LPR);       // 16-byte pieces per lane and row
-  static constexpr int RPW = 64 / LPR;           // rows per wave and pass
-  static_assert(NV * 8 * LPR == D, "a row is a whole number of pieces per lane");
-};
-template <int LPR>
-__device__ __forceinline__ float group_sum(float v) {
-  if constexpr (LPR >= 16) return lanes_sum<LPR>(v);
-#pragma unroll
-  for (int o = LPR / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-__device__ __forceinline__ void unpack8(const uint4& w, float* v) {
-  v[0] = lo_bf(w.x); v[1] = hi_bf(w.x); v[2] = lo_bf(w.y); v[3] = hi_bf(w.y);
-  v[4] = lo_bf(w.z); v[5] = hi_bf(w.z); v[6] = lo_bf(w.w); v[7] = hi_bf(w.w);
-}
-
 template <int DD>
 __global__ __launch_bounds__(256) void layernorm_fwd_bf16_kernel(const uint16_t* x, long xs, int rows,
                                                                  const float* g, const float* b, float eps,
@@ -447,35 +422,17 @@ __global__ __launch_bounds__(256) void layernorm_fwd_bf16_kernel(const uint16_t*
   const int lane = threadIdx.x & 63, lr = lane % LPR;
   const int row = (blockIdx.x * 4 + (threadIdx.x >> 6)) * RPW + lane / LPR;
   const bool ok = row < rows;
-  float v[8 * NV];
-  float s = 0.f;
+  uint4 w[NV], o[NV];
 #pragma unroll
   for (int j = 0; j < NV; ++j) {
-    uint4 w = make_uint4(0, 0, 0, 0);
-    if (ok) w = *reinterpret_cast<const uint4*>(x + (size_t)row * xs + 8 * lr + 8 * LPR * j);
-    unpack8(w, v + 8 * j);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) s += v[8 * j + e];
+    w[j] = make_uint4(0, 0, 0, 0);
+    if (ok) w[j] = *reinterpret_cast<const uint4*>(x + (size_t)row * xs + 8 * lr + 8 * LPR * j);
   }
-  const float mu = group_sum<LPR>(s) * (1.0f / D);
-  float q = 0.f;
-#pragma unroll
-  for (int j = 0; j < 8 * NV; ++j) { v[j] -= mu; q += v[j] * v[j]; }
-  const float rs = rsqrtf(group_sum<LPR>(q) * (1.0f / D) + eps);
+  float mu, rs;
+  ln_fwd_row<S>(w, lr, g, b, eps, mu, rs, o);
   if (!ok) return;
 #pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    const int c = 8 * lr + 8 * LPR * j;
-    const float4 g0 = *reinterpret_cast<const float4*>(g + c), g1 = *reinterpret_cast<const float4*>(g + c + 4);
-    const float4 b0 = *reinterpret_cast<const float4*>(b + c), b1 = *reinterpret_cast<const float4*>(b + c + 4);
-    const float* t = v + 8 * j;
-    uint4 o;
-    o.x = pack_bf(t[0] * rs * g0.x + b0.x, t[1] * rs * g0.y + b0.y);
-    o.y = pack_bf(t[2] * rs * g0.z + b0.z, t[3] * rs * g0.w + b0.w);
-    o.z = pack_bf(t[4] * rs * g1.x + b1.x, t[5] * rs * g1.y + b1.y);
-    o.w = pack_bf(t[6] * rs * g1.z + b1.z, t[7] * rs * g1.w + b1.w);
-    *reinterpret_cast<uint4*>(y + (size_t)row * D + c) = o;
-  }
+  for (int j = 0; j < NV; ++j) *reinterpret_cast<uint4*>(y + (size_t)row * D + 8 * lr + 8 * LPR * j) = o[j];
   if (lr == 0) { mean[row] = mu; rstd[row] = rs; }
 }
 
@@ -483,18 +440,6 @@ __global__ __launch_bounds__(256) void layernorm_fwd_bf16_kernel(const uint16_t*
 // delivers) is the latency of one row's chain - loads, two row sums, the write - so the rows are spread over as many waves
 // as there are: eight waves per workgroup, one pass over 64 / LPR rows each up to just under 1024 workgroups (four per unit on
 // 256 units), 512 to 1024 workgroups of more passes beyond (each leaves one partial row of dg, db, which a later kernel adds up).
-constexpr int LNB_WAVES = 8;
-template <int DD> constexpr int lnb_rows_per_pass() { return LNB_WAVES * LnShape<DD>::RPW; }
-// lane l and lane l ^ 32 (16): after the swap the sum a + b holds a's total on the lanes whose bit 5 (4) is clear and b's
-// on the others: one exchange folds two values
-__device__ __forceinline__ float fold32(float a, float b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float fold16(float a, float b) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
 // dres_every: rows r with r % dres_every == 0 take row r / dres_every of dres, the others none (1: every row its own)
 template <int DD, bool ONE, bool SPARSE>
 __global__ __launch_bounds__(64 * LNB_WAVES, 2) void layernorm_bwd_bf16_kernel(const uint16_t* dy, const uint16_t* x, long xs,
@@ -509,12 +454,10 @@ __global__ __launch_bounds__(64 * LNB_WAVES, 2) void layernorm_bwd_bf16_kernel(c
 #pragma unroll
   for (int j = 0; j < 8 * NV; ++j) { adg[j] = 0.f; adb[j] = 0.f; }
   const int r0 = blockIdx.x * (ONE ? 1 : passes) * (LNB_WAVES * RPW);
-  // the rows of a workgroup are summed in the same order whatever the grid: pass by pass inside a lane group, then across
-  // lane groups, then across waves
   for (int pass = 0; pass < (ONE ? 1 : passes); ++pass) {
     const int row = r0 + pass * (LNB_WAVES * RPW) + wave * RPW + sub;
     const bool ok = row < rows;
-    uint4 wx[NV], wd[NV], wr[NV];
+    uint4 wx[NV], wd[NV], wr[NV], o[NV];
     long rrow = row;
     bool has_res = dres != nullptr && ok;
     if (SPARSE) { rrow = row / dres_every; has_res = has_res && row % dres_every == 0; }
@@ -529,89 +472,15 @@ __global__ __launch_bounds__(64 * LNB_WAVES, 2) void layernorm_bwd_bf16_kernel(c
       if (has_res) wr[j] = *reinterpret_cast<const uint4*>(dres + (size_t)rrow * D + c);
     }
     const float mu = ok ? mean[row] : 0.f, rs = ok ? rstd[row] : 0.f;
-    float xh[8 * NV], dyh[8 * NV];
-    float s1 = 0.f, s2 = 0.f;
+    // a compact dres is added to the stored gradient: rounded to the activation type before and after
+    ln_bwd_row<S, SPARSE>(wx, wd, wr, ok, mu, rs, lr, g, adg, adb, o);
+    if (dx && ok)
 #pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const int c = 8 * lr + 8 * LPR * j;
-      const float4 g0 = *reinterpret_cast<const float4*>(g + c), g1 = *reinterpret_cast<const float4*>(g + c + 4);
-      const float gg[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-      float xv[8], dv[8];
-      unpack8(wx[j], xv);
-      unpack8(wd[j], dv);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int i = 8 * j + e;
-        xh[i] = ok ? (xv[e] - mu) * rs : 0.f;
-        adg[i] += dv[e] * xh[i];
-        adb[i] += dv[e];
-        dyh[i] = dv[e] * gg[e];
-        s1 += dyh[i];
-        s2 += dyh[i] * xh[i];
-      }
-    }
-    s1 = group_sum<LPR>(s1) * (1.0f / D);
-    s2 = group_sum<LPR>(s2) * (1.0f / D);
-    if (dx && ok) {
-#pragma unroll
-      for (int j = 0; j < NV; ++j) {
-        float o[8], rv[8];
-        unpack8(wr[j], rv);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          o[e] = rs * (dyh[8 * j + e] - s1 - xh[8 * j + e] * s2);
-          // a compact dres is added to the stored gradient: rounded to the activation type before and after
-          if (SPARSE) o[e] = bf16_to_f32(f32_to_bf16(o[e]));
-          o[e] += rv[e];
-        }
-        *reinterpret_cast<uint4*>(dx + (size_t)row * D + 8 * lr + 8 * LPR * j) =
-            make_uint4(pack_bf(o[0], o[1]), pack_bf(o[2], o[3]), pack_bf(o[4], o[5]), pack_bf(o[6], o[7]));
-      }
-    }
+      for (int j = 0; j < NV; ++j) *reinterpret_cast<uint4*>(dx + (size_t)row * D + 8 * lr + 8 * LPR * j) = o[j];
   }
-  // lane groups of a wave hold the same columns: fold them (dg to the lower half of the lanes, db to the upper half, then
-  // the halves of each in turn), then the waves through LDS
-  if (LPR <= 32) {
-    float f[8 * NV];
-#pragma unroll
-    for (int i = 0; i < 8 * NV; ++i) f[i] = fold32(adg[i], adb[i]);
-    if (LPR <= 16) {
-#pragma unroll
-      for (int i = 0; i < 4 * NV; ++i) f[i] = fold16(f[i], f[i + 4 * NV]);   // bit 4 of the lane now picks value i or i + 4 NV
-      if (LPR == 8) {
-#pragma unroll
-        for (int i = 0; i < 4 * NV; ++i) f[i] += __shfl_xor(f[i], 8, 64);
-      }
-      const int half = (lane >> 4) & 1, kind = lane >> 5;
-      if ((lane & 15) < LPR) {
-#pragma unroll
-        for (int i = 0; i < 4 * NV; ++i) {
-          const int v = i + half * 4 * NV;
-          sm[wave][kind * D + 8 * lr + 8 * LPR * (v >> 3) + (v & 7)] = f[i];
-        }
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < 8 * NV; ++i) sm[wave][(lane >> 5) * D + 8 * lr + 8 * LPR * (i >> 3) + (i & 7)] = f[i];
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < 8 * NV; ++i) {
-      const int c = 8 * lr + 8 * LPR * (i >> 3) + (i & 7);
-      sm[wave][c] = adg[i];
-      sm[wave][D + c] = adb[i];
-    }
-  }
+  ln_bwd_fold<S>(adg, adb, lane, sm[wave]);
   __syncthreads();
-  for (int i = threadIdx.x; i < D / 2; i += 64 * LNB_WAVES) {   // four of the 2 D columns
-    float4 t = *reinterpret_cast<const float4*>(&sm[0][4 * i]);
-#pragma unroll
-    for (int w = 1; w < LNB_WAVES; ++w) {
-      const float4 q = *reinterpret_cast<const float4*>(&sm[w][4 * i]);
-      t.x += q.x; t.y += q.y; t.z += q.z; t.w += q.w;
-    }
-    *reinterpret_cast<float4*>(partial + (size_t)blockIdx.x * 2 * D + 4 * i) = t;
-  }
+  ln_bwd_sum<D>(&sm[0][0], partial + (size_t)blockIdx.x * 2 * D, threadIdx.x, 64 * LNB_WAVES);
 }
 
 bool ln_fast_dim(int D) {
@@ -660,9 +529,10 @@ static int lnb_passes(int rows, int D) {
   const int p = rows / (lnb_pass_rows(D) * 512);
   return p < 1 ? 1 : p;
 }
+int layernorm_bwd_rows(int rows, int D) { return lnb_pass_rows(D) * lnb_passes(rows, D); }
 static size_t ln_floats(int rows, int D, int per) { return (size_t)((rows + per - 1) / per) * 2 * D; }
 size_t layernorm_bwd_partial_floats(int rows, int D, int dt) {
-  return ln_floats(rows, D, dt == BF16 && ln_fast_dim(D) ? lnb_pass_rows(D) * lnb_passes(rows, D) : LN_ROWS);
+  return ln_floats(rows, D, dt == BF16 && ln_fast_dim(D) ? layernorm_bwd_rows(rows, D) : LN_ROWS);
 }
 size_t layernorm_bwd_most_floats(int rows, int D, int dt) {
   const size_t usual = layernorm_bwd_partial_floats(rows, D, dt), stand_in = ln_floats(rows, D, LN_ROWS);
@@ -677,7 +547,7 @@ int launch_layernorm_bwd(hipStream_t s, const void* dy, const void* x, int dt, l
   bool queued;
   float* partials = rq.space(fast ? layernorm_bwd_partial_floats(rows, D, dt) : ln_floats(rows, D, LN_ROWS), &queued);
   if (fast) {
-    const int passes = lnb_passes(rows, D), per = lnb_pass_rows(D) * passes;
+    const int passes = lnb_passes(rows, D), per = layernorm_bwd_rows(rows, D);
     chunks = (rows + per - 1) / per;
 #define LNB_LAUNCH(ONE, SPARSE)                                                                                            \
   LN_DISPATCH(D, hipLaunchKernelGGL((layernorm_bwd_bf16_kernel<DD, ONE, SPARSE>), dim3(chunks), dim3(64 * LNB_WAVES), 0, s, \
@@ -695,6 +565,10 @@ int launch_layernorm_bwd(hipStream_t s, const void* dy, const void* x, int dt, l
                        dres, dres_every, dx_out, partials);
   }
   PPLL_HIP(hipGetLastError());
+  return layernorm_bwd_reduce(s, rq, queued, partials, chunks, D, dg, db);
+}
+
+int layernorm_bwd_reduce(hipStream_t s, ReduceQueue& rq, bool queued, const float* partials, int chunks, int D, float* dg, float* db) {
   // each partial row is [dg | db]; the two gradients are neighbours in the parameter table
   if (db == dg + D) return rq.reduce(s, queued, partials, chunks, 2 * D, 2L * D, 1.0f, dg);
   PPLL_TRY(rq.reduce(s, queued, partials, chunks, D, 2L * D, 1.0f, dg));

@@ -220,6 +220,23 @@ inline int unit_tile_rows(int M, int N, int K, ProductEnd end, int wide, int uni
   return t8 <= t10 ? 8 : 10;
 }
 
+// ---- A product of width 192 or 384 and the LayerNorm behind it in one launch, on whole rows: 64 of them a workgroup, two workgroups a unit
+// at width 192, one at 384.  Never where the product alone would be on the kernel that splits k (few_tiles): its sums are others.
+// Microseconds alone, two launches / one; K = N forward, 4 N forward, 4 N backward, 3 N backward:
+//   192:   4160 rows   9.8 / 7.3   12.2 / 11.9   16.2 / 16.4   15.2 / 14.6      384:   4160 rows  11.0 / 11.9   17.5 / 26.0   23.3 / 31.7   20.6 / 26.3
+//          8320       11.4 / 7.5   16.1 / 12.1   20.9 / 18.0   19.0 / 16.0             5200       12.5 / 12.0   22.8 / 26.2   29.0 / 32.5   25.4 / 27.3
+//         16640       14.1 / 10.4  23.6 / 21.5   34.0 / 27.6   29.3 / 23.0             8320       14.0 / 12.1   25.1 / 31.4   36.6 / 38.8   31.4 / 29.9
+//         25216       16.1 / 10.8  29.3 / 25.0   38.9 / 35.1   35.4 / 30.8            16640       24.0 / 26.2   42.9 / 62.6   57.8 / 77.9   51.0 / 65.6
+// Width 192: where the product alone is not on the kernel with copying waves (two blocks of 4160 rows with it on both sides of that line:
+// 405 us a step in two launches, 412 in one).  Width 384: one workgroup a unit waits for its own operands (0.78 us per 64 k), so only a
+// short reduction and one round (25216 rows: a step of 2 + 1 layers 0.3 % behind), not too small a part of one (5200 rows, 82 tiles: 0.4 %
+// behind; 8320 rows, 130: level, evaluation 0.9 % ahead).
+inline bool norm_tiles(int M, int N, int K, int units) {
+  if (units < 8 || few_tiles(M, N, K, units) || split_tiles(M, N, K, units)) return false;
+  const long tiles = (M + 63) / 64;
+  return N <= 192 || (K <= N && tiles <= units && 10 * tiles >= 4 * units);
+}
+
 // ---- The matrix-core attention addresses the keys, queries and values of an image with 32-bit byte offsets
 inline bool att_offsets_fit(int T, int H) { return (long)T * H * (3 * 64 * 2) <= 0x7fffffffL; }
 
