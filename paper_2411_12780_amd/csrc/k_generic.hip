@@ -424,10 +424,10 @@ __global__ __launch_bounds__(256) void layernorm_fwd_bf16_kernel(const uint16_t*
   const bool ok = row < rows;
   uint4 w[NV], o[NV];
 #pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    w[j] = make_uint4(0, 0, 0, 0);
-    if (ok) w[j] = *reinterpret_cast<const uint4*>(x + (size_t)row * xs + 8 * lr + 8 * LPR * j);
-  }
+  for (int j = 0; j < NV; ++j) w[j] = make_uint4(0, 0, 0, 0);
+  if (ok)
+#pragma unroll
+    for (int j = 0; j < NV; ++j) w[j] = *reinterpret_cast<const uint4*>(x + (size_t)row * xs + 8 * lr + 8 * LPR * j);
   float mu, rs;
   ln_fwd_row<S>(w, lr, g, b, eps, mu, rs, o);
   if (!ok) return;
