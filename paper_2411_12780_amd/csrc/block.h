@@ -122,8 +122,9 @@ struct Block {
   // Side stream of the backward pass (created at first use, default priority).  The weight-gradient products of a
   // layer are launched there once the layer's backward is enqueued, so they run next to the input-gradient chain of
   // the layers below, which never reads them; the step's stream waits for the side stream before the update.
-  // Off for blocks driven by a pipeline: there the other blocks' streams already fill the chip.
-  bool use_side = true;
+  // Off for blocks driven by a pipeline (alone = false): there the other blocks' streams already fill the chip.
+  bool alone = true;
+  GemmArgs gemm_args() const;
   bool time_launches = false;          // bracket every contraction launch of this block's steps with events
   LaunchTimes times;
   hipStream_t side = nullptr;

@@ -30,13 +30,14 @@ struct Bump {
   }
   float* floats(size_t n) { return (float*)take(n * sizeof(float)); }
 };
+}  // namespace
 
-GemmArgs gemm_args() {
+GemmArgs Block::gemm_args() const {
   GemmArgs g{};
   g.epilogue = EPI_NONE;
+  g.shared = !alone;
   return g;
 }
-}  // namespace
 
 int validate_config(const ppll_block_config* c) {
   if (!c) { set_error("config is null"); return PPLL_ERR_NULL; }
@@ -629,7 +630,7 @@ int Block::vit_step(const void* x_in, const int32_t* labels, void* x_out, hipStr
     // (not while launches are being timed one by one: overlapping kernels would stretch each other's brackets; nor where the launch
     // at the end runs on tiles of 384 x 192, which fill the chip by themselves and share no unit with the chain: width 768, 25216 rows:
     // 5129 us a step with the side stream, 5035 without)
-    if (use_side && !wgrad_big && dt == BF16 && !profile_enabled() && l > 0 && M >= SIDE_MIN_ROWS && wgrad_jobs.size() > 1) {
+    if (alone && !wgrad_big && dt == BF16 && !profile_enabled() && l > 0 && M >= SIDE_MIN_ROWS && wgrad_jobs.size() > 1) {
       long tiles = 0;
       for (size_t j = first_job; j < wgrad_jobs.size(); ++j)
         tiles += (long)((wgrad_jobs[j].M + 127) / 128) * ((wgrad_jobs[j].N + 127) / 128);

@@ -177,14 +177,15 @@ struct GemmArgs {
   const void* aux; int aux_dt; long ldaux;    // EPI_DGELU: the saved GELU derivative
   float* colsum;                              // optional: out[n] = sum_k B(k,n) (bias gradient of a dW product);
                                               // honoured only by the matrix-core kernels
+  bool shared;                                // launches of other blocks want the device's units at the same time (a pipeline)
 };
 int launch_gemm(hipStream_t s, const GemmArgs& g);          // picks the MFMA kernel when the shape allows
 int launch_gemm_generic(hipStream_t s, const GemmArgs& g);
 // Products with few output rows (the class-token rows of a pruned auxiliary layer): see k_gemm_rows.hip
 bool gemm_rows_supported(const GemmArgs& g);
 int launch_gemm_rows(hipStream_t s, const GemmArgs& g);
-// Products with many output tiles, bf16 output: see k_gemm_pipe.hip.  The choice (rows of a tile / 32, 0: not this kernel) goes to the
-// launch.
+// Products with many output tiles, bf16 output: see k_gemm_pipe.hip.  The choice (0: not this kernel, 3: 128 x 128 tiles with copying waves,
+// else rows of a tile / 32) goes to the launch.
 int gemm_pipe_choice(const GemmArgs& g);
 bool gemm_pipe_supported(const GemmArgs& g);
 int launch_gemm_pipe(hipStream_t s, const GemmArgs& g, int choice);

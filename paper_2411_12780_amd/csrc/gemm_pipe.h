@@ -67,14 +67,17 @@ template <bool TR, int ROWS, int KT = KS> struct Operand {
   }
 };
 
-// A workgroup of WGM_ x WGN_ waves, each 32 IM_ x 64 of the output tile, and NS_ stages in LDS
+// A workgroup of WGM_ x WGN_ waves, each 32 IM_ x 64 of the output tile, and NS_ stages in LDS.  Four stages of 64 k: as many waves again
+// that do nothing but copy.
 template <bool AT, bool BT, int WGM_, int WGN_, int IM_, int NS_, int KT_ = KS> struct Shape {
-  static constexpr int KT = KT_, WGN = WGN_, IM = IM_, NS = NS_, W = WGM_ * WGN_, THREADS = 64 * W, BM = WGM_ * IM * 32, BN = WGN_ * 64;
+  static constexpr int KT = KT_, WGN = WGN_, IM = IM_, NS = NS_, W = WGM_ * WGN_, BM = WGM_ * IM * 32, BN = WGN_ * 64;
+  static constexpr bool COPY_WAVES = KT == 64 && NS == 4;
+  static constexpr int THREADS = 64 * W * (COPY_WAVES ? 2 : 1);
   using OA = Operand<AT, BM, KT>;
   using OB = Operand<BT, BN, KT>;
   static constexpr int STAGE = OA::BYTES + OB::BYTES, LDS = NS * STAGE;
   static constexpr int COPIES = OA::COPIES / W + OB::COPIES / W;   // per wave and stage, of some waves one more
-  static_assert(OB::COPIES % W == 0 && (!AT || OA::COPIES % W == 0) && W % 2 == 0 && (KT == 32 ? NS >= 3 : NS == 2 && W == 8), "");
+  static_assert(OB::COPIES % W == 0 && (!AT || OA::COPIES % W == 0) && W % 2 == 0 && (KT == 32 ? NS >= 3 : (NS == 2 && W == 8) || COPY_WAVES), "");
 };
 
 // The fragments (8 consecutive k of one row per lane) of a wave's tile, 32 IM rows of A and 64 of B, at one k step of 16.  A
@@ -182,7 +185,82 @@ __device__ __forceinline__ void k_step(f32x16 (&acc)[2][IM], const Frags<AT, IM>
 #undef PPLL_CUR
 #undef PPLL_ROWS
 
-// acc[jn][im]: C^T tiles (the B fragment goes first into the MFMA): lane l holds row im*32 + l%32, columns jn*32 + 8 q +
+// The four k steps of a stage of 64 k in a wave that has 64 x 64 of a 128 x 128 tile, in order, and under them the reads of all
+// fragments of the next stage, which are there when the block ends.  (Read a k step ahead instead, 4 products do not cover the reads'
+// way: a stage of 8320 x 384 x 1536 took 0.49 us, 0.38 in one block.)
+template <bool BT> struct StageFrags {
+  Frags<false, 8> a;      // fragment 2 kk + i: k step kk, 32-row tile i
+  Frags<BT, 8> b;
+};
+template <bool BT>
+__device__ __forceinline__ void stage_step(f32x16 (&acc)[2][2], const StageFrags<BT>& f, StageFrags<BT>& n, int addrA, int addrB) {
+  if constexpr (BT) {
+    asm volatile("ds_read_b128 %[x0], %[ra0]\n ds_read_b128 %[x1], %[ra0] offset:4096\n ds_read_b64_tr_b16 %[l0], %[rb0] offset:0\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c00], %[q0], %[p0], %[c00]\n ds_read_b64_tr_b16 %[h0], %[rb0] offset:1024\n "
+                 "ds_read_b64_tr_b16 %[l1], %[rb1] offset:0\n ds_read_b64_tr_b16 %[h1], %[rb1] offset:1024\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c01], %[q0], %[p1], %[c01]\n ds_read_b128 %[x2], %[ra1]\n "
+                 "ds_read_b128 %[x3], %[ra1] offset:4096\n ds_read_b64_tr_b16 %[l2], %[rb0] offset:4096\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c10], %[q1], %[p0], %[c10]\n ds_read_b64_tr_b16 %[h2], %[rb0] offset:5120\n "
+                 "ds_read_b64_tr_b16 %[l3], %[rb1] offset:4096\n ds_read_b64_tr_b16 %[h3], %[rb1] offset:5120\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c11], %[q1], %[p1], %[c11]\n ds_read_b128 %[x4], %[ra2]\n "
+                 "ds_read_b128 %[x5], %[ra2] offset:4096\n ds_read_b64_tr_b16 %[l4], %[rb0] offset:8192\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c00], %[q2], %[p2], %[c00]\n ds_read_b64_tr_b16 %[h4], %[rb0] offset:9216\n "
+                 "ds_read_b64_tr_b16 %[l5], %[rb1] offset:8192\n ds_read_b64_tr_b16 %[h5], %[rb1] offset:9216\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c01], %[q2], %[p3], %[c01]\n ds_read_b128 %[x6], %[ra3]\n "
+                 "ds_read_b128 %[x7], %[ra3] offset:4096\n ds_read_b64_tr_b16 %[l6], %[rb0] offset:12288\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c10], %[q3], %[p2], %[c10]\n ds_read_b64_tr_b16 %[h6], %[rb0] offset:13312\n "
+                 "ds_read_b64_tr_b16 %[l7], %[rb1] offset:12288\n ds_read_b64_tr_b16 %[h7], %[rb1] offset:13312\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c11], %[q3], %[p3], %[c11]\n v_mfma_f32_32x32x16_bf16 %[c00], %[q4], %[p4], %[c00]\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c01], %[q4], %[p5], %[c01]\n v_mfma_f32_32x32x16_bf16 %[c10], %[q5], %[p4], %[c10]\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c11], %[q5], %[p5], %[c11]\n v_mfma_f32_32x32x16_bf16 %[c00], %[q6], %[p6], %[c00]\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c01], %[q6], %[p7], %[c01]\n v_mfma_f32_32x32x16_bf16 %[c10], %[q7], %[p6], %[c10]\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c11], %[q7], %[p7], %[c11]\n s_waitcnt lgkmcnt(0)"
+                 : [c00] "+v"(acc[0][0]), [c01] "+v"(acc[0][1]), [c10] "+v"(acc[1][0]), [c11] "+v"(acc[1][1]), [x0] "=&v"(n.a.v[0]),
+                   [x1] "=&v"(n.a.v[1]), [x2] "=&v"(n.a.v[2]), [x3] "=&v"(n.a.v[3]), [x4] "=&v"(n.a.v[4]), [x5] "=&v"(n.a.v[5]),
+                   [x6] "=&v"(n.a.v[6]), [x7] "=&v"(n.a.v[7]), [l0] "=&v"(n.b.lo[0]), [h0] "=&v"(n.b.hi[0]),
+                   [l1] "=&v"(n.b.lo[1]), [h1] "=&v"(n.b.hi[1]), [l2] "=&v"(n.b.lo[2]), [h2] "=&v"(n.b.hi[2]),
+                   [l3] "=&v"(n.b.lo[3]), [h3] "=&v"(n.b.hi[3]), [l4] "=&v"(n.b.lo[4]), [h4] "=&v"(n.b.hi[4]),
+                   [l5] "=&v"(n.b.lo[5]), [h5] "=&v"(n.b.hi[5]), [l6] "=&v"(n.b.lo[6]), [h6] "=&v"(n.b.hi[6]),
+                   [l7] "=&v"(n.b.lo[7]), [h7] "=&v"(n.b.hi[7])
+                 : [p0] "v"(f.a.get(0)), [q0] "v"(f.b.get(0)), [p1] "v"(f.a.get(1)), [q1] "v"(f.b.get(1)),
+                   [p2] "v"(f.a.get(2)), [q2] "v"(f.b.get(2)), [p3] "v"(f.a.get(3)), [q3] "v"(f.b.get(3)),
+                   [p4] "v"(f.a.get(4)), [q4] "v"(f.b.get(4)), [p5] "v"(f.a.get(5)), [q5] "v"(f.b.get(5)),
+                   [p6] "v"(f.a.get(6)), [q6] "v"(f.b.get(6)), [p7] "v"(f.a.get(7)), [q7] "v"(f.b.get(7)), [ra0] "v"(addrA),
+                   [ra1] "v"(addrA ^ 32), [ra2] "v"(addrA ^ 64), [ra3] "v"(addrA ^ 96), [rb0] "v"(addrB), [rb1] "v"(addrB ^ 64)
+                 : "memory");
+  } else {
+    asm volatile("ds_read_b128 %[x0], %[ra0]\n ds_read_b128 %[x1], %[ra0] offset:4096\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c00], %[q0], %[p0], %[c00]\n ds_read_b128 %[y0], %[rb0]\n "
+                 "ds_read_b128 %[y1], %[rb0] offset:4096\n v_mfma_f32_32x32x16_bf16 %[c01], %[q0], %[p1], %[c01]\n "
+                 "ds_read_b128 %[x2], %[ra1]\n ds_read_b128 %[x3], %[ra1] offset:4096\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c10], %[q1], %[p0], %[c10]\n ds_read_b128 %[y2], %[rb1]\n "
+                 "ds_read_b128 %[y3], %[rb1] offset:4096\n v_mfma_f32_32x32x16_bf16 %[c11], %[q1], %[p1], %[c11]\n "
+                 "ds_read_b128 %[x4], %[ra2]\n ds_read_b128 %[x5], %[ra2] offset:4096\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c00], %[q2], %[p2], %[c00]\n ds_read_b128 %[y4], %[rb2]\n "
+                 "ds_read_b128 %[y5], %[rb2] offset:4096\n v_mfma_f32_32x32x16_bf16 %[c01], %[q2], %[p3], %[c01]\n "
+                 "ds_read_b128 %[x6], %[ra3]\n ds_read_b128 %[x7], %[ra3] offset:4096\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c10], %[q3], %[p2], %[c10]\n ds_read_b128 %[y6], %[rb3]\n "
+                 "ds_read_b128 %[y7], %[rb3] offset:4096\n v_mfma_f32_32x32x16_bf16 %[c11], %[q3], %[p3], %[c11]\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c00], %[q4], %[p4], %[c00]\n v_mfma_f32_32x32x16_bf16 %[c01], %[q4], %[p5], %[c01]\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c10], %[q5], %[p4], %[c10]\n v_mfma_f32_32x32x16_bf16 %[c11], %[q5], %[p5], %[c11]\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c00], %[q6], %[p6], %[c00]\n v_mfma_f32_32x32x16_bf16 %[c01], %[q6], %[p7], %[c01]\n "
+                 "v_mfma_f32_32x32x16_bf16 %[c10], %[q7], %[p6], %[c10]\n v_mfma_f32_32x32x16_bf16 %[c11], %[q7], %[p7], %[c11]\n "
+                 "s_waitcnt lgkmcnt(0)"
+                 : [c00] "+v"(acc[0][0]), [c01] "+v"(acc[0][1]), [c10] "+v"(acc[1][0]), [c11] "+v"(acc[1][1]), [x0] "=&v"(n.a.v[0]),
+                   [x1] "=&v"(n.a.v[1]), [x2] "=&v"(n.a.v[2]), [x3] "=&v"(n.a.v[3]), [x4] "=&v"(n.a.v[4]), [x5] "=&v"(n.a.v[5]),
+                   [x6] "=&v"(n.a.v[6]), [x7] "=&v"(n.a.v[7]), [y0] "=&v"(n.b.v[0]), [y1] "=&v"(n.b.v[1]), [y2] "=&v"(n.b.v[2]),
+                   [y3] "=&v"(n.b.v[3]), [y4] "=&v"(n.b.v[4]), [y5] "=&v"(n.b.v[5]), [y6] "=&v"(n.b.v[6]), [y7] "=&v"(n.b.v[7])
+                 : [p0] "v"(f.a.get(0)), [q0] "v"(f.b.get(0)), [p1] "v"(f.a.get(1)), [q1] "v"(f.b.get(1)),
+                   [p2] "v"(f.a.get(2)), [q2] "v"(f.b.get(2)), [p3] "v"(f.a.get(3)), [q3] "v"(f.b.get(3)),
+                   [p4] "v"(f.a.get(4)), [q4] "v"(f.b.get(4)), [p5] "v"(f.a.get(5)), [q5] "v"(f.b.get(5)),
+                   [p6] "v"(f.a.get(6)), [q6] "v"(f.b.get(6)), [p7] "v"(f.a.get(7)), [q7] "v"(f.b.get(7)), [ra0] "v"(addrA),
+                   [ra1] "v"(addrA ^ 32), [ra2] "v"(addrA ^ 64), [ra3] "v"(addrA ^ 96), [rb0] "v"(addrB), [rb1] "v"(addrB ^ 32),
+                   [rb2] "v"(addrB ^ 64), [rb3] "v"(addrB ^ 96)
+                 : "memory");
+  }
+}
+
+// acc[jn][im] (of a wave that multiplies): C^T tiles (the B fragment goes first into the MFMA): lane l holds row im*32 + l%32, columns jn*32 + 8 q +
 // 4 (l/32) + e in element 4 q + e.  csum[jn] (COLSUM, wave-uniform do_colsum): this lane's share, k % 8 = e of its half of every
 // k step in element e, of the sum over k of B's row jn*32 + l%32.
 template <class S, bool AT, bool BT, bool COLSUM>
@@ -192,7 +270,7 @@ __device__ __forceinline__ void multiply(const __amdgpu_buffer_rsrc_t rsA, const
   constexpr int NS = S::NS, IM = S::IM, KT = S::KT;
   const int nk = (K + KT - 1) / KT;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % S::W;
   const int wm = wave / S::WGN, wn = wave % S::WGN;
   using OA = typename S::OA;
   using OB = typename S::OB;
@@ -253,6 +331,41 @@ __device__ __forceinline__ void multiply(const __amdgpu_buffer_rsrc_t rsA, const
       k_step<AT, BT, S::BM, S::BN, 1, IM>(acc, a0, b0, a1, b1, fa0 + st, fb0 + st);
       column_sums(b1);
       k_step<AT, BT, S::BM, S::BN, 0, IM>(acc, a1, b1, a0, b0, fa0 + nx, fb0 + nx);
+    }
+  } else if constexpr (S::COPY_WAVES) {
+    // All fragments of a stage are in registers before it is multiplied, so its place in LDS is filled again meanwhile: NS - 1 stages are on
+    // their way.  Issuing 32 copies takes a unit about as long as a stage's products take (0.35 us and 0.29, each without the other), and a
+    // wave that does both waits for them in turn (0.45): so four waves copy and four multiply (0.37).
+    static_assert(!AT && IM == 2 && S::BM == 128 && S::BN == 128, "");
+    if (tid >= 64 * S::W) {
+      for (int i = 0; i < NS; ++i) issue(i);
+      wait_vm<(NS - 1) * S::COPIES>();
+      barrier();
+      for (int i = 0; i < nk; ++i) {
+        wait_vm<(NS - 2) * S::COPIES>();     // this wave's part of stage i + 1 is in LDS
+        barrier();                           // and everyone's; nobody reads stage i any more
+        issue(i + NS);
+      }
+      wait_vm<0>();
+      barrier();
+      return;
+    }
+    StageFrags<BT> f0, f1;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { set_zero(f1.a, i); set_zero(f1.b, i); }
+    barrier();
+    stage_step<BT>(acc, f1, f0, fa0, fb0);   // the first fragments: products with zeros under the reads
+    int st = 0;
+    auto next = [&] {
+      barrier();
+      st = st + S::STAGE == NS * S::STAGE ? 0 : st + S::STAGE;
+    };
+    for (int i = 0; i < nk; i += 2) {
+      next();
+      stage_step<BT>(acc, f0, f1, fa0 + st, fb0 + st);
+      if (i + 1 >= nk) break;
+      next();
+      stage_step<BT>(acc, f1, f0, fa0 + st, fb0 + st);
     }
   } else {
     // two stages of 64 k: one is filled from the moment that everyone has read it until the same point a stage later

@@ -117,7 +117,7 @@ int launch_attention_bwd(hipStream_t s, const void* qkv, const void* out, const 
 
 }  // namespace ppll
 
-// One product on one kernel, for tests of a kernel against another (no part of the public interface): 1 few tiles, 2 tiled, 4 / 5 /
+// One product on one kernel, for tests of a kernel against another (no part of the public interface): 1 few tiles, 2 tiled, 3 tiles of 128 x 128 with copying waves, 4 / 5 /
 // 8 / 10 tiles of 128 / 160 / 256 / 320 rows of 256 columns, 6 tiles of 64 x 64.  C[M,N] = A[M][K] B, B [K][N] (bt) or [N][K], bf16 throughout.
 extern "C" int ppll_internal_product(int kernel, int M, int N, int K, const void* A, long lda, const void* B, long ldb, int bt,
                                      void* C, long ldc, const float* bias, const void* residual, int epilogue, void* C2,
@@ -132,7 +132,7 @@ extern "C" int ppll_internal_product(int kernel, int M, int N, int K, const void
   hipStream_t s = (hipStream_t)stream;
   if (kernel == 1 && gemm_rows_supported(g)) return launch_gemm_rows(s, g);
   if (kernel == 2 && gemm_mfma_supported(g)) return launch_gemm_mfma(s, g);
-  if ((kernel == 4 || kernel == 5 || kernel == 8 || kernel == 10) && gemm_pipe_supported(g)) return launch_gemm_pipe(s, g, kernel);
+  if ((kernel == 3 || kernel == 4 || kernel == 5 || kernel == 8 || kernel == 10) && gemm_pipe_supported(g)) return launch_gemm_pipe(s, g, kernel);
   if (kernel == 6 && gemm_split_supported(g)) return launch_gemm_split(s, g);
   set_error("kernel %d does not take this product", kernel);
   return PPLL_ERR_CONFIG;

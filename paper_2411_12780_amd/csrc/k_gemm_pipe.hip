@@ -2,13 +2,17 @@
 // tiled kernel, bit-identical results (the same order of k).
 //
 // The tiled kernel is held by the data movement of a 128 x 128 tile: 32 KB into LDS and 96 KB of LDS traffic per 64 k, through
-// registers, a wave reading 64 x 64.  Here a wave owns 128 x 64 or 160 x 64, operands go straight to LDS, and the fragment reads of a
-// k step run under the products of the one before.  Two forms (the rules are in plan.h):
+// registers, a wave reading 64 x 64.  Here operands go straight to LDS, and the fragment reads of a k step run under the products of the
+// one before.  Three forms (the rules are in plan.h), a wave owning 128 x 64 or 160 x 64 in the first two:
 //  128 x 256 or 160 x 256 tiles of four waves, three stages of 32 k, two workgroups a unit (72 or 78 KB of LDS each), so that one
 //    stores its tile under the other's products: where the epilogue is long or tiles are few;
 //  256 x 256 or 320 x 256 tiles of eight waves, two stages of 64 k, a unit to themselves (128 or 144 KB): a third less to bring into LDS,
 //    and rows of 128 bytes of an operand with k contiguous.  Rows of 64 bytes come from L2 at 26 bytes a clock and unit, whole cache
 //    lines at 52; brought 64 bytes a row, the copies of 25216 x 768 x 3072 alone took 76 us, whole lines 72 from HBM and 47 from L2.
+//  128 x 128 tiles of four waves that multiply, 64 x 64 each, and four that copy, four stages of 64 k, a unit to themselves (128 KB): where
+//    every tile finds a unit.  Units left over bring A into L2 ahead of the tiles.  Operands from beyond L2, tiled kernel -> without that
+//    -> with it: 8320 x 384 x 1536 21.4 -> 19.3 -> 15.8, x 1152 17.0 -> 15.2 -> 12.7, 8320 x 384 x 384 with a residual 10.5 -> 10.0 -> 9.6;
+//    5200 x 384 x 1536 20.1 -> 14.2, 4160 x 768 x 3072 36.5 -> 26 us.
 // Microseconds, tiled kernel -> first form -> second: 25216 x 768 x 3072 138 -> 117 -> 100 (1192 TFLOP/s), 25216 x 2304 x 768 132 -> 105 ->
 // 93, 25216 x 3072 x 768 with GELU 198 -> 172 -> 162 and with its derivative 182 -> 165 -> 151 (310 MB of epilogue traffic each),
 // 8320 x 1152 x 384 16.8 -> 16.4 -> 14.8, 8320 x 1536 x 384 with GELU 27.9 -> 24.8 -> 24.0.  What bounds it: in the main loop LDS reads and
@@ -27,6 +31,8 @@ struct PipeArgs {
   const uint16_t* B; long ldb;      // BT ? B[k*ldb + n] : B[n*ldb + k]
   uint16_t* C; long ldc;
   int M, N, K, tiles_n, tiles, per_xcd;
+  int tiles_m;                      // 0, or tiles are numbered column by column
+  int helpers;                      // workgroups an XCD that have no tile
   const float* bias;
   const uint16_t* residual; long ldr;
   int epilogue;
@@ -40,16 +46,50 @@ __device__ __forceinline__ u32x4 pack8(const float (&v)[8]) {
   return (u32x4){f32x2_to_bf16x2(v[0], v[1]), f32x2_to_bf16x2(v[2], v[3]), f32x2_to_bf16x2(v[4], v[5]), f32x2_to_bf16x2(v[6], v[7])};
 }
 
+// A workgroup beyond those that have tiles brings a share of what its XCD's tiles read into the L2 there, rows of A and columns of B k by k
+// ahead of them, then the residual, a word of every cache line (the words go to LDS that nothing reads, as in CodeToL2).  Tiles of a row of
+// them read the same rows at the same time, and a unit has about 25 GB/s of lines on their way from beyond L2: three tiles to a row get
+// through A at 1.6 TB/s.
+template <bool BT, int BM, int BN, int THREADS> __device__ __forceinline__ void bring_operands(const PipeArgs& p, int helper, lds_char* to) {
+  const int t0 = (blockIdx.x & 7) * p.per_xcd, t1 = min(t0 + p.per_xcd, p.tiles);
+  if (t0 >= t1) return;
+  const int row0 = p.tiles_m ? 0 : t0 / p.tiles_n * BM, rows = (p.tiles_m ? p.M : min(((t1 - 1) / p.tiles_n + 1) * BM, p.M)) - row0;
+  const int col0 = p.tiles_m ? t0 / p.tiles_m * BN : 0, cols = (p.tiles_m ? min(((t1 - 1) / p.tiles_m + 1) * BN, p.N) : p.N) - col0;
+  const int nl = (cols + 63) / 64, chunk = rows + (BT ? 64 * nl : cols), lines = chunk * ((p.K + 63) / 64);    // of 64 k, and in all
+  const int lda2 = (int)(p.lda * 2), ldb2 = (int)(p.ldb * 2), ldr2 = (int)(p.ldr * 2);
+  const __amdgpu_buffer_rsrc_t rsA = make_rsrc(p.A, p.a_bytes), rsB = make_rsrc(p.B, p.b_bytes), rsR = make_rsrc(p.residual, p.r_bytes);
+  const int lane = threadIdx.x & 63, first = helper * THREADS + (int)(threadIdx.x & ~63), step = p.helpers * THREADS;
+  for (int i0 = first; i0 < lines; i0 += step) {
+    const int i = i0 + lane, c = i / chunk, r = i - c * chunk, q = r - rows;
+    const int k = BT ? c * 64 + q / nl : 0;
+    const int offB = BT ? k < p.K ? k * ldb2 + col0 * 2 + q % nl * 128 : OOB : (col0 + q) * ldb2 + c * 128;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, to, 4, i < lines && q < 0 ? (row0 + r) * lda2 + c * 128 : OOB, 0, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, to, 4, i < lines && q >= 0 ? offB : OOB, 0, 0, 0);
+    wait_vm<2>();      // not so far ahead that L2 has lost it again (4160 x 768 x 3072: 26.8 us without this, 25.4)
+  }
+  if (p.residual)
+    for (int i0 = first; i0 < rows * nl; i0 += step) {
+      const int i = i0 + lane, r = i / nl;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsR, to, 4, r < rows ? (row0 + r) * ldr2 + col0 * 2 + (i - r * nl) * 128 : OOB, 0, 0, 0);
+    }
+  wait_vm<0>();
+}
+
 template <bool BT, int WGM, int WGN, int IM, int NS, int KT>
-__global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(PipeArgs p) {
+__global__ __launch_bounds__((Shape<false, BT, WGM, WGN, IM, NS, KT>::THREADS), 2) void gemm_pipe_kernel(PipeArgs p) {
   PPLL_CODE_TO_L2(4);
   using S = Shape<false, BT, WGM, WGN, IM, NS, KT>;
   constexpr int JN = 2;
   extern __shared__ __align__(1024) char smem[];
-  // XCD x (workgroup id % 8) takes a contiguous range of the tiles, row by row: they share operand panels in its L2
+  // XCD x (workgroup id % 8) takes a contiguous range of the tiles, row by row, or column by column where rows are the longer: they share
+  // operand panels in its L2
   const int slot = blockIdx.x >> 3, t = (blockIdx.x & 7) * p.per_xcd + slot;
+  if (S::COPY_WAVES && slot >= p.per_xcd) {   // a unit without a tile
+    bring_operands<BT, S::BM, S::BN, S::THREADS>(p, slot - p.per_xcd, (lds_char*)code_words__);
+    return;
+  }
   if (slot >= p.per_xcd || t >= p.tiles) return;
-  const int m0 = t / p.tiles_n * S::BM, n0 = t % p.tiles_n * S::BN;
+  const int m0 = (S::COPY_WAVES && p.tiles_m ? t % p.tiles_m : t / p.tiles_n) * S::BM, n0 = (S::COPY_WAVES && p.tiles_m ? t / p.tiles_m : t % p.tiles_n) * S::BN;
   f32x16 acc[JN][IM];
   float none[JN][8];
 #pragma unroll
@@ -60,6 +100,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(PipeArgs p
       for (int e = 0; e < 16; ++e) acc[j][i][e] = 0.f;
   multiply<S, false, BT, false>(make_rsrc(p.A, p.a_bytes), make_rsrc(p.B, p.b_bytes), p.lda, p.ldb, m0, n0, p.M, p.N, p.K,
                                 (lds_char*)smem, acc, none, false);
+  if (S::COPY_WAVES && threadIdx.x >= 64 * S::W) return;
 
   // Epilogue: a wave passes its accumulators (lane = one row, 4 consecutive columns a group) through its own piece of LDS, 32 rows
   // at a time, and takes them out 8 consecutive columns a lane; what a piece needs from memory is asked for one piece ahead.
@@ -142,17 +183,18 @@ __global__ __launch_bounds__(64 * WGM * WGN, 2) void gemm_pipe_kernel(PipeArgs p
   }
 }
 
-constexpr int WAVES_N = 4;
-
-template <bool BT, int WGM, int IM, int STAGES, int KT>
+template <bool BT, int WGM, int IM, int STAGES, int KT, int WAVES_N = 4>
 int pipe_launch(hipStream_t s, PipeArgs& p) {
   using S = Shape<false, BT, WGM, WAVES_N, IM, STAGES, KT>;
   p.tiles_n = (p.N + S::BN - 1) / S::BN;
-  p.tiles = (p.M + S::BM - 1) / S::BM * p.tiles_n;
+  const int tiles_m = (p.M + S::BM - 1) / S::BM;
+  p.tiles = tiles_m * p.tiles_n;
+  p.tiles_m = S::COPY_WAVES && tiles_m < p.tiles_n ? tiles_m : 0;
   p.per_xcd = (p.tiles + 7) / 8;
+  p.helpers = S::COPY_WAVES ? helper_workgroups(p.per_xcd, compute_units()) : 0;
   static OncePerDevice once;
   PPLL_TRY(raise_lds((const void*)gemm_pipe_kernel<BT, WGM, WAVES_N, IM, STAGES, KT>, S::LDS, once));
-  hipLaunchKernelGGL((gemm_pipe_kernel<BT, WGM, WAVES_N, IM, STAGES, KT>), dim3(8 * p.per_xcd), dim3(S::THREADS), S::LDS, s, p);
+  hipLaunchKernelGGL((gemm_pipe_kernel<BT, WGM, WAVES_N, IM, STAGES, KT>), dim3(8 * (p.per_xcd + p.helpers)), dim3(S::THREADS), S::LDS, s, p);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;
 }
@@ -168,7 +210,9 @@ bool gemm_pipe_supported(const GemmArgs& g) {
 int gemm_pipe_choice(const GemmArgs& g) {
   if (!gemm_pipe_supported(g)) return 0;
   const ProductEnd end = g.epilogue == EPI_GELU ? END_GELU : g.epilogue == EPI_DGELU ? END_DGELU : g.residual ? END_RESIDUAL : g.bias ? END_BIAS : END_PLAIN;
-  const int units = compute_units(), wide = wide_tile_rows(g.M, g.N, g.K, end, units), alone = unit_tile_rows(g.M, g.N, g.K, end, wide, units);
+  const int units = compute_units();
+  if (!g.shared && copy_wave_tiles(g.M, g.N, g.K, units)) return 3;
+  const int wide = wide_tile_rows(g.M, g.N, g.K, end, units), alone = unit_tile_rows(g.M, g.N, g.K, end, wide, units);
   return alone ? alone : wide;
 }
 
@@ -188,7 +232,8 @@ int launch_gemm_pipe(hipStream_t s, const GemmArgs& g, int im) {
   p.aux_bytes = g.epilogue == EPI_DGELU ? (uint32_t)(((long)(g.M - 1) * g.ldaux + g.N) * 2) : 0u;
   void* prof = nullptr;
   PPLL_TRY(profile_begin(s, 2.0 * g.M * g.N * g.K, &prof));
-  if (im == 4) PPLL_TRY((bt ? pipe_launch<true, 1, 4, 3, 32>(s, p) : pipe_launch<false, 1, 4, 3, 32>(s, p)));
+  if (im == 3) PPLL_TRY((bt ? pipe_launch<true, 2, 2, 4, 64, 2>(s, p) : pipe_launch<false, 2, 2, 4, 64, 2>(s, p)));
+  else if (im == 4) PPLL_TRY((bt ? pipe_launch<true, 1, 4, 3, 32>(s, p) : pipe_launch<false, 1, 4, 3, 32>(s, p)));
   else if (im == 5) PPLL_TRY((bt ? pipe_launch<true, 1, 5, 3, 32>(s, p) : pipe_launch<false, 1, 5, 3, 32>(s, p)));
   else if (im == 8) PPLL_TRY((bt ? pipe_launch<true, 2, 4, 2, 64>(s, p) : pipe_launch<false, 2, 4, 2, 64>(s, p)));
   else PPLL_TRY((bt ? pipe_launch<true, 2, 5, 2, 64>(s, p) : pipe_launch<false, 2, 5, 2, 64>(s, p)));

@@ -189,6 +189,31 @@ inline int wide_tile_rows(int M, int N, int K, ProductEnd end, int units) {
   return c4 <= c5 ? 4 : 5;
 }
 
+// Workgroups per XCD of a launch of copy_wave_tiles() that have no tile and bring operands into L2: one to a unit left over, up to 8 (more are no faster);
+// fewer than 4 cannot keep ahead of the tiles (9280 x 384 x 1536, microseconds: none 19.3, two 20.5, four 19.0; 8320 rows: none 19.3,
+// three 19.3, seven 17.3)
+inline int helper_workgroups(int per_xcd, int units) {
+  const int left = std::min(8, (units - 8 * per_xcd) / 8);
+  return left >= 4 ? left : 0;
+}
+
+// Tiles of 128 x 128 with copying waves, a unit each: wherever no unit gets two, unless they are few and the reduction is short, where the
+// tiled kernel's tiles of 64 rows find twice the units.  Microseconds, tiled kernel / this one, operands from beyond L2, by tiles:
+//   K = 384:   66 6.4 / 7.3    99 6.6 / 7.5   123 8.6 / 8.4   150 10.2 / 8.9   195 10.6 / 9.8   255 13.5 / 10.8
+//   K = 768:   72 8.7 / 9.2   102 9.2 / 9.5   144 13.5 / 10.8   198 14.2 / 12.1   252 19.2 / 14.3
+//   K = 1152:  66 11.1 / 10.5   99 13.0 / 11.9   123 15.8 / 11.9   195 17.2 / 13.0   255 22.9 / 15.9
+//   K = 3072:  72 25.6 / 23.4   102 26.7 / 23.5   144 34.0 / 24.0   198 36.5 / 26.9   252 49.5 / 34.6
+// (products whose 64 x 64 tiles find a unit each are on the kernel above).  Not for a block of a pipeline, beside whose launches others want
+// units (four blocks of width 384, 8320 rows: 2566 us a batch on the tiled kernel, 2600 here).  Nor where too few units are left over to bring
+// operands, as long as the tiled kernel's grid of whole rows of tiles per XCD needs no second round (9850 rows of width 384, 231 tiles, a
+// step of 2 + 1 layers 751 and 756 us; 10500 rows, 249 tiles, x 384 x 1536 30.4 and 22.2).
+inline bool copy_wave_tiles(int M, int N, int K, int units) {
+  const long rows = (M + 127) / 128, columns = (N + 127) / 128, tiles = rows * columns;
+  if (K < PIPE_MIN_K || units < 8 || tiles > units) return false;
+  if (helper_workgroups((int)(tiles + 7) / 8, units) == 0 && (rows + 7) / 8 * 8 * columns <= units) return false;
+  return K >= 1024 || 2 * tiles >= units;
+}
+
 // Rows / 32 of tiles that have a unit to themselves (256 x 256 or 320 x 256, eight waves), where they are expected to beat what
 // wide_tile_rows() says (`wide`), else 0.  Microseconds of a round of such a launch: per k, and with the epilogue; fits to 182
 // products of widths 192 to 1024 with 1800 to 50000 rows (within 5 % rms; the other tiles 8 to 11 %):

@@ -9,7 +9,7 @@ from paper_2411_12780_amd import binding as P
 
 pytestmark = pytest.mark.gpu
 
-FEW, TILED, WIDE_128, WIDE_160, SPLIT, UNIT_256, UNIT_320 = 1, 2, 4, 5, 6, 8, 10
+FEW, TILED, COPYING, WIDE_128, WIDE_160, SPLIT, UNIT_256, UNIT_320 = 1, 2, 3, 4, 5, 6, 8, 10
 NONE, GELU, DGELU = 0, 1, 2
 
 
@@ -241,3 +241,34 @@ def test_column_sums_on_big_tiles_are_sixteen_chains_a_column(K, cuts):
         halves = (pairs[:, 0] + pairs[:, 1]) + (pairs[:, 2] + pairs[:, 3])
         want = halves[0] + halves[1] if want is None else want + (halves[0] + halves[1])
     assert torch.equal(sums, want)
+
+
+@pytest.mark.parametrize("epilogue", [NONE, GELU, DGELU])
+@pytest.mark.parametrize("bt", [0, 1])
+@pytest.mark.parametrize("M,N,K", [
+    # edges of 128 x 128 tiles and of a stage of 64 k; one to sixteen stages, of which four are in LDS; more rows than columns of tiles and
+    # the other way round; tiles on some XCDs alone; 224 tiles, which leave four units an XCD over, and 232, which leave fewer
+    (1, 8, 128), (129, 136, 136), (127, 520, 200), (257, 128, 256), (640, 248, 1000), (130, 1160, 392), (128 * 16, 128 * 14, 192),
+    (128 * 29, 128 * 8, 136),
+])
+def test_tiles_with_copying_waves_give_what_the_tiled_kernel_gives(M, N, K, bt, epilogue):
+    g = torch.Generator(device="cuda").manual_seed(M * 1000 + N + K)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    A, B = rnd(M, K + 40)[:, :K], rnd(K, N + 8)[:, :N] if bt else rnd(N, K + 16)[:, :K]     # rows further apart than they are long
+    bias = torch.randn(N, generator=g, device="cuda") if epilogue != DGELU else None
+    residual = rnd(M, N) if epilogue == NONE else None
+    aux = rnd(M, N)
+    wide = [torch.full((M, N + 24), 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    status, C, C2 = product(TILED, A, B, bt, bias, None, epilogue, None if epilogue != DGELU else aux)
+    assert status == 0
+    status, D, D2 = product(COPYING, A, B, bt, bias, None, epilogue, None if epilogue != DGELU else aux)
+    assert status == 0
+    assert torch.equal(C, D) and torch.equal(C2, D2)
+    if residual is not None:                                  # its rows are brought ahead as well
+        a, b = (product(kernel, A, B, bt, bias, residual, epilogue, aux)[1] for kernel in (TILED, COPYING))
+        assert torch.equal(a, b)
+    # into a buffer wider than the result
+    if epilogue != DGELU:
+        for kernel, into in ((TILED, wide[0]), (COPYING, wide[1])):
+            assert product(kernel, A, B, bt, bias, None, NONE, None, C=into[:, :N], C2=into[:, :N])[0] == 0
+        assert torch.equal(wide[0], wide[1]) and bool((wide[1][:, N:] == 7.0).all())
