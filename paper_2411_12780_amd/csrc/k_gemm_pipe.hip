@@ -30,8 +30,8 @@ struct PipeArgs {
   const uint16_t* A; long lda;      // A[m*lda + k]
   const uint16_t* B; long ldb;      // BT ? B[k*ldb + n] : B[n*ldb + k]
   uint16_t* C; long ldc;
-  int M, N, K, tiles_n, tiles, per_xcd;
-  int tiles_m;                      // 0, or tiles are numbered column by column
+  int M, N, K;
+  TileMap map;
   int helpers;                      // workgroups an XCD that have no tile
   const float* bias;
   const uint16_t* residual; long ldr;
@@ -46,50 +46,29 @@ __device__ __forceinline__ u32x4 pack8(const float (&v)[8]) {
   return (u32x4){f32x2_to_bf16x2(v[0], v[1]), f32x2_to_bf16x2(v[2], v[3]), f32x2_to_bf16x2(v[4], v[5]), f32x2_to_bf16x2(v[6], v[7])};
 }
 
-// A workgroup beyond those that have tiles brings a share of what its XCD's tiles read into the L2 there, rows of A and columns of B k by k
-// ahead of them, then the residual, a word of every cache line (the words go to LDS that nothing reads, as in CodeToL2).  Tiles of a row of
-// them read the same rows at the same time, and a unit has about 25 GB/s of lines on their way from beyond L2: three tiles to a row get
-// through A at 1.6 TB/s.
-template <bool BT, int BM, int BN, int THREADS> __device__ __forceinline__ void bring_operands(const PipeArgs& p, int helper, lds_char* to) {
-  const int t0 = (blockIdx.x & 7) * p.per_xcd, t1 = min(t0 + p.per_xcd, p.tiles);
-  if (t0 >= t1) return;
-  const int row0 = p.tiles_m ? 0 : t0 / p.tiles_n * BM, rows = (p.tiles_m ? p.M : min(((t1 - 1) / p.tiles_n + 1) * BM, p.M)) - row0;
-  const int col0 = p.tiles_m ? t0 / p.tiles_m * BN : 0, cols = (p.tiles_m ? min(((t1 - 1) / p.tiles_m + 1) * BN, p.N) : p.N) - col0;
-  const int nl = (cols + 63) / 64, chunk = rows + (BT ? 64 * nl : cols), lines = chunk * ((p.K + 63) / 64);    // of 64 k, and in all
-  const int lda2 = (int)(p.lda * 2), ldb2 = (int)(p.ldb * 2), ldr2 = (int)(p.ldr * 2);
-  const __amdgpu_buffer_rsrc_t rsA = make_rsrc(p.A, p.a_bytes), rsB = make_rsrc(p.B, p.b_bytes), rsR = make_rsrc(p.residual, p.r_bytes);
-  const int lane = threadIdx.x & 63, first = helper * THREADS + (int)(threadIdx.x & ~63), step = p.helpers * THREADS;
-  for (int i0 = first; i0 < lines; i0 += step) {
-    const int i = i0 + lane, c = i / chunk, r = i - c * chunk, q = r - rows;
-    const int k = BT ? c * 64 + q / nl : 0;
-    const int offB = BT ? k < p.K ? k * ldb2 + col0 * 2 + q % nl * 128 : OOB : (col0 + q) * ldb2 + c * 128;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsA, to, 4, i < lines && q < 0 ? (row0 + r) * lda2 + c * 128 : OOB, 0, 0, 0);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsB, to, 4, i < lines && q >= 0 ? offB : OOB, 0, 0, 0);
-    wait_vm<2>();      // not so far ahead that L2 has lost it again (4160 x 768 x 3072: 26.8 us without this, 25.4)
-  }
-  if (p.residual)
-    for (int i0 = first; i0 < rows * nl; i0 += step) {
-      const int i = i0 + lane, r = i / nl;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsR, to, 4, r < rows ? (row0 + r) * ldr2 + col0 * 2 + (i - r * nl) * 128 : OOB, 0, 0, 0);
-    }
-  wait_vm<0>();
-}
-
 template <bool BT, int WGM, int WGN, int IM, int NS, int KT>
 __global__ __launch_bounds__((Shape<false, BT, WGM, WGN, IM, NS, KT>::THREADS), 2) void gemm_pipe_kernel(PipeArgs p) {
   PPLL_CODE_TO_L2(4);
   using S = Shape<false, BT, WGM, WGN, IM, NS, KT>;
   constexpr int JN = 2;
   extern __shared__ __align__(1024) char smem[];
-  // XCD x (workgroup id % 8) takes a contiguous range of the tiles, row by row, or column by column where rows are the longer: they share
-  // operand panels in its L2
-  const int slot = blockIdx.x >> 3, t = (blockIdx.x & 7) * p.per_xcd + slot;
-  if (S::COPY_WAVES && slot >= p.per_xcd) {   // a unit without a tile
-    bring_operands<BT, S::BM, S::BN, S::THREADS>(p, slot - p.per_xcd, (lds_char*)code_words__);
+  const int slot = blockIdx.x >> 3;
+  int tm, tn;
+  if (S::COPY_WAVES && slot >= p.map.per_xcd) {
+    const Bring b{p.A, p.B, p.residual, p.a_bytes, p.b_bytes, p.r_bytes, (int)(p.lda * 2), (int)(p.ldb * 2), (int)(p.ldr * 2), p.M, p.N, p.K, S::BM, S::BN, p.helpers};
+    bring_operands<BT, S::THREADS>(b, p.map, blockIdx.x & 7, slot - p.map.per_xcd, (lds_char*)code_words__);
     return;
   }
-  if (slot >= p.per_xcd || t >= p.tiles) return;
-  const int m0 = (S::COPY_WAVES && p.tiles_m ? t % p.tiles_m : t / p.tiles_n) * S::BM, n0 = (S::COPY_WAVES && p.tiles_m ? t / p.tiles_m : t % p.tiles_n) * S::BN;
+  if (S::COPY_WAVES) {
+    if (!tile_at(p.map, blockIdx.x & 7, slot, tm, tn)) return;
+  } else {
+    // XCD x (workgroup id % 8) takes a contiguous range of the tiles, row by row: they share operand panels in its L2
+    const int t = (blockIdx.x & 7) * p.map.per_xcd + slot;
+    tm = t / p.map.tiles_n;
+    tn = t % p.map.tiles_n;
+    if (slot >= p.map.per_xcd || tm >= p.map.tiles_m) return;
+  }
+  const int m0 = tm * S::BM, n0 = tn * S::BN;
   f32x16 acc[JN][IM];
   float none[JN][8];
 #pragma unroll
@@ -186,15 +165,17 @@ __global__ __launch_bounds__((Shape<false, BT, WGM, WGN, IM, NS, KT>::THREADS), 
 template <bool BT, int WGM, int IM, int STAGES, int KT, int WAVES_N = 4>
 int pipe_launch(hipStream_t s, PipeArgs& p) {
   using S = Shape<false, BT, WGM, WAVES_N, IM, STAGES, KT>;
-  p.tiles_n = (p.N + S::BN - 1) / S::BN;
-  const int tiles_m = (p.M + S::BM - 1) / S::BM;
-  p.tiles = tiles_m * p.tiles_n;
-  p.tiles_m = S::COPY_WAVES && tiles_m < p.tiles_n ? tiles_m : 0;
-  p.per_xcd = (p.tiles + 7) / 8;
-  p.helpers = S::COPY_WAVES ? helper_workgroups(p.per_xcd, compute_units()) : 0;
+  const int units = compute_units();
+  if (S::COPY_WAVES) {
+    p.map = tile_map(p.M, p.N, S::BM, S::BN, units);
+    p.helpers = helper_workgroups(p.map.per_xcd, units);
+  } else {
+    const int tiles_m = (p.M + S::BM - 1) / S::BM, tiles_n = (p.N + S::BN - 1) / S::BN;
+    p.map = TileMap{tiles_m, tiles_n, (int)(((long)tiles_m * tiles_n + 7) / 8), 0, 0, 0, false};
+  }
   static OncePerDevice once;
   PPLL_TRY(raise_lds((const void*)gemm_pipe_kernel<BT, WGM, WAVES_N, IM, STAGES, KT>, S::LDS, once));
-  hipLaunchKernelGGL((gemm_pipe_kernel<BT, WGM, WAVES_N, IM, STAGES, KT>), dim3(8 * (p.per_xcd + p.helpers)), dim3(S::THREADS), S::LDS, s, p);
+  hipLaunchKernelGGL((gemm_pipe_kernel<BT, WGM, WAVES_N, IM, STAGES, KT>), dim3(8 * (p.map.per_xcd + p.helpers)), dim3(S::THREADS), S::LDS, s, p);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;
 }

@@ -11,6 +11,9 @@
 // the loop took half as long again, the lines being fetched twice from beyond L2.  Smaller tiles find more units and copy more per
 // product; beyond one a unit the tiled kernel catches up (`split_tiles`).  64 KB of LDS and 118 registers a wave leave room for a workgroup of
 // another stream (with stages twice as deep a pipeline of three blocks of width 192, 4160 rows, took 570 us a batch instead of 520).
+// Operands from beyond L2, as in a step, took the loop half as long again; units without a tile bring them into L2 ahead of the tiles (Bring,
+// in gemm_pipe.h), and an XCD takes a block of the tiles where that shares more of them (tile_map): 640 x 768 x 3072 19.2 -> 11.9 us, x 2304
+// 15.3 -> 9.6, x 768 6.5 -> 5.5, 1105 x 768 x 3072 20.1 -> 17.0, 2176 x 384 x 1536 11.7 -> 9.3.
 // Microseconds, tiled kernel -> this one: 640 x 768 x 768 8.6 -> 5.8, 640 x 768 x 2304 17.7 -> 11.3, 640 x 768 x 3072 22.4 -> 14.2,
 // 1500 x 384 x 384 6.2 -> 4.3, 1500 x 384 x 1536 13.0 -> 8.3; a step of 3 + 1 layers of width 768, 640 rows, 776 -> 680.
 #include "common.h"
@@ -26,7 +29,9 @@ struct SplitArgs {
   const uint16_t* A; long lda;      // A[m*lda + k]
   const uint16_t* B; long ldb;      // BT ? B[k*ldb + n] : B[n*ldb + k]
   uint16_t* C; long ldc;
-  int M, N, K, tiles_n, tiles, per_xcd;
+  int M, N, K;
+  TileMap map;
+  int helpers;                      // workgroups an XCD that have no tile
   const float* bias;
   const uint16_t* side; long lds;   // residual, or the saved GELU derivative (EPI_DGELU)
   int epilogue;
@@ -156,10 +161,15 @@ template <bool BT>
 __global__ __launch_bounds__(64 * (WAVES + COPY_WAVES), 4) void gemm_split_kernel(SplitArgs p) {
   PPLL_CODE_TO_L2(1);
   __shared__ __align__(1024) char smem[STAGES * STAGE];
-  // XCD x (workgroup id % 8) takes a contiguous range of the tiles, row by row: they share operand panels in its L2
-  const int t = (blockIdx.x & 7) * p.per_xcd + (blockIdx.x >> 3);
-  if (t >= p.tiles) return;
-  const int m0 = t / p.tiles_n * EDGE, n0 = t % p.tiles_n * EDGE;
+  const int slot = blockIdx.x >> 3;
+  if (slot >= p.map.per_xcd) {
+    const Bring b{p.A, p.B, p.side, p.a_bytes, p.b_bytes, p.s_bytes, (int)(p.lda * 2), (int)(p.ldb * 2), (int)(p.lds * 2), p.M, p.N, p.K, EDGE, EDGE, p.helpers};
+    bring_operands<BT, 64 * (WAVES + COPY_WAVES)>(b, p.map, blockIdx.x & 7, slot - p.map.per_xcd, (lds_char*)code_words__);
+    return;
+  }
+  int tm, tn;
+  if (!tile_at(p.map, blockIdx.x & 7, slot, tm, tn)) return;
+  const int m0 = tm * EDGE, n0 = tn * EDGE;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int K = p.K, stages = (K + KT - 1) / KT;
   lds_char* lds = (lds_char*)smem;
@@ -264,10 +274,10 @@ int launch_gemm_split(hipStream_t s, const GemmArgs& g) {
   p.b_bytes = (uint32_t)((bt ? (long)(g.K - 1) * p.ldb + g.N : (long)(g.N - 1) * p.ldb + g.K) * 2);
   p.c_bytes = (uint32_t)(((long)(g.M - 1) * g.ldc + g.N) * 2);
   p.s_bytes = p.side ? (uint32_t)(((long)(g.M - 1) * p.lds + g.N) * 2) : 0u;
-  p.tiles_n = (g.N + EDGE - 1) / EDGE;
-  p.tiles = (g.M + EDGE - 1) / EDGE * p.tiles_n;
-  p.per_xcd = (p.tiles + 7) / 8;
-  const dim3 grid(8 * p.per_xcd), block(64 * (WAVES + COPY_WAVES));
+  const int units = compute_units();
+  p.map = tile_map(g.M, g.N, EDGE, EDGE, units);
+  p.helpers = g.shared ? 0 : helper_workgroups(p.map.per_xcd, units);
+  const dim3 grid(8 * (p.map.per_xcd + p.helpers)), block(64 * (WAVES + COPY_WAVES));
   void* prof = nullptr;
   PPLL_TRY(profile_begin(s, 2.0 * g.M * g.N * g.K, &prof));
   if (bt) hipLaunchKernelGGL(gemm_split_kernel<true>, grid, block, 0, s, p);

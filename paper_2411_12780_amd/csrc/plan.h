@@ -189,12 +189,39 @@ inline int wide_tile_rows(int M, int N, int K, ProductEnd end, int units) {
   return c4 <= c5 ? 4 : 5;
 }
 
-// Workgroups per XCD of a launch of copy_wave_tiles() that have no tile and bring operands into L2: one to a unit left over, up to 8 (more are no faster);
-// fewer than 4 cannot keep ahead of the tiles (9280 x 384 x 1536, microseconds: none 19.3, two 20.5, four 19.0; 8320 rows: none 19.3,
-// three 19.3, seven 17.3)
+// ---- Which tiles of a launch of one round go to which XCD (workgroup id % 8).  What an XCD's tiles read passes into its L2 from beyond,
+// so the fewer rows of A and columns of B they share among them, the better.
+constexpr int HELPERS_LEAST = 4, HELPERS_MOST = 8;   // of an XCD, see helper_workgroups()
+struct TileMap {
+  int tiles_m, tiles_n, per_xcd;   // workgroups an XCD: tiles, or places of which some have none
+  int rows, cols, across;          // blocks of rows x cols tiles, `across` of them side by side; rows = 0: a contiguous stretch, row by row
+  bool columns;                    // (of a stretch) column by column
+};
+// Stretches where they do: they are even, and leave each XCD as many units over.  Blocks where they read a fifth less: 640 x 768 in tiles of
+// 64 x 64 is 15 tiles an XCD, in stretches all columns and a row or two of rows, 960 rows and columns, in blocks 5 x 3, 512.
+inline TileMap tile_map(int M, int N, int bm, int bn, int units) {
+  TileMap t{(M + bm - 1) / bm, (N + bn - 1) / bn, 0, 0, 0, 0, false};
+  t.per_xcd = (int)(((long)t.tiles_m * t.tiles_n + 7) / 8);
+  t.columns = t.tiles_m < t.tiles_n;
+  const int shorter = std::min(t.tiles_m, t.tiles_n), longer = std::max(t.tiles_m, t.tiles_n);
+  const int places = units / 8 - t.per_xcd >= HELPERS_LEAST ? units / 8 - HELPERS_LEAST : units / 8;   // units an XCD that may have a tile
+  double least = 0.8 * (shorter + std::min(longer, (t.per_xcd + shorter - 1) / shorter + 1));
+  for (int across = 1; across <= 8; across *= 2) {
+    const int rows = (t.tiles_m * across + 7) / 8, cols = (t.tiles_n + across - 1) / across;
+    if ((long)rows * cols > places || rows + cols >= least) continue;
+    least = rows + cols;
+    t.rows = rows; t.cols = cols; t.across = across;
+  }
+  if (t.rows) t.per_xcd = t.rows * t.cols;
+  return t;
+}
+
+// Workgroups per XCD that have no tile and bring operands into L2 (Bring, in gemm_pipe.h): one to a unit left over, up to 8 (640 x 768 x 3072 in
+// tiles of 64 x 64, microseconds: none 19.2, four 15.7, eight 11.9, twelve 11.3, sixteen 12.0); fewer than 4 cannot keep ahead of the
+// tiles (9280 x 384 x 1536: none 19.3, two 20.5, four 19.0; 8320 rows: none 19.3, three 19.3, seven 17.3)
 inline int helper_workgroups(int per_xcd, int units) {
-  const int left = std::min(8, (units - 8 * per_xcd) / 8);
-  return left >= 4 ? left : 0;
+  const int left = std::min(HELPERS_MOST, units / 8 - per_xcd);
+  return left >= HELPERS_LEAST ? left : 0;
 }
 
 // Tiles of 128 x 128 with copying waves, a unit each: wherever no unit gets two, unless they are few and the reduction is short, where the

@@ -272,3 +272,21 @@ def test_tiles_with_copying_waves_give_what_the_tiled_kernel_gives(M, N, K, bt, 
         for kernel, into in ((TILED, wide[0]), (COPYING, wide[1])):
             assert product(kernel, A, B, bt, bias, None, NONE, None, C=into[:, :N], C2=into[:, :N])[0] == 0
         assert torch.equal(wide[0], wide[1]) and bool((wide[1][:, N:] == 7.0).all())
+
+
+@pytest.mark.parametrize("bt", [0, 1])
+@pytest.mark.parametrize("M,N,K", [
+    # tiles of 64 x 64 in blocks per XCD (the last ones ragged or empty) and in stretches; K in and out of whole stages
+    (640, 768, 384), (577, 712, 200), (300, 768, 136), (1105, 768, 128), (1000, 968, 264), (65, 960, 192), (705, 136, 392),
+])
+def test_maps_of_few_tiles_give_what_the_tiled_kernel_gives(M, N, K, bt):
+    g = torch.Generator(device="cuda").manual_seed(M * 1000 + N + K)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    A, B = rnd(M, K + 40)[:, :K], rnd(K, N + 8)[:, :N] if bt else rnd(N, K + 16)[:, :K]
+    bias, residual = torch.randn(N, generator=g, device="cuda"), rnd(M, N)
+    status, C, _ = product(TILED, A, B, bt, bias, residual, NONE, None)
+    assert status == 0
+    for kernel in (SPLIT, COPYING):
+        status, D, _ = product(kernel, A, B, bt, bias, residual, NONE, None)
+        assert status == 0
+        assert torch.equal(C, D), kernel
