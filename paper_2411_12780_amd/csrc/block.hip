@@ -294,6 +294,7 @@ size_t Block::plan(char* base) {
       if (conv_bn_ok(dt, B, d.Ho, d.Wo, d.Co)) {
         const size_t f = (size_t)conv_bn_stat_blocks(B, d.Ho, d.Wo, d.Co) * 2 * d.Co;
         if (f > partial_floats) partial_floats = f;
+        if (conv_bn_filter_floats(B, d.Ho, d.Wo, d.Co) > partial_floats) partial_floats = conv_bn_filter_floats(B, d.Ho, d.Wo, d.Co);
       }
   partials = bump.floats(partial_floats);
   // a convolution that finishes the sums in one area leaves those of its result in the other
@@ -320,9 +321,11 @@ size_t Block::plan(char* base) {
     const int Ch = cfg.channels, A = cfg.aux_channels, Hh = cfg.height, W = cfg.width;
     arena_floats = (size_t)conv3x3_wgrad_partial_floats(cfg.batch, Hh, W, Ch, A, 2) + 64 +
                    vit_head_partial_floats(cfg.batch, A, cfg.num_classes) + 256;
-    for (const BasicBlockDims& d : rb_d)
-      arena_floats += (size_t)conv3x3_wgrad_partial_floats(cfg.batch, d.Hin, d.Win, d.Ci, d.Co, d.stride) +
-                      (size_t)conv3x3_wgrad_partial_floats(cfg.batch, d.Ho, d.Wo, d.Co, d.Co, 1) + 128;
+    for (const BasicBlockDims& d : rb_d) {
+      const size_t here = conv_bn_ok(dt, cfg.batch, d.Ho, d.Wo, d.Co) ? conv_bn_filter_floats(cfg.batch, d.Ho, d.Wo, d.Co) : 0;
+      arena_floats += std::max((size_t)conv3x3_wgrad_partial_floats(cfg.batch, d.Hin, d.Win, d.Ci, d.Co, d.stride), here) +
+                      std::max((size_t)conv3x3_wgrad_partial_floats(cfg.batch, d.Ho, d.Wo, d.Co, d.Co, 1), here) + 128;
+    }
     if (stem) arena_floats += (size_t)conv3x3_wgrad_partial_floats(cfg.batch, in_h, in_w, stem_pad ? 16 : cfg.img_c, in_c, 1) + 64;
   }
   rq.arena = arena_floats ? bump.floats(arena_floats) : nullptr;
@@ -686,6 +689,13 @@ int Block::resnet_step(const void* x_in, const int32_t* labels, void* x_out, hip
   std::vector<const void*> block_in(n);
   std::vector<void*> block_out(n);
   const void* x = x_in;
+  // Whether the backward pass forms the weight gradient of a block's second convolution with its input gradient, and whether it goes on
+  // through the first one in the same way (the block input has a gradient, over an identity shortcut)
+  auto second_filter_from_bn = [&](int i) {
+    const BasicBlockDims& d = rb_d[i];
+    return conv_bn_ok(dt, B, d.Ho, d.Wo, d.Co) && conv_bn_filter_floats(B, d.Ho, d.Wo, d.Co) > 0;
+  };
+  auto whole_chain = [&](int i) { return rb_d[i].stride == 1 && rb_d[i].Ci == rb_d[i].Co && (i > 0 || stem); };
   // A BatchNorm whose input has just been written waits here: the next convolution applies it on the way in where it can
   // (stride 1, equal channels, bf16), else it runs on its own.  `area` holds its sums (bn.blocks rows; 0: none yet).
   // (x_in and x_out are the caller's, on a 16-byte boundary: every entry point checks that)
@@ -734,7 +744,9 @@ int Block::resnet_step(const void* x_in, const int32_t* labels, void* x_out, hip
     block_out[i] = i == n - 1 ? x_out : a.out;
     int ready = 0;
     PPLL_TRY(conv(x, wptr(p.conv1_w), d.Hin, d.Win, d.Ci, d.Co, d.stride, a.c1, &ready));
-    wait_bn(a.c1, rows, d.Co, a.mean1, a.rstd1, b1, p.bn1_g, p.bn1_b, nullptr, a.y1, a.mask1, ready);
+    // y1 is stored where something but the second convolution reads it
+    wait_bn(a.c1, rows, d.Co, a.mean1, a.rstd1, b1, p.bn1_g, p.bn1_b, nullptr, second_filter_from_bn(i) && whole_chain(i) ? nullptr : a.y1, a.mask1,
+            ready);
     PPLL_TRY(conv(a.y1, wptr(p.conv2_w), d.Ho, d.Wo, d.Co, d.Co, 1, a.c2, &ready));
     const void* skip = x;
     if (d.stride != 1 || d.Ci != d.Co) {
@@ -803,13 +815,14 @@ int Block::resnet_step(const void* x_in, const int32_t* labels, void* x_out, hip
   int ready = 0;
   // backward of the BatchNorm (in, out) with output gradient dy into d, then the input gradient of the convolution in front
   // of it into dst (+ the shortcut's gradient dres where dmask is set); next: the BatchNorm that dst is the output gradient of
+  // fg: the convolution's weight gradient as well, instead of d
   auto bn_conv_bwd = [&](const void* dy, const void* y, const uint8_t* mask, const void* xin, const float* mean, const float* rstd,
                          size_t g_off, size_t b_off, void* d, const void* w, int Hh, int Ww, int Co, const void* dres,
-                         const uint8_t* dmask, void* dst, const BnBwdSums* next) -> int {
+                         const uint8_t* dmask, void* dst, const BnBwdSums* next, const ConvFilterGrad* fg) -> int {
     if (ready == 0) PPLL_TRY(launch_bn_sums_bwd_bf16(s, dy, y, xin, B * Hh * Ww, Co, mean, rstd, area, &ready));
     BnGrad g{dy, xin, mask, area, ready, mean, rstd, params + g_off, params + b_off, grads + g_off, grads + b_off};
     ready = 0;
-    PPLL_TRY(launch_conv_bn_bwd(s, g, w, B, Hh, Ww, Co, d, dres, dmask, dst, next, other, &ready));
+    PPLL_TRY(launch_conv_bn_bwd(s, g, w, B, Hh, Ww, Co, d, dres, dmask, dst, next, other, &ready, fg, &rq));
     std::swap(area, other);
     return PPLL_OK;
   };
@@ -819,11 +832,13 @@ int Block::resnet_step(const void* x_in, const int32_t* labels, void* x_out, hip
     BasicBlockActs& a = rb_a[i];
     const int rows = B * d.Ho * d.Wo;
     const bool fused = conv_bn_ok(dt, B, d.Ho, d.Wo, d.Co), identity = d.stride == 1 && d.Ci == d.Co;
-    defer(a.y1, a.d2, grads + p.conv2_w, d.Ho, d.Wo, d.Co, d.Co, 1);
+    const bool filters = second_filter_from_bn(i);
+    if (!filters) defer(a.y1, a.d2, grads + p.conv2_w, d.Ho, d.Wo, d.Co, d.Co, 1);
     if (fused) {
       const BnBwdSums bn1{a.y1, a.c1, a.mean1, a.rstd1, area, a.mask1};
+      const ConvFilterGrad fg{grads + p.conv2_w, nullptr, params + p.bn1_g, params + p.bn1_b};
       PPLL_TRY(bn_conv_bwd(gcur, block_out[i], a.mask2, a.c2, a.mean2, a.rstd2, p.bn2_g, p.bn2_b, a.d2, wptr(p.conv2_w), d.Ho, d.Wo,
-                           d.Co, nullptr, nullptr, r_t1, &bn1));
+                           d.Co, nullptr, nullptr, r_t1, &bn1, filters ? &fg : nullptr));
     } else {
       PPLL_TRY(launch_bn_bwd(s, gcur, block_out[i], a.c2, dt, rows, d.Co, a.mean2, a.rstd2, params + p.bn2_g, area,
                              grads + p.bn2_g, grads + p.bn2_b, a.d2, ready));
@@ -832,14 +847,15 @@ int Block::resnet_step(const void* x_in, const int32_t* labels, void* x_out, hip
       PPLL_TRY(launch_conv3x3_dgrad(s, a.d2, wptr(p.conv2_w), wdt(), dt, B, d.Ho, d.Wo, d.Co, d.Co, 1, nullptr, nullptr, r_t1, &bn1,
                                     &ready));
     }
-    defer(block_in[i], a.d1, grads + p.conv1_w, d.Hin, d.Win, d.Ci, d.Co, d.stride);
+    if (!(filters && whole_chain(i))) defer(block_in[i], a.d1, grads + p.conv1_w, d.Hin, d.Win, d.Ci, d.Co, d.stride);
     // the BatchNorm in front of conv1: the second one of the block before (output block_out[i - 1]) or the stem's
     BnBwdSums front{};
     if (i > 0) front = BnBwdSums{block_out[i - 1], rb_a[i - 1].c2, rb_a[i - 1].mean2, rb_a[i - 1].rstd2, area, rb_a[i - 1].mask2};
     else if (stem) front = BnBwdSums{stem_y, stem_c, stem_mean, stem_rstd, area, stem_mask};
-    if (fused && identity && (i > 0 || stem)) {   // identity shortcut folded into the input gradient
+    if (fused && whole_chain(i)) {   // identity shortcut folded into the input gradient
+      const ConvFilterGrad fg{grads + p.conv1_w, block_in[i], nullptr, nullptr};
       PPLL_TRY(bn_conv_bwd(r_t1, a.y1, a.mask1, a.c1, a.mean1, a.rstd1, p.bn1_g, p.bn1_b, a.d1, wptr(p.conv1_w), d.Hin, d.Win, d.Ci,
-                           gcur, a.mask2, gcur, &front));
+                           gcur, a.mask2, gcur, &front, filters ? &fg : nullptr));
       continue;
     }
     PPLL_TRY(launch_bn_bwd(s, r_t1, a.y1, a.c1, dt, rows, d.Co, a.mean1, a.rstd1, params + p.bn1_g, area,

@@ -378,7 +378,8 @@ int launch_conv3x3_dgrad(hipStream_t s, const void* dy, const void* w, int wdt, 
 struct BnInput {
   const void* x; float* partials; int blocks;
   float eps, momentum; float *mean, *rstd, *run_mean, *run_var;
-  const float *g, *b; const void* res; void* y; uint8_t* mask;   // mask (nullable): receives the ReLU mask of y, a bit an element
+  const float *g, *b; const void* res; void* y; uint8_t* mask;   // mask (nullable): receives the ReLU mask of y, a bit an element; y
+                                                                 // may be null with 16 channels where nothing else reads it
 };
 // Backward: gradient dy at the BatchNorm's output, the output's ReLU mask, partial rows of its two sums, saved statistics,
 // where dgamma and dbeta go.
@@ -393,8 +394,13 @@ int launch_conv_bn_fwd(hipStream_t s, const BnInput* bn, const void* x, const vo
                        float* stat, int* stat_blocks);
 // d = gradient at the BatchNorm's input, dst = conv^T(d) (+ dres where dmask is set); next (nullable): the BatchNorm whose
 // output gradient dst is, its sums go to stat
+// fg (nullable, where conv_bn_filter_floats() says so): the convolution's weight gradient dw as well, in place of d, which is not stored.
+// in: its input, or null: that is relu(bn) of next->x with these g and b.
+struct ConvFilterGrad { float* dw; const void* in; const float *g, *b; };
+size_t conv_bn_filter_floats(int B, int H, int W, int C);      // room for the partial sums, 0: not from this kernel
 int launch_conv_bn_bwd(hipStream_t s, const BnGrad& bn, const void* w, int B, int H, int W, int C, void* d, const void* dres,
-                       const uint8_t* dmask, void* dst, const BnBwdSums* next, float* stat, int* stat_blocks);
+                       const uint8_t* dmask, void* dst, const BnBwdSums* next, float* stat, int* stat_blocks,
+                       const ConvFilterGrad* fg = nullptr, ReduceQueue* rq = nullptr);
 // the sums alone ([*blocks][2][C] partial rows, at most 256)
 int launch_bn_sums_fwd_bf16(hipStream_t s, const void* x, int rows, int C, float* partials, int* blocks);
 int launch_bn_sums_bwd_bf16(hipStream_t s, const void* dy, const void* y, const void* x, int rows, int C, const float* mean,

@@ -17,6 +17,7 @@ __device__ __forceinline__ int out_dim(int in, int stride) { return (in - 1) / s
 // no branch, only the offset CONV_OOB (buffers here stay below 2^30 bytes, checked by the launcher).
 typedef __attribute__((ext_vector_type(4))) uint32_t conv_u32x4;
 constexpr int CONV_OOB = 0x7fffffff;
+constexpr int CONV_OOB_BASE = 0x40000000;   // out of range after anything small is added
 __device__ __forceinline__ uint4 conv_buf_load16(__amdgpu_buffer_rsrc_t r, int off) {
   const conv_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
   return make_uint4(v.x, v.y, v.z, v.w);
