@@ -1,39 +1,35 @@
 // Linear-layer products with few output tiles: C[M,N] = A[M,K] B[K,N], bf16 operands, fp32 accumulation (v_mfma_f32_32x32x16_bf16), the epilogues of the tiled kernel.
 //
-// These are the products of the last auxiliary encoder layer when only its class-token rows are
-// computed (one row per image: M = batch) and all products of small batches.  They have almost no
-// arithmetic (0.04-0.15 GFLOP) and a reduction index of 384 to 3072, so what they cost is latency:
-// 64- or 128-row tiles give a few dozen workgroups that walk K one 64-wide step after the other
-// (0.4 us each).  Here a workgroup owns a 32 x 32 (32 x 64) output tile and its four waves
-// split K between them (each wave a contiguous quarter), every wave reading its operand fragments
-// straight from memory in the MFMA's register layout, several k-steps in flight at once; the four
-// partial tiles meet in LDS, are added in wave order (results do not depend on timing) and pass
-// through the epilogue.  Measured against the tiled kernel: 585 x 384 x 384 3.9 / 6.3 us, 585 x 384
-// x 1536 7.6 / 13.1 us.  Every tile reads its own operand rows, so once there are more tiles than
-// compute units the tiled kernel with its larger tiles is ahead (585 x 2304 x 768: 13.4 / 9.4 us):
-// see few_tiles in plan.h.
+// These are the products of the last auxiliary encoder layer when only its class-token rows are computed (one row per image: M = batch)
+// and all products of small batches.  They have almost no arithmetic (0.04 - 0.15 GFLOP) and a reduction index of 384 to 3072, so what
+// they cost is the way of their operands: 64- or 128-row tiles give a few dozen workgroups that walk K one 64-wide step after the other.
+// Here a workgroup owns a 32 x 32 (32 x 64) output tile and its four waves split K between them, each a contiguous quarter; the four
+// partial tiles meet in LDS, are added in wave order (results do not depend on timing) and pass through the epilogue.
+//  A wave copies its part of both operands straight into stages of its own in LDS, 64 k each and in whole cache lines, up to four stages
+// on their way, and waits for nobody.  (Fragments read from memory in the MFMA's layout, 32 bytes of a line at a time, filled the L1 with
+// lines that were gone before the next 32 bytes were asked for: more loads in flight made it slower.)  Units without a tile bring the
+// operands into the L2s (Bring, in gemm_pipe.h), an XCD's tiles share what they read (tile_map), and what the epilogue takes is asked for
+// before the products.  Two stages where the range of a wave is no longer, where there are more tiles than units, and in a pipeline, whose
+// other streams want LDS.  Microseconds, fragments from memory -> this, operands from beyond L2 (in brackets: from L2):
+//   128 x 768 x 3072  [K][N] 14.1 -> 8.6 (9.1 -> 6.4)   [N][K] 16.1 -> 7.6 (12.6 -> 6.0)      128 x 3072 x 768  GELU 9.0 -> 6.4   its derivative 10.2 -> 5.9
+//   128 x 384 x 1536          7.3 -> 5.4 (5.7 -> 4.8)           8.6 -> 5.0 (7.4 -> 4.7)       256 x 1536 x 384  GELU 5.5 -> 5.4   its derivative  6.2 -> 4.9
+//   128 x 768 x 768           5.4 -> 4.6                        5.9 -> 4.5                    256 x 3072 x 768  GELU 11.8 -> 11.0  its derivative 14.3 -> 9.6
+// A step of 3 + 1 layers of width 768, 640 rows, 610 -> 590 us, of width 384, 8320 rows, 890 -> 861, its evaluation 337 -> 323.
 //
-// Operand layouts: A is [M][K] with k contiguous (row stride lda: the class-token rows of a token
-// matrix are T*D apart).  B is either [N][K] with k contiguous (input gradients: W stored
-// [in,out] read as B(k = out, n = in)), one 16-byte load per fragment, or [K][N] with n contiguous
-// (forward: W [in,out]): a lane then needs 8 consecutive k of one column.  Each wave copies its
-// 64 x 32 piece of B to a private LDS tile as it lies in memory (16-byte loads and stores) and
-// takes the fragments out with the transposing LDS read; eight two-byte loads per fragment
-// instead were measured at 12.9 us per product against 5.7 us for the k-contiguous case.
+// Operand layouts: A is [M][K] with k contiguous (row stride lda: the class-token rows of a token matrix are T*D apart).  B is either
+// [N][K] with k contiguous (input gradients: W stored [in,out] read as B(k = out, n = in)) or [K][N] with n contiguous (forward: W
+// [in,out]), taken out of LDS with the transposing read.
 #include "common.h"
+#include "gemm_pipe.h"
 #include "plan.h"
 
 namespace ppll {
 
 namespace {
+using namespace pipe;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-constexpr int OOB = 0x7fffffff;        // no buffer here reaches 2^30 bytes (checked on the host)
-constexpr int OOB_BASE = 0x40000000;   // stays out of range after a k offset (< 2^30) is added
-constexpr int U = 4;                   // k-steps (of 16) per group of loads
-
+constexpr int KT = 64;                 // k of a stage: 128 bytes, one cache line, of a row of an operand with k contiguous
 struct RowsArgs {
   const uint16_t* A; long lda;
   const uint16_t* B; long ldb;
@@ -44,128 +40,152 @@ struct RowsArgs {
   int epilogue;
   uint16_t* C2;
   const uint16_t* aux; long ldaux;
-  uint32_t a_bytes, b_bytes;
+  const void* side; int lds2;          // what the epilogue takes, the residual or the saved GELU derivative, for the helpers; bytes from row to row
+  uint32_t a_bytes, b_bytes, s_bytes;
   int steps_per_wave;                  // 16-wide k-steps of each of the four waves
+  TileMap map;
+  int helpers;                         // workgroups an XCD that have no tile
 };
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const void* ptr, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(ptr), 0, (int)bytes, 0x00020000);
-}
-__device__ __forceinline__ bf16x8 load8(__amdgpu_buffer_rsrc_t r, int off) {
-  const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
-  return __builtin_bit_cast(bf16x8, v);
-}
-typedef __attribute__((ext_vector_type(4))) short s16x4;
-template <int JN> constexpr int tr_pitch() { return 64 * JN + 16; }   // bytes between the k rows of a wave's [64 k][32 JN n] tile of B in LDS
-// 4 consecutive k of one column out of a [k][n] tile: lane r of a 16-lane group hands in the address of 4 columns
-// (4 (r % 4) ..) at k row r / 4 and receives column r of the group's 16 at those four k rows
-__device__ __forceinline__ uint2 lds_read_tr(const char* p) {
-  const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p);
-  return __builtin_bit_cast(uint2, v);
+// A wave's stages in LDS: 32 rows of A and 32 JN of B, 64 k each.
+//  k contiguous in memory: [row][64 k], the 16-byte granule g of row r at g ^ ((r / 2) % 8).
+//  B with n contiguous: [64 k][32 JN n] as in memory; 64-byte windows (JN = 2) w of k row k at w ^ (k / 2 % 2).
+// The fragment reads then spread over all banks.  A copy instruction fills 1 KB in lane order: the lanes fetch in that order.
+constexpr int A_BYTES = 32 * KT * 2;
+template <int JN> constexpr int copies() { return 4 + 4 * JN; }
+template <int JN> constexpr int stage_bytes() { return copies<JN>() * 1024; }
+
+// The fragments of a stage, all there when the block ends (the compiler would order LDS reads that it knows of behind the copies into LDS)
+template <bool BT, int JN> __device__ __forceinline__ void read_stage(u32x4 (&a)[4], u32x4 (&b)[4][JN], int addrA, int addrB) {
+  asm volatile("ds_read_b128 %0, %4\n ds_read_b128 %1, %5\n ds_read_b128 %2, %6\n ds_read_b128 %3, %7\n s_waitcnt lgkmcnt(0)"
+               : "=&v"(a[0]), "=&v"(a[1]), "=&v"(a[2]), "=&v"(a[3])
+               : "v"(addrA), "v"(addrA ^ 32), "v"(addrA ^ 64), "v"(addrA ^ 96)
+               : "memory");
+#pragma unroll
+  for (int j = 0; j < JN; ++j) {
+    if constexpr (BT) {
+      constexpr int P = 64 * JN;       // bytes of a k row
+      const int at = addrB ^ (64 * j);
+      u32x2 lo[4], hi[4];
+      asm volatile("ds_read_b64_tr_b16 %0, %8\n ds_read_b64_tr_b16 %1, %8 offset:%9\n ds_read_b64_tr_b16 %2, %8 offset:%10\n "
+                   "ds_read_b64_tr_b16 %3, %8 offset:%11\n ds_read_b64_tr_b16 %4, %8 offset:%12\n ds_read_b64_tr_b16 %5, %8 offset:%13\n "
+                   "ds_read_b64_tr_b16 %6, %8 offset:%14\n ds_read_b64_tr_b16 %7, %8 offset:%15\n s_waitcnt lgkmcnt(0)"
+                   : "=&v"(lo[0]), "=&v"(hi[0]), "=&v"(lo[1]), "=&v"(hi[1]), "=&v"(lo[2]), "=&v"(hi[2]), "=&v"(lo[3]), "=&v"(hi[3])
+                   : "v"(at), "n"(4 * P), "n"(16 * P), "n"(20 * P), "n"(32 * P), "n"(36 * P), "n"(48 * P), "n"(52 * P)
+                   : "memory");
+#pragma unroll
+      for (int u = 0; u < 4; ++u) b[u][j] = (u32x4){lo[u].x, lo[u].y, hi[u].x, hi[u].y};
+    } else {
+      const int at = addrB + 32 * KT * 2 * j;
+      asm volatile("ds_read_b128 %0, %4\n ds_read_b128 %1, %5\n ds_read_b128 %2, %6\n ds_read_b128 %3, %7\n s_waitcnt lgkmcnt(0)"
+                   : "=&v"(b[0][j]), "=&v"(b[1][j]), "=&v"(b[2][j]), "=&v"(b[3][j])
+                   : "v"(at), "v"(at ^ 32), "v"(at ^ 64), "v"(at ^ 96)
+                   : "memory");
+    }
+  }
 }
 
-template <int JN> struct Frags { bf16x8 a[U], b[U][JN]; uint4 raw[U * JN]; };   // raw: a [K][N] operand on its way to LDS
-
-template <bool BT, int JN>
+// NS stages a wave
+template <bool BT, int JN, int NS>
 __global__ __launch_bounds__(256) void gemm_rows_kernel(RowsArgs p) {
-  constexpr int TN = 32 * JN, PART_LD = TN + 4, TR_PITCH = tr_pitch<JN>();
-  constexpr int BT_BYTES = BT ? U * 16 * TR_PITCH : 0, PART_BYTES = 4 * 32 * PART_LD * 4;
-  // the waves' B tiles, then (behind a barrier) their partial tiles
-  __shared__ __align__(16) char lds[4 * BT_BYTES > PART_BYTES ? 4 * BT_BYTES : PART_BYTES];
+  constexpr int TN = 32 * JN, PART_LD = TN + 4, STAGE = stage_bytes<JN>(), COPIES = copies<JN>();
+  // the waves' stages, then (behind a barrier) their partial tiles
+  extern __shared__ __align__(1024) char lds[];
   float (*part)[32][PART_LD] = reinterpret_cast<float (*)[32][PART_LD]>(lds);
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int r = lane & 31, g = lane >> 5;
-  const int m0 = blockIdx.y * 32, n0 = blockIdx.x * TN;
-  const __amdgpu_buffer_rsrc_t rsA = rows_rsrc(p.A, p.a_bytes), rsB = rows_rsrc(p.B, p.b_bytes);
-  // this lane's fragment row of A (output row m0 + r) and of B (output column n0 + 32 j + r), 8 k from k = .. + 8 g on
-  const int a_base = m0 + r < p.M ? (int)((long)(m0 + r) * p.lda * 2) : OOB_BASE;
-  int b_base[JN];   // [N][K]
+  static_assert(4 * 32 * PART_LD * 4 <= 4 * NS * STAGE, "");
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int r = lane & 31, half = lane >> 5;
+  const int slot = blockIdx.x >> 3;
+  if (slot >= p.map.per_xcd) {
+    const Bring b{p.A, p.B, p.side, p.a_bytes, p.b_bytes, p.s_bytes, (int)(p.lda * 2), (int)(p.ldb * 2), p.lds2, p.M, p.N, p.K, 32, TN, p.helpers};
+    bring_operands<BT, 256>(b, p.map, blockIdx.x & 7, slot - p.map.per_xcd, (lds_char*)lds);
+    return;
+  }
+  int tm, tn;
+  if (!tile_at(p.map, blockIdx.x & 7, slot, tm, tn)) return;
+  const int m0 = tm * 32, n0 = tn * TN;
+  const __amdgpu_buffer_rsrc_t rsA = make_rsrc(p.A, p.a_bytes), rsB = make_rsrc(p.B, p.b_bytes);
+  const int k_wave = wave * p.steps_per_wave * 16, k_end = min(p.K, k_wave + p.steps_per_wave * 16), lda2 = (int)(p.lda * 2), ldb2 = (int)(p.ldb * 2);
+  // what the lane fetches: byte offsets at the wave's first k, and that k
+  int va[4], vb[4 * JN], ka[2], kb = 0;
 #pragma unroll
-  for (int j = 0; j < JN; ++j) b_base[j] = n0 + 32 * j + r < p.N ? (int)((long)(n0 + 32 * j + r) * p.ldb * 2) : OOB_BASE;
-  const int k_wave = wave * p.steps_per_wave * 16, k_first = k_wave + 8 * g;
-  // [K][N]: a copy instruction covers RPI k rows of the group, 8 columns per lane
-  constexpr int SL = 4 * JN, RPI = 64 / SL;
-  const int t_row = lane / SL, t_col = (lane % SL) * 8;
-  const int t_base = n0 + t_col < p.N ? (n0 + t_col) * 2 : OOB_BASE;
-  const int b_step = (int)(p.ldb * 2);   // [K][N]: bytes between consecutive k
-  const int k_end = min(p.K, k_wave + p.steps_per_wave * 16);
-  // lane part of a fragment address in the LDS tile: k row 8 (lane / 32) + (lane % 16) / 4, columns 16 ((lane / 16) % 2) + 4 (lane % 4)
-  const int tr_lane = (8 * g + ((lane & 15) >> 2)) * TR_PITCH + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
-
-  auto load_group = [&](int gi, Frags<JN>& f) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int s = gi * U + u, k = k_first + 16 * s;
-      const bool in = s < p.steps_per_wave && k < p.K;
-      f.a[u] = load8(rsA, in ? a_base + 2 * k : OOB);
-      if (!BT) {
-#pragma unroll
-        for (int j = 0; j < JN; ++j) f.b[u][j] = load8(rsB, in ? b_base[j] + 2 * k : OOB);
-      }
+  for (int c = 0; c < 4 * JN; ++c) {
+    const int row = 8 * c + (lane >> 3), gran = (lane & 7) ^ ((lane >> 4) + 4 * (c & 1));
+    if (c < 2) ka[c] = k_wave + 8 * gran;
+    if (c < 4) va[c] = m0 + row < p.M ? (m0 + row) * lda2 + (k_wave + 8 * gran) * 2 : OOB_BASE;
+    if (!BT) {
+      vb[c] = n0 + row < p.N ? (n0 + row) * ldb2 + (k_wave + 8 * gran) * 2 : OOB_BASE;
+    } else {
+      constexpr int SL = 4 * JN, ROWS = 64 / SL;         // 16-byte slots of a k row, k rows of a copy
+      const int kr = ROWS * c + lane / SL, slot16 = JN == 1 ? lane & 3 : ((((lane & 7) >> 2) ^ ((kr >> 1) & 1)) * 4 + (lane & 3)), col = n0 + 8 * slot16;
+      if (c == 0) kb = k_wave + kr;
+      vb[c] = col < p.N && k_wave + kr < k_end ? (k_wave + kr) * ldb2 + col * 2 : OOB_BASE;
     }
-    if (BT) {
+  }
+  lds_char* to = (lds_char*)lds + wave * (NS * STAGE);
+  auto bring = [&](int s, int at) {    // stage s of the wave; what lies past its range of k reads as zeros
 #pragma unroll
-      for (int i = 0; i < U * JN; ++i) {
-        const int kr = k_wave + 16 * U * gi + RPI * i + t_row;
-        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rsB, kr < k_end ? t_base + kr * b_step : OOB, 0, 0);
-        f.raw[i] = make_uint4(v.x, v.y, v.z, v.w);
-      }
+    for (int c = 0; c < 4; ++c) load_to_lds(rsA, to + at + c * 1024, ka[c & 1] + KT * s < k_end ? va[c] + 2 * KT * s : OOB);
+#pragma unroll
+    for (int c = 0; c < 4 * JN; ++c) {
+      const int k = BT ? kb + 16 / JN * c : ka[c & 1];
+      load_to_lds(rsB, to + at + A_BYTES + c * 1024, k + KT * s < k_end ? vb[c] + (BT ? KT * s * ldb2 : 2 * KT * s) : OOB);
     }
   };
-  // [K][N] operand: through the wave's LDS tile into fragments
-  auto transpose_group = [&](Frags<JN>& f) {
-    if (!BT) return;
-    char* tile = lds + wave * BT_BYTES;
+  const int base = wave * (NS * STAGE) + (int)(uintptr_t)(lds_char*)lds;
+  const int addrA = base + r * 128 + ((half ^ ((r >> 1) & 7)) << 4);
+  const int kr = 8 * half + ((lane & 15) >> 2);
+  const int addrB = base + A_BYTES + (BT ? kr * (64 * JN) + (JN == 2 ? ((kr >> 1) & 1) << 6 : 0) + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2
+                                         : r * 128 + ((half ^ ((r >> 1) & 7)) << 4));
 #pragma unroll
-    for (int i = 0; i < U * JN; ++i) *reinterpret_cast<uint4*>(tile + (RPI * i + t_row) * TR_PITCH + t_col * 2) = f.raw[i];
-    wave_sync();
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int j = 0; j < JN; ++j) {
-        const char* q = tile + tr_lane + u * 16 * TR_PITCH + j * 64;
-        const uint2 lo = lds_read_tr(q), hi = lds_read_tr(q + 4 * TR_PITCH);
-        f.b[u][j] = __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
-      }
-    wave_sync();   // every lane has its fragments before the tile is written again
-  };
+  for (int s = 0; s < NS; ++s) bring(s, s * STAGE);
   f32x16 acc[JN];
 #pragma unroll
   for (int j = 0; j < JN; ++j)
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[j][i] = 0.f;
-  // the MFMA takes the B fragment first: a lane then holds 4 consecutive columns (n) of one output row (m)
-  auto multiply = [&](const Frags<JN>& f) {
+  // what the epilogue takes is on its way before the products
+  constexpr int TPR = TN / 4;
+  const int n = n0 + tid % TPR * 4;                      // N is a multiple of 8: four columns from a multiple of 4 below N are all inside
+  float4 bias = make_float4(0.f, 0.f, 0.f, 0.f);
+  uint2 side[JN][2];                                     // residual, factor
+  if (n < p.N && p.bias) bias = *reinterpret_cast<const float4*>(p.bias + n);
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int j = 0; j < JN; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[u][j], f.a[u], acc[j], 0, 0, 0);
-  };
-  Frags<JN> f0, f1;
-  const int groups = (p.steps_per_wave + U - 1) / U;
-  load_group(0, f0);
-  for (int gi = 0; gi < groups; gi += 2) {   // groups past the wave's range read as zeros
-    load_group(gi + 1, f1);
-    transpose_group(f0);
-    multiply(f0);
-    load_group(gi + 2, f0);
-    transpose_group(f1);
-    multiply(f1);
+  for (int pass = 0; pass < JN; ++pass) {
+    const int m = m0 + pass * (256 / TPR) + tid / TPR;
+    if (m < p.M && n < p.N) {
+      if (p.residual) side[pass][0] = *reinterpret_cast<const uint2*>(p.residual + (size_t)m * p.ldr + n);
+      if (p.epilogue == EPI_DGELU) side[pass][1] = *reinterpret_cast<const uint2*>(p.aux + (size_t)m * p.ldaux + n);
+    }
   }
-  if (BT) __syncthreads();
-  // acc[j][4 q + e] = C[m0 + r][n0 + 32 j + 8 q + 4 g + e] summed over this wave's k
+  const int stages = (p.steps_per_wave + KT / 16 - 1) / (KT / 16);
+  for (int s = 0, at = 0; s < stages; ++s) {
+    wait_vm<(NS - 1) * COPIES>();      // the oldest stage is there
+    u32x4 a[4], b[4][JN];
+    read_stage<BT, JN>(a, b, addrA + at, addrB + at);
+    bring(s + NS, at);
+    // the MFMA takes the B fragment first: a lane then holds 4 consecutive columns (n) of one output row (m)
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int j = 0; j < JN; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, b[u][j]), __builtin_bit_cast(bf16x8, a[u]), acc[j], 0, 0, 0);
+    at = at + STAGE == NS * STAGE ? 0 : at + STAGE;
+  }
+  wait_vm<0>();                        // no copy lands in a partial tile
+  __syncthreads();
+  // acc[j][4 q + e] = C[m0 + r][n0 + 32 j + 8 q + 4 half + e] summed over this wave's k
 #pragma unroll
   for (int j = 0; j < JN; ++j)
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      *reinterpret_cast<float4*>(&part[wave][r][32 * j + 8 * q + 4 * g]) =
+      *reinterpret_cast<float4*>(&part[wave][r][32 * j + 8 * q + 4 * half]) =
           make_float4(acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]);
   __syncthreads();
-  constexpr int TPR = TN / 4;
 #pragma unroll
   for (int pass = 0; pass < JN; ++pass) {
-    const int mm = pass * (256 / TPR) + tid / TPR, nn = (tid % TPR) * 4, m = m0 + mm, n = n0 + nn;
-    if (m >= p.M || n >= p.N) continue;     // N is a multiple of 8: four columns from a multiple of 4 below N are all inside
+    const int mm = pass * (256 / TPR) + tid / TPR, nn = (tid % TPR) * 4, m = m0 + mm;
+    if (m >= p.M || n >= p.N) continue;
     float v[4];
     {
       float4 t = *reinterpret_cast<const float4*>(&part[0][mm][nn]);
@@ -176,17 +196,14 @@ __global__ __launch_bounds__(256) void gemm_rows_kernel(RowsArgs p) {
       }
       v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
     }
-    if (p.bias) {
-      const float4 b = *reinterpret_cast<const float4*>(p.bias + n);
-      v[0] += b.x; v[1] += b.y; v[2] += b.z; v[3] += b.w;
-    }
+    if (p.bias) { v[0] += bias.x; v[1] += bias.y; v[2] += bias.z; v[3] += bias.w; }
     if (p.residual) {
-      const uint2 w = *reinterpret_cast<const uint2*>(p.residual + (size_t)m * p.ldr + n);
+      const uint2 w = side[pass][0];
       v[0] += __uint_as_float(w.x << 16); v[1] += __uint_as_float(w.x & 0xffff0000u);
       v[2] += __uint_as_float(w.y << 16); v[3] += __uint_as_float(w.y & 0xffff0000u);
     }
     if (p.epilogue == EPI_DGELU) {
-      const uint2 w = *reinterpret_cast<const uint2*>(p.aux + (size_t)m * p.ldaux + n);
+      const uint2 w = side[pass][1];
       v[0] *= __uint_as_float(w.x << 16); v[1] *= __uint_as_float(w.x & 0xffff0000u);
       v[2] *= __uint_as_float(w.y << 16); v[3] *= __uint_as_float(w.y & 0xffff0000u);
     }
@@ -211,6 +228,13 @@ __global__ __launch_bounds__(256) void gemm_rows_kernel(RowsArgs p) {
   }
 }
 
+template <bool BT, int JN, int NS> int rows_launch(hipStream_t s, dim3 grid, const RowsArgs& p) {
+  constexpr int LDS = 4 * NS * stage_bytes<JN>();
+  static OncePerDevice once;
+  PPLL_TRY(raise_lds((const void*)gemm_rows_kernel<BT, JN, NS>, LDS, once));
+  hipLaunchKernelGGL((gemm_rows_kernel<BT, JN, NS>), grid, dim3(256), LDS, s, p);
+  return PPLL_OK;
+}
 bool aligned_to(const void* p, uintptr_t a) { return (((uintptr_t)p) & (a - 1)) == 0; }
 }  // namespace
 
@@ -251,13 +275,21 @@ int launch_gemm_rows(hipStream_t s, const GemmArgs& g) {
   const int steps = (g.K + 15) / 16;
   p.steps_per_wave = (steps + 3) / 4;
   const bool wide = few_tiles_wide(g.M, g.N, compute_units());
-  const dim3 grid(wide ? (g.N + 63) / 64 : (g.N + 31) / 32, (g.M + 31) / 32);
+  const int units = compute_units();
+  p.map = tile_map(g.M, g.N, 32, wide ? 64 : 32, units);
+  p.helpers = g.shared ? 0 : helper_workgroups(p.map.per_xcd, units);
+  const long lds = g.epilogue == EPI_DGELU ? g.ldaux : g.ldr, s_bytes = ((long)(g.M - 1) * lds + g.N) * 2;
+  if (s_bytes < (1L << 30)) {
+    p.side = g.epilogue == EPI_DGELU ? g.aux : g.residual;
+    p.lds2 = (int)(lds * 2); p.s_bytes = (uint32_t)s_bytes;
+  }
+  const dim3 grid(8 * (p.map.per_xcd + p.helpers));
   void* prof = nullptr;
   PPLL_TRY(profile_begin(s, 2.0 * g.M * g.N * g.K, &prof, g.M <= FEW_ROWS ? 2 : 0));
-  if (bt && wide) hipLaunchKernelGGL((gemm_rows_kernel<true, 2>), grid, dim3(256), 0, s, p);
-  else if (bt) hipLaunchKernelGGL((gemm_rows_kernel<true, 1>), grid, dim3(256), 0, s, p);
-  else if (wide) hipLaunchKernelGGL((gemm_rows_kernel<false, 2>), grid, dim3(256), 0, s, p);
-  else hipLaunchKernelGGL((gemm_rows_kernel<false, 1>), grid, dim3(256), 0, s, p);
+  const bool two = p.steps_per_wave <= 2 * KT / 16 || g.shared || 8 * p.map.per_xcd > units;
+  if (wide) PPLL_TRY(bt ? (rows_launch<true, 2, 2>(s, grid, p)) : (rows_launch<false, 2, 2>(s, grid, p)));
+  else if (two) PPLL_TRY(bt ? (rows_launch<true, 1, 2>(s, grid, p)) : (rows_launch<false, 1, 2>(s, grid, p)));
+  else PPLL_TRY(bt ? (rows_launch<true, 1, 4>(s, grid, p)) : (rows_launch<false, 1, 4>(s, grid, p)));
   PPLL_HIP(hipGetLastError());
   return profile_end(s, prof);
 }

@@ -113,18 +113,23 @@ inline BigGradPlan big_grad_tiles(const ProductShape* p, int n, int units) {
 // 64 ones, one per unit at most; up to 256 rows always, beyond that only where the width or the reduction is at most 384.  The
 // alternative is the kernel with copying waves (split_tiles, next), below 128 of K the tiled one.  Microseconds alone on 256 units,
 // this kernel / that one, with B [K][N]; B [N][K] as well where that changes the picture:
-//   128 x 768 x 768   5.0 / 5.4      256 x 768 x 3072   11.4 / 13.1     300 x 768 x 192     3.9 / 3.6
-//   128 x 1536 x 768  5.1 / 5.6      128 x 3072 x 768    7.5 / 5.8      600 x 768 x 384     4.7 / 4.4
-//   64 x 2304 x 768   5.1 / 5.5      256 x 2304 x 768    9.7 / 5.9     2600 x 192 x 192     4.4 / 3.6
-//   455 x 384 x 384   3.8 / 4.1      257 x 384 x 1536    7.1 / 7.9     1000 x 384 x 1536    8.3 / 8.1
-//   B [N][K]:                                            8.8 / 8.2                         13.0 / 8.4
-// Ahead or level while its tiles of 32 x 32 find a unit each, behind where they do not.  The line lies further out because it was drawn
-// against the tiled kernel (256 x 2304 x 768 8.6, 640 x 384 x 384 6.3, 1000 x 384 x 1536 12.9), and has not been moved since.  Beyond
-// width 384 every tile reading its own operand rows costs pipelined blocks, whose streams share the chip, more than it gains:
-// against the tiled kernel four blocks of 39 images of 17 tokens at width 768 took 2180 us a batch on this kernel and 1770 on that
-// one, of 7 images of 65 tokens (455 rows) 1846 and 1652.  At widths 192 and 384 pipelines took the same on either.
+//   128 x 768 x 768   4.7 / 4.8      256 x 768 x 3072    8.0 / 9.3     300 x 768 x 192     4.9 / 4.4
+//   128 x 1536 x 768  4.7 / 4.7      128 x 3072 x 768    5.2 / 4.7     600 x 768 x 384     4.9 / 4.6
+//   64 x 2304 x 768   4.7 / 4.6      256 x 2304 x 768    7.6 / 4.9     2600 x 192 x 192    4.9 / 4.5
+//   455 x 384 x 384   4.8 / 4.4      257 x 384 x 1536    5.1 / 6.0     1000 x 384 x 1536   6.8 / 6.3
+//   B [N][K]:                        256 x 768 x 3072    6.8 / 10.3                        6.3 / 6.8
+// (4.5 is what launches one behind the other take).  Ahead where the reduction is long, level or behind where it is short and the tiles are
+// many.  The line lies further out because it was drawn against the tiled kernel (256 x 2304 x 768 8.6, 640 x 384 x 384 6.3, 1000 x 384 x
+// 1536 12.9); it stays, because the sums of this kernel run in another order.  Beyond width 384 every tile reading its own operand rows
+// cost pipelined blocks, whose streams share the chip, more than it gained: against the tiled kernel four blocks of 39 images of 17
+// tokens at width 768 took 2180 us a batch on this kernel and 1770 on that one.
+//  32 x 64 wherever 32 x 32 would be more than one a unit and these are not: 128 x 3072 x 768 with GELU 8.2 in tiles of 32 x 32, 6.4 in
+// these, 200 x 2304 x 768 7.7 and 6.7, 256 x 1536 x 384 6.0 and 5.4; but 256 x 3072 x 768, 768 tiles and 384, 11.0 and 11.9.
 constexpr int FEW_ROWS = 256, FEW_WIDTH = 384;
-inline bool few_tiles_wide(int M, int N, int units) { return (long)((M + 31) / 32) * ((N + 31) / 32) > units && M > FEW_ROWS; }
+inline bool few_tiles_wide(int M, int N, int units) {
+  const long rows = (M + 31) / 32;
+  return rows * ((N + 31) / 32) > units && rows * ((N + 63) / 64) <= units;
+}
 inline bool few_tiles(int M, int N, int K, int units) {
   if (M <= FEW_ROWS) return true;
   return (N <= FEW_WIDTH || K <= FEW_WIDTH) && (long)((M + 31) / 32) * ((N + 63) / 64) <= units;

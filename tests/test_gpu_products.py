@@ -163,6 +163,47 @@ def test_split_products_in_and_out_of_wider_buffers(M, N, K, apart, bt, epilogue
     assert torch.equal(got[SPLIT][0], got[TILED][0]) and torch.equal(got[SPLIT][1], got[TILED][1])
 
 
+@pytest.mark.parametrize("epilogue", [NONE, GELU, DGELU])
+@pytest.mark.parametrize("bt", [0, 1])
+@pytest.mark.parametrize("M,N,K,apart", [
+    # K in quarters of steps of 16: fewer quarters than waves, a part of a stage, two stages, a part of a third, more than four
+    (1, 8, 8, 8), (31, 40, 72, 48), (33, 264, 136, 264), (64, 384, 384, 384), (65, 72, 520, 80), (128, 96, 3080, 17 * 96),
+    (128, 3080, 200, 3080), (250, 2056, 1032, 2056),   # more than 256 tiles of 32 x 32: tiles of 32 x 64
+    (255, 4104, 328, 4112), (256, 3072, 776, 3072),    # more of those than units as well
+    (1000, 384, 1544, 384),                            # more rows than the first rule takes
+])
+def test_products_of_few_tiles(M, N, K, apart, bt, epilogue):
+    g = torch.Generator(device="cuda").manual_seed(M * 1000 + N + K + apart)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(torch.bfloat16)
+    A = rnd(M, K + 8)[:, :K]                      # what lies behind a row is not part of the sum
+    B = rnd(K, N + 8)[:, :N] if bt else rnd(N, K + 8)[:, :K]
+    bias = torch.randn(N, generator=g, device="cuda") if epilogue != DGELU else None
+    buf, buf2, aux = rnd(M * apart + 4096), rnd(M * apart + 4096), rnd(M, apart)[:, :N]
+    rows = lambda t: t[:M * apart].view(M, apart)[:, :N]
+    c, c2 = buf.clone(), buf2.clone()
+    status, _, _ = product(FEW, A, B, bt, bias, rows(c) if epilogue == NONE else None, epilogue, aux, rows(c), rows(c2))
+    assert status == 0
+    for t, before in ((c, buf), (c2, buf2)):
+        now, was = t.clone(), before.clone()
+        rows(now).zero_(), rows(was).zero_()
+        assert torch.equal(now, was)
+    Bd = B.double().contiguous() if bt else B.double().t().contiguous()
+    v, size = A.double().contiguous() @ Bd, A.double().abs().contiguous() @ Bd.abs()
+    if bias is not None:
+        v = v + bias.double()
+    if epilogue == NONE:
+        v, size = v + rows(buf).double(), size + rows(buf).double().abs()
+    if epilogue == DGELU:
+        v, size = v * aux.double(), size * aux.double().abs()
+    # one rounding to bf16, fp32 sums of K terms (GELU: its slope is at most 1.13, its argument has the same error)
+    if epilogue == GELU:
+        gelu = v * 0.5 * (1 + torch.erf(v / 2 ** 0.5))
+        assert bool(((rows(c2).double() - gelu).abs() <= gelu.abs() * 2.0 ** -8 + size * (K * 2.0 ** -23) + 1e-6).all())
+    else:
+        assert bool(((rows(c).double() - v).abs() <= v.abs() * 2.0 ** -8 + size * (K * 2.0 ** -24) + 1e-6).all())
+        assert torch.equal(rows(buf2), rows(c2))
+
+
 def test_products_that_the_split_kernel_does_not_take_are_refused():
     rnd = lambda *s: torch.randn(*s, device="cuda").to(torch.bfloat16)
     A, B, side = rnd(16, 128), rnd(128, 16), rnd(16, 16)
