@@ -356,7 +356,7 @@ def main() -> int:
             achieved = gemm_flops / (gemm_ms * 1e-3) / 1e12
             traffic, why_not = measured_traffic(args.workload, "gemm", launches / args.steps)
             out["roofline"] = {"bound": "mfma",
-                               "kernel": "gemm_mfma_kernel / gemm_pipe_kernel, with few tiles gemm_split_kernel / gemm_rows_kernel, on the token matrices (Linear forward, input gradient) and the grouped weight-gradient launch",
+                               "kernel": "gemm_mfma_kernel / gemm_pipe_kernel, with few tiles gemm_split_kernel / gemm_rows_kernel, with a LayerNorm behind gemm_norm_kernel, on the token matrices (Linear forward, input gradient) and the grouped weight-gradient launch",
                                "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                                "frac": achieved / PEAK_BF16_TFLOPS, "traffic": traffic,
                                **({"traffic_missing_because": why_not} if why_not else {}),
