@@ -194,8 +194,10 @@ struct Block {
   int resnet_step(const void* x_in, const int32_t* labels, void* x_out, hipStream_t s,
                   const std::function<int()>& after_forward);
   // The layer's first LayerNorm has run (first_norm, or the layer before); `next`: the buffers of the layer that reads x2_out, whose first
-  // LayerNorm then runs here as well
-  int encoder_fwd(int l, const EncoderActs& a, const void* x, void* x2_out, const EncoderActs* next, hipStream_t s);
+  // LayerNorm then runs here as well; `stored` is called behind the launch that stores x2_out, which is ahead of that LayerNorm where the
+  // two are launches of their own
+  int encoder_fwd(int l, const EncoderActs& a, const void* x, void* x2_out, const EncoderActs* next, hipStream_t s,
+                  const std::function<int()>& stored = nullptr);
   int first_norm(int l, const EncoderActs& a, const void* x, hipStream_t s);
   NormOut first_norm_out(int l, const EncoderActs& a) const;
   int forward_eval_with(const EvalBuffers& e, const void* x_in, void* x_out, float* logits_out, hipStream_t s);

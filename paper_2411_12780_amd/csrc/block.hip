@@ -342,7 +342,8 @@ int Block::first_norm(int l, const EncoderActs& a, const void* x, hipStream_t s)
   return launch_layernorm_fwd(s, x, dt, cfg.dim, cfg.batch * cfg.tokens, cfg.dim, n.g, n.b, n.eps, n.y, n.mean, n.rstd);
 }
 
-int Block::encoder_fwd(int l, const EncoderActs& a, const void* x, void* x2_out, const EncoderActs* next, hipStream_t s) {
+int Block::encoder_fwd(int l, const EncoderActs& a, const void* x, void* x2_out, const EncoderActs* next, hipStream_t s,
+                       const std::function<int()>& stored) {
   const int D = cfg.dim, F = cfg.mlp_dim, T = cfg.tokens, H = cfg.heads, M = cfg.batch * T;
   const EncoderParams& p = enc_p[l];
   GemmArgs g = gemm_args();
@@ -356,7 +357,7 @@ int Block::encoder_fwd(int l, const EncoderActs& a, const void* x, void* x2_out,
   g.B = wptr(p.proj_w); g.b_dt = wdt(); g.b_sk = D; g.b_sn = 1;
   g.C = a.x1; g.c_dt = dt; g.ldc = D; g.M = M; g.N = D; g.K = D; g.bias = params + p.proj_b;
   g.residual = x; g.r_dt = dt; g.ldr = D;
-  PPLL_TRY(launch_gemm_then_norm(s, g, {params + p.ln2_g, params + p.ln2_b, cfg.ln_eps, a.u2, a.mean2, a.rstd2}));
+  PPLL_TRY(launch_gemm_then_norm(s, g, {params + p.ln2_g, params + p.ln2_b, cfg.ln_eps, a.u2, a.mean2, a.rstd2}, nullptr));
   g = gemm_args();
   g.A = a.u2; g.a_dt = dt; g.a_sm = D; g.a_sk = 1;
   g.B = wptr(p.fc1_w); g.b_dt = wdt(); g.b_sk = F; g.b_sn = 1;
@@ -368,7 +369,9 @@ int Block::encoder_fwd(int l, const EncoderActs& a, const void* x, void* x2_out,
   g.B = wptr(p.fc2_w); g.b_dt = wdt(); g.b_sk = D; g.b_sn = 1;
   g.C = x2_out; g.c_dt = dt; g.ldc = D; g.M = M; g.N = D; g.K = F; g.bias = params + p.fc2_b;
   g.residual = a.x1; g.r_dt = dt; g.ldr = D;
-  return next ? launch_gemm_then_norm(s, g, first_norm_out(l + 1, *next)) : launch_gemm(s, g);
+  if (next) return launch_gemm_then_norm(s, g, first_norm_out(l + 1, *next), stored);
+  PPLL_TRY(launch_gemm(s, g));
+  return stored ? stored() : PPLL_OK;
 }
 
 // g_in: gradient w.r.t. the layer output; g_tmp receives the gradient at the
@@ -565,14 +568,16 @@ int Block::vit_step(const void* x_in, const int32_t* labels, void* x_out, hipStr
   }
   PPLL_TRY(first_norm(0, enc_a[0], x, s));
   auto next = [&](int l) { return l + 1 < L + A ? &enc_a[l + 1] : nullptr; };
+  const std::function<int()> nothing, forward_done = [&]() -> int {   // x_out is on its way: a next block waits for no more
+    PPLL_TRY(mark_phase(1, s));
+    return after_forward ? after_forward() : PPLL_OK;
+  };
   for (int l = 0; l < L; ++l) {
     layer_in[l] = x;
     void* dst = l == L - 1 ? x_out : enc_a[l].x2;
-    PPLL_TRY(encoder_fwd(l, enc_a[l], x, dst, next(l), s));
+    PPLL_TRY(encoder_fwd(l, enc_a[l], x, dst, next(l), s, l == L - 1 ? forward_done : nothing));
     x = dst;
   }
-  PPLL_TRY(mark_phase(1, s));   // module forward done
-  if (after_forward) PPLL_TRY(after_forward());
   // ---- auxiliary forward
   long head_xs = (long)T * D;   // distance between the class-token rows the head reads
   for (int l = L; l < L + A; ++l) {

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <functional>
 #include <vector>
 #include <stddef.h>
 #include <stdint.h>
@@ -278,9 +279,9 @@ int layernorm_bwd_rows(int rows, int D);       // rows that leave one partial ro
 int layernorm_bwd_reduce(hipStream_t s, ReduceQueue& rq, bool queued, const float* partials, int chunks, int D, float* dg, float* db);
 
 // A Linear product and the LayerNorm behind it, in one launch where that is ahead (k_gemm_norm.hip), else in two.
-// forward: C = product, y = LayerNorm(C)
+// forward: C = product, y = LayerNorm(C); `stored` (may be empty) is called behind the launch that stores C
 struct NormOut { const float *g, *b; float eps; void* y; float *mean, *rstd; };
-int launch_gemm_then_norm(hipStream_t s, const GemmArgs& g, const NormOut& n);
+int launch_gemm_then_norm(hipStream_t s, const GemmArgs& g, const NormOut& n, const std::function<int()>& stored);
 // backward: the product is the gradient dy at the output of the LayerNorm of x, dx = dres + LN'(dy) (dres, dx may be null).  C is where
 // dy goes if it goes anywhere: nothing else may read it.
 struct NormGrad { const void* x; const float *mean, *rstd, *g; const void* dres; void* dx; float *dg, *db; };

@@ -85,9 +85,13 @@ int launch_gemm(hipStream_t s, const GemmArgs& g) {
   return gemm_f32_supported(g) && g.a_sk == 1 ? launch_gemm_f32(s, g) : launch_gemm_generic(s, g);
 }
 
-int launch_gemm_then_norm(hipStream_t s, const GemmArgs& g, const NormOut& n) {
-  if (gemm_norm_fwd_supported(g, n) && norm_tiles(g.M, g.N, g.K, compute_units())) return launch_gemm_norm_fwd(s, g, n);
+int launch_gemm_then_norm(hipStream_t s, const GemmArgs& g, const NormOut& n, const std::function<int()>& stored) {
+  if (gemm_norm_fwd_supported(g, n) && norm_tiles(g.M, g.N, g.K, compute_units())) {
+    PPLL_TRY(launch_gemm_norm_fwd(s, g, n));
+    return stored ? stored() : PPLL_OK;
+  }
   PPLL_TRY(launch_gemm(s, g));
+  if (stored) PPLL_TRY(stored());
   return launch_layernorm_fwd(s, g.C, g.c_dt, g.ldc, g.M, g.N, n.g, n.b, n.eps, n.y, n.mean, n.rstd);
 }
 int launch_gemm_then_norm_bwd(hipStream_t s, const GemmArgs& g, const NormGrad& n, ReduceQueue& rq) {

@@ -1,0 +1,27 @@
+"""What a call asks of the HIP runtime, and in which order: on the CPU, against a stand-in for the runtime (host_hip.py)."""
+import pytest
+
+from host_hip import calls, compile_runtime
+from paper_2411_12780_amd import synth
+
+
+@pytest.fixture(scope="module")
+def runtime(tmp_path_factory):
+    exe = compile_runtime(str(tmp_path_factory.mktemp("runtime")))
+    return lambda workloads, *what: calls(exe, workloads, *what)
+
+
+def vit(dim, batch, tokens, precision=synth.BF16, **more):
+    return synth.workload("vit_stage_act_bf16", tokens=tokens, dim=dim, heads=dim // 64, mlp_dim=4 * dim, batch=batch, precision=precision, **more)
+
+
+@pytest.mark.parametrize("wl", [vit(768, 8, 65, depth=2, aux_depth=2), vit(768, 4, 5, depth=1, aux_depth=1), vit(384, 128, 65, depth=2, aux_depth=1),
+                                vit(192, 128, 65, depth=2, aux_depth=2), vit(64, 4, 5, precision=synth.FP32, depth=2, aux_depth=1),
+                                vit(384, 16, 65, depth=1, aux_depth=0)])
+def test_a_block_publishes_its_output_behind_the_launch_that_stores_it(runtime, wl):
+    # the next block of a pipeline waits for this record: no launch of the auxiliary layers may come before it
+    (batch,) = runtime([wl, wl], "batch")
+    (wait,) = [c for c in batch if c[0] == "wait"]
+    at = batch.index(("record", 1, wait[2]))
+    last = [c[5] for c in batch[:at] if c[0] == "launch"][-1]
+    assert "gemm" in last, last
