@@ -124,6 +124,9 @@ struct Block {
   // the layers below, which never reads them; the step's stream waits for the side stream before the update.
   // Off for blocks driven by a pipeline (alone = false): there the other blocks' streams already fill the chip.
   bool alone = true;
+  // Compute units, for the rules of the products: asked for once a call and not at each of them (54 ns a query, beside some 2.7 us that
+  // the host takes for a launch; a batch of small pipelined blocks is bound by that)
+  int units = 0;
   GemmArgs gemm_args() const;
   bool time_launches = false;          // bracket every contraction launch of this block's steps with events
   LaunchTimes times;

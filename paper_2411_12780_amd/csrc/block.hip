@@ -36,6 +36,7 @@ GemmArgs Block::gemm_args() const {
   GemmArgs g{};
   g.epilogue = EPI_NONE;
   g.shared = !alone;
+  g.units = units;
   return g;
 }
 
@@ -982,6 +983,7 @@ int Block::forward_eval_in_scratch(const void* x_in, void* x_out, float* logits_
 
 int Block::forward_eval_with(const EvalBuffers& e, const void* x_in, void* x_out, float* logits_out, hipStream_t s) {
   last_stream = s;
+  units = compute_units();
   const int B = cfg.batch, C = cfg.num_classes;
   GemmArgs g = gemm_args();
   if (cfg.arch == PPLL_VIT) {
@@ -1115,6 +1117,7 @@ struct TimesBinding {   // binds a block's launch record to this thread for the 
 int Block::step(const void* x_in, const int32_t* labels, float lr, void* x_out, float* loss_out, hipStream_t s,
                 const std::function<int()>& after_forward) {
   last_stream = s;
+  units = compute_units();
   TimesBinding binding(time_launches ? &times : nullptr);
   rq.reset();
   loss_copy = loss_out;   // the loss kernel writes it there as well

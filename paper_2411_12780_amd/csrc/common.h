@@ -179,7 +179,9 @@ struct GemmArgs {
   float* colsum;                              // optional: out[n] = sum_k B(k,n) (bias gradient of a dW product);
                                               // honoured only by the matrix-core kernels
   bool shared;                                // launches of other blocks want the device's units at the same time (a pipeline)
+  int units;                                  // compute units of the device, 0: whoever needs them asks (product_units)
 };
+inline int product_units(const GemmArgs& g) { return g.units ? g.units : compute_units(); }
 int launch_gemm(hipStream_t s, const GemmArgs& g);          // picks the MFMA kernel when the shape allows
 int launch_gemm_generic(hipStream_t s, const GemmArgs& g);
 // Products with few output rows (the class-token rows of a pruned auxiliary layer): see k_gemm_rows.hip

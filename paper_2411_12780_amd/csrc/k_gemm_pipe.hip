@@ -163,9 +163,8 @@ __global__ __launch_bounds__((Shape<false, BT, WGM, WGN, IM, NS, KT>::THREADS), 
 }
 
 template <bool BT, int WGM, int IM, int STAGES, int KT, int WAVES_N = 4>
-int pipe_launch(hipStream_t s, PipeArgs& p) {
+int pipe_launch(hipStream_t s, PipeArgs& p, int units = 0) {
   using S = Shape<false, BT, WGM, WAVES_N, IM, STAGES, KT>;
-  const int units = compute_units();
   if (S::COPY_WAVES) {
     p.map = tile_map(p.M, p.N, S::BM, S::BN, units);
     p.helpers = helper_workgroups(p.map.per_xcd, units);
@@ -191,7 +190,7 @@ bool gemm_pipe_supported(const GemmArgs& g) {
 int gemm_pipe_choice(const GemmArgs& g) {
   if (!gemm_pipe_supported(g)) return 0;
   const ProductEnd end = g.epilogue == EPI_GELU ? END_GELU : g.epilogue == EPI_DGELU ? END_DGELU : g.residual ? END_RESIDUAL : g.bias ? END_BIAS : END_PLAIN;
-  const int units = compute_units();
+  const int units = product_units(g);
   if (!g.shared && copy_wave_tiles(g.M, g.N, g.K, units)) return 3;
   const int wide = wide_tile_rows(g.M, g.N, g.K, end, units), alone = unit_tile_rows(g.M, g.N, g.K, end, wide, units);
   return alone ? alone : wide;
@@ -213,7 +212,7 @@ int launch_gemm_pipe(hipStream_t s, const GemmArgs& g, int im) {
   p.aux_bytes = g.epilogue == EPI_DGELU ? (uint32_t)(((long)(g.M - 1) * g.ldaux + g.N) * 2) : 0u;
   void* prof = nullptr;
   PPLL_TRY(profile_begin(s, 2.0 * g.M * g.N * g.K, &prof));
-  if (im == 3) PPLL_TRY((bt ? pipe_launch<true, 2, 2, 4, 64, 2>(s, p) : pipe_launch<false, 2, 2, 4, 64, 2>(s, p)));
+  if (im == 3) PPLL_TRY((bt ? pipe_launch<true, 2, 2, 4, 64, 2>(s, p, product_units(g)) : pipe_launch<false, 2, 2, 4, 64, 2>(s, p, product_units(g))));
   else if (im == 4) PPLL_TRY((bt ? pipe_launch<true, 1, 4, 3, 32>(s, p) : pipe_launch<false, 1, 4, 3, 32>(s, p)));
   else if (im == 5) PPLL_TRY((bt ? pipe_launch<true, 1, 5, 3, 32>(s, p) : pipe_launch<false, 1, 5, 3, 32>(s, p)));
   else if (im == 8) PPLL_TRY((bt ? pipe_launch<true, 2, 4, 2, 64>(s, p) : pipe_launch<false, 2, 4, 2, 64>(s, p)));

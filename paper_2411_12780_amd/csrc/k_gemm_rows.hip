@@ -231,7 +231,7 @@ __global__ __launch_bounds__(256) void gemm_rows_kernel(RowsArgs p) {
 template <bool BT, int JN, int NS> int rows_launch(hipStream_t s, dim3 grid, const RowsArgs& p) {
   constexpr int LDS = 4 * NS * stage_bytes<JN>();
   static OncePerDevice once;
-  PPLL_TRY(raise_lds((const void*)gemm_rows_kernel<BT, JN, NS>, LDS, once));
+  if (LDS > 64 * 1024) PPLL_TRY(raise_lds((const void*)gemm_rows_kernel<BT, JN, NS>, LDS, once));
   hipLaunchKernelGGL((gemm_rows_kernel<BT, JN, NS>), grid, dim3(256), LDS, s, p);
   return PPLL_OK;
 }
@@ -240,7 +240,7 @@ bool aligned_to(const void* p, uintptr_t a) { return (((uintptr_t)p) & (a - 1)) 
 
 bool gemm_rows_supported(const GemmArgs& g) {
   if (g.a_dt != BF16 || g.b_dt != BF16 || g.colsum) return false;
-  if (g.M < 1 || !few_tiles(g.M, g.N, g.K, compute_units()) || g.N < 1 || g.K < 1 || (g.N & 7) || (g.K & 7)) return false;
+  if (g.M < 1 || !few_tiles(g.M, g.N, g.K, product_units(g)) || g.N < 1 || g.K < 1 || (g.N & 7) || (g.K & 7)) return false;
   if (g.a_sk != 1 || (g.a_sm & 7) || !aligned_to(g.A, 16)) return false;
   const bool bt = g.b_sn == 1 && g.b_sk != 1;
   if (bt) {
@@ -274,8 +274,8 @@ int launch_gemm_rows(hipStream_t s, const GemmArgs& g) {
   p.b_bytes = (uint32_t)(bt ? ((long)(g.K - 1) * g.b_sk + g.N) * 2 : ((long)(g.N - 1) * g.b_sn + g.K) * 2);
   const int steps = (g.K + 15) / 16;
   p.steps_per_wave = (steps + 3) / 4;
-  const bool wide = few_tiles_wide(g.M, g.N, compute_units());
-  const int units = compute_units();
+  const int units = product_units(g);
+  const bool wide = few_tiles_wide(g.M, g.N, units);
   p.map = tile_map(g.M, g.N, 32, wide ? 64 : 32, units);
   p.helpers = g.shared ? 0 : helper_workgroups(p.map.per_xcd, units);
   const long lds = g.epilogue == EPI_DGELU ? g.ldaux : g.ldr, s_bytes = ((long)(g.M - 1) * lds + g.N) * 2;

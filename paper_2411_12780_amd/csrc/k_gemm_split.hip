@@ -257,7 +257,7 @@ __global__ __launch_bounds__(64 * (WAVES + COPY_WAVES), 4) void gemm_split_kerne
 
 }  // namespace
 
-bool gemm_split_choice(const GemmArgs& g) { return gemm_split_supported(g) && split_tiles(g.M, g.N, g.K, compute_units()); }
+bool gemm_split_choice(const GemmArgs& g) { return gemm_split_supported(g) && split_tiles(g.M, g.N, g.K, product_units(g)); }
 bool gemm_split_supported(const GemmArgs& g) { return gemm_pipe_supported(g) && !(g.residual && g.epilogue == EPI_DGELU); }
 
 int launch_gemm_split(hipStream_t s, const GemmArgs& g) {
@@ -274,7 +274,7 @@ int launch_gemm_split(hipStream_t s, const GemmArgs& g) {
   p.b_bytes = (uint32_t)((bt ? (long)(g.K - 1) * p.ldb + g.N : (long)(g.N - 1) * p.ldb + g.K) * 2);
   p.c_bytes = (uint32_t)(((long)(g.M - 1) * g.ldc + g.N) * 2);
   p.s_bytes = p.side ? (uint32_t)(((long)(g.M - 1) * p.lds + g.N) * 2) : 0u;
-  const int units = compute_units();
+  const int units = product_units(g);
   p.map = tile_map(g.M, g.N, EDGE, EDGE, units);
   p.helpers = g.shared ? 0 : helper_workgroups(p.map.per_xcd, units);
   const dim3 grid(8 * (p.map.per_xcd + p.helpers)), block(64 * (WAVES + COPY_WAVES));

@@ -25,3 +25,13 @@ def test_a_block_publishes_its_output_behind_the_launch_that_stores_it(runtime, 
     at = batch.index(("record", 1, wait[2]))
     last = [c[5] for c in batch[:at] if c[0] == "launch"][-1]
     assert "gemm" in last, last
+
+
+@pytest.mark.parametrize("wl,call", [(vit(192, 4, 5, depth=3, aux_depth=3), "batch"), (vit(384, 48, 5, depth=3, aux_depth=1), "batch"),
+                                     (vit(768, 12, 17, depth=2, aux_depth=1), "batch"), (vit(384, 4, 5, depth=1, aux_depth=1), "step"),
+                                     (vit(384, 4, 5, depth=1, aux_depth=1), "eval")])
+def test_a_launch_asks_for_the_device_less_than_once(runtime, wl, call):
+    # each query is host time that a batch of small blocks waits for
+    (made,) = runtime([wl] * (3 if call == "batch" else 1), call)
+    asked, launches = (sum(c[0] == kind for c in made) for kind in ("device", "launch"))
+    assert asked < launches, (asked, launches)
