@@ -1039,7 +1039,7 @@ int Block::forward_eval_with(const EvalBuffers& e, const void* x_in, void* x_out
     PPLL_TRY(stem_conv_fwd(x_in, e.stem_xp, e.stem_wp, e.stem_c, s));
     PPLL_TRY(launch_bn_running_stats(s, bn_mean_run + bn_off[0], bn_var_run + bn_off[0], in_c, eps, e.stem_mean, e.stem_rstd));
     PPLL_TRY(launch_bn_apply(s, e.stem_c, dt, B * in_h * in_w, in_c, e.stem_mean, e.stem_rstd, params + stem_g, params + stem_b,
-                             nullptr, e.stem_y));
+                             nullptr, e.stem_y, units));
     x = e.stem_y;
   }
   for (int i = 0; i < n; ++i) {
@@ -1050,7 +1050,7 @@ int Block::forward_eval_with(const EvalBuffers& e, const void* x_in, void* x_out
     void* out = i == n - 1 ? x_out : a.out;
     PPLL_TRY(launch_conv3x3_fwd(s, x, wptr(p.conv1_w), wdt(), dt, B, d.Hin, d.Win, d.Ci, d.Co, d.stride, a.c1));
     PPLL_TRY(launch_bn_running_stats(s, bn_mean_run + bn_off[b1], bn_var_run + bn_off[b1], d.Co, eps, a.mean1, a.rstd1));
-    PPLL_TRY(launch_bn_apply(s, a.c1, dt, rows, d.Co, a.mean1, a.rstd1, params + p.bn1_g, params + p.bn1_b, nullptr, a.y1));
+    PPLL_TRY(launch_bn_apply(s, a.c1, dt, rows, d.Co, a.mean1, a.rstd1, params + p.bn1_g, params + p.bn1_b, nullptr, a.y1, units));
     PPLL_TRY(launch_conv3x3_fwd(s, a.y1, wptr(p.conv2_w), wdt(), dt, B, d.Ho, d.Wo, d.Co, d.Co, 1, a.c2));
     PPLL_TRY(launch_bn_running_stats(s, bn_mean_run + bn_off[b2], bn_var_run + bn_off[b2], d.Co, eps, a.mean2, a.rstd2));
     const void* skip = x;
@@ -1058,7 +1058,7 @@ int Block::forward_eval_with(const EvalBuffers& e, const void* x_in, void* x_out
       PPLL_TRY(launch_shortcut_fwd(s, x, dt, B, d.Hin, d.Win, d.Ci, d.Co, d.stride, e.shortcut));
       skip = e.shortcut;
     }
-    PPLL_TRY(launch_bn_apply(s, a.c2, dt, rows, d.Co, a.mean2, a.rstd2, params + p.bn2_g, params + p.bn2_b, skip, out));
+    PPLL_TRY(launch_bn_apply(s, a.c2, dt, rows, d.Co, a.mean2, a.rstd2, params + p.bn2_g, params + p.bn2_b, skip, out, units));
     x = out;
   }
   if (!logits_out) return PPLL_OK;
@@ -1066,7 +1066,7 @@ int Block::forward_eval_with(const EvalBuffers& e, const void* x_in, void* x_out
   PPLL_TRY(launch_bn_running_stats(s, bn_mean_run + bn_off[bn_base + 2 * n], bn_var_run + bn_off[bn_base + 2 * n], A, eps,
                                    e.aux_mean, e.aux_rstd));
   PPLL_TRY(launch_bn_apply(s, e.aux_c, dt, arows, A, e.aux_mean, e.aux_rstd, params + aux_bn_g, params + aux_bn_b, nullptr,
-                           e.aux_y));
+                           e.aux_y, units));
   PPLL_TRY(launch_gap_fwd(s, e.aux_y, dt, B, Ho * Wo, A, e.pooled));
   g.A = e.pooled; g.a_dt = dt; g.a_sm = A; g.a_sk = 1;
   g.B = params + head_w; g.b_dt = F32; g.b_sk = C; g.b_sn = 1;

@@ -441,11 +441,11 @@ int launch_bn_stats(hipStream_t s, const void* x, int dt, int rows, int C, float
 int launch_bn_train_fwd(hipStream_t s, const void* x, int dt, int rows, int C, float eps, float momentum, float* partials,
                         float* mean, float* rstd, float* run_mean, float* run_var, const float* g, const float* b,
                         const void* res, void* y, int ready_blocks = 0, uint8_t* mask = nullptr);
-// y = relu(bn(x) (+ res))
+// y = relu(bn(x) (+ res)); units: compute units of the device, 0: asked for
 int launch_bn_running_stats(hipStream_t s, const float* run_mean, const float* run_var, int C, float eps, float* mean,
                             float* rstd);
 int launch_bn_apply(hipStream_t s, const void* x, int dt, int rows, int C, const float* mean, const float* rstd,
-                    const float* g, const float* b, const void* res, void* y);
+                    const float* g, const float* b, const void* res, void* y, int units = 0);
 // dyh = dy * (y > 0); dx = bn'(dyh); dg = sum dyh*xhat; db = sum dyh
 // ready_blocks: rows of `partials` the convolution that produced dy has already filled (see launch_conv3x3_dgrad), else 0
 int launch_bn_bwd(hipStream_t s, const void* dy, const void* y, const void* x, int dt, int rows, int C,
@@ -483,7 +483,7 @@ int launch_bn_train_fwd_bf16(hipStream_t s, const void* x, int rows, int C, floa
                              float* mean, float* rstd, float* run_mean, float* run_var, const float* g, const float* b,
                              const void* res, void* y, int ready_blocks = 0, uint8_t* mask = nullptr);
 int launch_bn_apply_bf16(hipStream_t s, const void* x, int rows, int C, const float* mean, const float* rstd,
-                         const float* g, const float* b, const void* res, void* y, uint8_t* mask = nullptr);
+                         const float* g, const float* b, const void* res, void* y, uint8_t* mask = nullptr, int units = 0);
 int launch_bn_bwd_bf16(hipStream_t s, const void* dy, const void* y, const void* x, int rows, int C, const float* mean,
                        const float* rstd, const float* g, float* partials, float* dg, float* db, void* dx, int ready_blocks = 0);
 int launch_gap_fwd(hipStream_t s, const void* x, int dt, int B, int HW, int C, void* pooled);

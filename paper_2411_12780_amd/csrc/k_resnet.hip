@@ -375,9 +375,9 @@ int launch_bn_train_fwd(hipStream_t s, const void* x, int dt, int rows, int C, f
 }
 
 int launch_bn_apply(hipStream_t s, const void* x, int dt, int rows, int C, const float* mean, const float* rstd,
-                    const float* g, const float* b, const void* res, void* y) {
+                    const float* g, const float* b, const void* res, void* y, int units) {
   if (bn_bf16_supported(dt, rows, C, x, res, y, nullptr))
-    return launch_bn_apply_bf16(s, x, rows, C, mean, rstd, g, b, res, y);
+    return launch_bn_apply_bf16(s, x, rows, C, mean, rstd, g, b, res, y, nullptr, units);
   size_t total = (size_t)rows * C;
   hipLaunchKernelGGL(bn_apply_kernel, dim3((total + 255) / 256), dim3(256), 0, s, x, dt, total, C, mean, rstd, g, b, res, y);
   PPLL_HIP(hipGetLastError());

@@ -12,6 +12,7 @@
 //    last-arrival scheme in one launch was slower: device-scope fences cost more).
 //  * the elementwise pieces: shortcut of a downsampling block, global average pooling.
 #include "resnet_bf16.h"
+#include "plan.h"
 
 namespace ppll {
 
@@ -439,18 +440,19 @@ __global__ __launch_bounds__(1024) void bn_finish_kernel(BnSumArgs p, unsigned n
   bn_finish<KIND, 1024>(p, nblocks, red, nullptr, nullptr, true);
 }
 
-// The passes of large tensors: AP_PIECES pieces of 8 channels a thread, 256 apart, so of the same channels (256 % (C / 8) = 0).  One piece a
-// thread, as this was before, spent eight loads of parameters and in the backward pass eight divisions on each of it: 1024 x 32 x 32 x 16
-// forward 17.3 -> 15.7 us, backward 21.0 -> 20.4; beside other blocks of a pipeline 19.6 -> 17.0 and 25.1 -> 23.4.
-constexpr int AP_PIECES = 4;
+// Pieces of 8 channels a thread, 256 apart, so of the same channels (256 % (C / 8) = 0).  One piece a thread spends eight loads of parameters and
+// in the backward pass eight divisions on each of it: with AP_PIECES of them, 1024 x 32 x 32 x 16 forward 17.3 -> 15.7 us, backward 21.0 ->
+// 20.4; beside other blocks of a pipeline 19.6 -> 17.0 and 25.1 -> 23.4.  Small maps, which only an evaluation has here, take one
+// (bn_apply_pieces): five basic blocks on 24 x 8 x 8 x 64 evaluated 170.0 us, with four 172.0.
 // y = relu(bn(x) (+ res))
+template <int PIECES>
 __global__ __launch_bounds__(256) void bn_apply_bf16_kernel(const uint16_t* x, size_t chunks, int C, const float* mean,
                                                             const float* rstd, const float* g, const float* b,
                                                             const uint16_t* res, uint16_t* y, uint8_t* mask) {
-  const size_t i0 = (size_t)blockIdx.x * (256 * AP_PIECES) + threadIdx.x;
-  uint4 xv[AP_PIECES], rv[AP_PIECES];
+  const size_t i0 = (size_t)blockIdx.x * (256 * PIECES) + threadIdx.x;
+  uint4 xv[PIECES], rv[PIECES];
 #pragma unroll
-  for (int u = 0; u < AP_PIECES; ++u) {
+  for (int u = 0; u < PIECES; ++u) {
     const size_t i = i0 + 256 * u;
     xv[u] = rv[u] = make_uint4(0, 0, 0, 0);
     if (i < chunks) {
@@ -463,7 +465,7 @@ __global__ __launch_bounds__(256) void bn_apply_bf16_kernel(const uint16_t* x, s
 #pragma unroll
   for (int c = 0; c < 8; ++c) { mu[c] = mean[c0 + c]; k[c] = rstd[c0 + c] * g[c0 + c]; sh[c] = b[c0 + c]; }
 #pragma unroll
-  for (int u = 0; u < AP_PIECES; ++u) {
+  for (int u = 0; u < PIECES; ++u) {
     const size_t i = i0 + 256 * u;
     if (i >= chunks) return;
     const uint32_t* xw = reinterpret_cast<const uint32_t*>(&xv[u]);
@@ -910,13 +912,18 @@ int launch_bn_train_fwd_bf16(hipStream_t s, const void* x, int rows, int C, floa
   return PPLL_OK;
 }
 
-int launch_bn_apply_bf16(hipStream_t s, const void* x, int rows, int C, const float* mean, const float* rstd,
-                         const float* g, const float* b, const void* res, void* y, uint8_t* mask) {
-  const size_t chunks = (size_t)rows * C / 8;
-  hipLaunchKernelGGL(bn_apply_bf16_kernel, dim3((unsigned)((chunks + 256 * AP_PIECES - 1) / (256 * AP_PIECES))), dim3(256), 0, s, (const uint16_t*)x,
-                     chunks, C, mean, rstd, g, b, (const uint16_t*)res, (uint16_t*)y, mask);
+static int bn_apply_launch(hipStream_t s, int pieces, const void* x, size_t chunks, int C, const float* mean, const float* rstd,
+                           const float* g, const float* b, const void* res, void* y, uint8_t* mask) {
+  const dim3 grid((unsigned)((chunks + 256 * pieces - 1) / (256 * pieces)));
+  auto kernel = pieces == 1 ? bn_apply_bf16_kernel<1> : bn_apply_bf16_kernel<AP_PIECES>;
+  hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, (const uint16_t*)x, chunks, C, mean, rstd, g, b, (const uint16_t*)res, (uint16_t*)y, mask);
   PPLL_HIP(hipGetLastError());
   return PPLL_OK;
+}
+int launch_bn_apply_bf16(hipStream_t s, const void* x, int rows, int C, const float* mean, const float* rstd,
+                         const float* g, const float* b, const void* res, void* y, uint8_t* mask, int units) {
+  const size_t chunks = (size_t)rows * C / 8;
+  return bn_apply_launch(s, bn_apply_pieces(chunks, units ? units : compute_units()), x, chunks, C, mean, rstd, g, b, res, y, mask);
 }
 
 // ready_blocks > 0: `partials` already holds that many rows of the two sums, written by the convolution that produced dy
@@ -972,4 +979,12 @@ extern "C" int ppll_internal_conv_dgrad_s2(int B, int H, int W, int Ci, int Co, 
     return PPLL_ERR_CONFIG;
   }
   return launch_conv3x3_dgrad_bf16((hipStream_t)stream, dy, w, B, H, W, Ci, Co, 2, nullptr, nullptr, dx, nullptr, nullptr);
+}
+
+// y = relu(bn(x) (+ res)) and its mask, bf16, 1 or AP_PIECES pieces a thread, for tests (no part of the public interface)
+extern "C" int ppll_internal_bn_apply(int pieces, int rows, int C, const void* x, const float* mean, const float* rstd, const float* g,
+                                      const float* b, const void* res, void* y, void* mask, void* stream) {
+  using namespace ppll;
+  if ((pieces != 1 && pieces != AP_PIECES) || !bn_bf16_supported(BF16, rows, C, x, y, res, nullptr)) { set_error("no such launch"); return PPLL_ERR_CONFIG; }
+  return bn_apply_launch((hipStream_t)stream, pieces, x, (size_t)rows * C / 8, C, mean, rstd, g, b, res, y, (uint8_t*)mask);
 }

@@ -294,6 +294,15 @@ inline bool norm_tiles(int M, int N, int K, int units) {
   return N <= 192 || (K <= N && tiles <= units && 10 * tiles >= 4 * units);
 }
 
+// ---- Pieces of 8 channels a thread of a BatchNorm's apply pass: four share the loads of their channels' parameters, one where four would
+// occupy too few units.  Microseconds of a launch on 256 units, one / four pieces (with a residual), by workgroups of four:
+//   16 2.1 / 2.6 (2.1 / 2.7)   96 2.5 / 2.7 (2.7 / 2.8)   128 2.6 / 2.8 (2.7 / 2.9)   176 2.9 / 2.9 (3.1 / 2.9)   224 3.1 / 2.9 (3.4 / 3.0)
+//   288 3.5 / 3.4 (3.7 / 3.6)   512 4.8 / 3.9 (5.1 / 4.0)   1024 7.8 / 6.3 (9.1 / 7.2)   2048 13.4 / 11.5 (18.0 / 15.6)
+constexpr int AP_PIECES = 4;
+inline int bn_apply_pieces(size_t chunks, int units) {
+  return 8 * ((chunks + 256 * AP_PIECES - 1) / (256 * AP_PIECES)) <= 5 * (size_t)units ? 1 : AP_PIECES;
+}
+
 // ---- The matrix-core attention addresses the keys, queries and values of an image with 32-bit byte offsets
 inline bool att_offsets_fit(int T, int H) { return (long)T * H * (3 * 64 * 2) <= 0x7fffffffL; }
 

@@ -35,3 +35,14 @@ def test_a_launch_asks_for_the_device_less_than_once(runtime, wl, call):
     (made,) = runtime([wl] * (3 if call == "batch" else 1), call)
     asked, launches = (sum(c[0] == kind for c in made) for kind in ("device", "launch"))
     assert asked < launches, (asked, launches)
+
+
+@pytest.mark.parametrize("batch,workgroups", [
+    # maps of 8 x 8 x 64 and, behind the auxiliary convolution, 4 x 4 x 64: of 256 threads with a piece of 8 channels each up to 160
+    # workgroups of four pieces, with four beyond
+    (24, [12, 48]), (320, [160, 640]), (322, [161, 161]), (1024, [512, 512]),
+])
+def test_an_evaluation_of_small_maps_keeps_the_units_busy(runtime, batch, workgroups):
+    (made,) = runtime([synth.workload("resnet32_stage3_bf16", batch=batch)], "eval")
+    grids = [c[2][0] for c in made if c[0] == "launch" and "bn_apply_bf16" in c[5]]
+    assert [grids[-1], grids[0]] == workgroups
