@@ -122,7 +122,15 @@ struct Block {
   // Side stream of the backward pass (created at first use, default priority).  The weight-gradient products of a
   // layer are launched there once the layer's backward is enqueued, so they run next to the input-gradient chain of
   // the layers below, which never reads them; the step's stream waits for the side stream before the update.
-  // Off for blocks driven by a pipeline (alone = false): there the other blocks' streams already fill the chip.
+  // Off for blocks driven by a pipeline: there the other blocks' streams already fill the chip.
+  hipStream_t side = nullptr;
+  hipEvent_t side_fork = nullptr, side_join = nullptr;
+  bool side_busy = false;              // something was launched on the side stream in this step
+  int side_launch_wgrads(hipStream_t s);   // launches wgrad_jobs on the side stream behind everything enqueued on s
+  int side_wait(hipStream_t s);            // s waits for the side stream's work of this step
+  void side_destroy();
+  // Whether the call in flight has the device to itself: a step or an evaluation of its own, not a step of a pipeline.  Every call says so
+  // anew.  It decides over the side stream and, as GemmArgs::shared, over the kernels of the products; never over results.
   bool alone = true;
   // Compute units, for the rules of the products: asked for once a call and not at each of them (54 ns a query, beside some 2.7 us that
   // the host takes for a launch; a batch of small pipelined blocks is bound by that)
@@ -130,12 +138,6 @@ struct Block {
   GemmArgs gemm_args() const;
   bool time_launches = false;          // bracket every contraction launch of this block's steps with events
   LaunchTimes times;
-  hipStream_t side = nullptr;
-  hipEvent_t side_fork = nullptr, side_join = nullptr;
-  bool side_busy = false;              // something was launched on the side stream in this step
-  int side_launch_wgrads(hipStream_t s);   // launches wgrad_jobs on the side stream behind everything enqueued on s
-  int side_wait(hipStream_t s);            // s waits for the side stream's work of this step
-  void side_destroy();
 
   // ResNet
   std::vector<BasicBlockParams> rb_p;

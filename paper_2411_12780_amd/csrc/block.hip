@@ -984,6 +984,7 @@ int Block::forward_eval_in_scratch(const void* x_in, void* x_out, float* logits_
 int Block::forward_eval_with(const EvalBuffers& e, const void* x_in, void* x_out, float* logits_out, hipStream_t s) {
   last_stream = s;
   units = compute_units();
+  alone = true;
   const int B = cfg.batch, C = cfg.num_classes;
   GemmArgs g = gemm_args();
   if (cfg.arch == PPLL_VIT) {

@@ -46,3 +46,13 @@ def test_an_evaluation_of_small_maps_keeps_the_units_busy(runtime, batch, workgr
     (made,) = runtime([synth.workload("resnet32_stage3_bf16", batch=batch)], "eval")
     grids = [c[2][0] for c in made if c[0] == "launch" and "bn_apply_bf16" in c[5]]
     assert [grids[-1], grids[0]] == workgroups
+
+
+@pytest.mark.parametrize("evaluate", ["eval", "eval_noalloc"])
+@pytest.mark.parametrize("wl", [vit(384, 70, 65, depth=1, aux_depth=1), vit(768, 8, 65, depth=2, aux_depth=1), vit(384, 40, 5, depth=1, aux_depth=2)])
+def test_an_evaluation_is_the_same_whatever_trained_the_block(runtime, wl, evaluate):
+    # a pipeline's blocks share the chip while it runs; a block that is evaluated has it to itself
+    launches = lambda made: [c[2:] for c in made if c[0] == "launch"]
+    _, behind_a_batch = runtime([wl, wl], "batch", evaluate)
+    fresh, _, behind_a_step = runtime([wl], evaluate, "step", evaluate)
+    assert launches(behind_a_batch) == launches(fresh) == launches(behind_a_step)
