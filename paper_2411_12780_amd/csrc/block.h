@@ -36,7 +36,7 @@ struct BasicBlockParams { size_t conv1_w, bn1_g, bn1_b, conv2_w, bn2_g, bn2_b; }
 struct BasicBlockDims { int Ci, Co, stride, Hin, Win, Ho, Wo; };
 struct BasicBlockActs {
   void *c1, *y1, *c2, *out;
-  void *d1, *d2;   // gradients at the outputs of conv1 / conv2, kept until the grouped weight-gradient launch
+  void *d1, *d2;   // gradients at the outputs of conv1 / conv2, kept until the grouped weight-gradient launch; null where none needs them
   uint8_t *mask1, *mask2;   // ReLU masks of y1 and of `out` (or the block's x_out), for the fused backward; null where that does not run
   float *mean1, *rstd1, *mean2, *rstd2;
 };
@@ -143,6 +143,10 @@ struct Block {
   std::vector<BasicBlockParams> rb_p;
   std::vector<BasicBlockActs> rb_a;
   std::vector<BasicBlockDims> rb_d;
+  // Whether the backward pass forms the weight gradient of a basic block's second convolution with its input gradient, and whether it goes
+  // on through the first one in the same way (the block input has a gradient, over an identity shortcut)
+  bool second_filter_from_bn(int i) const;
+  bool whole_chain(int i) const;
   int in_h = 0, in_w = 0, in_c = 0;      // activation the first basic block reads
   bool stem = false;                     // conv3x3 (img_c -> in_c) - BN - ReLU on the image in front of the blocks
   size_t stem_w = 0, stem_g = 0, stem_b = 0;

@@ -270,7 +270,9 @@ size_t Block::plan(char* base) {
       if (act > widest) widest = act;
       BasicBlockActs a;
       a.c1 = bump.take(act * esz); a.y1 = bump.take(act * esz); a.c2 = bump.take(act * esz); a.out = bump.take(act * esz);
-      a.d1 = bump.take(act * esz); a.d2 = bump.take(act * esz);
+      // not where the launch that forms them leaves the weight gradient instead (y1 an evaluation needs all the same)
+      a.d1 = second_filter_from_bn(i) && whole_chain(i) ? nullptr : bump.take(act * esz);
+      a.d2 = second_filter_from_bn(i) ? nullptr : bump.take(act * esz);
       const bool masks = conv_bn_ok(dt, B, d.Ho, d.Wo, d.Co);
       a.mask1 = masks ? (uint8_t*)bump.take(act / 8) : nullptr; a.mask2 = masks ? (uint8_t*)bump.take(act / 8) : nullptr;
       a.mean1 = bump.floats(d.Co); a.rstd1 = bump.floats(d.Co); a.mean2 = bump.floats(d.Co); a.rstd2 = bump.floats(d.Co);
@@ -295,7 +297,6 @@ size_t Block::plan(char* base) {
       if (conv_bn_ok(dt, B, d.Ho, d.Wo, d.Co)) {
         const size_t f = (size_t)conv_bn_stat_blocks(B, d.Ho, d.Wo, d.Co) * 2 * d.Co;
         if (f > partial_floats) partial_floats = f;
-        if (conv_bn_filter_floats(B, d.Ho, d.Wo, d.Co) > partial_floats) partial_floats = conv_bn_filter_floats(B, d.Ho, d.Wo, d.Co);
       }
   partials = bump.floats(partial_floats);
   // a convolution that finishes the sums in one area leaves those of its result in the other
@@ -684,6 +685,12 @@ int Block::stem_conv_fwd(const void* x_in, void* xp, void* wp, void* out, hipStr
   return launch_conv3x3_fwd(s, xp, wp, BF16, dt, B, in_h, in_w, 16, in_c, 1, out, stat, stat_blocks);
 }
 
+bool Block::second_filter_from_bn(int i) const {
+  const BasicBlockDims& d = rb_d[i];
+  return conv_bn_ok(dt, cfg.batch, d.Ho, d.Wo, d.Co) && conv_bn_filter_floats(cfg.batch, d.Ho, d.Wo, d.Co) > 0;
+}
+bool Block::whole_chain(int i) const { return rb_d[i].stride == 1 && rb_d[i].Ci == rb_d[i].Co && (i > 0 || stem); }
+
 int Block::resnet_step(const void* x_in, const int32_t* labels, void* x_out, hipStream_t s,
                        const std::function<int()>& after_forward) {
   const int B = cfg.batch, Ch = cfg.channels, A = cfg.aux_channels, H = cfg.height, W = cfg.width;
@@ -695,13 +702,6 @@ int Block::resnet_step(const void* x_in, const int32_t* labels, void* x_out, hip
   std::vector<const void*> block_in(n);
   std::vector<void*> block_out(n);
   const void* x = x_in;
-  // Whether the backward pass forms the weight gradient of a block's second convolution with its input gradient, and whether it goes on
-  // through the first one in the same way (the block input has a gradient, over an identity shortcut)
-  auto second_filter_from_bn = [&](int i) {
-    const BasicBlockDims& d = rb_d[i];
-    return conv_bn_ok(dt, B, d.Ho, d.Wo, d.Co) && conv_bn_filter_floats(B, d.Ho, d.Wo, d.Co) > 0;
-  };
-  auto whole_chain = [&](int i) { return rb_d[i].stride == 1 && rb_d[i].Ci == rb_d[i].Co && (i > 0 || stem); };
   // A BatchNorm whose input has just been written waits here: the next convolution applies it on the way in where it can
   // (stride 1, equal channels, bf16), else it runs on its own.  `area` holds its sums (bn.blocks rows; 0: none yet).
   // (x_in and x_out are the caller's, on a 16-byte boundary: every entry point checks that)

@@ -52,6 +52,16 @@ def test_layernorm_scratch_does_not_outgrow_the_activations():
     assert P.ppll_block_workspace_bytes(P.make_config(synth.workload("vit_base_224_bf16"))) < 4.60e9
 
 
+@pytest.mark.parametrize("more,gradients", [({}, 0), (dict(input_kind=synth.ACTIVATION), 1)])
+def test_a_resnet_workspace_holds_no_gradient_that_is_never_stored(more, gradients):
+    # 16 channels at 1024 x 32 x 32, five basic blocks: the launch that forms the gradient at a convolution's output leaves its weight
+    # gradient instead, but for a first convolution whose input has no gradient.  Beyond 512 tiles of 256 pixels, that is; at 128 images
+    # all ten are stored, and the workspace grows with the images otherwise.
+    size = lambda batch: P.ppll_block_workspace_bytes(P.make_config(synth.workload("resnet32_stage1_bf16", batch=batch, **more)))
+    one = 32 * 32 * 16 * 2
+    assert size(1024) - 8 * size(128) < (gradients - 10 + 1) * 1024 * one
+
+
 def test_attention_wider_than_its_offsets_is_refused_before_a_launch():
     f = P.lib().ppll_internal_attention
     f.restype = ctypes.c_int
