@@ -86,7 +86,7 @@ int launch_gemm(hipStream_t s, const GemmArgs& g) {
 }
 
 int launch_gemm_then_norm(hipStream_t s, const GemmArgs& g, const NormOut& n, const std::function<int()>& stored) {
-  if (gemm_norm_fwd_supported(g, n) && norm_tiles(g.M, g.N, g.K, product_units(g))) {
+  if (gemm_norm_fwd_supported(g, n) && norm_with_product(g.M, g.N, g.K, g.shared, product_units(g))) {
     PPLL_TRY(launch_gemm_norm_fwd(s, g, n));
     return stored ? stored() : PPLL_OK;
   }
@@ -95,7 +95,7 @@ int launch_gemm_then_norm(hipStream_t s, const GemmArgs& g, const NormOut& n, co
   return launch_layernorm_fwd(s, g.C, g.c_dt, g.ldc, g.M, g.N, n.g, n.b, n.eps, n.y, n.mean, n.rstd);
 }
 int launch_gemm_then_norm_bwd(hipStream_t s, const GemmArgs& g, const NormGrad& n, ReduceQueue& rq) {
-  if (gemm_norm_bwd_supported(g, n) && norm_tiles(g.M, g.N, g.K, product_units(g))) return launch_gemm_norm_bwd(s, g, n, rq);
+  if (gemm_norm_bwd_supported(g, n) && norm_with_product(g.M, g.N, g.K, g.shared, product_units(g))) return launch_gemm_norm_bwd(s, g, n, rq);
   PPLL_TRY(launch_gemm(s, g));
   return launch_layernorm_bwd(s, g.C, n.x, g.c_dt, g.N, g.M, g.N, n.g, n.mean, n.rstd, n.dres, 1, n.dx, rq, n.dg, n.db);
 }

@@ -287,11 +287,20 @@ inline int unit_tile_rows(int M, int N, int K, ProductEnd end, int wide, int uni
 // Width 192: where the product alone is not on the kernel with copying waves (two blocks of 4160 rows with it on both sides of that line:
 // 405 us a step in two launches, 412 in one).  Width 384: one workgroup a unit waits for its own operands (0.78 us per 64 k), so only a
 // short reduction and one round (25216 rows: a step of 2 + 1 layers 0.3 % behind), not too small a part of one (5200 rows, 82 tiles: 0.4 %
-// behind; 8320 rows, 130: level, evaluation 0.9 % ahead).
+// behind).
 inline bool norm_tiles(int M, int N, int K, int units) {
   if (units < 8 || few_tiles(M, N, K, units) || split_tiles(M, N, K, units)) return false;
   const long tiles = (M + 63) / 64;
   return N <= 192 || (K <= N && tiles <= units && 10 * tiles >= 4 * units);
+}
+// Of these, at width 384, not where the product alone would be on 128 x 128 tiles with copying waves: alone on the device, 3 + 1 layers,
+// us a step (an evaluation) in two launches and in one, with them 8320 rows 867 and 872 (339 and 343), 9280 976 and 979 (361 and 365),
+// 10465 985 and 986 (377 and 378), 10790 997 and 1001 (380 and 383); without them 9815 959 and 959 (361 and 360), 11050 1092 and 1085
+// (405 and 398), 12325 1195 and 1187 (435 and 426), 15950 rows, 2 + 2 layers, 1408 and 1399 (514 and 502).  Beside other streams those tiles are
+// not taken, and the one launch is level: pipelines of four and three blocks of width 384, 6500 rows 2140 and 2140 us a batch, 8320 rows 2560
+// and 2558, 2573 and 2566; of width 192, 8320 rows, 1222 and 1172.
+inline bool norm_with_product(int M, int N, int K, bool shared, int units) {
+  return norm_tiles(M, N, K, units) && (N <= 192 || shared || !copy_wave_tiles(M, N, K, units));
 }
 
 // ---- Pieces of 8 channels a thread of a BatchNorm's apply pass: four share the loads of their channels' parameters, one where four would

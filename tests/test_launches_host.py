@@ -56,3 +56,17 @@ def test_an_evaluation_is_the_same_whatever_trained_the_block(runtime, wl, evalu
     _, behind_a_batch = runtime([wl, wl], "batch", evaluate)
     fresh, _, behind_a_step = runtime([wl], evaluate, "step", evaluate)
     assert launches(behind_a_batch) == launches(fresh) == launches(behind_a_step)
+
+
+@pytest.mark.parametrize("dim,batch,alone,shared", [
+    # rows of 65 tokens: at width 384 a LayerNorm is behind in the product's launch where that product alone has 128 x 128 tiles with copying
+    # waves, up to 10880 rows, and those are for launches that share the device with none
+    (384, 128, False, True), (384, 151, True, True), (384, 166, False, True), (384, 170, True, True), (384, 100, False, False),
+    (192, 128, True, True), (192, 32, False, False),
+])
+def test_which_products_take_the_layernorm_behind_them(runtime, dim, batch, alone, shared):
+    wl = vit(dim, batch, 65, depth=2, aux_depth=1)
+    takes = lambda made: any(c[0] == "launch" and "gemm_norm" in c[5] for c in made)
+    assert [takes(made) for made in runtime([wl], "step", "eval")] == [alone, alone]
+    batch_made, eval_made = runtime([wl, wl], "batch", "eval")
+    assert (takes(batch_made), takes(eval_made)) == (shared, alone)
