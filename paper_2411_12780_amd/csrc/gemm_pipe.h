@@ -33,20 +33,6 @@ __device__ __forceinline__ void barrier() {
   asm volatile("" ::: "memory");
 }
 
-// The tile of place `slot` of an XCD; false: none
-__device__ __forceinline__ bool tile_at(const TileMap& t, int xcd, int slot, int& tm, int& tn) {
-  if (slot >= t.per_xcd) return false;
-  if (t.rows) {
-    tm = xcd / t.across * t.rows + slot / t.cols;
-    tn = xcd % t.across * t.cols + slot % t.cols;
-    return tm < t.tiles_m && tn < t.tiles_n;
-  }
-  const int i = xcd * t.per_xcd + slot;
-  tm = t.columns ? i % t.tiles_m : i / t.tiles_n;
-  tn = t.columns ? i / t.tiles_m : i % t.tiles_n;
-  return i < t.tiles_m * t.tiles_n;
-}
-
 // Helpers: workgroups beyond those that have tiles, on units that have none.  Each brings a share of what its XCD's tiles read into the L2
 // there, rows of A and columns of B k by k ahead of them, then what the epilogue takes, a word of every cache line (the words go to LDS that
 // nothing reads, as in CodeToL2).  Tiles of a row of them read the same rows at the same time, and a unit has about 25 GB/s of lines on
@@ -58,18 +44,9 @@ struct Bring {
   int M, N, K, bm, bn, helpers;        // helpers: of an XCD
 };
 template <bool BT, int THREADS> __device__ __forceinline__ void bring_operands(const Bring& p, const TileMap& t, int xcd, int helper, lds_char* to) {
-  int m0 = 0, m1 = t.tiles_m, n0 = 0, n1 = t.tiles_n;       // tiles of this XCD
-  if (t.rows) {
-    m0 = xcd / t.across * t.rows; m1 = min(m0 + t.rows, m1);
-    n0 = xcd % t.across * t.cols; n1 = min(n0 + t.cols, n1);
-  } else {
-    const int i0 = xcd * t.per_xcd, i1 = min(i0 + t.per_xcd, t.tiles_m * t.tiles_n);
-    if (i0 >= i1) return;
-    if (t.columns) { n0 = i0 / t.tiles_m; n1 = (i1 - 1) / t.tiles_m + 1; }
-    else { m0 = i0 / t.tiles_n; m1 = (i1 - 1) / t.tiles_n + 1; }
-  }
-  if (m0 >= m1 || n0 >= n1) return;
-  const int row0 = m0 * p.bm, rows = min(m1 * p.bm, p.M) - row0, col0 = n0 * p.bn, cols = min(n1 * p.bn, p.N) - col0;
+  const TileRange x = tiles_of(t, xcd);
+  if (x.m0 >= x.m1 || x.n0 >= x.n1) return;
+  const int row0 = x.m0 * p.bm, rows = min(x.m1 * p.bm, p.M) - row0, col0 = x.n0 * p.bn, cols = min(x.n1 * p.bn, p.N) - col0;
   const int nl = (cols + 63) / 64, chunk = rows + (BT ? 64 * nl : cols), lines = chunk * ((p.K + 63) / 64);    // of 64 k, and in all
   const __amdgpu_buffer_rsrc_t rsA = make_rsrc(p.A, p.a_bytes), rsB = make_rsrc(p.B, p.b_bytes), rsS = make_rsrc(p.side, p.s_bytes);
   const int lane = threadIdx.x & 63, first = helper * THREADS + (int)(threadIdx.x & ~63), step = p.helpers * THREADS;

@@ -221,6 +221,33 @@ inline TileMap tile_map(int M, int N, int bm, int bn, int units) {
   return t;
 }
 
+// The tile of place `slot` of an XCD; false: none.  (Both this and the next are called by kernels; constexpr makes them callable there.)
+constexpr bool tile_at(const TileMap& t, int xcd, int slot, int& tm, int& tn) {
+  if (slot >= t.per_xcd) return false;
+  if (t.rows) {
+    tm = xcd / t.across * t.rows + slot / t.cols;
+    tn = xcd % t.across * t.cols + slot % t.cols;
+    return tm < t.tiles_m && tn < t.tiles_n;
+  }
+  const int i = xcd * t.per_xcd + slot;
+  tm = t.columns ? i % t.tiles_m : i / t.tiles_n;
+  tn = t.columns ? i / t.tiles_m : i % t.tiles_n;
+  return i < t.tiles_m * t.tiles_n;
+}
+
+// Rows m0 .. m1 and columns n0 .. n1 of tiles that hold all tiles of an XCD, what its helpers bring; may be empty
+struct TileRange { int m0, m1, n0, n1; };
+constexpr TileRange tiles_of(const TileMap& t, int xcd) {
+  if (t.rows) {
+    const int m = xcd / t.across * t.rows, n = xcd % t.across * t.cols;
+    return {m, std::min(m + t.rows, t.tiles_m), n, std::min(n + t.cols, t.tiles_n)};
+  }
+  const int i0 = xcd * t.per_xcd, i1 = std::min(i0 + t.per_xcd, t.tiles_m * t.tiles_n);
+  if (i0 >= i1) return {0, 0, 0, 0};
+  if (t.columns) return {0, t.tiles_m, i0 / t.tiles_m, (i1 - 1) / t.tiles_m + 1};
+  return {i0 / t.tiles_n, (i1 - 1) / t.tiles_n + 1, 0, t.tiles_n};
+}
+
 // Workgroups per XCD that have no tile and bring operands into L2 (Bring, in gemm_pipe.h): one to a unit left over, up to 8 (640 x 768 x 3072 in
 // tiles of 64 x 64, microseconds: none 19.2, four 15.7, eight 11.9, twelve 11.3, sixteen 12.0); fewer than 4 cannot keep ahead of the
 // tiles (9280 x 384 x 1536: none 19.3, two 20.5, four 19.0; 8320 rows: none 19.3, three 19.3, seven 17.3)
