@@ -687,7 +687,7 @@ int Block::stem_conv_fwd(const void* x_in, void* xp, void* wp, void* out, hipStr
 
 bool Block::second_filter_from_bn(int i) const {
   const BasicBlockDims& d = rb_d[i];
-  return conv_bn_ok(dt, cfg.batch, d.Ho, d.Wo, d.Co) && conv_bn_filter_floats(cfg.batch, d.Ho, d.Wo, d.Co) > 0;
+  return conv_bn_ok(dt, cfg.batch, d.Ho, d.Wo, d.Co) && conv_bn_filter_floats(cfg.batch, d.Ho, d.Wo, d.Co, units) > 0;
 }
 bool Block::whole_chain(int i) const { return rb_d[i].stride == 1 && rb_d[i].Ci == rb_d[i].Co && (i > 0 || stem); }
 
@@ -727,7 +727,7 @@ int Block::resnet_step(const void* x_in, const int32_t* labels, void* x_out, hip
       if (waiting && bn.blocks == 0) PPLL_TRY(launch_bn_sums_fwd_bf16(s, bn.x, bn_rows, bn_c, area, &bn.blocks));
       const bool take = waiting;
       waiting = false;
-      PPLL_TRY(launch_conv_bn_fwd(s, take ? &bn : nullptr, in, w, B, Hi, Wi, Ci, out, other, ready));
+      PPLL_TRY(launch_conv_bn_fwd(s, take ? &bn : nullptr, in, w, B, Hi, Wi, Ci, out, other, ready, units));
       std::swap(area, other);
       return PPLL_OK;
     }
@@ -828,7 +828,7 @@ int Block::resnet_step(const void* x_in, const int32_t* labels, void* x_out, hip
     if (ready == 0) PPLL_TRY(launch_bn_sums_bwd_bf16(s, dy, y, xin, B * Hh * Ww, Co, mean, rstd, area, &ready));
     BnGrad g{dy, xin, mask, area, ready, mean, rstd, params + g_off, params + b_off, grads + g_off, grads + b_off};
     ready = 0;
-    PPLL_TRY(launch_conv_bn_bwd(s, g, w, B, Hh, Ww, Co, d, dres, dmask, dst, next, other, &ready, fg, &rq));
+    PPLL_TRY(launch_conv_bn_bwd(s, g, w, B, Hh, Ww, Co, d, dres, dmask, dst, next, other, &ready, fg, &rq, units));
     std::swap(area, other);
     return PPLL_OK;
   };

@@ -392,18 +392,19 @@ struct BnGrad {
 };
 bool conv_bn_ok(int dt, int B, int H, int W, int C);
 int conv_bn_stat_blocks(int B, int H, int W, int C);   // partial rows it leaves
-// dst = conv(y) with y = relu(bn(bn->x) + bn->res), stored in bn->y; without bn, dst = conv(x).  stat: sums of dst.
+// dst = conv(y) with y = relu(bn(bn->x) + bn->res), stored in bn->y; without bn, dst = conv(x).  stat: sums of dst.  units (here and
+// below): compute units of the device, 0: asked for.
 int launch_conv_bn_fwd(hipStream_t s, const BnInput* bn, const void* x, const void* w, int B, int H, int W, int C, void* dst,
-                       float* stat, int* stat_blocks);
+                       float* stat, int* stat_blocks, int units = 0);
 // d = gradient at the BatchNorm's input, dst = conv^T(d) (+ dres where dmask is set); next (nullable): the BatchNorm whose
 // output gradient dst is, its sums go to stat
 // fg (nullable, where conv_bn_filter_floats() says so): the convolution's weight gradient dw as well, in place of d, which is not stored.
 // in: its input, or null: that is relu(bn) of next->x with these g and b.
 struct ConvFilterGrad { float* dw; const void* in; const float *g, *b; };
-size_t conv_bn_filter_floats(int B, int H, int W, int C);      // room for the partial sums, 0: not from this kernel
+size_t conv_bn_filter_floats(int B, int H, int W, int C, int units = 0);      // room for the partial sums, 0: not from this kernel
 int launch_conv_bn_bwd(hipStream_t s, const BnGrad& bn, const void* w, int B, int H, int W, int C, void* d, const void* dres,
                        const uint8_t* dmask, void* dst, const BnBwdSums* next, float* stat, int* stat_blocks,
-                       const ConvFilterGrad* fg = nullptr, ReduceQueue* rq = nullptr);
+                       const ConvFilterGrad* fg = nullptr, ReduceQueue* rq = nullptr, int units = 0);
 // the sums alone ([*blocks][2][C] partial rows, at most 256)
 int launch_bn_sums_fwd_bf16(hipStream_t s, const void* x, int rows, int C, float* partials, int* blocks);
 int launch_bn_sums_bwd_bf16(hipStream_t s, const void* dy, const void* y, const void* x, int rows, int C, const float* mean,

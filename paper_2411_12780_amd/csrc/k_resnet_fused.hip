@@ -548,10 +548,10 @@ int conv_bn_launch(hipStream_t s, const ConvBnArgs& p, int grid, int in_lds) {
 // Eight waves (256 pixels) a tile once those give most compute units one (at least 200 tiles), else four: with fewer, half the
 // compute units would stand idle, with more, the smaller tile loads its two border rows for half as many pixels.
 struct TileShape { int waves, sr, seg, tiles, grid; };
-TileShape tile_shape(int B, int H, int W, int C) {
+TileShape tile_shape(int B, int H, int W, int C, int units) {
   TileShape t{};
   const long px = (long)B * H * W;
-  const int units = compute_units(), cus = units > 0 ? units : 256;
+  const int asked = units ? units : compute_units(), cus = asked > 0 ? asked : 256;
   t.waves = px >= 200L * 256 ? 8 : 4;
   const int rt = 32 * t.waves / W;
   t.sr = tile_rows(t.waves, H, W);
@@ -562,8 +562,7 @@ TileShape tile_shape(int B, int H, int W, int C) {
   return t;
 }
 template <bool BWD>
-int conv_bn_dispatch(hipStream_t s, ConvBnArgs& p, int B, int H, int W, int C, int* stat_blocks) {
-  const TileShape t = tile_shape(B, H, W, C);
+int conv_bn_dispatch(hipStream_t s, ConvBnArgs& p, const TileShape& t, int B, int H, int W, int C, int* stat_blocks) {
   p.H = H; p.wl = log2_of(W); p.rows = B * H; p.sr = t.sr; p.srl = log2_of(t.sr); p.seg = t.seg;
   p.inv = (65536 + t.sr + 1) / (t.sr + 2); p.tiles = t.tiles; p.bytes = (uint32_t)((long)B * H * W * C * 2);
   const int in_lds = tile_bytes(t.waves, H, W, C);
@@ -583,16 +582,14 @@ bool conv_bn_ok(int dt, int B, int H, int W, int C) {
   auto side = [](int v) { return v == 8 || v == 16 || v == 32; };
   return dt == BF16 && (C == 16 || C == 32 || C == 64) && side(H) && side(W) && (long)B * H * W * C * 2 < (1L << 30) - 64;
 }
-int conv_bn_stat_blocks(int B, int H, int W, int C) { return tile_shape(B, H, W, C).grid; }
+int conv_bn_stat_blocks(int B, int H, int W, int C) { return tile_shape(B, H, W, C, 0).grid; }
 // Where a workgroup has several tiles (above 512 of them, always of eight waves): a partial filter, 9 KB, is written and read again for
 // every workgroup, against 32 KB of maps a tile that need not be.  With 32 and 64 channels a filter is 37 and 147 KB.
-size_t conv_bn_filter_floats(int B, int H, int W, int C) {
-  const TileShape t = tile_shape(B, H, W, C);
-  return C == 16 && t.waves == 8 && t.tiles > t.grid ? (size_t)t.grid * filter_row(C) : 0;
-}
+static size_t filter_floats(const TileShape& t, int C) { return C == 16 && t.waves == 8 && t.tiles > t.grid ? (size_t)t.grid * filter_row(C) : 0; }
+size_t conv_bn_filter_floats(int B, int H, int W, int C, int units) { return C == 16 ? filter_floats(tile_shape(B, H, W, C, units), C) : 0; }
 
 int launch_conv_bn_fwd(hipStream_t s, const BnInput* bn, const void* x, const void* w, int B, int H, int W, int C, void* dst,
-                       float* stat, int* stat_blocks) {
+                       float* stat, int* stat_blocks, int units) {
   ConvBnArgs p{};
   p.x = (const uint16_t*)(bn ? bn->x : x); p.w = (const uint16_t*)w; p.dst = (uint16_t*)dst; p.stat = stat;
   if (bn) {
@@ -604,17 +601,18 @@ int launch_conv_bn_fwd(hipStream_t s, const BnInput* bn, const void* x, const vo
   if (!cb_al16(p.x) || !cb_al16(w) || !cb_al16(dst)) { set_error("conv_bn: unaligned tensors"); return PPLL_ERR_CONFIG; }
   void* prof = nullptr;   // the bytes of the convolution alone: input, output and filter once
   PPLL_TRY(profile_begin(s, 2.0 * (2.0 * B * H * W * C + 9.0 * C * C), &prof, 1));
-  PPLL_TRY(conv_bn_dispatch<false>(s, p, B, H, W, C, stat_blocks));
+  PPLL_TRY(conv_bn_dispatch<false>(s, p, tile_shape(B, H, W, C, units), B, H, W, C, stat_blocks));
   return profile_end(s, prof);
 }
 
 int launch_conv_bn_bwd(hipStream_t s, const BnGrad& bn, const void* w, int B, int H, int W, int C, void* d, const void* dres,
                        const uint8_t* dmask, void* dst, const BnBwdSums* next, float* stat,
-                       int* stat_blocks, const ConvFilterGrad* fg, ReduceQueue* rq) {
+                       int* stat_blocks, const ConvFilterGrad* fg, ReduceQueue* rq, int units) {
   ConvBnArgs p{};
+  const TileShape t = tile_shape(B, H, W, C, units);
   bool queued = false;
   if (fg) {
-    const size_t room = conv_bn_filter_floats(B, H, W, C);
+    const size_t room = filter_floats(t, C);
     if (!room || (!fg->in && (!next || !fg->g || !fg->b))) { set_error("conv_bn: no weight gradient from this launch"); return PPLL_ERR_CONFIG; }
     p.filters = rq->space(room, &queued);
     if (!queued) { set_error("conv_bn: no room for partial filters"); return PPLL_ERR_WORKSPACE; }   // what is shared holds the sums of a BatchNorm
@@ -633,10 +631,10 @@ int launch_conv_bn_bwd(hipStream_t s, const BnGrad& bn, const void* w, int B, in
     if (!cb_al16(q)) { set_error("conv_bn: unaligned tensors"); return PPLL_ERR_CONFIG; }
   void* prof = nullptr;   // the bytes of the convolution alone: its two maps and the filter once, the shortcut gradient where present
   PPLL_TRY(profile_begin(s, 2.0 * ((double)B * H * W * C * (dres ? 3.0 : 2.0) + 9.0 * C * C), &prof, 1));
-  PPLL_TRY(conv_bn_dispatch<true>(s, p, B, H, W, C, stat_blocks));
+  PPLL_TRY(conv_bn_dispatch<true>(s, p, t, B, H, W, C, stat_blocks));
   PPLL_TRY(profile_end(s, prof));
   if (!fg) return PPLL_OK;
-  return reduce_conv_filters(s, *rq, queued, p.filters, tile_shape(B, H, W, C).grid, filter_row(C), C, C, C, fg->dw);
+  return reduce_conv_filters(s, *rq, queued, p.filters, t.grid, filter_row(C), C, C, C, fg->dw);
 }
 
 }  // namespace ppll

@@ -70,3 +70,11 @@ def test_which_products_take_the_layernorm_behind_them(runtime, dim, batch, alon
     assert [takes(made) for made in runtime([wl], "step", "eval")] == [alone, alone]
     batch_made, eval_made = runtime([wl, wl], "batch", "eval")
     assert (takes(batch_made), takes(eval_made)) == (shared, alone)
+
+
+@pytest.mark.parametrize("stage,batch,blocks", [(1, 64, 4), (1, 200, 8), (3, 64, 1), (1, 200, 1), (2, 48, 1)])
+def test_a_resnet_call_asks_for_the_device_less_than_once_a_launch(runtime, stage, batch, blocks):
+    wls = synth.resnet32_modules(blocks, batch=batch) if blocks > 1 else [synth.workload("resnet32_stage%d_bf16" % stage, batch=batch)]
+    for made in runtime(wls, "batch" if blocks > 1 else "step", "eval"):
+        asked, launches = (sum(c[0] == kind for c in made) for kind in ("device", "launch"))
+        assert asked < launches, (asked, launches)
