@@ -8,7 +8,8 @@
 // stages of 64 k in LDS (more of them do not fit beside 384 columns), the finished tile as fp32 in LDS, from which lane groups take whole
 // rows as the LayerNorm kernels hold them.  At width 192 two workgroups share a unit, so that one multiplies while the other copies.
 // Microseconds as two launches and here, 8320 rows of width 192: K = 192 forward 11.4 -> 7.5, K = 768 16.1 -> 12.1, backward 20.9 -> 18.0;
-// steps of 3 + 1 layers of width 192, 8320 rows, 543 -> 507, 2 + 1 layers of 25216 rows 778 -> 744.  The rule and its figures: norm_tiles().
+// steps of 3 + 1 layers of width 192, 8320 rows, 543 -> 507, 2 + 1 layers of 25216 rows 778 -> 744.  The rule and its figures: norm_tiles() and
+// norm_with_product().
 #include "common.h"
 #include "ln_rows.h"
 #include "plan.h"
@@ -318,6 +319,7 @@ int norm_dispatch(hipStream_t s, const GemmArgs& g, NormArgs& p) {
   p.b_bytes = (uint32_t)((bt ? (long)(g.K - 1) * p.ldb + g.N : (long)(g.N - 1) * p.ldb + g.K) * 2);
   void* prof = nullptr;
   PPLL_TRY(profile_begin(s, 2.0 * g.M * g.N * g.K, &prof));
+  // a block has its forward products with B [K][N] and its input gradients with [N][K]; the other two forms serve the test of the kernel
   if (g.N == 384) PPLL_TRY((bt ? norm_launch<true, 384, BWD>(s, p) : norm_launch<false, 384, BWD>(s, p)));
   else PPLL_TRY((bt ? norm_launch<true, 192, BWD>(s, p) : norm_launch<false, 192, BWD>(s, p)));
   return profile_end(s, prof);

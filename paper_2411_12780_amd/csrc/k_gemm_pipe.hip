@@ -10,9 +10,11 @@
 //    and rows of 128 bytes of an operand with k contiguous.  Rows of 64 bytes come from L2 at 26 bytes a clock and unit, whole cache
 //    lines at 52; brought 64 bytes a row, the copies of 25216 x 768 x 3072 alone took 76 us, whole lines 72 from HBM and 47 from L2.
 //  128 x 128 tiles of four waves that multiply, 64 x 64 each, and four that copy, four stages of 64 k, a unit to themselves (128 KB): where
-//    every tile finds a unit.  Units left over bring A into L2 ahead of the tiles.  Operands from beyond L2, tiled kernel -> without that
-//    -> with it: 8320 x 384 x 1536 21.4 -> 19.3 -> 15.8, x 1152 17.0 -> 15.2 -> 12.7, 8320 x 384 x 384 with a residual 10.5 -> 10.0 -> 9.6;
-//    5200 x 384 x 1536 20.1 -> 14.2, 4160 x 768 x 3072 36.5 -> 26 us.
+//    every tile finds a unit.  Units left over bring rows of A, columns of B and what the epilogue takes into L2 ahead of the tiles.
+//    Tiled kernel -> without that -> with it, B [K][N], bias and residual, us a launch behind others on other operands, from memory (in
+//    brackets: from the last-level cache): 8320 x 384 x 1536 21.2 -> 21.2 -> 18.2 (18.6 -> 14.2 -> 13.7), x 384 10.6 -> 10.1 -> 9.7 (9.0 ->
+//    8.0 -> 7.6), 5200 x 384 x 1536 19.6 -> 19.8 -> 14.5 (17.9 -> 13.5 -> 12.6), 4160 x 768 x 3072 34.3 -> 32.8 -> 26.1 (30.9 -> 22.7 -> 23.0);
+//    B [N][K], neither: 8320 x 384 x 1536 21.4 -> 19.9 -> 17.2 (18.3 -> 13.7 -> 13.3), x 1152 16.8 -> 15.8 -> 13.9 (14.6 -> 11.2 -> 11.0).
 // Microseconds, tiled kernel -> first form -> second: 25216 x 768 x 3072 138 -> 117 -> 100 (1192 TFLOP/s), 25216 x 2304 x 768 132 -> 105 ->
 // 93, 25216 x 3072 x 768 with GELU 198 -> 172 -> 162 and with its derivative 182 -> 165 -> 151 (310 MB of epilogue traffic each),
 // 8320 x 1152 x 384 16.8 -> 16.4 -> 14.8, 8320 x 1536 x 384 with GELU 27.9 -> 24.8 -> 24.0.  What bounds it: in the main loop LDS reads and

@@ -9,12 +9,15 @@
 // on their way, and waits for nobody.  (Fragments read from memory in the MFMA's layout, 32 bytes of a line at a time, filled the L1 with
 // lines that were gone before the next 32 bytes were asked for: more loads in flight made it slower.)  Units without a tile bring the
 // operands into the L2s (Bring, in gemm_pipe.h), an XCD's tiles share what they read (tile_map), and what the epilogue takes is asked for
-// before the products.  Two stages where the range of a wave is no longer, where there are more tiles than units, and in a pipeline, whose
-// other streams want LDS.  Microseconds, fragments from memory -> this, operands from beyond L2 (in brackets: from L2):
+// before the products.  Two stages (64 KB a workgroup, 96 with tiles of 32 x 64) where the range of a wave is no longer, where there are more
+// tiles than units, with tiles of 32 x 64, and in a pipeline, whose other streams want LDS.  There one stage, 32 and 48 KB, is no better: four
+// blocks of width 768, 85 rows 1627 us a batch with one and 1593 with two, 240 rows 1779 and 1818, of width 384, 204 and 240 rows, 923 and
+// 921, 943 and 943; and fragments from memory, 20 and 37 KB, in the library of that time took 1543 where these take 1326 (768, 85 rows), 1851 and 1550 (240 rows), 1039 and
+// 946 (384, 240 rows).  Microseconds, fragments from memory -> this, operands from beyond L2 (in brackets: from L2):
 //   128 x 768 x 3072  [K][N] 14.1 -> 8.6 (9.1 -> 6.4)   [N][K] 16.1 -> 7.6 (12.6 -> 6.0)      128 x 3072 x 768  GELU 9.0 -> 6.4   its derivative 10.2 -> 5.9
 //   128 x 384 x 1536          7.3 -> 5.4 (5.7 -> 4.8)           8.6 -> 5.0 (7.4 -> 4.7)       256 x 1536 x 384  GELU 5.5 -> 5.4   its derivative  6.2 -> 4.9
 //   128 x 768 x 768           5.4 -> 4.6                        5.9 -> 4.5                    256 x 3072 x 768  GELU 11.8 -> 11.0  its derivative 14.3 -> 9.6
-// A step of 3 + 1 layers of width 768, 640 rows, 610 -> 590 us, of width 384, 8320 rows, 890 -> 861, its evaluation 337 -> 323.
+// A step of 3 + 1 layers of width 768, 640 rows, 611 -> 590 us, of width 384, 8320 rows, 847 -> 839, its evaluation 320 -> 317.
 //
 // Operand layouts: A is [M][K] with k contiguous (row stride lda: the class-token rows of a token matrix are T*D apart).  B is either
 // [N][K] with k contiguous (input gradients: W stored [in,out] read as B(k = out, n = in)) or [K][N] with n contiguous (forward: W

@@ -139,9 +139,7 @@ inline bool few_tiles(int M, int N, int K, int units) {
 // 120 tiles: 5.8 us, 8.6 on the tiled kernel).  Beyond that tiles share units: alone on the chip it is ahead a little further (2700 x
 // 384 x 384, 258 tiles: 5.2 and 6.3), level or behind from some 320 tiles on (520 x 2304 x 768, 324: 9.1 and 8.9; 640 x 3072 x 768,
 // 480: 10.0 and 9.0).  It starts where the kernel does, at 128 of K (1500 x 384 x 136: 3.7 and 4.8).  Tiles of 128 x 128 on the same
-// scheme (128 KB of LDS) are ahead alone (8320 x 384 x 1536: 14.4 us, 19.5 on the tiled kernel), but not in a step, where the operands
-// come from further off (22 and 22.5), and behind beside other streams (four pipelined blocks of width 384, 8320 rows: 3060 us a batch
-// and 3000).
+// scheme take over further on: copy_wave_tiles().
 constexpr int SPLIT_MIN_K = 128;
 inline bool split_tiles(int M, int N, int K, int units) {
   return K >= SPLIT_MIN_K && units >= 8 && (long)((M + 63) / 64) * ((N + 63) / 64) <= units;
@@ -250,7 +248,7 @@ constexpr TileRange tiles_of(const TileMap& t, int xcd) {
 
 // Workgroups per XCD that have no tile and bring operands into L2 (Bring, in gemm_pipe.h): one to a unit left over, up to 8 (640 x 768 x 3072 in
 // tiles of 64 x 64, microseconds: none 19.2, four 15.7, eight 11.9, twelve 11.3, sixteen 12.0); fewer than 4 cannot keep ahead of the
-// tiles (9280 x 384 x 1536: none 19.3, two 20.5, four 19.0; 8320 rows: none 19.3, three 19.3, seven 17.3)
+// tiles (9280 x 384 x 1536 from memory, no residual: none 19.3, two 20.5, four 19.0; 8320 rows: none 19.5, three 19.3, seven 17.0)
 inline int helper_workgroups(int per_xcd, int units) {
   const int left = std::min(HELPERS_MOST, units / 8 - per_xcd);
   return left >= HELPERS_LEAST ? left : 0;
@@ -323,9 +321,10 @@ inline bool norm_tiles(int M, int N, int K, int units) {
 // Of these, at width 384, not where the product alone would be on 128 x 128 tiles with copying waves: alone on the device, 3 + 1 layers,
 // us a step (an evaluation) in two launches and in one, with them 8320 rows 867 and 872 (339 and 343), 9280 976 and 979 (361 and 365),
 // 10465 985 and 986 (377 and 378), 10790 997 and 1001 (380 and 383); without them 9815 959 and 959 (361 and 360), 11050 1092 and 1085
-// (405 and 398), 12325 1195 and 1187 (435 and 426), 15950 rows, 2 + 2 layers, 1408 and 1399 (514 and 502).  Beside other streams those tiles are
-// not taken, and the one launch is level: pipelines of four and three blocks of width 384, 6500 rows 2140 and 2140 us a batch, 8320 rows 2560
-// and 2558, 2573 and 2566; of width 192, 8320 rows, 1222 and 1172.
+// (405 and 398), 12325 1195 and 1187 (435 and 426), 15950 rows, 2 + 2 layers, 1408 and 1399 (514 and 502).  At width 192 one launch is
+// ahead of those tiles too: 8320 rows 519 and 507 (217 and 212), 12480 rows 644 and 609 (268 and 253).  Beside other streams they are not taken,
+// and one launch is level or ahead: pipelines of four and three blocks of width 384, 8320 rows, 2560 and 2558 us a batch, 2573 and 2566; of
+// four of width 192, 8320 rows, 1222 and 1172.
 inline bool norm_with_product(int M, int N, int K, bool shared, int units) {
   return norm_tiles(M, N, K, units) && (N <= 192 || shared || !copy_wave_tiles(M, N, K, units));
 }
